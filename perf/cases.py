@@ -31,24 +31,24 @@ def _case(name, kind, hidden, heads, ffn, layers, batch, len_lo, len_hi, steps=0
 def listed():
     return [
         # a handful of short requests through one GPT-2-small layer: the smallest call, launches and latency
-        _case("short prompts, 768", "prefill", 768, 12, 3072, 1, 4, 16, 64),
+        _case("short prompts 768", "prefill", 768, 12, 3072, 1, 4, 16, 64),
         # one user of a GPT-2-medium-sized model: a short prompt, then token after token
-        _case("one reply, 24 x 1024", "generate", 1024, 16, 4096, 24, 1, 37, 37, 16),
+        _case("one reply 24x1024", "generate", 1024, 16, 4096, 24, 1, 37, 37, 16),
         # a batch of prompts, and the tokens that follow, of a GPT-2-medium-sized stack
-        _case("prompts, 24 x 1024", "prefill", 1024, 16, 4096, 24, 8, 256, 512),
-        _case("tokens, 24 x 1024", "decode", 1024, 16, 4096, 24, 8, 384, 768, 16),
+        _case("prompts 24x1024", "prefill", 1024, 16, 4096, 24, 8, 256, 512),
+        _case("tokens 24x1024", "decode", 1024, 16, 4096, 24, 8, 384, 768, 16),
         # sentences of half the padded length through an encoder of the same size
-        _case("sentences, 24 x 1024", "encode", 1024, 16, 4096, 24, 16, 64, 192),
+        _case("sentences 24x1024", "encode", 1024, 16, 4096, 24, 16, 64, 192),
         # one layer of a 7B-sized model: a small batch of prompts, its tokens, and a server's batch of tokens
-        _case("prompts, 4096", "prefill", 4096, 32, 16384, 1, 4, 512, 1024),
-        _case("tokens, 4096", "decode", 4096, 32, 16384, 1, 4, 512, 1279, 16),
-        _case("server tokens, 4096", "decode", 4096, 32, 16384, 1, 48, 100, 1500, 16),
+        _case("prompts 4096", "prefill", 4096, 32, 16384, 1, 4, 512, 1024),
+        _case("tokens 4096", "decode", 4096, 32, 16384, 1, 4, 512, 1279, 16),
+        _case("server tokens 4096", "decode", 4096, 32, 16384, 1, 48, 100, 1500, 16),
         # long documents
-        _case("long prompts, 2048", "prefill", 2048, 16, 8192, 1, 2, 2048, 4096),
-        _case("long tokens, 2048", "decode", 2048, 16, 8192, 1, 2, 2048, 4160, 16),
+        _case("long prompts 2048", "prefill", 2048, 16, 8192, 1, 2, 2048, 4096),
+        _case("long tokens 2048", "decode", 2048, 16, 8192, 1, 2, 2048, 4160, 16),
         # one layer of GPT-3's width, full batch: the largest work
-        _case("prompts, 12288", "prefill", 12288, 96, 49152, 1, 16, 1024, 2048),
-        _case("tokens, 12288", "decode", 12288, 96, 49152, 1, 16, 1024, 2104, 8),
+        _case("prompts 12288", "prefill", 12288, 96, 49152, 1, 16, 1024, 2048),
+        _case("tokens 12288", "decode", 12288, 96, 49152, 1, 16, 1024, 2104, 8),
     ]
 
 
