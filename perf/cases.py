@@ -162,32 +162,122 @@ def _layer_weights(r, c):
             "w_fc1": r.normal((F, H), s), "b_fc1": r.normal((F,), s), "w_fc2": r.normal((H, F), s), "b_fc2": r.normal((H,), s)}
 
 
-def prepare(case, seed):
-    r, c = _Draws(seed), case
+def _inputs(c, seed):
+    """Weights, activations, caches and token ids of a case, from the seed alone."""
+    r = _Draws(seed)
     H, B, lens, steps = c["hidden"], c["batch"], _lens(c), c["steps"]
-    # a decode-only program never sees a prompt longer than a token: its scratch stays small
-    prompt, room = (1, max(lens) + steps) if c["kind"] == "decode" else (max(lens), max(lens) + steps)
-    cfg = eet.make_config(H, c["heads"], c["ffn"], B, prompt, room)
-    weights = [_layer_weights(r, c) for _ in range(c["layers"])]
-    s = {"kind": c["kind"], "lens": lens, "steps": steps, "stream": _stream(), "layers": c["layers"]}
+    prompt, room = _room(c)
+    d = {"weights": [_layer_weights(r, c) for _ in range(c["layers"])]}
     if c["kind"] == "generate":
-        head = {"wte": r.normal((GPT2_VOCAB, H), 0.02), "wpe": r.normal((room, H), 0.01), "lnf_g": r.normal((H,), 0.1, 1.0), "lnf_b": r.normal((H,), 0.1)}
-        s["model"] = eet.DecoderModel(cfg, weights, head, GPT2_VOCAB, device=DEVICE)
-        s["prompt"] = r.ids((B, prompt))
-        s["next"] = r.ids((steps, B))
+        d["head"] = {"wte": r.normal((GPT2_VOCAB, H), 0.02), "wpe": r.normal((room, H), 0.01), "lnf_g": r.normal((H,), 0.1, 1.0), "lnf_b": r.normal((H,), 0.1)}
+        d["prompt"] = r.ids((B, prompt))
+        d["next"] = r.ids((steps, B))
+    elif c["kind"] == "decode":
+        sigma = (0.02 if H <= 4096 else 0.006) * math.sqrt(H)          # what the K and V projections of normalised rows give
+        d["kv"] = r.normal((c["layers"] * 2 * B * room * H,), sigma)
+        d["x"] = r.normal((steps, B, H))
+    else:
+        d["x"] = r.normal((B, prompt, H))
+    return d
+
+
+def _room(c):
+    """Padded prompt length and cache rows per sequence; a decode-only program never sees a prompt longer than a token, so
+    its scratch stays small."""
+    longest = max(_lens(c))
+    return (1 if c["kind"] == "decode" else longest), longest + c["steps"]
+
+
+def prepare(case, seed):
+    c, d = case, _inputs(case, seed)
+    prompt, room = _room(c)
+    cfg = eet.make_config(c["hidden"], c["heads"], c["ffn"], c["batch"], prompt, room)
+    s = {"kind": c["kind"], "lens": _lens(c), "steps": c["steps"], "stream": _stream(), "layers": c["layers"]}
+    if c["kind"] == "generate":
+        s["model"] = eet.DecoderModel(cfg, d["weights"], d["head"], GPT2_VOCAB, device=DEVICE)
+        s["prompt"], s["next"] = d["prompt"], d["next"]
         return s
     # one layer on its own is a layer handle; several are a stack
-    s["net"] = eet.DecoderLayer(cfg, weights[0], device=DEVICE) if c["layers"] == 1 else eet.DecoderStack(cfg, weights, device=DEVICE)
+    s["net"] = eet.DecoderLayer(cfg, d["weights"][0], device=DEVICE) if c["layers"] == 1 else eet.DecoderStack(cfg, d["weights"], device=DEVICE)
+    s["x"] = d["x"]
+    s["out"] = torch.empty_like(s["x"])
     if c["kind"] == "decode":
-        sigma = (0.02 if H <= 4096 else 0.006) * math.sqrt(H)          # what the K and V projections of normalised rows give
-        s["net"].kv_cache.copy_(r.normal(s["net"].kv_cache.shape, sigma))
-        s["x"] = r.normal((steps, B, H))
+        s["net"].kv_cache.copy_(d["kv"])
         s["tok"], s["row"] = torch.empty_like(s["x"][0]), torch.empty_like(s["x"][0])
-        s["out"] = torch.empty_like(s["x"])
-    else:
-        s["x"] = r.normal((B, prompt, H))
-        s["out"] = torch.empty_like(s["x"])
     return s
+
+
+def _exact_layer(w, heads, x, kv, rows, causal):
+    """One pre-LN layer in 64 bits.  x: the packed rows [T, H]; rows: per sequence its rows of x and its cached length before
+    them; kv: [2, B, heads, room, d] to write keys and values into, or None (the rows see one another only)."""
+    F = torch.nn.functional
+    H = x.shape[1]
+    d = H // heads
+    g = lambda name: w[name].double()                                  # noqa: E731
+    a = F.layer_norm(x, (H,), g("ln1_g"), g("ln1_b"), 1e-5)
+    qkv = F.linear(a, g("w_qkv"), g("b_qkv"))
+    ctx = torch.empty_like(x)
+    for b, (r0, r1, n0) in enumerate(rows):
+        q, k, v = (qkv[r0:r1, i * H:(i + 1) * H].view(r1 - r0, heads, d).transpose(0, 1).contiguous() for i in range(3))
+        if kv is not None:
+            kv[0, b, :, n0:n0 + r1 - r0] = k
+            kv[1, b, :, n0:n0 + r1 - r0] = v
+            k, v = (kv[i, b, :, :n0 + r1 - r0].contiguous() for i in range(2))
+        seen = torch.ones((q.shape[1], k.shape[1]), dtype=torch.bool, device=x.device).tril(n0) if causal else None
+        for h in range(0, heads, 16):
+            s = torch.matmul(q[h:h + 16], k[h:h + 16].transpose(1, 2).contiguous()) / math.sqrt(d)
+            if seen is not None:
+                s.masked_fill_(~seen, -math.inf)
+            o = torch.matmul(torch.softmax(s, -1), v[h:h + 16])
+            ctx[r0:r1, h * d:(h + o.shape[0]) * d] = o.transpose(0, 1).reshape(r1 - r0, -1)
+    y = x + F.linear(ctx, g("w_o"), g("b_o"))
+    del qkv, ctx
+    a = F.layer_norm(y, (H,), g("ln2_g"), g("ln2_b"), 1e-5)
+    a = F.gelu(F.linear(a, g("w_fc1"), g("b_fc1")), approximate="tanh")
+    return y + F.linear(a, g("w_fc2"), g("b_fc2"))
+
+
+def exact(case, seed):
+    """What run() returns for these inputs, by plain torch in 64 bits."""
+    if _flops(case) > 1.5e14:
+        return None
+    c, d = case, _inputs(case, seed)
+    H, B, heads, lens, n = c["hidden"], c["batch"], c["heads"], _lens(c), c["layers"]
+    prompt, room = _room(c)
+    kv = None
+    if c["kind"] != "encode":
+        kv = d["kv"].double() if c["kind"] == "decode" else torch.zeros(n * 2 * B * room * H, dtype=torch.float64, device=DEVICE)
+        kv = kv.view(n, 2, B, heads, room, H // heads)
+
+    def through(x, rows, causal=True):
+        for i, w in enumerate(d["weights"]):
+            x = _exact_layer(w, heads, x, None if kv is None else kv[i], rows, causal)
+        return x
+
+    def steps_of(inputs):
+        return [through(x, [(b, b + 1, lens[b] + k) for b in range(B)]) for k, x in enumerate(inputs)]
+
+    ends = [sum(lens[:b + 1]) for b in range(B)]
+    packed = [(e - m, e, 0) for e, m in zip(ends, lens)]
+    if c["kind"] == "generate":
+        head = {k: v.double() for k, v in d["head"].items()}
+
+        def logits(x):
+            x = torch.nn.functional.layer_norm(x, (H,), head["lnf_g"], head["lnf_b"], 1e-5)
+            return torch.nn.functional.pad(x @ head["wte"].T, (0, -GPT2_VOCAB % 64))     # columns up to the next multiple of 64 are zero rows of the table
+
+        x = torch.cat([head["wte"][d["prompt"][b, :m].long()] + head["wpe"][:m] for b, m in enumerate(lens)])
+        got = [logits(through(x, packed)[[e - 1 for e in ends]])]
+        at = torch.tensor(lens, device=DEVICE)
+        got += [logits(y) for y in steps_of([head["wte"][d["next"][k].long()] + head["wpe"][at + k] for k in range(c["steps"])])]
+        return {"logits": got, "kv": kv.reshape(-1)}
+    if c["kind"] == "decode":
+        return {"out": torch.stack(steps_of(d["x"].double())), "kv": kv.reshape(-1)}
+    x = through(torch.cat([d["x"][b, :m] for b, m in enumerate(lens)]).double(), packed, c["kind"] == "prefill")
+    out = torch.zeros((B, prompt, H), dtype=torch.float64, device=DEVICE)                # pad rows come back as zeros
+    for b, (r0, r1, _) in enumerate(packed):
+        out[b, :r1 - r0] = x[r0:r1]
+    return {"out": out} if kv is None else {"out": out, "kv": kv.reshape(-1)}
 
 
 def run(state):
