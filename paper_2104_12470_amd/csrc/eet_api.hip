@@ -46,9 +46,17 @@ constexpr int kFfnPadFrom = 32768;
 
 // Byte offsets of the pieces of a layer's workspace.
 struct WorkspaceLayout {
-    size_t lens, cu, row_map, buf_a, buf_b, buf_y, buf_f, part, row_stats, total;
+    size_t lens, cu, row_map, buf_a, buf_b, buf_y, buf_f, part, row_stats, cut, total;
     int splits;
+    size_t cut_room_f() const { return part - buf_f; }      // idle during the attention output projection
+    size_t cut_room_ab() const { return buf_y - buf_a; }    // idle during the second feed-forward projection
 };
+
+// bytes of the sums of all K ranges of an M x N x K bias + residual projection; 0: not cut
+size_t cut_bytes(int M, int N, int K) {
+    const int ranges = gemm_k_ranges(M, N, K);
+    return ranges > 1 ? (size_t)ranges * M * N * sizeof(float) : 0;
+}
 
 const char* config_problem(const eet_layer_config* c) {
     if (!c) return "config is null";
@@ -94,6 +102,16 @@ WorkspaceLayout layout_of(const eet_layer_config* c) {
     // (mean, squared deviations) per row and workgroup of the producer, at most hidden/16 workgroups of 16 rows
     w.row_stats = off;
     off = align_up(off + (H / 16 + 1) * 16 * 2 * sizeof(float), 256);
+    // K ranges of a cut projection (gemm_k_ranges): they go to activation buffers that are idle at that point where those
+    // hold them (cut_area), else here
+    w.cut = off;
+    size_t cut = 0;
+    for (size_t m = 17; m <= (T < (size_t)kGemmCutMaxM ? T : (size_t)kGemmCutMaxM); ++m) {
+        const size_t for_o = cut_bytes((int)m, c->hidden, c->hidden), for_f2 = cut_bytes((int)m, c->hidden, c->ffn);
+        if (for_o > w.cut_room_f() && for_o > cut) cut = for_o;
+        if (for_f2 > w.cut_room_ab() && for_f2 > cut) cut = for_f2;
+    }
+    off = align_up(off + cut, 256);
     w.total = off;
     return w;
 }
@@ -167,6 +185,15 @@ int eet_layer_destroy(eet_layer_t* layer) {
     return EET_OK;
 }
 
+// Cuts the K of a bias + residual projection of `L` where that pays; `idle`, `room`: the activation buffers nobody needs
+// while it runs.  The rule and the sizes are those layout_of reserved by.
+static void cut_projection(eet_layer* L, GemmArgs& g, size_t idle, size_t room) {
+    const size_t need = cut_bytes(g.M, g.N, g.K);
+    if (need == 0) return;
+    g.k_ranges = gemm_k_ranges(g.M, g.N, g.K);
+    g.part = reinterpret_cast<float*>(L->ws + (need <= room ? idle : L->lay.cut));
+}
+
 #define EET_LAUNCH(expr, what)                        \
     do {                                              \
         hipError_t e_ = (expr);                       \
@@ -203,8 +230,11 @@ static int enqueue_prefill(eet_layer* L, const SeqLens& lens, int batch, int pad
                                 nullptr, 0, s), "layernorm 1");
     // a3: QKV projection; K and V rows land directly in their cache slots
     GemmArgs g{};
+    // a short prompt reads every weight once, as a decode step does: with the non-temporal hint where nothing keeps them until
+    // the next call anyway (enqueue_decode has the reasons)
+    const int once = T <= 128 && (size_t)(L->stack_layers > 0 ? L->stack_layers : 1) * 2 * ((size_t)4 * H * H + (size_t)2 * H * F) > kMemorySideCacheBytes;
     g.x = bufA; g.w = (const half_t*)L->w.w_qkv; g.bias = (const half_t*)L->w.b_qkv; g.y = bufB;
-    g.M = (int)T; g.N = 3 * H; g.K = H;
+    g.M = (int)T; g.N = 3 * H; g.K = H; g.read_once = once;
     g.k_cache = kc; g.v_cache = vc; g.tok_row_map = d_map; g.lens = left_padded ? d_lens : nullptr;
     g.left_pad = left_padded ? 1 : 0;
     g.S = padded_len; g.hidden = H; g.heads = c.heads; g.d = L->d; g.max_seq = c.max_seq;
@@ -218,19 +248,25 @@ static int enqueue_prefill(eet_layer* L, const SeqLens& lens, int batch, int pad
     // a6: output projection + bias + residual (residual gathered from the padded input)
     GemmArgs o{};
     o.x = bufA; o.w = (const half_t*)L->w.w_o; o.bias = (const half_t*)L->w.b_o; o.y = bufY;
-    o.M = (int)T; o.N = H; o.K = H; o.res = x; o.res_row_map = d_map;
+    o.M = (int)T; o.N = H; o.K = H; o.res = x; o.res_row_map = d_map; o.read_once = once;
+    cut_projection(L, o, L->lay.buf_f, L->lay.cut_room_f());
+    // a7: LN2, by the launch that adds up the K ranges where the projection is cut
+    if (o.k_ranges > 1) {
+        o.fin_gamma = (const half_t*)L->w.ln2_g; o.fin_beta = (const half_t*)L->w.ln2_b; o.fin_y = bufB; o.fin_eps = c.ln_eps;
+    }
     EET_LAUNCH(launch_gemm(o, EPI_BIAS_RES, s), "output projection");
-    // a7: LN2
-    EET_LAUNCH(launch_layernorm(bufY, nullptr, (const half_t*)L->w.ln2_g, (const half_t*)L->w.ln2_b, bufB, T, H,
-                                c.ln_eps, nullptr, 0, s), "layernorm 2");
+    if (o.k_ranges <= 1)
+        EET_LAUNCH(launch_layernorm(bufY, nullptr, (const half_t*)L->w.ln2_g, (const half_t*)L->w.ln2_b, bufB, T, H,
+                                    c.ln_eps, nullptr, 0, s), "layernorm 2");
     // a8: FFN1 + bias + GELU
     GemmArgs f1{};
     f1.x = bufB; f1.w = (const half_t*)L->w.w_fc1; f1.bias = (const half_t*)L->w.b_fc1; f1.y = bufF;
-    f1.M = (int)T; f1.N = F; f1.K = H;
+    f1.M = (int)T; f1.N = F; f1.K = H; f1.read_once = once;
     // a9: FFN2 + bias + residual, scattered back to the padded layout
     GemmArgs f2{};
     f2.x = bufF; f2.w = (const half_t*)L->w.w_fc2; f2.bias = (const half_t*)L->w.b_fc2; f2.y = static_cast<half_t*>(out);
-    f2.M = (int)T; f2.N = H; f2.K = F; f2.res = bufY; f2.res_row_map = nullptr; f2.out_row_map = d_map;
+    f2.M = (int)T; f2.N = H; f2.K = F; f2.res = bufY; f2.res_row_map = nullptr; f2.out_row_map = d_map; f2.read_once = once;
+    cut_projection(L, f2, L->lay.buf_a, L->lay.cut_room_ab());
     if (F >= kFfnPadFrom && gemm_takes_row_strides(f1) && gemm_takes_row_strides(f2)) f1.ldy = f2.lda = F + (int)kFfnRowPad;
     EET_LAUNCH(launch_gemm(f1, EPI_BIAS_GELU, s), "ffn 1");
     EET_LAUNCH(launch_gemm(f2, EPI_BIAS_RES, s), "ffn 2");
@@ -408,10 +444,18 @@ static int enqueue_decode(eet_layer* L, const void* tokens, void* out, void* kv_
             f1.row_stats_in = o.row_stats_out; f1.row_stats_groups = groups; f1.row_stats_cols = cols;
         }
     }
+    cut_projection(L, o, L->lay.buf_f, L->lay.cut_room_f());
+    const bool ln2_in_finish = o.k_ranges > 1;            // more than 16 sequences: the launch that adds up the K ranges normalises and advances n_b
+    if (ln2_in_finish) {
+        o.fin_gamma = (const half_t*)L->w.ln2_g; o.fin_beta = (const half_t*)L->w.ln2_b; o.fin_y = bufB; o.fin_eps = c.ln_eps;
+        if (bump) { o.bump_lens = d_lens; o.bump_count = B; }
+    }
     EET_LAUNCH(launch_gemm(o, EPI_BIAS_RES, s), "output projection");
     if (!hand_stats) {
         const half_t* fc1_in = bufY;
-        if (!fuse_ln || !bump_in_gemm) {
+        if (ln2_in_finish) {
+            fc1_in = bufB;
+        } else if (!fuse_ln || !bump_in_gemm) {
             EET_LAUNCH(launch_layernorm(bufY, nullptr, (const half_t*)L->w.ln2_g, (const half_t*)L->w.ln2_b, bufB, B, H,
                                         c.ln_eps, (bump && !bump_in_gemm) ? d_lens : nullptr, B, s), "layernorm 2");
             fc1_in = bufB;
@@ -423,6 +467,7 @@ static int enqueue_decode(eet_layer* L, const void* tokens, void* out, void* kv_
     GemmArgs f2{};
     f2.x = bufF; f2.w = (const half_t*)L->w.w_fc2; f2.bias = (const half_t*)L->w.b_fc2; f2.y = static_cast<half_t*>(out);
     f2.M = B; f2.N = H; f2.K = F; f2.res = bufY; f2.read_once = once;
+    cut_projection(L, f2, L->lay.buf_a, L->lay.cut_room_ab());
     if (prefetch && next != nullptr) {                    // during FFN-2 (128 workgroups): the QKV matrix and the K/V rows of the step that follows
         f2.pf.lin[0] = next->w.w_qkv; f2.pf.lin_lines[0] = lines((size_t)3 * H * H * 2);
         f2.pf.k_cache = static_cast<const half_t*>(next_kv);

@@ -255,8 +255,10 @@ __device__ __forceinline__ void epilogue_via_lds(const GemmArgs& a, const float4
 
 // 16 bytes per lane from global memory straight into LDS: lane l lands at lds + 16*l (the LDS
 // base must be wave-uniform).  Kept out of the templates: the builtin only exists for the device.
+// NT: with the non-temporal hint (cache policy bit 1), for weights that the launch reads once (common.hpp: load_once).
+template <bool NT = false>
 __device__ __forceinline__ void load_lds_16B(const half_t* gptr, half_t* lds) {
-    __builtin_amdgcn_global_load_lds(gptr, lds, 16, 0, 0);
+    __builtin_amdgcn_global_load_lds(gptr, lds, 16, 0, NT ? 2 : 0);
 }
 
 template <int N>
@@ -295,7 +297,7 @@ __device__ __forceinline__ void wait_vm() {
 // included, until the LDS queue drains (16 reads in a row in front of 64 multiplies: 1840 cycles against 1055 for the
 // multiplies alone; one read after every third multiply: 1080); there the fragments of a whole k half are
 // double-buffered and every request sits between two multiplies.
-template <int BM, int BN, int NW, int NS, int KS, int AM, int AN>
+template <int BM, int BN, int NW, int NS, int KS, int AM, int AN, bool NTW = false, bool ROT = false>
 struct GemmTileExec {
     static constexpr int BK = 64, AH = AM / 2;
     static constexpr int LRA = BM / NW, LRW = BN / NW, LIA = LRA / 8, LIW = LRW / 8;
@@ -311,13 +313,19 @@ struct GemmTileExec {
     half8v ga[2][AM], gw[2][AN];           // the one-wave-per-SIMD schedule: all fragments of k half h
     float4v acc[AM][AN];
 
+    int k_first, k_count;                  // ROT: the walk over the K tiles starts at k_first and wraps at k_count
+
     __device__ __forceinline__ void load(int tile, int stage) {
+        if constexpr (ROT) {
+            tile += k_first;
+            if (tile >= k_count) tile -= k_count;
+        }
 #pragma unroll
         for (int v = 0; v < LIA; ++v)
             load_lds_16B(pa[v] + (int64_t)(tile * KS + kg) * BK, as_base + stage * (BM * BK) + (wave * LRA + v * 8) * BK);
 #pragma unroll
         for (int v = 0; v < LIW; ++v)
-            load_lds_16B(pw[v] + (int64_t)(tile * KS + kg) * BK, ws_base + stage * (BN * BK) + (wave * LRW + v * 8) * BK);
+            load_lds_16B<NTW>(pw[v] + (int64_t)(tile * KS + kg) * BK, ws_base + stage * (BN * BK) + (wave * LRW + v * 8) * BK);
     }
     template <int L>
     __device__ __forceinline__ void wait_vmem() {
@@ -445,7 +453,13 @@ struct GemmTileExec {
 // per SIMD (pipe::gemm_k_loop_interleaved; two stages, one K group)
 // NTS: the output is stored with the non-temporal hint (outputs of 256 MB and more, which no cache keeps for their reader:
 // 24576 x 49152 x 12288 21.70 -> 21.53 ms, 24576 x 12288 x 12288 5.69 -> 5.59, 8192 x 16384 x 12288 2.436 -> 2.393).
-template <int BM, int BN, int WGM, int WGN, int EPI, int NS, int KS, int SCHED, bool NTS = false>
+// NTW: the weights are loaded with the non-temporal hint (one row tile: every weight is read once by the launch).
+// ROT: the workgroups of an XCD start their walk over K in eight different places and wrap, as in gemm_stream, so that not
+// all of them ask for the same K offset of weight rows a power of two apart, and for the same activation lines, at the same
+// time (48 x 16384 x 4096: 28.0 -> 24.9 us, 48 x 4096 x 16384 in four K ranges: 37.2 -> 29.1).
+// EPI_PARTIAL: the K range is cut into a.k_ranges equal parts, one workgroup per tile and part, and the fp32 accumulators go
+// to a.part[range][row][column] for finish_rows to add up.
+template <int BM, int BN, int WGM, int WGN, int EPI, int NS, int KS, int SCHED, bool NTS = false, bool NTW = false, bool ROT = false>
 __global__ __launch_bounds__(WGM* WGN* KS * 64) void gemm_mfma_dma64(GemmArgs a, int tiles_m, int tiles_n) {
     static_assert(SCHED == 0 || (NS == 2 && KS == 1 && (SCHED == 1 || SCHED == 2)), "schedule");
     // KS > 1: KS groups of WGM x WGN waves share the tile and take every KS-th K step each, through LDS stages of their
@@ -453,7 +467,7 @@ __global__ __launch_bounds__(WGM* WGN* KS * 64) void gemm_mfma_dma64(GemmArgs a,
     // tiles of a narrow output with a long K, where nothing else puts more loads in flight per CU.
     constexpr int NW = WGM * WGN, BK = 64;
     static_assert(NS == 2 || NS == 3, "LDS stages");
-    static_assert(KS == 1 || KS == 2, "K groups");
+    static_assert(KS == 1 || KS == 2 || KS == 4, "K groups");
     constexpr int WM = BM / WGM, WN = BN / WGN, AM = WM / 16, AN = WN / 16;   // wave tile in 16 x 16 accumulator blocks
     constexpr int LRA = BM / NW, LRW = BN / NW;   // rows of each operand tile a wave loads per K step
     constexpr int LIA = LRA / 8, LIW = LRW / 8;   // wave-level load instructions per operand per K step
@@ -462,7 +476,17 @@ __global__ __launch_bounds__(WGM* WGN* KS * 64) void gemm_mfma_dma64(GemmArgs a,
     __shared__ __attribute__((aligned(1024))) half_t Ws[KS * NS][BN * BK];
 
     int tile_m, tile_n;
-    pipe::tile_of_block((int)blockIdx.x, tiles_m, tiles_n, tile_m, tile_n);
+    int range = 0;                                           // K range of this workgroup
+    if constexpr (EPI == EPI_PARTIAL) {
+        // consecutive workgroups, which go to different XCDs, take different ranges: with 2, 4 or 8 of them an XCD's L2
+        // holds the activations of one range only
+        range = (int)blockIdx.x % a.k_ranges;
+        const int t = (int)blockIdx.x / a.k_ranges;
+        tile_m = t % tiles_m;
+        tile_n = t / tiles_m;
+    } else {
+        pipe::tile_of_block((int)blockIdx.x, tiles_m, tiles_n, tile_m, tile_n);
+    }
     const int m0 = tile_m * BM, n0 = tile_n * BN;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);   // wave-uniform by construction: keeps LDS bases in scalar registers
@@ -470,12 +494,17 @@ __global__ __launch_bounds__(WGM* WGN* KS * 64) void gemm_mfma_dma64(GemmArgs a,
     const int wave = KS == 1 ? wv : wv % NW;                 // wave inside its group
     const int wm0 = (wave / WGN) * WM, wn0 = (wave % WGN) * WN;
     const int M = a.M, N = a.N, K = a.K;
-    const int nk = K / (BK * KS);                            // steps of this group (the host sends whole multiples)
+    const int k_range = EPI == EPI_PARTIAL ? K / a.k_ranges : K;
+    const int nk = k_range / (BK * KS);                      // steps of this group (the host sends whole multiples)
 
-    GemmTileExec<BM, BN, NW, NS, KS, AM, AN> ex;
+    GemmTileExec<BM, BN, NW, NS, KS, AM, AN, NTW, ROT> ex;
     static_assert(decltype(ex)::LIA == LIA && decltype(ex)::LIW == LIW, "load instructions per K step");
     ex.kg = kg;
     ex.wave = wave;
+    if constexpr (ROT) {
+        ex.k_first = (((int)blockIdx.x >> 3) & 7) * nk >> 3;
+        ex.k_count = nk;
+    }
     ex.as_base = &As[kg * NS][0];
     ex.ws_base = &Ws[kg * NS][0];
 #pragma unroll
@@ -484,7 +513,7 @@ __global__ __launch_bounds__(WGM* WGN* KS * 64) void gemm_mfma_dma64(GemmArgs a,
         const int c = (lane & 7) ^ ((row >> 1) & 7);
         int gr = m0 + row;
         gr = gr < M ? gr : M - 1;
-        ex.pa[v] = a.x + (int64_t)gr * (a.lda ? a.lda : K) + c * 8;
+        ex.pa[v] = a.x + (int64_t)gr * (a.lda ? a.lda : K) + range * k_range + c * 8;
     }
 #pragma unroll
     for (int v = 0; v < LIW; ++v) {
@@ -492,7 +521,7 @@ __global__ __launch_bounds__(WGM* WGN* KS * 64) void gemm_mfma_dma64(GemmArgs a,
         const int c = (lane & 7) ^ ((row >> 1) & 7);
         int gr = n0 + row;
         gr = gr < N ? gr : N - 1;
-        ex.pw[v] = a.w + (int64_t)gr * K + c * 8;
+        ex.pw[v] = a.w + (int64_t)gr * K + range * k_range + c * 8;
     }
     // fragment rows: lane l reads row l%16 of a block, the 16 bytes (l/16) of k half h; rows are 128 bytes with their
     // 16-byte chunks XOR-permuted by (row/2)%8, and blocks start at multiples of 16 rows, so the permutation is the lane's own
@@ -535,6 +564,19 @@ __global__ __launch_bounds__(WGM* WGN* KS * 64) void gemm_mfma_dma64(GemmArgs a,
                 for (int j = 0; j < AN; ++j)
 #pragma unroll
                     for (int r = 0; r < 4; ++r) acc[i][j][r] += red[g * (NW * PT) + ((i * AN + j) * 4 + r) * 64];
+    }
+    if constexpr (EPI == EPI_PARTIAL) {
+#pragma unroll
+        for (int i = 0; i < AM; ++i) {
+            const int m = m0 + wm0 + i * 16 + (lane & 15);
+            if (m >= M) continue;
+#pragma unroll
+            for (int j = 0; j < AN; ++j) {
+                const int n = n0 + wn0 + j * 16 + (lane >> 4) * 4;
+                if (n < N) *reinterpret_cast<float4v*>(a.part + ((int64_t)range * M + m) * N + n) = acc[i][j];
+            }
+        }
+        return;
     }
     constexpr int EB = WM * 128;                           // bytes of a wave's turn-around area
     // row lookups and residual lines of the wave tile: all requested here, consumed by the passes below
@@ -1507,6 +1549,83 @@ static bool try_stream(const GemmArgs& a, Epilogue epi, hipStream_t s) {
     return true;
 }
 
+// --------------------------------------------------------------------------------------------
+// 17 to 1024 rows: a weight stream through the tile kernel
+// --------------------------------------------------------------------------------------------
+// A decode step of 17 to 128 sequences (or as short a prompt) reads every weight once, and what bounds it is how fast the
+// weights come in.  The general tile choice below makes that slow in two ways: a narrow output with a long K has only N/64
+// workgroups (48 x 4096 x 16384: 64 of them, 71 us, 1.9 TB/s), and 128-row tiles pull twice the activations through L2 that
+// 33 to 64 rows need.  Here one row tile of 32, 64 or 128 rows covers all rows, the columns come in tiles of 64, four waves
+// of a workgroup (two or four K groups) keep two K steps each in flight, and a bias + residual projection whose columns leave
+// CUs idle has K cut into 2, 4 or 8 ranges, whose fp32 sums finish_rows adds up.  Measured on cold weights, before -> now, us
+// (cut ones with finish_rows): 48 rows: 4096 x 16384 70.8 -> 29.0, 4096 x 4096 21.0 -> 13.2 (and the LayerNorm launch behind it
+// gone), 12288 x 4096 27.9 -> 23.9, 16384 x 4096 32.8 -> 25.1, 49152 x 12288 251 -> 212, 12288 x 49152 280 -> 248, 8192 x
+// 32768 166 -> 102; 24 rows: 16384 x 4096 32.4 -> 23.4; 128 rows: 4096 x 16384 73.5 -> 36.2, 36864 x 12288 267 -> 235.
+// More rows (129 to 1024) take it only for the cut, and with the plain K walk and plain loads, since several row tiles then
+// share the weights: 200 x 2048 x 8192 33.8 -> 20.6, 512 x 2048 x 8192 47.5 -> 32.4, 512 x 1024 x 4096 19.5 -> 16.7.
+constexpr int kRowsStreamMaxM = 128;
+static int rows_tile(int M) { return M <= 32 ? 32 : M <= 64 ? 64 : 128; }
+// K ranges that fill the CUs without a second round; at least 512 columns each (below that a range is all start-up: 32 x 1024
+// x 1024 gains nothing in two), whole steps of both K groups.
+static int rows_ranges(int M, int N, int K) {
+    const int tiles = (M + rows_tile(M) - 1) / rows_tile(M) * ((N + 63) / 64);
+    int s = 1;
+    while (s < 8 && tiles * s * 2 <= 256 && K % (128 * s * 2) == 0 && K / (s * 2) >= 512) s *= 2;
+    return s;
+}
+// Weights below about 24 MB stay with the row slices (48 x 2048 x 2048 7.8 us in slices, 9.2 here; 32 x 1024 x 4096 6.7
+// against 9.1).  At most 32 rows want no eighth-cut (32 x 2048 x 8192 11.5 against 13.2), more than 64 rows a long K (96 x
+// 6144 x 2048 12.1 against 16.0).
+static bool rows_stream_pays(int M, int N, int K, int ranges) {
+    if (M <= 16 || K % 128 != 0 || N % 64 != 0) return false;
+    const int64_t weights = (int64_t)N * K;
+    if (M > kRowsStreamMaxM) return M <= kGemmCutMaxM && ranges > 1 && K >= 4096 && weights >= ((int64_t)4 << 20);
+    if (weights < ((int64_t)12 << 20)) return false;
+    if (M <= 32 && ranges >= 8) return false;
+    return M <= 64 || K >= 4096;
+}
+int gemm_k_ranges(int M, int N, int K) {
+    const int s = N <= kFinishRowsMaxWidth ? rows_ranges(M, N, K) : 1;
+    return s > 1 && rows_stream_pays(M, N, K, s) ? s : 1;
+}
+static bool rows_stream(const GemmArgs& a, Epilogue epi) {
+    if (a.k_ranges > 1 && epi == EPI_BIAS_RES) return true;          // the caller asked gemm_k_ranges
+    return a.M <= kRowsStreamMaxM && rows_stream_pays(a.M, a.N, a.K, 1) && (a.ln_gamma == nullptr && a.pf.blocks == 0 && a.bump_lens == nullptr) &&
+           // without the cut a narrow output stays where it was
+           rows_ranges(a.M, a.N, a.K) == 1;
+}
+
+template <int BM, int WGM, int KS, bool NTW, bool ROT, int EPI>
+static void launch_rows_epi(const GemmArgs& a, hipStream_t s) {
+    const int tm = (a.M + BM - 1) / BM, tn = (a.N + 63) / 64;
+    const dim3 grid(tm * tn * (EPI == EPI_PARTIAL ? a.k_ranges : 1)), block(WGM * KS * 64);
+    hipLaunchKernelGGL((gemm_mfma_dma64<BM, 64, WGM, 1, EPI, 3, KS, 0, false, NTW, ROT>), grid, block, 0, s, a, tm, tn);
+}
+template <int BM, int WGM, int KS, bool NTW>
+static void launch_rows_tile(const GemmArgs& a, Epilogue epi, hipStream_t s) {
+    if (a.k_ranges > 1) { launch_rows_epi<BM, WGM, KS, NTW, true, EPI_PARTIAL>(a, s); return; }
+    switch (epi) {
+        case EPI_BIAS: launch_rows_epi<BM, WGM, KS, NTW, true, EPI_BIAS>(a, s); break;
+        case EPI_BIAS_GELU: launch_rows_epi<BM, WGM, KS, NTW, true, EPI_BIAS_GELU>(a, s); break;
+        case EPI_BIAS_RES: launch_rows_epi<BM, WGM, KS, NTW, true, EPI_BIAS_RES>(a, s); break;
+        case EPI_QKV: launch_rows_epi<BM, WGM, KS, NTW, true, EPI_QKV>(a, s); break;
+    }
+}
+template <bool NTW>
+static void launch_rows_nt(const GemmArgs& a, Epilogue epi, hipStream_t s) {
+    const int ranges = a.k_ranges > 1 ? a.k_ranges : 1;
+    if (a.M <= 32 && a.K % (256 * ranges) == 0) launch_rows_tile<32, 1, 4, NTW>(a, epi, s);
+    else if (a.M <= 64) launch_rows_tile<64, 2, 2, NTW>(a, epi, s);
+    else launch_rows_tile<128, 2, 2, NTW>(a, epi, s);
+}
+static hipError_t launch_rows(const GemmArgs& a, Epilogue epi, hipStream_t s) {
+    if (a.M > kRowsStreamMaxM) launch_rows_epi<128, 4, 2, false, false, EPI_PARTIAL>(a, s);
+    else if (a.read_once) launch_rows_nt<true>(a, epi, s);
+    else launch_rows_nt<false>(a, epi, s);
+    const hipError_t e = hipGetLastError();
+    return a.k_ranges > 1 && e == hipSuccess ? launch_finish_rows(a, s) : e;
+}
+
 // Row slices of the weight-streaming kernels against the tile kernels for a problem of 17 to 512 rows, from two cost
 // estimates in microseconds whose constants are measured (projections of 2 to 400 MB, 17 to 1024 rows).  Slices: the
 // first reads the weights at about 4 TB/s, every further one reads them again out of L2 or the memory-side cache at about
@@ -1615,6 +1734,10 @@ hipError_t launch_gemm(const GemmArgs& a, Epilogue epi, hipStream_t s) {
     if (a.row_stats_out != nullptr && !(leaves_row_stats(a, epi) && !try_flat(a, epi, nullptr, true) && stream_column_blocks(a, epi) != 0 &&
                                         a.N % (16 * stream_column_blocks(a, epi)) == 0)) return hipErrorInvalidValue;
     if (a.row_stats_in != nullptr && !(takes_row_stats(a, epi) && !try_flat(a, epi, nullptr, true) && stream_column_blocks(a, epi) != 0)) return hipErrorInvalidValue;
+    // the cut along K is the caller's choice, and its operands are its own
+    if (a.k_ranges > 1 && (epi != EPI_BIAS_RES || a.part == nullptr || a.k_ranges != gemm_k_ranges(a.M, a.N, a.K) || (a.ldy != 0 && a.ldy != a.N) || a.ln_gamma != nullptr || a.pf.blocks != 0)) return hipErrorInvalidValue;
+    if (a.fin_gamma != nullptr && a.k_ranges <= 1) return hipErrorInvalidValue;
+    if (a.M > 16 && rows_stream(a, epi)) return launch_rows(a, epi, s);
     // A few more rows than the weight-streaming kernels take at once (a decode step of more than 16 sequences, a very
     // short prompt): the same kernels with the rows cut into slices of 16 along gridDim.y, where that beats a tile kernel
     // that would run a handful of workgroups through the whole K loop (decode layer-step of the hidden-1024 layer at 32

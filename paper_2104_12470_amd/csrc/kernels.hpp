@@ -46,6 +46,7 @@ struct PrefetchArgs {
 
 // ---- dense projections (gemm.hip) ------------------------------------------------------------
 enum Epilogue : int { EPI_BIAS = 0, EPI_BIAS_GELU = 1, EPI_BIAS_RES = 2, EPI_QKV = 3 };
+constexpr int EPI_PARTIAL = 4;   // inside gemm.hip only: the sums of one K range, unrounded (GemmArgs::part)
 
 struct GemmArgs {
     const half_t* x;        // [M, K] activations, row-major
@@ -97,6 +98,16 @@ struct GemmArgs {
     // could keep them cached until their next use anyway (a decode step that moves more than the memory-side cache holds);
     // wrong for a layer small enough to live in that cache from step to step, which the hint would keep out of it.
     int read_once;
+    // EPI_BIAS_RES with 17 rows and more: room for the fp32 sums of the K ranges a narrow output is cut into, k_ranges of
+    // them (gemm_k_ranges says how many; <= 1 or part == nullptr: no cut).  [k_ranges][M][N], read by finish_rows.
+    float* part;
+    int k_ranges;
+    // with k_ranges > 1 only: LayerNorm of the finished rows into fin_y[m] ([M, N]) by the same launch (nullptr = no), and
+    // n_b += 1 for the first bump_count sequences (bump_lens above)
+    const half_t* fin_gamma;
+    const half_t* fin_beta;
+    half_t* fin_y;
+    float fin_eps;
 };
 // the memory-side cache of the part: what a decode step must exceed, in bytes moved between two uses of an operand, before
 // its read-once operands are loaded with the non-temporal hint
@@ -108,6 +119,14 @@ bool gemm_hands_row_stats(const GemmArgs& producer, const GemmArgs& consumer, Ep
 bool gemm_takes_row_strides(const GemmArgs& a);
 // true when launch_gemm would give this bias+residual projection to the kernel that can merge the key ranges itself
 bool gemm_merges_attention_ranges(const GemmArgs& a);
+
+// How many ranges the K of a bias + residual projection is worth cutting into (1: none), a function of the sizes alone: the
+// caller that has room for their sums ([ranges][M][N] floats) sets GemmArgs::part and k_ranges, for M up to kGemmCutMaxM.
+constexpr int kGemmCutMaxM = 1024;
+int gemm_k_ranges(int M, int N, int K);
+// Adds up the K ranges a.part of a cut projection (rowops.hip); N a multiple of 8, at most kFinishRowsMaxWidth.
+constexpr int kFinishRowsMaxWidth = 16384;
+hipError_t launch_finish_rows(const GemmArgs& a, hipStream_t s);
 
 // M > 16: MFMA tile kernel.  M <= 16 (decode): weight-streaming kernel.
 hipError_t launch_gemm(const GemmArgs& a, Epilogue epi, hipStream_t s);

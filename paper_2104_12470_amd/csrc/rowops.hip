@@ -157,6 +157,86 @@ __global__ __launch_bounds__(256) void layernorm_generic(const half_t* __restric
     if (bump_lens != nullptr && tid == 0 && row < bump_count) bump_lens[row] += 1;
 }
 
+// The K ranges of a projection whose narrow output was cut along K (gemm_mfma_dma64 with EPI_PARTIAL): y = sum over the
+// ranges, in order, + bias + residual, rounded once; and, with `gamma`, the LayerNorm that follows, of the row as stored.
+// One workgroup per row, the row in registers: what it costs is one trip for the partial sums (out of L2 or the memory-side
+// cache) and, with the LayerNorm, two block reductions, instead of a launch of its own for it.  n_b += 1 as in the kernels above.
+template <int NT, int NV>
+__global__ __launch_bounds__(NT) void finish_rows(const float* __restrict__ part, int ranges, int64_t range_stride, const half_t* __restrict__ bias,
+                                                  const half_t* res, const int32_t* __restrict__ res_row_map, half_t* y,
+                                                  const int32_t* __restrict__ out_row_map, const half_t* __restrict__ gamma,
+                                                  const half_t* __restrict__ beta, half_t* __restrict__ ln_y, float eps, int width,
+                                                  int32_t* bump_lens, int bump_count) {
+    __shared__ float red[NT / kWave];
+    const int row = blockIdx.x, tid = threadIdx.x, nvec = width >> 3;
+    const int64_t rres = res_row_map ? (int64_t)res_row_map[row] : (int64_t)row;
+    const int64_t rout = out_row_map ? (int64_t)out_row_map[row] : (int64_t)row;
+    const float* pr = part + (int64_t)row * width;
+    half8v v[NV];
+    float sum = 0.f;
+#pragma unroll
+    for (int i = 0; i < NV; ++i) {
+        const int idx = tid + i * NT;
+        if (idx >= nvec) continue;
+        const half8v b = reinterpret_cast<const half8v*>(bias)[idx];
+        const half8v r = reinterpret_cast<const half8v*>(res + rres * width)[idx];
+        const float* pv = pr + idx * 8;
+        float4v lo = *reinterpret_cast<const float4v*>(pv), hi = *reinterpret_cast<const float4v*>(pv + 4);
+#pragma unroll 4
+        for (int k = 1; k < ranges; ++k) {
+            lo += *reinterpret_cast<const float4v*>(pv + k * range_stride);
+            hi += *reinterpret_cast<const float4v*>(pv + k * range_stride + 4);
+        }
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            v[i][e] = (half_t)((e < 4 ? lo[e & 3] : hi[e & 3]) + (float)b[e] + (float)r[e]);
+            sum += (float)v[i][e];
+        }
+        reinterpret_cast<half8v*>(y + rout * width)[idx] = v[i];
+    }
+    if (gamma != nullptr) {                                    // uniform over the launch
+        const float mean = block_sum<NT / kWave>(sum, red) / (float)width;
+        float sq = 0.f;
+#pragma unroll
+        for (int i = 0; i < NV; ++i) {
+            if (tid + i * NT >= nvec) continue;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                const float dlt = (float)v[i][e] - mean;
+                sq += dlt * dlt;
+            }
+        }
+        const float rstd = rsqrtf(block_sum<NT / kWave>(sq, red) / (float)width + eps);
+        half8v* yr = reinterpret_cast<half8v*>(ln_y + (int64_t)row * width);
+#pragma unroll
+        for (int i = 0; i < NV; ++i) {
+            const int idx = tid + i * NT;
+            if (idx >= nvec) continue;
+            const half8v g = reinterpret_cast<const half8v*>(gamma)[idx], b = reinterpret_cast<const half8v*>(beta)[idx];
+            half8v o;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) o[e] = (half_t)(((float)v[i][e] - mean) * rstd * (float)g[e] + (float)b[e]);
+            yr[idx] = o;
+        }
+    }
+    if (bump_lens != nullptr && tid == 0 && row < bump_count) bump_lens[row] += 1;
+}
+
+hipError_t launch_finish_rows(const GemmArgs& a, hipStream_t s) {
+    const dim3 grid(a.M);
+#define EET_FINISH(NT, NV)                                                                                                       \
+    hipLaunchKernelGGL((finish_rows<NT, NV>), grid, dim3(NT), 0, s, a.part, a.k_ranges, (int64_t)a.M * a.N, a.bias, a.res,       \
+                       a.res_row_map, a.y, a.out_row_map, a.fin_gamma, a.fin_beta, a.fin_y, a.fin_eps, a.N, a.bump_lens, a.bump_count)
+    if (a.N <= 1024) EET_FINISH(128, 1);
+    else if (a.N <= 2048) EET_FINISH(256, 1);
+    else if (a.N <= 4096) EET_FINISH(512, 1);
+    else if (a.N <= 8192) EET_FINISH(512, 2);
+    else if (a.N <= kFinishRowsMaxWidth) EET_FINISH(512, 4);
+    else return hipErrorInvalidValue;
+#undef EET_FINISH
+    return hipGetLastError();
+}
+
 static bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 
 hipError_t launch_layernorm(const half_t* x, const int32_t* in_row_map, const half_t* gamma,

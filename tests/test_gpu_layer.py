@@ -110,6 +110,19 @@ def test_decode_of_100_sequences_on_a_layer_with_large_projections(eet):
     full_parity(eet, w, random_affine=False)
 
 
+@pytest.mark.parametrize("hidden,heads,ffn,B,S,max_seq", [
+    (4096, 32, 4096, 17, 1, 4),        # decode only: both bias + residual projections cut in four, the sums in the region of their own
+    (4096, 32, 16384, 33, 2, 6),       # the feed-forward sums fit the idle activation buffers in the prompt, not with one row per sequence
+    (2048, 16, 8192, 128, 2, 4),       # FFN-2 cut in eight; 256 prompt rows take the 128-row tiles, more than one of them
+    (1024, 16, 4096, 5, 61, 66),       # a short prompt: FFN-2 alone is cut, its rows scattered to the padded layout
+])
+def test_projections_cut_along_k(eet, hidden, heads, ffn, B, S, max_seq):
+    """Narrow outputs with a long K and 17 rows or more: the K ranges of the output and the second feed-forward projection are
+    summed by the launch that also does the LayerNorm between them and advances the lengths."""
+    w = wl.Workload(f"cut{hidden}x{B}", 29, hidden, heads, ffn, 1, B, S, max(1, S // 2), S, 2, max_seq)
+    full_parity(eet, w)
+
+
 @pytest.mark.parametrize("heads,B,max_seq,lo,hi", [(4, 3, 512, 300, 500), (2, 1, 4096, 3900, 4000)])
 def test_decode_with_the_key_range_split_and_merged_by_the_output_projection(eet, heads, B, max_seq, lo, hi):
     """Few (sequence, head) pairs and a long cache: the decode attention splits the key range (4 ranges per pair in the

@@ -236,6 +236,25 @@ def test_linear_weight_stream_with_wide_workgroups(eet, M, K, N):
     gate(host(y), lin + r.astype(np.float64), f"wide-workgroup stream linear+res {M}x{K}x{N}", OP_MAX, OP_MEAN)
 
 
+@pytest.mark.parametrize("M,K,N", [(17, 1024, 16384), (32, 1152, 12288),      # one tile of 32 rows: four K groups, two where K is no multiple of 256
+                                   (33, 1024, 16448), (64, 128, 98304),       # one tile of 64 rows; a single K step per group
+                                   (65, 4096, 16384), (128, 4224, 16384)])    # one tile of 128 rows
+def test_linear_rows_stream(eet, M, K, N):
+    """17 to 128 rows over weights large enough to be read as a stream: ragged row tiles, K walks that start and wrap anywhere."""
+    x = wl.normal(380, M, (M, K))
+    w = wl.normal(381, N, (N, K), 1.0 / np.sqrt(K))
+    b = wl.normal(382, N, (N,), 0.5)
+    y = torch.full((M, N), float("nan"), dtype=torch.float16, device="cuda:0")
+    lin = orc.linear(x, w, b)
+    eet.eet_op_linear(dev(x), dev(w), dev(b), y)
+    torch.cuda.synchronize()
+    gate(host(y), lin, f"rows stream linear {M}x{K}x{N}", OP_MAX, OP_MEAN)
+    y.fill_(float("nan"))
+    eet.eet_op_linear(dev(x), dev(w), dev(b), y, act=1)
+    torch.cuda.synchronize()
+    gate(host(y), orc.gelu_tanh(lin), f"rows stream linear+gelu {M}x{K}x{N}", OP_MAX, OP_MEAN)
+
+
 @pytest.mark.parametrize("M,K,N", [(3000, 1024, 4160), (4099, 192, 3136), (2049, 4096, 6144)])
 def test_linear_large_tiles(eet, M, K, N):
     """Shapes that take the 256x256 direct-to-LDS tile kernel, with ragged row and column tails."""
