@@ -460,7 +460,9 @@ struct GemmTileExec {
 // EPI_PARTIAL: the K range is cut into a.k_ranges equal parts, one workgroup per tile and part, and the fp32 accumulators go
 // to a.part[range][row][column] for finish_rows to add up.
 template <int BM, int BN, int WGM, int WGN, int EPI, int NS, int KS, int SCHED, bool NTS = false, bool NTW = false, bool ROT = false>
-__global__ __launch_bounds__(WGM* WGN* KS * 64) void gemm_mfma_dma64(GemmArgs a, int tiles_m, int tiles_n) {
+// (192 x 128 tiles are made for two workgroups per CU: the residual and cache-row look-ups of their epilogue would take the
+// kernel past 256 registers and halve that: 2000 x 4096 x 4096 with a residual 135 us)
+__global__ __launch_bounds__(WGM* WGN* KS * 64, BM == 192 ? 2 : 1) void gemm_mfma_dma64(GemmArgs a, int tiles_m, int tiles_n) {
     static_assert(SCHED == 0 || (NS == 2 && KS == 1 && (SCHED == 1 || SCHED == 2)), "schedule");
     // KS > 1: KS groups of WGM x WGN waves share the tile and take every KS-th K step each, through LDS stages of their
     // own; the other groups' accumulators are added to the first's through LDS at the end.  For the few
@@ -1582,7 +1584,13 @@ static bool rows_stream_pays(int M, int N, int K, int ranges) {
     if (M > kRowsStreamMaxM) return M <= kGemmCutMaxM && ranges > 1 && K >= 4096 && weights >= ((int64_t)4 << 20);
     if (weights < ((int64_t)12 << 20)) return false;
     if (M <= 32 && ranges >= 8) return false;
-    return M <= 64 || K >= 4096;
+    return K >= (M <= 64 ? 2048 : 4096);
+}
+// Up to 64 rows over a wide output with a short K (the vocabulary): a workgroup is mostly start-up and epilogue, so two per
+// CU, of 64 x 128 with three stages (47 x 50304 x 1024: 22.1 us, as a rows stream 30.0, 128 x 128 tiles 25.8; 24 x 50304 x 256
+// 8.0, 16.9 and 9.4; even at K = 2048: 47.9 and 49.6).  More rows than 64: 128 x 128 tiles (68 x 50304 x 1024 24.7, 64 x 128 29.5).
+static bool short_k_wide(const GemmArgs& a, Epilogue epi) {
+    return epi == EPI_BIAS && a.M > 16 && a.M <= 64 && a.K < 2048 && a.N > 256 * 128 && a.ln_gamma == nullptr && a.pf.blocks == 0 && a.bump_lens == nullptr;
 }
 int gemm_k_ranges(int M, int N, int K) {
     const int s = N <= kFinishRowsMaxWidth ? rows_ranges(M, N, K) : 1;
@@ -1591,8 +1599,9 @@ int gemm_k_ranges(int M, int N, int K) {
 static bool rows_stream(const GemmArgs& a, Epilogue epi) {
     if (a.k_ranges > 1 && epi == EPI_BIAS_RES) return true;          // the caller asked gemm_k_ranges
     return a.M <= kRowsStreamMaxM && rows_stream_pays(a.M, a.N, a.K, 1) && (a.ln_gamma == nullptr && a.pf.blocks == 0 && a.bump_lens == nullptr) &&
-           // without the cut a narrow output stays where it was
-           rows_ranges(a.M, a.N, a.K) == 1;
+           // without the cut a narrow output stays where it was (48 x 4096 x 4096 20.3 us here, 21.0 there; 17 x 6144 x 2048 10.0
+           // and 11.5)
+           (a.N + 63) / 64 >= 96;
 }
 
 template <int BM, int WGM, int KS, bool NTW, bool ROT, int EPI>
@@ -1725,6 +1734,31 @@ static int rows_in_whole_rounds(const GemmArgs& a, Epilogue epi, int big_tiles) 
     return 0;
 }
 
+// The tile of a launch with 128 x 128 tiles for every CU, by the time its rounds take.  Measured over K at full rounds, us with
+// K in thousands (of 1024): 256 x 256, one workgroup per CU: 10 + 21.5 K; 192 x 128, two per CU: 8 + 21.3 K for both; 128 x 128,
+// two per CU: 6 + 14.5 K for both.  A last round that gives every CU at most one workgroup takes about 0.76 (192 x 128)
+// or 0.58 (128 x 128) of the time of two, a fuller one 0.92 of a whole round.  So the large tile, the best per flop, gives
+// way where its last round would leave much of the chip idle (us, 256 x 256 / 192 x 128 / 128 x 128): 3054 x 3072 x 1024 31.3 /
+// 25.1 / 31.0, 2140 x 4096 x 1024 33.9 / 27.1 / 33.1, 1500 x 6144 x 2048 48.8 / 44.2 / 55.1, 1200 x 16384 x 4096 188 / 173 / 190,
+// 6000 x 3072 x 768 55.5 / 41.9 / 41.7; and not where it would not: 6758 x 6144 x 2048 149 / 157 / 162, 3262 x 12288 x 4096
+// 276 / 306 / 315, 1200 x 4096 x 4096 87 / 70 / 61.  256 x 128 and 128 x 256 tiles were never the best (LDS for one per CU
+// either way, a third more operand traffic than 256 x 256).  At most 128 rows: half of a taller tile would be idle.
+enum TileChoice { kTileSmall, kTile128, kTile192, kTile256 };
+static TileChoice choose_tile(int M, int N, int K) {
+    auto tiles = [&](int bm, int bn) { return (double)((M + bm - 1) / bm) * ((N + bn - 1) / bn); };
+    const double n256 = tiles(256, 256), n192 = tiles(192, 128), n128 = tiles(128, 128), k = K / 1024.0;
+    if (n128 <= 256) return kTileSmall;
+    if (M <= 128) return kTile128;
+    auto pairs = [](double n, double two, double one) {         // n tiles, two per CU, `two` the time of both, `one` the share of one
+        const double whole = (double)(int64_t)(n / 512), rest = n - whole * 512;
+        return two * (whole + (rest == 0 ? 0.0 : rest <= 256 ? one : 0.92));
+    };
+    const double t256 = (double)(int64_t)((n256 + 255) / 256) * (10 + 21.5 * k);
+    const double t192 = pairs(n192, 8 + 21.3 * k, 0.76), t128 = pairs(n128, 6 + 14.5 * k, 0.58);
+    if (t256 <= 1.03 * t192 && t256 <= 1.03 * t128) return kTile256;
+    return t192 <= t128 ? kTile192 : kTile128;
+}
+
 hipError_t launch_gemm(const GemmArgs& a, Epilogue epi, hipStream_t s) {
     if (a.M <= 0) return hipSuccess;
     const bool bad_stride = (a.lda != 0 && (a.lda < a.K || a.lda % 8 != 0)) || (a.ldy != 0 && (a.ldy < a.N || a.ldy % 8 != 0));
@@ -1738,6 +1772,11 @@ hipError_t launch_gemm(const GemmArgs& a, Epilogue epi, hipStream_t s) {
     if (a.k_ranges > 1 && (epi != EPI_BIAS_RES || a.part == nullptr || a.k_ranges != gemm_k_ranges(a.M, a.N, a.K) || (a.ldy != 0 && a.ldy != a.N) || a.ln_gamma != nullptr || a.pf.blocks != 0)) return hipErrorInvalidValue;
     if (a.fin_gamma != nullptr && a.k_ranges <= 1) return hipErrorInvalidValue;
     if (a.M > 16 && rows_stream(a, epi)) return launch_rows(a, epi, s);
+    if (short_k_wide(a, epi)) {
+        const int tn = (a.N + 127) / 128;
+        hipLaunchKernelGGL((gemm_mfma_dma64<64, 128, 2, 2, EPI_BIAS, 3, 1, 0>), dim3(tn), dim3(256), 0, s, a, 1, tn);
+        return hipGetLastError();
+    }
     // A few more rows than the weight-streaming kernels take at once (a decode step of more than 16 sequences, a very
     // short prompt): the same kernels with the rows cut into slices of 16 along gridDim.y, where that beats a tile kernel
     // that would run a handful of workgroups through the whole K loop (decode layer-step of the hidden-1024 layer at 32
@@ -1750,10 +1789,6 @@ hipError_t launch_gemm(const GemmArgs& a, Epilogue epi, hipStream_t s) {
         else if (a.N >= 32 * 1024) launch_skinny_cfg<2>(a, epi, s);
         else launch_skinny_cfg<1>(a, epi, s);
     } else {
-        // 256x256 tiles once they cover about 60 % of the CUs, smaller tiles below that
-        // (measured: 156 tiles 592 vs 514 TFLOP/s in favour of the large tiles, 112 tiles 563 vs 673 against them), and
-        // never for at most 128 rows, where half of every large tile would be idle (a decode step of many sequences
-        // over a very wide output, e.g. the vocabulary: 128 x 1024 x 50304 39.7 -> 30.9 us with 128x128 tiles)
         const int big_tiles = ((a.M + 255) / 256) * ((a.N + 255) / 256);
         if (int m_whole = rows_in_whole_rounds(a, epi, big_tiles)) {
             // whole rounds of large tiles first, then the last few hundred rows as a problem of their own (small tiles)
@@ -1763,7 +1798,10 @@ hipError_t launch_gemm(const GemmArgs& a, Epilogue epi, hipStream_t s) {
             if (e != hipSuccess) return e;
             return launch_gemm(rows_from(a, epi, m_whole), epi, s);
         }
-        if (big_tiles >= 150 && a.M > 128) {
+        const TileChoice choice = choose_tile(a.M, a.N, a.K);
+        if (choice == kTile192) {
+            launch_dma64_cfg<2, 2, 192, 128, 2, 1, 0>(a, epi, s);
+        } else if (choice == kTile256) {
             // Four waves with 128 x 128 each: a third less LDS read traffic per flop than eight waves of 128 x 64, and the
             // LDS of a CU -- fragment reads plus the arriving tiles -- is what the matrix pipes otherwise wait for
             // (rows x N x K, eight waves in two alternating groups -> four waves: 25082 x 49152 x 12288 1.16 -> 1.23 PFLOP/s,
@@ -1796,9 +1834,16 @@ hipError_t launch_gemm(const GemmArgs& a, Epilogue epi, hipStream_t s) {
                 if (k_split && wg64 <= 256) launch_dma64_cfg<2, 1, 64, 64, 3, 2>(a, epi, s);
                 else launch_dma64_cfg<2, 1, 64, 64, 3>(a, epi, s);
             } else if (tiles128 < 256 && k_split && wg128 <= 256) launch_dma64_cfg<4, 1, 128, 64, 3, 2>(a, epi, s);
+            // 128 x 128 tiles for most CUs, one each and three stages (128 x 64 -> 128 x 128: 700 x 4096 x 16384 173 -> 140 us, 1500 x
+            // 2048 x 8192 81 -> 72, 3000 x 1280 x 5120 59 -> 51, 1000 x 3072 x 1024 14.7 -> 13.5); not for 8 column tiles (3054 x
+            // 1024 x 4096 37.5 -> 40.0) or a short K (1000 x 3072 x 512 8.3 -> 9.5)
+            else if (tiles128 == 256 || (tiles128 >= 176 && tiles128 < 256 && a.N >= 1280 && a.K >= 1024)) launch_dma64_cfg<2, 2, 128, 128, 3>(a, epi, s);
             else if (tiles128 < 256) launch_dma64_cfg<4, 1, 128, 64, 3>(a, epi, s);
-            else if (tiles128 == 256) launch_dma64_cfg<2, 2, 128, 128, 3>(a, epi, s);      // one per CU
-            else launch_dma64_cfg<2, 2, 128, 128>(a, epi, s);                               // two per CU
+            // two per CU.  The one-wave-per-SIMD schedule serves two of them as well, and better than the shared one
+            // (6000 x 768 x 3072 48.5 -> 45.3 us, 1200 x 4096 x 16384 238 -> 221, 3054 x 3072 x 1024 32.7 -> 31.0), but for the wide
+            // outputs with a short K that few rows come here with (68 x 50304 x 256 11.2 us against 10.5, x 1280 34.6 against 33.3)
+            else if (a.M <= 128) launch_dma64_cfg<2, 2, 128, 128>(a, epi, s);
+            else launch_dma64_cfg<2, 2, 128, 128, 2, 1, 2>(a, epi, s);
         }
     }
     return hipGetLastError();

@@ -236,8 +236,9 @@ def test_linear_weight_stream_with_wide_workgroups(eet, M, K, N):
     gate(host(y), lin + r.astype(np.float64), f"wide-workgroup stream linear+res {M}x{K}x{N}", OP_MAX, OP_MEAN)
 
 
-@pytest.mark.parametrize("M,K,N", [(17, 1024, 16384), (32, 1152, 12288),      # one tile of 32 rows: four K groups, two where K is no multiple of 256
-                                   (33, 1024, 16448), (64, 128, 98304),       # one tile of 64 rows; a single K step per group
+@pytest.mark.parametrize("M,K,N", [(17, 2048, 8192), (32, 2176, 6144),        # one tile of 32 rows: four K groups, two where K is no multiple of 256
+                                   (33, 2048, 8256), (64, 2176, 6144),        # one tile of 64 rows
+                                   (20, 64, 33024), (64, 192, 32832),         # a wide output with a short K: 64 x 128 tiles, two per CU
                                    (65, 4096, 16384), (128, 4224, 16384)])    # one tile of 128 rows
 def test_linear_rows_stream(eet, M, K, N):
     """17 to 128 rows over weights large enough to be read as a stream: ragged row tiles, K walks that start and wrap anywhere."""
@@ -255,9 +256,12 @@ def test_linear_rows_stream(eet, M, K, N):
     gate(host(y), orc.gelu_tanh(lin), f"rows stream linear+gelu {M}x{K}x{N}", OP_MAX, OP_MEAN)
 
 
-@pytest.mark.parametrize("M,K,N", [(3000, 1024, 4160), (4099, 192, 3136), (2049, 4096, 6144)])
+@pytest.mark.parametrize("M,K,N", [(3000, 1024, 4160), (4099, 192, 3136), (2049, 4096, 6144),
+                                   (800, 128, 12352), (961, 64, 12352),       # 192 x 128 tiles, two per CU
+                                   (300, 128, 12352),                         # 128 x 128 tiles, two per CU
+                                   (1500, 128, 2112)])                        # 128 x 128 tiles, one per CU, three stages
 def test_linear_large_tiles(eet, M, K, N):
-    """Shapes that take the 256x256 direct-to-LDS tile kernel, with ragged row and column tails."""
+    """Shapes that take the larger tiles of the direct-to-LDS tile kernel, with ragged row and column tails."""
     x = wl.normal(350, M, (M, K))
     w = wl.normal(351, N, (N, K), 1.0 / np.sqrt(K))
     b = wl.normal(352, N, (N,), 0.5)
