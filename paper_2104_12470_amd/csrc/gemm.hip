@@ -457,7 +457,7 @@ struct GemmTileExec {
 // ROT: the workgroups of an XCD start their walk over K in eight different places and wrap, as in gemm_stream, so that not
 // all of them ask for the same K offset of weight rows a power of two apart, and for the same activation lines, at the same
 // time (48 x 16384 x 4096: 28.0 -> 24.9 us, 48 x 4096 x 16384 in four K ranges: 37.2 -> 29.1).
-// EPI_PARTIAL: the K range is cut into a.k_ranges equal parts, one workgroup per tile and part, and the fp32 accumulators go
+// EPI_PARTIAL: the K range is cut into a.k_ranges parts, one workgroup per tile and part, and the fp32 accumulators go
 // to a.part[range][row][column] for finish_rows to add up.
 template <int BM, int BN, int WGM, int WGN, int EPI, int NS, int KS, int SCHED, bool NTS = false, bool NTW = false, bool ROT = false>
 // (192 x 128 tiles are made for two workgroups per CU: the residual and cache-row look-ups of their epilogue would take the
@@ -496,8 +496,10 @@ __global__ __launch_bounds__(WGM* WGN* KS * 64, BM == 192 ? 2 : 1) void gemm_mfm
     const int wave = KS == 1 ? wv : wv % NW;                 // wave inside its group
     const int wm0 = (wave / WGN) * WM, wn0 = (wave % WGN) * WN;
     const int M = a.M, N = a.N, K = a.K;
-    const int k_range = EPI == EPI_PARTIAL ? K / a.k_ranges : K;
-    const int nk = k_range / (BK * KS);                      // steps of this group (the host sends whole multiples)
+    // steps of this group (the host sends whole multiples); the ranges of a cut K differ by at most one step
+    const int k_step0 = EPI == EPI_PARTIAL ? K / (BK * KS) * range / a.k_ranges : 0;
+    const int nk = (EPI == EPI_PARTIAL ? K / (BK * KS) * (range + 1) / a.k_ranges : K / (BK * KS)) - k_step0;
+    const int k0 = k_step0 * (BK * KS);
 
     GemmTileExec<BM, BN, NW, NS, KS, AM, AN, NTW, ROT> ex;
     static_assert(decltype(ex)::LIA == LIA && decltype(ex)::LIW == LIW, "load instructions per K step");
@@ -515,7 +517,7 @@ __global__ __launch_bounds__(WGM* WGN* KS * 64, BM == 192 ? 2 : 1) void gemm_mfm
         const int c = (lane & 7) ^ ((row >> 1) & 7);
         int gr = m0 + row;
         gr = gr < M ? gr : M - 1;
-        ex.pa[v] = a.x + (int64_t)gr * (a.lda ? a.lda : K) + range * k_range + c * 8;
+        ex.pa[v] = a.x + (int64_t)gr * (a.lda ? a.lda : K) + k0 + c * 8;
     }
 #pragma unroll
     for (int v = 0; v < LIW; ++v) {
@@ -523,7 +525,7 @@ __global__ __launch_bounds__(WGM* WGN* KS * 64, BM == 192 ? 2 : 1) void gemm_mfm
         const int c = (lane & 7) ^ ((row >> 1) & 7);
         int gr = n0 + row;
         gr = gr < N ? gr : N - 1;
-        ex.pw[v] = a.w + (int64_t)gr * K + range * k_range + c * 8;
+        ex.pw[v] = a.w + (int64_t)gr * K + k0 + c * 8;
     }
     // fragment rows: lane l reads row l%16 of a block, the 16 bytes (l/16) of k half h; rows are 128 bytes with their
     // 16-byte chunks XOR-permuted by (row/2)%8, and blocks start at multiples of 16 rows, so the permutation is the lane's own
@@ -1559,7 +1561,7 @@ static bool try_stream(const GemmArgs& a, Epilogue epi, hipStream_t s) {
 // workgroups (48 x 4096 x 16384: 64 of them, 71 us, 1.9 TB/s), and 128-row tiles pull twice the activations through L2 that
 // 33 to 64 rows need.  Here one row tile of 32, 64 or 128 rows covers all rows, the columns come in tiles of 64, four waves
 // of a workgroup (two or four K groups) keep two K steps each in flight, and a bias + residual projection whose columns leave
-// CUs idle has K cut into 2, 4 or 8 ranges, whose fp32 sums finish_rows adds up.  Measured on cold weights, before -> now, us
+// CUs idle has K cut into 2 to 8 ranges, whose fp32 sums finish_rows adds up.  Measured on cold weights, before -> now, us
 // (cut ones with finish_rows): 48 rows: 4096 x 16384 70.8 -> 29.0, 4096 x 4096 21.0 -> 13.2 (and the LayerNorm launch behind it
 // gone), 12288 x 4096 27.9 -> 23.9, 16384 x 4096 32.8 -> 25.1, 49152 x 12288 251 -> 212, 12288 x 49152 280 -> 248, 8192 x
 // 32768 166 -> 102; 24 rows: 16384 x 4096 32.4 -> 23.4; 128 rows: 4096 x 16384 73.5 -> 36.2, 36864 x 12288 267 -> 235.
@@ -1567,24 +1569,26 @@ static bool try_stream(const GemmArgs& a, Epilogue epi, hipStream_t s) {
 // share the weights: 200 x 2048 x 8192 33.8 -> 20.6, 512 x 2048 x 8192 47.5 -> 32.4, 512 x 1024 x 4096 19.5 -> 16.7.
 constexpr int kRowsStreamMaxM = 128;
 static int rows_tile(int M) { return M <= 32 ? 32 : M <= 64 ? 64 : 128; }
-// K ranges that fill the CUs without a second round; at least 512 columns each (below that a range is all start-up: 32 x 1024
-// x 1024 gains nothing in two), whole steps of both K groups.
+// K ranges that fill the CUs without a second round, up to 8; at least 512 columns each (below that a range is all start-up: 32 x
+// 1024 x 1024 gains nothing in two).
 static int rows_ranges(int M, int N, int K) {
     const int tiles = (M + rows_tile(M) - 1) / rows_tile(M) * ((N + 63) / 64);
-    int s = 1;
-    while (s < 8 && tiles * s * 2 <= 256 && K % (128 * s * 2) == 0 && K / (s * 2) >= 512) s *= 2;
-    return s;
+    int s = 256 / tiles;
+    s = s < K / 512 ? s : K / 512;
+    return s < 1 ? 1 : s > 8 ? 8 : s;
 }
-// Weights below about 24 MB stay with the row slices (48 x 2048 x 2048 7.8 us in slices, 9.2 here; 32 x 1024 x 4096 6.7
-// against 9.1).  At most 32 rows want no eighth-cut (32 x 2048 x 8192 11.5 against 13.2), more than 64 rows a long K (96 x
-// 6144 x 2048 12.1 against 16.0).
+// Weights below 18 MB (24 MB for at most 32 rows) stay with the row slices (48 x 2048 x 2048 7.9 us in slices, 9.1 here; 17 x 1536 x
+// 6144 8.6 and 10.5; but 48 x 1536 x 6144 13.3 and 11.2, 64 x 3072 x 3072 17.9 and 11.9).  At most 32 rows want no cut in eight
+// (32 x 2048 x 8192 11.7 against 13.4), more than 64 rows without a cut a long K (96 x 6144 x 2048 12.1 against 16.0).
 static bool rows_stream_pays(int M, int N, int K, int ranges) {
     if (M <= 16 || K % 128 != 0 || N % 64 != 0) return false;
+    // a cut that still leaves half of the CUs idle: 20 to 31 x 1984 x 7936 in two ranges (62 workgroups) took half again as long as the slices
+    if (ranges > 1 && (M + rows_tile(M) - 1) / rows_tile(M) * ((N + 63) / 64) * ranges < 128) return false;
     const int64_t weights = (int64_t)N * K;
     if (M > kRowsStreamMaxM) return M <= kGemmCutMaxM && ranges > 1 && K >= 4096 && weights >= ((int64_t)4 << 20);
-    if (weights < ((int64_t)12 << 20)) return false;
+    if (weights < ((int64_t)(M <= 32 ? 12 : 9) << 20)) return false;
     if (M <= 32 && ranges >= 8) return false;
-    return K >= (M <= 64 ? 2048 : 4096);
+    return ranges > 1 || K >= (M <= 64 ? 2048 : 4096);
 }
 // Up to 64 rows over a wide output with a short K (the vocabulary): a workgroup is mostly start-up and epilogue, so two per
 // CU, of 64 x 128 with three stages (47 x 50304 x 1024: 22.1 us, as a rows stream 30.0, 128 x 128 tiles 25.8; 24 x 50304 x 256
@@ -1622,8 +1626,7 @@ static void launch_rows_tile(const GemmArgs& a, Epilogue epi, hipStream_t s) {
 }
 template <bool NTW>
 static void launch_rows_nt(const GemmArgs& a, Epilogue epi, hipStream_t s) {
-    const int ranges = a.k_ranges > 1 ? a.k_ranges : 1;
-    if (a.M <= 32 && a.K % (256 * ranges) == 0) launch_rows_tile<32, 1, 4, NTW>(a, epi, s);
+    if (a.M <= 32 && a.K % 256 == 0) launch_rows_tile<32, 1, 4, NTW>(a, epi, s);
     else if (a.M <= 64) launch_rows_tile<64, 2, 2, NTW>(a, epi, s);
     else launch_rows_tile<128, 2, 2, NTW>(a, epi, s);
 }

@@ -114,6 +114,7 @@ def test_decode_of_100_sequences_on_a_layer_with_large_projections(eet):
     (4096, 32, 4096, 17, 1, 4),        # decode only: both bias + residual projections cut in four, the sums in the region of their own
     (4096, 32, 16384, 33, 2, 6),       # the feed-forward sums fit the idle activation buffers in the prompt, not with one row per sequence
     (2048, 16, 8192, 128, 2, 4),       # FFN-2 cut in eight; 256 prompt rows take the 128-row tiles, more than one of them
+    (5120, 40, 5120, 17, 1, 4),        # 20 steps of K in three ranges of 6, 7 and 7
     (1024, 16, 4096, 5, 61, 66),       # a short prompt: FFN-2 alone is cut, its rows scattered to the padded layout
 ])
 def test_projections_cut_along_k(eet, hidden, heads, ffn, B, S, max_seq):
