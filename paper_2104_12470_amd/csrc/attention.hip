@@ -65,8 +65,7 @@ __global__ __launch_bounds__(256, 2) void attn_prefill(AttnPrefillArgs a, SeqLen
     if (i0 >= L) return;                                          // pad queries are never visited
     int row0 = b * a.S;
     if (a.packed) {
-        row0 = 0;
-        for (int k = 0; k < b; ++k) row0 += lens.len[k];
+        row0 = tokens_before(lens, b, threadIdx.x & 63);
     }
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int li = lane & 31, G = lane >> 5;
@@ -341,8 +340,7 @@ __global__ __launch_bounds__(512) void attn_prefill_wide(AttnPrefillArgs a, SeqL
     if (i0 >= L) return;                                          // pad queries are never visited
     int row0 = b * a.S;
     if (a.packed) {
-        row0 = 0;
-        for (int k = 0; k < b; ++k) row0 += lens.len[k];
+        row0 = tokens_before(lens, b, threadIdx.x & 63);
     }
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int li = lane & 31, G = lane >> 5;

@@ -35,6 +35,15 @@ __device__ __forceinline__ float wave_max(float v) {
     return v;
 }
 
+// Tokens of the sequences before sequence b: two loads and six lane exchanges whatever b is (a loop over the kernel argument
+// is a scalar load and a wait per sequence).  Every lane of the wave calls it and gets the sum.
+__device__ __forceinline__ int tokens_before(const SeqLens& lens, int b, int lane) {
+    int n = (lane < b ? lens.len[lane] : 0) + (lane + 64 < b ? lens.len[lane + 64] : 0);
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) n += __shfl_xor(n, o, kWave);
+    return __builtin_amdgcn_readfirstlane(n);
+}
+
 // Sum over a workgroup of NW waves; every thread gets the result.  `red` is LDS scratch of
 // at least NW floats, reusable after the call returns.
 template <int NW>

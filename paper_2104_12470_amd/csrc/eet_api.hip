@@ -222,12 +222,18 @@ static int enqueue_prefill(eet_layer* L, const SeqLens& lens, int batch, int pad
     // a1: padding offsets -> integers on the device; pad rows of `out` zeroed
     // (left_padded: the packed->padded row map starts each sequence at row S - L_b; every kernel below works on
     // the packed rows and never sees the difference, except the cache scatter, which needs the position)
-    if (index_setup)
-        EET_LAUNCH(launch_prefill_setup(lens, batch, padded_len, H, d_lens, d_cu, d_map, static_cast<half_t*>(out), s,
-                                        left_padded), "prefill_setup");
-    // a2: LN1 over valid rows only (gathered into the packed layout)
-    EET_LAUNCH(launch_layernorm(x, d_map, (const half_t*)L->w.ln1_g, (const half_t*)L->w.ln1_b, bufA, T, H, c.ln_eps,
-                                nullptr, 0, s), "layernorm 1");
+    // a2: LN1 over valid rows only (gathered into the packed layout), in the same launch for rows of up to 2048
+    if (index_setup && prefill_setup_takes_layernorm(H)) {
+        EET_LAUNCH(launch_prefill_setup_layernorm(lens, batch, padded_len, H, d_lens, d_cu, d_map, static_cast<half_t*>(out), left_padded,
+                                                  x, (const half_t*)L->w.ln1_g, (const half_t*)L->w.ln1_b, bufA, c.ln_eps, s),
+                   "prefill set-up and layernorm 1");
+    } else {
+        if (index_setup)
+            EET_LAUNCH(launch_prefill_setup(lens, batch, padded_len, H, d_lens, d_cu, d_map, static_cast<half_t*>(out), s,
+                                            left_padded), "prefill_setup");
+        EET_LAUNCH(launch_layernorm(x, d_map, (const half_t*)L->w.ln1_g, (const half_t*)L->w.ln1_b, bufA, T, H, c.ln_eps,
+                                    nullptr, 0, s), "layernorm 1");
+    }
     // a3: QKV projection; K and V rows land directly in their cache slots
     GemmArgs g{};
     // a short prompt reads every weight once, as a decode step does: with the non-temporal hint where nothing keeps them until

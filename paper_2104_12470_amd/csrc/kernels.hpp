@@ -25,6 +25,11 @@ hipError_t launch_softmax_maskfree(half_t* scores, const SeqLens& lens, int batc
 hipError_t launch_prefill_setup(const SeqLens& lens, int batch, int S, int width, int32_t* cache_lens,
                                 int32_t* cu_seqlens, int32_t* row_map, half_t* out, hipStream_t s,
                                 bool left_padded = false);
+// The same together with the LayerNorm of the valid rows of x ([batch, S, width]) into the packed rows of y, where the width allows.
+bool prefill_setup_takes_layernorm(int width);
+hipError_t launch_prefill_setup_layernorm(const SeqLens& lens, int batch, int S, int width, int32_t* cache_lens, int32_t* cu_seqlens,
+                                          int32_t* row_map, half_t* out, bool left_padded, const half_t* x, const half_t* gamma,
+                                          const half_t* beta, half_t* y, float eps, hipStream_t s);
 
 // cache_lens[b] = lens.len[b] for b < batch (DEVICE array of the layer's workspace)
 hipError_t launch_set_cache_lens(const SeqLens& lens, int batch, int32_t* cache_lens, hipStream_t s);
