@@ -15,7 +15,11 @@ namespace eet {
 // LayerNorm
 // ============================================================================================
 // NV > 0: each thread caches NV vectors of 8 halfs (width <= NV*2048, width % 8 == 0).
-template <int NV>
+// EARLY: gamma and beta are requested with the row and not after the two reductions, where they are a second trip to memory for
+// the few rows of a decode step (16 steps of a hidden-4096 layer, two such launches each: 1501 -> 1494 us; 3262 x 4096 10.9 -> 10.2).
+// With many rows they are in the caches anyway, and the registers that hold them cost waves in flight (22640 x 4352 81 -> 94 us,
+// 25311 x 12288 252 -> 274): up to 4096 rows only.
+template <int NV, bool EARLY>
 __global__ __launch_bounds__(256) void layernorm_cached(const half_t* __restrict__ x,
                                                         const int32_t* __restrict__ in_row_map,
                                                         const half_t* __restrict__ gamma,
@@ -29,18 +33,18 @@ __global__ __launch_bounds__(256) void layernorm_cached(const half_t* __restrict
     const int nvec = width >> 3;
     const int tid = threadIdx.x;
 
-    // the row and its scale and shift are requested together: read after the two reductions, gamma and beta were a second
-    // trip to memory (16 decode steps of a hidden-4096 layer, two such launches each: 1501 -> 1494 us)
     const half8v* g8 = reinterpret_cast<const half8v*>(gamma);
     const half8v* b8 = reinterpret_cast<const half8v*>(beta);
-    half8v v[NV], g[NV], b[NV];
+    half8v v[NV], g[EARLY ? NV : 1], b[EARLY ? NV : 1];
 #pragma unroll
     for (int i = 0; i < NV; ++i) {
         const int idx = tid + i * 256;
         if (idx < nvec) {
             v[i] = xr[idx];
-            g[i] = g8[idx];
-            b[i] = b8[idx];
+            if constexpr (EARLY) {
+                g[i] = g8[idx];
+                b[i] = b8[idx];
+            }
         }
     }
     float sum = 0.f;
@@ -72,10 +76,15 @@ __global__ __launch_bounds__(256) void layernorm_cached(const half_t* __restrict
     for (int i = 0; i < NV; ++i) {
         const int idx = tid + i * 256;
         if (idx < nvec) {
+            const int k = EARLY ? i : 0;
+            if constexpr (!EARLY) {
+                g[0] = g8[idx];
+                b[0] = b8[idx];
+            }
             half8v o;
 #pragma unroll
             for (int e = 0; e < 8; ++e)
-                o[e] = (half_t)(((float)v[i][e] - mean) * rstd * (float)g[i][e] + (float)b[i][e]);
+                o[e] = (half_t)(((float)v[i][e] - mean) * rstd * (float)g[k][e] + (float)b[k][e]);
             yr[idx] = o;
         }
     }
@@ -267,7 +276,8 @@ hipError_t launch_layernorm(const half_t* x, const int32_t* in_row_map, const ha
     if (rows <= 0) return hipSuccess;
     const dim3 grid((unsigned)rows), block(256);
     const bool vec = (width % 8 == 0) && aligned16(x) && aligned16(y) && aligned16(gamma) && aligned16(beta);
-#define EET_LN(NV) hipLaunchKernelGGL(layernorm_cached<NV>, grid, block, 0, s, x, in_row_map, gamma, beta, y, width, eps, bump_lens, bump_count)
+#define EET_LN_AT(NV, EARLY) hipLaunchKernelGGL((layernorm_cached<NV, EARLY>), grid, block, 0, s, x, in_row_map, gamma, beta, y, width, eps, bump_lens, bump_count)
+#define EET_LN(NV) do { if (rows <= 4096) EET_LN_AT(NV, true); else EET_LN_AT(NV, false); } while (0)
 #define EET_LNW(NV) hipLaunchKernelGGL(layernorm_wave<NV>, dim3((unsigned)((rows + 3) / 4)), block, 0, s, x, in_row_map, gamma, beta, y, (int)rows, width, eps, bump_lens, bump_count)
     if (vec && width <= 2048 && rows >= 64) {                 // a prompt's rows: one wave each
         if (width <= 512) EET_LNW(1);
@@ -281,6 +291,7 @@ hipError_t launch_layernorm(const half_t* x, const int32_t* in_row_map, const ha
         hipLaunchKernelGGL(layernorm_generic, grid, block, 0, s, x, in_row_map, gamma, beta, y, width, eps,
                            bump_lens, bump_count);
 #undef EET_LN
+#undef EET_LN_AT
 #undef EET_LNW
     return hipGetLastError();
 }
