@@ -301,7 +301,7 @@ template <int BM, int BN, int NW, int NS, int KS, int AM, int AN, bool NTW = fal
 struct GemmTileExec {
     static constexpr int BK = 64, AH = AM / 2;
     static constexpr int LRA = BM / NW, LRW = BN / NW, LIA = LRA / 8, LIW = LRW / 8;
-    static_assert(AM % 2 == 0 && AH >= 1 && AH <= 4 && (AN == 4 || AN == 8), "wave tile shape");
+    static_assert(AM >= 2 && AH <= 4 && (AN == 4 || AN == 8), "wave tile shape");
     const half_t* pa[LIA];                 // this lane's source of each load instruction, K tile 0
     const half_t* pw[LIW];
     half_t* as_base;                       // stage 0 of this wave's K group: As[kg * NS], Ws[kg * NS]
@@ -450,7 +450,7 @@ struct GemmTileExec {
 };
 
 // SCHED: 0 = the schedule of pipe::gemm_k_loop<NS>, 1 = its early-release form (two stages), 2 = the schedule for one wave
-// per SIMD (pipe::gemm_k_loop_interleaved; two stages, one K group)
+// per SIMD (pipe::gemm_k_loop_interleaved<NS>; one K group; wave tiles of an odd number of 16-row blocks too)
 // NTS: the output is stored with the non-temporal hint (outputs of 256 MB and more, which no cache keeps for their reader:
 // 24576 x 49152 x 12288 21.70 -> 21.53 ms, 24576 x 12288 x 12288 5.69 -> 5.59, 8192 x 16384 x 12288 2.436 -> 2.393).
 // NTW: the weights are loaded with the non-temporal hint (one row tile: every weight is read once by the launch).
@@ -462,18 +462,18 @@ struct GemmTileExec {
 template <int BM, int BN, int WGM, int WGN, int EPI, int NS, int KS, int SCHED, bool NTS = false, bool NTW = false, bool ROT = false>
 // (192 x 128 tiles are made for two workgroups per CU: the residual and cache-row look-ups of their epilogue would take the
 // kernel past 256 registers and halve that: 2000 x 4096 x 4096 with a residual 135 us)
-__global__ __launch_bounds__(WGM* WGN* KS * 64, BM == 192 ? 2 : 1) void gemm_mfma_dma64(GemmArgs a, int tiles_m, int tiles_n) {
-    static_assert(SCHED == 0 || (NS == 2 && KS == 1 && (SCHED == 1 || SCHED == 2)), "schedule");
+__global__ __launch_bounds__(WGM* WGN* KS * 64, BM == 192 && NS == 2 ? 2 : 1) void gemm_mfma_dma64(GemmArgs a, int tiles_m, int tiles_n) {
+    static_assert(SCHED == 0 || (KS == 1 && ((NS == 2 && SCHED == 1) || SCHED == 2)), "schedule");
     // KS > 1: KS groups of WGM x WGN waves share the tile and take every KS-th K step each, through LDS stages of their
     // own; the other groups' accumulators are added to the first's through LDS at the end.  For the few
     // tiles of a narrow output with a long K, where nothing else puts more loads in flight per CU.
     constexpr int NW = WGM * WGN, BK = 64;
-    static_assert(NS == 2 || NS == 3, "LDS stages");
+    static_assert(NS == 2 || NS == 3 || (NS == 4 && SCHED == 2), "LDS stages");
     static_assert(KS == 1 || KS == 2 || KS == 4, "K groups");
     constexpr int WM = BM / WGM, WN = BN / WGN, AM = WM / 16, AN = WN / 16;   // wave tile in 16 x 16 accumulator blocks
     constexpr int LRA = BM / NW, LRW = BN / NW;   // rows of each operand tile a wave loads per K step
     constexpr int LIA = LRA / 8, LIW = LRW / 8;   // wave-level load instructions per operand per K step
-    static_assert(LRA % 8 == 0 && LRW % 8 == 0 && LIA >= 1 && LIW >= 1 && WM % 32 == 0 && (WN == 64 || WN == 128), "tile shape");
+    static_assert(LRA % 8 == 0 && LRW % 8 == 0 && LIA >= 1 && LIW >= 1 && WM % (SCHED == 2 ? 16 : 32) == 0 && (WN == 64 || WN == 128), "tile shape");
     __shared__ __attribute__((aligned(1024))) half_t As[KS * NS][BM * BK];
     __shared__ __attribute__((aligned(1024))) half_t Ws[KS * NS][BN * BK];
 
@@ -540,7 +540,7 @@ __global__ __launch_bounds__(WGM* WGN* KS * 64, BM == 192 ? 2 : 1) void gemm_mfm
     for (int i = 0; i < AM; ++i)
 #pragma unroll
         for (int j = 0; j < AN; ++j) acc[i][j] = float4v{0.f, 0.f, 0.f, 0.f};
-    if constexpr (SCHED == 2) pipe::gemm_k_loop_interleaved(ex, nk);
+    if constexpr (SCHED == 2) pipe::gemm_k_loop_interleaved<NS>(ex, nk);
     else pipe::gemm_k_loop<NS, SCHED == 1>(ex, nk);
 
     __syncthreads();                                      // every wave is done with the operand stages
@@ -1737,29 +1737,44 @@ static int rows_in_whole_rounds(const GemmArgs& a, Epilogue epi, int big_tiles) 
     return 0;
 }
 
-// The tile of a launch with 128 x 128 tiles for every CU, by the time its rounds take.  Measured over K at full rounds, us with
-// K in thousands (of 1024): 256 x 256, one workgroup per CU: 10 + 21.5 K; 192 x 128, two per CU: 8 + 21.3 K for both; 128 x 128,
-// two per CU: 6 + 14.5 K for both.  A last round that gives every CU at most one workgroup takes about 0.76 (192 x 128)
-// or 0.58 (128 x 128) of the time of two, a fuller one 0.92 of a whole round.  So the large tile, the best per flop, gives
-// way where its last round would leave much of the chip idle (us, 256 x 256 / 192 x 128 / 128 x 128): 3054 x 3072 x 1024 31.3 /
-// 25.1 / 31.0, 2140 x 4096 x 1024 33.9 / 27.1 / 33.1, 1500 x 6144 x 2048 48.8 / 44.2 / 55.1, 1200 x 16384 x 4096 188 / 173 / 190,
-// 6000 x 3072 x 768 55.5 / 41.9 / 41.7; and not where it would not: 6758 x 6144 x 2048 149 / 157 / 162, 3262 x 12288 x 4096
-// 276 / 306 / 315, 1200 x 4096 x 4096 87 / 70 / 61.  256 x 128 and 128 x 256 tiles were never the best (LDS for one per CU
-// either way, a third more operand traffic than 256 x 256).  At most 128 rows: half of a taller tile would be idle.
-enum TileChoice { kTileSmall, kTile128, kTile192, kTile256 };
+// The tile of a launch of more than 128 rows, by the time its rounds take.  Measured, us, K in thousands (of 1024):
+//   256 x 256, one workgroup per CU                    10 + 21.5 K   per round of up to 256 tiles
+//   128 x 256 (three stages), 192 x 128 (three stages), 128 x 128 (three), 96 x 128 (four), one per CU
+//                                       9 + 12 K, 7 + 9.2 K, 5 + 7.9 K, 4.5 + 6.9 K   for up to 256 tiles (one round only)
+//   192 x 128, 128 x 128, 128 x 64, two per CU         8 + 21.3 K, 6 + 14.5 K, 4.5 + 9 K   per whole round of 512; a last round
+//                                                      that gives every CU at most one takes 0.76, 0.58 (0.8 if it is the
+//                                                      only one), 0.75 of that, a fuller one 0.92
+// So the large tile, the best per flop, gives way where its last round would leave much of the chip idle, to whichever tile
+// fills the CUs once (or twice) with the least on top.  us, 256 x 256 / two per CU (192 x 128, 128 x 128, 128 x 64) / one per CU (its
+// tile): 3054 x 3072 x 1024 31 / 25, 32, 30 / 32; 2140 x 4096 x 1024 34 / 27, 33, 33; 1200 x 16384 x 4096 188 / 173, 190, 225;
+// 2140 x 1024 x 4096 83 / 68, 55, 35 / 29.5 (96 x 128); 1200 x 2048 x 8192 - / -, -, 81 / 54 (96 x 128); 700 x 4096 x 16384 302 / 263,
+// 215, 173 / 112 (96 x 128); 700 x 6144 x 2048 - / -, 32, 38 / 25 (192 x 128); 400 x 12288 x 4096 - / -, 64, 74 / 56.5 (128 x 256);
+// 2500 x 1280 x 5120 - / -, 50, 58 / 47 (128 x 128); and not where it would not: 6758 x 6144 x 2048 149 / 157, 162; 3262 x 12288 x 4096
+// 276 / 306, 315.  All of the one-per-CU tiles run the one-wave-per-SIMD schedule, a tenth ahead of the shared one at every
+// depth (700 x 4096 x 16384, 128 x 128: 141 with the shared schedule and 3, 4 or 5 stages, 130 and 123 with this one and 3 and 4).
+enum TileChoice { kTileSmall, kTile128x64, kTile128Pair, kTile192Pair, kTile96, kTile128, kTile192, kTile128x256, kTile256 };
 static TileChoice choose_tile(int M, int N, int K) {
     auto tiles = [&](int bm, int bn) { return (double)((M + bm - 1) / bm) * ((N + bn - 1) / bn); };
-    const double n256 = tiles(256, 256), n192 = tiles(192, 128), n128 = tiles(128, 128), k = K / 1024.0;
-    if (n128 <= 256) return kTileSmall;
-    if (M <= 128) return kTile128;
+    const double k = K / 1024.0;
+    double best = 1e30;
+    TileChoice choice = kTile128x64;
+    auto offer = [&](TileChoice c, double us) {
+        if (us < best) { best = us; choice = c; }
+    };
     auto pairs = [](double n, double two, double one) {         // n tiles, two per CU, `two` the time of both, `one` the share of one
         const double whole = (double)(int64_t)(n / 512), rest = n - whole * 512;
         return two * (whole + (rest == 0 ? 0.0 : rest <= 256 ? one : 0.92));
     };
-    const double t256 = (double)(int64_t)((n256 + 255) / 256) * (10 + 21.5 * k);
-    const double t192 = pairs(n192, 8 + 21.3 * k, 0.76), t128 = pairs(n128, 6 + 14.5 * k, 0.58);
-    if (t256 <= 1.03 * t192 && t256 <= 1.03 * t128) return kTile256;
-    return t192 <= t128 ? kTile192 : kTile128;
+    // (the large tile first and with 3 % in hand: past the first round the others' tails are rougher estimates than its own)
+    offer(kTile256, (double)(int64_t)((tiles(256, 256) + 255) / 256) * (10 + 21.5 * k) / 1.03);
+    offer(kTile192Pair, pairs(tiles(192, 128), 8 + 21.3 * k, 0.76));
+    offer(kTile128Pair, pairs(tiles(128, 128), 6 + 14.5 * k, tiles(128, 128) <= 256 ? 0.8 : 0.58));
+    offer(kTile128x64, pairs(tiles(128, 64), 4.5 + 9 * k, 0.75));
+    if (tiles(128, 256) <= 256) offer(kTile128x256, 9 + 12 * k);
+    if (tiles(192, 128) <= 256) offer(kTile192, 7 + 9.2 * k);
+    if (tiles(128, 128) <= 256) offer(kTile128, 5 + 7.9 * k);
+    if (tiles(96, 128) <= 256) offer(kTile96, 4.5 + 6.9 * k);
+    return choice;
 }
 
 hipError_t launch_gemm(const GemmArgs& a, Epilogue epi, hipStream_t s) {
@@ -1801,10 +1816,42 @@ hipError_t launch_gemm(const GemmArgs& a, Epilogue epi, hipStream_t s) {
             if (e != hipSuccess) return e;
             return launch_gemm(rows_from(a, epi, m_whole), epi, s);
         }
-        const TileChoice choice = choose_tile(a.M, a.N, a.K);
-        if (choice == kTile192) {
-            launch_dma64_cfg<2, 2, 192, 128, 2, 1, 0>(a, epi, s);
-        } else if (choice == kTile256) {
+        // Few tiles (short prompts, narrow layers): smaller tiles put more workgroups on the chip; the K loop of each is a chain
+        // of dependent steps, so what counts there is how many run side by side and how far ahead the loads run (rows x K x N,
+        // against two-stage register-staged tiles of the same sizes: 256 x 4096 x 4096 29.9 -> 23.8 us, 2048 x 4096 x 1024 37.6 -> 28.5
+        // us, 768 x 8192 x 2048 69.5 -> 51.9 us, 128 x 1600 x 6400 16.3 -> 11.8 us).  A long K with all tiles resident at one workgroup
+        // per CU: two groups of waves per tile, each with half of the K steps and LDS stages of its own, put twice the loads in
+        // flight (rows x K x N: 128 x 4096 x 4096 23.8 -> 16.5 us, 96 x 16384 x 4096 101.7 -> 67.7 us, 512 x 4096 x 1024 23.3 -> 16.5 us; 1959 x
+        // 4096 x 1024 24.8 against 30.1 with the best of the tiles below; four groups with two stages each were slower than two with
+        // three).
+        const bool k_split = a.K % 128 == 0 && a.K >= 1024;
+        const int wg128 = ((a.M + 127) / 128) * ((a.N + 63) / 64), wg64 = ((a.M + 63) / 64) * ((a.N + 63) / 64);
+        TileChoice choice = kTileSmall;
+        if (wg128 >= 128 && !(k_split && wg128 <= 256)) {
+            const int tiles128 = ((a.M + 127) / 128) * ((a.N + 127) / 128);
+            // at most 128 rows: half of a taller tile would be idle
+            choice = a.M > 128 ? choose_tile(a.M, a.N, a.K) : tiles128 > 256 ? kTile128Pair : tiles128 == 256 ? kTile128 : kTile128x64;
+        }
+        switch (choice) {
+        case kTileSmall:
+            if (k_split && wg64 <= 256) launch_dma64_cfg<2, 1, 64, 64, 3, 2>(a, epi, s);       // (1000 x 1024 x 4096: 25.1 -> 20.1)
+            else if (wg128 >= 128) launch_dma64_cfg<4, 1, 128, 64, 3, 2>(a, epi, s);
+            else launch_dma64_cfg<2, 1, 64, 64, 3>(a, epi, s);
+            break;
+        case kTile128x64: launch_dma64_cfg<4, 1, 128, 64, 3>(a, epi, s); break;
+        case kTile192Pair: launch_dma64_cfg<2, 2, 192, 128, 2, 1, 0>(a, epi, s); break;
+        // The one-wave-per-SIMD schedule serves two workgroups per CU as well, and better than the shared one (6000 x 768 x 3072 48.5 ->
+        // 45.3 us, 1200 x 4096 x 16384 238 -> 221, 3054 x 3072 x 1024 32.7 -> 31.0), but for the wide outputs with a short K that few rows
+        // come here with (68 x 50304 x 256 11.2 us against 10.5, x 1280 34.6 against 33.3)
+        case kTile128Pair:
+            if (a.M <= 128) launch_dma64_cfg<2, 2, 128, 128>(a, epi, s);
+            else launch_dma64_cfg<2, 2, 128, 128, 2, 1, 2>(a, epi, s);
+            break;
+        case kTile96: launch_dma64_cfg<2, 2, 96, 128, 4, 1, 2>(a, epi, s); break;
+        case kTile128: launch_dma64_cfg<2, 2, 128, 128, 3, 1, 2>(a, epi, s); break;
+        case kTile192: launch_dma64_cfg<2, 2, 192, 128, 3, 1, 2>(a, epi, s); break;
+        case kTile128x256: launch_dma64_cfg<2, 2, 128, 256, 3, 1, 2>(a, epi, s); break;
+        case kTile256:
             // Four waves with 128 x 128 each: a third less LDS read traffic per flop than eight waves of 128 x 64, and the
             // LDS of a CU -- fragment reads plus the arriving tiles -- is what the matrix pipes otherwise wait for
             // (rows x N x K, eight waves in two alternating groups -> four waves: 25082 x 49152 x 12288 1.16 -> 1.23 PFLOP/s,
@@ -1818,35 +1865,7 @@ hipError_t launch_gemm(const GemmArgs& a, Epilogue epi, hipStream_t s) {
             if (a.K >= 32768 && big_tiles % 256 != 0) launch_dma64_cfg<2, 4, 256, 256, 2, 1, 1>(a, epi, s);
             else if ((size_t)a.M * a.N * sizeof(half_t) >= kMemorySideCacheBytes) launch_dma64_cfg<2, 2, 256, 256, 2, 1, 2, true>(a, epi, s);
             else launch_dma64_cfg<2, 2, 256, 256, 2, 1, 2>(a, epi, s);
-        }
-        else {
-            // few tiles (short prompts, narrow layers): smaller tiles put more workgroups on the chip; the K loop of
-            // each is a chain of dependent steps, so what counts there is how many run side by side and how far ahead
-            // the loads run: three LDS stages for the tiles that share a CU with few others
-            // (rows x K x N, against two-stage register-staged tiles of the same sizes: 256 x 4096 x 4096 29.9 -> 23.8 us,
-            // 2048 x 4096 x 1024 37.6 -> 28.5 us, 768 x 8192 x 2048 69.5 -> 51.9 us, 128 x 1600 x 6400 16.3 -> 11.8 us)
-            const int tm = (a.M + 127) / 128;
-            const int tiles128 = tm * ((a.N + 127) / 128);
-            // A long K with all tiles resident at one workgroup per CU: two groups of waves per tile, each with half
-            // of the K steps and LDS stages of its own, put twice the loads in flight (rows x K x N: 128 x 4096 x 4096
-            // 23.8 -> 16.5 us, 96 x 16384 x 4096 101.7 -> 67.7 us, 512 x 4096 x 1024 23.3 -> 16.5 us; four groups with
-            // two stages each were slower than two with three).
-            const bool k_split = a.K % 128 == 0 && a.K >= 1024;
-            const int wg128 = tm * ((a.N + 63) / 64), wg64 = ((a.M + 63) / 64) * ((a.N + 63) / 64);
-            if (wg128 < 128) {
-                if (k_split && wg64 <= 256) launch_dma64_cfg<2, 1, 64, 64, 3, 2>(a, epi, s);
-                else launch_dma64_cfg<2, 1, 64, 64, 3>(a, epi, s);
-            } else if (tiles128 < 256 && k_split && wg128 <= 256) launch_dma64_cfg<4, 1, 128, 64, 3, 2>(a, epi, s);
-            // 128 x 128 tiles for most CUs, one each and three stages (128 x 64 -> 128 x 128: 700 x 4096 x 16384 173 -> 140 us, 1500 x
-            // 2048 x 8192 81 -> 72, 3000 x 1280 x 5120 59 -> 51, 1000 x 3072 x 1024 14.7 -> 13.5); not for 8 column tiles (3054 x
-            // 1024 x 4096 37.5 -> 40.0) or a short K (1000 x 3072 x 512 8.3 -> 9.5)
-            else if (tiles128 == 256 || (tiles128 >= 176 && tiles128 < 256 && a.N >= 1280 && a.K >= 1024)) launch_dma64_cfg<2, 2, 128, 128, 3>(a, epi, s);
-            else if (tiles128 < 256) launch_dma64_cfg<4, 1, 128, 64, 3>(a, epi, s);
-            // two per CU.  The one-wave-per-SIMD schedule serves two of them as well, and better than the shared one
-            // (6000 x 768 x 3072 48.5 -> 45.3 us, 1200 x 4096 x 16384 238 -> 221, 3054 x 3072 x 1024 32.7 -> 31.0), but for the wide
-            // outputs with a short K that few rows come here with (68 x 50304 x 256 11.2 us against 10.5, x 1280 34.6 against 33.3)
-            else if (a.M <= 128) launch_dma64_cfg<2, 2, 128, 128>(a, epi, s);
-            else launch_dma64_cfg<2, 2, 128, 128, 2, 1, 2>(a, epi, s);
+            break;
         }
     }
     return hipGetLastError();

@@ -164,7 +164,7 @@ EET_PIPE_FN void gemm_k_loop(Ops& op, int nk) {
 }
 
 // ---------------------------------------------------------------------------------------------------------
-// K loop of the MFMA tile kernel for one wave per SIMD, two LDS stages.  Nothing else runs on the SIMD while a wave
+// K loop of the MFMA tile kernel for one wave per SIMD, NS LDS stages.  Nothing else runs on the SIMD while a wave
 // waits, and the LDS of the CU is busy most of the time (fragment reads of four waves plus the arriving tiles), so
 // every request is issued between the multiplies of an earlier phase, spread evenly over them: a burst of LDS reads
 // stalls the wave's instruction stream, and the multiplies behind it, until the LDS queue has room.
@@ -172,7 +172,7 @@ EET_PIPE_FN void gemm_k_loop(Ops& op, int nk) {
 // A K tile is two phases, one per k half; the fragments of a whole k half have two register buffers (buffer = k half).
 // While k half 0 of tile kt is multiplied the reads of its k half 1 are issued.  After them every read of the stage
 // has been issued: the wave waits for them and for its part of tile kt+1, and the barrier hands the stage over with
-// half of the tile's multiplies still to come.  While k half 1 is multiplied the loads of tile kt+2 go into the stage
+// half of the tile's multiplies still to come.  While k half 1 is multiplied the loads of tile kt+NS go into the stage
 // just released and the reads of k half 0 of tile kt+1 are issued.  The loads past the last tile repeat the last tile
 // (the number of loads per step, and with it every wait count, stays fixed; nothing reads them).
 //
@@ -183,21 +183,22 @@ EET_PIPE_FN void gemm_k_loop(Ops& op, int nk) {
 //                                               of k half 1-H of `stage` into the other buffer
 //   mma_half_fetch_load<H>(stage, tile, lstage) the same, and issue the loads of K tile `tile` into stage `lstage`
 // ---------------------------------------------------------------------------------------------------------
-template <class Ops>
+template <int NS = 2, class Ops = void>
 EET_PIPE_FN void gemm_k_loop_interleaved(Ops& op, int nk) {
-    op.load(0, 0);
-    op.load(nk > 1 ? 1 : 0, 1);
-    op.template wait_vmem<1>();                   // tile 0 of this wave has landed ...
+    for (int t = 0; t < NS; ++t) op.load(t < nk ? t : nk - 1, t);
+    op.template wait_vmem<NS - 1>();              // tile 0 of this wave has landed ...
     op.barrier();                                 // ... and everybody else's
     op.template fetch_half<0>(0);
+    int st = 0;
     for (int kt = 0; kt < nk; ++kt) {
-        const int st = kt & 1;
+        const int st1 = st == NS - 1 ? 0 : st + 1;
         op.wait_fetched();
         op.template mma_half_fetch<0>(st);
         op.wait_fetched();                          // every read of stage st has landed
-        op.template wait_vmem<0>();               // this wave's part of tile kt+1 has landed
+        op.template wait_vmem<NS - 2>();          // this wave's part of tile kt+1 has landed
         op.barrier();                             // ... and everybody else's; stage st is free
-        op.template mma_half_fetch_load<1>(st ^ 1, kt + 2 < nk ? kt + 2 : nk - 1, st);   // (reads past the last tile: stale, never multiplied)
+        op.template mma_half_fetch_load<1>(st1, kt + NS < nk ? kt + NS : nk - 1, st);   // (reads past the last tile: stale, never multiplied)
+        st = st1;
     }
     op.wait_fetched();                              // the stale reads and the repeated loads too: the epilogue reuses the stages
     op.template wait_vmem<0>();

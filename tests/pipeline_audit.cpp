@@ -347,6 +347,18 @@ int main() {
             expect_ok(r.verdict(name), name);
         }
         {
+            HalfStepRecorder r(nk);
+            eet::pipe::gemm_k_loop_interleaved<3>(r, nk);
+            snprintf(name, sizeof name, "tile kernel, one wave per SIMD, three LDS stages, %d K tiles", nk);
+            expect_ok(r.verdict(name), name);
+        }
+        {
+            HalfStepRecorder r(nk);
+            eet::pipe::gemm_k_loop_interleaved<4>(r, nk);
+            snprintf(name, sizeof name, "tile kernel, one wave per SIMD, four LDS stages, %d K tiles", nk);
+            expect_ok(r.verdict(name), name);
+        }
+        {
             GemmRecorder r(nk);
             eet::pipe::gemm_k_loop<3>(r, nk);
             snprintf(name, sizeof name, "tile kernel, three LDS stages, %d K tiles", nk);

@@ -259,7 +259,10 @@ def test_linear_rows_stream(eet, M, K, N):
 @pytest.mark.parametrize("M,K,N", [(3000, 1024, 4160), (4099, 192, 3136), (2049, 4096, 6144),
                                    (800, 128, 12352), (961, 64, 12352),       # 192 x 128 tiles, two per CU
                                    (300, 128, 12352),                         # 128 x 128 tiles, two per CU
-                                   (1500, 128, 2112)])                        # 128 x 128 tiles, one per CU, three stages
+                                   (1500, 64, 2112), (1500, 128, 2112),       # one tile per CU: 128 x 64 ...
+                                   (1190, 1088, 2112), (2011, 2112, 1088),    # ... 96 x 128 in four stages
+                                   (2500, 1280, 1344), (1480, 320, 3136),     # ... 128 x 128, 192 x 128 in three stages
+                                   (400, 1088, 12352)])                       # ... 128 x 256 in three stages
 def test_linear_large_tiles(eet, M, K, N):
     """Shapes that take the larger tiles of the direct-to-LDS tile kernel, with ragged row and column tails."""
     x = wl.normal(350, M, (M, K))
