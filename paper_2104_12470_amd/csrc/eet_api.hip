@@ -369,7 +369,12 @@ static int enqueue_decode(eet_layer* L, const void* tokens, void* out, void* kv_
     // Small layers are launch-bound in decode: there the two LayerNorms run inside the projections
     // that consume them (each workgroup recomputes the row statistics of the <= 16 token rows).
     // Measured break-even is near 16 MB of FFN-1 weights; larger layers keep the separate row kernel.
-    const bool fuse_ln = B <= 16 && (size_t)F * H * sizeof(half_t) <= ((size_t)16 << 20);
+    // (Up to 20 MB where the small-layer kernel takes the rows in eight waves and three column units: hidden 1536, per layer-step, 1
+    // sequence 30.6 -> 26.4 us, 4 33.8 -> 29.5, 16 in a stack 48.6 -> 46.0.  Not at 33 MB, hidden 2048: 39.9 -> 44.4; nothing to gain
+    // with few units: 1024 x 8192 26.6 -> 26.9.)
+    const bool small = B <= 16 && (size_t)F * H * sizeof(half_t) <= ((size_t)16 << 20);
+    const size_t widest = (size_t)(F > 3 * H ? F : 3 * H) * H * sizeof(half_t);      // both consumers have to fit that kernel
+    const bool fuse_ln = small || (B <= 16 && H % 512 == 0 && H > 1024 && H <= 2048 && widest <= ((size_t)20 << 20));
     // What a decode step moves between two uses of the same weight or cache row: every layer's weights and visible K/V
     // once.  More than the memory-side cache holds: nothing survives there until the next step, and the read-once operands
     // are loaded with the non-temporal hint (a tenth faster from HBM).  Less (hidden 2048 on its own: 150 MB): the step
@@ -380,7 +385,7 @@ static int enqueue_decode(eet_layer* L, const void* tokens, void* out, void* kv_
                               (2 * ((size_t)4 * H * H + (size_t)2 * H * F) + (size_t)4 * H * visible);
     // (not for the small layers whose idle workgroups pull the next launches' operands into that cache: PrefetchArgs below;
     // the hint on the consumer's loads undoes that: 24 hidden-1024 layers 320.7 -> 330.4 ms for 512 steps)
-    const int once = (step_bytes > kMemorySideCacheBytes && !fuse_ln) ? 1 : 0;
+    const int once = (step_bytes > kMemorySideCacheBytes && !small) ? 1 : 0;
     // The same small layers leave CUs idle in every launch: extra workgroups of the two launches with the fewest
     // workgroups pull operands of later launches towards the memory-side cache (PrefetchArgs).  `next`: the layer
     // whose step follows this one (the next layer of a stack, or this layer's own next step).  Measured on the
@@ -390,7 +395,9 @@ static int enqueue_decode(eet_layer* L, const void* tokens, void* out, void* kv_
     // workgroups at one per CU.  Moving any share of the K/V rows (a quarter to all) from FFN-2's extra workgroups to
     // the output projection's was slower too (324 -> 361-367 ms).
     constexpr int kPrefetchBlocks = 128;
-    const bool prefetch = fuse_ln;
+    // (of the layers between 16 and 20 MB only those of a stack too large for that cache: 12 x hidden 1536, 8 sequences, 35.8 -> 34.7 us
+    // per layer-step, a single layer 26.4 -> 28.2)
+    const bool prefetch = small || (fuse_ln && step_bytes > kMemorySideCacheBytes);
     auto lines = [](size_t bytes) { return (uint32_t)(bytes / 128); };
     const half_t* qkv_in = x;
     if (!fuse_ln) {

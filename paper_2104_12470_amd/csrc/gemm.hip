@@ -1441,7 +1441,8 @@ static void launch_flat(const GemmArgs& a, int upw, Epilogue epi, int lds, hipSt
 // NW in {4, 8, 16} and UPW in 1..4, N a multiple of 16, no row maps
 static bool try_flat(const GemmArgs& a, Epilogue epi, hipStream_t s, bool ask_only = false) {
     constexpr int tn8_wgs = 128;                              // fewer 16-column workgroups than this: 8-column ones
-    if ((int64_t)a.N * a.K * 2 > (16 << 20) || a.N % 16 != 0 || a.K % 64 != 0) return false;
+    // (with the LayerNorm fused in front up to 20 MB: it replaces a launch)
+    if ((int64_t)a.N * a.K * 2 > ((a.ln_gamma != nullptr ? 20 : 16) << 20) || a.N % 16 != 0 || a.K % 64 != 0) return false;
     if (a.res_row_map != nullptr || a.out_row_map != nullptr || a.tok_row_map != nullptr) return false;
     const bool ln = a.ln_gamma != nullptr;
     const int units = a.K / 64;

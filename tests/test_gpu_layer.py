@@ -124,6 +124,13 @@ def test_projections_cut_along_k(eet, hidden, heads, ffn, B, S, max_seq):
     full_parity(eet, w)
 
 
+@pytest.mark.parametrize("B", [1, 9, 16])
+def test_decode_with_the_layernorms_inside_projections_of_16_to_20_mb(eet, B):
+    """Hidden 1536: the feed-forward matrix is 18.9 MB, the LayerNorms run inside the small-layer kernel all the same."""
+    w = wl.Workload(f"h1536x{B}", 37, 1536, 24, 6144, 1, B, 24, 3, 24, 3, 32)
+    full_parity(eet, w)
+
+
 @pytest.mark.parametrize("heads,B,max_seq,lo,hi", [(4, 3, 512, 300, 500), (2, 1, 4096, 3900, 4000)])
 def test_decode_with_the_key_range_split_and_merged_by_the_output_projection(eet, heads, B, max_seq, lo, hi):
     """Few (sequence, head) pairs and a long cache: the decode attention splits the key range (4 ranges per pair in the
