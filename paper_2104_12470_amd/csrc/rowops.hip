@@ -91,10 +91,27 @@ __global__ __launch_bounds__(256) void layernorm_cached(const half_t* __restrict
     if (bump_lens != nullptr && tid == 0 && row < bump_count) bump_lens[row] += 1;
 }
 
-// Many narrow rows (width <= 2048, width % 8 == 0): one wave per row, four rows per workgroup.  The row sits in NV
+constexpr int kLayerNormWaveRows = 64;
+// Many narrow rows (width <= 2048, width % 8 == 0; kLayerNormWaveRows and more): one wave per row, four rows per workgroup.  The row sits in NV
 // 16-byte vectors per lane, both reductions are lane exchanges, and there is no barrier and no LDS, so a prompt's few
 // thousand rows are all in flight at once instead of queueing behind 256-thread workgroups that each wait twice.
-template <int NV>
+//
+// BLOCK_ORDER: the two reductions add in the order of layernorm_cached (one exchange per 512 columns, as one of its waves does,
+// then those sums in turn), so that a row comes out with the same bits as there.  The launch that also sets up a prefill takes
+// it below 64 rows, where launch_layernorm takes the 256-thread kernel: a layer's result does not depend on which of the two
+// launches normalised its rows (the layers of a stack take one or the other).
+template <int NV, bool BLOCK_ORDER>
+__device__ __forceinline__ float sum_of_row(const float (&part)[NV]) {
+    float t = 0.f;
+    if constexpr (BLOCK_ORDER) {
+#pragma unroll
+        for (int i = 0; i < NV; ++i) t += wave_sum(part[i]);
+    } else {
+        t = wave_sum(part[NV - 1]);                           // part[i] goes on from part[i - 1]
+    }
+    return t;
+}
+template <int NV, bool BLOCK_ORDER = false>
 __device__ __forceinline__ void layernorm_row_of_wave(const half_t* xrow, const half_t* __restrict__ gamma, const half_t* __restrict__ beta,
                                                       half_t* yrow, int width, float eps, int lane) {
     const half8v* xr = reinterpret_cast<const half8v*>(xrow);
@@ -111,27 +128,28 @@ __device__ __forceinline__ void layernorm_row_of_wave(const half_t* xrow, const 
             b[i] = b8[idx];
         }
     }
-    float sum = 0.f;
+    float part[NV];
 #pragma unroll
     for (int i = 0; i < NV; ++i) {
+        part[i] = BLOCK_ORDER || i == 0 ? 0.f : part[i - 1];
         if (lane + i * 64 < nvec) {
 #pragma unroll
-            for (int e = 0; e < 8; ++e) sum += (float)v[i][e];
+            for (int e = 0; e < 8; ++e) part[i] += (float)v[i][e];
         }
     }
-    const float mean = wave_sum(sum) / (float)width;
-    float sq = 0.f;
+    const float mean = sum_of_row<NV, BLOCK_ORDER>(part) / (float)width;
 #pragma unroll
     for (int i = 0; i < NV; ++i) {
+        part[i] = BLOCK_ORDER || i == 0 ? 0.f : part[i - 1];
         if (lane + i * 64 < nvec) {
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
                 const float dlt = (float)v[i][e] - mean;
-                sq += dlt * dlt;
+                part[i] += dlt * dlt;
             }
         }
     }
-    const float rstd = rsqrtf(wave_sum(sq) / (float)width + eps);
+    const float rstd = rsqrtf(sum_of_row<NV, BLOCK_ORDER>(part) / (float)width + eps);
     half8v* yr = reinterpret_cast<half8v*>(yrow);
 #pragma unroll
     for (int i = 0; i < NV; ++i) {
@@ -279,7 +297,7 @@ hipError_t launch_layernorm(const half_t* x, const int32_t* in_row_map, const ha
 #define EET_LN_AT(NV, EARLY) hipLaunchKernelGGL((layernorm_cached<NV, EARLY>), grid, block, 0, s, x, in_row_map, gamma, beta, y, width, eps, bump_lens, bump_count)
 #define EET_LN(NV) do { if (rows <= 4096) EET_LN_AT(NV, true); else EET_LN_AT(NV, false); } while (0)
 #define EET_LNW(NV) hipLaunchKernelGGL(layernorm_wave<NV>, dim3((unsigned)((rows + 3) / 4)), block, 0, s, x, in_row_map, gamma, beta, y, (int)rows, width, eps, bump_lens, bump_count)
-    if (vec && width <= 2048 && rows >= 64) {                 // a prompt's rows: one wave each
+    if (vec && width <= 2048 && rows >= kLayerNormWaveRows) { // a prompt's rows: one wave each
         if (width <= 512) EET_LNW(1);
         else if (width <= 1024) EET_LNW(2);
         else EET_LNW(4);
@@ -504,7 +522,7 @@ __global__ __launch_bounds__(64) void prefill_setup(SeqLens lens, int batch, int
 // The same set-up and the first LayerNorm of a prefill in one launch, rows of up to 2048 (width % 8 == 0): one wave per padded
 // row, which is either zeroed in `out` or normalised into its packed place in `y`.  A short prompt is a chain of dependent
 // launches, and this is one of eight less (4 prompts of 16 to 64 tokens, hidden 768: 51.5 -> 49.6 us for the layer).
-template <int NV>
+template <int NV, bool FEW>
 __global__ __launch_bounds__(256) void prefill_setup_layernorm(SeqLens lens, int batch, int S, int width, int32_t* __restrict__ cache_lens,
                                                                int32_t* __restrict__ cu_seqlens, int32_t* __restrict__ row_map, half_t* out,
                                                                int left, const half_t* x, const half_t* __restrict__ gamma,
@@ -535,7 +553,7 @@ __global__ __launch_bounds__(256) void prefill_setup_layernorm(SeqLens lens, int
     if (i >= first && i < first + len) {
         const int t = tokens_before(lens, b, lane) + i - first;
         if (lane == 0) row_map[t] = r;
-        layernorm_row_of_wave<NV>(x + (int64_t)r * width, gamma, beta, y + (int64_t)t * width, width, eps, lane);
+        layernorm_row_of_wave<NV, FEW>(x + (int64_t)r * width, gamma, beta, y + (int64_t)t * width, width, eps, lane);
     } else {
         half8v z;
 #pragma unroll
@@ -549,11 +567,15 @@ hipError_t launch_prefill_setup_layernorm(const SeqLens& lens, int batch, int S,
                                           int32_t* row_map, half_t* out, bool left_padded, const half_t* x, const half_t* gamma,
                                           const half_t* beta, half_t* y, float eps, hipStream_t s) {
     const dim3 grid((batch * S + 3) / 4);
-#define EET_SETUP_LN(NV) hipLaunchKernelGGL(prefill_setup_layernorm<NV>, grid, dim3(256), 0, s, lens, batch, S, width, cache_lens, cu_seqlens, row_map, out, left_padded ? 1 : 0, x, gamma, beta, y, eps)
+    int64_t rows = 0;
+    for (int b = 0; b < batch; ++b) rows += lens.len[b];
+#define EET_SETUP_LN_AT(NV, FEW) hipLaunchKernelGGL((prefill_setup_layernorm<NV, FEW>), grid, dim3(256), 0, s, lens, batch, S, width, cache_lens, cu_seqlens, row_map, out, left_padded ? 1 : 0, x, gamma, beta, y, eps)
+#define EET_SETUP_LN(NV) do { if (rows < kLayerNormWaveRows) EET_SETUP_LN_AT(NV, true); else EET_SETUP_LN_AT(NV, false); } while (0)
     if (width <= 512) EET_SETUP_LN(1);
     else if (width <= 1024) EET_SETUP_LN(2);
     else EET_SETUP_LN(4);
 #undef EET_SETUP_LN
+#undef EET_SETUP_LN_AT
     return hipGetLastError();
 }
 

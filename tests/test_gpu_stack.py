@@ -69,6 +69,34 @@ def test_stack_equals_layer_chain_and_oracle(eet, name, n_layers):
         layer.close()
 
 
+@pytest.mark.parametrize("hidden,heads,lens", [(512, 8, [7, 30]), (768, 12, [24, 3, 9]), (1024, 16, [37]), (2048, 16, [20, 43]),
+                                               (2048, 16, [20, 44]), (1024, 16, [1])])
+@pytest.mark.parametrize("how", ["prefill", "prefill_left_padded", "encode"])
+def test_short_prompts_through_a_stack_equal_the_layer_chain(eet, hidden, heads, lens, how):
+    """Fewer than 64 rows (and 64, the first count that takes one wave per row everywhere): the first, second and last layer of
+    a stack normalise their rows in the launch that also sets up the prefill, the layers between in a launch of its own, a
+    chain of layers always in the set-up launch.  Every output bit is the same."""
+    g = torch.Generator(device="cuda:0").manual_seed(hidden + len(lens))
+    rnd = lambda shape, s, m=0.0: torch.empty(shape, dtype=torch.float16, device="cuda:0").normal_(m, s, generator=g)   # noqa: E731
+    H, F, n = hidden, 2 * hidden, 5
+    Ws = [{"ln1_g": rnd((H,), 0.1, 1.0), "ln1_b": rnd((H,), 0.1), "w_qkv": rnd((3 * H, H), 0.02), "b_qkv": rnd((3 * H,), 0.02),
+           "w_o": rnd((H, H), 0.02), "b_o": rnd((H,), 0.02), "ln2_g": rnd((H,), 0.1, 1.0), "ln2_b": rnd((H,), 0.1),
+           "w_fc1": rnd((F, H), 0.02), "b_fc1": rnd((F,), 0.02), "w_fc2": rnd((H, F), 0.02), "b_fc2": rnd((H,), 0.02)} for _ in range(n)]
+    cfg = eet.make_config(H, heads, F, len(lens), max(lens), max(lens))
+    stack, layers = eet.DecoderStack(cfg, Ws), [eet.DecoderLayer(cfg, W) for W in Ws]
+    x = rnd((len(lens), max(lens), H), 1.0)
+    torch.cuda.synchronize()
+    got = getattr(stack, how)(x, lens)
+    h = x
+    for layer in layers:
+        h = getattr(layer, how)(h, lens)
+    torch.cuda.synchronize()
+    assert torch.equal(got.view(torch.int16), h.view(torch.int16))
+    stack.close()
+    for layer in layers:
+        layer.close()
+
+
 def test_graph_replay_matches_direct_launches(eet):
     """Decode steps replayed from the recorded graph, with unrelated eager work and synchronisations
     between the replays, give the same bits as direct launches, step after step; a new prefill with
