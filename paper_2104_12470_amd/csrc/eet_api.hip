@@ -45,11 +45,17 @@ constexpr size_t kFfnRowPad = 64;
 constexpr int kFfnPadFrom = 32768;
 
 // Byte offsets of the pieces of a layer's workspace.
+// The fp32 sums of a projection cut along K (gemm_k_ranges) lie in activation buffers that nobody needs while it runs, and
+// run over into `cut` between them: buf_f + cut during the attention output projection (its input is in buf_a), cut + buf_a
+// + buf_b during the second feed-forward projection (its input is in buf_f, its residual in buf_y).  `cut` is what is missing:
+// nothing with a prompt capacity of a few thousand rows, and never more than 8 MiB, since a launch is cut into at most 256
+// tiles of 128 x 64 sums (4 MiB with at most 64 rows, 2 MiB with at most 32).  With few rows that takes a workspace past the
+// bound the paper gives for its buffers (hidden 4096, 48 sequences of one row: 3.0 -> 5.4 MB where the bound is 3.1; hidden
+// 1024, 512 rows: 7.5 -> 13.8, bound 9.4); held inside the bound the first could not cut its second feed-forward
+// projection at all (29 us -> 71 us).
 struct WorkspaceLayout {
-    size_t lens, cu, row_map, buf_a, buf_b, buf_y, buf_f, part, row_stats, cut, total;
+    size_t lens, cu, row_map, buf_f, cut, buf_a, buf_b, buf_y, part, row_stats, total;
     int splits;
-    size_t cut_room_f() const { return part - buf_f; }      // idle during the attention output projection
-    size_t cut_room_ab() const { return buf_y - buf_a; }    // idle during the second feed-forward projection
 };
 
 // bytes of the sums of all K ranges of an M x N x K bias + residual projection; 0: not cut
@@ -84,10 +90,17 @@ WorkspaceLayout layout_of(const eet_layer_config* c) {
     w.lens = off;    off = align_up(off + sizeof(int32_t) * EET_MAX_BATCH, 256);
     w.cu = off;      off = align_up(off + sizeof(int32_t) * (EET_MAX_BATCH + 1), 256);
     w.row_map = off; off = align_up(off + sizeof(int32_t) * T, 256);
+    w.buf_f = off;   off = align_up(off + 2 * T * (F + kFfnRowPad), 256);
+    w.cut = off;
+    const size_t room_f = w.cut - w.buf_f, room_ab = 2 * align_up(2 * T * H, 256);
+    for (size_t m = 17; m <= (T < (size_t)kGemmCutMaxM ? T : (size_t)kGemmCutMaxM); ++m) {
+        const size_t for_o = cut_bytes((int)m, c->hidden, c->hidden), for_f2 = cut_bytes((int)m, c->hidden, c->ffn);
+        if (for_o > room_f + (off - w.cut)) off = align_up(w.cut + for_o - room_f, 256);
+        if (for_f2 > room_ab + (off - w.cut)) off = align_up(w.cut + for_f2 - room_ab, 256);
+    }
     w.buf_a = off;   off = align_up(off + 2 * T * H, 256);
     w.buf_b = off;   off = align_up(off + 2 * T * H, 256);
     w.buf_y = off;   off = align_up(off + 2 * T * H, 256);
-    w.buf_f = off;   off = align_up(off + 2 * T * (F + kFfnRowPad), 256);
     w.splits = attention_decode_splits(c->max_batch, c->heads, c->max_seq);
     w.part = off;
     // sized for the split count of any batch <= max_batch (fewer sequences -> more splits)
@@ -102,16 +115,6 @@ WorkspaceLayout layout_of(const eet_layer_config* c) {
     // (mean, squared deviations) per row and workgroup of the producer, at most hidden/16 workgroups of 16 rows
     w.row_stats = off;
     off = align_up(off + (H / 16 + 1) * 16 * 2 * sizeof(float), 256);
-    // K ranges of a cut projection (gemm_k_ranges): they go to activation buffers that are idle at that point where those
-    // hold them (cut_area), else here
-    w.cut = off;
-    size_t cut = 0;
-    for (size_t m = 17; m <= (T < (size_t)kGemmCutMaxM ? T : (size_t)kGemmCutMaxM); ++m) {
-        const size_t for_o = cut_bytes((int)m, c->hidden, c->hidden), for_f2 = cut_bytes((int)m, c->hidden, c->ffn);
-        if (for_o > w.cut_room_f() && for_o > cut) cut = for_o;
-        if (for_f2 > w.cut_room_ab() && for_f2 > cut) cut = for_f2;
-    }
-    off = align_up(off + cut, 256);
     w.total = off;
     return w;
 }
@@ -185,13 +188,12 @@ int eet_layer_destroy(eet_layer_t* layer) {
     return EET_OK;
 }
 
-// Cuts the K of a bias + residual projection of `L` where that pays; `idle`, `room`: the activation buffers nobody needs
-// while it runs.  The rule and the sizes are those layout_of reserved by.
-static void cut_projection(eet_layer* L, GemmArgs& g, size_t idle, size_t room) {
-    const size_t need = cut_bytes(g.M, g.N, g.K);
-    if (need == 0) return;
+// Cuts the K of a bias + residual projection of `L` where that pays; `sums`: where in the workspace its sums lie.  The rule and
+// the sizes are those layout_of reserved by.
+static void cut_projection(eet_layer* L, GemmArgs& g, size_t sums) {
+    if (cut_bytes(g.M, g.N, g.K) == 0) return;
     g.k_ranges = gemm_k_ranges(g.M, g.N, g.K);
-    g.part = reinterpret_cast<float*>(L->ws + (need <= room ? idle : L->lay.cut));
+    g.part = reinterpret_cast<float*>(L->ws + sums);
 }
 
 #define EET_LAUNCH(expr, what)                        \
@@ -255,7 +257,7 @@ static int enqueue_prefill(eet_layer* L, const SeqLens& lens, int batch, int pad
     GemmArgs o{};
     o.x = bufA; o.w = (const half_t*)L->w.w_o; o.bias = (const half_t*)L->w.b_o; o.y = bufY;
     o.M = (int)T; o.N = H; o.K = H; o.res = x; o.res_row_map = d_map; o.read_once = once;
-    cut_projection(L, o, L->lay.buf_f, L->lay.cut_room_f());
+    cut_projection(L, o, L->lay.buf_f);
     // a7: LN2, by the launch that adds up the K ranges where the projection is cut
     if (o.k_ranges > 1) {
         o.fin_gamma = (const half_t*)L->w.ln2_g; o.fin_beta = (const half_t*)L->w.ln2_b; o.fin_y = bufB; o.fin_eps = c.ln_eps;
@@ -272,7 +274,7 @@ static int enqueue_prefill(eet_layer* L, const SeqLens& lens, int batch, int pad
     GemmArgs f2{};
     f2.x = bufF; f2.w = (const half_t*)L->w.w_fc2; f2.bias = (const half_t*)L->w.b_fc2; f2.y = static_cast<half_t*>(out);
     f2.M = (int)T; f2.N = H; f2.K = F; f2.res = bufY; f2.res_row_map = nullptr; f2.out_row_map = d_map; f2.read_once = once;
-    cut_projection(L, f2, L->lay.buf_a, L->lay.cut_room_ab());
+    cut_projection(L, f2, L->lay.cut);
     if (F >= kFfnPadFrom && gemm_takes_row_strides(f1) && gemm_takes_row_strides(f2)) f1.ldy = f2.lda = F + (int)kFfnRowPad;
     EET_LAUNCH(launch_gemm(f1, EPI_BIAS_GELU, s), "ffn 1");
     EET_LAUNCH(launch_gemm(f2, EPI_BIAS_RES, s), "ffn 2");
@@ -457,7 +459,7 @@ static int enqueue_decode(eet_layer* L, const void* tokens, void* out, void* kv_
             f1.row_stats_in = o.row_stats_out; f1.row_stats_groups = groups; f1.row_stats_cols = cols;
         }
     }
-    cut_projection(L, o, L->lay.buf_f, L->lay.cut_room_f());
+    cut_projection(L, o, L->lay.buf_f);
     const bool ln2_in_finish = o.k_ranges > 1;            // more than 16 sequences: the launch that adds up the K ranges normalises and advances n_b
     if (ln2_in_finish) {
         o.fin_gamma = (const half_t*)L->w.ln2_g; o.fin_beta = (const half_t*)L->w.ln2_b; o.fin_y = bufB; o.fin_eps = c.ln_eps;
@@ -480,7 +482,7 @@ static int enqueue_decode(eet_layer* L, const void* tokens, void* out, void* kv_
     GemmArgs f2{};
     f2.x = bufF; f2.w = (const half_t*)L->w.w_fc2; f2.bias = (const half_t*)L->w.b_fc2; f2.y = static_cast<half_t*>(out);
     f2.M = B; f2.N = H; f2.K = F; f2.res = bufY; f2.read_once = once;
-    cut_projection(L, f2, L->lay.buf_a, L->lay.cut_room_ab());
+    cut_projection(L, f2, L->lay.cut);
     if (prefetch && next != nullptr) {                    // during FFN-2 (128 workgroups): the QKV matrix and the K/V rows of the step that follows
         f2.pf.lin[0] = next->w.w_qkv; f2.pf.lin_lines[0] = lines((size_t)3 * H * H * 2);
         f2.pf.k_cache = static_cast<const half_t*>(next_kv);

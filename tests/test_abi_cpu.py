@@ -51,6 +51,24 @@ def test_size_queries(eet):
     assert eet.eet_kv_cache_bytes(eet.make_config(0, 1, 256, 1, 8, 8)) == 0
 
 
+@pytest.mark.parametrize("hidden,heads,batch,prompt", [(1024, 16, 8, 128), (1024, 16, 8, 64), (4096, 32, 48, 1), (2048, 16, 8, 64), (4096, 32, 128, 1),
+                                                       (5120, 40, 17, 1), (1024, 16, 8, 1024), (768, 12, 4, 64), (12288, 96, 16, 64)])
+def test_workspace_of_few_prompt_rows(eet, hidden, heads, batch, prompt):
+    """Few prompt rows: the fp32 sums of a projection cut along K may not fit the idle activation buffers.  What the workspace
+    holds for them beside the buffers is what is missing, and at most 256 tiles of 64 columns."""
+    cfg = eet.make_config(hidden, heads, 4 * hidden, batch, prompt, 1024)
+    T = batch * prompt
+    plain = 2 * T * (7 * hidden + 64)
+    extra = eet.eet_workspace_bytes(cfg) - plain
+    # lengths, row map, decode partials and row statistics: as in test_size_queries under 1 MB
+    sums = 256 * 64 * 4 * (32 if T <= 32 else 64 if T <= 64 else 128)
+    held = 2 * 2 * T * hidden                                 # buf_a and buf_b: one range of T rows
+    assert 0 <= extra <= max(0, sums - held) + (1 << 20)
+    # the paper's own bound from about a thousand rows on
+    bound = 2 * (orc.activation_cache_elements(batch, hidden, prompt) + orc.buffer_elements(batch, prompt, hidden, heads))
+    assert plain + extra <= bound or T < 1024
+
+
 def _fake_layer(eet, cfg):
     w = eet.LayerWeights(*[0x10000 + 0x100 * i for i in range(12)])
     h = C.c_void_p()

@@ -40,15 +40,15 @@ def first_difference(a: torch.Tensor, b: torch.Tensor):
 
 def workspace_piece(w, max_batch, offset):
     """Name of the workspace piece a byte offset falls in (the carve-up of csrc/eet_api.hip: lengths, prefix sums, row
-    map, then the [T, H] buffers A, B, Y, the [T, F] buffer, the decode partials, and for a stack the two activation
-    buffers)."""
+    map, then the [T, F] buffer, the [T, H] buffers A, B, Y, the decode partials, and for a stack the two activation
+    buffers; the capacities here leave no room of its own between F and A for the sums of a cut projection)."""
     al = lambda v: (v + 255) // 256 * 256
     T, H, F = max_batch * w.padded_len, w.hidden, w.ffn
     pieces = [("cache lengths", al(4 * 128)), ("prefix sums", al(4 * 129)), ("row map", al(4 * T)),
+              ("buffer F: first feed-forward projection + GELU", al(2 * T * (F + 64))),   # room for rows 128 bytes further apart
               ("buffer A: LayerNorm-1 rows, then the attention context", al(2 * T * H)),
               ("buffer B: Q rows, then LayerNorm-2 rows", al(2 * T * H)),
-              ("buffer Y: output projection + residual", al(2 * T * H)),
-              ("buffer F: first feed-forward projection + GELU", al(2 * T * (F + 64)))]   # room for rows 128 bytes further apart
+              ("buffer Y: output projection + residual", al(2 * T * H))]
     lo = 0
     for name, size in pieces:
         if offset < lo + size:
