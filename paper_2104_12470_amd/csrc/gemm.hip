@@ -1555,58 +1555,13 @@ static bool try_stream(const GemmArgs& a, Epilogue epi, hipStream_t s) {
 }
 
 // --------------------------------------------------------------------------------------------
-// 17 to 1024 rows: a weight stream through the tile kernel
+// 17 to 1024 rows: a weight stream through the tile kernel (which calls: tile_rules.hpp)
 // --------------------------------------------------------------------------------------------
-// A decode step of 17 to 128 sequences (or as short a prompt) reads every weight once, and what bounds it is how fast the
-// weights come in.  The general tile choice below makes that slow in two ways: a narrow output with a long K has only N/64
-// workgroups (48 x 4096 x 16384: 64 of them, 71 us, 1.9 TB/s), and 128-row tiles pull twice the activations through L2 that
-// 33 to 64 rows need.  Here one row tile of 32, 64 or 128 rows covers all rows, the columns come in tiles of 64, four waves
-// of a workgroup (two or four K groups) keep two K steps each in flight, and a bias + residual projection whose columns leave
-// CUs idle has K cut into 2 to 8 ranges, whose fp32 sums finish_rows adds up.  Measured on cold weights, before -> now, us
-// (cut ones with finish_rows): 48 rows: 4096 x 16384 70.8 -> 29.0, 4096 x 4096 21.0 -> 13.2 (and the LayerNorm launch behind it
-// gone), 12288 x 4096 27.9 -> 23.9, 16384 x 4096 32.8 -> 25.1, 49152 x 12288 251 -> 212, 12288 x 49152 280 -> 248, 8192 x
-// 32768 166 -> 102; 24 rows: 16384 x 4096 32.4 -> 23.4; 128 rows: 4096 x 16384 73.5 -> 36.2, 36864 x 12288 267 -> 235.
-// More rows (129 to 1024) take it only for the cut, and with the plain K walk and plain loads, since several row tiles then
-// share the weights: 200 x 2048 x 8192 33.8 -> 20.6, 512 x 2048 x 8192 47.5 -> 32.4, 512 x 1024 x 4096 19.5 -> 16.7.
-constexpr int kRowsStreamMaxM = 128;
-static int rows_tile(int M) { return M <= 32 ? 32 : M <= 64 ? 64 : 128; }
-// K ranges that fill the CUs without a second round, up to 8; at least 512 columns each (below that a range is all start-up: 32 x
-// 1024 x 1024 gains nothing in two).
-static int rows_ranges(int M, int N, int K) {
-    const int tiles = (M + rows_tile(M) - 1) / rows_tile(M) * ((N + 63) / 64);
-    int s = 256 / tiles;
-    s = s < K / 512 ? s : K / 512;
-    return s < 1 ? 1 : s > 8 ? 8 : s;
-}
-// Weights below 18 MB (24 MB for at most 32 rows) stay with the row slices (48 x 2048 x 2048 7.9 us in slices, 9.1 here; 17 x 1536 x
-// 6144 8.6 and 10.5; but 48 x 1536 x 6144 13.3 and 11.2, 64 x 3072 x 3072 17.9 and 11.9).  At most 32 rows want no cut in eight
-// (32 x 2048 x 8192 11.7 against 13.4), more than 64 rows without a cut a long K (96 x 6144 x 2048 12.1 against 16.0).
-static bool rows_stream_pays(int M, int N, int K, int ranges) {
-    if (M <= 16 || K % 128 != 0 || N % 64 != 0) return false;
-    // a cut that still leaves half of the CUs idle: 20 to 31 x 1984 x 7936 in two ranges (62 workgroups) took half again as long as the slices
-    if (ranges > 1 && (M + rows_tile(M) - 1) / rows_tile(M) * ((N + 63) / 64) * ranges < 128) return false;
-    const int64_t weights = (int64_t)N * K;
-    if (M > kRowsStreamMaxM) return M <= kGemmCutMaxM && ranges > 1 && K >= 4096 && weights >= ((int64_t)4 << 20);
-    if (weights < ((int64_t)(M <= 32 ? 12 : 9) << 20)) return false;
-    if (M <= 32 && ranges >= 8) return false;
-    return ranges > 1 || K >= (M <= 64 ? 2048 : 4096);
-}
-// Up to 64 rows over a wide output with a short K (the vocabulary): a workgroup is mostly start-up and epilogue, so two per
-// CU, of 64 x 128 with three stages (47 x 50304 x 1024: 22.1 us, as a rows stream 30.0, 128 x 128 tiles 25.8; 24 x 50304 x 256
-// 8.0, 16.9 and 9.4; even at K = 2048: 47.9 and 49.6).  More rows than 64: 128 x 128 tiles (68 x 50304 x 1024 24.7, 64 x 128 29.5).
-static bool short_k_wide(const GemmArgs& a, Epilogue epi) {
-    return epi == EPI_BIAS && a.M > 16 && a.M <= 64 && a.K < 2048 && a.N > 256 * 128 && a.ln_gamma == nullptr && a.pf.blocks == 0 && a.bump_lens == nullptr;
-}
-int gemm_k_ranges(int M, int N, int K) {
-    const int s = N <= kFinishRowsMaxWidth ? rows_ranges(M, N, K) : 1;
-    return s > 1 && rows_stream_pays(M, N, K, s) ? s : 1;
-}
+// no LayerNorm, prefetch or length update rides on the call (the weight-streaming kernels' business)
+static bool is_plain(const GemmArgs& a) { return a.ln_gamma == nullptr && a.pf.blocks == 0 && a.bump_lens == nullptr; }
 static bool rows_stream(const GemmArgs& a, Epilogue epi) {
     if (a.k_ranges > 1 && epi == EPI_BIAS_RES) return true;          // the caller asked gemm_k_ranges
-    return a.M <= kRowsStreamMaxM && rows_stream_pays(a.M, a.N, a.K, 1) && (a.ln_gamma == nullptr && a.pf.blocks == 0 && a.bump_lens == nullptr) &&
-           // without the cut a narrow output stays where it was (48 x 4096 x 4096 20.3 us here, 21.0 there; 17 x 6144 x 2048 10.0
-           // and 11.5)
-           (a.N + 63) / 64 >= 96;
+    return is_plain(a) && rows_stream_uncut(a.M, a.N, a.K);
 }
 
 template <int BM, int WGM, int KS, bool NTW, bool ROT, int EPI>
@@ -1639,28 +1594,6 @@ static hipError_t launch_rows(const GemmArgs& a, Epilogue epi, hipStream_t s) {
     return a.k_ranges > 1 && e == hipSuccess ? launch_finish_rows(a, s) : e;
 }
 
-// Row slices of the weight-streaming kernels against the tile kernels for a problem of 17 to 512 rows, from two cost
-// estimates in microseconds whose constants are measured (projections of 2 to 400 MB, 17 to 1024 rows).  Slices: the
-// first reads the weights at about 4 TB/s, every further one reads them again out of L2 or the memory-side cache at about
-// 7.5 TB/s.  Tiles: the time does not depend on the row count while all workgroups are resident at once; it is the larger
-// of the weights at about 3 TB/s and of the K loop (0.33 us per step of 64 columns, 0.23 us where two groups of waves
-// share it; longer in proportion once the tiles no longer fit the chip at once).  Wide outputs with a short K go
-// to the tiles from about 33 rows on, narrow outputs with a long K (the output and second feed-forward projections)
-// stay with the slices for up to a few hundred rows.
-static bool slices_beat_tiles(const GemmArgs& a) {
-    const int slices = (a.M + 15) / 16;
-    if (slices > 32) return false;
-    const double w_mb = (double)a.N * a.K * 2e-6;
-    const bool streams = a.K % 256 == 0 && a.N % 32 == 0;        // else the slower general kernel: 2.5 and 4.5 TB/s
-    const double again = w_mb / (streams ? 7.5 : 4.5);
-    const double est_slices = 2.0 + w_mb / (streams ? 4.0 : 2.5) + (slices - 1) * (again > 0.1 ? again : 0.1);
-    const double wg64 = (double)((a.M + 63) / 64) * ((a.N + 63) / 64);
-    const bool k_split = a.K % 128 == 0 && a.K >= 1024 && wg64 <= 256.0;     // two groups of waves share the K loop
-    const double k_loop = (a.K / 64) * (k_split ? 0.23 : 0.33) * (wg64 > 768.0 ? wg64 / 768.0 : 1.0);
-    const double est_tiles = 3.0 + (w_mb / 3.0 > k_loop ? w_mb / 3.0 : k_loop);
-    return est_slices < est_tiles;
-}
-
 bool gemm_hands_row_stats(const GemmArgs& producer, const GemmArgs& consumer, Epilogue consumer_epi, int& groups, int& cols) {
     GemmArgs p = producer, c = consumer;
     p.row_stats_out = reinterpret_cast<float*>(16);              // any non-null value: only asked, never launched
@@ -1690,7 +1623,7 @@ bool gemm_merges_attention_ranges(const GemmArgs& a) {
 static bool is_strided(const GemmArgs& a) { return (a.lda != 0 && a.lda != a.K) || (a.ldy != 0 && a.ldy != a.N); }
 static bool goes_to_tile_kernel(const GemmArgs& a) {
     const bool sliced = a.M > 16 && !is_strided(a) && a.res_row_map == nullptr && a.out_row_map == nullptr && a.tok_row_map == nullptr &&
-                        a.ln_gamma == nullptr && a.bump_lens == nullptr && a.pf.blocks == 0 && slices_beat_tiles(a);
+                        is_plain(a) && slices_beat_tiles(a.M, a.N, a.K);
     return a.M > 16 && !sliced;
 }
 bool gemm_takes_row_strides(const GemmArgs& a) { return a.M > 16 && a.x_splits <= 1; }
@@ -1715,69 +1648,6 @@ static GemmArgs rows_from(const GemmArgs& a, Epilogue epi, int m0) {
     return r;
 }
 
-// One workgroup of the large-tile kernels fills a CU, so the tiles run in rounds of 256, and a launch whose last round is
-// part-filled pays for more than that round: 25082 x 12288 x 49152 (18.4 rounds) 26.3 ms, 24832 rows (18.2 rounds) 26.35 ms,
-// 24576 rows (18 rounds) 24.6 ms; 25082 x 36864 x 12288 (55.1 rounds) 19.1 ms, 24576 rows (54 rounds) 18.2 ms.  Where some
-// number of row tiles gives whole rounds and leaves at most 16 row tiles, the launch is cut there and the rest is a launch
-// of its own: small tiles below 150 large tiles' worth of rows (about 0.6 of the large tiles' rate: 506 x 12288 x 49152
-// 0.85 ms), else large tiles again (506 x 36864 x 12288 0.58 ms, 506 x 49152 x 12288 0.63 ms).  Returns the rows of the
-// first part, 0 for no cut.  The whole rounds are also what the tile order that lets the XCDs share operand panels
-// needs (pipe::tile_of_block): 20000 x 12288 x 12288, 14.8 rounds, 4.92 ms as one launch.
-static int rows_in_whole_rounds(const GemmArgs& a, Epilogue epi, int big_tiles) {
-    constexpr int kCUs = 256;
-    if ((epi == EPI_QKV && a.tok_row_map == nullptr) || big_tiles < 2 * kCUs || big_tiles % kCUs == 0) return 0;
-    const int tm = (a.M + 255) / 256, tn = (a.N + 255) / 256;
-    for (int c = tm - 1; c >= 1 && c >= tm - 16; --c) {
-        if ((c * tn) % kCUs != 0) continue;
-        if (a.M - c * 256 <= 16) return 0;                 // the rest would be a decode-sized problem: other kernels, no row strides
-        const int rest = (tm - c) * tn;                   // large tiles' worth of rows left over
-        const double rest_rounds = rest < 150 ? rest / (0.6 * kCUs) : (double)((rest + kCUs - 1) / kCUs);
-        const double rounds_now = (big_tiles + kCUs - 1) / kCUs - c * tn / kCUs + 0.27;   // what the part-filled round costs on top
-        return rest_rounds + 0.1 < rounds_now ? c * 256 : 0;
-    }
-    return 0;
-}
-
-// The tile of a launch of more than 128 rows, by the time its rounds take.  Measured, us, K in thousands (of 1024):
-//   256 x 256, one workgroup per CU                    10 + 21.5 K   per round of up to 256 tiles
-//   128 x 256 (three stages), 192 x 128 (three stages), 128 x 128 (three), 96 x 128 (four), one per CU
-//                                       9 + 12 K, 7 + 9.2 K, 5 + 7.9 K, 4.5 + 6.9 K   for up to 256 tiles (one round only)
-//   192 x 128, 128 x 128, 128 x 64, two per CU         8 + 21.3 K, 6 + 14.5 K, 4.5 + 9 K   per whole round of 512; a last round
-//                                                      that gives every CU at most one takes 0.76, 0.58 (0.8 if it is the
-//                                                      only one), 0.75 of that, a fuller one 0.92
-// So the large tile, the best per flop, gives way where its last round would leave much of the chip idle, to whichever tile
-// fills the CUs once (or twice) with the least on top.  us, 256 x 256 / two per CU (192 x 128, 128 x 128, 128 x 64) / one per CU (its
-// tile): 3054 x 3072 x 1024 31 / 25, 32, 30 / 32; 2140 x 4096 x 1024 34 / 27, 33, 33; 1200 x 16384 x 4096 188 / 173, 190, 225;
-// 2140 x 1024 x 4096 83 / 68, 55, 35 / 29.5 (96 x 128); 1200 x 2048 x 8192 - / -, -, 81 / 54 (96 x 128); 700 x 4096 x 16384 302 / 263,
-// 215, 173 / 112 (96 x 128); 700 x 6144 x 2048 - / -, 32, 38 / 25 (192 x 128); 400 x 12288 x 4096 - / -, 64, 74 / 56.5 (128 x 256);
-// 2500 x 1280 x 5120 - / -, 50, 58 / 47 (128 x 128); and not where it would not: 6758 x 6144 x 2048 149 / 157, 162; 3262 x 12288 x 4096
-// 276 / 306, 315.  All of the one-per-CU tiles run the one-wave-per-SIMD schedule, a tenth ahead of the shared one at every
-// depth (700 x 4096 x 16384, 128 x 128: 141 with the shared schedule and 3, 4 or 5 stages, 130 and 123 with this one and 3 and 4).
-enum TileChoice { kTileSmall, kTile128x64, kTile128Pair, kTile192Pair, kTile96, kTile128, kTile192, kTile128x256, kTile256 };
-static TileChoice choose_tile(int M, int N, int K) {
-    auto tiles = [&](int bm, int bn) { return (double)((M + bm - 1) / bm) * ((N + bn - 1) / bn); };
-    const double k = K / 1024.0;
-    double best = 1e30;
-    TileChoice choice = kTile128x64;
-    auto offer = [&](TileChoice c, double us) {
-        if (us < best) { best = us; choice = c; }
-    };
-    auto pairs = [](double n, double two, double one) {         // n tiles, two per CU, `two` the time of both, `one` the share of one
-        const double whole = (double)(int64_t)(n / 512), rest = n - whole * 512;
-        return two * (whole + (rest == 0 ? 0.0 : rest <= 256 ? one : 0.92));
-    };
-    // (the large tile first and with 3 % in hand: past the first round the others' tails are rougher estimates than its own)
-    offer(kTile256, (double)(int64_t)((tiles(256, 256) + 255) / 256) * (10 + 21.5 * k) / 1.03);
-    offer(kTile192Pair, pairs(tiles(192, 128), 8 + 21.3 * k, 0.76));
-    offer(kTile128Pair, pairs(tiles(128, 128), 6 + 14.5 * k, tiles(128, 128) <= 256 ? 0.8 : 0.58));
-    offer(kTile128x64, pairs(tiles(128, 64), 4.5 + 9 * k, 0.75));
-    if (tiles(128, 256) <= 256) offer(kTile128x256, 9 + 12 * k);
-    if (tiles(192, 128) <= 256) offer(kTile192, 7 + 9.2 * k);
-    if (tiles(128, 128) <= 256) offer(kTile128, 5 + 7.9 * k);
-    if (tiles(96, 128) <= 256) offer(kTile96, 4.5 + 6.9 * k);
-    return choice;
-}
-
 hipError_t launch_gemm(const GemmArgs& a, Epilogue epi, hipStream_t s) {
     if (a.M <= 0) return hipSuccess;
     const bool bad_stride = (a.lda != 0 && (a.lda < a.K || a.lda % 8 != 0)) || (a.ldy != 0 && (a.ldy < a.N || a.ldy % 8 != 0));
@@ -1791,7 +1661,7 @@ hipError_t launch_gemm(const GemmArgs& a, Epilogue epi, hipStream_t s) {
     if (a.k_ranges > 1 && (epi != EPI_BIAS_RES || a.part == nullptr || a.k_ranges != gemm_k_ranges(a.M, a.N, a.K) || (a.ldy != 0 && a.ldy != a.N) || a.ln_gamma != nullptr || a.pf.blocks != 0)) return hipErrorInvalidValue;
     if (a.fin_gamma != nullptr && a.k_ranges <= 1) return hipErrorInvalidValue;
     if (a.M > 16 && rows_stream(a, epi)) return launch_rows(a, epi, s);
-    if (short_k_wide(a, epi)) {
+    if (epi == EPI_BIAS && is_plain(a) && short_k_wide(a.M, a.N, a.K)) {
         const int tn = (a.N + 127) / 128;
         hipLaunchKernelGGL((gemm_mfma_dma64<64, 128, 2, 2, EPI_BIAS, 3, 1, 0>), dim3(tn), dim3(256), 0, s, a, 1, tn);
         return hipGetLastError();
@@ -1808,37 +1678,19 @@ hipError_t launch_gemm(const GemmArgs& a, Epilogue epi, hipStream_t s) {
         else if (a.N >= 32 * 1024) launch_skinny_cfg<2>(a, epi, s);
         else launch_skinny_cfg<1>(a, epi, s);
     } else {
-        const int big_tiles = ((a.M + 255) / 256) * ((a.N + 255) / 256);
-        if (int m_whole = rows_in_whole_rounds(a, epi, big_tiles)) {
-            // whole rounds of large tiles first, then the last few hundred rows as a problem of their own (small tiles)
+        const bool divisible = epi != EPI_QKV || a.tok_row_map != nullptr;       // see rows_from
+        if (const int m_whole = divisible ? rows_in_whole_rounds(a.M, a.N) : 0) {
+            // whole rounds of large tiles first, then the last few hundred rows as a problem of their own
             GemmArgs head = a;
             head.M = m_whole;
             hipError_t e = launch_gemm(head, epi, s);
             if (e != hipSuccess) return e;
             return launch_gemm(rows_from(a, epi, m_whole), epi, s);
         }
-        // Few tiles (short prompts, narrow layers): smaller tiles put more workgroups on the chip; the K loop of each is a chain
-        // of dependent steps, so what counts there is how many run side by side and how far ahead the loads run (rows x K x N,
-        // against two-stage register-staged tiles of the same sizes: 256 x 4096 x 4096 29.9 -> 23.8 us, 2048 x 4096 x 1024 37.6 -> 28.5
-        // us, 768 x 8192 x 2048 69.5 -> 51.9 us, 128 x 1600 x 6400 16.3 -> 11.8 us).  A long K with all tiles resident at one workgroup
-        // per CU: two groups of waves per tile, each with half of the K steps and LDS stages of its own, put twice the loads in
-        // flight (rows x K x N: 128 x 4096 x 4096 23.8 -> 16.5 us, 96 x 16384 x 4096 101.7 -> 67.7 us, 512 x 4096 x 1024 23.3 -> 16.5 us; 1959 x
-        // 4096 x 1024 24.8 against 30.1 with the best of the tiles below; four groups with two stages each were slower than two with
-        // three).
-        const bool k_split = a.K % 128 == 0 && a.K >= 1024;
-        const int wg128 = ((a.M + 127) / 128) * ((a.N + 63) / 64), wg64 = ((a.M + 63) / 64) * ((a.N + 63) / 64);
-        TileChoice choice = kTileSmall;
-        if (wg128 >= 128 && !(k_split && wg128 <= 256)) {
-            const int tiles128 = ((a.M + 127) / 128) * ((a.N + 127) / 128);
-            // at most 128 rows: half of a taller tile would be idle
-            choice = a.M > 128 ? choose_tile(a.M, a.N, a.K) : tiles128 > 256 ? kTile128Pair : tiles128 == 256 ? kTile128 : kTile128x64;
-        }
-        switch (choice) {
-        case kTileSmall:
-            if (k_split && wg64 <= 256) launch_dma64_cfg<2, 1, 64, 64, 3, 2>(a, epi, s);       // (1000 x 1024 x 4096: 25.1 -> 20.1)
-            else if (wg128 >= 128) launch_dma64_cfg<4, 1, 128, 64, 3, 2>(a, epi, s);
-            else launch_dma64_cfg<2, 1, 64, 64, 3>(a, epi, s);
-            break;
+        switch (tile_for(a.M, a.N, a.K)) {
+        case kTile64: launch_dma64_cfg<2, 1, 64, 64, 3>(a, epi, s); break;
+        case kTile64Split: launch_dma64_cfg<2, 1, 64, 64, 3, 2>(a, epi, s); break;
+        case kTile128x64Split: launch_dma64_cfg<4, 1, 128, 64, 3, 2>(a, epi, s); break;
         case kTile128x64: launch_dma64_cfg<4, 1, 128, 64, 3>(a, epi, s); break;
         case kTile192Pair: launch_dma64_cfg<2, 2, 192, 128, 2, 1, 0>(a, epi, s); break;
         // The one-wave-per-SIMD schedule serves two workgroups per CU as well, and better than the shared one (6000 x 768 x 3072 48.5 ->
@@ -1863,7 +1715,7 @@ hipError_t launch_gemm(const GemmArgs& a, Epilogue epi, hipStream_t s) {
             // (that comparison was on 18.4 rounds of tiles.  On whole rounds -- which is what the cut above leaves of such a
             // launch -- the four waves are ahead at this K too: 24576 x 12288 x 49152 24.7 -> 23.7 ms, 4096 rows 3.97 -> 3.82;
             // on part-filled rounds the eight waves stay ahead: 3000 x 4096 x 32768 0.80 against 0.87 ms.)
-            if (a.K >= 32768 && big_tiles % 256 != 0) launch_dma64_cfg<2, 4, 256, 256, 2, 1, 1>(a, epi, s);
+            if (a.K >= 32768 && ((a.M + 255) / 256) * ((a.N + 255) / 256) % 256 != 0) launch_dma64_cfg<2, 4, 256, 256, 2, 1, 1>(a, epi, s);
             else if ((size_t)a.M * a.N * sizeof(half_t) >= kMemorySideCacheBytes) launch_dma64_cfg<2, 2, 256, 256, 2, 1, 2, true>(a, epi, s);
             else launch_dma64_cfg<2, 2, 256, 256, 2, 1, 2>(a, epi, s);
             break;

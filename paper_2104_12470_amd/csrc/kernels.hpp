@@ -3,6 +3,7 @@
 #pragma once
 
 #include "common.hpp"
+#include "tile_rules.hpp"
 
 namespace eet {
 
@@ -125,12 +126,9 @@ bool gemm_takes_row_strides(const GemmArgs& a);
 // true when launch_gemm would give this bias+residual projection to the kernel that can merge the key ranges itself
 bool gemm_merges_attention_ranges(const GemmArgs& a);
 
-// How many ranges the K of a bias + residual projection is worth cutting into (1: none), a function of the sizes alone: the
-// caller that has room for their sums ([ranges][M][N] floats) sets GemmArgs::part and k_ranges, for M up to kGemmCutMaxM.
-constexpr int kGemmCutMaxM = 1024;
-int gemm_k_ranges(int M, int N, int K);
 // Adds up the K ranges a.part of a cut projection (rowops.hip); N a multiple of 8, at most kFinishRowsMaxWidth.
-constexpr int kFinishRowsMaxWidth = 16384;
+// How many ranges the K of a bias + residual projection is worth cutting into is gemm_k_ranges (tile_rules.hpp): the caller
+// that has room for their sums ([ranges][M][N] floats) sets GemmArgs::part and k_ranges, for M up to kGemmCutMaxM.
 hipError_t launch_finish_rows(const GemmArgs& a, hipStream_t s);
 
 // M > 16: MFMA tile kernel.  M <= 16 (decode): weight-streaming kernel.

@@ -13,6 +13,7 @@ import torch
 
 from oracle import eet_oracle as orc
 from paper_2104_12470_amd import workloads as wl
+from tests import tile_shapes
 from tests.gpu_util import MAX_ABS, MEAN_ABS, dev, gate, host
 
 pytestmark = pytest.mark.gpu
@@ -122,6 +123,13 @@ def test_projections_cut_along_k(eet, hidden, heads, ffn, B, S, max_seq):
     summed by the launch that also does the LayerNorm between them and advances the lengths."""
     w = wl.Workload(f"cut{hidden}x{B}", 29, hidden, heads, ffn, 1, B, S, max(1, S // 2), S, 2, max_seq)
     full_parity(eet, w)
+
+
+@pytest.mark.parametrize("w", [w for w, _ in tile_shapes.LAYERS], ids=lambda w: w.name)
+def test_prompts_through_the_one_per_cu_tiles(eet, w):
+    """Prompts whose QKV projection (K and V rows to their cache slots), first feed-forward projection or mapped-row projections
+    take a tile that runs one per CU (which: tests/tile_shapes.py)."""
+    full_parity(eet, w, random_affine=False)
 
 
 @pytest.mark.parametrize("B", [1, 9, 16])

@@ -7,6 +7,7 @@ import torch
 
 from oracle import eet_oracle as orc
 from paper_2104_12470_amd import workloads as wl
+from tests import tile_shapes
 from tests.gpu_util import dev, gate, host
 
 pytestmark = pytest.mark.gpu
@@ -236,10 +237,7 @@ def test_linear_weight_stream_with_wide_workgroups(eet, M, K, N):
     gate(host(y), lin + r.astype(np.float64), f"wide-workgroup stream linear+res {M}x{K}x{N}", OP_MAX, OP_MEAN)
 
 
-@pytest.mark.parametrize("M,K,N", [(17, 2048, 8192), (32, 2176, 6144),        # one tile of 32 rows: four K groups, two where K is no multiple of 256
-                                   (33, 2048, 8256), (64, 2176, 6144),        # one tile of 64 rows
-                                   (20, 64, 33024), (64, 192, 32832),         # a wide output with a short K: 64 x 128 tiles, two per CU
-                                   (65, 4096, 16384), (128, 4224, 16384)])    # one tile of 128 rows
+@pytest.mark.parametrize("M,K,N", [s[:3] for s in tile_shapes.ROWS_STREAM])
 def test_linear_rows_stream(eet, M, K, N):
     """17 to 128 rows over weights large enough to be read as a stream: ragged row tiles, K walks that start and wrap anywhere."""
     x = wl.normal(380, M, (M, K))
@@ -256,13 +254,7 @@ def test_linear_rows_stream(eet, M, K, N):
     gate(host(y), orc.gelu_tanh(lin), f"rows stream linear+gelu {M}x{K}x{N}", OP_MAX, OP_MEAN)
 
 
-@pytest.mark.parametrize("M,K,N", [(3000, 1024, 4160), (4099, 192, 3136), (2049, 4096, 6144),
-                                   (800, 128, 12352), (961, 64, 12352),       # 192 x 128 tiles, two per CU
-                                   (300, 128, 12352),                         # 128 x 128 tiles, two per CU
-                                   (1500, 64, 2112), (1500, 128, 2112),       # one tile per CU: 128 x 64 ...
-                                   (1190, 1088, 2112), (2011, 2112, 1088),    # ... 96 x 128 in four stages
-                                   (2500, 1280, 1344), (1480, 320, 3136),     # ... 128 x 128, 192 x 128 in three stages
-                                   (400, 1088, 12352)])                       # ... 128 x 256 in three stages
+@pytest.mark.parametrize("M,K,N", [s[:3] for s in tile_shapes.LARGE_TILES])
 def test_linear_large_tiles(eet, M, K, N):
     """Shapes that take the larger tiles of the direct-to-LDS tile kernel, with ragged row and column tails."""
     x = wl.normal(350, M, (M, K))
@@ -280,11 +272,7 @@ def test_linear_large_tiles(eet, M, K, N):
     gate(host(y), lin + r.astype(np.float64), f"large linear+res {M}x{K}x{N}", OP_MAX, OP_MEAN)
 
 
-@pytest.mark.parametrize("M,K,N,padx,pady", [(3000, 1024, 4160, 64, 72),     # 256x256 tiles, four waves
-                                              (300, 512, 640, 8, 64),          # the small tiles
-                                              (2049, 4096, 6144, 64, 0),
-                                              (8492, 256, 4096, 64, 72),       # 544 large tiles: two whole rounds of 8192 rows, then 300 rows on small tiles
-                                              (2648, 256, 16384, 64, 0)])      # 704 large tiles: two whole rounds of 2048 rows, then 600 rows on large tiles again
+@pytest.mark.parametrize("M,K,N,padx,pady", [s[:5] for s in tile_shapes.STRIDED])
 def test_linear_strided(eet, M, K, N, padx, pady):
     """eet_op_linear_strided: x and y are column slices of wider buffers (the layout the layer gives its feed-forward
     rows); the columns between the rows are neither read into the result nor written."""

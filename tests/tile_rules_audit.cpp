@@ -1,0 +1,56 @@
+// Host-side questions to the dispatch rules of the projections (paper_2104_12470_amd/csrc/tile_rules.hpp, plain C++): the very
+// functions that launch_gemm and the layer's workspace compile.  tests/test_tile_rules.py asks.
+//
+// Usage: one question per line of the standard input, one answer per line of the standard output
+//   route M N K       where a dense operator call of M > 16 rows with an activation or a residual goes ("rows 64": the weight
+//                     stream with a tile of 64 rows, "slices", "192x128 x3": tile and LDS stages, "8192 + 128x64 x3": whole rounds
+//                     of large tiles, then the rest)
+//   bias M N K        the same with neither
+//   mapped M N K      the same for a projection whose rows are mapped (a prompt inside a layer), which is never sliced
+//   ranges M N K      K ranges of a bias + residual projection
+#include <cstdio>
+#include <cstring>
+#include <string>
+
+#include "../paper_2104_12470_amd/csrc/tile_rules.hpp"
+
+namespace {
+
+const char* tile_name(eet::TileChoice t) {
+    switch (t) {
+        case eet::kTile64: return "64x64 x3";
+        case eet::kTile64Split: return "64x64 x3, two K groups";
+        case eet::kTile128x64Split: return "128x64 x3, two K groups";
+        case eet::kTile128x64: return "128x64 x3";
+        case eet::kTile128Pair: return "128x128 x2";
+        case eet::kTile192Pair: return "192x128 x2";
+        case eet::kTile96: return "96x128 x4";
+        case eet::kTile128: return "128x128 x3";
+        case eet::kTile192: return "192x128 x3";
+        case eet::kTile128x256: return "128x256 x3";
+        case eet::kTile256: return "256x256 x2";
+    }
+    return "?";
+}
+
+std::string route(int M, int N, int K, bool sliceable) {
+    if (eet::rows_stream_uncut(M, N, K)) return "rows " + std::to_string(M <= 32 && K % 256 != 0 ? 64 : eet::rows_tile(M));
+    if (sliceable && eet::slices_beat_tiles(M, N, K)) return "slices";
+    if (const int head = eet::rows_in_whole_rounds(M, N)) return std::to_string(head) + " + " + route(M - head, N, K, sliceable);
+    return tile_name(eet::tile_for(M, N, K));
+}
+
+}  // namespace
+
+int main() {
+    char what[16];
+    int M, N, K;
+    while (std::scanf("%15s %d %d %d", what, &M, &N, &K) == 4) {
+        if (!std::strcmp(what, "route")) std::printf("%s\n", route(M, N, K, true).c_str());
+        else if (!std::strcmp(what, "bias")) std::printf("%s\n", !eet::rows_stream_uncut(M, N, K) && eet::short_k_wide(M, N, K) ? "64x128 x3" : route(M, N, K, true).c_str());
+        else if (!std::strcmp(what, "mapped")) std::printf("%s\n", route(M, N, K, false).c_str());
+        else if (!std::strcmp(what, "ranges")) std::printf("%d\n", eet::gemm_k_ranges(M, N, K));
+        else return 1;
+    }
+    return 0;
+}
