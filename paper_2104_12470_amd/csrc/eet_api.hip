@@ -58,12 +58,6 @@ struct WorkspaceLayout {
     int splits;
 };
 
-// bytes of the sums of all K ranges of an M x N x K bias + residual projection; 0: not cut
-size_t cut_bytes(int M, int N, int K) {
-    const int ranges = gemm_k_ranges(M, N, K);
-    return ranges > 1 ? (size_t)ranges * M * N * sizeof(float) : 0;
-}
-
 const char* config_problem(const eet_layer_config* c) {
     if (!c) return "config is null";
     if (c->hidden <= 0 || c->heads <= 0 || c->ffn <= 0) return "hidden, heads and ffn must be positive";
@@ -93,11 +87,9 @@ WorkspaceLayout layout_of(const eet_layer_config* c) {
     w.buf_f = off;   off = align_up(off + 2 * T * (F + kFfnRowPad), 256);
     w.cut = off;
     const size_t room_f = w.cut - w.buf_f, room_ab = 2 * align_up(2 * T * H, 256);
-    for (size_t m = 17; m <= (T < (size_t)kGemmCutMaxM ? T : (size_t)kGemmCutMaxM); ++m) {
-        const size_t for_o = cut_bytes((int)m, c->hidden, c->hidden), for_f2 = cut_bytes((int)m, c->hidden, c->ffn);
-        if (for_o > room_f + (off - w.cut)) off = align_up(w.cut + for_o - room_f, 256);
-        if (for_f2 > room_ab + (off - w.cut)) off = align_up(w.cut + for_f2 - room_ab, 256);
-    }
+    const size_t for_o = gemm_cut_bytes_up_to((int64_t)T, c->hidden, c->hidden), for_f2 = gemm_cut_bytes_up_to((int64_t)T, c->hidden, c->ffn);
+    if (for_o > room_f) off = align_up(w.cut + for_o - room_f, 256);
+    if (for_f2 > room_ab + (off - w.cut)) off = align_up(w.cut + for_f2 - room_ab, 256);
     w.buf_a = off;   off = align_up(off + 2 * T * H, 256);
     w.buf_b = off;   off = align_up(off + 2 * T * H, 256);
     w.buf_y = off;   off = align_up(off + 2 * T * H, 256);
@@ -191,8 +183,9 @@ int eet_layer_destroy(eet_layer_t* layer) {
 // Cuts the K of a bias + residual projection of `L` where that pays; `sums`: where in the workspace its sums lie.  The rule and
 // the sizes are those layout_of reserved by.
 static void cut_projection(eet_layer* L, GemmArgs& g, size_t sums) {
-    if (cut_bytes(g.M, g.N, g.K) == 0) return;
-    g.k_ranges = gemm_k_ranges(g.M, g.N, g.K);
+    const int ranges = gemm_k_ranges(g.M, g.N, g.K);
+    if (ranges <= 1) return;
+    g.k_ranges = ranges;
     g.part = reinterpret_cast<float*>(L->ws + sums);
 }
 

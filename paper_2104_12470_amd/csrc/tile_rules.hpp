@@ -49,6 +49,21 @@ inline int gemm_k_ranges(int M, int N, int K) {
     const int s = N <= kFinishRowsMaxWidth ? rows_ranges(M, N, K) : 1;
     return s > 1 && rows_stream_pays(M, N, K, s) ? s : 1;
 }
+// The largest fp32 sums, in bytes, that a cut N x K projection of up to max_rows rows leaves (0: never cut).  The number of ranges
+// depends on the row tiles alone, so the most rows of each number of them are all there is to ask (a walk over every row
+// count made the creation of a layer handle take 17 us instead of 1, and a stack does it for every layer).
+inline int64_t gemm_cut_bytes(int M, int N, int K) {
+    const int ranges = gemm_k_ranges(M, N, K);
+    return ranges > 1 ? (int64_t)ranges * M * N * (int64_t)sizeof(float) : 0;
+}
+inline int64_t gemm_cut_bytes_up_to(int64_t max_rows, int N, int K) {
+    int64_t most = 0;
+    for (int m = 32; ; m = m < 128 ? 2 * m : m + 128) {
+        const int64_t b = gemm_cut_bytes((int)(m < max_rows ? m : max_rows), N, K);
+        if (b > most) most = b;
+        if (m >= max_rows || m >= kGemmCutMaxM) return most;
+    }
+}
 // Without the cut (outputs other than bias + residual, and callers without room for the sums) a narrow output stays where it
 // was (48 x 4096 x 4096 20.3 us here, 21.0 there; 17 x 6144 x 2048 10.0 and 11.5).
 inline bool rows_stream_uncut(int M, int N, int K) {

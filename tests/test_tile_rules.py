@@ -52,3 +52,27 @@ def test_layer_shapes_take_the_kernel_they_are_there_for(ask):
             assert ask([("mapped", *sizes[name])]) == [want], (w.name, name, T)
             seen.add((want, "qkv" if name == "qkv" else "gelu" if name == "ffn1" else "res"))
     assert {("192x128 x3", "qkv"), ("192x128 x3", "res"), ("128x128 x3", "qkv"), ("128x256 x3", "qkv"), ("128x256 x3", "gelu")} <= seen
+
+
+def test_room_for_the_sums_of_cut_projections(ask):
+    """The workspace asks for a dozen row counts; every one up to the capacity is covered."""
+    sizes = [(H, K) for H in (64, 256, 768, 960, 1024, 1600, 1984, 2048, 3072, 4096, 5120, 8192, 12288, 16384) for K in (H, 4 * H, 8192)]
+    got = ask([("sums", M, H, K) for H, K in sizes for M in (1, 16, 17, 31, 32, 33, 48, 64, 65, 100, 128, 129, 255, 256, 257, 640, 1000, 1023, 1024, 1025, 3000)])
+    assert all(a.split()[0] == a.split()[1] for a in got)
+    assert sum(a != "0 0" for a in got) > 100
+
+
+def test_creating_a_handle_costs_microseconds():
+    """Sizing a layer's workspace is a few dozen arithmetic rules: one query stays below the price of a walk over a thousand row
+    counts (17 us where this takes one)."""
+    import time
+
+    from paper_2104_12470_amd import eet
+    cfg = eet.make_config(1024, 16, 4096, 8, 512, 1024)
+    best = 1e9
+    for _ in range(50):
+        t = time.perf_counter()
+        for _ in range(20):
+            eet.eet_workspace_bytes(cfg)
+        best = min(best, (time.perf_counter() - t) / 20)
+    assert best < 8e-6, f"{best * 1e6:.1f} us"

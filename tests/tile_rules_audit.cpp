@@ -8,6 +8,9 @@
 //   bias M N K        the same with neither
 //   mapped M N K      the same for a projection whose rows are mapped (a prompt inside a layer), which is never sliced
 //   ranges M N K      K ranges of a bias + residual projection
+//   sums M N K        bytes that the sums of such a cut projection of up to M rows need at most; then the same from a walk over
+//                     every row count
+#include <cstdint>
 #include <cstdio>
 #include <cstring>
 #include <string>
@@ -50,7 +53,14 @@ int main() {
         else if (!std::strcmp(what, "bias")) std::printf("%s\n", !eet::rows_stream_uncut(M, N, K) && eet::short_k_wide(M, N, K) ? "64x128 x3" : route(M, N, K, true).c_str());
         else if (!std::strcmp(what, "mapped")) std::printf("%s\n", route(M, N, K, false).c_str());
         else if (!std::strcmp(what, "ranges")) std::printf("%d\n", eet::gemm_k_ranges(M, N, K));
-        else return 1;
+        else if (!std::strcmp(what, "sums")) {
+            int64_t most = 0;
+            for (int m = 1; m <= M; ++m) {
+                const int64_t b = eet::gemm_cut_bytes(m, N, K);
+                if (b > most) most = b;
+            }
+            std::printf("%lld %lld\n", (long long)eet::gemm_cut_bytes_up_to(M, N, K), (long long)most);
+        } else return 1;
     }
     return 0;
 }
