@@ -37,10 +37,6 @@ inline bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 
 // Rows of the prefill's feed-forward buffer lie F + kFfnRowPad halfs apart when F >= kFfnPadFrom: rows a
 // multiple of 32 KB apart slow the second feed-forward projection down (25082 x 12288 x 49152: 0.97-1.09 PFLOP/s with
 // rows 96 KB apart, 1.16 with 128 bytes more; no gain at 16384 and below, a small loss at 4096).
-// The operator entry points do not know what else runs between two of their calls: an operand of this size or more
-// (weights of a projection, the K/V capacity of a decode attention) is taken to come from HBM every time and is read with
-// the non-temporal hint; the layer, stack and model entry points decide from what a whole decode step moves.
-constexpr size_t kReadOnceOperandBytes = (size_t)64 << 20;
 constexpr size_t kFfnRowPad = 64;
 constexpr int kFfnPadFrom = 32768;
 
@@ -851,6 +847,7 @@ static int model_head(eet_model* m, const void* hidden, const int32_t* row_map, 
     GemmArgs g{};
     g.x = ln; g.w = (const half_t*)m->w.wte; g.bias = reinterpret_cast<const half_t*>(m->ws + m->zero_bias);
     g.y = (half_t*)logits; g.M = batch; g.N = m->mc.vocab_padded; g.K = c.hidden;
+    g.read_once = batch > 16 && operator_weights_read_once(batch, g.N, g.K);     // a table that no cache keeps until the next call
     EET_LAUNCH(launch_gemm(g, EPI_BIAS, s), "output projection");
     if (next_ids) EET_LAUNCH(launch_argmax((const half_t*)logits, batch, m->mc.vocab, m->mc.vocab_padded, next_ids, s), "greedy choice");
     return EET_OK;
@@ -992,7 +989,7 @@ int eet_op_linear(const void* x, const void* w, const void* bias, const void* re
     GemmArgs g{};
     g.x = (const half_t*)x; g.w = (const half_t*)w; g.bias = (const half_t*)bias; g.y = (half_t*)y;
     g.M = (int)rows; g.N = out; g.K = in; g.res = (const half_t*)residual;
-    g.read_once = (size_t)out * in * sizeof(half_t) >= kReadOnceOperandBytes;
+    g.read_once = operator_weights_read_once(rows, out, in);
     EET_LAUNCH(launch_gemm(g, residual ? EPI_BIAS_RES : (act ? EPI_BIAS_GELU : EPI_BIAS), (hipStream_t)hip_stream), "linear");
     return EET_OK;
 }
@@ -1015,7 +1012,7 @@ int eet_op_linear_strided(const void* x, int64_t ldx, const void* w, const void*
         return fail(EET_ERR_UNSUPPORTED_SHAPE, "eet_op_linear_strided: %lld rows go to the weight-streaming path, which takes dense rows only",
                     (long long)rows);
     g.lda = (int)ldx; g.ldy = (int)ldy;
-    g.read_once = (size_t)out * in * sizeof(half_t) >= kReadOnceOperandBytes;
+    g.read_once = operator_weights_read_once(rows, out, in);
     EET_LAUNCH(launch_gemm(g, residual ? EPI_BIAS_RES : (act ? EPI_BIAS_GELU : EPI_BIAS), (hipStream_t)hip_stream), "linear");
     return EET_OK;
 }

@@ -1561,7 +1561,7 @@ static bool try_stream(const GemmArgs& a, Epilogue epi, hipStream_t s) {
 static bool is_plain(const GemmArgs& a) { return a.ln_gamma == nullptr && a.pf.blocks == 0 && a.bump_lens == nullptr; }
 static bool rows_stream(const GemmArgs& a, Epilogue epi) {
     if (a.k_ranges > 1 && epi == EPI_BIAS_RES) return true;          // the caller asked gemm_k_ranges
-    return is_plain(a) && rows_stream_uncut(a.M, a.N, a.K);
+    return is_plain(a) && rows_stream_uncut(a.M, a.N, a.K, a.read_once != 0);
 }
 
 template <int BM, int WGM, int KS, bool NTW, bool ROT, int EPI>

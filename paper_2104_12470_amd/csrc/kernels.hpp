@@ -100,7 +100,7 @@ struct GemmArgs {
     float* row_stats_out;
     const float* row_stats_in;
     int row_stats_groups, row_stats_cols;
-    // gemm_stream only: 1 = the weights are read with the non-temporal hint (common.hpp: load_once).  Right when nothing
+    // gemm_stream and the weight stream of 17 to 128 rows: 1 = the weights are read with the non-temporal hint (common.hpp: load_once).  Right when nothing
     // could keep them cached until their next use anyway (a decode step that moves more than the memory-side cache holds);
     // wrong for a layer small enough to live in that cache from step to step, which the hint would keep out of it.
     int read_once;
@@ -115,9 +115,6 @@ struct GemmArgs {
     half_t* fin_y;
     float fin_eps;
 };
-// the memory-side cache of the part: what a decode step must exceed, in bytes moved between two uses of an operand, before
-// its read-once operands are loaded with the non-temporal hint
-constexpr size_t kMemorySideCacheBytes = (size_t)256 << 20;
 // For a bias+residual projection that launch_gemm would give to gemm_stream and that then can leave row statistics for
 // `consumer` (which gemm_stream must take too): the layout of row_stats_out (workgroups, columns per workgroup); else false.
 bool gemm_hands_row_stats(const GemmArgs& producer, const GemmArgs& consumer, Epilogue consumer_epi, int& groups, int& cols);

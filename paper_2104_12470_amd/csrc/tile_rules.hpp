@@ -3,6 +3,7 @@
 // them on the host, so that a test that names a tile can be held to it.
 #pragma once
 
+#include <cstddef>
 #include <cstdint>
 
 namespace eet {
@@ -64,10 +65,34 @@ inline int64_t gemm_cut_bytes_up_to(int64_t max_rows, int N, int K) {
         if (m >= max_rows || m >= kGemmCutMaxM) return most;
     }
 }
-// Without the cut (outputs other than bias + residual, and callers without room for the sums) a narrow output stays where it
-// was (48 x 4096 x 4096 20.3 us here, 21.0 there; 17 x 6144 x 2048 10.0 and 11.5).
-inline bool rows_stream_uncut(int M, int N, int K) {
-    return M <= kRowsStreamMaxM && rows_stream_pays(M, N, K, 1) && (N + 63) / 64 >= 96;
+// Without the cut (outputs other than bias + residual, and callers without room for the sums), by column tiles.  us, the kernels
+// below / as a stream, on weights out of HBM with the non-temporal hint (read_once); then the same on weights that the
+// memory-side cache holds, with plain loads:
+//   at most 32 rows: a narrow output stays where it was (17 x 6144 x 2048, 96 tiles: 11.5 / 10.0; 32 x 4096 x 4096 no better);
+//   33 to 64 rows: 33 x 7168 x 4096, 112 tiles 21.7 / 23.0; 64 x 8192 x 4096, 128 tiles 26.0 / 24.2, 20.9 / 18.9; x 16384, 256 tiles 34.4 / 26.7,
+//     23.4 / 22.3; x 20480, 320 tiles 52.5 / 47.1, 33.5 / 37.6; x 32768, 512 tiles 68.4 / 53.9; 64 x 36864 x 2048 48.1 / 41.3, 29.9 / 33.6;
+//   65 to 128 rows are more arithmetic than the four waves of a workgroup hide behind the loads: cached weights never take it (100
+//     x 8192 x 4096 21.0 / 28.5, x 16384 24.5 / 29.1), others where the CUs are full: 100 x 7168 x 4096, 112 tiles 22.1 / 29.6; x 8192
+//     28.8 / 28.9; x 10240 31.5 / 29.8; 128 x 16384 x 4096 41.9 / 34.9; 100 x 20480 x 8192 110 / 108; with fewer than 96 rows in well filled
+//     rounds only: 68 x 8192 x 8192 47.7 / 52.0; x 16384 66.2 / 59.5; x 18432, 288 tiles 98 / 104; 66 x 36864 x 4096, 576 tiles 82.0 / 89.1;
+//   more than 768 tiles (a vocabulary) fill two 128 x 128 tiles per CU: 100 x 49152 x 4096 107 / 103, x 50304 109 / 121, x 65536 x 8192 209 /
+//     242; 52 x 50304 x 7552, 786 tiles 155 / 171; 64 x 65536 x 4096 135 / 101; 24 x 50304 x 2048 plain 52.5 / 50.5, 33.1 / 40.8.
+// (17 to 32 rows run in the 64-row tile where K is no multiple of 256: 26 x 19968 x 4992 plain 39.6 / 45.6, as 33 to 64 rows do.)
+inline bool rows_stream_uncut(int M, int N, int K, bool read_once) {
+    if (M > kRowsStreamMaxM || !rows_stream_pays(M, N, K, 1)) return false;
+    const int tiles = (N + 63) / 64, rounds = (tiles + 255) / 256;
+    if (M <= 32 && K % 256 == 0) return tiles >= 96 && (read_once || tiles <= 768);
+    if (M <= 64) return tiles >= (M <= 32 ? 96 : 128) && (read_once ? tiles <= 768 || rounds * 208 <= tiles : tiles <= 256);
+    return read_once && tiles >= 128 && tiles <= 768 && (M >= 96 || rounds * 208 <= tiles);
+}
+// The operator entry points do not know what else runs between two of their calls.  Up to 16 rows weights of this size or more
+// are taken to come from HBM every time and are read with the non-temporal hint.  Calls of more rows ask more of a second read: where
+// the memory-side cache can hold the weights they are read with plain loads, which costs a caller whose weights do come from HBM
+// 3 to 9 % (64 x 16384 x 4096 26.7 -> 29.3 us, 34.4 without the stream) and spares the others 10 to 35 % (25.1 -> 22.3).
+constexpr size_t kReadOnceOperandBytes = (size_t)64 << 20;
+constexpr size_t kMemorySideCacheBytes = (size_t)256 << 20;   // of the part
+inline bool operator_weights_read_once(int64_t M, int N, int K) {
+    return (size_t)N * K * 2 >= (M <= 16 ? kReadOnceOperandBytes : kMemorySideCacheBytes);
 }
 // Up to 64 rows over a wide output with a short K (the vocabulary): a workgroup is mostly start-up and epilogue, so two per
 // CU, of 64 x 128 with three stages (47 x 50304 x 1024: 22.1 us, as a rows stream 30.0, 128 x 128 tiles 25.8; 24 x 50304 x 256

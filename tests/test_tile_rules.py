@@ -54,6 +54,21 @@ def test_layer_shapes_take_the_kernel_they_are_there_for(ask):
     assert {("192x128 x3", "qkv"), ("192x128 x3", "res"), ("128x128 x3", "qkv"), ("128x256 x3", "qkv"), ("128x256 x3", "gelu")} <= seen
 
 
+def test_the_weight_stream_takes_no_call_that_it_slows_down(ask):
+    """17 to 128 rows without a cut, shapes measured slower as a stream of weights (by 4 to 60 %) than on the kernels they have
+    otherwise: an output too narrow to fill the CUs, cached weights under 65 rows and more or in a part-filled second round, a
+    vocabulary.  And shapes that it serves better stay with it."""
+    slower = [("route", M, N, K) for M, N, K in ((75, 6144, 6144), (109, 7808, 7808), (105, 7936, 7936), (110, 7872, 31488), (68, 8192, 8192), (68, 18432, 8192),
+                                                 (33, 7168, 4096), (92, 16704, 6272), (102, 13440, 4480), (64, 20480, 2048), (40, 20480, 4096), (64, 36864, 2048),
+                                                 (26, 19968, 4992), (24, 50304, 2048), (64, 50304, 2432), (52, 50304, 7552), (100, 50304, 4096), (128, 65536, 8192))]
+    slower += [("mapped", 100, 12288, 4096), ("mapped", 128, 16384, 4096), ("mapped_once", 66, 36864, 4096)]
+    assert not any(r.startswith("rows") for r in ask(slower)), dict(zip(slower, ask(slower)))
+    better = [("route", M, N, K) for M, N, K in ((20, 6912, 2304), (32, 20480, 4096), (48, 12288, 4096), (64, 16384, 4096), (64, 49152, 12288), (64, 65536, 4096), (28, 50304, 4096),
+                                                 (100, 40960, 8192), (128, 36864, 12288))]
+    better += [("mapped_once", 100, 12288, 4096), ("mapped_once", 128, 16384, 4096), ("mapped_once", 68, 16384, 4096), ("mapped", 48, 12288, 4096)]
+    assert all(r.startswith("rows") for r in ask(better)), dict(zip(better, ask(better)))
+
+
 def test_room_for_the_sums_of_cut_projections(ask):
     """The workspace asks for a dozen row counts; every one up to the capacity is covered."""
     sizes = [(H, K) for H in (64, 256, 768, 960, 1024, 1600, 1984, 2048, 3072, 4096, 5120, 8192, 12288, 16384) for K in (H, 4 * H, 8192)]

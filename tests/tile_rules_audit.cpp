@@ -7,6 +7,7 @@
 //                     of large tiles, then the rest)
 //   bias M N K        the same with neither
 //   mapped M N K      the same for a projection whose rows are mapped (a prompt inside a layer), which is never sliced
+//   mapped_once M N K and whose weights come from HBM every time
 //   ranges M N K      K ranges of a bias + residual projection
 //   sums M N K        bytes that the sums of such a cut projection of up to M rows need at most; then the same from a walk over
 //                     every row count
@@ -36,10 +37,10 @@ const char* tile_name(eet::TileChoice t) {
     return "?";
 }
 
-std::string route(int M, int N, int K, bool sliceable) {
-    if (eet::rows_stream_uncut(M, N, K)) return "rows " + std::to_string(M <= 32 && K % 256 != 0 ? 64 : eet::rows_tile(M));
+std::string route(int M, int N, int K, bool sliceable, bool once) {
+    if (eet::rows_stream_uncut(M, N, K, once)) return "rows " + std::to_string(M <= 32 && K % 256 != 0 ? 64 : eet::rows_tile(M));
     if (sliceable && eet::slices_beat_tiles(M, N, K)) return "slices";
-    if (const int head = eet::rows_in_whole_rounds(M, N)) return std::to_string(head) + " + " + route(M - head, N, K, sliceable);
+    if (const int head = eet::rows_in_whole_rounds(M, N)) return std::to_string(head) + " + " + route(M - head, N, K, sliceable, once);
     return tile_name(eet::tile_for(M, N, K));
 }
 
@@ -49,9 +50,13 @@ int main() {
     char what[16];
     int M, N, K;
     while (std::scanf("%15s %d %d %d", what, &M, &N, &K) == 4) {
-        if (!std::strcmp(what, "route")) std::printf("%s\n", route(M, N, K, true).c_str());
-        else if (!std::strcmp(what, "bias")) std::printf("%s\n", !eet::rows_stream_uncut(M, N, K) && eet::short_k_wide(M, N, K) ? "64x128 x3" : route(M, N, K, true).c_str());
-        else if (!std::strcmp(what, "mapped")) std::printf("%s\n", route(M, N, K, false).c_str());
+        if (!std::strcmp(what, "route")) std::printf("%s\n", route(M, N, K, true, eet::operator_weights_read_once(M, N, K)).c_str());
+        else if (!std::strcmp(what, "bias")) {
+            const bool once = eet::operator_weights_read_once(M, N, K), stream = eet::rows_stream_uncut(M, N, K, once);
+            std::printf("%s\n", !stream && eet::short_k_wide(M, N, K) ? "64x128 x3" : route(M, N, K, true, once).c_str());
+        }
+        else if (!std::strcmp(what, "mapped")) std::printf("%s\n", route(M, N, K, false, false).c_str());
+        else if (!std::strcmp(what, "mapped_once")) std::printf("%s\n", route(M, N, K, false, true).c_str());
         else if (!std::strcmp(what, "ranges")) std::printf("%d\n", eet::gemm_k_ranges(M, N, K));
         else if (!std::strcmp(what, "sums")) {
             int64_t most = 0;

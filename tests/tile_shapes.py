@@ -19,9 +19,11 @@ LARGE_TILES = [
 # operator calls without activation and residual, then with GELU
 ROWS_STREAM = [
     (17, 2048, 8192, "rows 32", "rows 32"), (32, 2176, 6144, "rows 64", "rows 64"),            # four K groups, two where K is no multiple of 256
-    (33, 2048, 8256, "rows 64", "rows 64"), (64, 2176, 6144, "rows 64", "rows 64"),
+    (33, 2048, 8256, "rows 64", "rows 64"), (64, 2176, 8192, "rows 64", "rows 64"),
+    (64, 2176, 6144, "64x64 x3, two K groups", "64x64 x3, two K groups"),
     (20, 64, 33024, "64x128 x3", "128x128 x2"), (64, 192, 32832, "64x128 x3", "128x128 x2"),   # a wide output with a short K
-    (65, 4096, 16384, "rows 128", "rows 128"), (128, 4224, 16384, "rows 128", "rows 128"),
+    (97, 8192, 16448, "rows 128", "rows 128"),                                                 # weights no cache holds
+    (65, 4096, 16384, "128x64 x3, two K groups", "128x64 x3, two K groups"), (128, 4224, 16384, "128x64 x3, two K groups", "128x64 x3, two K groups"),
 ]
 
 # (M, K, N, halfs between rows of x and y beyond K and N) of strided operator calls
