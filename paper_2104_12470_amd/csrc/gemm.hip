@@ -1693,13 +1693,8 @@ hipError_t launch_gemm(const GemmArgs& a, Epilogue epi, hipStream_t s) {
         case kTile128x64Split: launch_dma64_cfg<4, 1, 128, 64, 3, 2>(a, epi, s); break;
         case kTile128x64: launch_dma64_cfg<4, 1, 128, 64, 3>(a, epi, s); break;
         case kTile192Pair: launch_dma64_cfg<2, 2, 192, 128, 2, 1, 0>(a, epi, s); break;
-        // The one-wave-per-SIMD schedule serves two workgroups per CU as well, and better than the shared one (6000 x 768 x 3072 48.5 ->
-        // 45.3 us, 1200 x 4096 x 16384 238 -> 221, 3054 x 3072 x 1024 32.7 -> 31.0), but for the wide outputs with a short K that few rows
-        // come here with (68 x 50304 x 256 11.2 us against 10.5, x 1280 34.6 against 33.3)
-        case kTile128Pair:
-            if (a.M <= 128) launch_dma64_cfg<2, 2, 128, 128>(a, epi, s);
-            else launch_dma64_cfg<2, 2, 128, 128, 2, 1, 2>(a, epi, s);
-            break;
+        case kTile128PairShared: launch_dma64_cfg<2, 2, 128, 128>(a, epi, s); break;
+        case kTile128Pair: launch_dma64_cfg<2, 2, 128, 128, 2, 1, 2>(a, epi, s); break;
         case kTile96: launch_dma64_cfg<2, 2, 96, 128, 4, 1, 2>(a, epi, s); break;
         case kTile128: launch_dma64_cfg<2, 2, 128, 128, 3, 1, 2>(a, epi, s); break;
         case kTile192: launch_dma64_cfg<2, 2, 192, 128, 3, 1, 2>(a, epi, s); break;

@@ -161,7 +161,7 @@ inline int rows_in_whole_rounds(int M, int N) {
 // 2500 x 1280 x 5120 - / -, 50, 58 / 47 (128 x 128); and not where it would not: 6758 x 6144 x 2048 149 / 157, 162; 3262 x 12288 x 4096
 // 276 / 306, 315.  All of the one-per-CU tiles run the one-wave-per-SIMD schedule, a tenth ahead of the shared one at every
 // depth (700 x 4096 x 16384, 128 x 128: 141 with the shared schedule and 3, 4 or 5 stages, 130 and 123 with this one and 3 and 4).
-enum TileChoice { kTile64, kTile64Split, kTile128x64Split, kTile128x64, kTile128Pair, kTile192Pair, kTile96, kTile128, kTile192, kTile128x256, kTile256 };
+enum TileChoice { kTile64, kTile64Split, kTile128x64Split, kTile128x64, kTile128PairShared, kTile128Pair, kTile192Pair, kTile96, kTile128, kTile192, kTile128x256, kTile256 };
 inline TileChoice choose_tile(int M, int N, int K) {
     auto tiles = [&](int bm, int bn) { return (double)((M + bm - 1) / bm) * ((N + bn - 1) / bn); };
     const double k = K / 1024.0;
@@ -201,10 +201,17 @@ inline TileChoice tile_for(int M, int N, int K) {
         if (k_split && wg64 <= 256) return kTile64Split;              // (1000 x 1024 x 4096: 25.1 -> 20.1)
         return wg128 >= 128 ? kTile128x64Split : kTile64;
     }
-    if (M > 128) return choose_tile(M, N, K);
+    // The one-wave-per-SIMD schedule serves two 128 x 128 workgroups per CU better than the one the two-stage kernels share (6000 x 768 x
+    // 3072 48.5 -> 45.3 us, 1200 x 4096 x 16384 238 -> 221, 3054 x 3072 x 1024 32.7 -> 31.0, 5007 x 960 x 832 16.4 -> 15.7), but for a short K (9831 x
+    // 576 x 320 10.5 -> 11.2 us, 4120 x 1728 x 192 9.7 -> 10.1; at 576 14.47 -> 14.42 and 13.7 -> 14.2) and for the wide outputs that at most 128
+    // rows come here with (68 x 50304 x 256 10.5 -> 11.2, x 1280 33.3 -> 34.6).
+    if (M > 128) {
+        const TileChoice choice = choose_tile(M, N, K);
+        return choice == kTile128Pair && K < 512 ? kTile128PairShared : choice;
+    }
     // at most 128 rows: half of a taller tile would be idle
     const int tiles128 = (N + 127) / 128;
-    return tiles128 > 256 ? kTile128Pair : tiles128 == 256 ? kTile128 : kTile128x64;
+    return tiles128 > 256 ? kTile128PairShared : tiles128 == 256 ? kTile128 : kTile128x64;
 }
 
 }  // namespace eet

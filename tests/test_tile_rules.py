@@ -36,7 +36,7 @@ def test_operator_shapes_take_the_kernel_they_are_there_for(ask):
     got = ask([q for q, _ in want])
     assert [(q, r) for (q, _), r in zip(want, got)] == want
     tiles = {r for _, r in want}
-    for name in ("256x256 x2", "192x128 x2", "128x128 x2", "128x64 x3", "96x128 x4", "128x128 x3", "192x128 x3", "128x256 x3", "64x64 x3",
+    for name in ("256x256 x2", "192x128 x2", "128x128 x2", "128x128 x2, shared schedule", "128x64 x3", "96x128 x4", "128x128 x3", "192x128 x3", "128x256 x3", "64x64 x3",
                  "rows 32", "rows 64", "rows 128", "64x128 x3"):
         assert name in tiles, f"no operator test for {name}"
 

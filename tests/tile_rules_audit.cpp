@@ -26,6 +26,7 @@ const char* tile_name(eet::TileChoice t) {
         case eet::kTile64Split: return "64x64 x3, two K groups";
         case eet::kTile128x64Split: return "128x64 x3, two K groups";
         case eet::kTile128x64: return "128x64 x3";
+        case eet::kTile128PairShared: return "128x128 x2, shared schedule";
         case eet::kTile128Pair: return "128x128 x2";
         case eet::kTile192Pair: return "192x128 x2";
         case eet::kTile96: return "96x128 x4";

@@ -8,7 +8,8 @@ from paper_2104_12470_amd import workloads as wl
 LARGE_TILES = [
     (3000, 1024, 4160, "256x256 x2"), (4099, 192, 3136, "256x256 x2"), (2049, 4096, 6144, "256x256 x2"), (961, 64, 12352, "256x256 x2"),
     (800, 128, 12352, "192x128 x2"), (801, 128, 12352, "192x128 x2"), (960, 64, 12352, "192x128 x2"),               # two per CU
-    (300, 128, 12352, "128x128 x2"), (1480, 320, 3136, "128x128 x2"), (400, 1088, 12352, "128x128 x2"),
+    (400, 1088, 12352, "128x128 x2"), (2006, 576, 3136, "128x128 x2"),
+    (300, 128, 12352, "128x128 x2, shared schedule"), (1480, 320, 3136, "128x128 x2, shared schedule"),
     (1500, 64, 2112, "128x64 x3"), (1500, 128, 2112, "128x64 x3"), (2500, 1280, 1344, "128x64 x3"),
     (1190, 1088, 2112, "96x128 x4"), (2011, 2112, 1088, "96x128 x4"),                                                # one per CU
     (2500, 2560, 1344, "128x128 x3"),
@@ -21,7 +22,7 @@ ROWS_STREAM = [
     (17, 2048, 8192, "rows 32", "rows 32"), (32, 2176, 6144, "rows 64", "rows 64"),            # four K groups, two where K is no multiple of 256
     (33, 2048, 8256, "rows 64", "rows 64"), (64, 2176, 8192, "rows 64", "rows 64"),
     (64, 2176, 6144, "64x64 x3, two K groups", "64x64 x3, two K groups"),
-    (20, 64, 33024, "64x128 x3", "128x128 x2"), (64, 192, 32832, "64x128 x3", "128x128 x2"),   # a wide output with a short K
+    (20, 64, 33024, "64x128 x3", "128x128 x2, shared schedule"), (64, 192, 32832, "64x128 x3", "128x128 x2, shared schedule"),   # a wide output with a short K
     (97, 8192, 16448, "rows 128", "rows 128"),                                                 # weights no cache holds
     (65, 4096, 16384, "128x64 x3, two K groups", "128x64 x3, two K groups"), (128, 4224, 16384, "128x64 x3, two K groups", "128x64 x3, two K groups"),
 ]
