@@ -360,12 +360,17 @@ static int enqueue_decode(eet_layer* L, const void* tokens, void* out, void* kv_
     // Small layers are launch-bound in decode: there the two LayerNorms run inside the projections
     // that consume them (each workgroup recomputes the row statistics of the <= 16 token rows).
     // Measured break-even is near 16 MB of FFN-1 weights; larger layers keep the separate row kernel.
-    // (Up to 20 MB where the small-layer kernel takes the rows in eight waves and three column units: hidden 1536, per layer-step, 1
-    // sequence 30.6 -> 26.4 us, 4 33.8 -> 29.5, 16 in a stack 48.6 -> 46.0.  Not at 33 MB, hidden 2048: 39.9 -> 44.4; nothing to gain
-    // with few units: 1024 x 8192 26.6 -> 26.9.)
+    // Above that only where the small-layer kernel takes both consumers with the LayerNorm in front (weights up to 20 MB) and its
+    // waves hold three units of K or more each, which is hidden 1536 with up to 6784 feed-forward columns: of the wider ones it
+    // takes only 2048, which has 25 MB of QKV weights.  Per layer-step, hidden 1536, 1 sequence 32.3 -> 28.2 us, 4 36.0 -> 31.1, 16 in a stack of 24 50.5 -> 46.0; with few
+    // units nothing to gain (1024 x 8192 26.6 -> 26.9), and not at 33 MB (hidden 2048 39.9 -> 44.4).
     const bool small = B <= 16 && (size_t)F * H * sizeof(half_t) <= ((size_t)16 << 20);
-    const size_t widest = (size_t)(F > 3 * H ? F : 3 * H) * H * sizeof(half_t);      // both consumers have to fit that kernel
-    const bool fuse_ln = small || (B <= 16 && H % 512 == 0 && H > 1024 && H <= 2048 && widest <= ((size_t)20 << 20));
+    auto takes_layernorm = [&](int N) {
+        GemmArgs p{};
+        p.M = B; p.N = N; p.K = H; p.ln_gamma = (const half_t*)L->w.ln1_g;
+        return gemm_takes_layernorm(p);
+    };
+    const bool fuse_ln = small || (H > 1024 && takes_layernorm(3 * H) && takes_layernorm(F));
     // What a decode step moves between two uses of the same weight or cache row: every layer's weights and visible K/V
     // once.  More than the memory-side cache holds: nothing survives there until the next step, and the read-once operands
     // are loaded with the non-temporal hint (a tenth faster from HBM).  Less (hidden 2048 on its own: 150 MB): the step
@@ -375,7 +380,10 @@ static int enqueue_decode(eet_layer* L, const void* tokens, void* out, void* kv_
     const size_t step_bytes = (size_t)(L->stack_layers > 0 ? L->stack_layers : 1) *
                               (2 * ((size_t)4 * H * H + (size_t)2 * H * F) + (size_t)4 * H * visible);
     // (not for the small layers whose idle workgroups pull the next launches' operands into that cache: PrefetchArgs below;
-    // the hint on the consumer's loads undoes that: 24 hidden-1024 layers 320.7 -> 330.4 ms for 512 steps)
+    // the hint on the consumer's loads undoes that: 24 hidden-1024 layers 320.7 -> 330.4 ms for 512 steps.  Between 16 and 20 MB the
+    // two together are no worse than either alone, 1 / 8 / 16 sequences, per layer-step: 12 x hidden 1536 both 31.0 / 34.8 / 46.1, prefetch
+    // without the hint 30.9 / 34.8 / 46.5, the hint without prefetch 32.4 / 36.2 / 47.0; 6 layers 29.9 / 32.8 / 45.6, 30.8 / 34.9 / 46.7 and
+    // 29.7 / 33.6 / 44.4)
     const int once = (step_bytes > kMemorySideCacheBytes && !small) ? 1 : 0;
     // The same small layers leave CUs idle in every launch: extra workgroups of the two launches with the fewest
     // workgroups pull operands of later launches towards the memory-side cache (PrefetchArgs).  `next`: the layer
@@ -386,8 +394,9 @@ static int enqueue_decode(eet_layer* L, const void* tokens, void* out, void* kv_
     // workgroups at one per CU.  Moving any share of the K/V rows (a quarter to all) from FFN-2's extra workgroups to
     // the output projection's was slower too (324 -> 361-367 ms).
     constexpr int kPrefetchBlocks = 128;
-    // (of the layers between 16 and 20 MB only those of a stack too large for that cache: 12 x hidden 1536, 8 sequences, 35.8 -> 34.7 us
-    // per layer-step, a single layer 26.4 -> 28.2)
+    // (of the layers between 16 and 20 MB only those of a stack too large for that cache, figures above; a single layer 26.4 -> 28.2;
+    // there the second feed-forward projection is a weight stream, which has no workgroups to spare: the output projection alone
+    // prefetches)
     const bool prefetch = small || (fuse_ln && step_bytes > kMemorySideCacheBytes);
     auto lines = [](size_t bytes) { return (uint32_t)(bytes / 128); };
     const half_t* qkv_in = x;
@@ -425,7 +434,7 @@ static int enqueue_decode(eet_layer* L, const void* tokens, void* out, void* kv_
     EET_LAUNCH(launch_attention_decode(at, s), "decode attention");
     const bool bump_in_gemm = B <= 16;
     if (bump && bump_in_gemm) { o.bump_lens = d_lens; o.bump_count = B; }
-    if (prefetch) {                                       // during the output projection (64 workgroups): the second feed-forward matrix
+    if (prefetch && gemm_takes_prefetch(o)) {             // during the output projection (64 workgroups): the second feed-forward matrix
         o.pf.lin[0] = L->w.w_fc2; o.pf.lin_lines[0] = lines((size_t)H * F * 2);
         o.pf.blocks = kPrefetchBlocks;
     }
@@ -472,7 +481,7 @@ static int enqueue_decode(eet_layer* L, const void* tokens, void* out, void* kv_
     f2.x = bufF; f2.w = (const half_t*)L->w.w_fc2; f2.bias = (const half_t*)L->w.b_fc2; f2.y = static_cast<half_t*>(out);
     f2.M = B; f2.N = H; f2.K = F; f2.res = bufY; f2.read_once = once;
     cut_projection(L, f2, L->lay.cut);
-    if (prefetch && next != nullptr) {                    // during FFN-2 (128 workgroups): the QKV matrix and the K/V rows of the step that follows
+    if (prefetch && next != nullptr && gemm_takes_prefetch(f2)) {   // during FFN-2 (128 workgroups): the QKV matrix and the K/V rows of the step that follows
         f2.pf.lin[0] = next->w.w_qkv; f2.pf.lin_lines[0] = lines((size_t)3 * H * H * 2);
         f2.pf.k_cache = static_cast<const half_t*>(next_kv);
         f2.pf.v_cache = f2.pf.k_cache + (size_t)c.max_batch * H * c.max_seq;

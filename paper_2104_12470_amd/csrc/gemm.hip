@@ -1613,6 +1613,9 @@ bool gemm_hands_row_stats(const GemmArgs& producer, const GemmArgs& consumer, Ep
     return true;
 }
 
+bool gemm_takes_layernorm(const GemmArgs& a) { return a.M >= 1 && a.M <= 16 && a.ln_gamma != nullptr && try_flat(a, EPI_BIAS, nullptr, true); }
+bool gemm_takes_prefetch(const GemmArgs& a) { return a.M >= 1 && a.M <= 16 && try_flat(a, EPI_BIAS_RES, nullptr, true); }
+
 bool gemm_merges_attention_ranges(const GemmArgs& a) {
     return a.M >= 1 && a.M <= 16 && a.ln_gamma == nullptr && a.d >= 8 && a.d % 8 == 0 && a.heads * a.d == a.K &&
            try_flat(a, EPI_BIAS_RES, nullptr, true);

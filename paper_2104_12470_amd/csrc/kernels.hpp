@@ -120,6 +120,10 @@ struct GemmArgs {
 bool gemm_hands_row_stats(const GemmArgs& producer, const GemmArgs& consumer, Epilogue consumer_epi, int& groups, int& cols);
 // true when launch_gemm can serve this problem with row strides (more than 16 rows: an MFMA tile kernel)
 bool gemm_takes_row_strides(const GemmArgs& a);
+// true when launch_gemm would give this projection of at most 16 rows, LayerNorm attached, to the small-layer kernel
+bool gemm_takes_layernorm(const GemmArgs& a);
+// true when it would give this bias+residual projection of at most 16 rows there: no other kernel has workgroups to prefetch with
+bool gemm_takes_prefetch(const GemmArgs& a);
 // true when launch_gemm would give this bias+residual projection to the kernel that can merge the key ranges itself
 bool gemm_merges_attention_ranges(const GemmArgs& a);
 
