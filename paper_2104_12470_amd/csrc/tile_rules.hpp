@@ -127,9 +127,9 @@ inline bool slices_beat_tiles(int M, int N, int K) {
 // part-filled pays for more than that round: 25082 x 12288 x 49152 (18.4 rounds) 26.3 ms, 24832 rows (18.2 rounds) 26.35 ms,
 // 24576 rows (18 rounds) 24.6 ms; 25082 x 36864 x 12288 (55.1 rounds) 19.1 ms, 24576 rows (54 rounds) 18.2 ms.  Where some
 // number of row tiles gives whole rounds and leaves at most 16 row tiles, the launch is cut there and the rest is a launch
-// of its own: small tiles below 150 large tiles' worth of rows (about 0.6 of the large tiles' rate: 506 x 12288 x 49152
-// 0.85 ms), else large tiles again (506 x 36864 x 12288 0.58 ms, 506 x 49152 x 12288 0.63 ms).  Returns the rows of the
-// first part, 0 for no cut.  The whole rounds are also what the tile order that lets the XCDs share operand panels
+// of its own, which takes whatever tile_for gives it (506 x 12288 x 49152: 128 x 256 tiles).  The rest is priced in large tiles, at 0.6
+// of their rate below 150 of them; with choose_tile's estimate of the rest in its place the decision is the same for each of 587
+// thousand drawn sizes of two rounds and more.  Returns the rows of the first part, 0 for no cut.  The whole rounds are also what the tile order that lets the XCDs share operand panels
 // needs (pipe::tile_of_block): 20000 x 12288 x 12288, 14.8 rounds, 4.92 ms as one launch.
 inline int rows_in_whole_rounds(int M, int N) {
     constexpr int kCUs = 256;
@@ -151,8 +151,8 @@ inline int rows_in_whole_rounds(int M, int N) {
 //   128 x 256 (three stages), 192 x 128 (three stages), 128 x 128 (three), 96 x 128 (four), one per CU
 //                                       9 + 12 K, 7 + 9.2 K, 5 + 7.9 K, 4.5 + 6.9 K   for up to 256 tiles (one round only)
 //   192 x 128, 128 x 128, 128 x 64, two per CU         8 + 21.3 K, 6 + 14.5 K, 4.5 + 9 K   per whole round of 512; a last round
-//                                                      that gives every CU at most one takes 0.76, 0.58 (0.8 if it is the
-//                                                      only one), 0.75 of that, a fuller one 0.92
+//                                                      that gives every CU at most one takes 0.76, 0.58, 0.75 of that, a
+//                                                      fuller one 0.92 (128 x 128 in one such round alone: three stages, above)
 // So the large tile, the best per flop, gives way where its last round would leave much of the chip idle, to whichever tile
 // fills the CUs once (or twice) with the least on top.  us, 256 x 256 / two per CU (192 x 128, 128 x 128, 128 x 64) / one per CU (its
 // tile): 3054 x 3072 x 1024 31 / 25, 32, 30 / 32; 2140 x 4096 x 1024 34 / 27, 33, 33; 1200 x 16384 x 4096 188 / 173, 190, 225;
@@ -177,7 +177,7 @@ inline TileChoice choose_tile(int M, int N, int K) {
     // (the large tile first and with 3 % in hand: past the first round the others' tails are rougher estimates than its own)
     offer(kTile256, (double)(int64_t)((tiles(256, 256) + 255) / 256) * (10 + 21.5 * k) / 1.03);
     offer(kTile192Pair, pairs(tiles(192, 128), 8 + 21.3 * k, 0.76));
-    offer(kTile128Pair, pairs(tiles(128, 128), 6 + 14.5 * k, tiles(128, 128) <= 256 ? 0.8 : 0.58));
+    if (tiles(128, 128) > 256) offer(kTile128Pair, pairs(tiles(128, 128), 6 + 14.5 * k, 0.58));
     offer(kTile128x64, pairs(tiles(128, 64), 4.5 + 9 * k, 0.75));
     if (tiles(128, 256) <= 256) offer(kTile128x256, 9 + 12 * k);
     if (tiles(192, 128) <= 256) offer(kTile192, 7 + 9.2 * k);
