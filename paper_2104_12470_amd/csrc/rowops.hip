@@ -94,7 +94,9 @@ __global__ __launch_bounds__(256) void layernorm_cached(const half_t* __restrict
 constexpr int kLayerNormWaveRows = 64;
 // Many narrow rows (width <= 2048, width % 8 == 0; kLayerNormWaveRows and more): one wave per row, four rows per workgroup.  The row sits in NV
 // 16-byte vectors per lane, both reductions are lane exchanges, and there is no barrier and no LDS, so a prompt's few
-// thousand rows are all in flight at once instead of queueing behind 256-thread workgroups that each wait twice.
+// thousand rows are all in flight at once instead of queueing behind 256-thread workgroups that each wait twice.  Scale and
+// shift come with the row at every row count: against loads after the reductions 16000 x 768 10.4 -> 9.2 us, 64000 x 512 22.2 ->
+// 21.1, 32000 x 2048 41.3 -> 39.0, at worst 8000 x 1536 9.65 -> 9.97 (54 sizes, up to 64000 rows).
 //
 // BLOCK_ORDER: the two reductions add in the order of layernorm_cached (one exchange per 512 columns, as one of its waves does,
 // then those sums in turn), so that a row comes out with the same bits as there.  The launch that also sets up a prefill takes
