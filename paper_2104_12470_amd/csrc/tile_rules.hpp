@@ -35,7 +35,9 @@ inline int rows_ranges(int M, int N, int K) {
 }
 // Weights below 18 MB (24 MB for at most 32 rows) stay with the row slices (48 x 2048 x 2048 7.9 us in slices, 9.1 here; 17 x 1536 x
 // 6144 8.6 and 10.5; but 48 x 1536 x 6144 13.3 and 11.2, 64 x 3072 x 3072 17.9 and 11.9).  At most 32 rows want no cut in eight
-// (32 x 2048 x 8192 11.7 against 13.4), more than 64 rows without a cut a long K (96 x 6144 x 2048 12.1 against 16.0).
+// (32 x 2048 x 8192 11.7 against 13.4), more than 64 rows without a cut a long K (96 x 6144 x 2048 12.1 against 16.0).  These floors
+// are measured on calls that the slices can take, a decode step's and the operators'.  A prompt's output and second feed-forward
+// projection carry row maps and are never sliced: below the floors they run on the 64-row tiles, and the cut is not measured there.
 inline bool rows_stream_pays(int M, int N, int K, int ranges) {
     if (M <= 16 || K % 128 != 0 || N % 64 != 0) return false;
     // a cut that still leaves half of the CUs idle: 20 to 31 x 1984 x 7936 in two ranges (62 workgroups) took half again as long as the slices
