@@ -100,9 +100,10 @@ struct GemmArgs {
     float* row_stats_out;
     const float* row_stats_in;
     int row_stats_groups, row_stats_cols;
-    // gemm_stream and the weight stream of 17 to 128 rows: 1 = the weights are read with the non-temporal hint (common.hpp: load_once).  Right when nothing
-    // could keep them cached until their next use anyway (a decode step that moves more than the memory-side cache holds);
-    // wrong for a layer small enough to live in that cache from step to step, which the hint would keep out of it.
+    // gemm_stream and the weight stream of 17 to 128 rows: 1 = the weights are read with the non-temporal hint (common.hpp:
+    // load_once).  Right when nothing could keep them cached until their next use anyway (a decode step that moves more than the
+    // memory-side cache holds); wrong for a layer small enough to live in that cache from step to step, which the hint would keep
+    // out of it.  Uncut projections of 65 rows and more take that stream with the hint only (tile_rules.hpp: rows_stream_uncut).
     int read_once;
     // EPI_BIAS_RES with 17 rows and more: room for the fp32 sums of the K ranges a narrow output is cut into, k_ranges of
     // them (gemm_k_ranges says how many; <= 1 or part == nullptr: no cut).  [k_ranges][M][N], read by finish_rows.

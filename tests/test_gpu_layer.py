@@ -117,6 +117,7 @@ def test_decode_of_100_sequences_on_a_layer_with_large_projections(eet):
     (2048, 16, 8192, 128, 2, 4),       # FFN-2 cut in eight; 256 prompt rows take the 128-row tiles, more than one of them
     (5120, 40, 5120, 17, 1, 4),        # 20 steps of K in three ranges of 6, 7 and 7
     (1024, 16, 4096, 5, 61, 66),       # a short prompt: FFN-2 alone is cut, its rows scattered to the padded layout
+    (2048, 16, 32768, 5, 9, 14),       # feed-forward rows of a prompt 128 bytes further apart than their length, FFN-2 cut in eight
 ])
 def test_projections_cut_along_k(eet, hidden, heads, ffn, B, S, max_seq):
     """Narrow outputs with a long K and 17 rows or more: the K ranges of the output and the second feed-forward projection are
