@@ -1,0 +1,759 @@
+// Decode steps of small layers: all layers of a step in one launch.
+//
+// A decode step of a small layer (up to 16 sequences, a few MB per projection) is a chain of five dependent phases, and as five
+// launches each of them costs the floor of a dependent launch (drain, start, first trip to memory: about 4 us for 1 to 8 MB of
+// weights), whatever its bytes.  Here the chain runs inside one launch.  A workgroup is one ITEM of one layer: 64 columns of a projection (16
+// of the second feed-forward one), or one key range of a (sequence, head) pair.  It requests its weights (or K/V rows), up to 256 KB, into
+// registers first, since they depend on nothing, and only then waits for its input, which the items of the phase before hand
+// over through memory.  While a phase runs, the CUs that it leaves idle hold the weights of the next ones: HBM never waits for the chain, and a
+// phase costs its hand-over (0.6 to 0.9 us one way, of which 0.45 to 0.7 is one store seen by one load across the chip) and its arithmetic.
+// us per layer-step, five launches -> now: hidden 1024 in a stack of 24, 1 sequence 21.2 -> 10.6, 8 sequences of 384 to 768 tokens
+// 26.4 -> 14.0; 60 drawn sizes (hidden 256 to 2048, 1 to 24 layers, 1 to 8 sequences of 1 to 3200 tokens) 1.18 to 3.1 times as
+// fast, geometric mean 1.86; 30 of 9 to 16 sequences 1.09 to 2.9, 1.58.
+//
+//   hand-over   The exchange buffers hold 8-byte words (four halfs, or two floats) that are all ones until their producer stores them,
+//               and a producer never stores all ones in either half (a NaN of that pattern becomes another NaN).  A consumer loads
+//               the words it needs until none is empty: the data is its own flag, one trip to memory per phase.  Stores and loads are at
+//               agent scope (relaxed), which is what makes them coherent between the XCDs' caches; nothing else is ordered by them and nothing
+//               else needs to be.  Flags or a counter beside the data cost a second trip (256 workgroups, all to all: 2.9 and 4.8 us
+//               against 2.5), release and acquire fences write back and invalidate whole caches (22).
+//   lines       A line is written by one workgroup, in one go: every store to a line that others are polling takes the line away from all
+//               of them first.  Four producers per line: 21.8 us per layer-step where 16-column items with a line each take 20.4, and
+//               64-column items, with a quarter of the lines to poll, 12.4.
+//   reuse       Layer number g (counted on over all steps since the last prefill) uses exchange set g % 2.  An item of the QKV
+//               projection of layer g has seen all of x(g) when it starts to normalise: every item of layer g-1 has handed on its result, so
+//               nobody reads the other set any more, and the QKV items empty it, each its part, and count themselves in `resets` when their
+//               part is empty in memory.  An item of layer g touches its set only once resets >= g * (QKV items); the second feed-forward projection,
+//               which writes x(g+1) into the other set, once resets >= (g+1) * (QKV items).
+//   progress    An item waits only for items with lower numbers, and a workgroup takes its number from a counter when it starts
+//               to run, so whatever an item waits for runs already or has finished: no assumption about how many workgroups are resident, in
+//               which order they start, or what else runs on the device.  The waits are bounded all the same (kSpinLimit).
+//
+// K/V rows of earlier tokens are ordinary memory (written by earlier launches); the new token's K and V row reaches the attention
+// through the exchange set, and the cache for the steps that follow.
+//
+// One workgroup per CU (the registers see to that): two, with 128 registers each, start so far ahead that their polling
+// slows the phases they wait for (12.4 -> 14.2 us per layer-step with one sequence).
+#include "kernels.hpp"
+
+namespace eet {
+
+namespace {
+
+typedef unsigned long long word_t;                 // four halfs or two floats
+typedef unsigned uint4v __attribute__((ext_vector_type(4)));
+constexpr word_t kEmpty = ~0ull;
+constexpr unsigned kEmptyHalf = ~0u;
+constexpr int kAgentScope = 16;                    // cache policy of a buffer load at agent scope: sc1
+constexpr int kSWaves = 8, kSThreads = 64 * kSWaves;
+constexpr int kSRow = 72;                          // halfs of a staged row: 128 bytes + 16
+constexpr int kSUnitsH = 4, kSUnitsF = 16;         // units of 64 K values a wave holds: K = hidden up to 2048, K = ffn up to 8192
+// Polls before an item gives up (its input then reads as NaN and the launch still ends): seconds, where a wait takes microseconds.
+constexpr int kSpinLimit = 1 << 20;
+
+__device__ __forceinline__ word_t ld_word(const word_t* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+__device__ __forceinline__ void st_word(word_t* p, word_t v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+// Neither 4-byte half of a published word is all ones, so a consumer may also load 16 bytes at once and look at each.
+__device__ __forceinline__ void publish(word_t* p, half4v v) {
+    const word_t w = __builtin_bit_cast(word_t, v);
+    const unsigned lo = (unsigned)w, hi = (unsigned)(w >> 32);
+    st_word(p, (word_t)(hi == kEmptyHalf ? 0xFE00FE00u : hi) << 32 | (lo == kEmptyHalf ? 0xFE00FE00u : lo));
+}
+__device__ __forceinline__ void publish(word_t* p, float x, float y) {
+    const unsigned lo = __builtin_bit_cast(unsigned, x), hi = __builtin_bit_cast(unsigned, y);
+    st_word(p, (word_t)(hi == kEmptyHalf ? 0xFFC00000u : hi) << 32 | (lo == kEmptyHalf ? 0xFFC00000u : lo));
+}
+
+// words of a key range's partial result: D/2 of values, one of (maximum, sum), whole lines
+__host__ __device__ constexpr int step_range_words(int d) { return d / 2 + 16; }
+
+struct StepSmem {
+    // wave-private: 2 weight units of 16 rows, or units of the input with 32 rows in all; the attention's merge lies over it
+    half_t stage[kSWaves][2 * 16 * kSRow];
+    float red[kSWaves][16 * 68];                   // [wave][row][up to 64 columns + 4]
+    float stat[kSWaves][16][2];                    // [wave][row] mean and squared deviations of the wave's share of the row
+    word_t ticket;
+};
+
+template <int CTRL>
+__device__ __forceinline__ float dpp_move(float x) {
+    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), CTRL, 0xf, 0xf, false));
+}
+__device__ __forceinline__ float sum8(float v) {   // over aligned groups of 8 lanes
+    v += dpp_move<0xb1>(v);
+    v += dpp_move<0x4e>(v);
+    return v + dpp_move<0x141>(v);
+}
+
+// where this item stands
+struct Where {
+    int layer;                                     // inside the launch
+    uint32_t g;                                    // layer number since the last prefill
+    int lane, wave, tid;
+    word_t* set;                                   // exchange set of layer g
+    word_t* other;                                 // ... and of layers g-1 and g+1
+};
+
+// Thread 0 waits until the exchange set is this layer's, then for one word of the phase before the one whose output the item
+// needs: the tight polling that follows lasts one phase instead of a whole layer.  `input`: a word of the input itself, for the QKV
+// projection, whose faster items empty the set of that earlier word as soon as they have all of theirs; looked at now and then only, since
+// every look at a line that is still to be written makes the write slower.
+__device__ __forceinline__ void wait_resets(const StepArgs& a, uint32_t layers) {
+    const uint32_t* resets = reinterpret_cast<const uint32_t*>(a.ctl + 16);
+    const uint32_t target = layers * (uint32_t)a.n_qkv;
+    for (int spin = 0; spin < kSpinLimit; ++spin) {
+        if ((int32_t)(__hip_atomic_load(resets, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) - target) >= 0) break;
+        __builtin_amdgcn_s_sleep(16);
+    }
+}
+__device__ __forceinline__ void gate(const StepArgs& a, const Where& w, const word_t* before, const word_t* input, bool emptied_by_this_layer) {
+    if (w.tid == 0) {
+        wait_resets(a, w.g);
+        if (before != nullptr)
+            for (int spin = 0; spin < kSpinLimit; ++spin) {
+                if (ld_word(before) != kEmpty) break;
+                if (input != nullptr && spin % 16 == 15 && ld_word(input) != kEmpty) break;
+                __builtin_amdgcn_s_sleep(4);
+            }
+        if (emptied_by_this_layer) wait_resets(a, w.g + 1u);
+    }
+    __syncthreads();
+}
+
+__device__ __forceinline__ word_t wait_word(const word_t* p) {
+    word_t v = ld_word(p);
+    for (int spin = 0; v == kEmpty && spin < kSpinLimit; ++spin) v = ld_word(p);
+    return v;
+}
+
+// ---- one item of a projection: 16*NT columns, all rows (at most 16), K in units of 64 dealt round-robin to the waves ------------
+enum StepPhase { kStepQkv = 0, kStepOut = 1, kStepFfn1 = 2, kStepFfn2 = 3 };
+
+// Exchange buffers hold a producer's output as a block: [row][its columns], whole lines of 16 words.  Word of (row, column):
+__device__ __forceinline__ uint32_t word_at(const StepBuffer& b, int row, int col) {
+    return b.at + (uint32_t)(col >> b.log_cols) * b.block + (((uint32_t)row << b.log_cols) + (uint32_t)(col & ((1 << b.log_cols) - 1))) / 4u;
+}
+
+// How the 16 words of a unit's rows lie over a wave: VW words per lane, LPR lanes per row, UPI units per load instruction.  Rows
+// that do not exist cost lanes, i.e. instructions of the LayerNorm and of the polling, hence the variants of 1, 2, 4, 8 and 16 rows
+// (one sequence on the variant of 8: 12.4 us per layer-step instead of 10.7).
+template <int ROWS>
+struct RowLanes {
+    static constexpr int VW = ROWS == 16 ? 4 : ROWS == 8 ? 2 : 1, LPR = 16 / VW, UPI = 64 / (LPR * ROWS);
+};
+// sum over the lanes of a row
+template <int ROWS>
+__device__ __forceinline__ float row_sum(float v) {
+    v += dpp_move<0xb1>(v);                                    // lane ^ 1
+    v += dpp_move<0x4e>(v);                                    // lane ^ 2: 4 lanes
+    if (ROWS <= 8) v += dpp_move<0x141>(v);                    // 8 lanes
+    if (ROWS <= 4) v += dpp_move<0x140>(v);                    // 16 lanes
+    if (ROWS == 1) v += __shfl_xor(v, 16, kWave);
+    if (ROWS <= 2) v += __shfl_xor(v, 32, kWave);
+    return v;
+}
+
+template <int ROWS, int U, int NT, int PH, bool ONCE>
+__device__ __forceinline__ void project(const StepArgs& a, const Where& w, StepSmem& sm, int tile) {
+    constexpr bool LN = PH == kStepQkv || PH == kStepFfn1, RES = PH == kStepOut || PH == kStepFfn2;
+    constexpr int TN = 16 * NT, RT = TN + 4;                   // columns, floats of a row of a partial tile
+    constexpr int VW = RowLanes<ROWS>::VW, LPR = RowLanes<ROWS>::LPR, UPI = RowLanes<ROWS>::UPI, E = 4 * VW;
+    constexpr int STEPS = (U + UPI - 1) / UPI;
+    typedef half_t halfE __attribute__((ext_vector_type(E), aligned(E == 4 ? 8 : 16)));
+    constexpr int XU = ROWS == 16 ? 2 : 4;                     // units of the input staged at a time
+    const StepLayer& L = a.layer[w.layer];
+    const int M = a.M, H = a.H, K = PH == kStepFfn2 ? a.F : H;
+    const int units = K / 64, n0 = tile * TN;
+    const int lane = w.lane, wave = w.wave;
+    const int wrow = lane >> 3, wchunk = lane & 7;             // this lane's 16 bytes of 8 weight rows
+    const int row = lane / LPR % ROWS, sub = lane / (LPR * ROWS), e0 = lane % LPR * E;   // its part of the input: row, unit of a step, first column in it
+    const int fr = lane & 15, G = lane >> 4;                   // ... and as a matrix operand
+    const half_t* weights = PH == kStepQkv ? L.w_qkv : PH == kStepOut ? L.w_o : PH == kStepFfn1 ? L.w_fc1 : L.w_fc2;
+    const half_t* bias = PH == kStepQkv ? L.b_qkv : PH == kStepOut ? L.b_o : PH == kStepFfn1 ? L.b_fc1 : L.b_fc2;
+    const bool first = w.layer == 0, last = w.layer == a.n_layers - 1;
+    auto has = [&](int s) { return s * UPI + sub < U && wave + kSWaves * (s * UPI + sub) < units; };   // step s brings this lane a unit
+    auto column = [&](int s) { return (wave + kSWaves * (s * UPI + sub)) * 64 + e0; };
+
+    // ---- what depends on nothing: weights, scale and shift, bias, cache slot ----
+    half8v wf[U][NT][2];
+    {
+        const char* wb = reinterpret_cast<const char*>(weights) + (size_t)n0 * K * 2;
+        const uint32_t off = ((uint32_t)wrow * K + wchunk * 8) * 2u;
+#pragma unroll
+        for (int i = 0; i < U; ++i)
+            if (wave + kSWaves * i < units) {
+#pragma unroll
+                for (int t = 0; t < NT; ++t)
+#pragma unroll
+                    for (int h = 0; h < 2; ++h) {
+                        const half8v* p = reinterpret_cast<const half8v*>(wb + (off + (uint32_t)((t * 16 + h * 8) * K + (wave + kSWaves * i) * 64) * 2u));
+                        wf[i][t][h] = ONCE ? load_once(p) : *p;
+                    }
+            }
+    }
+    halfE gv[LN ? STEPS : 1], bv[LN ? STEPS : 1];
+    if constexpr (LN) {
+        const half_t* gamma = PH == kStepQkv ? L.ln1_g : L.ln2_g;
+        const half_t* beta = PH == kStepQkv ? L.ln1_b : L.ln2_b;
+#pragma unroll
+        for (int s = 0; s < STEPS; ++s)
+            if (has(s)) {
+                gv[s] = *reinterpret_cast<const halfE*>(gamma + column(s));
+                bv[s] = *reinterpret_cast<const halfE*>(beta + column(s));
+            }
+    }
+    const int em = w.tid / (TN / 4), ec = (w.tid % (TN / 4)) * 4, en = n0 + ec;   // the M * TN/4 threads that write: row, first of four columns
+    const bool writer = w.tid < M * (TN / 4);
+    half4v eb, er;
+    int epos = 0;
+    if (writer) {
+        eb = *reinterpret_cast<const half4v*>(bias + en);
+        if (PH == kStepQkv) epos = a.lens[em];
+        if (PH == kStepOut && first) er = *reinterpret_cast<const half4v*>(a.x + (size_t)em * H + en);
+    }
+    // weights into matrix-operand layout by way of LDS (whole lines per load instruction), while there is nothing else to do: two
+    // 16-row units at a time
+    half_t* st = sm.stage[wave];
+#pragma unroll
+    for (int q = 0; q < U * NT; q += 2) {
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+            if (q + j < U * NT && wave + kSWaves * ((q + j) / NT) < units)
+#pragma unroll
+                for (int h = 0; h < 2; ++h) *reinterpret_cast<half8v*>(&st[(j * 16 + 8 * h + wrow) * kSRow + wchunk * 8]) = wf[(q + j) / NT][(q + j) % NT][h];
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+            if (q + j < U * NT && wave + kSWaves * ((q + j) / NT) < units)
+#pragma unroll
+                for (int h = 0; h < 2; ++h) wf[(q + j) / NT][(q + j) % NT][h] = *reinterpret_cast<const half8v*>(&st[(j * 16 + fr) * kSRow + G * 8 + 32 * h]);
+    }
+
+    // ---- the input ----
+    const StepBuffer& in = PH == kStepQkv ? a.bx : PH == kStepOut ? a.bctx : PH == kStepFfn1 ? a.by : a.bf;
+    const word_t* before = PH == kStepQkv ? (first ? nullptr : w.other + a.bf.at)
+                         : PH == kStepOut ? w.set + a.bqkv.at
+                         : PH == kStepFfn1 ? w.set + a.bctx.at : w.set + a.by.at;
+    gate(a, w, before, PH == kStepQkv ? w.set + in.at : nullptr, PH == kStepFfn2);
+    if (RES && writer && !(PH == kStepOut && first))
+        er = __builtin_bit_cast(half4v, wait_word(w.set + word_at(PH == kStepOut ? a.bx : a.by, em, en)));
+    halfE xv[STEPS];
+    const bool mine = row < M;
+    if (PH == kStepQkv && first) {
+#pragma unroll
+        for (int s = 0; s < STEPS; ++s)
+            if (has(s) && mine) xv[s] = *reinterpret_cast<const halfE*>(a.x + (size_t)row * H + column(s));
+    } else if (PH == kStepOut && a.splits > 1) {
+        // the attention's key ranges: merge them (common maximum, rescaled sums, one division)
+        const int stride = step_range_words(a.d);
+#pragma unroll
+        for (int s = 0; s < STEPS; ++s) {
+            float lsum = 0.f, mx = -INFINITY, av[E];
+#pragma unroll
+            for (int e = 0; e < E; ++e) av[e] = 0.f;
+            if (has(s) && mine) {
+                const int k = column(s);
+                const word_t* p = w.set + in.at + (size_t)(row * a.heads + k / a.d) * a.splits * stride;
+                const int at = (k % a.d) / 2;
+                for (int s0 = 0; s0 < a.splits; s0 += 2, p += 2 * stride) {      // a power of two of them
+                    word_t v[2][E / 2 + 1];
+                    for (int spin = 0; spin < kSpinLimit; ++spin) {
+                        bool ok = true;
+#pragma unroll
+                        for (int r = 0; r < 2; ++r) {
+#pragma unroll
+                            for (int e = 0; e < E / 2; ++e) v[r][e] = ld_word(p + r * stride + at + e);
+                            v[r][E / 2] = ld_word(p + r * stride + a.d / 2);
+                        }
+#pragma unroll
+                        for (int r = 0; r < 2; ++r)
+#pragma unroll
+                            for (int e = 0; e <= E / 2; ++e) ok &= v[r][e] != kEmpty;
+                        if (ok) break;
+                    }
+#pragma unroll
+                    for (int r = 0; r < 2; ++r) {
+                        const float2v ml = __builtin_bit_cast(float2v, v[r][E / 2]);
+                        const float m_new = fmaxf(mx, ml[0]);
+                        const float keep = exp2f(mx - m_new), add = exp2f(ml[0] - m_new);
+                        lsum = lsum * keep + ml[1] * add;
+#pragma unroll
+                        for (int e = 0; e < E / 2; ++e) {
+                            const float2v q = __builtin_bit_cast(float2v, v[r][e]);
+                            av[2 * e] = av[2 * e] * keep + q[0] * add;
+                            av[2 * e + 1] = av[2 * e + 1] * keep + q[1] * add;
+                        }
+                        mx = m_new;
+                    }
+                }
+            }
+            const float inv = lsum > 0.f ? 1.0f / lsum : 0.f;
+#pragma unroll
+            for (int e = 0; e < E; ++e) xv[s][e] = (half_t)(av[e] * inv);
+        }
+    } else {
+        // (a unit is a whole number of blocks)
+        const word_t* p = w.set + word_at(in, row, column(0));
+        const uint32_t per_step = (uint32_t)(UPI * kSWaves) * (64u >> in.log_cols) * in.block;
+        word_t v[STEPS][VW];
+        const auto set = __builtin_amdgcn_make_buffer_rsrc(w.set, 0, (int)(a.set_words * sizeof(word_t)), 0x00027000);
+        const uint32_t off = (uint32_t)(p - w.set);
+        for (int spin = 0; spin < kSpinLimit; ++spin) {
+            asm volatile("" ::: "memory");
+            unsigned most = 0;                                 // a half that is kEmptyHalf is the largest there is
+#pragma unroll
+            for (int s = 0; s < STEPS; ++s)
+                if (has(s) && mine) {
+                    if constexpr (VW >= 2) {
+#pragma unroll
+                        for (int q = 0; q < VW; q += 2) {
+                            const uint4v r = __builtin_amdgcn_raw_buffer_load_b128(set, (int)((off + s * per_step + q) * sizeof(word_t)), 0, kAgentScope);
+                            v[s][q] = (word_t)r[1] << 32 | r[0];
+                            v[s][(q + 1) % VW] = (word_t)r[3] << 32 | r[2];
+                        }
+                    } else {
+                        v[s][0] = ld_word(p + s * per_step);
+                    }
+                }
+            // (a loop of its own: every load is requested before the first is waited for)
+#pragma unroll
+            for (int s = 0; s < STEPS; ++s)
+                if (has(s) && mine) {
+#pragma unroll
+                    for (int q = 0; q < VW; ++q) most = max(most, max((unsigned)v[s][q], (unsigned)(v[s][q] >> 32)));
+                }
+            if (__all(most != kEmptyHalf)) break;
+        }
+        struct Words { word_t w[VW]; };
+#pragma unroll
+        for (int s = 0; s < STEPS; ++s) {
+            Words x;
+#pragma unroll
+            for (int q = 0; q < VW; ++q) x.w[q] = v[s][q];
+            xv[s] = __builtin_bit_cast(halfE, x);
+        }
+    }
+    asm volatile("" ::: "memory");
+    if constexpr (PH == kStepFfn2) {
+        // everyone who reads the cache lengths in this step is an ancestor of this item's input
+        if (last && a.bump && tile == 0) {
+            __syncthreads();                                   // all waves have their share of the input: together, all of it
+            if (w.tid < M) a.lens[w.tid] += 1;
+        }
+    }
+
+    if constexpr (LN) {
+        // mean and squared deviations of the wave's share of each row, then of the row (shares merged by their sizes)
+        int count = (units - wave + kSWaves - 1) / kSWaves;
+        count = count < 0 ? 0 : count;
+        float sum = 0.f, sq = 0.f;
+#pragma unroll
+        for (int s = 0; s < STEPS; ++s)
+            if (has(s)) {
+#pragma unroll
+                for (int e = 0; e < E; ++e) sum = __builtin_fmaf((float)xv[s][e], 1.0f, sum);
+            }
+        sum = row_sum<ROWS>(sum);
+        const float mw = count > 0 ? sum * __builtin_amdgcn_rcpf((float)(64 * count)) : 0.f;      // a power of two, or rounded once: any value near the mean serves
+#pragma unroll
+        for (int s = 0; s < STEPS; ++s)
+            if (has(s)) {
+#pragma unroll
+                for (int e = 0; e < E; ++e) {
+                    const float d = __builtin_fmaf((float)xv[s][e], 1.0f, -mw);
+                    sq = __builtin_fmaf(d, d, sq);
+                }
+            }
+        sq = row_sum<ROWS>(sq);
+        if (lane % LPR == 0 && sub == 0) *reinterpret_cast<float2v*>(&sm.stat[wave][row][0]) = float2v{mw, sq};
+        __syncthreads();
+        if constexpr (PH == kStepQkv) {
+            // all waves together have seen all of x(g): layer g-1 is finished, its exchange set is nobody's (the acknowledgement
+            // is awaited below, before anything of this item is handed on)
+            const uint32_t per = ((a.set_words + a.n_qkv - 1) / a.n_qkv + 15) / 16 * 16, lo = tile * per;
+            const uint32_t hi = lo + per < a.set_words ? lo + per : a.set_words;
+            for (uint32_t c = lo + w.tid; c < hi; c += kSThreads) st_word(w.other + c, kEmpty);
+        }
+        float2v sv[kSWaves];
+#pragma unroll
+        for (int v = 0; v < kSWaves; ++v) sv[v] = *reinterpret_cast<const float2v*>(&sm.stat[v][row][0]);
+        const float inv_k = 1.0f / (float)K;
+        float mean = 0.f, m2 = 0.f;
+#pragma unroll
+        for (int v = 0; v < kSWaves; ++v) {
+            int c = (units - v + kSWaves - 1) / kSWaves;
+            c = c < 0 ? 0 : c;
+            mean += sv[v][0] * ((float)(64 * c) * inv_k);
+        }
+#pragma unroll
+        for (int v = 0; v < kSWaves; ++v) {
+            int c = (units - v + kSWaves - 1) / kSWaves;
+            c = c < 0 ? 0 : c;
+            const float d = sv[v][0] - mean;
+            m2 += sv[v][1] + (float)(64 * c) * d * d;
+        }
+        const float rstd = rsqrtf(m2 * inv_k + a.eps);
+#pragma unroll
+        for (int s = 0; s < STEPS; ++s)
+#pragma unroll
+            for (int e = 0; e < E; ++e) {
+                // fused multiply-adds that take their fp16 operands directly
+                const float sc = __builtin_fmaf((float)gv[s][e], rstd, 0.f);
+                const float sh = __builtin_fmaf(-mean, sc, (float)bv[s][e]);
+                xv[s][e] = (half_t)__builtin_fmaf((float)xv[s][e], sc, sh);
+            }
+    }
+
+    // ---- contraction: acc[t][r] = output column n0 + 16t + 4G + r of row fr ----
+    float4v acc[NT];
+#pragma unroll
+    for (int t = 0; t < NT; ++t) acc[t] = float4v{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int i = 0; i < U; i += XU) {                          // through the staging area
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll
+        for (int s = i / UPI; s < (i + XU) / UPI && s < STEPS; ++s)
+            if (has(s)) *reinterpret_cast<halfE*>(&st[((s * UPI + sub - i) * ROWS + row) * kSRow + e0]) = xv[s];
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll
+        for (int j = 0; j < XU && i + j < U; ++j)
+            if (wave + kSWaves * (i + j) < units) {
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    const half8v xf = *reinterpret_cast<const half8v*>(&st[(j * ROWS + (fr & (ROWS - 1))) * kSRow + G * 8 + 32 * h]);
+#pragma unroll
+                    for (int t = 0; t < NT; ++t) acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_f16(wf[i + j][t][h], xf, acc[t], 0, 0, 0);
+                }
+            }
+    }
+    static_assert(ROWS * RT <= (int)(sizeof(sm.red[0]) / sizeof(float)), "a wave's partial tile");
+    if (fr < ROWS) {
+#pragma unroll
+        for (int t = 0; t < NT; ++t) *reinterpret_cast<float4v*>(&sm.red[wave][fr * RT + 16 * t + 4 * G]) = acc[t];
+    }
+    __syncthreads();
+    if (writer) {
+    float4v v = *reinterpret_cast<const float4v*>(&sm.red[0][em * RT + ec]);
+#pragma unroll
+    for (int o = 1; o < kSWaves; ++o) v += *reinterpret_cast<const float4v*>(&sm.red[o][em * RT + ec]);
+    half4v out;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        float f = v[e] + (float)eb[e];
+        if (PH == kStepFfn1) f = gelu_tanh(f);
+        if (RES) f += (float)er[e];
+        out[e] = (half_t)f;
+    }
+    if constexpr (PH == kStepQkv) {
+        publish(w.set + word_at(a.bqkv, em, en), out);
+        const int which = en / H, c = en - which * H;
+        if (which != 0 && epos >= 0 && epos < a.max_seq)      // past the capacity (replays the host never saw): dropped
+            *reinterpret_cast<half4v*>((which == 1 ? L.k_cache : L.v_cache) + ((size_t)(em * a.heads + c / a.d) * a.max_seq + epos) * a.d + c % a.d) = out;
+    } else if constexpr (PH == kStepOut) {
+        publish(w.set + word_at(a.by, em, en), out);
+    } else if constexpr (PH == kStepFfn1) {
+        publish(w.set + word_at(a.bf, em, en), out);
+    } else {
+        if (last) *reinterpret_cast<half4v*>(a.out + (size_t)em * H + en) = out;
+        else publish(w.other + word_at(a.bx, em, en), out);
+    }
+    }
+    if constexpr (PH == kStepQkv) {
+        // what this item emptied of the other set is empty in memory before it is counted
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        __syncthreads();
+        if (w.tid == 0) __hip_atomic_fetch_add(reinterpret_cast<uint32_t*>(a.ctl + 16), 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+}
+
+// ---- one key range of a (sequence, head) pair ----------------------------------------------------------------------------------
+// As attn_decode (attention.hip): a key row over D/8 adjacent lanes, running (max, sum, values) per lane group, merged at the end.
+// Up to 1024 keys (heads of 64; 512 of 128) are in registers before the query arrives; half as many cost 0.9 us per layer-step with
+// eight sequences of 384 to 768 tokens.
+template <int D, bool ONCE>
+__device__ __forceinline__ void attend(const StepArgs& a, const Where& w, StepSmem& sm, int item) {
+    constexpr int LPK = D / 8, KPI = 64 / LPK, U = 4, BK = U * KPI, PF = 4;      // PF blocks of BK keys in flight per wave
+    constexpr float kNone = -1e30f, kLog2e = 1.4426950408889634f;
+    const StepLayer& L = a.layer[w.layer];
+    const int sp = item % a.splits, bh = item / a.splits, b = bh / a.heads, h = bh - b * a.heads;
+    const int lane = w.lane, wave = w.wave, kslot = lane / LPK, chunk = lane % LPK;
+    int n = a.lens[b];                                        // cached keys; the new token's is number n
+    n = n < 0 ? 0 : n;
+    const bool room = n < a.max_seq;
+    const int visible = room ? n + 1 : a.max_seq;
+    int per = (visible + a.splits - 1) / a.splits;
+    per = (per + 15) & ~15;
+    const int c0 = sp * per, c1 = c0 + per < visible ? c0 + per : visible;
+    const bool has_new = room && c0 <= n && n < c1;
+    const int ce = has_new ? n : c1;                          // cached keys of the range: [c0, ce)
+    const char* kbase = reinterpret_cast<const char*>(L.k_cache + (size_t)bh * a.max_seq * D);
+    const char* vbase = reinterpret_cast<const char*>(L.v_cache + (size_t)bh * a.max_seq * D);
+    half8v kr[PF][U], vr[PF][U];
+    auto request = [&](half8v (&kf)[U], half8v (&vf)[U], int j0) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            int r = j0 + u * KPI + kslot;
+            r = r < ce ? r : ce - 1;
+            const uint32_t off = (uint32_t)r * (uint32_t)(D * 2) + (uint32_t)chunk * 16u;
+            const half8v* kp = reinterpret_cast<const half8v*>(kbase + off);
+            const half8v* vp = reinterpret_cast<const half8v*>(vbase + off);
+            kf[u] = ONCE ? load_once(kp) : *kp;
+            vf[u] = ONCE ? load_once(vp) : *vp;
+        }
+    };
+    const int j0 = c0 + wave * BK;                            // blocks wave, wave + 8, ... of the range
+#pragma unroll
+    for (int i = 0; i < PF; ++i)
+        if (j0 + i * kSWaves * BK < ce) request(kr[i], vr[i], j0 + i * kSWaves * BK);
+    gate(a, w, w.layer == 0 ? nullptr : w.set + a.bx.at, nullptr, false);
+    const word_t* qkv = w.set + word_at(a.bqkv, b, h * D + chunk * 8);
+    const uint32_t to_k = (uint32_t)(a.H >> a.bqkv.log_cols) * a.bqkv.block;
+    half8v qv, kn, vn;
+    const bool take_new = has_new && wave == 0;
+    {
+        word_t v[6];
+        const word_t* p = qkv;
+        for (int spin = 0; spin < kSpinLimit; ++spin) {
+            v[0] = ld_word(p);
+            v[1] = ld_word(p + 1);
+            if (take_new) {
+                v[2] = ld_word(p + to_k);
+                v[3] = ld_word(p + to_k + 1);
+                v[4] = ld_word(p + 2 * to_k);
+                v[5] = ld_word(p + 2 * to_k + 1);
+            }
+            bool ok = v[0] != kEmpty && v[1] != kEmpty;
+            if (take_new) ok &= v[2] != kEmpty && v[3] != kEmpty && v[4] != kEmpty && v[5] != kEmpty;
+            if (__all(ok)) break;
+        }
+        auto join = [](word_t x, word_t y) {
+            return __builtin_shufflevector(__builtin_bit_cast(half4v, x), __builtin_bit_cast(half4v, y), 0, 1, 2, 3, 4, 5, 6, 7);
+        };
+        qv = join(v[0], v[1]);
+        if (take_new) {
+            kn = join(v[2], v[3]);
+            vn = join(v[4], v[5]);
+        }
+    }
+    const float c = rsqrtf((float)D) * kLog2e;
+    auto score = [&](const half8v& k) {
+        float d = 0.f;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) d = __builtin_amdgcn_fdot2(half2v{k[2 * e], k[2 * e + 1]}, half2v{qv[2 * e], qv[2 * e + 1]}, d, false);
+        d = sum8(d);
+        if (LPK == 16) d += dpp_move<0x140>(d);
+        return d * c;
+    };
+    float acc[8], m = kNone, l = 0.f;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) acc[e] = 0.f;
+    auto consume = [&](const half8v (&kf)[U], const half8v (&vf)[U], int j) {
+        float sc[U], mx = kNone;
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const float s = score(kf[u]);
+            sc[u] = j + u * KPI + kslot < ce ? s : -INFINITY;
+            mx = fmaxf(mx, sc[u]);
+        }
+        const float m_new = fmaxf(m, mx), alpha = __builtin_amdgcn_exp2f(m - m_new);
+        l *= alpha;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) acc[e] *= alpha;
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const float p = __builtin_amdgcn_exp2f(sc[u] - m_new);
+            l += p;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) acc[e] = __builtin_fmaf(p, (float)vf[u][e], acc[e]);
+        }
+        m = m_new;
+    };
+    for (int jb = j0; jb < ce; jb += PF * kSWaves * BK) {
+#pragma unroll
+        for (int i = 0; i < PF; ++i) {
+            const int jc = jb + i * kSWaves * BK, jn = jc + PF * kSWaves * BK;
+            if (jc >= ce) break;
+            consume(kr[i], vr[i], jc);
+            if (jn < ce) request(kr[i], vr[i], jn);
+        }
+    }
+    if (take_new) {                                           // the new token's key: lane group 0 of wave 0
+        const float s = kslot == 0 ? score(kn) : -INFINITY;
+        const float m_new = fmaxf(m, s), alpha = __builtin_amdgcn_exp2f(m - m_new), p = __builtin_amdgcn_exp2f(s - m_new);
+        l = l * alpha + p;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) acc[e] = __builtin_fmaf(p, (float)vn[e], acc[e] * alpha);
+        m = m_new;
+    }
+    // lane groups, then waves
+    float mw = m;
+    if (LPK == 8) mw = fmaxf(mw, dpp_move<0x128>(mw));
+    mw = fmaxf(mw, __shfl_xor(mw, 16, kWave));
+    mw = fmaxf(mw, __shfl_xor(mw, 32, kWave));
+    const float r = __builtin_amdgcn_exp2f(m - mw);
+    l *= r;
+    if (LPK == 8) l += dpp_move<0x128>(l);
+    l += __shfl_xor(l, 16, kWave);
+    l += __shfl_xor(l, 32, kWave);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+        acc[e] *= r;
+        if (LPK == 8) acc[e] += dpp_move<0x128>(acc[e]);
+        acc[e] += __shfl_xor(acc[e], 16, kWave);
+        acc[e] += __shfl_xor(acc[e], 32, kWave);
+    }
+    float* sm_acc = reinterpret_cast<float*>(&sm.stage[0][0]);       // [waves][D]
+    static_assert(sizeof(float) * kSWaves * 128 <= sizeof(sm.stage), "merge over the staging areas");
+    if (lane < LPK) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) sm_acc[wave * D + lane * 8 + e] = acc[e];
+    }
+    if (lane == 0) *reinterpret_cast<float2v*>(&sm.stat[wave][0][0]) = float2v{mw, l};
+    __syncthreads();
+    if (w.tid >= D / 2) return;
+    float2v ml[kSWaves];
+    float mx = kNone;
+#pragma unroll
+    for (int v = 0; v < kSWaves; ++v) {
+        ml[v] = *reinterpret_cast<const float2v*>(&sm.stat[v][0][0]);
+        mx = fmaxf(mx, ml[v][0]);
+    }
+    float sum = 0.f, a0 = 0.f, a1 = 0.f;
+#pragma unroll
+    for (int v = 0; v < kSWaves; ++v) {
+        const float f = __builtin_amdgcn_exp2f(ml[v][0] - mx);
+        const float2v x = *reinterpret_cast<const float2v*>(&sm_acc[v * D + w.tid * 2]);
+        sum += ml[v][1] * f;
+        a0 += x[0] * f;
+        a1 += x[1] * f;
+    }
+    if (a.splits > 1) {
+        word_t* p = w.set + a.bctx.at + (size_t)item * step_range_words(D);
+        publish(p + w.tid, a0, a1);
+        if (w.tid == 0) publish(p + D / 2, mx, sum);
+        return;
+    }
+    const float inv = sum > 0.f ? 1.0f / sum : 0.f;
+    const float b0 = a0 * inv, b1 = a1 * inv;
+    const float c0_ = __shfl_xor(b0, 1, kWave), c1_ = __shfl_xor(b1, 1, kWave);
+    if ((w.tid & 1) == 0)
+        publish(w.set + word_at(a.bctx, b, h * D + w.tid * 2), half4v{(half_t)b0, (half_t)b1, (half_t)c0_, (half_t)c1_});
+}
+
+// ROWS: rows, rounded up.  UH, NTH: units of K = hidden per wave and blocks of 16 columns per item in the three projections from
+// there; UF: units of K = ffn per wave.  The weights of an item take 64 registers per lane (hidden up to 1024) or 128.
+template <int ROWS, int UH, int NTH, int UF, bool ONCE>
+__global__ __launch_bounds__(kSThreads, 2) void decode_layers(StepArgs a) {
+    __shared__ __attribute__((aligned(16))) StepSmem sm;
+    Where w;
+    w.tid = threadIdx.x;
+    w.lane = w.tid & 63;
+    w.wave = __builtin_amdgcn_readfirstlane(w.tid >> 6);
+    // The number of this item, in the order in which workgroups start (low half), and the layer number of the launch's first layer
+    // (high half).  The launch's last workgroup to ask turns both on for the next launch.
+    if (w.tid == 0) {
+        const word_t t = __hip_atomic_fetch_add(a.ctl, (word_t)1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if ((uint32_t)t == (uint32_t)a.items - 1u)
+            __hip_atomic_fetch_add(a.ctl, ((word_t)a.n_layers << 32) - (word_t)a.items, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        sm.ticket = t;
+    }
+    __syncthreads();
+    const uint32_t item = __builtin_amdgcn_readfirstlane((uint32_t)sm.ticket), g0 = __builtin_amdgcn_readfirstlane((uint32_t)(sm.ticket >> 32));
+    if (item >= (uint32_t)a.items) return;
+    w.layer = (int)(item / (uint32_t)a.per_layer);
+    int r = (int)(item - (uint32_t)w.layer * (uint32_t)a.per_layer);
+    w.g = g0 + (uint32_t)w.layer;
+    w.set = a.ex + (size_t)(w.g & 1u) * a.set_words;
+    w.other = a.ex + (size_t)(~w.g & 1u) * a.set_words;
+    if (r < a.n_qkv) { project<ROWS, UH, NTH, kStepQkv, ONCE>(a, w, sm, r); return; }
+    r -= a.n_qkv;
+    if (r < a.n_att) {
+        if (a.d == 64) attend<64, ONCE>(a, w, sm, r);
+        else attend<128, ONCE>(a, w, sm, r);
+        return;
+    }
+    r -= a.n_att;
+    if (r < a.n_out) { project<ROWS, UH, NTH, kStepOut, ONCE>(a, w, sm, r); return; }
+    r -= a.n_out;
+    if (r < a.n_ffn1) { project<ROWS, UH, NTH, kStepFfn1, ONCE>(a, w, sm, r); return; }
+    project<ROWS, UF, 1, kStepFfn2, ONCE>(a, w, sm, r - a.n_ffn1);
+}
+
+// Key ranges per pair: up to 128 items of at least 128 keys at full capacity, so that the attention's items leave CUs to the
+// projections that follow (256 of them: 8 sequences of 384 to 768 tokens, 16 heads: 15.6 -> 19.9 us per layer-step).
+int step_splits(int rows, int heads, int capacity) {
+    const int pairs = rows * heads;
+    int s = 1;
+    while (2 * s * pairs <= 128 && capacity / (2 * s) >= 128 && s < 16) s *= 2;
+    return s;
+}
+
+}  // namespace
+
+// More than 8 rows double the registers of the input: only where the weights leave them.
+static bool step_is_narrow(int hidden, int ffn) { return hidden <= 64 * kSWaves * 2 && ffn <= 64 * kSWaves * 8; }
+bool decode_step_fits(int rows, int hidden, int heads, int ffn) {
+    const int d = hidden / heads;
+    return rows >= 1 && rows <= (step_is_narrow(hidden, ffn) ? 16 : 8) && (d == 64 || d == 128) && hidden % 64 == 0 && ffn % 64 == 0 &&
+           hidden <= 64 * kSWaves * kSUnitsH && ffn <= 64 * kSWaves * kSUnitsF;
+}
+
+static void step_layout(StepArgs& a) {
+    const int d = a.H / a.heads, log_h = 6;                   // 64 columns per item
+    a.d = d;
+    a.splits = step_splits(a.M, a.heads, a.max_seq);
+    uint32_t at = 0;
+    auto buffer = [&](int cols, int log_cols) {
+        const uint32_t block = (uint32_t)((a.M << log_cols) / 4 + 15) / 16 * 16;
+        const StepBuffer b{at, block, log_cols};
+        at += (uint32_t)(cols >> log_cols) * block;
+        return b;
+    };
+    a.bx = buffer(a.H, 4);
+    a.bqkv = buffer(3 * a.H, log_h);
+    a.bctx = buffer(a.H, 6);
+    if (a.splits > 1) at = a.bctx.at + (uint32_t)(a.M * a.heads * a.splits * step_range_words(d));
+    a.by = buffer(a.H, log_h);
+    a.bf = buffer(a.F, log_h);
+    a.set_words = at;
+}
+
+size_t decode_step_bytes(int rows, int hidden, int heads, int ffn, int max_seq) {
+    if (!decode_step_fits(rows, hidden, heads, ffn)) return 0;
+    StepArgs a{};
+    a.M = rows; a.H = hidden; a.heads = heads; a.F = ffn; a.max_seq = max_seq;
+    step_layout(a);
+    return (kStepCtlWords + 2 * (size_t)a.set_words) * sizeof(word_t);
+}
+
+hipError_t launch_decode_layers(StepArgs& a, bool read_once, hipStream_t s) {
+    step_layout(a);
+    a.ex = a.ctl + kStepCtlWords;
+    const int log_h = a.bqkv.log_cols;
+    a.n_qkv = 3 * a.H >> log_h;
+    a.n_att = a.M * a.heads * a.splits;
+    a.n_out = a.H >> log_h;
+    a.n_ffn1 = a.F >> log_h;
+    a.per_layer = a.n_qkv + a.n_att + a.n_out + a.n_ffn1 + a.H / 16;
+    a.items = a.per_layer * a.n_layers;
+    const dim3 grid(a.items), block(kSThreads);
+#define EET_STEP(ROWS, UH, UF) do { if (read_once) hipLaunchKernelGGL((decode_layers<ROWS, UH, 4, UF, true>), grid, block, 0, s, a); \
+                                    else hipLaunchKernelGGL((decode_layers<ROWS, UH, 4, UF, false>), grid, block, 0, s, a); } while (0)
+    if (step_is_narrow(a.H, a.F)) {
+        if (a.M <= 1) EET_STEP(1, 2, 8);
+        else if (a.M <= 2) EET_STEP(2, 2, 8);
+        else if (a.M <= 4) EET_STEP(4, 2, 8);
+        else if (a.M <= 8) EET_STEP(8, 2, 8);
+        else EET_STEP(16, 2, 8);
+    } else {
+        if (a.M <= 1) EET_STEP(1, 4, 16);
+        else if (a.M <= 2) EET_STEP(2, 4, 16);
+        else if (a.M <= 4) EET_STEP(4, 4, 16);
+        else EET_STEP(8, 4, 16);
+    }
+#undef EET_STEP
+    return hipGetLastError();
+}
+
+}  // namespace eet

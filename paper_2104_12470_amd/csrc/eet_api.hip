@@ -50,7 +50,7 @@ constexpr int kFfnPadFrom = 32768;
 // 1024, 512 rows: 7.5 -> 13.8, bound 9.4); held inside the bound the first could not cut its second feed-forward
 // projection at all (29 us -> 71 us).
 struct WorkspaceLayout {
-    size_t lens, cu, row_map, buf_f, cut, buf_a, buf_b, buf_y, part, row_stats, total;
+    size_t lens, cu, row_map, buf_f, cut, buf_a, buf_b, buf_y, part, step, row_stats, total;
     int splits;
 };
 
@@ -99,6 +99,14 @@ WorkspaceLayout layout_of(const eet_layer_config* c) {
         part = p > part ? p : part;
     }
     off = align_up(off + part, 256);
+    // the exchange area of the decode steps that run as one launch (decode_step.hip), which need no partials: in the same place
+    w.step = w.part;
+    size_t step = 0;
+    for (int b = 1; b <= c->max_batch && b <= 16; ++b) {
+        const size_t p = decode_step_bytes(b, c->hidden, c->heads, c->ffn, c->max_seq);
+        step = p > step ? p : step;
+    }
+    if (w.step + step > off) off = align_up(w.step + step, 256);
     // LayerNorm statistics handed from the output projection of a decode step to the first feed-forward projection:
     // (mean, squared deviations) per row and workgroup of the producer, at most hidden/16 workgroups of 16 rows
     w.row_stats = off;
@@ -185,6 +193,13 @@ static void cut_projection(eet_layer* L, GemmArgs& g, size_t sums) {
     g.part = reinterpret_cast<float*>(L->ws + sums);
 }
 
+// The exchange area of `L`'s decode steps of `batch` sequences, to be set up wherever the cache lengths are set
+static StepArea step_area(const eet_layer* L, int batch) {
+    const eet_layer_config& c = L->cfg;
+    return StepArea{reinterpret_cast<unsigned long long*>(L->ws + L->lay.step),
+                    (uint32_t)(decode_step_bytes(batch, c.hidden, c.heads, c.ffn, c.max_seq) / sizeof(unsigned long long))};
+}
+
 #define EET_LAUNCH(expr, what)                        \
     do {                                              \
         hipError_t e_ = (expr);                       \
@@ -196,7 +211,7 @@ static void cut_projection(eet_layer* L, GemmArgs& g, size_t sums) {
 // and whose output buffer already has its pad rows zeroed (an earlier layer of the same call did both).
 static int enqueue_prefill(eet_layer* L, const SeqLens& lens, int batch, int padded_len, int64_t T, int max_len,
                            const void* tokens, void* out, void* kv_cache, hipStream_t s, bool causal = true,
-                           bool left_padded = false, bool index_setup = true) {
+                           bool left_padded = false, bool index_setup = true, bool sets_lengths = true) {
     const eet_layer_config& c = L->cfg;
     const int H = c.hidden, F = c.ffn;
     int32_t* d_lens = reinterpret_cast<int32_t*>(L->ws + L->lay.lens);
@@ -216,7 +231,8 @@ static int enqueue_prefill(eet_layer* L, const SeqLens& lens, int batch, int pad
     // a2: LN1 over valid rows only (gathered into the packed layout), in the same launch for rows of up to 2048
     if (index_setup && prefill_setup_takes_layernorm(H)) {
         EET_LAUNCH(launch_prefill_setup_layernorm(lens, batch, padded_len, H, d_lens, d_cu, d_map, static_cast<half_t*>(out), left_padded,
-                                                  x, (const half_t*)L->w.ln1_g, (const half_t*)L->w.ln1_b, bufA, c.ln_eps, s),
+                                                  x, (const half_t*)L->w.ln1_g, (const half_t*)L->w.ln1_b, bufA, c.ln_eps,
+                                                  causal && sets_lengths ? step_area(L, batch) : StepArea{}, s),
                    "prefill set-up and layernorm 1");
     } else {
         if (index_setup)
@@ -493,6 +509,43 @@ static int enqueue_decode(eet_layer* L, const void* tokens, void* out, void* kv_
     return EET_OK;
 }
 
+// A decode step through `n` layers of one configuration that share a workspace, as one launch per kStepLayers of them.  The last
+// layer's launch advances the lengths.  act: where a launch leaves its output for the next (two buffers, alternating).
+static bool decodes_in_one_launch(const eet_layer* L) { return decode_step_fits(L->batch, L->cfg.hidden, L->cfg.heads, L->cfg.ffn); }
+static int enqueue_decode_layers(eet_layer* const* layers, int n, const void* tokens, void* out, void* kv_cache, size_t layer_cache_bytes,
+                                 void* const* act, hipStream_t s) {
+    const eet_layer* L0 = layers[0];
+    const eet_layer_config& c = L0->cfg;
+    const int H = c.hidden, F = c.ffn;
+    size_t visible = 0;
+    for (int b = 0; b < L0->batch; ++b) visible += (size_t)L0->host_lens[b] + 1;
+    const size_t step_bytes = (size_t)n * (2 * ((size_t)4 * H * H + (size_t)2 * H * F) + (size_t)4 * H * visible);
+    const void* in = tokens;
+    for (int l0 = 0, k = 0; l0 < n; l0 += kStepLayers, ++k) {
+        StepArgs a{};
+        a.n_layers = n - l0 < kStepLayers ? n - l0 : kStepLayers;
+        const bool last = l0 + a.n_layers == n;
+        void* o = last ? out : act[k & 1];
+        a.x = static_cast<const half_t*>(in);
+        a.out = static_cast<half_t*>(o);
+        a.ctl = reinterpret_cast<unsigned long long*>(L0->ws + L0->lay.step);
+        a.lens = reinterpret_cast<int32_t*>(L0->ws + L0->lay.lens);
+        a.eps = c.ln_eps;
+        a.bump = last ? 1 : 0;
+        a.M = L0->batch; a.H = H; a.F = F; a.heads = c.heads; a.max_seq = c.max_seq;
+        for (int l = 0; l < a.n_layers; ++l) {
+            const eet_layer_weights& w = layers[l0 + l]->w;
+            half_t* kv = reinterpret_cast<half_t*>(static_cast<char*>(kv_cache) + (size_t)(l0 + l) * layer_cache_bytes);
+            auto p = [](const void* q) { return static_cast<const half_t*>(q); };
+            a.layer[l] = StepLayer{p(w.ln1_g), p(w.ln1_b), p(w.w_qkv), p(w.b_qkv), p(w.w_o), p(w.b_o), p(w.ln2_g), p(w.ln2_b), p(w.w_fc1),
+                                   p(w.b_fc1), p(w.w_fc2), p(w.b_fc2), kv, kv + (size_t)c.max_batch * H * c.max_seq};
+        }
+        EET_LAUNCH(launch_decode_layers(a, step_bytes > kMemorySideCacheBytes, s), "decode layers");
+        in = o;
+    }
+    return EET_OK;
+}
+
 int eet_decode_step(eet_layer_t* L, const void* tokens, void* out, void* kv_cache, void* hip_stream) {
     if (!L || !tokens || !out || !kv_cache) return fail(EET_ERR_INVALID_ARG, "eet_decode_step: null argument");
     if (L->batch == 0) return fail(EET_ERR_STATE, "eet_decode_step: no prefill has been run on this layer");
@@ -503,7 +556,8 @@ int eet_decode_step(eet_layer_t* L, const void* tokens, void* out, void* kv_cach
     for (int b = 0; b < B; ++b)
         if (L->host_lens[b] + 1 > c.max_seq)
             return fail(EET_ERR_CAPACITY, "eet_decode_step: sequence %d is at the cache capacity %d", b, c.max_seq);
-    const int rc = enqueue_decode(L, tokens, out, kv_cache, static_cast<hipStream_t>(hip_stream), true, L, kv_cache);
+    const int rc = decodes_in_one_launch(L) ? enqueue_decode_layers(&L, 1, tokens, out, kv_cache, 0, nullptr, static_cast<hipStream_t>(hip_stream))
+                                            : enqueue_decode(L, tokens, out, kv_cache, static_cast<hipStream_t>(hip_stream), true, L, kv_cache);
     if (rc != EET_OK) return rc;
     for (int b = 0; b < B; ++b) L->host_lens[b] += 1;
     return EET_OK;
@@ -526,7 +580,8 @@ int eet_restore(eet_layer_t* L, const int32_t* cache_lens, int32_t batch, void* 
     if (!L) return fail(EET_ERR_INVALID_ARG, "eet_restore: null argument");
     SeqLens lens;
     if (const int rc = check_restore("eet_restore", L->cfg, cache_lens, batch, lens)) return rc;
-    EET_LAUNCH(launch_set_cache_lens(lens, batch, reinterpret_cast<int32_t*>(L->ws + L->lay.lens), static_cast<hipStream_t>(hip_stream)),
+    EET_LAUNCH(launch_set_cache_lens(lens, batch, reinterpret_cast<int32_t*>(L->ws + L->lay.lens), step_area(L, batch),
+                                     static_cast<hipStream_t>(hip_stream)),
                "set cache lengths");
     L->batch = batch;
     for (int b = 0; b < batch; ++b) L->host_lens[b] = cache_lens[b];
@@ -642,7 +697,7 @@ static int stack_prefill(const char* who, bool left_padded, eet_stack_t* st, con
         void* o = (l == st->n_layers - 1) ? out : static_cast<void*>(st->ws + st->act[l & 1]);
         char* kv = static_cast<char*>(kv_cache) + (size_t)l * st->layer_cache_bytes;
         const int rc = enqueue_prefill(st->layers[l], lens, batch, padded_len, T, max_len, in, o, kv, s, true, left_padded,
-                                       stack_layer_needs_setup(l, st->n_layers));
+                                       stack_layer_needs_setup(l, st->n_layers), l == 0);
         if (rc != EET_OK) return rc;
         st->layers[l]->batch = batch;
         in = o;
@@ -686,6 +741,10 @@ int eet_stack_encode(eet_stack_t* st, const int32_t* q_lens, int32_t batch, int3
 }
 
 static int stack_enqueue_decode(eet_stack* st, const void* tokens, void* out, void* kv_cache, hipStream_t s) {
+    if (decodes_in_one_launch(st->layers[0])) {
+        void* act[2] = {st->ws + st->act[0], st->ws + st->act[1]};
+        return enqueue_decode_layers(st->layers, st->n_layers, tokens, out, kv_cache, st->layer_cache_bytes, act, s);
+    }
     const void* in = tokens;
     for (int l = 0; l < st->n_layers; ++l) {
         const bool last = l == st->n_layers - 1;
@@ -754,7 +813,8 @@ int eet_stack_restore(eet_stack_t* st, const int32_t* cache_lens, int32_t batch,
     SeqLens lens;
     if (const int rc = check_restore("eet_stack_restore", st->cfg, cache_lens, batch, lens)) return rc;
     eet_layer* L0 = st->layers[0];                       // the layers share one set of device-side lengths
-    EET_LAUNCH(launch_set_cache_lens(lens, batch, reinterpret_cast<int32_t*>(L0->ws + L0->lay.lens), static_cast<hipStream_t>(hip_stream)),
+    EET_LAUNCH(launch_set_cache_lens(lens, batch, reinterpret_cast<int32_t*>(L0->ws + L0->lay.lens), step_area(L0, batch),
+                                     static_cast<hipStream_t>(hip_stream)),
                "set cache lengths");
     for (int l = 0; l < st->n_layers; ++l) st->layers[l]->batch = batch;
     st->batch = batch;

@@ -26,14 +26,20 @@ hipError_t launch_softmax_maskfree(half_t* scores, const SeqLens& lens, int batc
 hipError_t launch_prefill_setup(const SeqLens& lens, int batch, int S, int width, int32_t* cache_lens,
                                 int32_t* cu_seqlens, int32_t* row_map, half_t* out, hipStream_t s,
                                 bool left_padded = false);
+// The exchange area of decode_step.hip, for the launches that set the cache lengths: its first kStepCtlWords words become zero,
+// the others all ones.  words == 0: none.
+struct StepArea {
+    unsigned long long* ctl;
+    uint32_t words;
+};
 // The same together with the LayerNorm of the valid rows of x ([batch, S, width]) into the packed rows of y, where the width allows.
 bool prefill_setup_takes_layernorm(int width);
 hipError_t launch_prefill_setup_layernorm(const SeqLens& lens, int batch, int S, int width, int32_t* cache_lens, int32_t* cu_seqlens,
                                           int32_t* row_map, half_t* out, bool left_padded, const half_t* x, const half_t* gamma,
-                                          const half_t* beta, half_t* y, float eps, hipStream_t s);
+                                          const half_t* beta, half_t* y, float eps, StepArea step, hipStream_t s);
 
 // cache_lens[b] = lens.len[b] for b < batch (DEVICE array of the layer's workspace)
-hipError_t launch_set_cache_lens(const SeqLens& lens, int batch, int32_t* cache_lens, hipStream_t s);
+hipError_t launch_set_cache_lens(const SeqLens& lens, int batch, int32_t* cache_lens, StepArea step, hipStream_t s);
 
 // ---- operands of the launches that follow, pulled towards the memory-side cache -------------
 // A latency-bound decode projection leaves CUs idle (64-128 workgroups on 256 CUs).  Extra workgroups of the same
@@ -173,6 +179,37 @@ struct AttnDecodeArgs {
 int attention_decode_splits(int batch, int heads, int capacity);
 size_t attention_decode_scratch_bytes(int batch, int heads, int d, int splits);
 hipError_t launch_attention_decode(const AttnDecodeArgs& a, hipStream_t s);
+
+// ---- all layers of a decode step in one launch (decode_step.hip) ----------------------------------
+constexpr int kStepLayers = 32;          // layers per launch (their pointers travel as kernel arguments)
+constexpr int kStepCtlWords = 32;        // ctl[0]: next item and layer number; ctl[16]: items that have reset their part; a line each
+struct StepLayer {
+    const half_t *ln1_g, *ln1_b, *w_qkv, *b_qkv, *w_o, *b_o, *ln2_g, *ln2_b, *w_fc1, *b_fc1, *w_fc2, *b_fc2;
+    half_t *k_cache, *v_cache;
+};
+struct StepBuffer {                      // part of an exchange set (words): blocks of 2^log_cols columns, one producer each
+    uint32_t at, block;
+    int log_cols;
+};
+struct StepArgs {
+    const half_t* x;                     // [M, H] input of the first layer
+    half_t* out;                         // [M, H] output of the last
+    unsigned long long* ctl;             // kStepCtlWords words, then the two exchange sets (decode_step_bytes)
+    int32_t* lens;                       // DEVICE: cached keys; += 1 by the launch when bump
+    float eps;
+    int bump, M, H, F, heads, max_seq, n_layers;
+    // set by the launcher
+    unsigned long long* ex;
+    StepBuffer bx, bqkv, bctx, by, bf;
+    uint32_t set_words;
+    int d, splits, n_qkv, n_att, n_out, n_ffn1, per_layer, items;
+    StepLayer layer[kStepLayers];
+};
+// Rows, widths the kernel takes, and the bytes of its exchange area (0: not its problem).  The area is set up by the launches
+// that set the cache lengths (launch_prefill_setup_layernorm, launch_set_cache_lens) for the same rows.
+bool decode_step_fits(int rows, int hidden, int heads, int ffn);
+size_t decode_step_bytes(int rows, int hidden, int heads, int ffn, int max_seq);
+hipError_t launch_decode_layers(StepArgs& a, bool read_once, hipStream_t s);
 
 // ---- operators around the stack (model.hip) ------------------------------------------------------
 // out[b*S + i] = wte[ids[b*S + i]] + wpe[i - first] for first <= i < first + lens.len[b] (first = 0, or S - lens.len[b]

@@ -521,6 +521,12 @@ __global__ __launch_bounds__(64) void prefill_setup(SeqLens lens, int batch, int
     }
 }
 
+// Part `part` of `parts` of the exchange area of a decode step (kernels.hpp: StepArea), `nthreads` threads
+__device__ __forceinline__ void set_up_step_area(const StepArea& st, int part, int parts, int tid, int nthreads) {
+    for (uint32_t i = part * nthreads + tid; i < st.words; i += parts * nthreads) st.ctl[i] = i < (uint32_t)kStepCtlWords ? 0ull : ~0ull;
+}
+static int step_area_blocks(const StepArea& st, int nthreads) { return (int)((st.words + 4 * nthreads - 1) / (4 * nthreads)); }
+
 // The same set-up and the first LayerNorm of a prefill in one launch, rows of up to 2048 (width % 8 == 0): one wave per padded
 // row, which is either zeroed in `out` or normalised into its packed place in `y`.  A short prompt is a chain of dependent
 // launches, and this is one of eight less (4 prompts of 16 to 64 tokens, hidden 768: 51.5 -> 49.6 us for the layer).
@@ -528,8 +534,13 @@ template <int NV, bool FEW>
 __global__ __launch_bounds__(256) void prefill_setup_layernorm(SeqLens lens, int batch, int S, int width, int32_t* __restrict__ cache_lens,
                                                                int32_t* __restrict__ cu_seqlens, int32_t* __restrict__ row_map, half_t* out,
                                                                int left, const half_t* x, const half_t* __restrict__ gamma,
-                                                               const half_t* __restrict__ beta, half_t* __restrict__ y, float eps) {
+                                                               const half_t* __restrict__ beta, half_t* __restrict__ y, float eps, StepArea step) {
     const int lane = threadIdx.x & 63;
+    const int row_blocks = (batch * S + 3) / 4;
+    if ((int)blockIdx.x >= row_blocks) {                      // workgroups past the rows: the exchange area of the decode steps to come
+        set_up_step_area(step, (int)blockIdx.x - row_blocks, (int)gridDim.x - row_blocks, threadIdx.x, 256);
+        return;
+    }
     const int r = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     if (r == 0) {
         static_assert(kMaxBatch == 2 * kWave, "two lengths per lane");
@@ -567,11 +578,11 @@ __global__ __launch_bounds__(256) void prefill_setup_layernorm(SeqLens lens, int
 bool prefill_setup_takes_layernorm(int width) { return width % 8 == 0 && width <= 2048; }
 hipError_t launch_prefill_setup_layernorm(const SeqLens& lens, int batch, int S, int width, int32_t* cache_lens, int32_t* cu_seqlens,
                                           int32_t* row_map, half_t* out, bool left_padded, const half_t* x, const half_t* gamma,
-                                          const half_t* beta, half_t* y, float eps, hipStream_t s) {
-    const dim3 grid((batch * S + 3) / 4);
+                                          const half_t* beta, half_t* y, float eps, StepArea step, hipStream_t s) {
+    const dim3 grid((batch * S + 3) / 4 + step_area_blocks(step, 256));
     int64_t rows = 0;
     for (int b = 0; b < batch; ++b) rows += lens.len[b];
-#define EET_SETUP_LN_AT(NV, FEW) hipLaunchKernelGGL((prefill_setup_layernorm<NV, FEW>), grid, dim3(256), 0, s, lens, batch, S, width, cache_lens, cu_seqlens, row_map, out, left_padded ? 1 : 0, x, gamma, beta, y, eps)
+#define EET_SETUP_LN_AT(NV, FEW) hipLaunchKernelGGL((prefill_setup_layernorm<NV, FEW>), grid, dim3(256), 0, s, lens, batch, S, width, cache_lens, cu_seqlens, row_map, out, left_padded ? 1 : 0, x, gamma, beta, y, eps, step)
 #define EET_SETUP_LN(NV) do { if (rows < kLayerNormWaveRows) EET_SETUP_LN_AT(NV, true); else EET_SETUP_LN_AT(NV, false); } while (0)
     if (width <= 512) EET_SETUP_LN(1);
     else if (width <= 1024) EET_SETUP_LN(2);
@@ -583,12 +594,13 @@ hipError_t launch_prefill_setup_layernorm(const SeqLens& lens, int batch, int S,
 
 // The device-side cache lengths set from the host (resuming from a saved K/V cache): one small fill kernel, so the
 // call can sit in a stream or a captured graph like every other.
-__global__ __launch_bounds__(kMaxBatch) void set_cache_lens(SeqLens lens, int batch, int32_t* __restrict__ cache_lens) {
-    if ((int)threadIdx.x < batch) cache_lens[threadIdx.x] = lens.len[threadIdx.x];
+__global__ __launch_bounds__(kMaxBatch) void set_cache_lens(SeqLens lens, int batch, int32_t* __restrict__ cache_lens, StepArea step) {
+    if (blockIdx.x > 0) set_up_step_area(step, (int)blockIdx.x - 1, (int)gridDim.x - 1, threadIdx.x, kMaxBatch);
+    else if ((int)threadIdx.x < batch) cache_lens[threadIdx.x] = lens.len[threadIdx.x];
 }
 
-hipError_t launch_set_cache_lens(const SeqLens& lens, int batch, int32_t* cache_lens, hipStream_t s) {
-    hipLaunchKernelGGL(set_cache_lens, dim3(1), dim3(kMaxBatch), 0, s, lens, batch, cache_lens);
+hipError_t launch_set_cache_lens(const SeqLens& lens, int batch, int32_t* cache_lens, StepArea step, hipStream_t s) {
+    hipLaunchKernelGGL(set_cache_lens, dim3(1 + step_area_blocks(step, kMaxBatch)), dim3(kMaxBatch), 0, s, lens, batch, cache_lens, step);
     return hipGetLastError();
 }
 

@@ -1,0 +1,119 @@
+"""Decode steps that run as one launch (csrc/decode_step.hip), at the edges of what it takes: waves without a unit of K and
+with unequal numbers of them, 1 to 16 rows and the rows just past each variant, both head sizes, key ranges that are merged,
+empty or end at the new token, the widest layer, one that is just past the narrow variant, and stacks of more layers than a launch takes."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import eet_oracle as orc
+from paper_2104_12470_amd import workloads as wl
+from tests.gpu_util import dev, gate, host
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def eet():
+    from paper_2104_12470_amd import eet as binding
+    binding.lib()
+    assert torch.cuda.is_available()
+    return binding
+
+
+def layer_and_oracle(eet, w, layer=0):
+    W = wl.layer_weights(w, layer, random_affine=True)
+    cfg = eet.make_config(w.hidden, w.heads, w.ffn, w.batch, w.padded_len, w.max_seq, w.ln_eps)
+    return eet.DecoderLayer(cfg, {k: torch.from_numpy(v) for k, v in W.items()}), orc.DecoderLayerOracle(W, w.heads, w.batch, w.max_seq, w.ln_eps)
+
+
+@pytest.mark.parametrize("hidden,heads,ffn,batch,len_hi,max_seq", [
+    (64, 1, 64, 1, 9, 16),             # one unit of K: seven waves idle
+    (192, 3, 320, 3, 20, 32),          # three and five units
+    (576, 9, 1536, 9, 12, 24),         # nine units; the variant of 16 rows
+    (1024, 16, 4096, 16, 8, 16),       # the narrow variant full
+    (1088, 17, 4352, 8, 8, 16),        # just past it
+    (1024, 8, 4160, 5, 8, 16),         # past it by the feed-forward width alone
+    (2048, 16, 8192, 2, 8, 16),        # the widest
+    (256, 2, 704, 2, 300, 1040),       # four key ranges per pair, the last ones empty
+    (256, 4, 640, 4, 144, 528),        # four ranges; key 144 is the first of its range when it is the new token
+    (128, 2, 256, 8, 70, 74),          # the variant of 8 rows; up to the capacity
+])
+def test_steps_against_the_oracle(eet, hidden, heads, ffn, batch, len_hi, max_seq):
+    steps = 4
+    w = wl.Workload(f"step{hidden}x{ffn}", 31, hidden, heads, ffn, 1, batch, len_hi, max(1, len_hi - 7), len_hi, steps, max_seq)
+    layer, oracle = layer_and_oracle(eet, w)
+    lens, x = wl.lengths(w), wl.prompt_embeddings(w)
+    layer.prefill(dev(x), lens)
+    oracle.prefill(x, lens)
+    for k in range(steps):
+        xs = wl.decode_embeddings(w, k)
+        got = layer.decode_step(dev(xs))
+        torch.cuda.synchronize()
+        gate(host(got), oracle.decode_step(xs), f"step {k}")
+    assert layer.cache_lens(batch) == oracle.lens[:batch].tolist()
+    kc, vc = layer.cache_views()
+    for b in range(batch):
+        n = int(lens[b]) + steps
+        gate(host(kc[b, :, :n]), oracle.k_cache[b, :, :n], f"K cache b={b}", 1.5e-2, 1.5e-3)
+        gate(host(vc[b, :, :n]), oracle.v_cache[b, :, :n], f"V cache b={b}", 1.5e-2, 1.5e-3)
+    layer.close()
+
+
+@pytest.mark.parametrize("n_layers", [2, 3, 33])
+def test_stack_equals_the_layer_chain(eet, n_layers):
+    """Layers of one launch exchange their rows on the device; one after the other they go through memory.  The same bits, also after a
+    second prefill with another number of sequences (another layout of the exchange area) and where a step takes two launches (33 layers)."""
+    w = wl.Workload(f"chain{n_layers}", 37, 192, 3, 448, n_layers, 3, 24, 3, 24, 6, 32)
+    cfg = eet.make_config(w.hidden, w.heads, w.ffn, w.batch, w.padded_len, w.max_seq, w.ln_eps)
+    Ws = [{k: torch.from_numpy(v) for k, v in wl.layer_weights(w, li, random_affine=True).items()} for li in range(n_layers)]
+    stack = eet.DecoderStack(cfg, Ws)
+    layers = [eet.DecoderLayer(cfg, W) for W in Ws]
+    lens, x = wl.lengths(w), wl.prompt_embeddings(w)
+    stream = torch.cuda.Stream()
+    with torch.cuda.stream(stream):
+        for B in (3, 1, 2):
+            h = dev(x[:B])
+            stack.prefill(h, lens[:B])
+            for layer in layers:
+                h = layer.prefill(h, lens[:B])
+            for k in range(5):
+                h = dev(wl.decode_embeddings(w, k)[:B])
+                got = stack.decode_step(h)
+                for layer in layers:
+                    h = layer.decode_step(h)
+                stream.synchronize()
+                assert np.array_equal(host(got).view(np.uint16), host(h).view(np.uint16)), (B, k)
+    stack.close()
+    for layer in layers:
+        layer.close()
+
+
+def test_two_streams_at_once(eet):
+    """Two stacks whose steps run side by side on two streams, more items each than the device holds: both finish, with the
+    bits that each gives on its own."""
+    w = wl.Workload("twostreams", 41, 512, 8, 2048, 12, 4, 16, 16, 16, 6, 32)
+    cfg = eet.make_config(w.hidden, w.heads, w.ffn, w.batch, w.padded_len, w.max_seq, w.ln_eps)
+    Ws = [{k: torch.from_numpy(v) for k, v in wl.layer_weights(w, li, random_affine=True).items()} for li in range(12)]
+    lens, x = wl.lengths(w), wl.prompt_embeddings(w)
+    xs = [dev(wl.decode_embeddings(w, k)) for k in range(6)]
+    stacks, streams = [eet.DecoderStack(cfg, Ws) for _ in range(3)], [torch.cuda.Stream() for _ in range(3)]
+    outs = [[torch.empty_like(xs[0]) for _ in xs] for _ in stacks]
+    torch.cuda.synchronize()
+    for i in range(3):
+        with torch.cuda.stream(streams[i]):
+            stacks[i].prefill(dev(x), lens)
+    torch.cuda.synchronize()
+    for k in range(6):                                         # stack 0 alone, then 1 and 2 together
+        with torch.cuda.stream(streams[0]):
+            stacks[0].decode_step(xs[k], outs[0][k])
+    torch.cuda.synchronize()
+    for k in range(6):
+        for i in (1, 2):
+            with torch.cuda.stream(streams[i]):
+                stacks[i].decode_step(xs[k], outs[i][k])
+    torch.cuda.synchronize()
+    for i in (1, 2):
+        for k in range(6):
+            assert np.array_equal(host(outs[i][k]).view(np.uint16), host(outs[0][k]).view(np.uint16)), (i, k)
+    for st in stacks:
+        st.close()
