@@ -187,7 +187,7 @@ int eet_layer_destroy(eet_layer_t* layer) {
 // Cuts the K of a bias + residual projection of `L` where that pays; `sums`: where in the workspace its sums lie.  The rule and
 // the sizes are those layout_of reserved by.
 static void cut_projection(eet_layer* L, GemmArgs& g, size_t sums) {
-    const int ranges = gemm_k_ranges(g.M, g.N, g.K);
+    const int ranges = g.res_row_map != nullptr || g.out_row_map != nullptr ? prompt_k_ranges(g.M, g.N, g.K) : gemm_k_ranges(g.M, g.N, g.K);
     if (ranges <= 1) return;
     g.k_ranges = ranges;
     g.part = reinterpret_cast<float*>(L->ws + sums);

@@ -1661,7 +1661,7 @@ hipError_t launch_gemm(const GemmArgs& a, Epilogue epi, hipStream_t s) {
                                         a.N % (16 * stream_column_blocks(a, epi)) == 0)) return hipErrorInvalidValue;
     if (a.row_stats_in != nullptr && !(takes_row_stats(a, epi) && !try_flat(a, epi, nullptr, true) && stream_column_blocks(a, epi) != 0)) return hipErrorInvalidValue;
     // the cut along K is the caller's choice, and its operands are its own
-    if (a.k_ranges > 1 && (epi != EPI_BIAS_RES || a.part == nullptr || a.k_ranges != gemm_k_ranges(a.M, a.N, a.K) || (a.ldy != 0 && a.ldy != a.N) || a.ln_gamma != nullptr || a.pf.blocks != 0)) return hipErrorInvalidValue;
+    if (a.k_ranges > 1 && (epi != EPI_BIAS_RES || a.part == nullptr || a.k_ranges != (a.res_row_map != nullptr || a.out_row_map != nullptr ? prompt_k_ranges(a.M, a.N, a.K) : gemm_k_ranges(a.M, a.N, a.K)) || (a.ldy != 0 && a.ldy != a.N) || a.ln_gamma != nullptr || a.pf.blocks != 0)) return hipErrorInvalidValue;
     if (a.fin_gamma != nullptr && a.k_ranges <= 1) return hipErrorInvalidValue;
     if (a.M > 16 && rows_stream(a, epi)) return launch_rows(a, epi, s);
     if (epi == EPI_BIAS && is_plain(a) && short_k_wide(a.M, a.N, a.K)) {

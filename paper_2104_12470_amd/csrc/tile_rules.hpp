@@ -36,8 +36,7 @@ inline int rows_ranges(int M, int N, int K) {
 // Weights below 18 MB (24 MB for at most 32 rows) stay with the row slices (48 x 2048 x 2048 7.9 us in slices, 9.1 here; 17 x 1536 x
 // 6144 8.6 and 10.5; but 48 x 1536 x 6144 13.3 and 11.2, 64 x 3072 x 3072 17.9 and 11.9).  At most 32 rows want no cut in eight
 // (32 x 2048 x 8192 11.7 against 13.4), more than 64 rows without a cut a long K (96 x 6144 x 2048 12.1 against 16.0).  These floors
-// are measured on calls that the slices can take, a decode step's and the operators'.  A prompt's output and second feed-forward
-// projection carry row maps and are never sliced: below the floors they run on the 64-row tiles, and the cut is not measured there.
+// are measured on calls that the slices can take, a decode step's and the operators' (prompts: prompt_k_ranges).
 inline bool rows_stream_pays(int M, int N, int K, int ranges) {
     if (M <= 16 || K % 128 != 0 || N % 64 != 0) return false;
     // a cut that still leaves half of the CUs idle: 20 to 31 x 1984 x 7936 in two ranges (62 workgroups) took half again as long as the slices
@@ -52,11 +51,28 @@ inline int gemm_k_ranges(int M, int N, int K) {
     const int s = N <= kFinishRowsMaxWidth ? rows_ranges(M, N, K) : 1;
     return s > 1 && rows_stream_pays(M, N, K, s) ? s : 1;
 }
+// A prompt's output and second feed-forward projection carry row maps, so the row slices cannot take them: with up to 256 rows and weights
+// below the floors above they ran on N/64 or 2N/64 workgroups through the whole K (37 x 1024 x 4096: 16 of them, 15 us).  The cut
+// pays there for much smaller weights, with ranges of 256 columns up to 64 rows, and it takes the LayerNorm launch behind the output
+// projection along.  us per layer of a prompt, before -> now (stacks of 8): hidden 768, 20 rows 44 -> 36, 64 47 -> 39, 128 50 ->
+// 47, 250 51 -> 47; 1024, 37 rows 50 -> 40, 100 53 -> 47; 1536, 20 rows 69 -> 48, 64 61 -> 55; 2048, 20 rows 81 -> 56, 64 72 -> 63, 250
+// 88 -> 84; one layer of 1280 x 5120, 64 rows 63 -> 49.  Where it stops: 20 to 64 rows of hidden 256 (a quarter of a million weights: 32 -> 34);
+// 65 to 128 of 640 x 1664 (one million: 44.2 -> 45.3); 160 of hidden 1024 (output projection, one million: 47 -> 48.5); 400 and 700 rows
+// (1024 54 -> 55, 63 -> 66; 768 and 2048 gain 4 % at 400 and nothing at 700).
+inline int prompt_k_ranges(int M, int N, int K) {
+    if (M > 16 && M <= 256 && K % 128 == 0 && N % 64 == 0 && N <= kFinishRowsMaxWidth && (int64_t)N * K >= (M <= 64 ? (int64_t)1 << 19 : (int64_t)2 << 20)) {
+        const int tiles = (M + rows_tile(M) - 1) / rows_tile(M) * ((N + 63) / 64), least = M <= 64 ? 256 : 512;
+        int s = 256 / tiles;
+        s = s < K / least ? s : K / least;
+        if (s > 1) return s > 8 ? 8 : s;
+    }
+    return gemm_k_ranges(M, N, K);
+}
 // The largest fp32 sums, in bytes, that a cut N x K projection of up to max_rows rows leaves (0: never cut).  The number of ranges
 // depends on the row tiles alone, so the most rows of each number of them are all there is to ask (a walk over every row
 // count made the creation of a layer handle take 17 us instead of 1, and a stack does it for every layer).
 inline int64_t gemm_cut_bytes(int M, int N, int K) {
-    const int ranges = gemm_k_ranges(M, N, K);
+    const int p = prompt_k_ranges(M, N, K), ranges = p > 1 ? p : gemm_k_ranges(M, N, K);
     return ranges > 1 ? (int64_t)ranges * M * N * (int64_t)sizeof(float) : 0;
 }
 inline int64_t gemm_cut_bytes_up_to(int64_t max_rows, int N, int K) {
