@@ -211,9 +211,10 @@ inline TileChoice choose_tile(int M, int N, int K) {
 // per CU: two groups of waves per tile, each with half of the K steps and LDS stages of its own, put twice the loads in
 // flight (rows x K x N: 128 x 4096 x 4096 23.8 -> 16.5 us, 96 x 16384 x 4096 101.7 -> 67.7 us, 512 x 4096 x 1024 23.3 -> 16.5 us; 1959 x
 // 4096 x 1024 24.8 against 30.1 with the best of the tiles below; four groups with two stages each were slower than two with
-// three).
+// three).  From K = 640 on, five steps per group: prompts of 20 to 900 rows through layers of 640, 768 and 896 take 0.88 to 0.98 of the time
+// that they took with one group (768: 160 rows 46.8 -> 44.4 us per layer, 600 57.9 -> 53.7); at 256 and 384 there is nothing to gain.
 inline TileChoice tile_for(int M, int N, int K) {
-    const bool k_split = K % 128 == 0 && K >= 1024;
+    const bool k_split = K % 128 == 0 && K >= 640;
     const int wg128 = ((M + 127) / 128) * ((N + 63) / 64), wg64 = ((M + 63) / 64) * ((N + 63) / 64);
     if (wg128 < 128 || (k_split && wg128 <= 256)) {
         if (k_split && wg64 <= 256) return kTile64Split;              // (1000 x 1024 x 4096: 25.1 -> 20.1)
