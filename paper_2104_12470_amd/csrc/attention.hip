@@ -20,6 +20,7 @@ constexpr float kLog2e = 1.4426950408889634f;
 // ============================================================================================
 // Prefill: flash-style, v_mfma_f32_32x32x16_f16
 // ============================================================================================
+// Heads of 64 and prompts of more than 256 tokens; the two kernels that follow take the others.
 // Workgroup = 4 waves = 128 query rows of one (sequence, head); wave w owns rows 32w..32w+31.
 // Key tiles of 64 are staged through LDS: K row-major, V transposed (so that both MFMA operands
 // of P.V read 8-byte runs along the key axis).  The kernel computes S^T = K Q^T, which leaves
@@ -46,9 +47,9 @@ __device__ __forceinline__ bool prefill_pair_and_tile(const AttnPrefillArgs& a, 
     return pair < a.batch * a.heads;
 }
 
-template <int D, bool CAUSAL>
+template <bool CAUSAL>
 __global__ __launch_bounds__(256, 2) void attn_prefill(AttnPrefillArgs a, SeqLens lens) {
-    constexpr int BQ = 128, BKV = 64;
+    constexpr int D = 64, BQ = 128, BKV = 64;
     constexpr int LDKS = D + 8;         // K tile row stride (halfs): 16-byte reads conflict-free
     constexpr int LDVT = BKV + 4;       // V^T tile row stride: 34 dwords, so the 8-byte reads of 32 rows cover all 64 banks once
     constexpr int KVEC = BKV * D / 8 / 256;   // 16-byte vectors of K per thread per tile
@@ -122,15 +123,9 @@ __global__ __launch_bounds__(256, 2) void attn_prefill(AttnPrefillArgs a, SeqLen
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
             half_t* dst = &Vt[(v_dc * 8 + e) * LDVT + v_jg * RPT];
-            if (RPT == 4) {
-                half4v t;
-                t[0] = rv[0][e]; t[1] = rv[1][e]; t[2] = rv[2 % RPT][e]; t[3] = rv[3 % RPT][e];
-                *reinterpret_cast<half4v*>(dst) = t;
-            } else {
-                half2v t;
-                t[0] = rv[0][e]; t[1] = rv[1][e];
-                *reinterpret_cast<half2v*>(dst) = t;
-            }
+            half2v t;
+            t[0] = rv[0][e]; t[1] = rv[1][e];
+            *reinterpret_cast<half2v*>(dst) = t;
         }
     };
 
@@ -584,16 +579,191 @@ __global__ __launch_bounds__(512) void attn_prefill_wide(AttnPrefillArgs a, SeqL
         }
 }
 
+// --------------------------------------------------------------------------------------------
+// Prefill, prompts of up to 512 tokens (heads of 128) or 256 (of 64): 16 query rows per wave
+// --------------------------------------------------------------------------------------------
+// The arithmetic of attn_prefill in 16 x 16 x 32 matrix instructions: 8 waves for 128 query rows (4 for 64 where a launch has few of
+// them), so a key tile is half as long a chain for every wave (16 scores per lane instead of 32) and the SIMDs have twice as many
+// waves to choose from.  K and V tiles lie row-major in two LDS buffers, filled through registers one tile ahead: one barrier per key
+// tile, and V is turned around by the LDS transpose read instead of eight scalar stores per vector.  What bounds it: per key tile the CU
+// reads 128 KB of fragments (1024 cycles) and a SIMD issues 1100 cycles of vector and 512 of matrix instructions, in phases
+// that the barrier keeps in step; loads two tiles ahead changed nothing (14.3 -> 13.9 us, heads of 128 21.3 -> 22.8).
+// us per launch, attn_prefill -> this (8 waves): 16 prompts of 64-192 tokens, 16 heads of 64, no sequence mask 10.0 -> 9.2; 8 of 256-512 14.7 -> 14.3;
+// one of 37 tokens 4.5 -> 4.1; 128 of 256-512, 32 heads 281 -> 272; heads of 128: 16 of 64-192, 32 heads 28.3 -> 24.6, 8 of
+// 256-512, 16 heads 23.1 -> 21.3, 64 of 256-512, 32 heads 266 -> 247.  Longer prompts read every fragment for half as many
+// rows: 16 of 512-1024, 32 heads of 64 85 -> 91, 16 of 1024-2048, 64 heads 552 -> 588; they stay where they were.
+__device__ __forceinline__ float max_xor16(float x) {
+    const unsigned u = __builtin_bit_cast(unsigned, x);
+    const auto r = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+    const unsigned r0 = r[0], r1 = r[1];                     // (copied first: see max_xor32)
+    return fmaxf(__builtin_bit_cast(float, r0), __builtin_bit_cast(float, r1));
+}
+
+template <int D, bool CAUSAL, int NW>
+__global__ __launch_bounds__(64 * NW) void attn_prefill16(AttnPrefillArgs a, SeqLens lens) {
+    constexpr int BQ = 16 * NW, BKV = 64, KK = D / 32, DB = D / 16;
+    constexpr int LDK = D + 8;               // halfs between K rows: the 16-byte reads of 16 rows cover every bank once
+    constexpr int LDV = D + 16;              // and between V rows: so do the transpose reads of 8 rows x 32 bytes
+    constexpr int VEC = BKV * D / 8 / (64 * NW);   // 16-byte vectors of K, and of V, per thread and tile
+    constexpr int CH = D / 8;
+    __shared__ __attribute__((aligned(16))) half_t Ks[2][BKV * LDK];
+    __shared__ __attribute__((aligned(16))) half_t Vs[2][BKV * LDV];
+
+    int pair, tile;
+    if (!prefill_pair_and_tile(a, pair, tile)) return;
+    const int b = pair / a.heads, g = pair % a.heads;
+    const int L = lens.len[b];
+    const int i0 = tile * BQ;
+    if (i0 >= L) return;                                          // pad queries are never visited
+    int row0 = b * a.S;
+    if (a.packed) row0 = tokens_before(lens, b, threadIdx.x & 63);
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int fr = lane & 15, G = lane >> 4;
+    const int iw0 = i0 + wave * 16;
+    const int i = iw0 + fr;                  // this lane's query
+    const bool row_ok = i < L;
+
+    half8v qf[KK];                           // Q^T (B operand): query fr, depth kk*32 + G*8 .. +8
+    {
+        const half_t* qp = a.q + (int64_t)(row0 + (row_ok ? i : L - 1)) * a.hidden + g * D + G * 8;
+#pragma unroll
+        for (int kk = 0; kk < KK; ++kk) qf[kk] = *reinterpret_cast<const half8v*>(qp + kk * 32);
+    }
+    const int64_t head_off = ((int64_t)b * a.heads + g) * a.capacity * D;
+    const half_t* kbase = a.k_cache + head_off;
+    const half_t* vbase = a.v_cache + head_off;
+
+    float4v o[DB];
+#pragma unroll
+    for (int db = 0; db < DB; ++db) o[db] = float4v{0.f, 0.f, 0.f, 0.f};
+    float m = -INFINITY, l = 0.f;
+    const float c = rsqrtf((float)D) * kLog2e;
+    const int jlast = (CAUSAL && i0 + BQ - 1 < L - 1) ? i0 + BQ - 1 : L - 1;
+    const int ntiles = jlast / BKV + 1;
+
+    half8v rk[VEC], rv[VEC];
+    auto gload = [&](int jt) {
+#pragma unroll
+        for (int v = 0; v < VEC; ++v) {
+            const int idx = tid + v * (64 * NW), ch = idx % CH;
+            int jr = jt * BKV + idx / CH;
+            jr = jr < L ? jr : L - 1;        // slots >= L are never read (they may hold anything)
+            rk[v] = *reinterpret_cast<const half8v*>(kbase + (int64_t)jr * D + ch * 8);
+            rv[v] = *reinterpret_cast<const half8v*>(vbase + (int64_t)jr * D + ch * 8);
+        }
+    };
+    auto sstore = [&](int buf) {
+#pragma unroll
+        for (int v = 0; v < VEC; ++v) {
+            const int idx = tid + v * (64 * NW), row = idx / CH, ch = idx % CH;
+            *reinterpret_cast<half8v*>(&Ks[buf][row * LDK + ch * 8]) = rk[v];
+            *reinterpret_cast<half8v*>(&Vs[buf][row * LDV + ch * 8]) = rv[v];
+        }
+    };
+
+    gload(0);
+    sstore(0);
+    __syncthreads();
+    for (int jt = 0; jt < ntiles; ++jt) {
+        const int buf = jt & 1, j0 = jt * BKV;
+        if (jt + 1 < ntiles) gload(jt + 1);                       // in flight during the arithmetic
+        if (iw0 < L && !(CAUSAL && j0 > iw0 + 15)) {              // else: no valid row, or the whole tile is in the future of this wave's rows
+            // S^T: st[kb][r] belongs to key j0 + kb*16 + 4G + r and query fr
+            float4v st[4];
+#pragma unroll
+            for (int kb = 0; kb < 4; ++kb) st[kb] = float4v{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int kk = 0; kk < KK; ++kk)
+#pragma unroll
+                for (int kb = 0; kb < 4; ++kb) {
+                    const half8v kf = *reinterpret_cast<const half8v*>(&Ks[buf][(kb * 16 + fr) * LDK + kk * 32 + G * 8]);
+                    st[kb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(kf, qf[kk], st[kb], 0, 0, 0);
+                }
+            float tmax = -INFINITY;
+            const int jmax = CAUSAL ? i : L - 1;                  // last key this lane's query sees
+            if (CAUSAL ? j0 + BKV - 1 > iw0 : j0 + BKV > L) {
+#pragma unroll
+                for (int kb = 0; kb < 4; ++kb)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        if (j0 + kb * 16 + G * 4 + r > jmax) st[kb][r] = -INFINITY;
+                        tmax = fmaxf(tmax, st[kb][r]);
+                    }
+            } else {
+#pragma unroll
+                for (int kb = 0; kb < 4; ++kb)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) tmax = fmaxf(tmax, st[kb][r]);
+            }
+            tmax = max_xor32(max_xor16(tmax));
+            // the reference of the exponentials and its slack: see attn_prefill
+            constexpr float kSlack = 8.0f;
+            const float tm = tmax * c;
+            if (__any(tm > m + kSlack)) {
+                const float m_new = fmaxf(m, tm);
+                const float alpha = __builtin_amdgcn_exp2f(m - m_new);
+                l *= alpha;
+                m = m_new;
+#pragma unroll
+                for (int db = 0; db < DB; ++db)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) o[db][r] *= alpha;
+            }
+            half8v pf[2];                                         // P^T (B operand): slots 0..3 of lane group G are keys 4G.. of block 2p, 4..7 of block 2p+1
+#pragma unroll
+            for (int kb = 0; kb < 4; ++kb)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const float p = __builtin_amdgcn_exp2f(__builtin_fmaf(st[kb][r], c, -m));
+                    l += p;
+                    pf[kb >> 1][(kb & 1) * 4 + r] = (half_t)p;
+                }
+            // O^T += V^T P^T: the transpose read hands lane fr of a group the halfs V[4G + 0..3][fr]; lane r supplies row 4G + r/4, columns (r%4)*4
+#pragma unroll
+            for (int p = 0; p < 2; ++p)
+#pragma unroll
+                for (int db = 0; db < DB; ++db) {
+                    const char* vp = reinterpret_cast<const char*>(&Vs[buf][(p * 32 + G * 4 + (fr >> 2)) * LDV + db * 16 + (fr & 3) * 4]);
+                    const half4v lo = lds_read_tr16(vp), hi = lds_read_tr16(vp + 16 * LDV * 2);
+                    const half8v vf = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+                    o[db] = __builtin_amdgcn_mfma_f32_16x16x32_f16(vf, pf[p], o[db], 0, 0, 0);
+                }
+        }
+        if (jt + 1 < ntiles) {
+            sstore(buf ^ 1);                                      // read last before the barrier that closed the tile before
+            __syncthreads();
+        }
+    }
+    l += __shfl_xor(l, 16, kWave);
+    l += __shfl_xor(l, 32, kWave);
+    if (!row_ok) return;
+    const float inv = 1.0f / l;
+    half_t* op = a.ctx + (int64_t)(row0 + i) * a.hidden + g * D + G * 4;
+#pragma unroll
+    for (int db = 0; db < DB; ++db) {
+        half4v t;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) t[e] = (half_t)(o[db][e] * inv);
+        *reinterpret_cast<half4v*>(op + db * 16) = t;
+    }
+}
+
 // K/V of the pairs of one chunk of a prefill launch (16 to 48 pairs: two to six per XCD)
 constexpr size_t kChunkKvBytes = (size_t)64 << 20;
 hipError_t launch_attention_prefill(const AttnPrefillArgs& a, const SeqLens& lens, hipStream_t s) {
-    // 256-row kernel for heads of 128 and prompts beyond 512 tokens (measured, one call: equal to the 128-row kernel
-    // from 512 to 1024 tokens, 15-20 % ahead from 2048 on, 6-15 % behind up to 512, where twice as many workgroups
-    // matter more than the deeper pipeline); heads of 64 have half the matrix work per score, and the 128-row kernel
-    // (softmax over 64 keys at a time) is the faster one there.
-    const bool wide = a.d == 128 && a.max_len > 512;
-    const int bq = wide ? 256 : 128;
-    const dim3 grid(a.heads * a.batch, (a.max_len + bq - 1) / bq), block(wide ? 512 : 256);
+    // 256-row kernel for heads of 128 and prompts beyond 512 tokens (measured, one call: equal to 128 rows of 32 per wave from 512 to
+    // 1024 tokens, 15-20 % ahead from 2048 on, 6-15 % behind up to 512, where twice as many workgroups matter more than the
+    // deeper pipeline); heads of 64 have half the matrix work per score, and the 128-row kernel (softmax over 64 keys at
+    // a time) is the faster one there.
+    // Up to 512 tokens of heads of 128, and up to 256 of heads of 64 (8 prompts of 256-512 in a stack of 24: 3277 against 3285 us for the
+    // pass), the kernel of 16 rows per wave, with 64 query rows per workgroup where 128 would not give every CU one (4 prompts of
+    // 400-512 tokens, 4 heads of 128: 16.9 -> 13.9 us; 8 of 200-400, 4 heads of 64 10.9 -> 9.6; with 512 workgroups and more 3 to 20 % behind).
+    const bool fine = a.max_len <= (a.d == 128 ? 512 : 256), wide = !fine && a.d == 128;
+    int64_t tiles128 = 0;
+    for (int b = 0; b < a.batch; ++b) tiles128 += (int64_t)a.heads * ((lens.len[b] + 127) / 128);
+    const bool few = fine && tiles128 < 256;
+    const int bq = wide ? 256 : few ? 64 : 128;
+    const dim3 grid(a.heads * a.batch, (a.max_len + bq - 1) / bq), block(wide || (fine && !few) ? 512 : 256);
     // In chunks of pairs once the K/V of the launch is more than the memory-side cache holds: with the tiles of all
     // pairs in turn, a pair's K/V then comes from HBM again for every one of its tiles (16 prompts of 1024-2048
     // tokens, 96 heads: 6.3 GB fetched for 1.2 GB of K/V and 0.6 GB of Q).  TFLOP/s by pairs per chunk, one call
@@ -616,15 +786,23 @@ hipError_t launch_attention_prefill(const AttnPrefillArgs& a, const SeqLens& len
     w.chunk_pairs = chunk >= pairs ? 0 : chunk;
     w.chunk_tiles = (int)grid.y;
     const dim3 wgrid = w.chunk_pairs ? dim3((pairs + chunk - 1) / chunk * chunk * grid.y) : grid;
-    if (wide) {
+    if (fine) {
+#define EET_FINE(D, C) do { if (few) hipLaunchKernelGGL((attn_prefill16<D, C, 4>), wgrid, block, 0, s, w, lens); \
+                            else hipLaunchKernelGGL((attn_prefill16<D, C, 8>), wgrid, block, 0, s, w, lens); } while (0)
+        if (a.d == 128) {
+            if (a.causal) EET_FINE(128, true);
+            else EET_FINE(128, false);
+        } else {
+            if (a.causal) EET_FINE(64, true);
+            else EET_FINE(64, false);
+        }
+#undef EET_FINE
+    } else if (wide) {
         if (a.causal) hipLaunchKernelGGL((attn_prefill_wide<128, true>), wgrid, block, 0, s, w, lens);
         else hipLaunchKernelGGL((attn_prefill_wide<128, false>), wgrid, block, 0, s, w, lens);
-    } else if (a.causal) {
-        if (a.d == 128) hipLaunchKernelGGL((attn_prefill<128, true>), wgrid, block, 0, s, w, lens);
-        else hipLaunchKernelGGL((attn_prefill<64, true>), wgrid, block, 0, s, w, lens);
     } else {
-        if (a.d == 128) hipLaunchKernelGGL((attn_prefill<128, false>), wgrid, block, 0, s, w, lens);
-        else hipLaunchKernelGGL((attn_prefill<64, false>), wgrid, block, 0, s, w, lens);
+        if (a.causal) hipLaunchKernelGGL((attn_prefill<true>), wgrid, block, 0, s, w, lens);
+        else hipLaunchKernelGGL((attn_prefill<false>), wgrid, block, 0, s, w, lens);
     }
     return hipGetLastError();
 }
