@@ -582,8 +582,8 @@ __global__ __launch_bounds__(512) void attn_prefill_wide(AttnPrefillArgs a, SeqL
 // --------------------------------------------------------------------------------------------
 // Prefill, prompts of up to 512 tokens (heads of 128) or 256 (of 64): 16 query rows per wave
 // --------------------------------------------------------------------------------------------
-// The arithmetic of attn_prefill in 16 x 16 x 32 matrix instructions: 8 waves for 128 query rows (4 for 64 where a launch has few of
-// them), so a key tile is half as long a chain for every wave (16 scores per lane instead of 32) and the SIMDs have twice as many
+// The arithmetic of attn_prefill in 16 x 16 x 32 matrix instructions: 8 waves for 128 query rows (4 for 64 where a launch has few
+// tiles), so a key tile is half as long a chain for every wave (16 scores per lane instead of 32) and the SIMDs have twice as many
 // waves to choose from.  K and V tiles lie row-major in two LDS buffers, filled through registers one tile ahead: one barrier per key
 // tile, and V is turned around by the LDS transpose read instead of eight scalar stores per vector.  What bounds it: per key tile the CU
 // reads 128 KB of fragments (1024 cycles) and a SIMD issues 1100 cycles of vector and 512 of matrix instructions, in phases
@@ -756,12 +756,13 @@ hipError_t launch_attention_prefill(const AttnPrefillArgs& a, const SeqLens& len
     // deeper pipeline); heads of 64 have half the matrix work per score, and the 128-row kernel (softmax over 64 keys at
     // a time) is the faster one there.
     // Up to 512 tokens of heads of 128, and up to 256 of heads of 64 (8 prompts of 256-512 in a stack of 24: 3277 against 3285 us for the
-    // pass), the kernel of 16 rows per wave, with 64 query rows per workgroup where 128 would not give every CU one (4 prompts of
-    // 400-512 tokens, 4 heads of 128: 16.9 -> 13.9 us; 8 of 200-400, 4 heads of 64 10.9 -> 9.6; with 512 workgroups and more 3 to 20 % behind).
+    // pass), the kernel of 16 rows per wave, with 64 query rows per workgroup where a launch has
+    // few tiles.  us, 128 / 64 rows per workgroup, by tiles of 128: heads of 128: 16 tiles 16.9 / 13.9, 120 7.9 / 7.4, 128 10.4 / 9.8, 192 8.3 / 8.8,
+    // 220 11.6 / 13.6, 232 19.1 / 22.2; of 64 (half the LDS per workgroup): 100 10.9 / 9.6, 224 6.1 / 6.0, 304 9.2 / 8.9, 320 9.1 / 8.7, 512 8.6 / 10.8.
     const bool fine = a.max_len <= (a.d == 128 ? 512 : 256), wide = !fine && a.d == 128;
     int64_t tiles128 = 0;
     for (int b = 0; b < a.batch; ++b) tiles128 += (int64_t)a.heads * ((lens.len[b] + 127) / 128);
-    const bool few = fine && tiles128 < 256;
+    const bool few = fine && tiles128 < (a.d == 128 ? 160 : 320);
     const int bq = wide ? 256 : few ? 64 : 128;
     const dim3 grid(a.heads * a.batch, (a.max_len + bq - 1) / bq), block(wide || (fine && !few) ? 512 : 256);
     // In chunks of pairs once the K/V of the launch is more than the memory-side cache holds: with the tiles of all

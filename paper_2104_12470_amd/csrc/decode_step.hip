@@ -48,7 +48,8 @@ constexpr int kAgentScope = 16;                    // cache policy of a buffer l
 constexpr int kSWaves = 8, kSThreads = 64 * kSWaves;
 constexpr int kSRow = 72;                          // halfs of a staged row: 128 bytes + 16
 constexpr int kSUnitsH = 4, kSUnitsF = 16;         // units of 64 K values a wave holds: K = hidden up to 2048, K = ffn up to 8192
-// Polls before an item gives up (its input then reads as NaN and the launch still ends): seconds, where a wait takes microseconds.
+// Polls before an item gives up (its input then reads as NaN and the launch still ends): a tenth of a second at the least, where a wait takes
+// microseconds and whatever it waits for is running.
 constexpr int kSpinLimit = 1 << 20;
 
 __device__ __forceinline__ word_t ld_word(const word_t* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }

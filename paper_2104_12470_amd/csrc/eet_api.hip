@@ -373,6 +373,7 @@ static int enqueue_decode(eet_layer* L, const void* tokens, void* out, void* kv_
     half_t* kc = static_cast<half_t*>(kv_cache);
     half_t* vc = kc + (size_t)c.max_batch * H * c.max_seq;
 
+    // (Layers that decode_layers takes, kernels.hpp, do not come here.)
     // Small layers are launch-bound in decode: there the two LayerNorms run inside the projections
     // that consume them (each workgroup recomputes the row statistics of the <= 16 token rows).
     // Measured break-even is near 16 MB of FFN-1 weights; larger layers keep the separate row kernel.
