@@ -700,7 +700,8 @@ bool decode_step_fits(int rows, int hidden, int heads, int ffn) {
            hidden <= 64 * kSWaves * kSUnitsH && ffn <= 64 * kSWaves * kSUnitsF;
 }
 
-static void step_layout(StepArgs& a) {
+// Where the buffers of a step of a.M rows lie in an exchange set; the words that they take
+static uint32_t step_layout(StepArgs& a) {
     const int d = a.H / a.heads, log_h = 6;                   // 64 columns per item
     a.d = d;
     a.splits = step_splits(a.M, a.heads, a.max_seq);
@@ -717,19 +718,22 @@ static void step_layout(StepArgs& a) {
     if (a.splits > 1) at = a.bctx.at + (uint32_t)(a.M * a.heads * a.splits * step_range_words(d));
     a.by = buffer(a.H, log_h);
     a.bf = buffer(a.F, log_h);
-    a.set_words = at;
+    return at;
 }
 
-size_t decode_step_bytes(int rows, int hidden, int heads, int ffn, int max_seq) {
-    if (!decode_step_fits(rows, hidden, heads, ffn)) return 0;
-    StepArgs a{};
-    a.M = rows; a.H = hidden; a.heads = heads; a.F = ffn; a.max_seq = max_seq;
-    step_layout(a);
-    return (kStepCtlWords + 2 * (size_t)a.set_words) * sizeof(word_t);
+uint32_t decode_step_set_words(int max_rows, int hidden, int heads, int ffn, int max_seq) {
+    uint32_t most = 0;
+    for (int rows = 1; rows <= max_rows && decode_step_fits(rows, hidden, heads, ffn); ++rows) {
+        StepArgs a{};
+        a.M = rows; a.H = hidden; a.heads = heads; a.F = ffn; a.max_seq = max_seq;
+        const uint32_t words = step_layout(a);
+        most = words > most ? words : most;
+    }
+    return most;
 }
 
 hipError_t launch_decode_layers(StepArgs& a, bool read_once, hipStream_t s) {
-    step_layout(a);
+    if (step_layout(a) > a.set_words) return hipErrorInvalidValue;
     a.ex = a.ctl + kStepCtlWords;
     const int log_h = a.bqkv.log_cols;
     a.n_qkv = 3 * a.H >> log_h;

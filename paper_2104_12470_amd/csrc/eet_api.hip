@@ -51,6 +51,7 @@ constexpr int kFfnPadFrom = 32768;
 // projection at all (29 us -> 71 us).
 struct WorkspaceLayout {
     size_t lens, cu, row_map, buf_f, cut, buf_a, buf_b, buf_y, part, step, row_stats, total;
+    uint32_t step_set_words;           // of one exchange set of the decode steps that run as one launch (0: none do)
     int splits;
 };
 
@@ -91,22 +92,19 @@ WorkspaceLayout layout_of(const eet_layer_config* c) {
     w.buf_y = off;   off = align_up(off + 2 * T * H, 256);
     w.splits = attention_decode_splits(c->max_batch, c->heads, c->max_seq);
     w.part = off;
-    // sized for the split count of any batch <= max_batch (fewer sequences -> more splits)
+    // sized for the split count of any batch <= max_batch (fewer sequences -> more splits) that does not run as one launch
     size_t part = 0;
     for (int b = 1; b <= c->max_batch; ++b) {
+        if (decode_step_fits(b, c->hidden, c->heads, c->ffn)) continue;
         const size_t p = attention_decode_scratch_bytes(b, c->heads, H / c->heads,
                                                         attention_decode_splits(b, c->heads, c->max_seq));
         part = p > part ? p : part;
     }
     off = align_up(off + part, 256);
-    // the exchange area of the decode steps that run as one launch (decode_step.hip), which need no partials: in the same place
-    w.step = w.part;
-    size_t step = 0;
-    for (int b = 1; b <= c->max_batch && b <= 16; ++b) {
-        const size_t p = decode_step_bytes(b, c->hidden, c->heads, c->ffn, c->max_seq);
-        step = p > step ? p : step;
-    }
-    if (w.step + step > off) off = align_up(w.step + step, 256);
+    // the exchange area of those that do (decode_step.hip); no other step writes to it
+    w.step = off;
+    w.step_set_words = decode_step_set_words(c->max_batch, c->hidden, c->heads, c->ffn, c->max_seq);
+    if (w.step_set_words > 0) off = align_up(off + (kStepCtlWords + 2 * (size_t)w.step_set_words) * sizeof(unsigned long long), 256);
     // LayerNorm statistics handed from the output projection of a decode step to the first feed-forward projection:
     // (mean, squared deviations) per row and workgroup of the producer, at most hidden/16 workgroups of 16 rows
     w.row_stats = off;
@@ -193,11 +191,10 @@ static void cut_projection(eet_layer* L, GemmArgs& g, size_t sums) {
     g.part = reinterpret_cast<float*>(L->ws + sums);
 }
 
-// The exchange area of `L`'s decode steps of `batch` sequences, to be set up wherever the cache lengths are set
-static StepArea step_area(const eet_layer* L, int batch) {
-    const eet_layer_config& c = L->cfg;
-    return StepArea{reinterpret_cast<unsigned long long*>(L->ws + L->lay.step),
-                    (uint32_t)(decode_step_bytes(batch, c.hidden, c.heads, c.ffn, c.max_seq) / sizeof(unsigned long long))};
+// The exchange area of `L`'s decode steps, to be set up wherever the cache lengths are set
+static StepArea step_area(const eet_layer* L) {
+    const uint32_t set_words = L->lay.step_set_words;
+    return StepArea{reinterpret_cast<unsigned long long*>(L->ws + L->lay.step), set_words > 0 ? kStepCtlWords + 2 * set_words : 0};
 }
 
 #define EET_LAUNCH(expr, what)                        \
@@ -232,7 +229,7 @@ static int enqueue_prefill(eet_layer* L, const SeqLens& lens, int batch, int pad
     if (index_setup && prefill_setup_takes_layernorm(H)) {
         EET_LAUNCH(launch_prefill_setup_layernorm(lens, batch, padded_len, H, d_lens, d_cu, d_map, static_cast<half_t*>(out), left_padded,
                                                   x, (const half_t*)L->w.ln1_g, (const half_t*)L->w.ln1_b, bufA, c.ln_eps,
-                                                  causal && sets_lengths ? step_area(L, batch) : StepArea{}, s),
+                                                  causal && sets_lengths ? step_area(L) : StepArea{}, s),
                    "prefill set-up and layernorm 1");
     } else {
         if (index_setup)
@@ -530,6 +527,7 @@ static int enqueue_decode_layers(eet_layer* const* layers, int n, const void* to
         a.x = static_cast<const half_t*>(in);
         a.out = static_cast<half_t*>(o);
         a.ctl = reinterpret_cast<unsigned long long*>(L0->ws + L0->lay.step);
+        a.set_words = L0->lay.step_set_words;
         a.lens = reinterpret_cast<int32_t*>(L0->ws + L0->lay.lens);
         a.eps = c.ln_eps;
         a.bump = last ? 1 : 0;
@@ -581,7 +579,7 @@ int eet_restore(eet_layer_t* L, const int32_t* cache_lens, int32_t batch, void* 
     if (!L) return fail(EET_ERR_INVALID_ARG, "eet_restore: null argument");
     SeqLens lens;
     if (const int rc = check_restore("eet_restore", L->cfg, cache_lens, batch, lens)) return rc;
-    EET_LAUNCH(launch_set_cache_lens(lens, batch, reinterpret_cast<int32_t*>(L->ws + L->lay.lens), step_area(L, batch),
+    EET_LAUNCH(launch_set_cache_lens(lens, batch, reinterpret_cast<int32_t*>(L->ws + L->lay.lens), step_area(L),
                                      static_cast<hipStream_t>(hip_stream)),
                "set cache lengths");
     L->batch = batch;
@@ -814,7 +812,7 @@ int eet_stack_restore(eet_stack_t* st, const int32_t* cache_lens, int32_t batch,
     SeqLens lens;
     if (const int rc = check_restore("eet_stack_restore", st->cfg, cache_lens, batch, lens)) return rc;
     eet_layer* L0 = st->layers[0];                       // the layers share one set of device-side lengths
-    EET_LAUNCH(launch_set_cache_lens(lens, batch, reinterpret_cast<int32_t*>(L0->ws + L0->lay.lens), step_area(L0, batch),
+    EET_LAUNCH(launch_set_cache_lens(lens, batch, reinterpret_cast<int32_t*>(L0->ws + L0->lay.lens), step_area(L0),
                                      static_cast<hipStream_t>(hip_stream)),
                "set cache lengths");
     for (int l = 0; l < st->n_layers; ++l) st->layers[l]->batch = batch;

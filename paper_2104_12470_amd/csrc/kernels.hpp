@@ -194,21 +194,24 @@ struct StepBuffer {                      // part of an exchange set (words): blo
 struct StepArgs {
     const half_t* x;                     // [M, H] input of the first layer
     half_t* out;                         // [M, H] output of the last
-    unsigned long long* ctl;             // kStepCtlWords words, then the two exchange sets (decode_step_bytes)
+    unsigned long long* ctl;             // kStepCtlWords words, then the two exchange sets
+    uint32_t set_words;                  // words of a set: decode_step_set_words of the layer's configuration, whatever M is
     int32_t* lens;                       // DEVICE: cached keys; += 1 by the launch when bump
     float eps;
     int bump, M, H, F, heads, max_seq, n_layers;
     // set by the launcher
     unsigned long long* ex;
     StepBuffer bx, bqkv, bctx, by, bf;
-    uint32_t set_words;
     int d, splits, n_qkv, n_att, n_out, n_ffn1, per_layer, items;
     StepLayer layer[kStepLayers];
 };
-// Rows, widths the kernel takes, and the bytes of its exchange area (0: not its problem).  The area is set up by the launches
-// that set the cache lengths (launch_prefill_setup_layernorm, launch_set_cache_lens) for the same rows.
+// Rows and widths the kernel takes.
 bool decode_step_fits(int rows, int hidden, int heads, int ffn);
-size_t decode_step_bytes(int rows, int hidden, int heads, int ffn, int max_seq);
+// Words of an exchange set that holds a step of any number of rows up to max_rows that the kernel takes (0: it takes none).  A set has
+// this size, is set up (by the launches that set the cache lengths: launch_prefill_setup_layernorm, launch_set_cache_lens) and is
+// emptied whole, whatever the rows of a step: a caller may have recorded a step of another number of sequences than those
+// of the latest prefill or of the step before, and replay it now.
+uint32_t decode_step_set_words(int max_rows, int hidden, int heads, int ffn, int max_seq);
 hipError_t launch_decode_layers(StepArgs& a, bool read_once, hipStream_t s);
 
 // ---- operators around the stack (model.hip) ------------------------------------------------------

@@ -117,3 +117,39 @@ def test_two_streams_at_once(eet):
             assert np.array_equal(host(outs[i][k]).view(np.uint16), host(outs[0][k]).view(np.uint16)), (i, k)
     for st in stacks:
         st.close()
+
+
+@pytest.mark.parametrize("max_batch,latest", [(5, 2), (18, 2), (18, 18)])
+def test_recorded_steps_of_other_numbers_of_sequences(eet, max_batch, latest):
+    """Steps that a caller recorded for 5 sequences and for 1 are replayed in turn after a prefill of `latest` sequences, between eager steps
+    of that many (18: launch by launch, through the attention partials).  Each is another layout of the exchange area; the sequences that a
+    step shares with the latest prefill get what the oracle gives, and the others disturb nothing."""
+    w = wl.Workload(f"recorded{max_batch}x{latest}", 47, 256, 2, 704, 1, max_batch, 40, 9, 40, 8, 1040)
+    W = wl.layer_weights(w, 0, random_affine=True)
+    cfg = eet.make_config(w.hidden, w.heads, w.ffn, max_batch, w.padded_len, w.max_seq, w.ln_eps)
+    layer = eet.DecoderLayer(cfg, {k: torch.from_numpy(v) for k, v in W.items()})
+    lens, x, xs = wl.lengths(w), wl.prompt_embeddings(w), wl.decode_embeddings(w, 0)
+    recorded = {}
+    for B in (5, 1):
+        layer.prefill(dev(x[:B]), lens[:B])
+        tok, g = dev(xs[:B]), torch.cuda.CUDAGraph()
+        out = torch.empty_like(tok)
+        torch.cuda.synchronize()
+        with torch.cuda.graph(g):
+            layer.decode_step(tok, out)
+        recorded[B] = (g, tok, out)
+    layer.prefill(dev(x[:latest]), lens[:latest])
+    oracles = [orc.DecoderLayerOracle(W, w.heads, 1, w.max_seq, w.ln_eps) for _ in range(2)]
+    for b, o in enumerate(oracles):
+        o.prefill(x[b:b + 1], lens[b:b + 1])
+    for k, B in enumerate((5, latest, 1, 5, 5, latest, latest, 1, 1, latest, 5)):
+        if B == latest:
+            got = layer.decode_step(dev(xs[:B]))
+        else:
+            recorded[B][0].replay()
+            got = recorded[B][2]
+        torch.cuda.synchronize()
+        for b in range(min(B, 2)):
+            gate(host(got)[b:b + 1], oracles[b].decode_step(xs[b:b + 1]), f"step {k} of {B}, sequence {b}")
+    assert layer.cache_lens(latest)[:2] == [int(o.lens[0]) for o in oracles]
+    layer.close()
