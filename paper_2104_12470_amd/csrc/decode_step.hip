@@ -27,7 +27,9 @@
 //               which writes x(g+1) into the other set, once resets >= (g+1) * (QKV items).
 //   progress    An item waits only for items with lower numbers, and a workgroup takes its number from a counter when it starts
 //               to run, so whatever an item waits for runs already or has finished: no assumption about how many workgroups are resident, in
-//               which order they start, or what else runs on the device.  The waits are bounded all the same (kSpinLimit).
+//               which order they start, or what else runs on the device.  The waits are bounded all the same (kSpinLimit), and one that
+//               gives up says so in ctl before its item hands anything on: from then on the exchange sets may hold words of another layer, so
+//               every output of this launch and of those that follow is NaN until the area is set up again (prefill, restore).
 //
 // K/V rows of earlier tokens are ordinary memory (written by earlier launches); the new token's K and V row reaches the attention
 // through the exchange set, and the cache for the steps that follow.
@@ -48,8 +50,9 @@ constexpr int kAgentScope = 16;                    // cache policy of a buffer l
 constexpr int kSWaves = 8, kSThreads = 64 * kSWaves;
 constexpr int kSRow = 72;                          // halfs of a staged row: 128 bytes + 16
 constexpr int kSUnitsH = 4, kSUnitsF = 16;         // units of 64 K values a wave holds: K = hidden up to 2048, K = ffn up to 8192
-// Polls before an item gives up (its input then reads as NaN and the launch still ends): a tenth of a second at the least, where a wait takes
-// microseconds and whatever it waits for is running.
+// Polls before an item gives up (the launch still ends): a tenth of a second at the least, where a wait takes microseconds and
+// whatever it waits for is running.  (The loops below end in one place, `ok` or the bound: with a way out for each the compiler copies
+// the loop, a quarter more code for the kernel.)
 constexpr int kSpinLimit = 1 << 20;
 
 __device__ __forceinline__ word_t ld_word(const word_t* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
@@ -74,6 +77,7 @@ struct StepSmem {
     float red[kSWaves][16 * 68];                   // [wave][row][up to 64 columns + 4]
     float stat[kSWaves][16][2];                    // [wave][row] mean and squared deviations of the wave's share of the row
     word_t ticket;
+    int gave_up;                                   // a wait of this item came to its bound
 };
 
 template <int CTRL>
@@ -95,36 +99,56 @@ struct Where {
     word_t* other;                                 // ... and of layers g-1 and g+1
 };
 
+// A wait of this item came to its bound: said in ctl, and in memory, before anything that follows from it.  (At the wait itself, where it
+// costs the chain nothing: a flag looked at once, before the item hands its result on, is 10.56 -> 10.72 us per layer-step of 24 x hidden 1024.)
+__device__ __forceinline__ void give_up(const StepArgs& a, StepSmem& sm) {
+    sm.gave_up = 1;
+    __hip_atomic_fetch_or(a.ctl, (word_t)kStepGaveUp, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+}
+
 // Thread 0 waits until the exchange set is this layer's, then for one word of the phase before the one whose output the item
 // needs: the tight polling that follows lasts one phase instead of a whole layer.  `input`: a word of the input itself, for the QKV
 // projection, whose faster items empty the set of that earlier word as soon as they have all of theirs; looked at now and then only, since
-// every look at a line that is still to be written makes the write slower.
-__device__ __forceinline__ void wait_resets(const StepArgs& a, uint32_t layers) {
+// every look at a line that is still to be written makes the write slower.  (Giving up on that word loses nothing: the input
+// itself is waited for next.)
+__device__ __forceinline__ void wait_resets(const StepArgs& a, StepSmem& sm, uint32_t layers) {
     const uint32_t* resets = reinterpret_cast<const uint32_t*>(a.ctl + 16);
     const uint32_t target = layers * (uint32_t)a.n_qkv;
-    for (int spin = 0; spin < kSpinLimit; ++spin) {
-        if ((int32_t)(__hip_atomic_load(resets, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) - target) >= 0) break;
+    int spin = 0;
+    while (true) {
+        if ((int32_t)(__hip_atomic_load(resets, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) - target) >= 0) return;
+        if (++spin == kSpinLimit) break;
         __builtin_amdgcn_s_sleep(16);
     }
+    give_up(a, sm);
 }
-__device__ __forceinline__ void gate(const StepArgs& a, const Where& w, const word_t* before, const word_t* input, bool emptied_by_this_layer) {
+__device__ __forceinline__ void gate(const StepArgs& a, const Where& w, StepSmem& sm, const word_t* before, const word_t* input, bool emptied_by_this_layer) {
     if (w.tid == 0) {
-        wait_resets(a, w.g);
+        wait_resets(a, sm, w.g);
         if (before != nullptr)
             for (int spin = 0; spin < kSpinLimit; ++spin) {
                 if (ld_word(before) != kEmpty) break;
                 if (input != nullptr && spin % 16 == 15 && ld_word(input) != kEmpty) break;
                 __builtin_amdgcn_s_sleep(4);
             }
-        if (emptied_by_this_layer) wait_resets(a, w.g + 1u);
+        if (emptied_by_this_layer) wait_resets(a, sm, w.g + 1u);
     }
     __syncthreads();
 }
 
-__device__ __forceinline__ word_t wait_word(const word_t* p) {
-    word_t v = ld_word(p);
-    for (int spin = 0; v == kEmpty && spin < kSpinLimit; ++spin) v = ld_word(p);
+__device__ __forceinline__ word_t wait_word(const StepArgs& a, StepSmem& sm, const word_t* p) {
+    word_t v;
+    int spin = 0;
+    do v = ld_word(p);
+    while ((v == kEmpty) & (++spin < kSpinLimit));
+    if (v == kEmpty) give_up(a, sm);
     return v;
+}
+
+__device__ __forceinline__ half4v no_result() {
+    const half_t nan = __builtin_bit_cast(half_t, (unsigned short)0x7e00);
+    return half4v{nan, nan, nan, nan};
 }
 
 // ---- one item of a projection: 16*NT columns, all rows (at most 16), K in units of 64 dealt round-robin to the waves ------------
@@ -236,9 +260,9 @@ __device__ __forceinline__ void project(const StepArgs& a, const Where& w, StepS
     const word_t* before = PH == kStepQkv ? (first ? nullptr : w.other + a.bf.at)
                          : PH == kStepOut ? w.set + a.bqkv.at
                          : PH == kStepFfn1 ? w.set + a.bctx.at : w.set + a.by.at;
-    gate(a, w, before, PH == kStepQkv ? w.set + in.at : nullptr, PH == kStepFfn2);
+    gate(a, w, sm, before, PH == kStepQkv ? w.set + in.at : nullptr, PH == kStepFfn2);
     if (RES && writer && !(PH == kStepOut && first))
-        er = __builtin_bit_cast(half4v, wait_word(w.set + word_at(PH == kStepOut ? a.bx : a.by, em, en)));
+        er = __builtin_bit_cast(half4v, wait_word(a, sm, w.set + word_at(PH == kStepOut ? a.bx : a.by, em, en)));
     halfE xv[STEPS];
     const bool mine = row < M;
     if (PH == kStepQkv && first) {
@@ -259,8 +283,10 @@ __device__ __forceinline__ void project(const StepArgs& a, const Where& w, StepS
                 const int at = (k % a.d) / 2;
                 for (int s0 = 0; s0 < a.splits; s0 += 2, p += 2 * stride) {      // a power of two of them
                     word_t v[2][E / 2 + 1];
-                    for (int spin = 0; spin < kSpinLimit; ++spin) {
-                        bool ok = true;
+                    int spin = 0;
+                    bool ok;
+                    do {
+                        ok = true;
 #pragma unroll
                         for (int r = 0; r < 2; ++r) {
 #pragma unroll
@@ -271,8 +297,8 @@ __device__ __forceinline__ void project(const StepArgs& a, const Where& w, StepS
                         for (int r = 0; r < 2; ++r)
 #pragma unroll
                             for (int e = 0; e <= E / 2; ++e) ok &= v[r][e] != kEmpty;
-                        if (ok) break;
-                    }
+                    } while (!ok & (++spin < kSpinLimit));
+                    if (!ok) give_up(a, sm);
 #pragma unroll
                     for (int r = 0; r < 2; ++r) {
                         const float2v ml = __builtin_bit_cast(float2v, v[r][E / 2]);
@@ -300,7 +326,9 @@ __device__ __forceinline__ void project(const StepArgs& a, const Where& w, StepS
         word_t v[STEPS][VW];
         const auto set = __builtin_amdgcn_make_buffer_rsrc(w.set, 0, (int)(a.set_words * sizeof(word_t)), 0x00027000);
         const uint32_t off = (uint32_t)(p - w.set);
-        for (int spin = 0; spin < kSpinLimit; ++spin) {
+        int spin = 0;
+        bool ok;
+        do {
             asm volatile("" ::: "memory");
             unsigned most = 0;                                 // a half that is kEmptyHalf is the largest there is
 #pragma unroll
@@ -324,8 +352,9 @@ __device__ __forceinline__ void project(const StepArgs& a, const Where& w, StepS
 #pragma unroll
                     for (int q = 0; q < VW; ++q) most = max(most, max((unsigned)v[s][q], (unsigned)(v[s][q] >> 32)));
                 }
-            if (__all(most != kEmptyHalf)) break;
-        }
+            ok = __all(most != kEmptyHalf);
+        } while (!ok & (++spin < kSpinLimit));
+        if (!ok) give_up(a, sm);
         struct Words { word_t w[VW]; };
 #pragma unroll
         for (int s = 0; s < STEPS; ++s) {
@@ -336,7 +365,10 @@ __device__ __forceinline__ void project(const StepArgs& a, const Where& w, StepS
         }
     }
     asm volatile("" ::: "memory");
+    uint32_t state = 0;
     if constexpr (PH == kStepFfn2) {
+        // looked at after all that this item's output comes from, and back before the output is written
+        if (last && writer) state = __hip_atomic_load(reinterpret_cast<const uint32_t*>(a.ctl), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         // everyone who reads the cache lengths in this step is an ancestor of this item's input
         if (last && a.bump && tile == 0) {
             __syncthreads();                                   // all waves have their share of the input: together, all of it
@@ -456,7 +488,7 @@ __device__ __forceinline__ void project(const StepArgs& a, const Where& w, StepS
     } else if constexpr (PH == kStepFfn1) {
         publish(w.set + word_at(a.bf, em, en), out);
     } else {
-        if (last) *reinterpret_cast<half4v*>(a.out + (size_t)em * H + en) = out;
+        if (last) *reinterpret_cast<half4v*>(a.out + (size_t)em * H + en) = state & kStepGaveUp || sm.gave_up ? no_result() : out;
         else publish(w.other + word_at(a.bx, em, en), out);
     }
     }
@@ -507,7 +539,7 @@ __device__ __forceinline__ void attend(const StepArgs& a, const Where& w, StepSm
 #pragma unroll
     for (int i = 0; i < PF; ++i)
         if (j0 + i * kSWaves * BK < ce) request(kr[i], vr[i], j0 + i * kSWaves * BK);
-    gate(a, w, w.layer == 0 ? nullptr : w.set + a.bx.at, nullptr, false);
+    gate(a, w, sm, w.layer == 0 ? nullptr : w.set + a.bx.at, nullptr, false);
     const word_t* qkv = w.set + word_at(a.bqkv, b, h * D + chunk * 8);
     const uint32_t to_k = (uint32_t)(a.H >> a.bqkv.log_cols) * a.bqkv.block;
     half8v qv, kn, vn;
@@ -515,7 +547,9 @@ __device__ __forceinline__ void attend(const StepArgs& a, const Where& w, StepSm
     {
         word_t v[6];
         const word_t* p = qkv;
-        for (int spin = 0; spin < kSpinLimit; ++spin) {
+        int spin = 0;
+        bool ok;
+        do {
             v[0] = ld_word(p);
             v[1] = ld_word(p + 1);
             if (take_new) {
@@ -524,10 +558,11 @@ __device__ __forceinline__ void attend(const StepArgs& a, const Where& w, StepSm
                 v[4] = ld_word(p + 2 * to_k);
                 v[5] = ld_word(p + 2 * to_k + 1);
             }
-            bool ok = v[0] != kEmpty && v[1] != kEmpty;
+            ok = v[0] != kEmpty && v[1] != kEmpty;
             if (take_new) ok &= v[2] != kEmpty && v[3] != kEmpty && v[4] != kEmpty && v[5] != kEmpty;
-            if (__all(ok)) break;
-        }
+            ok = __all(ok);
+        } while (!ok & (++spin < kSpinLimit));
+        if (!ok) give_up(a, sm);
         auto join = [](word_t x, word_t y) {
             return __builtin_shufflevector(__builtin_bit_cast(half4v, x), __builtin_bit_cast(half4v, y), 0, 1, 2, 3, 4, 5, 6, 7);
         };
@@ -655,12 +690,13 @@ __global__ __launch_bounds__(kSThreads, 2) void decode_layers(StepArgs a) {
     // (high half).  The launch's last workgroup to ask turns both on for the next launch.
     if (w.tid == 0) {
         const word_t t = __hip_atomic_fetch_add(a.ctl, (word_t)1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        if ((uint32_t)t == (uint32_t)a.items - 1u)
+        if (((uint32_t)t & ~kStepGaveUp) == (uint32_t)a.items - 1u)
             __hip_atomic_fetch_add(a.ctl, ((word_t)a.n_layers << 32) - (word_t)a.items, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         sm.ticket = t;
+        sm.gave_up = 0;
     }
     __syncthreads();
-    const uint32_t item = __builtin_amdgcn_readfirstlane((uint32_t)sm.ticket), g0 = __builtin_amdgcn_readfirstlane((uint32_t)(sm.ticket >> 32));
+    const uint32_t item = __builtin_amdgcn_readfirstlane((uint32_t)sm.ticket) & ~kStepGaveUp, g0 = __builtin_amdgcn_readfirstlane((uint32_t)(sm.ticket >> 32));
     if (item >= (uint32_t)a.items) return;
     w.layer = (int)(item / (uint32_t)a.per_layer);
     int r = (int)(item - (uint32_t)w.layer * (uint32_t)a.per_layer);

@@ -593,7 +593,13 @@ int eet_cache_lens(eet_layer_t* L, int32_t* out_host, void* hip_stream) {
     hipStream_t s = static_cast<hipStream_t>(hip_stream);
     EET_LAUNCH(hipMemcpyAsync(out_host, L->ws + L->lay.lens, sizeof(int32_t) * L->batch, hipMemcpyDeviceToHost, s),
                "copy of cache lengths");
+    uint32_t step_state = 0;
+    if (L->lay.step_set_words > 0)
+        EET_LAUNCH(hipMemcpyAsync(&step_state, L->ws + L->lay.step, sizeof(step_state), hipMemcpyDeviceToHost, s), "copy of the decode state");
     EET_LAUNCH(hipStreamSynchronize(s), "stream synchronise");
+    if (step_state & kStepGaveUp)
+        return fail(EET_ERR_HIP, "eet_cache_lens: a decode step gave up waiting for a part of its own launch: its output and all since are NaN "
+                                 "until the next prefill or restore");
     return EET_OK;
 }
 

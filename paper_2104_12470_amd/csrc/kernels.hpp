@@ -182,7 +182,8 @@ hipError_t launch_attention_decode(const AttnDecodeArgs& a, hipStream_t s);
 
 // ---- all layers of a decode step in one launch (decode_step.hip) ----------------------------------
 constexpr int kStepLayers = 32;          // layers per launch (their pointers travel as kernel arguments)
-constexpr int kStepCtlWords = 32;        // ctl[0]: next item and layer number; ctl[16]: items that have reset their part; a line each
+constexpr int kStepCtlWords = 32;        // ctl[0]: next item (and kStepGaveUp), layer number; ctl[16]: items that have reset their part; a line each
+constexpr uint32_t kStepGaveUp = 1u << 31;
 struct StepLayer {
     const half_t *ln1_g, *ln1_b, *w_qkv, *b_qkv, *w_o, *b_o, *ln2_g, *ln2_b, *w_fc1, *b_fc1, *w_fc2, *b_fc2;
     half_t *k_cache, *v_cache;

@@ -153,3 +153,46 @@ def test_recorded_steps_of_other_numbers_of_sequences(eet, max_batch, latest):
             gate(host(got)[b:b + 1], oracles[b].decode_step(xs[b:b + 1]), f"step {k} of {B}, sequence {b}")
     assert layer.cache_lens(latest)[:2] == [int(o.lens[0]) for o in oracles]
     layer.close()
+
+
+def step_control(layer):
+    """The words that the items of a decode step share (kernels.hpp: kStepCtlWords), found as what the set-up of the exchange area leaves: 32
+    words of zeros, then sets of all ones."""
+    words = layer.workspace.view(torch.int64)
+    now = words.cpu().numpy()
+    at = [i for i in range(0, len(now) - 256, 32) if not now[i:i + 32].any() and np.all(now[i + 32:i + 256] == -1)]
+    assert len(at) == 1
+    return words[at[0]:at[0] + 32]
+
+
+@pytest.mark.parametrize("how", ["said before", "a wait that ends by itself"])
+def test_a_wait_given_up_is_not_taken_for_a_result(eet, how):
+    """Once a wait inside a step has given up, the step and all that follow leave NaN, count as steps, and the lengths come back with an
+    error; a prefill or a restore makes the handle whole.  The wait is one that no item can end: the count of emptied parts starts far
+    below what they wait for, so each of them runs into its own bound."""
+    w = wl.Workload("gaveup", 53, 128, 2, 256, 1, 3, 9, 2, 9, 4, 32)
+    layer, oracle = layer_and_oracle(eet, w)
+    lens, x = wl.lengths(w), wl.prompt_embeddings(w)
+    layer.prefill(dev(x), lens)
+    oracle.prefill(x, lens)
+    torch.cuda.synchronize()
+    control = step_control(layer)
+    if how == "said before":
+        control[0] = 1 << 31
+    else:
+        control[16] = 0xfff00000
+    for k in range(2):
+        got = layer.decode_step(dev(wl.decode_embeddings(w, k)))
+        torch.cuda.synchronize()
+        assert np.all(np.isnan(host(got))), k
+        with pytest.raises(eet.EETError) as e:
+            layer.cache_lens(3)
+        assert e.value.code == eet.EET_ERR_HIP
+    eet.eet_restore(layer.handle, lens)
+    for k in range(2):
+        xs = wl.decode_embeddings(w, k)
+        got = layer.decode_step(dev(xs))
+        torch.cuda.synchronize()
+        gate(host(got), oracle.decode_step(xs), f"step {k}")
+    assert layer.cache_lens(3) == oracle.lens[:3].tolist()
+    layer.close()
