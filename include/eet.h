@@ -176,8 +176,9 @@ size_t eet_stack_workspace_bytes(const eet_layer_config *cfg, int32_t n_layers);
 /* weights: HOST array of n_layers structs of DEVICE pointers (borrowed).  workspace: DEVICE,
  * eet_stack_workspace_bytes, 256-byte aligned.  use_graph != 0: eet_stack_decode_step records its
  * launches into a HIP graph the first time it sees a (tokens, out, kv_cache) triple and replays
- * it afterwards (the graph is instantiated inside that call; it is skipped on the null stream
- * and while the caller is capturing the stream itself).  Errors as eet_layer_create. */
+ * it afterwards (the graph is instantiated inside that call, and once more when what the sequences hold
+ * outgrows the memory-side cache; it is skipped on the null stream and while the caller is capturing the
+ * stream itself).  Errors as eet_layer_create. */
 int eet_stack_create(const eet_layer_config *cfg, int32_t n_layers, const eet_layer_weights *weights,
                      void *workspace, int32_t use_graph, eet_stack_t **out_stack);
 

@@ -196,3 +196,41 @@ def test_a_wait_given_up_is_not_taken_for_a_result(eet, how):
         gate(host(got), oracle.decode_step(xs), f"step {k}")
     assert layer.cache_lens(3) == oracle.lens[:3].tolist()
     layer.close()
+
+
+def kernels_of(call):
+    from torch.profiler import ProfilerActivity, profile
+    with profile(activities=[ProfilerActivity.CUDA]) as p:
+        call()
+        torch.cuda.synchronize()
+    return [e.name for e in p.events()]
+
+
+def test_a_stack_counts_the_keys_its_sequences_hold(eet):
+    """Weights and K/V rows of a step that moves more than the memory-side cache (256 MiB) holds are loaded as read once, and what a step moves
+    grows with the sequences: two layers of hidden 1024 (50 MB of weights) pass the line at 25000 keys.  The recorded step changes with
+    it: direct launches and replays give the same bits on both sides, back and forth."""
+    layers, H, line = 2, 1024, (256 << 20) - 2 * 2 * 12 * 1024 * 1024
+    keys = line // (layers * 4 * H)                            # visible keys of both sequences together, the new tokens' among them: the last that fit
+    w = wl.Workload("held", 59, H, 16, 4 * H, layers, 2, 1, 1, 1, 4, keys // 2 + 8)
+    cfg = eet.make_config(w.hidden, w.heads, w.ffn, w.batch, w.padded_len, w.max_seq, w.ln_eps)
+    Ws = [{k: torch.from_numpy(v) for k, v in wl.layer_weights(w, li).items()} for li in range(layers)]
+    direct, graph = eet.DecoderStack(cfg, Ws, use_graph=False), eet.DecoderStack(cfg, Ws)
+    direct.kv_cache.copy_(torch.randn(direct.kv_cache.shape, dtype=torch.float16, device="cuda:0"))
+    graph.kv_cache.copy_(direct.kv_cache)
+    below = [keys // 2 - 1, keys - keys // 2 - 1]
+    tok, stream = dev(wl.decode_embeddings(w, 0)), torch.cuda.Stream()
+    out = [torch.empty_like(tok) for _ in range(2)]
+    torch.cuda.synchronize()
+    with torch.cuda.stream(stream):
+        for _ in range(2):
+            for st in (direct, graph):
+                eet.eet_stack_restore(st.handle, below)
+            for once in ("false", "true", "true"):
+                names = [n for n in kernels_of(lambda: direct.decode_step(tok, out[0])) if "decode_layers" in n]
+                assert len(names) == 1 and names[0].split("decode_layers<")[1].split(">")[0].endswith(once), names
+                graph.decode_step(tok, out[1])
+                stream.synchronize()
+                assert np.array_equal(host(out[0]).view(np.uint16), host(out[1]).view(np.uint16))
+    direct.close()
+    graph.close()
