@@ -736,6 +736,18 @@ bool decode_step_fits(int rows, int hidden, int heads, int ffn) {
            hidden <= 64 * kSWaves * kSUnitsH && ffn <= 64 * kSWaves * kSUnitsF;
 }
 
+// Long sequences: a CU streams the K/V rows of one item at a time, and next to that the launches that are saved count for little.  Where
+// the pairs leave CUs idle (65 to 112 of them are not split) or their number fills a round that the QKV items have already begun (224
+// and more), the attention kernel of its own is ahead from 6000 to 10000 tokens per sequence on.  us per layer-step, launch by launch / one
+// launch, 16000 tokens: 96 pairs of heads of 128: hidden 1024 161 / 181, 1536 151 / 184, 2048 163 / 194; 80 of 640 158 / 174; 112 of 2048 178 /
+// 202; 256 of heads of 64: 1024 193 / 206, 2048 192 / 223.  8000: 99 / 103, 105 / 101, 118 / 110, 97 / 94, 127 / 115, 108 / 111, 130 / 124.  Others
+// stay, 16000: 128 pairs of hidden 1024, heads of 128 208 / 199, of 64 199 / 105; 144 of 64 121 / 113, 192 148 / 131; 96 of 768, heads of 64,
+// 8000 95.7 / 55.6.
+bool decode_step_fits_keys(int rows, int heads, int d, size_t visible) {
+    const int pairs = rows * heads;
+    return visible <= (size_t)8192 * rows || !(pairs >= 224 || (d == 128 && pairs > 64 && pairs <= 112));
+}
+
 // Where the buffers of a step of a.M rows lie in an exchange set; the words that they take
 static uint32_t step_layout(StepArgs& a) {
     const int d = a.H / a.heads, log_h = 6;                   // 64 columns per item

@@ -95,7 +95,7 @@ WorkspaceLayout layout_of(const eet_layer_config* c) {
     // sized for the split count of any batch <= max_batch (fewer sequences -> more splits) that does not run as one launch
     size_t part = 0;
     for (int b = 1; b <= c->max_batch; ++b) {
-        if (decode_step_fits(b, c->hidden, c->heads, c->ffn)) continue;
+        if (decode_step_fits(b, c->hidden, c->heads, c->ffn) && decode_step_fits_keys(b, c->heads, (int)H / c->heads, (size_t)b * c->max_seq)) continue;
         const size_t p = attention_decode_scratch_bytes(b, c->heads, H / c->heads,
                                                         attention_decode_splits(b, c->heads, c->max_seq));
         part = p > part ? p : part;
@@ -355,18 +355,21 @@ int eet_layer_encode(eet_layer_t* L, const int32_t* q_lens, int32_t batch, int32
                            static_cast<hipStream_t>(hip_stream), false);
 }
 
-// Whether a decode step of `L`'s handle (a layer, or the stack it belongs to, whose sequences hold `cached` keys each) moves more
-// between two uses of the same weight or cache row than the memory-side cache holds: every layer's weights and visible K/V once.
-static bool step_exceeds_cache(const eet_layer* L, const int32_t* cached) {
+// How a decode step of `L`'s handle runs (a layer, or the stack it belongs to, whose sequences hold `cached` keys each).  kInCache: all
+// that it moves, every layer's weights and visible K/V, stays in the memory-side cache until the next step; kExceedsCache: more than
+// that; kLongKeys: more, and launch by launch where shorter sequences would run as one launch (kernels.hpp: decode_step_fits_keys).
+enum StepRegime { kInCache, kExceedsCache, kLongKeys, kStepRegimes };
+static StepRegime step_regime(const eet_layer* L, const int32_t* cached) {
     const size_t H = L->cfg.hidden, F = L->cfg.ffn;
     size_t visible = 0;
     for (int b = 0; b < L->batch; ++b) visible += (size_t)cached[b] + 1;
-    return (size_t)(L->stack_layers > 0 ? L->stack_layers : 1) * (2 * (4 * H * H + 2 * H * F) + 4 * H * visible) > kMemorySideCacheBytes;
+    if (decode_step_fits(L->batch, L->cfg.hidden, L->cfg.heads, L->cfg.ffn) && !decode_step_fits_keys(L->batch, L->cfg.heads, L->d, visible)) return kLongKeys;
+    return (size_t)(L->stack_layers > 0 ? L->stack_layers : 1) * (2 * (4 * H * H + 2 * H * F) + 4 * H * visible) > kMemorySideCacheBytes ? kExceedsCache : kInCache;
 }
 
 // Enqueue the kernels of one layer's decode step (arguments already validated).  `bump`: this
 // layer advances the device-side cache lengths (in a stack only the last layer does).
-static int enqueue_decode(eet_layer* L, const void* tokens, void* out, void* kv_cache, hipStream_t s, bool bump, bool exceeds_cache,
+static int enqueue_decode(eet_layer* L, const void* tokens, void* out, void* kv_cache, hipStream_t s, bool bump, StepRegime regime,
                           const eet_layer* next = nullptr, const void* next_kv = nullptr) {
     const eet_layer_config& c = L->cfg;
     const int B = L->batch, H = c.hidden, F = c.ffn;
@@ -402,7 +405,7 @@ static int enqueue_decode(eet_layer* L, const void* tokens, void* out, void* kv_
     // two together are no worse than either alone, 1 / 8 / 16 sequences, per layer-step: 12 x hidden 1536 both 31.0 / 34.8 / 46.1, prefetch
     // without the hint 30.9 / 34.8 / 46.5, the hint without prefetch 32.4 / 36.2 / 47.0; 6 layers 29.9 / 32.8 / 45.6, 30.8 / 34.9 / 46.7 and
     // 29.7 / 33.6 / 44.4)
-    const int once = exceeds_cache && !small ? 1 : 0;
+    const int once = regime != kInCache && !small ? 1 : 0;
     // The same small layers leave CUs idle in every launch: extra workgroups of the two launches with the fewest
     // workgroups pull operands of later launches towards the memory-side cache (PrefetchArgs).  `next`: the layer
     // whose step follows this one (the next layer of a stack, or this layer's own next step).  Measured on the
@@ -415,7 +418,7 @@ static int enqueue_decode(eet_layer* L, const void* tokens, void* out, void* kv_
     // (of the layers between 16 and 20 MB only those of a stack too large for that cache, figures above; a single layer 26.4 -> 28.2;
     // there the second feed-forward projection is a weight stream, which has no workgroups to spare: the output projection alone
     // prefetches)
-    const bool prefetch = small || (fuse_ln && exceeds_cache);
+    const bool prefetch = small || (fuse_ln && regime != kInCache);
     auto lines = [](size_t bytes) { return (uint32_t)(bytes / 128); };
     const half_t* qkv_in = x;
     if (!fuse_ln) {
@@ -513,9 +516,11 @@ static int enqueue_decode(eet_layer* L, const void* tokens, void* out, void* kv_
 
 // A decode step through `n` layers of one configuration that share a workspace, as one launch per kStepLayers of them.  The last
 // layer's launch advances the lengths.  act: where a launch leaves its output for the next (two buffers, alternating).
-static bool decodes_in_one_launch(const eet_layer* L) { return decode_step_fits(L->batch, L->cfg.hidden, L->cfg.heads, L->cfg.ffn); }
+static bool decodes_in_one_launch(const eet_layer* L, StepRegime regime) {
+    return regime != kLongKeys && decode_step_fits(L->batch, L->cfg.hidden, L->cfg.heads, L->cfg.ffn);
+}
 static int enqueue_decode_layers(eet_layer* const* layers, int n, const void* tokens, void* out, void* kv_cache, size_t layer_cache_bytes,
-                                 void* const* act, hipStream_t s, bool exceeds_cache) {
+                                 void* const* act, hipStream_t s, StepRegime regime) {
     const eet_layer* L0 = layers[0];
     const eet_layer_config& c = L0->cfg;
     const int H = c.hidden, F = c.ffn;
@@ -540,7 +545,7 @@ static int enqueue_decode_layers(eet_layer* const* layers, int n, const void* to
             a.layer[l] = StepLayer{p(w.ln1_g), p(w.ln1_b), p(w.w_qkv), p(w.b_qkv), p(w.w_o), p(w.b_o), p(w.ln2_g), p(w.ln2_b), p(w.w_fc1),
                                    p(w.b_fc1), p(w.w_fc2), p(w.b_fc2), kv, kv + (size_t)c.max_batch * H * c.max_seq};
         }
-        EET_LAUNCH(launch_decode_layers(a, exceeds_cache, s), "decode layers");
+        EET_LAUNCH(launch_decode_layers(a, regime != kInCache, s), "decode layers");
         in = o;
     }
     return EET_OK;
@@ -557,9 +562,9 @@ int eet_decode_step(eet_layer_t* L, const void* tokens, void* out, void* kv_cach
         if (L->host_lens[b] + 1 > c.max_seq)
             return fail(EET_ERR_CAPACITY, "eet_decode_step: sequence %d is at the cache capacity %d", b, c.max_seq);
     hipStream_t s = static_cast<hipStream_t>(hip_stream);
-    const bool exceeds_cache = step_exceeds_cache(L, L->host_lens);
-    const int rc = decodes_in_one_launch(L) ? enqueue_decode_layers(&L, 1, tokens, out, kv_cache, 0, nullptr, s, exceeds_cache)
-                                            : enqueue_decode(L, tokens, out, kv_cache, s, true, exceeds_cache, L, kv_cache);
+    const StepRegime regime = step_regime(L, L->host_lens);
+    const int rc = decodes_in_one_launch(L, regime) ? enqueue_decode_layers(&L, 1, tokens, out, kv_cache, 0, nullptr, s, regime)
+                                            : enqueue_decode(L, tokens, out, kv_cache, s, true, regime, L, kv_cache);
     if (rc != EET_OK) return rc;
     for (int b = 0; b < B; ++b) L->host_lens[b] += 1;
     return EET_OK;
@@ -619,8 +624,8 @@ struct eet_stack {
     int batch;
     int32_t host_lens[EET_MAX_BATCH];
     int use_graph;
-    hipGraphExec_t exec[2];            // captured decode steps, valid for (g_tokens, g_out, g_kv, g_batch), by step_exceeds_cache: the lengths
-                                       // grow past that line once, and a new prefill or restore goes back
+    hipGraphExec_t exec[kStepRegimes]; // captured decode steps, valid for (g_tokens, g_out, g_kv, g_batch): the lengths grow past each line
+                                       // between the regimes once, and a new prefill or restore goes back
     const void* g_tokens;
     void* g_out;
     void* g_kv;
@@ -755,10 +760,10 @@ int eet_stack_encode(eet_stack_t* st, const int32_t* q_lens, int32_t batch, int3
     return EET_OK;
 }
 
-static int stack_enqueue_decode(eet_stack* st, const void* tokens, void* out, void* kv_cache, hipStream_t s, bool exceeds_cache) {
-    if (decodes_in_one_launch(st->layers[0])) {
+static int stack_enqueue_decode(eet_stack* st, const void* tokens, void* out, void* kv_cache, hipStream_t s, StepRegime regime) {
+    if (decodes_in_one_launch(st->layers[0], regime)) {
         void* act[2] = {st->ws + st->act[0], st->ws + st->act[1]};
-        return enqueue_decode_layers(st->layers, st->n_layers, tokens, out, kv_cache, st->layer_cache_bytes, act, s, exceeds_cache);
+        return enqueue_decode_layers(st->layers, st->n_layers, tokens, out, kv_cache, st->layer_cache_bytes, act, s, regime);
     }
     const void* in = tokens;
     for (int l = 0; l < st->n_layers; ++l) {
@@ -766,7 +771,7 @@ static int stack_enqueue_decode(eet_stack* st, const void* tokens, void* out, vo
         void* o = last ? out : static_cast<void*>(st->ws + st->act[l & 1]);
         char* kv = static_cast<char*>(kv_cache) + (size_t)l * st->layer_cache_bytes;
         const int ln = last ? 0 : l + 1;                                    // the step that follows this layer's
-        const int rc = enqueue_decode(st->layers[l], in, o, kv, s, last, exceeds_cache,    // lengths shared: advanced once, at the end
+        const int rc = enqueue_decode(st->layers[l], in, o, kv, s, last, regime,    // lengths shared: advanced once, at the end
                                       st->layers[ln], static_cast<char*>(kv_cache) + (size_t)ln * st->layer_cache_bytes);
         if (rc != EET_OK) return rc;
         in = o;
@@ -784,7 +789,7 @@ int eet_stack_decode_step(eet_stack_t* st, const void* tokens, void* out, void* 
         if (st->host_lens[b] + 1 > st->cfg.max_seq)
             return fail(EET_ERR_CAPACITY, "eet_stack_decode_step: sequence %d is at the cache capacity %d", b, st->cfg.max_seq);
     hipStream_t s = static_cast<hipStream_t>(hip_stream);
-    const bool exceeds_cache = step_exceeds_cache(st->layers[0], st->host_lens);
+    const StepRegime regime = step_regime(st->layers[0], st->host_lens);
     // A step has no other host-varying argument (the cache lengths live on the device), so its launches
     // can be recorded once and replayed.  Not on the null stream (it cannot be captured) and not
     // while the caller is capturing this stream itself (then the launches join the caller's graph).
@@ -794,14 +799,14 @@ int eet_stack_decode_step(eet_stack_t* st, const void* tokens, void* out, void* 
         if (hipStreamIsCapturing(s, &cs) != hipSuccess || cs != hipStreamCaptureStatusNone) graph = false;
     }
     if (!graph) {
-        if (const int rc = stack_enqueue_decode(st, tokens, out, kv_cache, s, exceeds_cache)) return rc;
+        if (const int rc = stack_enqueue_decode(st, tokens, out, kv_cache, s, regime)) return rc;
     } else {
         if (st->g_tokens != tokens || st->g_out != out || st->g_kv != kv_cache || st->g_batch != B) drop_graphs(st);
-        hipGraphExec_t& exec = st->exec[exceeds_cache ? 1 : 0];
+        hipGraphExec_t& exec = st->exec[regime];
         if (!exec) {
             hipGraph_t g = nullptr;
             EET_LAUNCH(hipStreamBeginCapture(s, hipStreamCaptureModeThreadLocal), "begin capture");
-            const int rc = stack_enqueue_decode(st, tokens, out, kv_cache, s, exceeds_cache);
+            const int rc = stack_enqueue_decode(st, tokens, out, kv_cache, s, regime);
             const hipError_t e = hipStreamEndCapture(s, &g);
             if (rc != EET_OK) {
                 if (g) (void)hipGraphDestroy(g);

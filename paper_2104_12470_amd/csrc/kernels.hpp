@@ -208,6 +208,8 @@ struct StepArgs {
 };
 // Rows and widths the kernel takes.
 bool decode_step_fits(int rows, int hidden, int heads, int ffn);
+// ... and whether it is the faster way with `visible` keys in all (decode_step.hip has the figures).
+bool decode_step_fits_keys(int rows, int heads, int d, size_t visible);
 // Words of an exchange set that holds a step of any number of rows up to max_rows that the kernel takes (0: it takes none).  A set has
 // this size, is set up (by the launches that set the cache lengths: launch_prefill_setup_layernorm, launch_set_cache_lens) and is
 // emptied whole, whatever the rows of a step: a caller may have recorded a step of another number of sequences than those

@@ -234,3 +234,38 @@ def test_a_stack_counts_the_keys_its_sequences_hold(eet):
                 assert np.array_equal(host(out[0]).view(np.uint16), host(out[1]).view(np.uint16))
     direct.close()
     graph.close()
+
+
+@pytest.mark.parametrize("heads,batch,kernel", [(5, 13, "attn_decode"), (4, 16, "decode_layers"), (8, 14, "attn_decode"), (8, 15, "decode_layers")])
+def test_steps_that_outgrow_one_launch(eet, heads, batch, kernel):
+    """From 8192 keys per sequence on, 65 to 112 pairs of heads of 128 go launch by launch (64 and 113 and more, up to 223, never).  The sequences
+    cross the line between two steps, direct and recorded, and a restore takes them back; the oracle follows all of it."""
+    H, first = 128 * heads, 8190
+    w = wl.Workload(f"outgrow{heads}x{batch}", 61, H, heads, 256, 1, batch, 1, 1, 1, 4, 8208)
+    W = wl.layer_weights(w, 0, random_affine=True)
+    cfg = eet.make_config(H, heads, w.ffn, batch, 1, w.max_seq, w.ln_eps)
+    Ws = [{k: torch.from_numpy(v) for k, v in W.items()}]
+    direct, graph = eet.DecoderStack(cfg, Ws, use_graph=False), eet.DecoderStack(cfg, Ws)
+    oracle = orc.DecoderLayerOracle(W, heads, batch, w.max_seq, w.ln_eps)
+    rows = wl.normal(w.seed, 9, (2, batch, heads, w.max_seq, 128))
+    direct.kv_cache.copy_(dev(rows).view(-1))
+    graph.kv_cache.copy_(direct.kv_cache)
+    xs = wl.decode_embeddings(w, 0)
+    lens, stream, tok = [first] * batch, torch.cuda.Stream(), dev(xs)
+    out = [torch.empty_like(tok) for _ in range(2)]
+    torch.cuda.synchronize()
+    with torch.cuda.stream(stream):
+        for _ in range(2):
+            for st in (direct, graph):
+                eet.eet_stack_restore(st.handle, lens)
+            oracle.batch, oracle.lens[:batch] = batch, lens
+            oracle.k_cache[:batch], oracle.v_cache[:batch] = rows[0], rows[1]
+            for k in range(4):
+                names = kernels_of(lambda: direct.decode_step(tok, out[0]))
+                assert any(("decode_layers" if first + k + 1 <= 8192 else kernel) in n for n in names), (k, names)
+                graph.decode_step(tok, out[1])
+                stream.synchronize()
+                gate(host(out[0]), oracle.decode_step(xs), f"step {k}")
+                assert np.array_equal(host(out[0]).view(np.uint16), host(out[1]).view(np.uint16)), k
+    direct.close()
+    graph.close()
