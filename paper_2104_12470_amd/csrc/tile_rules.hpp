@@ -126,6 +126,13 @@ inline bool short_k_wide(int M, int N, int K) { return M > 16 && M <= 64 && K < 
 // share it; longer in proportion once the tiles no longer fit the chip at once).  Wide outputs with a short K go
 // to the tiles from about 33 rows on, narrow outputs with a long K (the output and second feed-forward projections)
 // stay with the slices for up to a few hundred rows.
+//
+// K = 640 to 896 with 33 rows and more: the tiles have the shared loop there, and its price holds where the slices run on the general
+// kernel (K no multiple of 256) or on 8-column workgroups (fewer than 2048 columns): slices / tiles 352 x 640 x 640 9.7 / 6.6, 144 x
+// 1536 x 640 9.8 / 6.7, 80 x 2560 x 640 9.7 / 6.8, 480 x 768 x 768 9.3 / 7.2, 176 x 1920 x 768 8.7 / 7.4, 224 x 896 x 896 9.7 / 7.7; the least,
+// weights out of HBM: 49 x 2304 x 896 7.4 / 8.0, out of the memory-side cache 6.7 / 6.5.  Not where they run on 16-column ones: 96 x 3072 x 768 6.2 /
+// 7.4, 64 x 4096 x 768 5.9 / 7.8, nor below 33 rows (24 x 4096 x 896 6.2 / 7.8).
+inline bool two_k_groups(int K) { return K % 128 == 0 && K >= 640; }    // what tile_for shares between two groups of waves
 inline bool slices_beat_tiles(int M, int N, int K) {
     const int slices = (M + 15) / 16;
     if (slices > 32) return false;
@@ -134,7 +141,7 @@ inline bool slices_beat_tiles(int M, int N, int K) {
     const double again = w_mb / (streams ? 7.5 : 4.5);
     const double est_slices = 2.0 + w_mb / (streams ? 4.0 : 2.5) + (slices - 1) * (again > 0.1 ? again : 0.1);
     const double wg64 = (double)((M + 63) / 64) * ((N + 63) / 64);
-    const bool k_split = K % 128 == 0 && K >= 1024 && wg64 <= 256.0;     // two groups of waves share the K loop
+    const bool k_split = two_k_groups(K) && wg64 <= 256.0 && (K >= 1024 || (M > 32 && (K % 256 != 0 || N < 2048)));
     const double k_loop = (K / 64) * (k_split ? 0.23 : 0.33) * (wg64 > 768.0 ? wg64 / 768.0 : 1.0);
     const double est_tiles = 3.0 + (w_mb / 3.0 > k_loop ? w_mb / 3.0 : k_loop);
     return est_slices < est_tiles;
@@ -214,7 +221,7 @@ inline TileChoice choose_tile(int M, int N, int K) {
 // three).  From K = 640 on, five steps per group: prompts of 20 to 900 rows through layers of 640, 768 and 896 take 0.88 to 0.98 of the time
 // that they took with one group (768: 160 rows 46.8 -> 44.4 us per layer, 600 57.9 -> 53.7); at 256 and 384 there is nothing to gain.
 inline TileChoice tile_for(int M, int N, int K) {
-    const bool k_split = K % 128 == 0 && K >= 640;
+    const bool k_split = two_k_groups(K);
     const int wg128 = ((M + 127) / 128) * ((N + 63) / 64), wg64 = ((M + 63) / 64) * ((N + 63) / 64);
     if (wg128 < 128 || (k_split && wg128 <= 256)) {
         if (k_split && wg64 <= 256) return kTile64Split;              // (1000 x 1024 x 4096: 25.1 -> 20.1)

@@ -24,6 +24,9 @@ ROWS_STREAM = [
     (64, 2176, 6144, "64x64 x3, two K groups", "64x64 x3, two K groups"),
     (20, 64, 33024, "64x128 x3", "128x128 x2, shared schedule"), (64, 192, 32832, "64x128 x3", "128x128 x2, shared schedule"),   # a wide output with a short K
     (97, 8192, 16448, "rows 128", "rows 128"),                                                 # weights no cache holds
+    (352, 640, 640, "64x64 x3, two K groups", "64x64 x3, two K groups"), (33, 640, 3584, "64x64 x3, two K groups", "64x64 x3, two K groups"),    # K shared from 640 on
+    (480, 768, 768, "64x64 x3, two K groups", "64x64 x3, two K groups"), (225, 896, 896, "64x64 x3, two K groups", "64x64 x3, two K groups"),
+    (96, 768, 3072, "slices", "slices"), (24, 896, 4096, "slices", "slices"),
     (65, 4096, 16384, "128x64 x3, two K groups", "128x64 x3, two K groups"), (128, 4224, 16384, "128x64 x3, two K groups", "128x64 x3, two K groups"),
 ]
 
