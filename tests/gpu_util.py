@@ -24,3 +24,12 @@ def gate(got, want, what="", max_abs=MAX_ABS, mean_abs=MEAN_ABS):
     mx, mn = float(err.max()) if err.size else 0.0, float(err.mean()) if err.size else 0.0
     assert mx <= max_abs and mn <= mean_abs, f"{what}: max abs {mx:.3e} (<= {max_abs}), mean abs {mn:.3e} (<= {mean_abs})"
     return mx, mn
+
+
+def kernels_of(call):
+    """Names of what `call` launches (directly: replays of a graph do not show)."""
+    from torch.profiler import ProfilerActivity, profile
+    with profile(activities=[ProfilerActivity.CUDA]) as p:
+        call()
+        torch.cuda.synchronize()
+    return [e.name for e in p.events()]

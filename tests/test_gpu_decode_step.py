@@ -7,7 +7,7 @@ import torch
 
 from oracle import eet_oracle as orc
 from paper_2104_12470_amd import workloads as wl
-from tests.gpu_util import dev, gate, host
+from tests.gpu_util import dev, gate, host, kernels_of
 
 pytestmark = pytest.mark.gpu
 
@@ -56,6 +56,29 @@ def test_steps_against_the_oracle(eet, hidden, heads, ffn, batch, len_hi, max_se
         n = int(lens[b]) + steps
         gate(host(kc[b, :, :n]), oracle.k_cache[b, :, :n], f"K cache b={b}", 1.5e-2, 1.5e-3)
         gate(host(vc[b, :, :n]), oracle.v_cache[b, :, :n], f"V cache b={b}", 1.5e-2, 1.5e-3)
+    layer.close()
+
+
+@pytest.mark.parametrize("d,lens", [(64, [1, 1022, 1023, 1024, 1025, 1055, 1056, 1100, 1535, 2046, 2047, 2048, 2100]),
+                                    (128, [1, 510, 511, 512, 513, 527, 528, 600, 767, 1022, 1023, 1024, 1100])])
+def test_more_keys_than_an_item_holds(eet, d, lens):
+    """65 pairs are not split, and an attention item requests 1024 keys (512 of heads of 128) before its query arrives and the rest as it
+    goes: caches that end on either side of one and of two such loads, and of a wave's blocks behind them."""
+    heads, batch, max_seq = 5, len(lens), max(lens) + 4
+    w = wl.Workload(f"refill{d}", 67, heads * d, heads, 448, 1, batch, 1, 1, 1, 2, max_seq)
+    layer, oracle = layer_and_oracle(eet, w)
+    rows = wl.normal(w.seed, 9, (2, batch, heads, max_seq, d))
+    for b, n in enumerate(lens):
+        rows[:, b, :, n:] = np.nan                             # slots that hold no key yet are never read
+    layer.kv_cache.copy_(dev(rows).view(-1))
+    eet.eet_restore(layer.handle, lens)
+    oracle.batch, oracle.lens[:], oracle.k_cache[:], oracle.v_cache[:] = batch, lens, rows[0], rows[1]
+    for k in range(2):
+        xs = wl.decode_embeddings(w, k)
+        got = torch.empty_like(dev(xs))
+        names = kernels_of(lambda: layer.decode_step(dev(xs), got))
+        assert any("decode_layers" in n for n in names), names
+        gate(host(got), oracle.decode_step(xs), f"step {k}")
     layer.close()
 
 
@@ -196,14 +219,6 @@ def test_a_wait_given_up_is_not_taken_for_a_result(eet, how):
         gate(host(got), oracle.decode_step(xs), f"step {k}")
     assert layer.cache_lens(3) == oracle.lens[:3].tolist()
     layer.close()
-
-
-def kernels_of(call):
-    from torch.profiler import ProfilerActivity, profile
-    with profile(activities=[ProfilerActivity.CUDA]) as p:
-        call()
-        torch.cuda.synchronize()
-    return [e.name for e in p.events()]
 
 
 def test_a_stack_counts_the_keys_its_sequences_hold(eet):

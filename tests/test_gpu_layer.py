@@ -14,7 +14,7 @@ import torch
 from oracle import eet_oracle as orc
 from paper_2104_12470_amd import workloads as wl
 from tests import tile_shapes
-from tests.gpu_util import MAX_ABS, MEAN_ABS, dev, gate, host
+from tests.gpu_util import MAX_ABS, MEAN_ABS, dev, gate, host, kernels_of
 
 pytestmark = pytest.mark.gpu
 
@@ -135,7 +135,8 @@ def test_prompts_through_the_one_per_cu_tiles(eet, w):
 
 @pytest.mark.parametrize("B", [1, 9, 16])
 def test_decode_with_the_layernorms_inside_projections_of_16_to_20_mb(eet, B):
-    """Hidden 1536: the feed-forward matrix is 18.9 MB, the LayerNorms run inside the small-layer kernel all the same."""
+    """Hidden 1536: the feed-forward matrix is 18.9 MB, the LayerNorms run inside the small-layer kernel all the same (from 9 sequences
+    on; a single one has its whole step in one launch)."""
     w = wl.Workload(f"h1536x{B}", 37, 1536, 24, 6144, 1, B, 24, 3, 24, 3, 32)
     full_parity(eet, w)
 
@@ -143,10 +144,41 @@ def test_decode_with_the_layernorms_inside_projections_of_16_to_20_mb(eet, B):
 @pytest.mark.parametrize("heads,B,max_seq,lo,hi", [(4, 3, 512, 300, 500), (2, 1, 4096, 3900, 4000)])
 def test_decode_with_the_key_range_split_and_merged_by_the_output_projection(eet, heads, B, max_seq, lo, hi):
     """Few (sequence, head) pairs and a long cache: the decode attention splits the key range (4 ranges per pair in the
-    first case, 32 in the second: more than the projection keeps in flight at once), and the output projection of
-    these small layers merges the ranges while it loads its activations.  Every element against the oracle."""
+    first case, 16 in the second), and the output projection's items of these small layers, whose step is one launch,
+    merge the ranges.  Every element against the oracle."""
     w = wl.Workload(f"ranges{heads}x{B}", 31, 256, heads, 1024, 1, B, hi, lo, hi, 3, max_seq)
     full_parity(eet, w, random_affine=False)
+
+
+@pytest.mark.parametrize("hidden,heads,ffn,B,max_seq,keys", [
+    (1536, 12, 4096, 9, 512, 300),       # 4 ranges; LayerNorms inside the projections and prefetch workgroups as well
+    (1536, 12, 3072, 9, 512, 500),       # 4 ranges; the second feed-forward projection prefetches too: the next QKV matrix and the K/V rows
+    (512, 4, 4160, 9, 1024, 700),        # 8 ranges; feed-forward part too wide for one launch
+    (256, 2, 8256, 1, 4096, 3900),       # 32 ranges: more than the projection keeps in flight at once
+])
+def test_launch_by_launch_with_the_key_range_split_and_merged_by_the_output_projection(eet, hidden, heads, ffn, B, max_seq, keys):
+    """Small layers whose steps go launch by launch (too many sequences or too wide a feed-forward part for one launch), few
+    (sequence, head) pairs and a long cache: the output projection merges the key ranges while it loads its activations."""
+    lens = [keys - 17 * b for b in range(B)]
+    w = wl.Workload(f"merged{hidden}x{B}", 31, hidden, heads, ffn, 1, B, 1, 1, 1, 3, max_seq)
+    W = wl.layer_weights(w, 0, True)
+    layer = make_gpu_layer(eet, w, W)
+    oracle = orc.DecoderLayerOracle(W, heads, B, max_seq, w.ln_eps)
+    rows = wl.normal(w.seed, 9, (2, B, heads, max_seq, hidden // heads))
+    for b, n in enumerate(lens):
+        rows[:, b, :, n:] = np.nan                             # slots that hold no key yet are never read
+    layer.kv_cache.copy_(dev(rows).view(-1))
+    eet.eet_restore(layer.handle, lens)
+    oracle.batch, oracle.lens[:], oracle.k_cache[:], oracle.v_cache[:] = B, lens, rows[0], rows[1]
+    for k in range(3):
+        xs = wl.decode_embeddings(w, k)
+        tok = dev(xs)
+        got = torch.empty_like(tok)
+        names = kernels_of(lambda: layer.decode_step(tok, got))
+        assert any("gemm_flat<" in n and n.split(">")[0].endswith("true") for n in names), names      # its last parameter: the merge
+        assert not any("decode_layers" in n or "combine" in n for n in names), names
+        gate(host(got), oracle.decode_step(xs), f"step {k}")
+    layer.close()
 
 
 @pytest.mark.parametrize("name", ["tiny", "small64", "small128", "bert1024"])
@@ -328,17 +360,22 @@ def test_replays_the_host_never_saw_stay_inside_the_slots(eet, name, lens):
     layer.close()
 
 
-@pytest.mark.parametrize("name", ["small64", "cfg2-2seq", "h2048", "h12288"])
+@pytest.mark.parametrize("name", ["small64", "cfg2-2seq", "h2048", "h1536-9seq", "h2048-9seq", "h12288"])
 def test_inputs_with_a_common_offset_and_an_outlier_channel(eet, name):
     """Hidden states as real models have them: every row shifted by a common offset of several standard deviations and
     one channel (the first: the pivot of the LayerNorm statistics fused into the decode projections) ten times larger
-    than the rest.  Prefill (row-kernel LayerNorm) and decode steps (LayerNorm fused into the small-layer kernel for
-    the first two, row kernel + weight-streaming kernel for the hidden-2048 layer; in the hidden-12288 layer of 5
-    sequences the output projection hands the statistics of the second LayerNorm to the first feed-forward projection,
-    both weight streams) against the oracle."""
+    than the rest.  Prefill (row-kernel LayerNorm) and decode steps (the first three in one launch, whose LayerNorm merges
+    the statistics of eight shares of a row; 9 sequences of hidden 1536 with it fused into the small-layer kernel, 9 of
+    hidden 2048 with the row kernel in front of weight streams; in the hidden-12288 layer of 5 sequences the output projection
+    hands the statistics of the second LayerNorm to the first feed-forward projection, both weight streams) against the
+    oracle."""
     from dataclasses import replace
     if name == "h2048":
         w = wl.Workload("h2048", 29, 2048, 16, 8192, 1, 3, 24, 8, 24, 3, 32)
+    elif name == "h1536-9seq":
+        w = wl.Workload(name, 29, 1536, 12, 4096, 1, 9, 24, 8, 24, 3, 32)
+    elif name == "h2048-9seq":
+        w = wl.Workload(name, 29, 2048, 16, 8192, 1, 9, 24, 8, 24, 3, 32)
     elif name == "h12288":
         w = wl.Workload("h12288", 31, 12288, 96, 12288, 1, 5, 24, 8, 24, 3, 32, sigma_w=0.006)
     else:

@@ -7,8 +7,9 @@ K/V region and the whole workspace, whose pieces are the intermediate results of
 context, output-projection result, normalised rows, feed-forward activations) and the stack's two activation buffers.
 A difference is reported with the first differing piece, so it names the kernel that produced it.
 
-Cases reach the paths the small workloads do not: 256x256 tiles, 128x64 and 64x64 tiles with two K groups, the
-prefetch workgroups of small-layer decode, decode steps replayed from the stack's graph, the 256-row attention."""
+Cases reach the paths the small workloads do not: 256x256 tiles, 128x64 and 64x64 tiles with two K groups, decode steps in
+one launch and, launch by launch, with prefetch workgroups and merged key ranges, all replayed from the stack's graph, the
+256-row attention."""
 from dataclasses import replace
 
 import numpy as np
@@ -40,8 +41,8 @@ def first_difference(a: torch.Tensor, b: torch.Tensor):
 
 def workspace_piece(w, max_batch, offset):
     """Name of the workspace piece a byte offset falls in (the carve-up of csrc/eet_api.hip: lengths, prefix sums, row
-    map, then the [T, F] buffer, the [T, H] buffers A, B, Y, the decode partials, and for a stack the two activation
-    buffers; the capacities here leave no room of its own between F and A for the sums of a cut projection)."""
+    map, then the [T, F] buffer, the [T, H] buffers A, B, Y, the decode partials, the exchange area of one-launch decode steps, and
+    for a stack the two activation buffers; the capacities here leave no room of its own between F and A for the sums of a cut projection)."""
     al = lambda v: (v + 255) // 256 * 256
     T, H, F = max_batch * w.padded_len, w.hidden, w.ffn
     pieces = [("cache lengths", al(4 * 128)), ("prefix sums", al(4 * 129)), ("row map", al(4 * T)),
@@ -54,7 +55,7 @@ def workspace_piece(w, max_batch, offset):
         if offset < lo + size:
             return f"{name} (+{offset - lo} bytes)"
         lo += size
-    return f"decode partials / stack activation buffers (+{offset - lo} bytes past the layer buffers)"
+    return f"decode partials / exchange area / stack activation buffers (+{offset - lo} bytes past the layer buffers)"
 
 
 def run_stack(eet, w, LW, steps):
@@ -78,10 +79,16 @@ def run_stack(eet, w, LW, steps):
     return st, outs
 
 
-@pytest.mark.parametrize("name,batch,layers", [("cfg2", 8, 24),      # 256x256 and 128x64 tiles, prefetch workgroups, graph
-                                               ("cfg2", 2, 4)])      # 128x64 and 64x64 tiles with two K groups
+# 9 sequences of hidden 1536: launch by launch, with the LayerNorms inside the projections, merged key ranges, and prefetch workgroups
+# in the output projection and in the second feed-forward one
+H1536 = wl.Workload("h1536", 1007, 1536, 12, 3072, 1, 9, 384, 128, 384, 3, 512)
+
+
+@pytest.mark.parametrize("name,batch,layers", [("cfg2", 8, 24),      # 256x256 and 128x64 tiles, decode steps in one launch, graph
+                                               ("cfg2", 2, 4),       # 128x64 and 64x64 tiles with two K groups
+                                               ("h1536", 9, 4)])
 def test_stack_runs_are_bitwise_reproducible_at_full_size(eet, name, batch, layers):
-    w = replace(wl.WORKLOADS[name], batch=batch, layers=layers)
+    w = replace(H1536 if name == "h1536" else wl.WORKLOADS[name], batch=batch, layers=layers)
     LW = [{k: torch.from_numpy(v) for k, v in wl.layer_weights(w, l).items()} for l in range(layers)]
     print(f"reproducibility: {name} batch {batch}, {layers} layers, prefill + 3 graph-replayed decode steps, two handles", flush=True)
     a, outs_a = run_stack(eet, w, LW, 3)
