@@ -382,42 +382,39 @@ static int enqueue_decode(eet_layer* L, const void* tokens, void* out, void* kv_
     half_t* kc = static_cast<half_t*>(kv_cache);
     half_t* vc = kc + (size_t)c.max_batch * H * c.max_seq;
 
-    // (Layers that decode_layers takes, kernels.hpp, do not come here.)
-    // Small layers are launch-bound in decode: there the two LayerNorms run inside the projections
-    // that consume them (each workgroup recomputes the row statistics of the <= 16 token rows).
-    // Measured break-even is near 16 MB of FFN-1 weights; larger layers keep the separate row kernel.
-    // Above that only where the small-layer kernel takes both consumers with the LayerNorm in front (weights up to 20 MB) and its
-    // waves hold three units of K or more each, which is hidden 1536 with up to 6784 feed-forward columns: of the wider ones it
-    // takes only 2048, which has 25 MB of QKV weights.  Per layer-step, hidden 1536, 1 sequence 32.3 -> 28.2 us, 4 36.0 -> 31.1, 16 in a stack of 24 50.5 -> 46.0; with few
-    // units nothing to gain (1024 x 8192 26.6 -> 26.9), and not at 33 MB (hidden 2048 39.9 -> 44.4).
-    const bool small = B <= 16 && (size_t)F * H * sizeof(half_t) <= ((size_t)16 << 20);
+    // (Steps that run as one launch, kernels.hpp: decode_step_fits, do not come here: of up to 16 sequences what is left are 9 to 16 of hidden
+    // 1088 and more, and any number with more than 4096, or 8192, feed-forward columns.)
+    // Small layers are launch-bound in decode: the two LayerNorms run inside the projections that consume them (each workgroup
+    // recomputes the row statistics of the <= 16 token rows) where the small-layer kernel takes both of them so: hidden 256, 512,
+    // 768, 1024 and 1536, with up to 20 MB of weights each.  us per layer-step, inside / as launches of their own: 16 x hidden 1536 x 4096, 9
+    // sequences 38.4 / 42.7, 16 36.3 / 40.6; 12 x 1536 x 6144, 9 38.8 / 39.8; 16 x 1024 x 5440, 9 32.6 / 38.2; 12 x 1024 x 9216, 16 35.6 / 41.3; 12 x
+    // 512 x 18432, 1 30.5 / 37.0.  The general kernel, which the other widths go to, is slower with them inside: 12 x 1280 x 5120, 12 sequences
+    // 48.7 / 39.2, 20 x 1152 x 4608, 9 41.6 / 39.2, 20 x 640 x 5120, 9 38.2 / 36.2 (4 x 640 x 5120 35.0 / 35.6).  Of hidden 2048 (25 MB of QKV
+    // weights) the small-layer kernel takes none: 33 MB 39.9 / 44.4 the other way round.
     auto takes_layernorm = [&](int N) {
         GemmArgs p{};
         p.M = B; p.N = N; p.K = H; p.ln_gamma = (const half_t*)L->w.ln1_g;
         return gemm_takes_layernorm(p);
     };
-    const bool fuse_ln = small || (H > 1024 && takes_layernorm(3 * H) && takes_layernorm(F));
+    const bool fuse_ln = takes_layernorm(3 * H) && takes_layernorm(F);
     // More than the memory-side cache holds: nothing survives there until the next step, and the read-once operands
     // are loaded with the non-temporal hint (a tenth faster from HBM).  Less (hidden 2048 on its own: 150 MB): the step
     // lives in that cache, which the hint would only disturb (6.68 -> 6.75 ms for 128 steps).
-    // (not for the small layers whose idle workgroups pull the next launches' operands into that cache: PrefetchArgs below;
-    // the hint on the consumer's loads undoes that: 24 hidden-1024 layers 320.7 -> 330.4 ms for 512 steps.  Between 16 and 20 MB the
-    // two together are no worse than either alone, 1 / 8 / 16 sequences, per layer-step: 12 x hidden 1536 both 31.0 / 34.8 / 46.1, prefetch
-    // without the hint 30.9 / 34.8 / 46.5, the hint without prefetch 32.4 / 36.2 / 47.0; 6 layers 29.9 / 32.8 / 45.6, 30.8 / 34.9 / 46.7 and
-    // 29.7 / 33.6 / 44.4)
-    const int once = regime != kInCache && !small ? 1 : 0;
-    // The same small layers leave CUs idle in every launch: extra workgroups of the two launches with the fewest
+    // (Beside the prefetch below as well: 20 x hidden 512 x 8704, 1 / 12 sequences, both 22.7 / 29.9, prefetch without the hint 24.0 / 31.1, the hint
+    // without prefetch 24.1 / 32.0; 16 x 1024 x 5440, 9 32.6, 32.6 and 33.9; 12 x 1024 x 8192 31.2, 32.1 and 30.6; 16 x 1536 x 4096 38.5, 38.4 and 39.1.)
+    const int once = regime != kInCache ? 1 : 0;
+    // Layers with up to 16 MB of feed-forward weights leave CUs idle in every launch: extra workgroups of the two launches with the fewest
     // workgroups pull operands of later launches towards the memory-side cache (PrefetchArgs).  `next`: the layer
-    // whose step follows this one (the next layer of a stack, or this layer's own next step).  Measured on the
-    // 24-layer hidden-1024 stack, one call: 346 -> 324 ms for 512 decode steps.  Prefetching during the attention or
-    // the QKV projection, other workgroup counts (64, 96, 112, 192, 256) and the first feed-forward matrix instead
-    // of the second were all slower: the attention streams from HBM itself, and 128 keeps main plus extra
-    // workgroups at one per CU.  Moving any share of the K/V rows (a quarter to all) from FFN-2's extra workgroups to
-    // the output projection's was slower too (324 -> 361-367 ms).
+    // whose step follows this one (the next layer of a stack, or this layer's own next step).  us per layer-step, without / with: 16 x hidden
+    // 1024 x 5440, 9 sequences 33.9 / 32.6, 16 37.9 / 35.7; 24 x 768 x 4608, 12 27.4 / 26.1; 16 x 1536 x 4096, 16 36.7 / 36.3; where all that a step
+    // moves stays in that cache it is worth nothing (4 x 1024 x 5440, 9 30.5 to 32.2 / 30.9 to 31.2; 4 x 512 x 8704, 1 22.9 to 23.2 / 23.4 to 23.7).  128 workgroups keep
+    // main plus extra ones at one per CU; during the attention or the QKV projection, and of the first feed-forward matrix instead of the
+    // second, all were slower on a stack of 24 x 1024 x 4096 (which is one launch by now): the attention streams from HBM itself.
     constexpr int kPrefetchBlocks = 128;
-    // (of the layers between 16 and 20 MB only those of a stack too large for that cache, figures above; a single layer 26.4 -> 28.2;
+    // (between 16 and 20 MB only layers of a stack too large for that cache: 12 x 1536 x 6144, 16 sequences 43.4 / 42.5; a single layer of it 26.4 / 28.2;
     // there the second feed-forward projection is a weight stream, which has no workgroups to spare: the output projection alone
     // prefetches)
+    const bool small = B <= 16 && (size_t)F * H * sizeof(half_t) <= ((size_t)16 << 20);
     const bool prefetch = small || (fuse_ln && regime != kInCache);
     auto lines = [](size_t bytes) { return (uint32_t)(bytes / 128); };
     const half_t* qkv_in = x;

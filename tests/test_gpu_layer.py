@@ -141,6 +141,23 @@ def test_decode_with_the_layernorms_inside_projections_of_16_to_20_mb(eet, B):
     full_parity(eet, w)
 
 
+@pytest.mark.parametrize("hidden,heads,ffn,B,inside", [
+    (1280, 10, 5120, 9, False), (1152, 9, 3072, 16, False),       # widths of the general kernel
+    (768, 12, 11520, 2, True), (1024, 16, 9216, 10, True),        # feed-forward weights of 16 to 20 MB, narrow
+    (1024, 16, 10304, 9, False),                                  # past 20 MB
+])
+def test_decode_launch_by_launch_with_the_layernorms_where_the_small_layer_kernel_takes_both(eet, hidden, heads, ffn, B, inside):
+    w = wl.Workload(f"norms{hidden}x{B}", 37, hidden, heads, ffn, 1, B, 24, 3, 24, 3, 32)
+    full_parity(eet, w)
+    layer = make_gpu_layer(eet, w, wl.layer_weights(w))
+    eet.eet_restore(layer.handle, [1] * B)
+    layer.kv_cache.zero_()
+    tok = dev(wl.decode_embeddings(w, 0))
+    names = [n for n in kernels_of(lambda: layer.decode_step(tok)) if "eet" in n]
+    assert not any("decode_layers" in n for n in names) and any("layernorm" in n for n in names) != inside, names
+    layer.close()
+
+
 @pytest.mark.parametrize("heads,B,max_seq,lo,hi", [(4, 3, 512, 300, 500), (2, 1, 4096, 3900, 4000)])
 def test_decode_with_the_key_range_split_and_merged_by_the_output_projection(eet, heads, B, max_seq, lo, hi):
     """Few (sequence, head) pairs and a long cache: the decode attention splits the key range (4 ranges per pair in the
