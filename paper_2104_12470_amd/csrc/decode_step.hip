@@ -6,7 +6,8 @@
 // of the second feed-forward one), or one key range of a (sequence, head) pair.  It requests its weights (or K/V rows), up to 256 KB, into
 // registers first, since they depend on nothing, and only then waits for its input, which the items of the phase before hand
 // over through memory.  While a phase runs, the CUs that it leaves idle hold the weights of the next ones: HBM never waits for the chain, and a
-// phase costs its hand-over (0.6 to 0.9 us one way, of which 0.45 to 0.7 is one store seen by one load across the chip) and its arithmetic.
+// phase costs its hand-over (1.0 to 1.5 us from the producers' sums to a consumer's whole input, of which 0.45 to 0.7 is one store seen by
+// one load across the chip) and its arithmetic.
 // us per layer-step, five launches -> now: hidden 1024 in a stack of 24, 1 sequence 21.2 -> 10.6, 8 sequences of 384 to 768 tokens
 // 26.4 -> 14.0; 60 drawn sizes (hidden 256 to 2048, 1 to 24 layers, 1 to 8 sequences of 1 to 3200 tokens) 1.18 to 3.1 times as
 // fast, geometric mean 1.86; 30 of 9 to 16 sequences 1.09 to 2.9, 1.58.
@@ -19,7 +20,7 @@
 //               against 2.5), release and acquire fences write back and invalidate whole caches (22).
 //   lines       A line is written by one workgroup, in one go: every store to a line that others are polling takes the line away from all
 //               of them first.  Four producers per line: 21.8 us per layer-step where 16-column items with a line each take 20.4, and
-//               64-column items, with a quarter of the lines to poll, 12.4.
+//               64-column items, with a quarter of the lines to poll, 12.4 (one sequence, on the variant of 8 rows).
 //   reuse       Layer number g (counted on over all steps since the last prefill) uses exchange set g % 2.  An item of the QKV
 //               projection of layer g has seen all of x(g) when it starts to normalise: every item of layer g-1 has handed on its result, so
 //               nobody reads the other set any more, and the QKV items empty it, each its part, and count themselves in `resets` when their
@@ -35,7 +36,7 @@
 // through the exchange set, and the cache for the steps that follow.
 //
 // One workgroup per CU (the registers see to that): two, with 128 registers each, start so far ahead that their polling
-// slows the phases they wait for (12.4 -> 14.2 us per layer-step with one sequence).
+// slows the phases they wait for (12.4 -> 14.2 us per layer-step with one sequence on the variant of 8 rows, 10.6 on its own).
 #include "kernels.hpp"
 
 namespace eet {
@@ -161,7 +162,7 @@ __device__ __forceinline__ uint32_t word_at(const StepBuffer& b, int row, int co
 
 // How the 16 words of a unit's rows lie over a wave: VW words per lane, LPR lanes per row, UPI units per load instruction.  Rows
 // that do not exist cost lanes, i.e. instructions of the LayerNorm and of the polling, hence the variants of 1, 2, 4, 8 and 16 rows
-// (one sequence on the variant of 8: 12.4 us per layer-step instead of 10.7).
+// (one sequence on the variant of 8: 12.4 us per layer-step instead of 10.6).
 template <int ROWS>
 struct RowLanes {
     static constexpr int VW = ROWS == 16 ? 4 : ROWS == 8 ? 2 : 1, LPR = 16 / VW, UPI = 64 / (LPR * ROWS);
@@ -467,30 +468,30 @@ __device__ __forceinline__ void project(const StepArgs& a, const Where& w, StepS
     }
     __syncthreads();
     if (writer) {
-    float4v v = *reinterpret_cast<const float4v*>(&sm.red[0][em * RT + ec]);
+        float4v v = *reinterpret_cast<const float4v*>(&sm.red[0][em * RT + ec]);
 #pragma unroll
-    for (int o = 1; o < kSWaves; ++o) v += *reinterpret_cast<const float4v*>(&sm.red[o][em * RT + ec]);
-    half4v out;
+        for (int o = 1; o < kSWaves; ++o) v += *reinterpret_cast<const float4v*>(&sm.red[o][em * RT + ec]);
+        half4v out;
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-        float f = v[e] + (float)eb[e];
-        if (PH == kStepFfn1) f = gelu_tanh(f);
-        if (RES) f += (float)er[e];
-        out[e] = (half_t)f;
-    }
-    if constexpr (PH == kStepQkv) {
-        publish(w.set + word_at(a.bqkv, em, en), out);
-        const int which = en / H, c = en - which * H;
-        if (which != 0 && epos >= 0 && epos < a.max_seq)      // past the capacity (replays the host never saw): dropped
-            *reinterpret_cast<half4v*>((which == 1 ? L.k_cache : L.v_cache) + ((size_t)(em * a.heads + c / a.d) * a.max_seq + epos) * a.d + c % a.d) = out;
-    } else if constexpr (PH == kStepOut) {
-        publish(w.set + word_at(a.by, em, en), out);
-    } else if constexpr (PH == kStepFfn1) {
-        publish(w.set + word_at(a.bf, em, en), out);
-    } else {
-        if (last) *reinterpret_cast<half4v*>(a.out + (size_t)em * H + en) = state & kStepGaveUp || sm.gave_up ? no_result() : out;
-        else publish(w.other + word_at(a.bx, em, en), out);
-    }
+        for (int e = 0; e < 4; ++e) {
+            float f = v[e] + (float)eb[e];
+            if (PH == kStepFfn1) f = gelu_tanh(f);
+            if (RES) f += (float)er[e];
+            out[e] = (half_t)f;
+        }
+        if constexpr (PH == kStepQkv) {
+            publish(w.set + word_at(a.bqkv, em, en), out);
+            const int which = en / H, c = en - which * H;
+            if (which != 0 && epos >= 0 && epos < a.max_seq)      // past the capacity (replays the host never saw): dropped
+                *reinterpret_cast<half4v*>((which == 1 ? L.k_cache : L.v_cache) + ((size_t)(em * a.heads + c / a.d) * a.max_seq + epos) * a.d + c % a.d) = out;
+        } else if constexpr (PH == kStepOut) {
+            publish(w.set + word_at(a.by, em, en), out);
+        } else if constexpr (PH == kStepFfn1) {
+            publish(w.set + word_at(a.bf, em, en), out);
+        } else {
+            if (last) *reinterpret_cast<half4v*>(a.out + (size_t)em * H + en) = state & kStepGaveUp || sm.gave_up ? no_result() : out;
+            else publish(w.other + word_at(a.bx, em, en), out);
+        }
     }
     if constexpr (PH == kStepQkv) {
         // what this item emptied of the other set is empty in memory before it is counted

@@ -41,14 +41,16 @@ constexpr size_t kFfnRowPad = 64;
 constexpr int kFfnPadFrom = 32768;
 
 // Byte offsets of the pieces of a layer's workspace.
-// The fp32 sums of a projection cut along K (gemm_k_ranges) lie in activation buffers that nobody needs while it runs, and
+// The fp32 sums of a projection cut along K (gemm_cut_ranges) lie in activation buffers that nobody needs while it runs, and
 // run over into `cut` between them: buf_f + cut during the attention output projection (its input is in buf_a), cut + buf_a
 // + buf_b during the second feed-forward projection (its input is in buf_f, its residual in buf_y).  `cut` is what is missing:
 // nothing with a prompt capacity of a few thousand rows, and never more than 8 MiB, since a launch is cut into at most 256
 // tiles of 128 x 64 sums (4 MiB with at most 64 rows, 2 MiB with at most 32).  With few rows that takes a workspace past the
 // bound the paper gives for its buffers (hidden 4096, 48 sequences of one row: 3.0 -> 5.4 MB where the bound is 3.1; hidden
-// 1024, 512 rows: 7.5 -> 13.8, bound 9.4); held inside the bound the first could not cut its second feed-forward
-// projection at all (29 us -> 71 us).
+// 1024, 512 rows: 7.5 -> 13.8, bound 9.4; since a prompt's projections are cut from smaller weights on: hidden 768, 4 x 64 rows 2.8 ->
+// 6.9, bound 3.5; hidden 1024, 64 rows 1.0 -> 2.9, bound 1.2, 37 rows 0.55 -> 1.7, bound 0.65); held inside the bound the first
+// could not cut its second feed-forward projection at all (29 us -> 71 us), a prompt of 37 rows would take 50 us per layer
+// instead of 40.  Decode steps that run as one launch add two exchange sets (hidden 1024, 16 sequences of one row 0.36 -> 0.90).
 struct WorkspaceLayout {
     size_t lens, cu, row_map, buf_f, cut, buf_a, buf_b, buf_y, part, step, row_stats, total;
     uint32_t step_set_words;           // of one exchange set of the decode steps that run as one launch (0: none do)
@@ -185,7 +187,7 @@ int eet_layer_destroy(eet_layer_t* layer) {
 // Cuts the K of a bias + residual projection of `L` where that pays; `sums`: where in the workspace its sums lie.  The rule and
 // the sizes are those layout_of reserved by.
 static void cut_projection(eet_layer* L, GemmArgs& g, size_t sums) {
-    const int ranges = g.res_row_map != nullptr || g.out_row_map != nullptr ? prompt_k_ranges(g.M, g.N, g.K) : gemm_k_ranges(g.M, g.N, g.K);
+    const int ranges = gemm_cut_ranges(g);
     if (ranges <= 1) return;
     g.k_ranges = ranges;
     g.part = reinterpret_cast<float*>(L->ws + sums);

@@ -1459,8 +1459,9 @@ static bool try_flat(const GemmArgs& a, Epilogue epi, hipStream_t s, bool ask_on
     if (lds > kFlatLdsLimit) return false;
     if (ask_only) return true;
     if (nw == 4) {
-        // few columns: 8 per workgroup put twice the workgroups on the chip (hidden-1024 output projection: 64 -> 128
-        // beside its 128 prefetch workgroups; 512 decode steps of the 24-layer stack 324.9 -> 322.6 ms, same call)
+        // few columns: 8 per workgroup put twice the workgroups on the chip (output projection of hidden 1024: 64 -> 128 beside
+        // its 128 prefetch workgroups, 324.9 -> 322.6 ms for 512 steps of 24 layers while such steps went launch by launch; wide
+        // feed-forward parts and more than 16 rows still come here)
         if (ln) launch_flat<4, 16, true>(a, upw, epi, lds, s);
         else if (a.N / 16 < tn8_wgs) launch_flat<4, 8, false>(a, upw, epi, lds, s);
         else launch_flat<4, 16, false>(a, upw, epi, lds, s);
@@ -1560,7 +1561,7 @@ static bool try_stream(const GemmArgs& a, Epilogue epi, hipStream_t s) {
 // no LayerNorm, prefetch or length update rides on the call (the weight-streaming kernels' business)
 static bool is_plain(const GemmArgs& a) { return a.ln_gamma == nullptr && a.pf.blocks == 0 && a.bump_lens == nullptr; }
 static bool rows_stream(const GemmArgs& a, Epilogue epi) {
-    if (a.k_ranges > 1 && epi == EPI_BIAS_RES) return true;          // the caller asked gemm_k_ranges
+    if (a.k_ranges > 1 && epi == EPI_BIAS_RES) return true;          // the caller asked gemm_cut_ranges
     return is_plain(a) && rows_stream_uncut(a.M, a.N, a.K, a.read_once != 0);
 }
 
@@ -1630,6 +1631,9 @@ static bool goes_to_tile_kernel(const GemmArgs& a) {
     return a.M > 16 && !sliced;
 }
 bool gemm_takes_row_strides(const GemmArgs& a) { return a.M > 16 && a.x_splits <= 1; }
+int gemm_cut_ranges(const GemmArgs& a) {
+    return a.res_row_map != nullptr || a.out_row_map != nullptr ? prompt_k_ranges(a.M, a.N, a.K) : gemm_k_ranges(a.M, a.N, a.K);
+}
 
 // The same problem without its first m0 rows (EPI_QKV: the prefill form, whose rows carry their sequence and position in
 // tok_row_map; the decode form takes the sequence from the row number and is never cut).
@@ -1661,7 +1665,7 @@ hipError_t launch_gemm(const GemmArgs& a, Epilogue epi, hipStream_t s) {
                                         a.N % (16 * stream_column_blocks(a, epi)) == 0)) return hipErrorInvalidValue;
     if (a.row_stats_in != nullptr && !(takes_row_stats(a, epi) && !try_flat(a, epi, nullptr, true) && stream_column_blocks(a, epi) != 0)) return hipErrorInvalidValue;
     // the cut along K is the caller's choice, and its operands are its own
-    if (a.k_ranges > 1 && (epi != EPI_BIAS_RES || a.part == nullptr || a.k_ranges != (a.res_row_map != nullptr || a.out_row_map != nullptr ? prompt_k_ranges(a.M, a.N, a.K) : gemm_k_ranges(a.M, a.N, a.K)) || (a.ldy != 0 && a.ldy != a.N) || a.ln_gamma != nullptr || a.pf.blocks != 0)) return hipErrorInvalidValue;
+    if (a.k_ranges > 1 && (epi != EPI_BIAS_RES || a.part == nullptr || a.k_ranges != gemm_cut_ranges(a) || (a.ldy != 0 && a.ldy != a.N) || a.ln_gamma != nullptr || a.pf.blocks != 0)) return hipErrorInvalidValue;
     if (a.fin_gamma != nullptr && a.k_ranges <= 1) return hipErrorInvalidValue;
     if (a.M > 16 && rows_stream(a, epi)) return launch_rows(a, epi, s);
     if (epi == EPI_BIAS && is_plain(a) && short_k_wide(a.M, a.N, a.K)) {

@@ -112,7 +112,7 @@ struct GemmArgs {
     // out of it.  Uncut projections of 65 rows and more take that stream with the hint only (tile_rules.hpp: rows_stream_uncut).
     int read_once;
     // EPI_BIAS_RES with 17 rows and more: room for the fp32 sums of the K ranges a narrow output is cut into, k_ranges of
-    // them (gemm_k_ranges, or prompt_k_ranges for a call with row maps, says how many; <= 1 or part == nullptr: no cut).  [k_ranges][M][N], read by finish_rows.
+    // them (gemm_cut_ranges says how many; <= 1 or part == nullptr: no cut).  [k_ranges][M][N], read by finish_rows.
     float* part;
     int k_ranges;
     // with k_ranges > 1 only: LayerNorm of the finished rows into fin_y[m] ([M, N]) by the same launch (nullptr = no), and
@@ -135,8 +135,9 @@ bool gemm_takes_prefetch(const GemmArgs& a);
 bool gemm_merges_attention_ranges(const GemmArgs& a);
 
 // Adds up the K ranges a.part of a cut projection (rowops.hip); N a multiple of 8, at most kFinishRowsMaxWidth.
-// How many ranges the K of a bias + residual projection is worth cutting into is gemm_k_ranges or, with row maps, prompt_k_ranges (tile_rules.hpp): the caller
-// that has room for their sums ([ranges][M][N] floats) sets GemmArgs::part and k_ranges, for M up to kGemmCutMaxM.
+// How many ranges the K of a bias + residual projection is worth cutting into (tile_rules.hpp: prompt_k_ranges for a call with row maps, gemm_k_ranges
+// otherwise): the caller that has room for their sums ([ranges][M][N] floats) sets GemmArgs::part and k_ranges, for M up to kGemmCutMaxM.
+int gemm_cut_ranges(const GemmArgs& a);
 hipError_t launch_finish_rows(const GemmArgs& a, hipStream_t s);
 
 // M > 16: MFMA tile kernel.  M <= 16 (decode): weight-streaming kernel.
