@@ -135,8 +135,9 @@ int eet_layer_encode(eet_layer_t *layer, const int32_t *q_lens, int32_t batch, i
  * not stored and the attention stops at max_seq keys: that sequence's results are then
  * meaningless, nothing else is affected).  The same holds for the stack and model entry points.
  * A step of a small layer is one launch whose parts wait for one another.  Should such a wait, which takes microseconds, have
- * to give up after a tenth of a second or more, the launch still ends, its output and that of all later steps is NaN, and
- * eet_cache_lens returns HIP, until the next prefill or restore; cache rows from that step on are then meaningless. */
+ * to give up after a tenth of a second or more, the launch still ends, what depends on it is NaN, and until the next
+ * prefill or restore the output of all later steps is NaN and eet_cache_lens returns HIP; cache rows from that step on are
+ * then meaningless. */
 int eet_decode_step(eet_layer_t *layer, const void *tokens, void *out, void *kv_cache,
                     void *hip_stream);
 

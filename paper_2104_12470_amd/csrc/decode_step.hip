@@ -28,9 +28,10 @@
 //               which writes x(g+1) into the other set, once resets >= (g+1) * (QKV items).
 //   progress    An item waits only for items with lower numbers, and a workgroup takes its number from a counter when it starts
 //               to run, so whatever an item waits for runs already or has finished: no assumption about how many workgroups are resident, in
-//               which order they start, or what else runs on the device.  The waits are bounded all the same (kSpinLimit), and one that
-//               gives up says so in ctl before its item hands anything on: from then on the exchange sets may hold words of another layer, so
-//               every output of this launch and of those that follow is NaN until the area is set up again (prefill, restore).
+//               which order they start, or what else runs on the device.  The waits are bounded all the same (kSpinLimit).  Words that did
+//               not come read as NaN, an item that found its exchange set still in use hands NaN on, and both say so in ctl: the sets
+//               may hold words of another layer from then on, so the output of every later launch is NaN until the area is set up again
+//               (prefill, restore).
 //
 // K/V rows of earlier tokens are ordinary memory (written by earlier launches); the new token's K and V row reaches the attention
 // through the exchange set, and the cache for the steps that follow.
@@ -78,7 +79,7 @@ struct StepSmem {
     float red[kSWaves][16 * 68];                   // [wave][row][up to 64 columns + 4]
     float stat[kSWaves][16][2];                    // [wave][row] mean and squared deviations of the wave's share of the row
     word_t ticket;
-    int gave_up;                                   // a wait of this item came to its bound
+    int in_use;                                    // the wait for the exchange set came to its bound
 };
 
 template <int CTRL>
@@ -98,15 +99,13 @@ struct Where {
     int lane, wave, tid;
     word_t* set;                                   // exchange set of layer g
     word_t* other;                                 // ... and of layers g-1 and g+1
+    bool void_area;                                // a wait was given up since the area was set up
 };
 
-// A wait of this item came to its bound: said in ctl, and in memory, before anything that follows from it.  (At the wait itself, where it
-// costs the chain nothing: a flag looked at once, before the item hands its result on, is 10.56 -> 10.72 us per layer-step of 24 x hidden 1024.)
-__device__ __forceinline__ void give_up(const StepArgs& a, StepSmem& sm) {
-    sm.gave_up = 1;
-    __hip_atomic_fetch_or(a.ctl, (word_t)kStepGaveUp, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-}
+// A wait came to its bound: said in ctl.  (At the wait itself, and read with the item's number in later launches, where neither costs the chain
+// anything: a flag looked at before each result is handed on was 10.56 -> 10.72 us per layer-step of 24 x hidden 1024, ctl looked at before
+// the last output is written up to 0.9 us per launch, 28.2 -> 29.0 for one layer of hidden 1280.)
+__device__ __forceinline__ void give_up(const StepArgs& a) { __hip_atomic_fetch_or(a.ctl, (word_t)kStepGaveUp, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 
 // Thread 0 waits until the exchange set is this layer's, then for one word of the phase before the one whose output the item
 // needs: the tight polling that follows lasts one phase instead of a whole layer.  `input`: a word of the input itself, for the QKV
@@ -122,9 +121,11 @@ __device__ __forceinline__ void wait_resets(const StepArgs& a, StepSmem& sm, uin
         if (++spin == kSpinLimit) break;
         __builtin_amdgcn_s_sleep(16);
     }
-    give_up(a, sm);
+    sm.in_use = 1;
+    give_up(a);
 }
-__device__ __forceinline__ void gate(const StepArgs& a, const Where& w, StepSmem& sm, const word_t* before, const word_t* input, bool emptied_by_this_layer) {
+// -> whether that set came in time
+__device__ __forceinline__ bool gate(const StepArgs& a, const Where& w, StepSmem& sm, const word_t* before, const word_t* input, bool emptied_by_this_layer) {
     if (w.tid == 0) {
         wait_resets(a, sm, w.g);
         if (before != nullptr)
@@ -136,21 +137,19 @@ __device__ __forceinline__ void gate(const StepArgs& a, const Where& w, StepSmem
         if (emptied_by_this_layer) wait_resets(a, sm, w.g + 1u);
     }
     __syncthreads();
+    return sm.in_use == 0;
 }
 
-__device__ __forceinline__ word_t wait_word(const StepArgs& a, StepSmem& sm, const word_t* p) {
+__device__ __forceinline__ word_t wait_word(const StepArgs& a, const word_t* p) {
     word_t v;
     int spin = 0;
     do v = ld_word(p);
     while ((v == kEmpty) & (++spin < kSpinLimit));
-    if (v == kEmpty) give_up(a, sm);
+    if (v == kEmpty) give_up(a);
     return v;
 }
 
-__device__ __forceinline__ half4v no_result() {
-    const half_t nan = __builtin_bit_cast(half_t, (unsigned short)0x7e00);
-    return half4v{nan, nan, nan, nan};
-}
+__device__ __forceinline__ half_t no_value() { return __builtin_bit_cast(half_t, (unsigned short)0x7e00); }
 
 // ---- one item of a projection: 16*NT columns, all rows (at most 16), K in units of 64 dealt round-robin to the waves ------------
 enum StepPhase { kStepQkv = 0, kStepOut = 1, kStepFfn1 = 2, kStepFfn2 = 3 };
@@ -261,9 +260,12 @@ __device__ __forceinline__ void project(const StepArgs& a, const Where& w, StepS
     const word_t* before = PH == kStepQkv ? (first ? nullptr : w.other + a.bf.at)
                          : PH == kStepOut ? w.set + a.bqkv.at
                          : PH == kStepFfn1 ? w.set + a.bctx.at : w.set + a.by.at;
-    gate(a, w, sm, before, PH == kStepQkv ? w.set + in.at : nullptr, PH == kStepFfn2);
+    const bool in_time = gate(a, w, sm, before, PH == kStepQkv ? w.set + in.at : nullptr, PH == kStepFfn2);
     if (RES && writer && !(PH == kStepOut && first))
-        er = __builtin_bit_cast(half4v, wait_word(a, sm, w.set + word_at(PH == kStepOut ? a.bx : a.by, em, en)));
+        er = __builtin_bit_cast(half4v, wait_word(a, w.set + word_at(PH == kStepOut ? a.bx : a.by, em, en)));
+    // not in time: every value of the item becomes NaN, by way of the LayerNorm or of the residual
+    const float eps = in_time ? a.eps : __builtin_nanf("");
+    if (RES && !in_time) er = half4v{no_value(), no_value(), no_value(), no_value()};
     halfE xv[STEPS];
     const bool mine = row < M;
     if (PH == kStepQkv && first) {
@@ -299,7 +301,7 @@ __device__ __forceinline__ void project(const StepArgs& a, const Where& w, StepS
 #pragma unroll
                             for (int e = 0; e <= E / 2; ++e) ok &= v[r][e] != kEmpty;
                     } while (!ok & (++spin < kSpinLimit));
-                    if (!ok) give_up(a, sm);
+                    if (!ok) give_up(a);
 #pragma unroll
                     for (int r = 0; r < 2; ++r) {
                         const float2v ml = __builtin_bit_cast(float2v, v[r][E / 2]);
@@ -355,7 +357,7 @@ __device__ __forceinline__ void project(const StepArgs& a, const Where& w, StepS
                 }
             ok = __all(most != kEmptyHalf);
         } while (!ok & (++spin < kSpinLimit));
-        if (!ok) give_up(a, sm);
+        if (!ok) give_up(a);
         struct Words { word_t w[VW]; };
 #pragma unroll
         for (int s = 0; s < STEPS; ++s) {
@@ -366,10 +368,7 @@ __device__ __forceinline__ void project(const StepArgs& a, const Where& w, StepS
         }
     }
     asm volatile("" ::: "memory");
-    uint32_t state = 0;
     if constexpr (PH == kStepFfn2) {
-        // looked at after all that this item's output comes from, and back before the output is written
-        if (last && writer) state = __hip_atomic_load(reinterpret_cast<const uint32_t*>(a.ctl), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         // everyone who reads the cache lengths in this step is an ancestor of this item's input
         if (last && a.bump && tile == 0) {
             __syncthreads();                                   // all waves have their share of the input: together, all of it
@@ -427,7 +426,7 @@ __device__ __forceinline__ void project(const StepArgs& a, const Where& w, StepS
             const float d = sv[v][0] - mean;
             m2 += sv[v][1] + (float)(64 * c) * d * d;
         }
-        const float rstd = rsqrtf(m2 * inv_k + a.eps);
+        const float rstd = rsqrtf(m2 * inv_k + eps);
 #pragma unroll
         for (int s = 0; s < STEPS; ++s)
 #pragma unroll
@@ -489,8 +488,10 @@ __device__ __forceinline__ void project(const StepArgs& a, const Where& w, StepS
         } else if constexpr (PH == kStepFfn1) {
             publish(w.set + word_at(a.bf, em, en), out);
         } else {
-            if (last) *reinterpret_cast<half4v*>(a.out + (size_t)em * H + en) = state & kStepGaveUp || sm.gave_up ? no_result() : out;
-            else publish(w.other + word_at(a.bx, em, en), out);
+            if (last) {
+                if (w.void_area) out = half4v{no_value(), no_value(), no_value(), no_value()};
+                *reinterpret_cast<half4v*>(a.out + (size_t)em * H + en) = out;
+            } else publish(w.other + word_at(a.bx, em, en), out);
         }
     }
     if constexpr (PH == kStepQkv) {
@@ -540,7 +541,7 @@ __device__ __forceinline__ void attend(const StepArgs& a, const Where& w, StepSm
 #pragma unroll
     for (int i = 0; i < PF; ++i)
         if (j0 + i * kSWaves * BK < ce) request(kr[i], vr[i], j0 + i * kSWaves * BK);
-    gate(a, w, sm, w.layer == 0 ? nullptr : w.set + a.bx.at, nullptr, false);
+    const bool in_time = gate(a, w, sm, w.layer == 0 ? nullptr : w.set + a.bx.at, nullptr, false);
     const word_t* qkv = w.set + word_at(a.bqkv, b, h * D + chunk * 8);
     const uint32_t to_k = (uint32_t)(a.H >> a.bqkv.log_cols) * a.bqkv.block;
     half8v qv, kn, vn;
@@ -563,7 +564,7 @@ __device__ __forceinline__ void attend(const StepArgs& a, const Where& w, StepSm
             if (take_new) ok &= v[2] != kEmpty && v[3] != kEmpty && v[4] != kEmpty && v[5] != kEmpty;
             ok = __all(ok);
         } while (!ok & (++spin < kSpinLimit));
-        if (!ok) give_up(a, sm);
+        if (!ok) give_up(a);
         auto join = [](word_t x, word_t y) {
             return __builtin_shufflevector(__builtin_bit_cast(half4v, x), __builtin_bit_cast(half4v, y), 0, 1, 2, 3, 4, 5, 6, 7);
         };
@@ -573,7 +574,7 @@ __device__ __forceinline__ void attend(const StepArgs& a, const Where& w, StepSm
             vn = join(v[4], v[5]);
         }
     }
-    const float c = rsqrtf((float)D) * kLog2e;
+    const float c = in_time ? rsqrtf((float)D) * kLog2e : __builtin_nanf("");      // not in time: NaN
     auto score = [&](const half8v& k) {
         float d = 0.f;
 #pragma unroll
@@ -694,16 +695,17 @@ __global__ __launch_bounds__(kSThreads, 2) void decode_layers(StepArgs a) {
         if (((uint32_t)t & ~kStepGaveUp) == (uint32_t)a.items - 1u)
             __hip_atomic_fetch_add(a.ctl, ((word_t)a.n_layers << 32) - (word_t)a.items, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         sm.ticket = t;
-        sm.gave_up = 0;
+        sm.in_use = 0;
     }
     __syncthreads();
-    const uint32_t item = __builtin_amdgcn_readfirstlane((uint32_t)sm.ticket) & ~kStepGaveUp, g0 = __builtin_amdgcn_readfirstlane((uint32_t)(sm.ticket >> 32));
+    const uint32_t low = __builtin_amdgcn_readfirstlane((uint32_t)sm.ticket), item = low & ~kStepGaveUp, g0 = __builtin_amdgcn_readfirstlane((uint32_t)(sm.ticket >> 32));
     if (item >= (uint32_t)a.items) return;
     w.layer = (int)(item / (uint32_t)a.per_layer);
     int r = (int)(item - (uint32_t)w.layer * (uint32_t)a.per_layer);
     w.g = g0 + (uint32_t)w.layer;
     w.set = a.ex + (size_t)(w.g & 1u) * a.set_words;
     w.other = a.ex + (size_t)(~w.g & 1u) * a.set_words;
+    w.void_area = (low & kStepGaveUp) != 0;
     if (r < a.n_qkv) { project<ROWS, UH, NTH, kStepQkv, ONCE>(a, w, sm, r); return; }
     r -= a.n_qkv;
     if (r < a.n_att) {
