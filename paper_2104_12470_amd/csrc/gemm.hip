@@ -293,7 +293,7 @@ __device__ __forceinline__ void wait_vm() {
 // fragments of a k half (AN reads of 16 bytes per lane) serve both row halves and are read with the first; every sub-step
 // reads AM/2 activation fragments; both kinds are double-buffered in registers, so the reads of sub-step s+1 fly during
 // the AM/2 * AN multiplies of sub-step s, and the other wave of the SIMD covers what still shows.  With one wave per SIMD
-// (pipe::gemm_k_loop_interleaved) nothing covers a stall, and a burst of LDS reads stalls the issuing wave, multiplies
+// (pipe::gemm_k_loop_spread) nothing covers a stall, and a burst of LDS reads stalls the issuing wave, multiplies
 // included, until the LDS queue drains (16 reads in a row in front of 64 multiplies: 1840 cycles against 1055 for the
 // multiplies alone; one read after every third multiply: 1080); there the fragments of a whole k half are
 // double-buffered and every request sits between two multiplies.
@@ -371,7 +371,7 @@ struct GemmTileExec {
             for (int j = 0; j < AN; ++j) asm volatile("" : "+v"(fw[SUB >> 1][j]));
         }
     }
-    // ---- the one-wave-per-SIMD schedule (pipe::gemm_k_loop_interleaved): whole k halves, double-buffered -------------
+    // ---- the one-wave-per-SIMD schedule (pipe::gemm_k_loop_spread): whole k halves, double-buffered -------------
     // LDS read number R of k half H into buffer H: the AN weight fragments, then the AM activation fragments
     template <int H, int R>
     __device__ __forceinline__ void half_read(unsigned va_, unsigned vw_) {
@@ -381,10 +381,6 @@ struct GemmTileExec {
     template <int H, int... R>
     __device__ __forceinline__ void half_read_all(unsigned va_, unsigned vw_, std::integer_sequence<int, R...>) {
         (half_read<H, R>(va_, vw_), ...);
-    }
-    template <int H>
-    __device__ __forceinline__ void fetch_half(int stage) {
-        half_read_all<H>(a_lds + stage * (BM * BK * 2) + foff[H], w_lds + stage * (BN * BK * 2) + foff[H], std::make_integer_sequence<int, AM + AN>{});
     }
     __device__ __forceinline__ void wait_fetched() {
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
@@ -397,11 +393,11 @@ struct GemmTileExec {
         }
     }
     // multiply number IDX of k half H, followed by its share of the side work: the reads of the other k half and the tile
-    // loads, each spread over the first three quarters of the phase (the last quarter lets the reads land; loads issued
-    // later arrive later); scheduling barriers pin each request between the two multiplies it was written between
-    template <int H, bool LOAD, int IDX>
+    // loads of one operand (LOADS: 1 the activations, 2 the weights), each spread over the first three quarters of the phase (the last quarter
+    // lets the reads land; loads issued later arrive later); scheduling barriers pin each request between the two multiplies it was written between
+    template <int H, int LOADS, int IDX>
     __device__ __forceinline__ void half_mma_one(unsigned va_, unsigned vw_, int64_t koff, int lstage) {
-        constexpr int MF = AM * AN, NR = AM + AN, NL = LIA + LIW;
+        constexpr int MF = AM * AN, NR = AM + AN, NL = LOADS == 1 ? LIA : LIW;
         constexpr int RS = (MF * 3 / 4) / NR, LS = (MF * 3 / 4) / NL;   // multiplies per read, per load (both measured best at 3 for 64)
         static_assert(RS >= 1 && LS >= 1, "side work fits between the multiplies");
         constexpr int i = IDX / AN, j = IDX % AN;
@@ -411,29 +407,45 @@ struct GemmTileExec {
             half_read<1 - H, IDX / RS>(va_, vw_);
             __builtin_amdgcn_sched_barrier(0);
         }
-        if constexpr (LOAD && IDX % LS == LS / 2 && IDX / LS < NL) {
+        if constexpr (IDX % LS == LS / 2 && IDX / LS < NL) {
             constexpr int v = IDX / LS;
             __builtin_amdgcn_sched_barrier(0);
-            if constexpr (v < LIA) load_lds_16B(pa[v % LIA] + koff, as_base + lstage * (BM * BK) + (wave * LRA + v * 8) * BK);
-            else load_lds_16B(pw[(v - LIA) % LIW] + koff, ws_base + lstage * (BN * BK) + (wave * LRW + (v - LIA) * 8) * BK);
+            if constexpr (LOADS == 1) load_lds_16B(pa[v % LIA] + koff, as_base + lstage * (BM * BK) + (wave * LRA + v * 8) * BK);
+            else load_lds_16B(pw[v % LIW] + koff, ws_base + lstage * (BN * BK) + (wave * LRW + v * 8) * BK);
             __builtin_amdgcn_sched_barrier(0);
         }
     }
-    template <int H, bool LOAD, int... I>
+    template <int H, int LOADS, int... I>
     __device__ __forceinline__ void half_mma_seq(unsigned va_, unsigned vw_, int64_t koff, int lstage, std::integer_sequence<int, I...>) {
         __builtin_amdgcn_sched_barrier(0);
-        (half_mma_one<H, LOAD, I>(va_, vw_, koff, lstage), ...);
+        (half_mma_one<H, LOADS, I>(va_, vw_, koff, lstage), ...);
         __builtin_amdgcn_sched_barrier(0);
     }
-    template <int H>
-    __device__ __forceinline__ void mma_half_fetch(int stage) {
-        half_mma_seq<H, false>(a_lds + stage * (BM * BK * 2) + foff[1 - H], w_lds + stage * (BN * BK * 2) + foff[1 - H], 0, 0,
-                               std::make_integer_sequence<int, AM * AN>{});
+    __device__ __forceinline__ void load_a(int tile, int stage) {
+#pragma unroll
+        for (int v = 0; v < LIA; ++v) load_lds_16B(pa[v] + (int64_t)tile * BK, as_base + stage * (BM * BK) + (wave * LRA + v * 8) * BK);
+    }
+    __device__ __forceinline__ void load_w(int tile, int stage) {
+#pragma unroll
+        for (int v = 0; v < LIW; ++v) load_lds_16B(pw[v] + (int64_t)tile * BK, ws_base + stage * (BN * BK) + (wave * LRW + v * 8) * BK);
+    }
+    template <int LA, int LW>
+    __device__ __forceinline__ void wait_loads() {
+        asm volatile("s_waitcnt vmcnt(%0)" ::"n"(LA * LIA + LW * LIW) : "memory");
     }
     template <int H>
-    __device__ __forceinline__ void mma_half_fetch_load(int stage, int tile, int lstage) {
-        half_mma_seq<H, true>(a_lds + stage * (BM * BK * 2) + foff[1 - H], w_lds + stage * (BN * BK * 2) + foff[1 - H],
-                              (int64_t)(tile * KS + kg) * BK, lstage, std::make_integer_sequence<int, AM * AN>{});
+    __device__ __forceinline__ void fetch_half(int astage, int wstage) {
+        half_read_all<H>(a_lds + astage * (BM * BK * 2) + foff[H], w_lds + wstage * (BN * BK * 2) + foff[H], std::make_integer_sequence<int, AM + AN>{});
+    }
+    template <int H>
+    __device__ __forceinline__ void mma_fetch_load_a(int astage, int wstage, int tile, int lstage) {
+        half_mma_seq<H, 1>(a_lds + astage * (BM * BK * 2) + foff[1 - H], w_lds + wstage * (BN * BK * 2) + foff[1 - H], (int64_t)tile * BK, lstage,
+                           std::make_integer_sequence<int, AM * AN>{});
+    }
+    template <int H>
+    __device__ __forceinline__ void mma_fetch_load_w(int astage, int wstage, int tile, int lstage) {
+        half_mma_seq<H, 2>(a_lds + astage * (BM * BK * 2) + foff[1 - H], w_lds + wstage * (BN * BK * 2) + foff[1 - H], (int64_t)tile * BK, lstage,
+                           std::make_integer_sequence<int, AM * AN>{});
     }
     template <int BUF, int SUB>
     __device__ __forceinline__ void mma() {
@@ -449,8 +461,13 @@ struct GemmTileExec {
     }
 };
 
-// SCHED: 0 = the schedule of pipe::gemm_k_loop<NS>, 1 = its early-release form (two stages), 2 = the schedule for one wave
-// per SIMD (pipe::gemm_k_loop_interleaved<NS>; one K group; wave tiles of an odd number of 16-row blocks too)
+// SCHED: 0 = the schedule of pipe::gemm_k_loop<NS>; the schedule for one wave per SIMD (one K group; wave tiles of an odd number of 16-row
+// blocks too) with NS stages of both operands, 2 = pipe::gemm_k_loop_spread<NS, NS>, or with one more of the activations, 1 = <NS + 1, NS>.
+// us, all loads of a step behind its barrier -> spread over both halves (rows x N x K): 256 x 256 tiles, two stages -> three and two: 3262 x 4096 x 4096
+// 95.9 -> 88.1, 6758 x 2048 x 8192 208 -> 186, 3262 x 4096 x 16384 351 -> 324, 12288 x 4096 x 12288 932 -> 873, 4096 x 8192 x 32768 2192 -> 1532 (rows
+// 64 KB apart; 128 bytes further 1884 -> 1532), at K = 2048 0 to 2 %; pairs of 128 x 128: 1200 x 6144 x 2048 33.5 -> 31.9; 192 x 128: 700 x 6144 x
+// 2048 24.4 -> 22.4; 96 x 128: 1200 x 2048 x 2048 15.4 -> 14.5, 3054 x 1024 x 4096 29.5 -> 28.4; 128 x 256: 400 x 12288 x 4096 55.4 -> 54.5.  More stages
+// than these gain nothing (96 x 128 in five, 192 x 128 in four, 128 x 256 in four and three: level or 1 to 3 % slower).
 // NTS: the output is stored with the non-temporal hint (outputs of 256 MB and more, which no cache keeps for their reader:
 // 24576 x 49152 x 12288 21.70 -> 21.53 ms, 24576 x 12288 x 12288 5.69 -> 5.59, 8192 x 16384 x 12288 2.436 -> 2.393).
 // NTW: the weights are loaded with the non-temporal hint (one row tile: every weight is read once by the launch).
@@ -463,7 +480,7 @@ template <int BM, int BN, int WGM, int WGN, int EPI, int NS, int KS, int SCHED, 
 // (192 x 128 tiles are made for two workgroups per CU: the residual and cache-row look-ups of their epilogue would take the
 // kernel past 256 registers and halve that: 2000 x 4096 x 4096 with a residual 135 us)
 __global__ __launch_bounds__(WGM* WGN* KS * 64, BM == 192 && NS == 2 ? 2 : 1) void gemm_mfma_dma64(GemmArgs a, int tiles_m, int tiles_n) {
-    static_assert(SCHED == 0 || (KS == 1 && ((NS == 2 && SCHED == 1) || SCHED == 2)), "schedule");
+    static_assert(SCHED == 0 || (KS == 1 && (SCHED == 1 || (SCHED == 2 && NS > 2))), "schedule");
     // KS > 1: KS groups of WGM x WGN waves share the tile and take every KS-th K step each, through LDS stages of their
     // own; the other groups' accumulators are added to the first's through LDS at the end.  For the few
     // tiles of a narrow output with a long K, where nothing else puts more loads in flight per CU.
@@ -473,8 +490,9 @@ __global__ __launch_bounds__(WGM* WGN* KS * 64, BM == 192 && NS == 2 ? 2 : 1) vo
     constexpr int WM = BM / WGM, WN = BN / WGN, AM = WM / 16, AN = WN / 16;   // wave tile in 16 x 16 accumulator blocks
     constexpr int LRA = BM / NW, LRW = BN / NW;   // rows of each operand tile a wave loads per K step
     constexpr int LIA = LRA / 8, LIW = LRW / 8;   // wave-level load instructions per operand per K step
-    static_assert(LRA % 8 == 0 && LRW % 8 == 0 && LIA >= 1 && LIW >= 1 && WM % (SCHED == 2 ? 16 : 32) == 0 && (WN == 64 || WN == 128), "tile shape");
-    __shared__ __attribute__((aligned(1024))) half_t As[KS * NS][BM * BK];
+    static_assert(LRA % 8 == 0 && LRW % 8 == 0 && LIA >= 1 && LIW >= 1 && WM % (SCHED != 0 ? 16 : 32) == 0 && (WN == 64 || WN == 128), "tile shape");
+    constexpr int NSA = SCHED == 1 ? NS + 1 : NS;            // stages of the activations
+    __shared__ __attribute__((aligned(1024))) half_t As[KS * NSA][BM * BK];
     __shared__ __attribute__((aligned(1024))) half_t Ws[KS * NS][BN * BK];
 
     int tile_m, tile_n;
@@ -509,7 +527,7 @@ __global__ __launch_bounds__(WGM* WGN* KS * 64, BM == 192 && NS == 2 ? 2 : 1) vo
         ex.k_first = (((int)blockIdx.x >> 3) & 7) * nk >> 3;
         ex.k_count = nk;
     }
-    ex.as_base = &As[kg * NS][0];
+    ex.as_base = &As[kg * NSA][0];
     ex.ws_base = &Ws[kg * NS][0];
 #pragma unroll
     for (int v = 0; v < LIA; ++v) {
@@ -530,7 +548,7 @@ __global__ __launch_bounds__(WGM* WGN* KS * 64, BM == 192 && NS == 2 ? 2 : 1) vo
     // fragment rows: lane l reads row l%16 of a block, the 16 bytes (l/16) of k half h; rows are 128 bytes with their
     // 16-byte chunks XOR-permuted by (row/2)%8, and blocks start at multiples of 16 rows, so the permutation is the lane's own
     const int frow = lane & 15, fG = lane >> 4, fsw = frow >> 1;
-    ex.a_lds = (unsigned)(uintptr_t)&As[kg * NS][(wm0 + frow) * BK];
+    ex.a_lds = (unsigned)(uintptr_t)&As[kg * NSA][(wm0 + frow) * BK];
     ex.w_lds = (unsigned)(uintptr_t)&Ws[kg * NS][(wn0 + frow) * BK];
 #pragma unroll
     for (int h = 0; h < 2; ++h) ex.foff[h] = (unsigned)(((h * 4 + fG) ^ fsw) * 16);
@@ -540,8 +558,8 @@ __global__ __launch_bounds__(WGM* WGN* KS * 64, BM == 192 && NS == 2 ? 2 : 1) vo
     for (int i = 0; i < AM; ++i)
 #pragma unroll
         for (int j = 0; j < AN; ++j) acc[i][j] = float4v{0.f, 0.f, 0.f, 0.f};
-    if constexpr (SCHED == 2) pipe::gemm_k_loop_interleaved<NS>(ex, nk);
-    else pipe::gemm_k_loop<NS, SCHED == 1>(ex, nk);
+    if constexpr (SCHED != 0) pipe::gemm_k_loop_spread<NSA, NS>(ex, nk);
+    else pipe::gemm_k_loop<NS>(ex, nk);
 
     __syncthreads();                                      // every wave is done with the operand stages
     if constexpr (KS > 1) {
@@ -594,16 +612,10 @@ __global__ __launch_bounds__(WGM* WGN* KS * 64, BM == 192 && NS == 2 ? 2 : 1) vo
     }
     // with K groups the partial tiles above sit in the weight stages and group 0 may still be summing them while a faster
     // wave of the group already turns its tile around: that must then happen in the activation stages only
-    static_assert(KS == 1 || NW * EB <= (int)sizeof(As), "turn-around areas must not touch the partial tiles");
-    if constexpr (NW * EB <= (int)sizeof(As)) {
-        char* area = reinterpret_cast<char*>(&As[0][0]) + wave * EB;
-        epilogue_via_lds<AM, AN, 0, EPI, NTS>(a, acc, rv0, er0, er1, area, m0 + wm0, n0 + wn0, lane);
-        if constexpr (AN == 8) epilogue_via_lds<AM, AN, 4, EPI, NTS>(a, acc, rv1, er0, er1, area, m0 + wm0, n0 + wn0 + 64, lane);   // second 64 columns, same area
-    } else {
-        static_assert(NW == 8 && AN == 4 && 4 * EB <= (int)sizeof(As) && 4 * EB <= (int)sizeof(Ws), "turn-around areas");
-        epilogue_via_lds<AM, AN, 0, EPI, NTS>(a, acc, rv0, er0, er1, reinterpret_cast<char*>(wave < 4 ? &As[0][0] : &Ws[0][0]) + (wave & 3) * EB,
-                                         m0 + wm0, n0 + wn0, lane);
-    }
+    static_assert(NW * EB <= (int)sizeof(As), "turn-around areas");
+    char* area = reinterpret_cast<char*>(&As[0][0]) + wave * EB;
+    epilogue_via_lds<AM, AN, 0, EPI, NTS>(a, acc, rv0, er0, er1, area, m0 + wm0, n0 + wn0, lane);
+    if constexpr (AN == 8) epilogue_via_lds<AM, AN, 4, EPI, NTS>(a, acc, rv1, er0, er1, area, m0 + wm0, n0 + wn0 + 64, lane);   // second 64 columns, same area
 }
 
 // --------------------------------------------------------------------------------------------
@@ -1701,25 +1713,18 @@ hipError_t launch_gemm(const GemmArgs& a, Epilogue epi, hipStream_t s) {
         case kTile128x64: launch_dma64_cfg<4, 1, 128, 64, 3>(a, epi, s); break;
         case kTile192Pair: launch_dma64_cfg<2, 2, 192, 128, 2, 1, 0>(a, epi, s); break;
         case kTile128PairShared: launch_dma64_cfg<2, 2, 128, 128>(a, epi, s); break;
-        case kTile128Pair: launch_dma64_cfg<2, 2, 128, 128, 2, 1, 2>(a, epi, s); break;
+        case kTile128Pair: launch_dma64_cfg<2, 2, 128, 128, 2, 1, 1>(a, epi, s); break;
         case kTile96: launch_dma64_cfg<2, 2, 96, 128, 4, 1, 2>(a, epi, s); break;
         case kTile128: launch_dma64_cfg<2, 2, 128, 128, 3, 1, 2>(a, epi, s); break;
         case kTile192: launch_dma64_cfg<2, 2, 192, 128, 3, 1, 2>(a, epi, s); break;
         case kTile128x256: launch_dma64_cfg<2, 2, 128, 256, 3, 1, 2>(a, epi, s); break;
         case kTile256:
-            // Four waves with 128 x 128 each: a third less LDS read traffic per flop than eight waves of 128 x 64, and the
-            // LDS of a CU -- fragment reads plus the arriving tiles -- is what the matrix pipes otherwise wait for
-            // (rows x N x K, eight waves in two alternating groups -> four waves: 25082 x 49152 x 12288 1.16 -> 1.23 PFLOP/s,
-            // 8192 x 16384 x 12288 1.20 -> 1.33, 2951 x 16384 x 4096 1.13 -> 1.24).  With a very long K and rows that are a
-            // multiple of 32 KB apart the eight-wave kernel with the early release of the stage is ahead (25082 x 12288 x
-            // 49152: 1.09 against 0.97); once the rows are 128 bytes further apart (the layer's own feed-forward buffer is
-            // laid out so) both reach 1.16.
-            // (that comparison was on 18.4 rounds of tiles.  On whole rounds -- which is what the cut above leaves of such a
-            // launch -- the four waves are ahead at this K too: 24576 x 12288 x 49152 24.7 -> 23.7 ms, 4096 rows 3.97 -> 3.82;
-            // on part-filled rounds the eight waves stay ahead: 3000 x 4096 x 32768 0.80 against 0.87 ms.)
-            if (a.K >= 32768 && ((a.M + 255) / 256) * ((a.N + 255) / 256) % 256 != 0) launch_dma64_cfg<2, 4, 256, 256, 2, 1, 1>(a, epi, s);
-            else if ((size_t)a.M * a.N * sizeof(half_t) >= kMemorySideCacheBytes) launch_dma64_cfg<2, 2, 256, 256, 2, 1, 2, true>(a, epi, s);
-            else launch_dma64_cfg<2, 2, 256, 256, 2, 1, 2>(a, epi, s);
+            // Four waves with 128 x 128 each: a third less LDS read traffic per flop than eight waves of 128 x 64 (25082 x 49152 x 12288 1.16 ->
+            // 1.23 PFLOP/s, 8192 x 16384 x 12288 1.20 -> 1.33, 2951 x 16384 x 4096 1.13 -> 1.24), at every K and row stride since the loads of a step are
+            // spread over both of its halves (against eight waves with an early release of the stage, us: 3000 x 4096 x 32768 799 -> 661, 2048 x
+            // 12288 x 49152 2518 -> 2149, its rows 128 bytes further apart 2379 -> 2077, 5000 x 10240 x 40960 4307 -> 3704).
+            if ((size_t)a.M * a.N * sizeof(half_t) >= kMemorySideCacheBytes) launch_dma64_cfg<2, 2, 256, 256, 2, 1, 1, true>(a, epi, s);
+            else launch_dma64_cfg<2, 2, 256, 256, 2, 1, 1>(a, epi, s);
             break;
         }
     }

@@ -205,6 +205,47 @@ EET_PIPE_FN void gemm_k_loop_interleaved(Ops& op, int nk) {
 }
 
 // ---------------------------------------------------------------------------------------------------------
+// The same with the tile loads spread over both halves of a step, and rings of their own for activations and weights (NSA and NSW stages, NSA =
+// NSW or NSW + 1; tile t in stage t % NSA and t % NSW).  Behind the barrier of step kt, while k half 1 is multiplied, the weights of tile kt+NSW go into
+// the stage just released; the activations of tile kt+NSA-1 follow while k half 0 of the next step's tile is multiplied.  What it gives: half as many
+// requests at a time wait for the memory system, and a wave whose request finds no room there stops multiplying.  With NSA = NSW + 1 they are on their
+// way for as long as the weights; the 256 x 256 tile has three and two stages, 160 KB, all of the LDS.
+//
+// Executor interface: wait_fetched(), barrier() as above, and
+//   load_a(tile, stage), load_w(tile, stage)   issue this wave's loads of the activations / the weights of K tile `tile`
+//   wait_loads<LA, LW>()                       the loads of this wave have landed, except those of the newest LA load_a and LW load_w calls
+//   fetch_half<H>(astage, wstage)              issue the LDS reads of k half H into buffer H
+//   mma_fetch_load_a<H>(astage, wstage, tile, lstage)   multiply k half H out of buffer H; between the multiplies issue the reads of k half 1-H
+//                                              out of the two stages and load_a(tile, lstage); mma_fetch_load_w: load_w
+// ---------------------------------------------------------------------------------------------------------
+template <int NSA, int NSW, class Ops>
+EET_PIPE_FN void gemm_k_loop_spread(Ops& op, int nk) {
+    static_assert(NSW >= 2 && (NSA == NSW || NSA == NSW + 1), "the newest loads are those of the latest tiles of either ring");
+    auto tile = [&](int t) { return t < nk ? t : nk - 1; };
+    for (int t = 0; t < NSW; ++t) {
+        if (t < NSA - 1) op.load_a(tile(t), t);
+        op.load_w(tile(t), t);
+    }
+    op.template wait_loads<NSA - 2, NSW - 1>();   // tile 0 of this wave has landed ...
+    op.barrier();                                 // ... and everybody else's
+    op.template fetch_half<0>(0, 0);
+    int sa = 0, sw = 0;                           // stages of tile kt
+    for (int kt = 0; kt < nk; ++kt) {
+        const int sa1 = sa == NSA - 1 ? 0 : sa + 1, sa_free = sa == 0 ? NSA - 1 : sa - 1, sw1 = sw == NSW - 1 ? 0 : sw + 1;
+        op.wait_fetched();
+        op.template mma_fetch_load_a<0>(sa, sw, tile(kt + NSA - 1), sa_free);   // its stage was last read during step kt-1, before the barrier there
+        op.wait_fetched();                          // every read of tile kt has landed
+        op.template wait_loads<NSA - 2, NSW - 2>();   // this wave's part of tile kt+1 has landed
+        op.barrier();                             // ... and everybody else's; the stages of tile kt are free
+        op.template mma_fetch_load_w<1>(sa1, sw1, tile(kt + NSW), sw);          // (reads past the last tile: stale, never multiplied)
+        sa = sa1;
+        sw = sw1;
+    }
+    op.wait_fetched();                              // the stale reads and the repeated loads too: the epilogue reuses the stages
+    op.template wait_loads<0, 0>();
+}
+
+// ---------------------------------------------------------------------------------------------------------
 // Key-tile loop of the 256-row prefill attention: K and V tiles of 64 keys through two rings of three stages
 // (tile t in stage t % 3 of its ring).  During step jt the waves read V(jt) and K(jt+1) -- the scores of tile
 // jt were formed during step jt-1 -- while K(jt+2), V(jt+1) (requested during step jt-1) and K(jt+3), V(jt+2)

@@ -219,6 +219,78 @@ struct HalfStepRecorder {
 };
 
 // ------------------------------------------------------------------------------------------------------------------
+// recorder for pipe::gemm_k_loop_spread: the same fragment buffers, rings of their own for activations (0) and weights (1)
+// ------------------------------------------------------------------------------------------------------------------
+struct SpreadRecorder {
+    Trace t;
+    int nk, nsa, nsw;
+    int buf_read[2] = {-1, -1};                            // the read of the activations; that of the weights is the next one
+    int issued = 0;
+    std::vector<int> consumed;
+    SpreadRecorder(int nk_, int nsa_, int nsw_) : nk(nk_), nsa(nsa_), nsw(nsw_) {}
+    void load_a(int tile, int stage) {
+        if (stage < 0 || stage >= nsa) t.fail("R1 no such stage of the activations");
+        t.issue_load(0, stage, tile);
+    }
+    void load_w(int tile, int stage) {
+        if (stage < 0 || stage >= nsw) t.fail("R1 no such stage of the weights");
+        t.issue_load(1, stage, tile);
+    }
+    template <int LA, int LW>
+    void wait_loads() {
+        // the counter knows no operands: the newest LA + LW calls stay in flight, and they have to be LA of one kind and LW of the other
+        const int n = (int)t.loads_in_flight.size();
+        int a = 0, w = 0;
+        for (int i = n - 1; i >= 0 && i >= n - (LA + LW); --i) (t.loads[t.loads_in_flight[i]].ring == 0 ? a : w) += 1;
+        if (a > LA || w > LW) t.fail("R3 a load count does not match the order the loads were issued in");
+        t.retire_loads((size_t)(LA + LW));
+    }
+    void barrier() { t.barrier(); }
+    template <int H>
+    void fetch_half(int astage, int wstage) {
+        const int idx = issued++;
+        if (H != idx % 2) t.fail("R4 fragment reads do not alternate between the two k halves");
+        if (buf_read[H] >= 0 && !t.reads[buf_read[H]].consumed) t.fail("R3 a fragment buffer is refilled before it was multiplied");
+        buf_read[H] = t.issue_read(0, astage, idx / 2, H);
+        t.issue_read(1, wstage, idx / 2, H);
+    }
+    void wait_fetched() { t.retire_reads(0); }
+    template <int H>
+    void multiply() {
+        ++t.pos;
+        if (buf_read[H] < 0) { t.fail("R3 multiply before any fragment was read"); return; }
+        for (int o = 0; o < 2; ++o) {
+            Read& r = t.reads[buf_read[H] + o];
+            if (r.retire_pos < 0) t.fail("R3 multiply consumes fragments that have not been waited for");
+            if (r.consumed) t.fail("R4 a k half is multiplied twice");
+            r.consumed = true;
+        }
+        consumed.push_back(t.reads[buf_read[H]].tile * 2 + H);
+    }
+    template <int H>
+    void mma_fetch_load_a(int astage, int wstage, int tile, int lstage) {
+        multiply<H>();
+        load_a(tile, lstage);
+        fetch_half<1 - H>(astage, wstage);
+    }
+    template <int H>
+    void mma_fetch_load_w(int astage, int wstage, int tile, int lstage) {
+        multiply<H>();
+        load_w(tile, lstage);
+        fetch_half<1 - H>(astage, wstage);
+    }
+    std::string verdict(const char* what) {
+        t.check(what);
+        if ((int)consumed.size() != 2 * nk) t.fail(std::string(what) + ": R4 number of multiply phases is not 2 per K tile");
+        for (int i = 0; i < (int)consumed.size() && i < 2 * nk; ++i)
+            if (consumed[i] != i) t.fail(std::string(what) + ": R4 k halves are not consumed once each, in order");
+        for (const Read& r : t.reads)
+            if (!r.consumed && r.tile < nk) t.fail(std::string(what) + ": R4 a fragment of a real tile is read and never multiplied");
+        return t.error;
+    }
+};
+
+// ------------------------------------------------------------------------------------------------------------------
 // recorder for pipe::attn_kv_loop (ring 0 = K, ring 1 = V)
 // ------------------------------------------------------------------------------------------------------------------
 struct AttnRecorder {
@@ -323,6 +395,15 @@ void expect_caught(const std::string& err, const char* what) {
     ++failures;
 }
 
+template <int NSA, int NSW>
+void audit_spread(int nk) {
+    char name[128];
+    SpreadRecorder r(nk, NSA, NSW);
+    eet::pipe::gemm_k_loop_spread<NSA, NSW>(r, nk);
+    snprintf(name, sizeof name, "tile kernel, one wave per SIMD, loads in both halves of a step, rings of %d and %d stages, %d K tiles", NSA, NSW, nk);
+    expect_ok(r.verdict(name), name);
+}
+
 }  // namespace
 
 int main() {
@@ -358,6 +439,12 @@ int main() {
             snprintf(name, sizeof name, "tile kernel, one wave per SIMD, four LDS stages, %d K tiles", nk);
             expect_ok(r.verdict(name), name);
         }
+        audit_spread<3, 2>(nk);
+        audit_spread<3, 3>(nk);
+        audit_spread<4, 3>(nk);
+        audit_spread<4, 4>(nk);
+        audit_spread<5, 4>(nk);
+        audit_spread<5, 5>(nk);
         {
             GemmRecorder r(nk);
             eet::pipe::gemm_k_loop<3>(r, nk);
