@@ -14,7 +14,7 @@
 //                    the kernel is a weight stream; v_mfma_f32_16x16x32_f16 does the 16-row contraction.
 //   gemm_skinny      decode, shapes the two above do not take.
 // All compute the transposed tile (weights as the MFMA "A" operand) so that each lane ends up
-// with 4 consecutive output columns of one row: 8-byte stores, and 8-byte bias/residual loads.
+// with 4 consecutive output columns of one row (the tile kernel: 8, see tile_column).
 #include <cstdlib>
 #include <mutex>
 #include <set>
@@ -93,141 +93,142 @@ __device__ __forceinline__ void epilogue4(const GemmArgs& a, int m, int n, float
 }
 
 // --------------------------------------------------------------------------------------------
-// epilogue of the MFMA tile kernels, through LDS
+// epilogue of the MFMA tile kernels
 // --------------------------------------------------------------------------------------------
-// The accumulator layout gives a lane one row and 4 consecutive columns: stored like that, a wave-level store
-// touches 32 rows with 16 bytes each, and the output (as large as an operand) leaves the chip at a fraction of
-// the memory rate.  Instead each wave turns its (AM*16) x 64 tile around in a private piece of the operand
-// stages, which are free after the main loop: the residual tile comes in with whole-line loads, the epilogue
-// arithmetic runs in fp32 on the accumulators, the rounded tile goes out with whole-line stores (8 rows x 128
-// bytes per instruction).  Rows are 128 bytes; their sixteen 8-byte units are XOR-permuted by (row/2)%16 so that
-// both access patterns spread over all banks.  `stage`: AM*16*128 bytes of LDS no other wave touches; mw, nw:
-// first row and column of the wave tile (its 64 columns are inside N or outside as a whole: N % 64 == 0).
-// A wave tile of 128 columns (ANT = 8 accumulator blocks across) is turned around in two passes of 64 columns, J0 = 0 and 4.
-// Row bookkeeping of a wave tile's whole-line accesses (lane -> row it*8 + lane/8 of the tile, it = 0 .. AM*2-1), looked up
-// once for both 64-column passes and with every lookup in flight together: r0 = output row (EPI_QKV: the sequence
-// whose cache the row's K and V go to), r1 = residual row (EPI_QKV: the cache slot; negative or >= max_seq: dropped).
-// Rows past M repeat row M-1; they are never stored.
-template <int AM, int EPI>
-__device__ __forceinline__ void epilogue_rows(const GemmArgs& a, int mw, int lane, int (&r0)[AM * 2], int (&r1)[AM * 2]) {
-    const int r8 = lane >> 3;
-    int m[AM * 2];
+// A lane of an accumulator block holds four values of one row.  Which columns they are is free, since the weight rows may be dealt to the
+// blocks in any order: block j, operand row i is column tile_column(j, i) of the wave tile, so that a lane has 8 consecutive columns in each pair of
+// blocks and the four lanes of a row 32, and the output goes straight out of the accumulators in pieces of 64 bytes.  (Blocks
+// of 16 consecutive columns left a lane 8 bytes here and 8 there: 0.7 TB/s.)  Turned around through LDS to whole lines first, as it was, a 256 x 256 tile took 5.6 us
+// behind its K loop with a bias, 10.1 with GELU and 12.2 with a residual, most of it one wave's chain of LDS writes, reads and stores; now 5.2, 7.2 and 9.
+// What is left: 1 us of look-ups, 3.4 for 33 MB of output from all CUs at once, 5 for as much of residual.  us, before -> now: 6758 x 8192 x 2048 with GELU 209
+// -> 198, 12288 x 4096 x 2048 177 -> 167, 3054 x 4096 x 1024 29.9 -> 28.3; with a residual 6758 x 2048 x 8192 188 -> 184, 12288 x 4096 x 2048 185 -> 179, 20000 x
+// 768 x 768 34.4 -> 31.2.
+__host__ __device__ constexpr int tile_column(int j, int i) { return (j / 2) * 32 + (i / 4) * 8 + (j % 2) * 4 + i % 4; }
+
+// Two loads of 8 rows by 64 columns (lanes 0-7 of 16 a row's 16 bytes of the first 32 columns, lanes 8-15 of the last 32) into 16 rows by 32 columns
+// each: the lower lanes keep the first load and take its other half from the upper lanes, which keep the second.
+__device__ __forceinline__ void lines_to_rows(half8v& first, half8v& second, bool upper) {
+    typedef int int4v __attribute__((ext_vector_type(4)));
+    int4v d0 = __builtin_bit_cast(int4v, first), d1 = __builtin_bit_cast(int4v, second);
 #pragma unroll
-    for (int it = 0; it < AM * 2; ++it) {
-        m[it] = mw + it * 8 + r8;
-        m[it] = m[it] < a.M ? m[it] : a.M - 1;
+    for (int q = 0; q < 4; ++q) {
+        const int y0 = __builtin_amdgcn_update_dpp(0, d0[q], 0x128, 0xf, 0xf, false);      // lane ^ 8
+        const int y1 = __builtin_amdgcn_update_dpp(0, d1[q], 0x128, 0xf, 0xf, false);
+        d0[q] = upper ? y1 : d0[q];
+        d1[q] = upper ? d1[q] : y0;
+    }
+    first = __builtin_bit_cast(half8v, d0);
+    second = __builtin_bit_cast(half8v, d1);
+}
+
+// mw, nw: first row and column of the wave tile; its columns are inside N in groups of 64, or outside (N % 64 == 0).  Row maps and residual are all
+// requested before anything waits for them: one trip to memory per tile.  (8192 x 16384 x 2048 with a residual: 634 -> 552 us; 25082 x 12288 x
+// 12288: 6.56 -> 6.37 ms).
+template <int AM, int AN, int EPI, bool NTS>
+__device__ __forceinline__ void epilogue_tile(const GemmArgs& a, const float4v (&acc)[AM][AN], int mw, int nw, int lane) {
+    constexpr int P = AN / 2;                             // pairs of blocks: 32 columns each, 8 of them this lane's
+    const int M = a.M, N = a.N, fr = lane & 15, G = lane >> 4;
+    if (nw >= N) return;
+    auto inside = [&](int p) { return P <= 2 || nw + (p / 2) * 64 < N; };
+    // rows: r0 = output row (EPI_QKV: the sequence whose cache the row's K and V go to, r1 = the cache slot; negative or >= max_seq:
+    // dropped).  Rows past M repeat row M-1; they are never stored.
+    int m[AM], r0[AM], r1[AM];
+#pragma unroll
+    for (int i = 0; i < AM; ++i) {
+        m[i] = mw + i * 16 + fr;
+        m[i] = m[i] < M ? m[i] : M - 1;
     }
     if constexpr (EPI == EPI_QKV) {
         if (a.tok_row_map) {                             // prefill: token -> (sequence, position)
-            int tok[AM * 2];
+            int tok[AM];
 #pragma unroll
-            for (int it = 0; it < AM * 2; ++it) tok[it] = a.tok_row_map[m[it]];
+            for (int i = 0; i < AM; ++i) tok[i] = a.tok_row_map[m[i]];
 #pragma unroll
-            for (int it = 0; it < AM * 2; ++it) {
-                r0[it] = tok[it] / a.S;
-                r1[it] = tok[it] - r0[it] * a.S;
+            for (int i = 0; i < AM; ++i) {
+                r0[i] = tok[i] / a.S;
+                r1[i] = tok[i] - r0[i] * a.S;
             }
             if (a.left_pad) {                            // pads lead: token 0 of the sequence is at row S - L_b
-                int len[AM * 2];
+                int len[AM];
 #pragma unroll
-                for (int it = 0; it < AM * 2; ++it) len[it] = a.lens[r0[it]];
+                for (int i = 0; i < AM; ++i) len[i] = a.lens[r0[i]];
 #pragma unroll
-                for (int it = 0; it < AM * 2; ++it) r1[it] -= a.S - len[it];
+                for (int i = 0; i < AM; ++i) r1[i] -= a.S - len[i];
             }
         } else {                                         // decode: the new token goes to slot n_b
 #pragma unroll
-            for (int it = 0; it < AM * 2; ++it) {
-                r0[it] = m[it];
-                r1[it] = a.lens[m[it]];
+            for (int i = 0; i < AM; ++i) {
+                r0[i] = m[i];
+                r1[i] = a.lens[m[i]];
             }
         }
     } else {
 #pragma unroll
-        for (int it = 0; it < AM * 2; ++it) {
-            r0[it] = a.out_row_map ? a.out_row_map[m[it]] : m[it];
-            r1[it] = (EPI == EPI_BIAS_RES && a.res_row_map) ? a.res_row_map[m[it]] : m[it];
-        }
+        for (int i = 0; i < AM; ++i) r0[i] = a.out_row_map ? a.out_row_map[m[i]] : m[i];
     }
-}
-
-// The residual rows under 64 columns of a wave tile, as whole lines (16-byte chunk lane%8 of each row): every request is
-// issued before anything waits for one, so the tile costs one trip to memory instead of one per group of rows
-// (8192 x 16384 x 2048 with a residual: 634 -> 552 us; 25082 x 12288 x 12288: 6.56 -> 6.37 ms).
-template <int AM>
-__device__ __forceinline__ void epilogue_request_residual(const GemmArgs& a, half8v (&rv)[AM * 2], const int (&rrow)[AM * 2], int nw, int lane) {
-    if (nw >= a.N) return;
-    const int c8 = lane & 7;
+    half8v bias[P];
 #pragma unroll
-    for (int it = 0; it < AM * 2; ++it) rv[it] = *reinterpret_cast<const half8v*>(a.res + (int64_t)rrow[it] * a.N + nw + c8 * 8);
-}
-
-template <int AM, int ANT, int J0, int EPI, bool NTS, int RV>
-__device__ __forceinline__ void epilogue_via_lds(const GemmArgs& a, const float4v (&acc)[AM][ANT], const half8v (&rv)[RV],
-                                                 const int (&r0)[AM * 2], const int (&r1)[AM * 2], char* stage, int mw, int nw, int lane) {
-    static_assert(J0 + 4 <= ANT, "64 columns per pass");
-    static_assert(EPI != EPI_BIAS_RES || RV == AM * 2, "the residual lines of the pass, from epilogue_request_residual");
-    constexpr int AN = 4;
-    constexpr int ROWS = AM * 16;                         // rows of the wave tile
-    const int M = a.M, N = a.N;
-    if (nw >= N) return;
-    const int r8 = lane >> 3, c8 = lane & 7;              // whole-line pattern: row it*8 + r8, 16-byte chunk c8
+    for (int p = 0; p < P; ++p)
+        if (inside(p)) bias[p] = *reinterpret_cast<const half8v*>(a.bias + nw + p * 32 + G * 8);
+    // The residual comes in whole lines, 8 rows by 64 columns per load: pair p of block i has rows 8*(p%2) ..+8, and its lanes of the upper half of
+    // 16 the columns 32 to 63 (64-byte pieces of 16 rows, as the output goes, slow the other workgroup of a CU down: 3054 x 3072 x 1024 27.8 us, so 27.0)
+    const bool upper = fr >= 8;
+    half8v res[EPI == EPI_BIAS_RES ? AM : 1][P];
     if constexpr (EPI == EPI_BIAS_RES) {
+        int rrow[AM][2];
 #pragma unroll
-        for (int it = 0; it < ROWS / 8; ++it) {
-            const int row = it * 8 + r8;
-            half8v v = rv[it];
-            const int sw = (row >> 1) & 15;
-            if (sw & 1) v = __builtin_shufflevector(v, v, 4, 5, 6, 7, 0, 1, 2, 3);
-            *reinterpret_cast<half8v*>(stage + row * 128 + ((c8 ^ (sw >> 1)) * 16)) = v;
-        }
+        for (int i = 0; i < AM; ++i)
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                int r = mw + i * 16 + 8 * h + (fr & 7);
+                r = r < M ? r : M - 1;
+                rrow[i][h] = a.res_row_map ? a.res_row_map[r] : r;
+            }
+#pragma unroll
+        for (int i = 0; i < AM; ++i)
+#pragma unroll
+            for (int p = 0; p < P; ++p)
+                if (inside(p)) res[i][p] = *reinterpret_cast<const half8v*>(a.res + (int64_t)rrow[i][p % 2] * N + nw + (p / 2) * 64 + (upper ? 32 : 0) + G * 8);
     }
-    // arithmetic on the accumulators: acc[i][j][0..3] = row i*16 + lane%16, columns j*16 + (lane/16)*4 ..+4
+    half_t* col[P];                                       // where column nw + p*32 + G*8 of row 0 goes
+    bool to_cache[P];
 #pragma unroll
-    for (int j = 0; j < AN; ++j) {
-        const int unit = j * 4 + (lane >> 4);             // 8-byte unit of the 128-byte row
-        const half4v bias = *reinterpret_cast<const half4v*>(a.bias + nw + unit * 4);
-#pragma unroll
-        for (int i = 0; i < AM; ++i) {
-            const int row = i * 16 + (lane & 15);
-            half4v* slot = reinterpret_cast<half4v*>(stage + row * 128 + ((unit ^ ((row >> 1) & 15)) * 8));
-            float v0 = acc[i][J0 + j][0] + (float)bias[0], v1 = acc[i][J0 + j][1] + (float)bias[1];
-            float v2 = acc[i][J0 + j][2] + (float)bias[2], v3 = acc[i][J0 + j][3] + (float)bias[3];
-            if (EPI == EPI_BIAS_GELU) {
-                v0 = gelu_tanh(v0); v1 = gelu_tanh(v1); v2 = gelu_tanh(v2); v3 = gelu_tanh(v3);
-            }
-            if (EPI == EPI_BIAS_RES) {
-                const half4v r = *slot;
-                v0 += (float)r[0]; v1 += (float)r[1]; v2 += (float)r[2]; v3 += (float)r[3];
-            }
-            *slot = half4v{(half_t)v0, (half_t)v1, (half_t)v2, (half_t)v3};
-        }
-    }
-    // whole lines out
-#pragma unroll
-    for (int it = 0; it < ROWS / 8; ++it) {
-        const int row = it * 8 + r8, m = mw + row;
-        if (m >= M) continue;
-        const int sw = (row >> 1) & 15;
-        half8v v = *reinterpret_cast<const half8v*>(stage + row * 128 + ((c8 ^ (sw >> 1)) * 16));
-        if (sw & 1) v = __builtin_shufflevector(v, v, 4, 5, 6, 7, 0, 1, 2, 3);
-        const int n = nw + c8 * 8;
-        half_t* dst;
-        if (EPI == EPI_QKV) {
-            const int which = n / a.hidden;              // 0 = Q, 1 = K, 2 = V
-            const int c = n - which * a.hidden;
-            if (which == 0) {
-                dst = a.y + (int64_t)m * a.hidden + c;
-            } else {
-                const int b_ = r0[it], pos = r1[it];
-                if (pos < 0 || pos >= a.max_seq) continue;   // see epilogue_apply: never outside the sequence's slots
-                const int g = c / a.d, dd = c - g * a.d;
-                dst = (which == 1 ? a.k_cache : a.v_cache) + (((int64_t)b_ * a.heads + g) * a.max_seq + pos) * a.d + dd;
-            }
+    for (int p = 0; p < P; ++p) {
+        const int n = nw + p * 32 + G * 8;
+        to_cache[p] = false;
+        if constexpr (EPI == EPI_QKV) {
+            const int which = n / a.hidden, c = n - which * a.hidden, g = c / a.d;      // 0 = Q, 1 = K, 2 = V
+            to_cache[p] = which != 0;
+            col[p] = which == 0 ? a.y + c : (which == 1 ? a.k_cache : a.v_cache) + (int64_t)g * a.max_seq * a.d + (c - g * a.d);
         } else {
-            dst = a.y + (int64_t)r0[it] * (a.ldy ? a.ldy : N) + n;
+            col[p] = a.y + n;
         }
-        if constexpr (NTS) __builtin_nontemporal_store(v, reinterpret_cast<half8v*>(dst));   // an output too large to stay cached for its reader
-        else *reinterpret_cast<half8v*>(dst) = v;
+    }
+    const int64_t ldy = EPI == EPI_QKV ? a.hidden : a.ldy ? a.ldy : N;
+#pragma unroll
+    for (int i = 0; i < AM; ++i) {
+        const bool row_inside = mw + i * 16 + fr < M;
+        const bool slot = EPI == EPI_QKV && r1[i] >= 0 && r1[i] < a.max_seq;            // see epilogue_apply: never outside the sequence's slots
+        const int64_t at = EPI == EPI_QKV ? (int64_t)m[i] * ldy : (int64_t)r0[i] * ldy;
+        const int64_t at_cache = EPI == EPI_QKV ? ((int64_t)r0[i] * a.heads * a.max_seq + r1[i]) * a.d : 0;
+#pragma unroll
+        for (int p = 0; p < P; ++p) {
+            if constexpr (EPI == EPI_BIAS_RES) {
+                if (p % 2 == 0) lines_to_rows(res[i][p], res[i][p + 1], upper);
+            }
+            half8v v;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                float f = acc[i][2 * p + e / 4][e % 4] + (float)bias[p][e];
+                if (EPI == EPI_BIAS_GELU) f = gelu_tanh(f);
+                if (EPI == EPI_BIAS_RES) f += (float)res[EPI == EPI_BIAS_RES ? i : 0][p][e];
+                v[e] = (half_t)f;
+            }
+            if (!(row_inside && inside(p) && (!to_cache[p] || slot))) continue;
+            half8v* dst = reinterpret_cast<half8v*>(col[p] + (to_cache[p] ? at_cache : at));
+            if constexpr (NTS) __builtin_nontemporal_store(v, dst);   // an output too large to stay cached for its reader
+            else *dst = v;
+        }
     }
 }
 
@@ -244,8 +245,8 @@ __device__ __forceinline__ void epilogue_via_lds(const GemmArgs& a, const float4
 // at the start of step kt, with three (the small tiles, where few workgroups share a CU and nothing else hides the
 // trip to memory) those of step kt+2.  An LDS row is the 128 bytes of one operand row, and a wave-level load
 // covers 8 rows x 128 bytes, i.e. whole cache lines.  Instead of padding, the eight 16-byte chunks
-// of a row are XOR-permuted by (row/2)%8 -- applied on the global address of each lane when loading
-// and on the LDS address when reading fragments -- which spreads consecutive rows over all banks.
+// of a row are XOR-permuted by half the row's number in its block (activations: (row/2)%8; weights: see tile_column) -- applied on the
+// global address of each lane when loading and on the LDS address when reading fragments -- which spreads the rows of a block over all banks.
 // MFMA fragments are double-buffered in registers: the reads of the next quarter-step are issued
 // before the MFMAs of the current one.
 //
@@ -306,7 +307,7 @@ struct GemmTileExec {
     const half_t* pw[LIW];
     half_t* as_base;                       // stage 0 of this wave's K group: As[kg * NS], Ws[kg * NS]
     half_t* ws_base;
-    unsigned a_lds, w_lds;                 // LDS byte address of row lane%16 of the wave tile's first block, stage 0
+    unsigned a_lds, w_lds;                 // LDS byte address of this lane's row of the wave tile's first block, stage 0
     unsigned foff[2];                      // byte offset of this lane's 16 bytes of k half h inside the (permuted) row
     int kg, wave;
     half8v fa[2][AH], fw[2][AN];           // fa[s & 1]: activations of sub-step s; fw[h & 1]: weights of k half h
@@ -346,16 +347,11 @@ struct GemmTileExec {
         if (AH > 3) EET_DREAD(fa[BUF][3 % AH], va_, (MH * AH + 3) * 2048);
         if (MH == 0) {
             const unsigned vw_ = w_lds + stage * (BN * BK * 2) + foff[H];
-            EET_DREAD(fw[H][0], vw_, 0);
-            EET_DREAD(fw[H][1], vw_, 2048);
-            EET_DREAD(fw[H][2], vw_, 4096);
-            EET_DREAD(fw[H][3], vw_, 6144);
-            if (AN > 4) {
-                EET_DREAD(fw[H][4 % AN], vw_, 8192);
-                EET_DREAD(fw[H][5 % AN], vw_, 10240);
-                EET_DREAD(fw[H][6 % AN], vw_, 12288);
-                EET_DREAD(fw[H][7 % AN], vw_, 14336);
-            }
+            static_assert(AN == 4, "wave tiles of 64 columns");
+            EET_DREAD(fw[H][0], vw_, tile_column(0, 0) * 128);
+            EET_DREAD(fw[H][1], vw_, tile_column(1, 0) * 128);
+            EET_DREAD(fw[H][2], vw_, tile_column(2, 0) * 128);
+            EET_DREAD(fw[H][3], vw_, tile_column(3, 0) * 128);
         }
     }
 #undef EET_DREAD
@@ -375,7 +371,7 @@ struct GemmTileExec {
     // LDS read number R of k half H into buffer H: the AN weight fragments, then the AM activation fragments
     template <int H, int R>
     __device__ __forceinline__ void half_read(unsigned va_, unsigned vw_) {
-        if constexpr (R < AN) asm volatile("ds_read_b128 %0, %1 offset:%2" : "=&v"(gw[H][R % AN]) : "v"(vw_), "n"(R * 2048) : "memory");
+        if constexpr (R < AN) asm volatile("ds_read_b128 %0, %1 offset:%2" : "=&v"(gw[H][R % AN]) : "v"(vw_), "n"(tile_column(R, 0) * 128) : "memory");
         else asm volatile("ds_read_b128 %0, %1 offset:%2" : "=&v"(ga[H][(R - AN) % AM]) : "v"(va_), "n"((R - AN) * 2048) : "memory");
     }
     template <int H, int... R>
@@ -540,16 +536,16 @@ __global__ __launch_bounds__(WGM* WGN* KS * 64, BM == 192 && NS == 2 ? 2 : 1) vo
 #pragma unroll
     for (int v = 0; v < LIW; ++v) {
         const int row = wave * LRW + v * 8 + (lane >> 3);
-        const int c = (lane & 7) ^ ((row >> 1) & 7);
+        const int c = (lane & 7) ^ (((row >> 1) & 1) | ((row >> 3) & 3) << 1);    // of the rows tile_column(j, 0..15), two share a permutation each
         int gr = n0 + row;
         gr = gr < N ? gr : N - 1;
         ex.pw[v] = a.w + (int64_t)gr * K + k0 + c * 8;
     }
-    // fragment rows: lane l reads row l%16 of a block, the 16 bytes (l/16) of k half h; rows are 128 bytes with their
-    // 16-byte chunks XOR-permuted by (row/2)%8, and blocks start at multiples of 16 rows, so the permutation is the lane's own
+    // fragment rows: lane l reads operand row l%16 of a block (of the weights: row tile_column(j, l%16) of the wave tile), the 16 bytes (l/16) of k half
+    // h; rows are 128 bytes with their 16-byte chunks XOR-permuted by (operand row)/2, so the permutation is the lane's own
     const int frow = lane & 15, fG = lane >> 4, fsw = frow >> 1;
     ex.a_lds = (unsigned)(uintptr_t)&As[kg * NSA][(wm0 + frow) * BK];
-    ex.w_lds = (unsigned)(uintptr_t)&Ws[kg * NS][(wn0 + frow) * BK];
+    ex.w_lds = (unsigned)(uintptr_t)&Ws[kg * NS][(wn0 + tile_column(0, frow)) * BK];
 #pragma unroll
     for (int h = 0; h < 2; ++h) ex.foff[h] = (unsigned)(((h * 4 + fG) ^ fsw) * 16);
 
@@ -561,8 +557,8 @@ __global__ __launch_bounds__(WGM* WGN* KS * 64, BM == 192 && NS == 2 ? 2 : 1) vo
     if constexpr (SCHED != 0) pipe::gemm_k_loop_spread<NSA, NS>(ex, nk);
     else pipe::gemm_k_loop<NS>(ex, nk);
 
-    __syncthreads();                                      // every wave is done with the operand stages
     if constexpr (KS > 1) {
+        __syncthreads();                                  // every wave is done with the operand stages
         // the other groups' partial tiles go over the weight stages, lane-major (no bank conflicts), to the first
         constexpr int PT = AM * AN * 4 * 64;                  // floats of one wave's partial tile
         static_assert((KS - 1) * NW * PT * 4 <= (int)sizeof(Ws), "partial tiles over the weight stages");
@@ -594,28 +590,13 @@ __global__ __launch_bounds__(WGM* WGN* KS * 64, BM == 192 && NS == 2 ? 2 : 1) vo
             if (m >= M) continue;
 #pragma unroll
             for (int j = 0; j < AN; ++j) {
-                const int n = n0 + wn0 + j * 16 + (lane >> 4) * 4;
+                const int n = n0 + wn0 + tile_column(j, (lane >> 4) * 4);
                 if (n < N) *reinterpret_cast<float4v*>(a.part + ((int64_t)range * M + m) * N + n) = acc[i][j];
             }
         }
         return;
     }
-    constexpr int EB = WM * 128;                           // bytes of a wave's turn-around area
-    // row lookups and residual lines of the wave tile: all requested here, consumed by the passes below
-    int er0[AM * 2], er1[AM * 2];
-    epilogue_rows<AM, EPI>(a, m0 + wm0, lane, er0, er1);
-    constexpr int RV = EPI == EPI_BIAS_RES ? AM * 2 : 1;
-    half8v rv0[RV], rv1[AN == 8 ? RV : 1];
-    if constexpr (EPI == EPI_BIAS_RES) {
-        epilogue_request_residual<AM>(a, rv0, er1, n0 + wn0, lane);
-        if constexpr (AN == 8) epilogue_request_residual<AM>(a, rv1, er1, n0 + wn0 + 64, lane);
-    }
-    // with K groups the partial tiles above sit in the weight stages and group 0 may still be summing them while a faster
-    // wave of the group already turns its tile around: that must then happen in the activation stages only
-    static_assert(NW * EB <= (int)sizeof(As), "turn-around areas");
-    char* area = reinterpret_cast<char*>(&As[0][0]) + wave * EB;
-    epilogue_via_lds<AM, AN, 0, EPI, NTS>(a, acc, rv0, er0, er1, area, m0 + wm0, n0 + wn0, lane);
-    if constexpr (AN == 8) epilogue_via_lds<AM, AN, 4, EPI, NTS>(a, acc, rv1, er0, er1, area, m0 + wm0, n0 + wn0 + 64, lane);   // second 64 columns, same area
+    epilogue_tile<AM, AN, EPI, NTS>(a, acc, m0 + wm0, n0 + wn0, lane);
 }
 
 // --------------------------------------------------------------------------------------------
