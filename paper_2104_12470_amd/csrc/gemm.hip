@@ -475,7 +475,7 @@ struct GemmTileExec {
 template <int BM, int BN, int WGM, int WGN, int EPI, int NS, int KS, int SCHED, bool NTS = false, bool NTW = false, bool ROT = false>
 // (192 x 128 tiles are made for two workgroups per CU: the residual and cache-row look-ups of their epilogue would take the
 // kernel past 256 registers and halve that: 2000 x 4096 x 4096 with a residual 135 us)
-__global__ __launch_bounds__(WGM* WGN* KS * 64, BM == 192 && NS == 2 ? 2 : 1) void gemm_mfma_dma64(GemmArgs a, int tiles_m, int tiles_n) {
+__global__ __launch_bounds__(WGM* WGN* KS * 64, BM == 192 && BN == 128 && NS == 2 ? 2 : 1) void gemm_mfma_dma64(GemmArgs a, int tiles_m, int tiles_n) {
     static_assert(SCHED == 0 || (KS == 1 && (SCHED == 1 || (SCHED == 2 && NS > 2))), "schedule");
     // KS > 1: KS groups of WGM x WGN waves share the tile and take every KS-th K step each, through LDS stages of their
     // own; the other groups' accumulators are added to the first's through LDS at the end.  For the few
@@ -1687,6 +1687,25 @@ hipError_t launch_gemm(const GemmArgs& a, Epilogue epi, hipStream_t s) {
             if (e != hipSuccess) return e;
             return launch_gemm(rows_from(a, epi, m_whole), epi, s);
         }
+        // Four waves with 128 x 128 each in the 256 x 256 tile: a third less LDS read traffic per flop than eight waves of 128 x 64 (25082 x 49152 x 12288
+        // 1.16 -> 1.23 PFLOP/s, 8192 x 16384 x 12288 1.20 -> 1.33, 2951 x 16384 x 4096 1.13 -> 1.24), at every K and row stride since the loads of a
+        // step are spread over both of its halves (against eight waves with an early release of the stage, us: 3000 x 4096 x 32768 799 -> 661, 2048 x
+        // 12288 x 49152 2518 -> 2149, its rows 128 bytes further apart 2379 -> 2077, 5000 x 10240 x 40960 4307 -> 3704).
+        auto tile256 = [&] {
+            if ((size_t)a.M * a.N * sizeof(half_t) >= kMemorySideCacheBytes) launch_dma64_cfg<2, 2, 256, 256, 2, 1, 1, true>(a, epi, s);
+            else launch_dma64_cfg<2, 2, 256, 256, 2, 1, 1>(a, epi, s);
+        };
+        switch (full_tile(a.M, a.N, a.K)) {
+        case kFull256: tile256(); return hipGetLastError();
+        case kFull224x256: launch_dma64_cfg<2, 2, 224, 256, 2, 1, 1>(a, epi, s); return hipGetLastError();
+        case kFull192x256: launch_dma64_cfg<2, 2, 192, 256, 2, 1, 1>(a, epi, s); return hipGetLastError();
+        case kFull160x256: launch_dma64_cfg<2, 2, 160, 256, 3, 1, 2>(a, epi, s); return hipGetLastError();
+        case kFull128x256: launch_dma64_cfg<2, 2, 128, 256, 3, 1, 2>(a, epi, s); return hipGetLastError();
+        case kFull192: launch_dma64_cfg<2, 2, 192, 128, 3, 1, 2>(a, epi, s); return hipGetLastError();
+        case kFull128: launch_dma64_cfg<2, 2, 128, 128, 3, 1, 2>(a, epi, s); return hipGetLastError();
+        case kFull96: launch_dma64_cfg<2, 2, 96, 128, 4, 1, 2>(a, epi, s); return hipGetLastError();
+        case kFullNone: break;
+        }
         switch (tile_for(a.M, a.N, a.K)) {
         case kTile64: launch_dma64_cfg<2, 1, 64, 64, 3>(a, epi, s); break;
         case kTile64Split: launch_dma64_cfg<2, 1, 64, 64, 3, 2>(a, epi, s); break;
@@ -1699,14 +1718,7 @@ hipError_t launch_gemm(const GemmArgs& a, Epilogue epi, hipStream_t s) {
         case kTile128: launch_dma64_cfg<2, 2, 128, 128, 3, 1, 2>(a, epi, s); break;
         case kTile192: launch_dma64_cfg<2, 2, 192, 128, 3, 1, 2>(a, epi, s); break;
         case kTile128x256: launch_dma64_cfg<2, 2, 128, 256, 3, 1, 2>(a, epi, s); break;
-        case kTile256:
-            // Four waves with 128 x 128 each: a third less LDS read traffic per flop than eight waves of 128 x 64 (25082 x 49152 x 12288 1.16 ->
-            // 1.23 PFLOP/s, 8192 x 16384 x 12288 1.20 -> 1.33, 2951 x 16384 x 4096 1.13 -> 1.24), at every K and row stride since the loads of a step are
-            // spread over both of its halves (against eight waves with an early release of the stage, us: 3000 x 4096 x 32768 799 -> 661, 2048 x
-            // 12288 x 49152 2518 -> 2149, its rows 128 bytes further apart 2379 -> 2077, 5000 x 10240 x 40960 4307 -> 3704).
-            if ((size_t)a.M * a.N * sizeof(half_t) >= kMemorySideCacheBytes) launch_dma64_cfg<2, 2, 256, 256, 2, 1, 1, true>(a, epi, s);
-            else launch_dma64_cfg<2, 2, 256, 256, 2, 1, 1>(a, epi, s);
-            break;
+        case kTile256: tile256(); break;
         }
     }
     return hipGetLastError();

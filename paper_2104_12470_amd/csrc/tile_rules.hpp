@@ -220,10 +220,14 @@ inline TileChoice choose_tile(int M, int N, int K) {
 // 4096 x 1024 24.8 against 30.1 with the best of the tiles below; four groups with two stages each were slower than two with
 // three).  From K = 640 on, five steps per group: prompts of 20 to 900 rows through layers of 640, 768 and 896 take 0.88 to 0.98 of the time
 // that they took with one group (768: 160 rows 46.8 -> 44.4 us per layer, 600 57.9 -> 53.7); at 256 and 384 there is nothing to gain.
+inline bool few_tiles(int M, int N, int K) {
+    const int wg128 = ((M + 127) / 128) * ((N + 63) / 64);
+    return wg128 < 128 || (two_k_groups(K) && wg128 <= 256);
+}
 inline TileChoice tile_for(int M, int N, int K) {
     const bool k_split = two_k_groups(K);
     const int wg128 = ((M + 127) / 128) * ((N + 63) / 64), wg64 = ((M + 63) / 64) * ((N + 63) / 64);
-    if (wg128 < 128 || (k_split && wg128 <= 256)) {
+    if (few_tiles(M, N, K)) {
         if (k_split && wg64 <= 256) return kTile64Split;              // (1000 x 1024 x 4096: 25.1 -> 20.1)
         return wg128 >= 128 ? kTile128x64Split : kTile64;
     }
@@ -238,6 +242,39 @@ inline TileChoice tile_for(int M, int N, int K) {
     // at most 128 rows: half of a taller tile would be idle
     const int tiles128 = (N + 127) / 128;
     return tiles128 > 256 ? kTile128PairShared : tiles128 == 256 ? kTile128 : kTile128x64;
+}
+
+// More than 128 rows over outputs of a multiple of 128 columns with K from 768 on (what the projections of a layer mostly are): one tile per CU in any
+// number of rounds, of the height that leaves the least of them idle.  Since the loads of a K step are spread over both of its halves and the
+// output goes straight to memory a tile alone on its CU is faster than two that share it, so what is left to choose is the size.  Measured, us, K in
+// thousands, a launch of one round / each of several rounds (540 sizes, hidden 512 to 4096, 300 to 10000 rows; mean error 6 and 3 %):
+//   256 x 256  12 + 18.9 K   10.5 + 21.4 K      128 x 256  8.3 + 10.8 K  6.8 + 12 K
+//   224 x 256  11.7 + 17.3 K  8.9 + 19.2 K      192 x 128  6.9 + 8.5 K   5.2 + 9.7 K
+//   192 x 256  10.2 + 15.5 K  7.4 + 17.3 K      128 x 128  5.6 + 6.4 K   3.9 + 7.1 K
+//   160 x 256  9.6 + 13 K     7.3 + 14.7 K       96 x 128  5.5 + 5.2 K   3.6 + 5.8 K
+// a part-filled last round takes 0.7 of a full one and 0.3 of what it fills.  Over those sizes the time falls to 0.967 of what tile_for's choice
+// takes (the best tile of each: 0.962; the worst of them 1.09), us: 3054 x 3072 x 12288 235 -> 190 (192 x 256), 2140 x 4096 x 4096 82 -> 70, 1700 x 12288 x 4096
+// 167 -> 144, 6758 x 2048 x 2048 60 -> 54 (224 x 256), 700 x 5120 x 1280 16.2 -> 13.3 (128 x 128).  Where it stops: at K = 512 the pairs of tile_for
+// are level or ahead (8200 x 2048 x 512 27.8 / 30.8, 3800 x 2048 x 512 14.4 / 15.3); 64 columns left over, which leave part of every last tile
+// idle, keep the tile they have; the tiles shared by two groups of waves are ahead of all of these (900 x 1280 x 5120 28.2 / 31.3, 700 x 2048 x
+// 8192 39.4 / 43.6).  224 rows only where at most one in sixteen of their rows is padding: beyond that 256 are as fast or the next smaller height is.
+enum FullTile { kFullNone, kFull256, kFull224x256, kFull192x256, kFull160x256, kFull128x256, kFull192, kFull128, kFull96 };
+inline FullTile full_tile(int M, int N, int K) {
+    if (M <= 128 || N % 128 != 0 || K < 768 || few_tiles(M, N, K)) return kFullNone;
+    constexpr struct { FullTile tile; int rows, cols; double one, one_k, each, each_k; } kTiles[] = {
+        {kFull256, 256, 256, 12, 18.9, 10.5, 21.4},     {kFull224x256, 224, 256, 11.7, 17.3, 8.9, 19.2}, {kFull192x256, 192, 256, 10.2, 15.5, 7.4, 17.3},
+        {kFull160x256, 160, 256, 9.6, 13, 7.3, 14.7},   {kFull128x256, 128, 256, 8.3, 10.8, 6.8, 12},    {kFull192, 192, 128, 6.9, 8.5, 5.2, 9.7},
+        {kFull128, 128, 128, 5.6, 6.4, 3.9, 7.1},       {kFull96, 96, 128, 5.5, 5.2, 3.6, 5.8}};
+    const double k = K / 1024.0;
+    double best = 1e30;
+    FullTile choice = kFullNone;
+    for (const auto& t : kTiles) {
+        const int64_t tm = (M + t.rows - 1) / t.rows, tiles = tm * ((N + t.cols - 1) / t.cols), whole = tiles / 256, rest = tiles % 256;
+        if (t.tile == kFull224x256 && (tm * t.rows - M) * 16 > tm * t.rows) continue;
+        const double us = tiles <= 256 ? t.one + t.one_k * k : ((double)whole + (rest == 0 ? 0.0 : 0.7 + 0.3 * (double)rest / 256)) * (t.each + t.each_k * k);
+        if (us < best) { best = us; choice = t.tile; }
+    }
+    return choice;
 }
 
 }  // namespace eet
