@@ -394,8 +394,9 @@ struct GemmTileExec {
     template <int H, int LOADS, int IDX>
     __device__ __forceinline__ void half_mma_one(unsigned va_, unsigned vw_, int64_t koff, int lstage) {
         constexpr int MF = AM * AN, NR = AM + AN, NL = LOADS == 1 ? LIA : LIW;
-        constexpr int RS = (MF * 3 / 4) / NR, LS = (MF * 3 / 4) / NL;   // multiplies per read, per load (both measured best at 3 for 64)
-        static_assert(RS >= 1 && LS >= 1, "side work fits between the multiplies");
+        constexpr int RS = (MF * 3 / 4) / NR, LS = (MF * 3 / 4) / NL > 0 ? (MF * 3 / 4) / NL : 1;   // multiplies per read, per load (both measured best at 3 for 64)
+        constexpr int LP = LS * MF * 3 / 4 >= NL ? 1 : (NL + MF * 3 / 4 - 1) / (MF * 3 / 4);          // loads at a time
+        static_assert(RS >= 1, "side work fits between the multiplies");
         constexpr int i = IDX / AN, j = IDX % AN;
         acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(gw[H][j], ga[H][i], acc[i][j], 0, 0, 0);
         if constexpr (IDX % RS == 0 && IDX / RS < NR) {
@@ -403,11 +404,13 @@ struct GemmTileExec {
             half_read<1 - H, IDX / RS>(va_, vw_);
             __builtin_amdgcn_sched_barrier(0);
         }
-        if constexpr (IDX % LS == LS / 2 && IDX / LS < NL) {
-            constexpr int v = IDX / LS;
+        if constexpr (IDX % LS == LS / 2 && IDX / LS * LP < NL) {
             __builtin_amdgcn_sched_barrier(0);
-            if constexpr (LOADS == 1) load_lds_16B(pa[v % LIA] + koff, as_base + lstage * (BM * BK) + (wave * LRA + v * 8) * BK);
-            else load_lds_16B(pw[v % LIW] + koff, ws_base + lstage * (BN * BK) + (wave * LRW + v * 8) * BK);
+#pragma unroll
+            for (int v = IDX / LS * LP; v < IDX / LS * LP + LP && v < NL; ++v) {
+                if constexpr (LOADS == 1) load_lds_16B(pa[v % LIA] + koff, as_base + lstage * (BM * BK) + (wave * LRA + v * 8) * BK);
+                else load_lds_16B<NTW>(pw[v % LIW] + koff, ws_base + lstage * (BN * BK) + (wave * LRW + v * 8) * BK);
+            }
             __builtin_amdgcn_sched_barrier(0);
         }
     }
@@ -417,13 +420,20 @@ struct GemmTileExec {
         (half_mma_one<H, LOADS, I>(va_, vw_, koff, lstage), ...);
         __builtin_amdgcn_sched_barrier(0);
     }
+    __device__ __forceinline__ int64_t column(int tile) {         // first column of this group's K tile `tile`
+        if constexpr (ROT) {
+            tile += k_first;
+            if (tile >= k_count) tile -= k_count;
+        }
+        return (int64_t)(tile * KS + kg) * BK;
+    }
     __device__ __forceinline__ void load_a(int tile, int stage) {
 #pragma unroll
-        for (int v = 0; v < LIA; ++v) load_lds_16B(pa[v] + (int64_t)tile * BK, as_base + stage * (BM * BK) + (wave * LRA + v * 8) * BK);
+        for (int v = 0; v < LIA; ++v) load_lds_16B(pa[v] + column(tile), as_base + stage * (BM * BK) + (wave * LRA + v * 8) * BK);
     }
     __device__ __forceinline__ void load_w(int tile, int stage) {
 #pragma unroll
-        for (int v = 0; v < LIW; ++v) load_lds_16B(pw[v] + (int64_t)tile * BK, ws_base + stage * (BN * BK) + (wave * LRW + v * 8) * BK);
+        for (int v = 0; v < LIW; ++v) load_lds_16B<NTW>(pw[v] + column(tile), ws_base + stage * (BN * BK) + (wave * LRW + v * 8) * BK);
     }
     template <int LA, int LW>
     __device__ __forceinline__ void wait_loads() {
@@ -435,12 +445,12 @@ struct GemmTileExec {
     }
     template <int H>
     __device__ __forceinline__ void mma_fetch_load_a(int astage, int wstage, int tile, int lstage) {
-        half_mma_seq<H, 1>(a_lds + astage * (BM * BK * 2) + foff[1 - H], w_lds + wstage * (BN * BK * 2) + foff[1 - H], (int64_t)tile * BK, lstage,
+        half_mma_seq<H, 1>(a_lds + astage * (BM * BK * 2) + foff[1 - H], w_lds + wstage * (BN * BK * 2) + foff[1 - H], column(tile), lstage,
                            std::make_integer_sequence<int, AM * AN>{});
     }
     template <int H>
     __device__ __forceinline__ void mma_fetch_load_w(int astage, int wstage, int tile, int lstage) {
-        half_mma_seq<H, 2>(a_lds + astage * (BM * BK * 2) + foff[1 - H], w_lds + wstage * (BN * BK * 2) + foff[1 - H], (int64_t)tile * BK, lstage,
+        half_mma_seq<H, 2>(a_lds + astage * (BM * BK * 2) + foff[1 - H], w_lds + wstage * (BN * BK * 2) + foff[1 - H], column(tile), lstage,
                            std::make_integer_sequence<int, AM * AN>{});
     }
     template <int BUF, int SUB>
@@ -457,12 +467,13 @@ struct GemmTileExec {
     }
 };
 
-// SCHED: 0 = the schedule of pipe::gemm_k_loop<NS>; the schedule for one wave per SIMD (one K group; wave tiles of an odd number of 16-row
-// blocks too) with NS stages of both operands, 2 = pipe::gemm_k_loop_spread<NS, NS>, or with one more of the activations, 1 = <NS + 1, NS>.
+// SCHED: 0 = the schedule of pipe::gemm_k_loop<NS>; the schedule for one wave per SIMD (wave tiles of an odd number of 16-row blocks too; and for the
+// two K groups of a small tile, two waves per SIMD, whose few multiplies per step want every request spread just as much) with NS stages of both operands, 2 = pipe::gemm_k_loop_spread<NS, NS>, or with one more of the activations, 1 = <NS + 1, NS>.
 // us, all loads of a step behind its barrier -> spread over both halves (rows x N x K): 256 x 256 tiles, two stages -> three and two: 3262 x 4096 x 4096
 // 95.9 -> 88.1, 6758 x 2048 x 8192 208 -> 186, 3262 x 4096 x 16384 351 -> 324, 12288 x 4096 x 12288 932 -> 873, 4096 x 8192 x 32768 2192 -> 1532 (rows
 // 64 KB apart; 128 bytes further 1884 -> 1532), at K = 2048 0 to 2 %; pairs of 128 x 128: 1200 x 6144 x 2048 33.5 -> 31.9; 192 x 128: 700 x 6144 x
-// 2048 24.4 -> 22.4; 96 x 128: 1200 x 2048 x 2048 15.4 -> 14.5, 3054 x 1024 x 4096 29.5 -> 28.4; 128 x 256: 400 x 12288 x 4096 55.4 -> 54.5.  More stages
+// 2048 24.4 -> 22.4; two K groups, from gemm_k_loop<3>: 300 x 1024 x 4096 17.4 -> 14.3, 100 x 8192 x 2048 11.3 -> 9.9, 300 x 1536 x 1536 9.0 -> 8.2, 160 x 2304 x
+// 768 6.5 -> 6.2 (the weight stream of 17 to 128 rows gains nothing: 120 x 12288 x 12288 79.2 -> 81.7); 96 x 128: 1200 x 2048 x 2048 15.4 -> 14.5, 3054 x 1024 x 4096 29.5 -> 28.4; 128 x 256: 400 x 12288 x 4096 55.4 -> 54.5.  More stages
 // than these gain nothing (96 x 128 in five, 192 x 128 in four, 128 x 256 in four and three: level or 1 to 3 % slower).
 // NTS: the output is stored with the non-temporal hint (outputs of 256 MB and more, which no cache keeps for their reader:
 // 24576 x 49152 x 12288 21.70 -> 21.53 ms, 24576 x 12288 x 12288 5.69 -> 5.59, 8192 x 16384 x 12288 2.436 -> 2.393).
@@ -476,7 +487,7 @@ template <int BM, int BN, int WGM, int WGN, int EPI, int NS, int KS, int SCHED, 
 // (192 x 128 tiles are made for two workgroups per CU: the residual and cache-row look-ups of their epilogue would take the
 // kernel past 256 registers and halve that: 2000 x 4096 x 4096 with a residual 135 us)
 __global__ __launch_bounds__(WGM* WGN* KS * 64, BM == 192 && BN == 128 && NS == 2 ? 2 : 1) void gemm_mfma_dma64(GemmArgs a, int tiles_m, int tiles_n) {
-    static_assert(SCHED == 0 || (KS == 1 && (SCHED == 1 || (SCHED == 2 && NS > 2))), "schedule");
+    static_assert(SCHED == 0 || SCHED == 1 || (SCHED == 2 && NS > 2), "schedule");
     // KS > 1: KS groups of WGM x WGN waves share the tile and take every KS-th K step each, through LDS stages of their
     // own; the other groups' accumulators are added to the first's through LDS at the end.  For the few
     // tiles of a narrow output with a long K, where nothing else puts more loads in flight per CU.
@@ -1707,9 +1718,9 @@ hipError_t launch_gemm(const GemmArgs& a, Epilogue epi, hipStream_t s) {
         case kFullNone: break;
         }
         switch (tile_for(a.M, a.N, a.K)) {
-        case kTile64: launch_dma64_cfg<2, 1, 64, 64, 3>(a, epi, s); break;
-        case kTile64Split: launch_dma64_cfg<2, 1, 64, 64, 3, 2>(a, epi, s); break;
-        case kTile128x64Split: launch_dma64_cfg<4, 1, 128, 64, 3, 2>(a, epi, s); break;
+        case kTile64: launch_dma64_cfg<2, 1, 64, 64, 3, 1, 2>(a, epi, s); break;
+        case kTile64Split: launch_dma64_cfg<2, 1, 64, 64, 3, 2, 2>(a, epi, s); break;
+        case kTile128x64Split: launch_dma64_cfg<4, 1, 128, 64, 3, 2, 2>(a, epi, s); break;
         case kTile128x64: launch_dma64_cfg<4, 1, 128, 64, 3>(a, epi, s); break;
         case kTile192Pair: launch_dma64_cfg<2, 2, 192, 128, 2, 1, 0>(a, epi, s); break;
         case kTile128PairShared: launch_dma64_cfg<2, 2, 128, 128>(a, epi, s); break;
