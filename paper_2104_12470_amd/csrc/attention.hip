@@ -33,17 +33,38 @@ constexpr float kLog2e = 1.4426950408889634f;
 // The (sequence, head) pairs and their query tiles over the workgroups of a prefill launch: the tiles of a pair on one
 // XCD (workgroups are dealt round-robin to the 8 XCDs; the chunk size is a multiple of 8), whose L2 then holds its K/V,
 // and within a chunk of pairs the longest tiles of all its pairs first, then the next longest ... (the best balance).
-// grid = (pairs, tiles) is one chunk; chunk_pairs != 0, grid = (chunks * chunk_pairs * chunk_tiles), takes the pairs
-// chunk after chunk, so that the K/V of the pairs in flight stays in the memory-side cache from one tile of a pair to its
-// next.  false: a pad workgroup of the last chunk.
-__device__ __forceinline__ bool prefill_pair_and_tile(const AttnPrefillArgs& a, int& pair, int& tile) {
-    pair = blockIdx.x;
-    tile = (int)gridDim.y - 1 - (int)blockIdx.y;
-    if (a.chunk_pairs != 0) {
-        const int per = a.chunk_pairs * a.chunk_tiles, c = blockIdx.x / per, r = blockIdx.x - c * per;
-        pair = c * a.chunk_pairs + r % a.chunk_pairs;
-        tile = a.chunk_tiles - 1 - r / a.chunk_pairs;
+// The work of one of the extra workgroups: one word of its share of the lines (pipe::ahead_line).  They come last in the grid, so they fill
+// what a launch of one round leaves of the CUs, and the tail of one of several.  Ordinary loads, kept by an empty use of their xor as in
+// run_prefetch.
+__device__ __forceinline__ void touch_weights(const WeightsAhead& w, uint32_t part, uint32_t tid, uint32_t nthreads) {
+    int acc = 0;
+    for (int r = 0; r < 2; ++r) {
+        const char* base = static_cast<const char*>(w.at[r]);
+        const uint32_t lines = w.lines[r], blocks = (uint32_t)w.blocks;
+        for (uint32_t i = pipe::ahead_line(part, blocks, tid, nthreads, 0); i < lines; i += 8u * blocks * nthreads) {
+            int v[8];
+#pragma unroll
+            for (uint32_t u = 0; u < 8; ++u) {
+                const uint32_t j = i + u * blocks * nthreads;
+                v[u] = j < lines ? *reinterpret_cast<const int*>(base + (size_t)j * 128) : 0;
+            }
+#pragma unroll
+            for (int u = 0; u < 8; ++u) acc ^= v[u];
+        }
     }
+    asm volatile("" ::"v"(acc));
+}
+
+// The pairs come in chunks of chunk_pairs, so that the K/V of the pairs in flight stays in the memory-side cache from one tile of a
+// pair to its next.  false: a pad workgroup of the last chunk, or one of the last a.ahead.blocks, which do nothing but touch weights.
+__device__ __forceinline__ bool prefill_pair_and_tile(const AttnPrefillArgs& a, int& pair, int& tile) {
+    if ((int)blockIdx.x >= a.tile_blocks) {
+        touch_weights(a.ahead, blockIdx.x - (uint32_t)a.tile_blocks, threadIdx.x, blockDim.x);
+        return false;
+    }
+    const int per = a.chunk_pairs * a.chunk_tiles, c = blockIdx.x / per, r = blockIdx.x - c * per;
+    pair = c * a.chunk_pairs + r % a.chunk_pairs;
+    tile = a.chunk_tiles - 1 - r / a.chunk_pairs;
     return pair < a.batch * a.heads;
 }
 
@@ -764,7 +785,8 @@ hipError_t launch_attention_prefill(const AttnPrefillArgs& a, const SeqLens& len
     for (int b = 0; b < a.batch; ++b) tiles128 += (int64_t)a.heads * ((lens.len[b] + 127) / 128);
     const bool few = fine && tiles128 < (a.d == 128 ? 160 : 320);
     const int bq = wide ? 256 : few ? 64 : 128;
-    const dim3 grid(a.heads * a.batch, (a.max_len + bq - 1) / bq), block(wide || (fine && !few) ? 512 : 256);
+    const int pairs = a.heads * a.batch, tiles = (a.max_len + bq - 1) / bq;
+    const dim3 block(wide || (fine && !few) ? 512 : 256);
     // In chunks of pairs once the K/V of the launch is more than the memory-side cache holds: with the tiles of all
     // pairs in turn, a pair's K/V then comes from HBM again for every one of its tiles (16 prompts of 1024-2048
     // tokens, 96 heads: 6.3 GB fetched for 1.2 GB of K/V and 0.6 GB of Q).  TFLOP/s by pairs per chunk, one call
@@ -778,18 +800,18 @@ hipError_t launch_attention_prefill(const AttnPrefillArgs& a, const SeqLens& len
     AttnPrefillArgs w = a;
     size_t kv_bytes = 0;
     for (int b = 0; b < a.batch; ++b) kv_bytes += (size_t)lens.len[b] * a.heads * a.d * 2 * sizeof(half_t);
-    const int pairs = (int)grid.x;
-    int chunk = 0;
+    int chunk = pairs;
     if (kv_bytes > kMemorySideCacheBytes) {
         chunk = (int)(kChunkKvBytes / (kv_bytes / pairs)) / 8 * 8;
         chunk = chunk < 16 ? 16 : chunk > 48 ? 48 : chunk;
     }
-    w.chunk_pairs = chunk >= pairs ? 0 : chunk;
-    w.chunk_tiles = (int)grid.y;
-    const dim3 wgrid = w.chunk_pairs ? dim3((pairs + chunk - 1) / chunk * chunk * grid.y) : grid;
+    w.chunk_pairs = chunk < pairs ? chunk : pairs;
+    w.chunk_tiles = tiles;
+    w.tile_blocks = (pairs + w.chunk_pairs - 1) / w.chunk_pairs * w.chunk_pairs * tiles;
+    const dim3 grid(w.tile_blocks + w.ahead.blocks);
     if (fine) {
-#define EET_FINE(D, C) do { if (few) hipLaunchKernelGGL((attn_prefill16<D, C, 4>), wgrid, block, 0, s, w, lens); \
-                            else hipLaunchKernelGGL((attn_prefill16<D, C, 8>), wgrid, block, 0, s, w, lens); } while (0)
+#define EET_FINE(D, C) do { if (few) hipLaunchKernelGGL((attn_prefill16<D, C, 4>), grid, block, 0, s, w, lens); \
+                            else hipLaunchKernelGGL((attn_prefill16<D, C, 8>), grid, block, 0, s, w, lens); } while (0)
         if (a.d == 128) {
             if (a.causal) EET_FINE(128, true);
             else EET_FINE(128, false);
@@ -799,11 +821,11 @@ hipError_t launch_attention_prefill(const AttnPrefillArgs& a, const SeqLens& len
         }
 #undef EET_FINE
     } else if (wide) {
-        if (a.causal) hipLaunchKernelGGL((attn_prefill_wide<128, true>), wgrid, block, 0, s, w, lens);
-        else hipLaunchKernelGGL((attn_prefill_wide<128, false>), wgrid, block, 0, s, w, lens);
+        if (a.causal) hipLaunchKernelGGL((attn_prefill_wide<128, true>), grid, block, 0, s, w, lens);
+        else hipLaunchKernelGGL((attn_prefill_wide<128, false>), grid, block, 0, s, w, lens);
     } else {
-        if (a.causal) hipLaunchKernelGGL((attn_prefill<true>), wgrid, block, 0, s, w, lens);
-        else hipLaunchKernelGGL((attn_prefill<false>), wgrid, block, 0, s, w, lens);
+        if (a.causal) hipLaunchKernelGGL((attn_prefill<true>), grid, block, 0, s, w, lens);
+        else hipLaunchKernelGGL((attn_prefill<false>), grid, block, 0, s, w, lens);
     }
     return hipGetLastError();
 }

@@ -56,6 +56,14 @@ struct PrefetchArgs {
     int blocks;                 // extra workgroups that do nothing else; 0 = no prefetch
 };
 
+// The same for weights that the launches behind a prefill's attention read: linear ranges in 128-byte lines, touched by `blocks` extra
+// workgroups (tile_rules.hpp: prefill_touches_weights has the rule).
+struct WeightsAhead {
+    const void* at[2];
+    uint32_t lines[2];
+    int blocks;                 // 0 = none
+};
+
 // ---- dense projections (gemm.hip) ------------------------------------------------------------
 enum Epilogue : int { EPI_BIAS = 0, EPI_BIAS_GELU = 1, EPI_BIAS_RES = 2, EPI_QKV = 3 };
 constexpr int EPI_PARTIAL = 4;   // inside gemm.hip only: the sums of one K range, unrounded (GemmArgs::part)
@@ -155,7 +163,8 @@ struct AttnPrefillArgs {
     int S;                  // padded length (row stride between sequences when not packed)
     int max_len;            // max over lens (sizes the grid)
     int causal;             // 1: query i sees keys 0..i; 0: every valid query sees all L_b keys (encoder)
-    int chunk_pairs, chunk_tiles;   // set by the launcher (callers leave 0): the grid order of the prefill kernels
+    WeightsAhead ahead;             // launch_attention_prefill only
+    int chunk_pairs, chunk_tiles, tile_blocks;   // set by the launcher (callers leave 0): the grid order of the prefill kernels, and their workgroups that have a tile
 };
 hipError_t launch_attention_prefill(const AttnPrefillArgs& a, const SeqLens& lens, hipStream_t s);
 // Unfused form (causal, not packed, S a multiple of 8): raw scores q.k into scores[batch, heads, S, S] for the tiles

@@ -63,6 +63,14 @@ EET_PIPE_FN void tile_of_block(int pid, int tiles_m, int tiles_n, int& tile_m, i
 }
 
 // ---------------------------------------------------------------------------------------------------------
+// Load number u of thread tid in part `part` of `blocks` parts that touch a range line by line.  A wave's load covers 64 consecutive lines,
+// and such pieces of 8 KB go to the parts in turn, that is to the XCDs.  Every line is one thread's (checked on the host).
+// ---------------------------------------------------------------------------------------------------------
+EET_PIPE_FN unsigned ahead_line(unsigned part, unsigned blocks, unsigned tid, unsigned nthreads, unsigned u) {
+    return ((u * (nthreads / 64) + tid / 64) * blocks + part) * 64 + tid % 64;
+}
+
+// ---------------------------------------------------------------------------------------------------------
 // K loop of the MFMA tile kernel: K tiles of 64 columns through NS LDS stages (tile t in stage t % NS), four
 // sub-steps per tile, fragments double-buffered in registers (buffer = sub-step % 2).
 //

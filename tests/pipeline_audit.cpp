@@ -458,6 +458,19 @@ int main() {
         snprintf(name, sizeof name, "256-row attention, K and V rings of three stages, %d key tiles", nt);
         expect_ok(r.verdict(name), name);
     }
+    // lines touched ahead: in any number of parts, every line of a range exactly once
+    for (unsigned blocks : {1u, 8u, 128u})
+        for (unsigned threads : {256u, 512u})
+            for (unsigned lines : {1u, 63u, 4097u, 150000u}) {
+                std::vector<int> seen(lines, 0);
+                for (unsigned part = 0; part < blocks; ++part)
+                    for (unsigned tid = 0; tid < threads; ++tid)
+                        for (unsigned u = 0, j; (j = eet::pipe::ahead_line(part, blocks, tid, threads, u)) < lines; ++u) ++seen[j];
+                bool once = true;
+                for (int n : seen) once &= n == 1;
+                snprintf(name, sizeof name, "%u lines in %u parts of %u threads", lines, blocks, threads);
+                expect_ok(once ? "" : "a line is not touched exactly once", name);
+            }
     {   // the tile order visits every tile exactly once, for every grid up to 40 x 40 tiles and a few large ones (all three orders)
         int bad = 0;
         auto check_grid = [&](int tm, int tn) {
