@@ -336,17 +336,19 @@ struct AttnRingExec {
     __device__ __forceinline__ void wait_reads() { wait_lds<0>(); }
 };
 
-template <int D, bool CAUSAL>
+// KG = 2: 128 query rows, and two groups of four waves that take the lower and the upper 32 keys of every tile and merge at the end.
+template <int D, bool CAUSAL, int KG>
 __global__ __launch_bounds__(512) void attn_prefill_wide(AttnPrefillArgs a, SeqLens lens) {
-    constexpr int BQ = 256, WQ = 32, BKV = 64, NWAVE = 8;
+    constexpr int WQ = 32, BKV = 64, NWAVE = 8, BQ = WQ * NWAVE / KG;
     constexpr int ROWB = D * 2;                  // bytes of a K / V row
     constexpr int TILEB = BKV * ROWB;            // bytes of a key tile
     constexpr int CPR = ROWB / 16;               // 16-byte chunks per row
     constexpr int RPI = 64 / CPR;                // rows one wave-level load instruction covers (1 KB of LDS)
     constexpr int NV = TILEB / 1024 / NWAVE;     // load instructions per wave per tile
     constexpr int KK = D / 16, DB = D / 32;
-    __shared__ __attribute__((aligned(1024))) char Ks[3][TILEB];
-    __shared__ __attribute__((aligned(1024))) char Vs[3][TILEB];
+    __shared__ __attribute__((aligned(1024))) char smem[6 * TILEB];
+    char* const Ks = smem;                       // rings of three stages
+    char* const Vs = smem + 3 * TILEB;
 
     int pair, tile;
     if (!prefill_pair_and_tile(a, pair, tile)) return;
@@ -360,13 +362,15 @@ __global__ __launch_bounds__(512) void attn_prefill_wide(AttnPrefillArgs a, SeqL
     }
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int li = lane & 31, G = lane >> 5;
-    const int iw0 = i0 + (wave < 4 ? wave : 11 - wave) * WQ;      // SIMD s hosts row blocks s and 7-s
+    const int kg = KG == 2 ? wave >> 2 : 0;
+    const int iw0 = i0 + (KG == 2 ? wave & 3 : wave < 4 ? wave : 11 - wave) * WQ;      // SIMD s hosts row blocks s and 7-s (KG = 2: both groups of block s)
     const int i = iw0 + li;                                       // this lane's query
 
     const int last_key = (CAUSAL && i0 + BQ - 1 < L - 1) ? i0 + BQ - 1 : L - 1;
     const int nt_wg = last_key / BKV + 1;                         // key tiles the workgroup stages
     // halves (32 keys) this wave uses; the last one is the only one with hidden keys
-    const int nh_w = iw0 >= L ? 0 : (CAUSAL ? iw0 / 32 + 1 : (L + 31) / 32);
+    const int nh_rows = iw0 >= L ? 0 : (CAUSAL ? iw0 / 32 + 1 : (L + 31) / 32);
+    const int nh_w = KG == 2 ? (nh_rows + 1 - kg) / 2 : nh_rows;  // KG = 2: of one tile each; both groups test their last one
 
     // Q^T fragments (B operand): query i, depth kk*16 + G*8 .. +8
     half8v qf[KK];
@@ -398,7 +402,7 @@ __global__ __launch_bounds__(512) void attn_prefill_wide(AttnPrefillArgs a, SeqL
         for (int v = 0; v < NV; ++v) {
             int key = jt * BKV + ld_row[v];
             key = key < L ? key : L - 1;
-            load_lds_16B(kbase + ((uint32_t)key * ROWB + ld_k[v]), &Ks[st][(wave * NV + v) * 1024]);
+            load_lds_16B(kbase + ((uint32_t)key * ROWB + ld_k[v]), Ks + st * TILEB + (wave * NV + v) * 1024);
         }
     };
     auto load_v = [&](int jt, int st) __attribute__((always_inline)) {
@@ -406,7 +410,7 @@ __global__ __launch_bounds__(512) void attn_prefill_wide(AttnPrefillArgs a, SeqL
         for (int v = 0; v < NV; ++v) {
             int key = jt * BKV + ld_row[v];
             key = key < L ? key : L - 1;
-            load_lds_16B(vbase + ((uint32_t)key * ROWB + ld_v[v]), &Vs[st][(wave * NV + v) * 1024]);
+            load_lds_16B(vbase + ((uint32_t)key * ROWB + ld_v[v]), Vs + st * TILEB + (wave * NV + v) * 1024);
         }
     };
 
@@ -415,7 +419,7 @@ __global__ __launch_bounds__(512) void attn_prefill_wide(AttnPrefillArgs a, SeqL
 #pragma unroll
     for (int kk = 0; kk < KK; ++kk) {
         const int sw = D == 128 ? (li & 15) : ((li >> 1) & 7);
-        kaddr[kk] = (unsigned)(uintptr_t)&Ks[0][0] + li * ROWB + (((kk * 2 + G) ^ sw) * 16);
+        kaddr[kk] = (unsigned)(uintptr_t)Ks + (kg * 32 + li) * ROWB + (((kk * 2 + G) ^ sw) * 16);
     }
     unsigned vaddr[DB];     // transpose read: this lane supplies key G*4 + (li%16)/4 (+ offset), 4 halfs at dv db*32 + (li/16)*16 + (li%4)*4
     {
@@ -424,7 +428,7 @@ __global__ __launch_bounds__(512) void attn_prefill_wide(AttnPrefillArgs a, SeqL
 #pragma unroll
         for (int db = 0; db < DB; ++db) {
             const int cc = db * 4 + blk * 2 + ((lb & 3) >> 1);
-            vaddr[db] = (unsigned)(uintptr_t)&Vs[0][0] + (G * 4 + (lb >> 2)) * ROWB + ((cc ^ sw) * 16) + (lb & 1) * 8;
+            vaddr[db] = (unsigned)(uintptr_t)Vs + (kg * 32 + G * 4 + (lb >> 2)) * ROWB + ((cc ^ sw) * 16) + (lb & 1) * 8;
         }
     }
 
@@ -549,7 +553,7 @@ __global__ __launch_bounds__(512) void attn_prefill_wide(AttnPrefillArgs a, SeqL
     constexpr std::false_type no{};
     // half h of the wave: cur holds its scores; the K fragments of half h+1 have been requested
     auto wave_half = [&](int h, auto jb, float16v& cur, float16v& nxt, const unsigned (&va)[DB], const unsigned (&ka2)[KK]) __attribute__((always_inline)) {
-        const int j0_next = (h + 1) * 32;
+        const int j0_next = KG == 2 ? (h + 1) * BKV + kg * 32 : (h + 1) * 32;
         if (h + 2 < nh_w) half_step(cur, nxt, va, jb, ka2, j0_next, yes, no, yes);
         else if (h + 2 == nh_w) half_step(cur, nxt, va, jb, ka2, j0_next, yes, yes, no);   // the next half is the last: its keys are tested
         else if (h + 1 == nh_w) half_step(cur, nxt, va, jb, ka2, j0_next, no, no, no);
@@ -567,24 +571,65 @@ __global__ __launch_bounds__(512) void attn_prefill_wide(AttnPrefillArgs a, SeqL
             wait_lds<0>();
             landed_k();
             scores(sa);
-            if (nh_w == 1) row_max(sa, 0, yes);
+            if (nh_w == 1) row_max(sa, kg * 32, yes);
             else row_max(sa, 0, no);                      // alpha = 0 and the accumulators are zero: nothing to rescale
-            if (nh_w > 1) read_k(kf, kaddr, jb1);
+            if (nh_w > 1) {
+                if constexpr (KG == 2) {
+                    unsigned ka1[KK];
+#pragma unroll
+                    for (int kk = 0; kk < KK; ++kk) ka1[kk] = kaddr[kk] + TILEB;
+                    read_k(kf, ka1, jb0);
+                } else {
+                    read_k(kf, kaddr, jb1);
+                }
+            }
             __builtin_amdgcn_sched_barrier(0);
         }
     };
     auto step = [&](int jt, int v_stage, int k_stage) __attribute__((always_inline)) {
-        unsigned ka2[KK], va[DB];                         // fragment addresses in the stages of K(jt+1) and V(jt)
+        unsigned ka2[KK], va[DB];                         // fragment addresses in the stages of K(jt+1) (KG = 2: K(jt+2)) and V(jt)
 #pragma unroll
         for (int kk = 0; kk < KK; ++kk) ka2[kk] = kaddr[kk] + k_stage * TILEB;
 #pragma unroll
         for (int db = 0; db < DB; ++db) va[db] = vaddr[db] + v_stage * TILEB;
+        if constexpr (KG == 2) {                          // (the groups' keys are in their addresses)
+            wave_half(jt, jb0, sa, sb, va, ka2);
+            sa = sb;
+            return;
+        }
         wave_half(2 * jt, jb0, sa, sb, va, ka2);          // requests the K fragments of half 2*jt+2: tile jt+1, jb 0
         wave_half(2 * jt + 1, jb1, sb, sa, va, ka2);      // ... of half 2*jt+3: tile jt+1, jb 1
     };
     AttnRingExec<2 * NV, decltype(load_k), decltype(load_v), decltype(first_scores), decltype(step)> ring{load_k, load_v, first_scores, step};
-    pipe::attn_kv_loop(ring, nt_wg);
+    pipe::attn_kv_loop<KG>(ring, nt_wg);
 
+    if constexpr (KG == 2) {
+        // the upper group hands its reference, sum and values over: 16 bytes per lane and instruction, a wave's side by side
+        __syncthreads();
+        float4v* const part = reinterpret_cast<float4v*>(smem) + (wave & 3) * (DB * 4 * 64) + lane;
+        float2v* const part_ml = reinterpret_cast<float2v*>(smem + 4 * DB * 4 * 64 * 16) + (wave & 3) * 64 + lane;
+        static_assert(4 * DB * 4 * 64 * 16 + 4 * 64 * 8 <= sizeof(smem), "the hand-over fits over the rings");
+        if (kg == 1) {
+#pragma unroll
+            for (int db = 0; db < DB; ++db)
+#pragma unroll
+                for (int rg = 0; rg < 4; ++rg) part[(db * 4 + rg) * 64] = float4v{o[db][rg * 4], o[db][rg * 4 + 1], o[db][rg * 4 + 2], o[db][rg * 4 + 3]};
+            *part_ml = float2v{m, l};
+        }
+        __syncthreads();
+        if (kg == 1) return;
+        const float2v ml = *part_ml;                      // a group that saw no key: reference -inf, sum and values zero
+        const float m_new = fmaxf(m, ml[0]), mine = __builtin_amdgcn_exp2f(m - m_new), theirs = __builtin_amdgcn_exp2f(ml[0] - m_new);
+        l = l * mine + ml[1] * theirs;
+#pragma unroll
+        for (int db = 0; db < DB; ++db)
+#pragma unroll
+            for (int rg = 0; rg < 4; ++rg) {
+                const float4v p = part[(db * 4 + rg) * 64];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) o[db][rg * 4 + e] = o[db][rg * 4 + e] * mine + p[e] * theirs;
+            }
+    }
     l += __shfl_xor(l, 32, kWave);
     if (i >= L) return;
     const float inv = 1.0f / l;
@@ -784,9 +829,16 @@ hipError_t launch_attention_prefill(const AttnPrefillArgs& a, const SeqLens& len
     int64_t tiles128 = 0;
     for (int b = 0; b < a.batch; ++b) tiles128 += (int64_t)a.heads * ((lens.len[b] + 127) / 128);
     const bool few = fine && tiles128 < (a.d == 128 ? 160 : 320);
-    const int bq = wide ? 256 : few ? 64 : 128;
+    // The 256-row kernel with its keys in two halves (KG = 2) where a workgroup is the whole chain: 128-row tiles that the CUs take in one round, or
+    // of long causal prompts, whose chains are of all lengths, in not quite two.  A full chip loses by it: every key tile is staged for half as
+    // many rows.  us, 256 rows / halves, heads of 128, by tiles of 128 rows: causal, one prompt of 600 tokens, 2 heads, 10 tiles 20.2 / 15.8; 8 heads of
+    // 4000, 256 98 / 64; 2 x 16 of 700 and 1000, 224 32.4 / 22.6; 2 x 16 of 1000 and 2000, 384 56 / 46; 16 of 4096, 512 112 / 87; 4 x 8 of 2048, 512 61 / 51;
+    // 4 of 16384, 512 418 / 311; and not 85 of 600, 425 25.7 / 30.4; 10 x 8 of 517 to 1024, 500 35 / 42; 2 x 16 of 1500 and 3000, 576 80 / 92; 2 x 16 of 2662 and 4096, 848
+    // 132 / 154.  Without a sequence mask: 8 of 4096, 256 109 / 81; 40 of 600, 200 25 / 18; 64 of 600, 320 25.7 / 32.6; 12 of 4096, 384 119 / 141.
+    const bool halves = wide && tiles128 <= (!a.causal || a.max_len < 1024 ? 256 : a.max_len < 2048 ? 384 : 512);
+    const int bq = halves ? 128 : wide ? 256 : few ? 64 : 128;
     const int pairs = a.heads * a.batch, tiles = (a.max_len + bq - 1) / bq;
-    const dim3 block(wide || (fine && !few) ? 512 : 256);
+    const dim3 block(wide || halves || (fine && !few) ? 512 : 256);
     // In chunks of pairs once the K/V of the launch is more than the memory-side cache holds: with the tiles of all
     // pairs in turn, a pair's K/V then comes from HBM again for every one of its tiles (16 prompts of 1024-2048
     // tokens, 96 heads: 6.3 GB fetched for 1.2 GB of K/V and 0.6 GB of Q).  TFLOP/s by pairs per chunk, one call
@@ -821,8 +873,11 @@ hipError_t launch_attention_prefill(const AttnPrefillArgs& a, const SeqLens& len
         }
 #undef EET_FINE
     } else if (wide) {
-        if (a.causal) hipLaunchKernelGGL((attn_prefill_wide<128, true>), grid, block, 0, s, w, lens);
-        else hipLaunchKernelGGL((attn_prefill_wide<128, false>), grid, block, 0, s, w, lens);
+#define EET_WIDE(C) do { if (halves) hipLaunchKernelGGL((attn_prefill_wide<128, C, 2>), grid, block, 0, s, w, lens); \
+                         else hipLaunchKernelGGL((attn_prefill_wide<128, C, 1>), grid, block, 0, s, w, lens); } while (0)
+        if (a.causal) EET_WIDE(true);
+        else EET_WIDE(false);
+#undef EET_WIDE
     } else {
         if (a.causal) hipLaunchKernelGGL((attn_prefill<true>), grid, block, 0, s, w, lens);
         else hipLaunchKernelGGL((attn_prefill<false>), grid, block, 0, s, w, lens);

@@ -269,27 +269,33 @@ EET_PIPE_FN void gemm_k_loop_spread(Ops& op, int nk) {
 //   first_scores()                             reads K(0) out of K stage 0 and waits for them (scores of tile 0)
 //   step(jt, v_stage, k_stage)                 reads V(jt) from v_stage and K(jt+1) from k_stage, multiplies
 //   wait_reads()                               every LDS read of this wave has landed
+//
+// AHEAD = 2 is for waves that take half of the keys of every tile each: a wave's next scores are then those of the next tile, whose fragments
+// have been requested a step earlier, so step jt reads K(jt+2) and K runs one tile further ahead of V.  first_scores reads K(0) and K(1).
 // ---------------------------------------------------------------------------------------------------------
-template <class Ops>
+template <int AHEAD = 1, class Ops = void>
 EET_PIPE_FN void attn_kv_loop(Ops& op, int nt) {
+    static_assert(AHEAD == 1 || AHEAD == 2, "tiles that the key reads are ahead");
     op.load_k(0, 0);
     op.load_k(1, 1);
     op.load_v(0, 0);
     op.load_k(2, 2);
     op.load_v(1, 1);
-    op.wait_loads_but_newest_pair();              // K(0), K(1), V(0) of this wave have landed ...
+    if (AHEAD == 2) op.wait_loads_all();          // K(2) is read in step 0 already
+    else op.wait_loads_but_newest_pair();         // K(0), K(1), V(0) of this wave have landed ...
     op.barrier();                                 // ... and everybody else's
     op.first_scores();
     op.wait_reads();
-    op.barrier();                                 // step 0 refills the stage of K(0)
+    op.barrier();                                 // what follows refills the stages of K(0) and, with AHEAD = 2, K(1)
+    if (AHEAD == 2) op.load_k(3, 0);
     int s0 = 0;                                   // stage of tile jt
     for (int jt = 0; jt < nt; ++jt) {
         const int s1 = s0 == 2 ? 0 : s0 + 1, s2 = s0 == 0 ? 2 : s0 - 1;
-        op.load_k(jt + 3, s0);                    // K(jt) was last read during step jt-1
+        op.load_k(jt + 2 + AHEAD, AHEAD == 2 ? s1 : s0);   // K(jt+AHEAD-1) was last read during step jt-1
         op.load_v(jt + 2, s2);                    // V(jt-1) was last read during step jt-1
-        op.step(jt, s0, s1);
+        op.step(jt, s0, AHEAD == 2 ? s2 : s1);
         op.wait_reads();                          // this wave is done reading the stages of this step
-        op.wait_loads_but_newest_pair();          // K(jt+2), V(jt+1) of this wave have landed ...
+        op.wait_loads_but_newest_pair();          // K(jt+1+AHEAD), V(jt+1) of this wave have landed ...
         op.barrier();                             // ... and everybody else's
         s0 = s1;
     }

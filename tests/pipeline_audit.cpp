@@ -295,28 +295,30 @@ struct SpreadRecorder {
 // ------------------------------------------------------------------------------------------------------------------
 struct AttnRecorder {
     Trace t;
-    int nt;
+    int nt, ahead;
     std::vector<int> k_seen, v_seen;
-    explicit AttnRecorder(int nt_) : nt(nt_), k_seen(nt_ + 4, 0), v_seen(nt_ + 4, 0) {}
+    explicit AttnRecorder(int nt_, int ahead_ = 1) : nt(nt_), ahead(ahead_), k_seen(nt_ + 5, 0), v_seen(nt_ + 5, 0) {}
     void load_k(int tile, int stage) { t.issue_load(0, stage, tile); }
     void load_v(int tile, int stage) { t.issue_load(1, stage, tile); }
     void wait_loads_but_newest_pair() { t.retire_loads(2); }
     void wait_loads_all() { t.retire_loads(0); }
     void barrier() { t.barrier(); }
     void first_scores() {
-        const int r = t.issue_read(0, 0, 0, 0);
-        t.reads[r].consumed = true;
-        ++k_seen[0];
+        for (int j = 0; j < ahead && j < nt; ++j) {
+            const int r = t.issue_read(0, j, j, 0);
+            t.reads[r].consumed = true;
+            ++k_seen[j];
+        }
         t.retire_reads(0);                                 // the kernel waits for these reads before it forms the scores
     }
     void step(int jt, int v_stage, int k_stage) {
         const int rv = t.issue_read(1, v_stage, jt, 0);
         t.reads[rv].consumed = true;
         ++v_seen[jt];
-        if (jt + 1 < nt) {                                 // the keys of the next tile, when there is one
-            const int rk = t.issue_read(0, k_stage, jt + 1, 0);
+        if (jt + ahead < nt) {                                 // the keys of the next tile (or the one behind it), when there is one
+            const int rk = t.issue_read(0, k_stage, jt + ahead, 0);
             t.reads[rk].consumed = true;
-            ++k_seen[jt + 1];
+            ++k_seen[jt + ahead];
         }
     }
     void wait_reads() { t.retire_reads(0); }
@@ -457,6 +459,10 @@ int main() {
         eet::pipe::attn_kv_loop(r, nt);
         snprintf(name, sizeof name, "256-row attention, K and V rings of three stages, %d key tiles", nt);
         expect_ok(r.verdict(name), name);
+        AttnRecorder r2(nt, 2);
+        eet::pipe::attn_kv_loop<2>(r2, nt);
+        snprintf(name, sizeof name, "the same with two groups of waves that take half of every tile, %d key tiles", nt);
+        expect_ok(r2.verdict(name), name);
     }
     // lines touched ahead: in any number of parts, every line of a range exactly once
     for (unsigned blocks : {1u, 8u, 128u})
