@@ -185,7 +185,10 @@ struct AttnDecodeArgs {
     float* part_ml;         // [batch*heads*splits, 2]
     int leave_ranges;       // 1: no merge launch, the projection that follows merges the ranges (GemmArgs::x_splits)
     int read_once;          // 1: K/V rows loaded with the non-temporal hint (see GemmArgs::read_once)
+    int waves;              // of a workgroup: 8, or 4 (also 0: the caller does not know the lengths); see attention_decode_waves
 };
+// by the visible keys of the longest sequence and of all together
+int attention_decode_waves(int d, int heads, int batch, size_t longest, size_t visible);
 int attention_decode_splits(int batch, int heads, int capacity);
 size_t attention_decode_scratch_bytes(int batch, int heads, int d, int splits);
 hipError_t launch_attention_decode(const AttnDecodeArgs& a, hipStream_t s);
