@@ -1069,6 +1069,39 @@ __device__ __forceinline__ float dpp_f(float x) {
     return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), CTRL, 0xf, 0xf, false));
 }
 
+// Column dd of a pair's key ranges, merged in range order: common maximum, rescaled sums, one division.  All loads of up to 16 ranges are requested before they
+// are combined.  AGENT: loads at agent scope, of words that other workgroups of the launch have stored so.
+template <int D, bool AGENT>
+__device__ __forceinline__ half_t merge_ranges(const float* ml, const float* pa, int splits) {
+    constexpr int MAXS = 16;                             // ranges held in registers at a time
+    auto load = [](const float* p) { return AGENT ? __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : *p; };
+    float Lsum = 0.f, A = 0.f;
+    float M = -INFINITY;                                 // an empty range reports the finite kEmpty and a zero sum
+    if (splits > MAXS)
+        for (int s = 0; s < splits; ++s) M = fmaxf(M, load(ml + s * 2));
+    for (int s0 = 0; s0 < splits; s0 += MAXS) {
+        float mv[MAXS], lv[MAXS], av[MAXS];
+#pragma unroll
+        for (int u = 0; u < MAXS; ++u) {
+            const int s = s0 + u < splits ? s0 + u : splits - 1;
+            mv[u] = load(ml + s * 2);
+            lv[u] = load(ml + s * 2 + 1);
+            av[u] = load(pa + s * D);
+        }
+        if (splits <= MAXS) {                            // the usual case: everything in one trip to memory
+#pragma unroll
+            for (int u = 0; u < MAXS; ++u) M = fmaxf(M, mv[u]);
+        }
+#pragma unroll
+        for (int u = 0; u < MAXS; ++u) {
+            const float sc = s0 + u < splits ? exp2f(mv[u] - M) : 0.f;
+            Lsum += lv[u] * sc;
+            A += av[u] * sc;
+        }
+    }
+    return (half_t)(Lsum > 0.f ? A / Lsum : 0.f);        // every range empty: zeros, not 0/0
+}
+
 // NT: K and V rows are loaded with the non-temporal hint (AttnDecodeArgs::read_once); a template parameter because the
 // compiler merges the arms of a branch whose loads differ in nothing but the hint, and drops it.
 template <int D, int NW, bool NT>
@@ -1086,7 +1119,12 @@ __global__ __launch_bounds__(NW * 64) void attn_decode(AttnDecodeArgs a) {
     const int kslot = lane / LPK, chunk = lane % LPK;
     int n = a.lens[b] + a.len_bias;                      // visible keys
     n = n < 0 ? 0 : (n > a.capacity ? a.capacity : n);   // whatever the device-side length says, never outside the pair's slots
-    const int splits = a.splits;
+    int splits = a.splits;
+    if (a.least_keys > 0) {                              // a pair of few keys is one range, and its other workgroups have nothing to do
+        const int most = n / a.least_keys;
+        splits = most < 1 ? 1 : most < splits ? most : splits;
+        if (sp >= splits) return;
+    }
     int per = (n + splits - 1) / splits;
     per = (per + 15) & ~15;
     const int c0 = sp * per;
@@ -1214,6 +1252,21 @@ __global__ __launch_bounds__(NW * 64) void attn_decode(AttnDecodeArgs a) {
         if (tid < D) a.ctx[bh * D + tid] = (half_t)(Lsum > 0.f ? A / Lsum : 0.f);   // a pair that sees no key: zeros, not 0/0
         return;
     }
+    if (a.arrived != nullptr) {
+        // The partials go out at agent scope, and are there once acknowledged; whoever then finds itself the pair's last to count has all of them to
+        // read.  No fence (which writes back and invalidates caches), no waiting for another workgroup, and no launch of its own (4 us).
+        if (tid < D) __hip_atomic_store(a.part_acc + (bh * splits + sp) * D + tid, A, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (tid == 0) {
+            __hip_atomic_store(a.part_ml + (bh * splits + sp) * 2, M, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            __hip_atomic_store(a.part_ml + (bh * splits + sp) * 2 + 1, Lsum, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        __syncthreads();
+        if (tid == 0) sm_l[0] = __hip_atomic_fetch_add(a.arrived + bh * kClearStride, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == (uint32_t)splits - 1u ? 1.f : 0.f;
+        __syncthreads();
+        if (sm_l[0] != 0.f && tid < D) a.ctx[bh * D + tid] = merge_ranges<D, true>(a.part_ml + bh * splits * 2, a.part_acc + bh * splits * D + tid, splits);
+        return;
+    }
     if (tid < D) a.part_acc[(bh * splits + sp) * D + tid] = A;
     if (tid == 0) {
         a.part_ml[(bh * splits + sp) * 2 + 0] = M;
@@ -1221,70 +1274,25 @@ __global__ __launch_bounds__(NW * 64) void attn_decode(AttnDecodeArgs a) {
     }
 }
 
-// Merge the per-range partials (max, sum, weighted values) of the (sequence, head) pairs, in
-// range order.  A separate launch: a device-scope release/acquire inside the attention kernel
-// (last workgroup merges) costs an L2 write-back and invalidate on this multi-die part, far more
-// than the launch it would save.  Workgroup = 256 threads = 256/d pairs; all loads of a pair's
-// ranges are issued before they are combined.
+// The merge as a launch of its own, for callers that have no counters (AttnDecodeArgs::arrived).  Workgroup = 256 threads = 256/d pairs.
 template <int D>
 __global__ __launch_bounds__(256) void attn_decode_combine(AttnDecodeArgs a) {
     constexpr int PPB = 256 / D;                         // pairs per workgroup
-    constexpr int MAXS = 16;                             // ranges held in registers at a time
     const int tid = threadIdx.x, dd = tid % D;
     const int64_t bh = (int64_t)blockIdx.x * PPB + tid / D;
     if (bh >= (int64_t)a.batch * a.heads) return;
-    const int splits = a.splits;
-    const float* ml = a.part_ml + bh * splits * 2;
-    const float* pa = a.part_acc + bh * splits * D + dd;
-    float Lsum = 0.f, A = 0.f;
-    if (splits <= MAXS) {                                // the usual case: everything in one trip to memory
-        float mv[MAXS], lv[MAXS], av[MAXS];
-#pragma unroll
-        for (int u = 0; u < MAXS; ++u) {
-            const int s = u < splits ? u : splits - 1;
-            mv[u] = ml[s * 2];
-            lv[u] = ml[s * 2 + 1];
-            av[u] = pa[s * D];
-        }
-        float M = mv[0];                                 // an empty range reports the finite kEmpty and a zero sum (clamped slots repeat the last range)
-#pragma unroll
-        for (int u = 1; u < MAXS; ++u) M = fmaxf(M, mv[u]);
-#pragma unroll
-        for (int u = 0; u < MAXS; ++u) {
-            const float sc = u < splits ? exp2f(mv[u] - M) : 0.f;
-            Lsum += lv[u] * sc;
-            A += av[u] * sc;
-        }
-        a.ctx[bh * D + dd] = (half_t)(Lsum > 0.f ? A / Lsum : 0.f);
-        return;
-    }
-    float M = -INFINITY;
-    for (int s = 0; s < splits; ++s) M = fmaxf(M, ml[s * 2]);     // an empty range reports the finite kEmpty and a zero sum
-    for (int s0 = 0; s0 < splits; s0 += MAXS) {
-        float mv[MAXS], lv[MAXS], av[MAXS];
-#pragma unroll
-        for (int u = 0; u < MAXS; ++u) {
-            const int s = s0 + u < splits ? s0 + u : splits - 1;
-            mv[u] = ml[s * 2];
-            lv[u] = ml[s * 2 + 1];
-            av[u] = pa[s * D];
-        }
-#pragma unroll
-        for (int u = 0; u < MAXS; ++u) {
-            const float sc = s0 + u < splits ? exp2f(mv[u] - M) : 0.f;
-            Lsum += lv[u] * sc;
-            A += av[u] * sc;
-        }
-    }
-    a.ctx[bh * D + dd] = (half_t)(Lsum > 0.f ? A / Lsum : 0.f);                 // every range empty: zeros, not 0/0
+    a.ctx[bh * D + dd] = merge_ranges<D, false>(a.part_ml + bh * a.splits * 2, a.part_acc + bh * a.splits * D + dd, a.splits);
 }
 
-int attention_decode_splits(int batch, int heads, int capacity) {
+constexpr int kLeastKeys = 384;
+int attention_decode_splits(int batch, int heads, int capacity, bool merges) {
     // One key range per (sequence, head) once there are 128 pairs (measured: as fast as splitting,
     // and no merge launch).  Below that, about 256 workgroups, a power of two, and no range shorter
-    // than 128 keys at full capacity.
+    // than 128 keys at full capacity.  Where the ranges are merged by the kernel itself 128 pairs, half of the CUs, are two ranges each, of
+    // kLeastKeys and more (4 sequences of 32 heads of 128, hidden 4096, us per step: 512 to 1279 keys 93.3 -> 91.3, 2000 to 4000 121.7 -> 113.3; two ranges
+    // of 200 keys 84.7 -> 85.5); more pairs are not: 192 of heads of 64 237.8 -> 244.3, 180 266 -> 276, 224 97.9 -> 99.8.
     const int pairs = batch * heads;
-    if (pairs >= 128) return 1;
+    if (pairs >= 128) return merges && pairs == 128 && capacity >= 2 * kLeastKeys ? 2 : 1;
     int s = 1;
     while (s * pairs < 256) s *= 2;
     while (s > 1 && capacity / s < 128) s /= 2;
@@ -1308,14 +1316,16 @@ size_t attention_decode_scratch_bytes(int batch, int heads, int d, int splits) {
     return (size_t)batch * heads * splits * (d + 2) * sizeof(float);
 }
 
-hipError_t launch_attention_decode(const AttnDecodeArgs& a, hipStream_t s) {
+hipError_t launch_attention_decode(const AttnDecodeArgs& args, hipStream_t s) {
+    AttnDecodeArgs a = args;
+    a.least_keys = a.arrived != nullptr && a.batch * a.heads == 128 ? kLeastKeys : 0;
     const dim3 grid(a.splits, a.heads, a.batch);
 #define EET_DECODE(D, NW) do { if (a.read_once) hipLaunchKernelGGL((attn_decode<D, NW, true>), grid, dim3(64 * NW), 0, s, a); \
                                else hipLaunchKernelGGL((attn_decode<D, NW, false>), grid, dim3(64 * NW), 0, s, a); } while (0)
     if (a.d == 128) { if (a.waves == 8) EET_DECODE(128, 8); else EET_DECODE(128, 4); }
     else { if (a.waves == 8) EET_DECODE(64, 8); else EET_DECODE(64, 4); }
 #undef EET_DECODE
-    if (a.splits > 1 && !a.leave_ranges) {
+    if (a.splits > 1 && !a.leave_ranges && a.arrived == nullptr) {
         const int pairs = a.batch * a.heads;
         if (a.d == 128) hipLaunchKernelGGL(attn_decode_combine<128>, dim3((pairs + 1) / 2), dim3(256), 0, s, a);
         else hipLaunchKernelGGL(attn_decode_combine<64>, dim3((pairs + 3) / 4), dim3(256), 0, s, a);

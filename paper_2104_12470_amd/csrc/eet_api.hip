@@ -52,9 +52,9 @@ constexpr int kFfnPadFrom = 32768;
 // could not cut its second feed-forward projection at all (29 us -> 71 us), a prompt of 37 rows would take 50 us per layer
 // instead of 40.  Decode steps that run as one launch add two exchange sets (hidden 1024, 16 sequences of one row 0.36 -> 0.90).
 struct WorkspaceLayout {
-    size_t lens, cu, row_map, buf_f, cut, buf_a, buf_b, buf_y, part, step, row_stats, total;
+    size_t lens, cu, row_map, buf_f, cut, buf_a, buf_b, buf_y, part, arrived, step, row_stats, total;
     uint32_t step_set_words;           // of one exchange set of the decode steps that run as one launch (0: none do)
-    int splits;
+    int arrived_lines;                 // counters of decode attention that merges its own key ranges (0: none does)
 };
 
 const char* config_problem(const eet_layer_config* c) {
@@ -92,7 +92,6 @@ WorkspaceLayout layout_of(const eet_layer_config* c) {
     w.buf_a = off;   off = align_up(off + 2 * T * H, 256);
     w.buf_b = off;   off = align_up(off + 2 * T * H, 256);
     w.buf_y = off;   off = align_up(off + 2 * T * H, 256);
-    w.splits = attention_decode_splits(c->max_batch, c->heads, c->max_seq);
     w.part = off;
     // sized for the split count of any batch <= max_batch (fewer sequences -> more splits) that does not run as one launch
     size_t part = 0;
@@ -101,8 +100,16 @@ WorkspaceLayout layout_of(const eet_layer_config* c) {
         const size_t p = attention_decode_scratch_bytes(b, c->heads, H / c->heads,
                                                         attention_decode_splits(b, c->heads, c->max_seq));
         part = p > part ? p : part;
+        const int splits = attention_decode_splits(b, c->heads, c->max_seq, true);
+        if (splits > 1 && layernorm_clears(b, c->hidden, b * c->heads)) {
+            const size_t q = attention_decode_scratch_bytes(b, c->heads, H / c->heads, splits);
+            part = q > part ? q : part;
+            w.arrived_lines = b * c->heads;
+        }
     }
     off = align_up(off + part, 256);
+    w.arrived = off;
+    off = align_up(off + (size_t)w.arrived_lines * kClearStride * sizeof(uint32_t), 256);
     // the exchange area of those that do (decode_step.hip); no other step writes to it
     w.step = off;
     w.step_set_words = decode_step_set_words(c->max_batch, c->hidden, c->heads, c->ffn, c->max_seq);
@@ -442,10 +449,30 @@ static int enqueue_decode(eet_layer* L, const void* tokens, void* out, void* kv_
     const bool small = B <= 16 && (size_t)F * H * sizeof(half_t) <= ((size_t)16 << 20);
     const bool prefetch = small || (fuse_ln && regime != kInCache);
     auto lines = [](size_t bytes) { return (uint32_t)(bytes / 128); };
+    // output projection + bias + residual; its first workgroup also advances n_b: every reader of
+    // n_b in this step (cache append, attention) is already ordered before it on the stream
+    GemmArgs o{};
+    o.x = bufA; o.w = (const half_t*)L->w.w_o; o.bias = (const half_t*)L->w.b_o; o.y = bufY;
+    o.M = B; o.N = H; o.K = H; o.res = x; o.read_once = once;
+    o.heads = c.heads; o.d = L->d;
+    // The key range is split where the (sequence, head) pairs are few.  Where the output projection goes to the small-layer kernel, that kernel merges
+    // the ranges while it loads its activations; elsewhere the pair's last workgroup does, by counters that the first LayerNorm's launch clears, and
+    // a merge launch (4 us, the floor of a dependent launch) is left where that LayerNorm has none.
+    const int pairs = B * c.heads;
+    int splits = attention_decode_splits(B, c.heads, c.max_seq);
+    const bool merged_by_projection = splits > 1 && gemm_merges_attention_ranges(o);
+    ClearLines arrived{nullptr, 0};
+    if (!fuse_ln && !merged_by_projection && pairs <= L->lay.arrived_lines && layernorm_clears(B, H, pairs)) {
+        const int merging = attention_decode_splits(B, c.heads, c.max_seq, true);
+        if (merging > 1) {
+            splits = merging;
+            arrived = ClearLines{reinterpret_cast<uint32_t*>(L->ws + L->lay.arrived), pairs};
+        }
+    }
     const half_t* qkv_in = x;
     if (!fuse_ln) {
         EET_LAUNCH(launch_layernorm(x, nullptr, (const half_t*)L->w.ln1_g, (const half_t*)L->w.ln1_b, bufA, B, H,
-                                    c.ln_eps, nullptr, 0, s), "layernorm 1");
+                                    c.ln_eps, nullptr, 0, s, arrived), "layernorm 1");
         qkv_in = bufA;
     }
     GemmArgs g{};
@@ -458,19 +485,10 @@ static int enqueue_decode(eet_layer* L, const void* tokens, void* out, void* kv_
     AttnDecodeArgs at{};
     at.q = bufB; at.ctx = bufA; at.k_cache = kc; at.v_cache = vc; at.lens = d_lens; at.len_bias = 1;
     at.batch = B; at.heads = c.heads; at.d = L->d; at.capacity = c.max_seq; at.read_once = once; at.waves = waves;
-    at.splits = attention_decode_splits(B, c.heads, c.max_seq);
+    at.splits = splits; at.arrived = arrived.at;
     at.part_acc = reinterpret_cast<float*>(L->ws + L->lay.part);
     at.part_ml = at.part_acc + (size_t)B * c.heads * at.splits * L->d;
-    // output projection + bias + residual; its first workgroup also advances n_b: every reader of
-    // n_b in this step (cache append, attention) is already ordered before it on the stream
-    GemmArgs o{};
-    o.x = bufA; o.w = (const half_t*)L->w.w_o; o.bias = (const half_t*)L->w.b_o; o.y = bufY;
-    o.M = B; o.N = H; o.K = H; o.res = x; o.read_once = once;
-    o.heads = c.heads; o.d = L->d;
-    // With the key range split (few (sequence, head) pairs) the ranges need merging.  Where the output projection goes to
-    // the small-layer kernel, that kernel merges them while it loads its activations, and the merge launch (4 us, the
-    // floor of a dependent launch) is gone; otherwise attn_decode_combine runs.
-    if (at.splits > 1 && gemm_merges_attention_ranges(o)) {
+    if (merged_by_projection) {
         at.leave_ranges = 1;
         o.x_part_acc = at.part_acc; o.x_part_ml = at.part_ml; o.x_splits = at.splits;
     }

@@ -11,9 +11,16 @@ namespace eet {
 // LayerNorm of `rows` rows.  Row r is read from x[in_row_map ? in_row_map[r] : r] and written
 // to y[r].  If bump_lens != nullptr, the block of row r < bump_count also does bump_lens[r] += 1
 // (advances the per-sequence cache length after all readers of this step were enqueued).
+// Words that a launch sets to zero on the side, one to a 128-byte line (counters of a later launch); layernorm_clears says where it can
+constexpr int kClearStride = 32;
+struct ClearLines {
+    uint32_t* at;
+    int lines;
+};
+bool layernorm_clears(int64_t rows, int width, int lines);
 hipError_t launch_layernorm(const half_t* x, const int32_t* in_row_map, const half_t* gamma,
                             const half_t* beta, half_t* y, int64_t rows, int width, float eps,
-                            int32_t* bump_lens, int bump_count, hipStream_t s);
+                            int32_t* bump_lens, int bump_count, hipStream_t s, ClearLines clear = {nullptr, 0});
 hipError_t launch_bias_gelu(const half_t* x, const half_t* bias, half_t* y, int64_t rows, int width,
                             hipStream_t s);
 hipError_t launch_bias_residual(const half_t* x, const half_t* bias, const half_t* res, half_t* y,
@@ -183,13 +190,16 @@ struct AttnDecodeArgs {
     int splits;             // key-range splits per (sequence, head)
     float* part_acc;        // [batch*heads*splits, d]   (splits > 1)
     float* part_ml;         // [batch*heads*splits, 2]
+    uint32_t* arrived;      // splits > 1: a zeroed counter per pair, kClearStride apart: the pair's last workgroup merges its ranges, no merge launch (nullptr: there is one)
+    int least_keys;         // set by the launcher: 0, or the keys that make a range of a pair worth a workgroup
     int leave_ranges;       // 1: no merge launch, the projection that follows merges the ranges (GemmArgs::x_splits)
     int read_once;          // 1: K/V rows loaded with the non-temporal hint (see GemmArgs::read_once)
     int waves;              // of a workgroup: 8, or 4 (also 0: the caller does not know the lengths); see attention_decode_waves
 };
 // by the visible keys of the longest sequence and of all together
 int attention_decode_waves(int d, int heads, int batch, size_t longest, size_t visible);
-int attention_decode_splits(int batch, int heads, int capacity);
+// merges: with AttnDecodeArgs::arrived
+int attention_decode_splits(int batch, int heads, int capacity, bool merges = false);
 size_t attention_decode_scratch_bytes(int batch, int heads, int d, int splits);
 hipError_t launch_attention_decode(const AttnDecodeArgs& a, hipStream_t s);
 

@@ -25,7 +25,8 @@ __global__ __launch_bounds__(256) void layernorm_cached(const half_t* __restrict
                                                         const half_t* __restrict__ gamma,
                                                         const half_t* __restrict__ beta,
                                                         half_t* __restrict__ y, int width, float eps,
-                                                        int32_t* bump_lens, int bump_count) {
+                                                        int32_t* bump_lens, int bump_count, ClearLines clear) {
+    if (blockIdx.x == 0 && (int)threadIdx.x < clear.lines) clear.at[threadIdx.x * kClearStride] = 0u;
     __shared__ float red[4];
     const int64_t row = blockIdx.x;
     const int64_t src = in_row_map ? (int64_t)in_row_map[row] : row;
@@ -290,13 +291,18 @@ hipError_t launch_finish_rows(const GemmArgs& a, hipStream_t s) {
 
 static bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 
+// (rows and width of a layer's own activations: aligned)
+bool layernorm_clears(int64_t rows, int width, int lines) {
+    return lines <= 256 && width % 8 == 0 && width <= 16384 && (width > 2048 || rows < kLayerNormWaveRows);
+}
 hipError_t launch_layernorm(const half_t* x, const int32_t* in_row_map, const half_t* gamma,
                             const half_t* beta, half_t* y, int64_t rows, int width, float eps,
-                            int32_t* bump_lens, int bump_count, hipStream_t s) {
+                            int32_t* bump_lens, int bump_count, hipStream_t s, ClearLines clear) {
     if (rows <= 0) return hipSuccess;
+    if (clear.lines > 0 && !layernorm_clears(rows, width, clear.lines)) return hipErrorInvalidValue;
     const dim3 grid((unsigned)rows), block(256);
     const bool vec = (width % 8 == 0) && aligned16(x) && aligned16(y) && aligned16(gamma) && aligned16(beta);
-#define EET_LN_AT(NV, EARLY) hipLaunchKernelGGL((layernorm_cached<NV, EARLY>), grid, block, 0, s, x, in_row_map, gamma, beta, y, width, eps, bump_lens, bump_count)
+#define EET_LN_AT(NV, EARLY) hipLaunchKernelGGL((layernorm_cached<NV, EARLY>), grid, block, 0, s, x, in_row_map, gamma, beta, y, width, eps, bump_lens, bump_count, clear)
 #define EET_LN(NV) do { if (rows <= 4096) EET_LN_AT(NV, true); else EET_LN_AT(NV, false); } while (0)
 #define EET_LNW(NV) hipLaunchKernelGGL(layernorm_wave<NV>, dim3((unsigned)((rows + 3) / 4)), block, 0, s, x, in_row_map, gamma, beta, y, (int)rows, width, eps, bump_lens, bump_count)
     if (vec && width <= 2048 && rows >= kLayerNormWaveRows) { // a prompt's rows: one wave each
