@@ -1062,8 +1062,8 @@ hipError_t launch_attention_apply(const AttnPrefillArgs& a, const SeqLens& lens,
 // the end.  The padding offset is the loop bound: slots >= n_b are never used (the tail of the
 // last block re-reads the last valid row with weight zero).
 //
-// With more than one range per (sequence, head) each workgroup writes a partial (max, sum,
-// values) and attn_decode_combine merges them.
+// With more than one range per (sequence, head) each workgroup writes a partial (max, sum, values), and the last of the pair merges them
+// (AttnDecodeArgs::arrived), or the projection that follows, or attn_decode_combine.
 template <int CTRL>
 __device__ __forceinline__ float dpp_f(float x) {
     return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), CTRL, 0xf, 0xf, false));
