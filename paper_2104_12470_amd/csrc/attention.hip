@@ -437,7 +437,8 @@ __global__ __launch_bounds__(512) void attn_prefill_wide(AttnPrefillArgs a, SeqL
     for (int db = 0; db < DB; ++db)
 #pragma unroll
         for (int r = 0; r < 16; ++r) o[db][r] = 0.f;
-    float m = -INFINITY, l = 0.f, alpha = 1.f;
+    // (KG = 2: finite, so that a group whose first keys all score -inf has the weights 0 for them and not -inf minus -inf; the other group may see finite ones)
+    float m = KG == 2 ? -1e30f : -INFINITY, l = 0.f, alpha = 1.f;
     bool rescale = false;
     constexpr float kSlack = 8.0f;
     const float c = rsqrtf((float)D) * kLog2e;
@@ -618,7 +619,7 @@ __global__ __launch_bounds__(512) void attn_prefill_wide(AttnPrefillArgs a, SeqL
         }
         __syncthreads();
         if (kg == 1) return;
-        const float2v ml = *part_ml;                      // a group that saw no key: reference -inf, sum and values zero
+        const float2v ml = *part_ml;                      // a group that saw no key: lowest reference, sum and values zero
         const float m_new = fmaxf(m, ml[0]), mine = __builtin_amdgcn_exp2f(m - m_new), theirs = __builtin_amdgcn_exp2f(ml[0] - m_new);
         l = l * mine + ml[1] * theirs;
 #pragma unroll

@@ -42,3 +42,18 @@ def test_against_the_oracle(heads, lens, causal):
     for b, n in enumerate(lens):
         gate(got[b, :n], want[b, :n], f"sequence {b} of {n}", 6e-3, 6e-4)
         assert np.all(got[b, n:] == 7.0)
+
+
+def test_a_group_whose_first_keys_score_minus_infinity():
+    """Keys 32 to 63 of -inf, all that the upper group sees in its first tile, have weight zero and leave the others' as they are."""
+    from paper_2104_12470_amd import eet
+    d, n = 128, 600
+    q, k, v = (wl.normal(701, t, (1, n, 1, d)) for t in (1, 2, 3))
+    q = np.abs(q) + np.float16(0.01)
+    k[:, 32:64] = -np.inf
+    want = orc.attention_prefill(q, k, v, [n], causal=True)
+    assert np.isfinite(want[0, :32]).all() and np.isfinite(want[0, 64:]).all()
+    ctx = torch.zeros((1, n, d), dtype=torch.float16, device="cuda:0")
+    eet.eet_op_attention_prefill(dev(q.reshape(1, n, d)), dev(k.transpose(0, 2, 1, 3).copy()), dev(v.transpose(0, 2, 1, 3).copy()), ctx, [n], 1)
+    torch.cuda.synchronize()
+    gate(host(ctx).reshape(n, 1, d), want[0], "with keys of -inf", 6e-3, 6e-4)
