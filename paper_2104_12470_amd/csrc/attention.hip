@@ -1300,18 +1300,6 @@ int attention_decode_splits(int batch, int heads, int capacity, bool merges) {
     return s > 64 ? 64 : s;
 }
 
-// Sequences of uneven lengths on more pairs than CUs: the launch ends with the longest, which a CU streams no faster than four waves ask for
-// them, while others have run out.  Eight waves ask for twice as much.  us, four / eight waves, heads of 128: 320 pairs, 100 to 1500 keys 34.8 / 27.8, 100
-// to 700 18.9 / 16.5, 1000 to 1500 42.2 / 40.5; 640, 100 to 1000 37.8 / 31.1; 1536, 100 to 1500 102 / 97; 3072, 100 to 1000 134 / 130.  Not for even lengths (640
-// pairs, 1000 keys 53.3 / 54.7; 1536, 1800 to 2000 219.7 / 218.9), short ones (768, 50 to 200 11.8 / 13.9), nor up to 256 pairs, where a CU has at most one (100 to 1500
-// 21.8 / 22.3).  Heads of 64 have half the bytes per key: 320 pairs, 100 to 1500 19.3 / 16.6; 384 20.5 / 18.7; but 512 22.5 / 22.9, 500 to 1000 on 320
-// 15.7 / 16.3, 1536, 100 to 1000 37.8 / 39.0.
-int attention_decode_waves(int d, int heads, int batch, size_t longest, size_t visible) {
-    const size_t pairs = (size_t)heads * batch;
-    if (pairs <= 256 || longest < 700) return 4;
-    return d == 128 ? (longest * batch * 20 >= visible * 23 ? 8 : 4) : (pairs < 512 && longest * batch * 10 >= visible * 14 ? 8 : 4);
-}
-
 size_t attention_decode_scratch_bytes(int batch, int heads, int d, int splits) {
     if (splits <= 1) return 0;
     return (size_t)batch * heads * splits * (d + 2) * sizeof(float);
@@ -1320,12 +1308,14 @@ size_t attention_decode_scratch_bytes(int batch, int heads, int d, int splits) {
 hipError_t launch_attention_decode(const AttnDecodeArgs& args, hipStream_t s) {
     AttnDecodeArgs a = args;
     a.least_keys = a.arrived != nullptr && a.batch * a.heads == 128 ? kLeastKeys : 0;
-    const dim3 grid(a.splits, a.heads, a.batch);
-#define EET_DECODE(D, NW) do { if (a.read_once) hipLaunchKernelGGL((attn_decode<D, NW, true>), grid, dim3(64 * NW), 0, s, a); \
-                               else hipLaunchKernelGGL((attn_decode<D, NW, false>), grid, dim3(64 * NW), 0, s, a); } while (0)
-    if (a.d == 128) { if (a.waves == 8) EET_DECODE(128, 8); else EET_DECODE(128, 4); }
-    else { if (a.waves == 8) EET_DECODE(64, 8); else EET_DECODE(64, 4); }
-#undef EET_DECODE
+    const dim3 grid(a.splits, a.heads, a.batch), block(256);
+    if (a.d == 128) {
+        if (a.read_once) hipLaunchKernelGGL((attn_decode<128, 4, true>), grid, block, 0, s, a);
+        else hipLaunchKernelGGL((attn_decode<128, 4, false>), grid, block, 0, s, a);
+    } else {
+        if (a.read_once) hipLaunchKernelGGL((attn_decode<64, 4, true>), grid, block, 0, s, a);
+        else hipLaunchKernelGGL((attn_decode<64, 4, false>), grid, block, 0, s, a);
+    }
     if (a.splits > 1 && !a.leave_ranges && a.arrived == nullptr) {
         const int pairs = a.batch * a.heads;
         if (a.d == 128) hipLaunchKernelGGL(attn_decode_combine<128>, dim3((pairs + 1) / 2), dim3(256), 0, s, a);

@@ -383,25 +383,9 @@ static StepRegime step_regime(const eet_layer* L, const int32_t* cached) {
     return (size_t)(L->stack_layers > 0 ? L->stack_layers : 1) * (2 * (4 * H * H + 2 * H * F) + 4 * H * visible) > kMemorySideCacheBytes ? kExceedsCache : kInCache;
 }
 
-static bool decodes_in_one_launch(const eet_layer* L, StepRegime regime) {
-    return regime != kLongKeys && decode_step_fits(L->batch, L->cfg.hidden, L->cfg.heads, L->cfg.ffn);
-}
-
-// Waves per workgroup of the attention of such a step, where it has a launch of its own
-static int step_attention_waves(const eet_layer* L, const int32_t* cached, StepRegime regime) {
-    if (decodes_in_one_launch(L, regime)) return 4;
-    size_t visible = 0, longest = 0;
-    for (int b = 0; b < L->batch; ++b) {
-        const size_t n = (size_t)cached[b] + 1;
-        visible += n;
-        longest = n > longest ? n : longest;
-    }
-    return attention_decode_waves(L->d, L->cfg.heads, L->batch, longest, visible);
-}
-
 // Enqueue the kernels of one layer's decode step (arguments already validated).  `bump`: this
 // layer advances the device-side cache lengths (in a stack only the last layer does).
-static int enqueue_decode(eet_layer* L, const void* tokens, void* out, void* kv_cache, hipStream_t s, bool bump, StepRegime regime, int waves,
+static int enqueue_decode(eet_layer* L, const void* tokens, void* out, void* kv_cache, hipStream_t s, bool bump, StepRegime regime,
                           const eet_layer* next = nullptr, const void* next_kv = nullptr) {
     const eet_layer_config& c = L->cfg;
     const int B = L->batch, H = c.hidden, F = c.ffn;
@@ -484,7 +468,7 @@ static int enqueue_decode(eet_layer* L, const void* tokens, void* out, void* kv_
     EET_LAUNCH(launch_gemm(g, EPI_QKV, s), "qkv projection");
     AttnDecodeArgs at{};
     at.q = bufB; at.ctx = bufA; at.k_cache = kc; at.v_cache = vc; at.lens = d_lens; at.len_bias = 1;
-    at.batch = B; at.heads = c.heads; at.d = L->d; at.capacity = c.max_seq; at.read_once = once; at.waves = waves;
+    at.batch = B; at.heads = c.heads; at.d = L->d; at.capacity = c.max_seq; at.read_once = once;
     at.splits = splits; at.arrived = arrived.at;
     at.part_acc = reinterpret_cast<float*>(L->ws + L->lay.part);
     at.part_ml = at.part_acc + (size_t)B * c.heads * at.splits * L->d;
@@ -554,6 +538,10 @@ static int enqueue_decode(eet_layer* L, const void* tokens, void* out, void* kv_
     return EET_OK;
 }
 
+static bool decodes_in_one_launch(const eet_layer* L, StepRegime regime) {
+    return regime != kLongKeys && decode_step_fits(L->batch, L->cfg.hidden, L->cfg.heads, L->cfg.ffn);
+}
+
 // A decode step through `n` layers of one configuration that share a workspace, as one launch per kStepLayers of them.  The last
 // layer's launch advances the lengths.  act: where a launch leaves its output for the next (two buffers, alternating).
 static int enqueue_decode_layers(eet_layer* const* layers, int n, const void* tokens, void* out, void* kv_cache, size_t layer_cache_bytes,
@@ -601,7 +589,7 @@ int eet_decode_step(eet_layer_t* L, const void* tokens, void* out, void* kv_cach
     hipStream_t s = static_cast<hipStream_t>(hip_stream);
     const StepRegime regime = step_regime(L, L->host_lens);
     const int rc = decodes_in_one_launch(L, regime) ? enqueue_decode_layers(&L, 1, tokens, out, kv_cache, 0, nullptr, s, regime)
-                                            : enqueue_decode(L, tokens, out, kv_cache, s, true, regime, step_attention_waves(L, L->host_lens, regime), L, kv_cache);
+                                            : enqueue_decode(L, tokens, out, kv_cache, s, true, regime, L, kv_cache);
     if (rc != EET_OK) return rc;
     for (int b = 0; b < B; ++b) L->host_lens[b] += 1;
     return EET_OK;
@@ -661,8 +649,8 @@ struct eet_stack {
     int batch;
     int32_t host_lens[EET_MAX_BATCH];
     int use_graph;
-    hipGraphExec_t exec[2 * kStepRegimes]; // captured decode steps, valid for (g_tokens, g_out, g_kv, g_batch), by regime and attention waves: the lengths grow
-                                       // past each line between them once, and a new prefill or restore goes back
+    hipGraphExec_t exec[kStepRegimes]; // captured decode steps, valid for (g_tokens, g_out, g_kv, g_batch): the lengths grow past each line
+                                       // between the regimes once, and a new prefill or restore goes back
     const void* g_tokens;
     void* g_out;
     void* g_kv;
@@ -797,7 +785,7 @@ int eet_stack_encode(eet_stack_t* st, const int32_t* q_lens, int32_t batch, int3
     return EET_OK;
 }
 
-static int stack_enqueue_decode(eet_stack* st, const void* tokens, void* out, void* kv_cache, hipStream_t s, StepRegime regime, int waves) {
+static int stack_enqueue_decode(eet_stack* st, const void* tokens, void* out, void* kv_cache, hipStream_t s, StepRegime regime) {
     if (decodes_in_one_launch(st->layers[0], regime)) {
         void* act[2] = {st->ws + st->act[0], st->ws + st->act[1]};
         return enqueue_decode_layers(st->layers, st->n_layers, tokens, out, kv_cache, st->layer_cache_bytes, act, s, regime);
@@ -808,7 +796,7 @@ static int stack_enqueue_decode(eet_stack* st, const void* tokens, void* out, vo
         void* o = last ? out : static_cast<void*>(st->ws + st->act[l & 1]);
         char* kv = static_cast<char*>(kv_cache) + (size_t)l * st->layer_cache_bytes;
         const int ln = last ? 0 : l + 1;                                    // the step that follows this layer's
-        const int rc = enqueue_decode(st->layers[l], in, o, kv, s, last, regime, waves,    // lengths shared: advanced once, at the end
+        const int rc = enqueue_decode(st->layers[l], in, o, kv, s, last, regime,    // lengths shared: advanced once, at the end
                                       st->layers[ln], static_cast<char*>(kv_cache) + (size_t)ln * st->layer_cache_bytes);
         if (rc != EET_OK) return rc;
         in = o;
@@ -827,7 +815,6 @@ int eet_stack_decode_step(eet_stack_t* st, const void* tokens, void* out, void* 
             return fail(EET_ERR_CAPACITY, "eet_stack_decode_step: sequence %d is at the cache capacity %d", b, st->cfg.max_seq);
     hipStream_t s = static_cast<hipStream_t>(hip_stream);
     const StepRegime regime = step_regime(st->layers[0], st->host_lens);
-    const int waves = step_attention_waves(st->layers[0], st->host_lens, regime);
     // A step has no other host-varying argument (the cache lengths live on the device), so its launches
     // can be recorded once and replayed.  Not on the null stream (it cannot be captured) and not
     // while the caller is capturing this stream itself (then the launches join the caller's graph).
@@ -837,14 +824,14 @@ int eet_stack_decode_step(eet_stack_t* st, const void* tokens, void* out, void* 
         if (hipStreamIsCapturing(s, &cs) != hipSuccess || cs != hipStreamCaptureStatusNone) graph = false;
     }
     if (!graph) {
-        if (const int rc = stack_enqueue_decode(st, tokens, out, kv_cache, s, regime, waves)) return rc;
+        if (const int rc = stack_enqueue_decode(st, tokens, out, kv_cache, s, regime)) return rc;
     } else {
         if (st->g_tokens != tokens || st->g_out != out || st->g_kv != kv_cache || st->g_batch != B) drop_graphs(st);
-        hipGraphExec_t& exec = st->exec[waves == 8 ? kStepRegimes + regime : regime];
+        hipGraphExec_t& exec = st->exec[regime];
         if (!exec) {
             hipGraph_t g = nullptr;
             EET_LAUNCH(hipStreamBeginCapture(s, hipStreamCaptureModeThreadLocal), "begin capture");
-            const int rc = stack_enqueue_decode(st, tokens, out, kv_cache, s, regime, waves);
+            const int rc = stack_enqueue_decode(st, tokens, out, kv_cache, s, regime);
             const hipError_t e = hipStreamEndCapture(s, &g);
             if (rc != EET_OK) {
                 if (g) (void)hipGraphDestroy(g);

@@ -194,10 +194,7 @@ struct AttnDecodeArgs {
     int least_keys;         // set by the launcher: 0, or the keys that make a range of a pair worth a workgroup
     int leave_ranges;       // 1: no merge launch, the projection that follows merges the ranges (GemmArgs::x_splits)
     int read_once;          // 1: K/V rows loaded with the non-temporal hint (see GemmArgs::read_once)
-    int waves;              // of a workgroup: 8, or 4 (also 0: the caller does not know the lengths); see attention_decode_waves
 };
-// by the visible keys of the longest sequence and of all together
-int attention_decode_waves(int d, int heads, int batch, size_t longest, size_t visible);
 // merges: with AttnDecodeArgs::arrived
 int attention_decode_splits(int batch, int heads, int capacity, bool merges = false);
 size_t attention_decode_scratch_bytes(int batch, int heads, int d, int splits);

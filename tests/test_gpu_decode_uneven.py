@@ -1,12 +1,12 @@
-"""Decode attention of uneven sequences on more (sequence, head) pairs than CUs: eight waves per workgroup instead of four, on either side of every line
-of the rule, in a layer's step and in a stack's recorded one, which keeps a recording for either side.  All of it against the oracle."""
+"""Decode attention of uneven and even sequences on more (sequence, head) pairs than CUs, in a layer's step and in a stack's recorded one.  All of it
+against the oracle."""
 import numpy as np
 import pytest
 import torch
 
 from oracle import eet_oracle as orc
 from paper_2104_12470_amd import workloads as wl
-from tests.gpu_util import dev, gate, host, kernels_of
+from tests.gpu_util import dev, gate, host
 
 pytestmark = pytest.mark.gpu
 
@@ -36,16 +36,15 @@ def set_oracle(oracle, lens, rows):
     oracle.k_cache[:], oracle.v_cache[:] = rows[0], rows[1]
 
 
-@pytest.mark.parametrize("heads,d,lens,waves", [
-    (4, 128, uneven(65, 1, 699), 8),                 # 260 pairs; the longest has 700 keys with the new token
-    (4, 128, uneven(65, 1, 698), 4),
-    (4, 128, uneven(64, 1, 720), 4),                 # 256 pairs
-    (4, 128, [720] * 65, 4),                         # even
-    (5, 64, uneven(52, 1, 800), 8),                  # 260 pairs
-    (8, 64, uneven(64, 1, 800), 4),                  # 512: too many of heads of 64
-    (5, 64, uneven(52, 500, 800), 4),
+@pytest.mark.parametrize("heads,d,lens", [
+    (4, 128, uneven(65, 1, 699)),                    # 260 pairs
+    (4, 128, uneven(64, 1, 720)),                    # 256
+    (4, 128, [720] * 65),                            # even
+    (5, 64, uneven(52, 1, 800)),
+    (8, 64, uneven(64, 1, 800)),                     # 512
+    (5, 64, uneven(52, 500, 800)),
 ])
-def test_step_against_the_oracle(heads, d, lens, waves):
+def test_step_against_the_oracle(heads, d, lens):
     eet, max_seq = eet_module(), max(lens) + 8
     rows = wl.normal(67, 9, (2, len(lens), heads, max_seq, d))
     for b, n in enumerate(lens):
@@ -59,14 +58,12 @@ def test_step_against_the_oracle(heads, d, lens, waves):
         xs = wl.decode_embeddings(w, k)
         tok = dev(xs)
         got = torch.empty_like(tok)
-        names = kernels_of(lambda: layer.decode_step(tok, got))
-        if k == 0:
-            assert any(f"attn_decode<{d}, {waves}" in n for n in names), names
+        layer.decode_step(tok, got)
         gate(host(got), oracle.decode_step(xs), f"step {k}")
     layer.close()
 
 
-def test_recorded_steps_on_both_sides():
+def test_recorded_steps_at_other_lengths():
     """A stack's recorded steps: uneven, then even sequences after a restore, then uneven ones again, each as the direct steps bit for bit."""
     eet, heads, d, batch, max_seq = eet_module(), 4, 128, 65, 760
     rows = wl.normal(67, 9, (2, batch, heads, max_seq, d))
@@ -77,17 +74,16 @@ def test_recorded_steps_on_both_sides():
     stream = torch.cuda.Stream()
     torch.cuda.synchronize()
     with torch.cuda.stream(stream):
-        for lens, waves in ((uneven(batch, 1, 720), 8), ([700] * batch, 4), (uneven(batch, 1, 730), 8)):
+        for lens in (uneven(batch, 1, 720), [700] * batch, uneven(batch, 1, 730)):
             for st in (direct, graph):
                 st.kv_cache.copy_(dev(rows).view(-1))
                 eet.eet_stack_restore(st.handle, lens)
             set_oracle(oracle, lens, rows)
             for k in range(2):
-                names = kernels_of(lambda: direct.decode_step(tok, out[0]))
-                assert any(f"attn_decode<{d}, {waves}" in n for n in names), names
+                direct.decode_step(tok, out[0])
                 graph.decode_step(tok, out[1])
                 stream.synchronize()
-                gate(host(out[0]), oracle.decode_step(wl.decode_embeddings(w, 0)), f"{waves} waves, step {k}")
+                gate(host(out[0]), oracle.decode_step(wl.decode_embeddings(w, 0)), f"{lens[:3]}, step {k}")
                 assert np.array_equal(host(out[0]).view(np.uint16), host(out[1]).view(np.uint16))
     direct.close()
     graph.close()
