@@ -1120,12 +1120,7 @@ __global__ __launch_bounds__(NW * 64) void attn_decode(AttnDecodeArgs a) {
     const int kslot = lane / LPK, chunk = lane % LPK;
     int n = a.lens[b] + a.len_bias;                      // visible keys
     n = n < 0 ? 0 : (n > a.capacity ? a.capacity : n);   // whatever the device-side length says, never outside the pair's slots
-    int splits = a.splits;
-    if (a.least_keys > 0) {                              // a pair of few keys is one range, and its other workgroups have nothing to do
-        const int most = n / a.least_keys;
-        splits = most < 1 ? 1 : most < splits ? most : splits;
-        if (sp >= splits) return;
-    }
+    const int splits = a.splits;
     int per = (n + splits - 1) / splits;
     per = (per + 15) & ~15;
     const int c0 = sp * per;
@@ -1285,15 +1280,12 @@ __global__ __launch_bounds__(256) void attn_decode_combine(AttnDecodeArgs a) {
     a.ctx[bh * D + dd] = merge_ranges<D, false>(a.part_ml + bh * a.splits * 2, a.part_acc + bh * a.splits * D + dd, a.splits);
 }
 
-constexpr int kLeastKeys = 384;
-int attention_decode_splits(int batch, int heads, int capacity, bool merges) {
+int attention_decode_splits(int batch, int heads, int capacity) {
     // One key range per (sequence, head) once there are 128 pairs (measured: as fast as splitting,
-    // and no merge launch).  Below that, about 256 workgroups, a power of two, and no range shorter
-    // than 128 keys at full capacity.  Where the ranges are merged by the kernel itself 128 pairs, half of the CUs, are two ranges each, of
-    // kLeastKeys and more (4 sequences of 32 heads of 128, hidden 4096, us per step: 512 to 1279 keys 93.3 -> 91.3, 2000 to 4000 121.7 -> 113.3; two ranges
-    // of 200 keys 84.7 -> 85.5); more pairs are not: 192 of heads of 64 237.8 -> 244.3, 180 266 -> 276, 224 97.9 -> 99.8.
+    // and no merge).  Below that, about 256 workgroups, a power of two, and no range shorter
+    // than 128 keys at full capacity.
     const int pairs = batch * heads;
-    if (pairs >= 128) return merges && pairs == 128 && capacity >= 2 * kLeastKeys ? 2 : 1;
+    if (pairs >= 128) return 1;
     int s = 1;
     while (s * pairs < 256) s *= 2;
     while (s > 1 && capacity / s < 128) s /= 2;
@@ -1305,9 +1297,7 @@ size_t attention_decode_scratch_bytes(int batch, int heads, int d, int splits) {
     return (size_t)batch * heads * splits * (d + 2) * sizeof(float);
 }
 
-hipError_t launch_attention_decode(const AttnDecodeArgs& args, hipStream_t s) {
-    AttnDecodeArgs a = args;
-    a.least_keys = a.arrived != nullptr && a.batch * a.heads == 128 ? kLeastKeys : 0;
+hipError_t launch_attention_decode(const AttnDecodeArgs& a, hipStream_t s) {
     const dim3 grid(a.splits, a.heads, a.batch), block(256);
     if (a.d == 128) {
         if (a.read_once) hipLaunchKernelGGL((attn_decode<128, 4, true>), grid, block, 0, s, a);

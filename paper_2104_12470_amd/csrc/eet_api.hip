@@ -97,15 +97,10 @@ WorkspaceLayout layout_of(const eet_layer_config* c) {
     size_t part = 0;
     for (int b = 1; b <= c->max_batch; ++b) {
         if (decode_step_fits(b, c->hidden, c->heads, c->ffn) && decode_step_fits_keys(b, c->heads, (int)H / c->heads, (size_t)b * c->max_seq)) continue;
-        const size_t p = attention_decode_scratch_bytes(b, c->heads, H / c->heads,
-                                                        attention_decode_splits(b, c->heads, c->max_seq));
+        const int splits = attention_decode_splits(b, c->heads, c->max_seq);
+        const size_t p = attention_decode_scratch_bytes(b, c->heads, H / c->heads, splits);
         part = p > part ? p : part;
-        const int splits = attention_decode_splits(b, c->heads, c->max_seq, true);
-        if (splits > 1 && layernorm_clears(b, c->hidden, b * c->heads)) {
-            const size_t q = attention_decode_scratch_bytes(b, c->heads, H / c->heads, splits);
-            part = q > part ? q : part;
-            w.arrived_lines = b * c->heads;
-        }
+        if (splits > 1 && layernorm_clears(b, c->hidden, b * c->heads)) w.arrived_lines = b * c->heads;
     }
     off = align_up(off + part, 256);
     w.arrived = off;
@@ -443,16 +438,11 @@ static int enqueue_decode(eet_layer* L, const void* tokens, void* out, void* kv_
     // the ranges while it loads its activations; elsewhere the pair's last workgroup does, by counters that the first LayerNorm's launch clears, and
     // a merge launch (4 us, the floor of a dependent launch) is left where that LayerNorm has none.
     const int pairs = B * c.heads;
-    int splits = attention_decode_splits(B, c.heads, c.max_seq);
+    const int splits = attention_decode_splits(B, c.heads, c.max_seq);
     const bool merged_by_projection = splits > 1 && gemm_merges_attention_ranges(o);
     ClearLines arrived{nullptr, 0};
-    if (!fuse_ln && !merged_by_projection && pairs <= L->lay.arrived_lines && layernorm_clears(B, H, pairs)) {
-        const int merging = attention_decode_splits(B, c.heads, c.max_seq, true);
-        if (merging > 1) {
-            splits = merging;
-            arrived = ClearLines{reinterpret_cast<uint32_t*>(L->ws + L->lay.arrived), pairs};
-        }
-    }
+    if (splits > 1 && !fuse_ln && !merged_by_projection && pairs <= L->lay.arrived_lines && layernorm_clears(B, H, pairs))
+        arrived = ClearLines{reinterpret_cast<uint32_t*>(L->ws + L->lay.arrived), pairs};
     const half_t* qkv_in = x;
     if (!fuse_ln) {
         EET_LAUNCH(launch_layernorm(x, nullptr, (const half_t*)L->w.ln1_g, (const half_t*)L->w.ln1_b, bufA, B, H,

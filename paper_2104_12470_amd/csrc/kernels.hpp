@@ -191,12 +191,10 @@ struct AttnDecodeArgs {
     float* part_acc;        // [batch*heads*splits, d]   (splits > 1)
     float* part_ml;         // [batch*heads*splits, 2]
     uint32_t* arrived;      // splits > 1: a zeroed counter per pair, kClearStride apart: the pair's last workgroup merges its ranges, no merge launch (nullptr: there is one)
-    int least_keys;         // set by the launcher: 0, or the keys that make a range of a pair worth a workgroup
     int leave_ranges;       // 1: no merge launch, the projection that follows merges the ranges (GemmArgs::x_splits)
     int read_once;          // 1: K/V rows loaded with the non-temporal hint (see GemmArgs::read_once)
 };
-// merges: with AttnDecodeArgs::arrived
-int attention_decode_splits(int batch, int heads, int capacity, bool merges = false);
+int attention_decode_splits(int batch, int heads, int capacity);
 size_t attention_decode_scratch_bytes(int batch, int heads, int d, int splits);
 hipError_t launch_attention_decode(const AttnDecodeArgs& a, hipStream_t s);
 

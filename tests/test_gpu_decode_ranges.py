@@ -1,6 +1,5 @@
 """Decode attention whose key ranges are merged by the last workgroup of each (sequence, head) pair to finish: layers too large for a step in one launch
-and for the small-layer output projection.  Fewer than 128 pairs, 128 (where short sequences stay one range, on either side of the line) and more (one range);
-an empty last range; step after step on the same counters, and in a stack's recorded step."""
+and for the small-layer output projection.  Fewer than 128 pairs, 128 and more (one range); an empty last range; step after step on the same counters, and in a stack's recorded step."""
 import numpy as np
 import pytest
 import torch
@@ -31,7 +30,7 @@ def setup(heads, d, lens, max_seq):
     (17, 128, [17], 2100),                           # sixteen, most of them empty
     (18, 128, [700, 1, 350], 720),                   # 54 pairs
     (36, 64, [500, 600], 640),                       # heads of 64
-    (64, 64, [766, 767], 800),                       # 128 pairs: one range, and two from the line on
+    (64, 64, [766, 767], 800),                       # 128 pairs: one range
     (32, 128, [767, 900, 30, 1279], 1300),
     (32, 128, [767, 900, 30, 200, 500], 920),        # 160: one range
 ])

@@ -49,7 +49,10 @@ def operator(eet, q, kv, lens, max_seq):
     (17, 128, [17], 2100),                           # sixteen, most of them empty
     (18, 128, [700, 1, 350], 720),                   # 54 pairs, four ranges
     (36, 64, [500, 600], 640),                       # heads of 64
-    (32, 128, uneven(5, 1, 900), 910),               # 160 pairs: one range
+    (31, 128, [767, 900, 30, 1279], 1300),           # 124, four ranges
+    (64, 64, [766, 767], 800),                       # 128 pairs and more: one range
+    (32, 128, [767, 900, 30, 1279], 1300),
+    (32, 128, uneven(5, 1, 900), 910),
     (4, 128, uneven(65, 1, 720), 730),               # 260, uneven
     (5, 64, uneven(52, 1, 800), 810),
     (4, 128, [720] * 65, 730),                       # even
