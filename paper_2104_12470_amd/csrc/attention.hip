@@ -30,11 +30,9 @@ constexpr float kLog2e = 1.4426950408889634f;
 // CAUSAL = false is the encoder's window (Section 4, Bert layer): padding skip only, no sequence
 // mask; every query tile then walks all key tiles of its sequence and only the last tile compares
 // key indices (against L_b).
-// The (sequence, head) pairs and their query tiles over the workgroups of a prefill launch: the tiles of a pair on one
-// XCD (workgroups are dealt round-robin to the 8 XCDs; the chunk size is a multiple of 8), whose L2 then holds its K/V,
-// and within a chunk of pairs the longest tiles of all its pairs first, then the next longest ... (the best balance).
-// The work of one of the extra workgroups: one word of its share of the lines (pipe::ahead_line).  They come last in the grid, so they fill
-// what a launch of one round leaves of the CUs, and the tail of one of several.  Ordinary loads, kept by an empty use of their xor as in
+
+// The work of one of the extra workgroups that touch weights: one word of each of its lines (pipe::ahead_line).  They come last in the grid, so they
+// fill what a launch of one round leaves of the CUs, and the tail of one of several.  Ordinary loads, kept by an empty use of their xor as in
 // run_prefetch.
 __device__ __forceinline__ void touch_weights(const WeightsAhead& w, uint32_t part, uint32_t tid, uint32_t nthreads) {
     int acc = 0;
@@ -55,21 +53,23 @@ __device__ __forceinline__ void touch_weights(const WeightsAhead& w, uint32_t pa
     asm volatile("" ::"v"(acc));
 }
 
-// The pairs come in chunks of chunk_pairs, so that the K/V of the pairs in flight stays in the memory-side cache from one tile of a
-// pair to its next.  false: a pad workgroup of the last chunk, or one of the last a.ahead.blocks, which do nothing but touch weights.
+// This workgroup's query tile (pipe::prefill_tile has the order).  false: it has none, as a pad workgroup of the last chunk or, AHEAD, one of those that
+// touch weights.  (Kernels of their own for AHEAD, and no division without chunks: with both in every launch a short call of the operators took 3 to 4 %
+// more, and attn_prefill16<64, true, 8> 86 registers, five waves per SIMD instead of six: 63 heads of 17 prompts of 43 tokens 8.1 us, 9.3 so.)
+template <bool AHEAD>
 __device__ __forceinline__ bool prefill_pair_and_tile(const AttnPrefillArgs& a, int& pair, int& tile) {
-    if ((int)blockIdx.x >= a.tile_blocks) {
-        touch_weights(a.ahead, blockIdx.x - (uint32_t)a.tile_blocks, threadIdx.x, blockDim.x);
+    int past;
+    pipe::prefill_tile(blockIdx.x, blockIdx.y, gridDim.x, a.chunk_pairs, a.chunk_tiles, a.tile_blocks, pair, tile, past);
+    if (AHEAD && past >= 0) {
+        if (past < a.ahead.blocks) touch_weights(a.ahead, past, threadIdx.x, blockDim.x);
         return false;
     }
-    const int per = a.chunk_pairs * a.chunk_tiles, c = blockIdx.x / per, r = blockIdx.x - c * per;
-    pair = c * a.chunk_pairs + r % a.chunk_pairs;
-    tile = a.chunk_tiles - 1 - r / a.chunk_pairs;
     return pair < a.batch * a.heads;
 }
 
-template <bool CAUSAL>
-__global__ __launch_bounds__(256, 2) void attn_prefill(AttnPrefillArgs a, SeqLens lens) {
+// (causal: 128 registers, four workgroups per CU; with AHEAD the compiler would take 145)
+template <bool CAUSAL, bool AHEAD>
+__global__ __launch_bounds__(256, CAUSAL && AHEAD ? 4 : 2) void attn_prefill(AttnPrefillArgs a, SeqLens lens) {
     constexpr int D = 64, BQ = 128, BKV = 64;
     constexpr int LDKS = D + 8;         // K tile row stride (halfs): 16-byte reads conflict-free
     constexpr int LDVT = BKV + 4;       // V^T tile row stride: 34 dwords, so the 8-byte reads of 32 rows cover all 64 banks once
@@ -80,7 +80,7 @@ __global__ __launch_bounds__(256, 2) void attn_prefill(AttnPrefillArgs a, SeqLen
     __shared__ __attribute__((aligned(16))) half_t Vt[D * LDVT];
 
     int pair, tile;
-    if (!prefill_pair_and_tile(a, pair, tile)) return;
+    if (!prefill_pair_and_tile<AHEAD>(a, pair, tile)) return;
     const int b = pair / a.heads, g = pair % a.heads;
     const int L = lens.len[b];
     const int i0 = tile * BQ;
@@ -337,7 +337,7 @@ struct AttnRingExec {
 };
 
 // KG = 2: 128 query rows, and two groups of four waves that take the lower and the upper 32 keys of every tile and merge at the end.
-template <int D, bool CAUSAL, int KG>
+template <int D, bool CAUSAL, int KG, bool AHEAD>
 __global__ __launch_bounds__(512) void attn_prefill_wide(AttnPrefillArgs a, SeqLens lens) {
     constexpr int WQ = 32, BKV = 64, NWAVE = 8, BQ = WQ * NWAVE / KG;
     constexpr int ROWB = D * 2;                  // bytes of a K / V row
@@ -351,7 +351,7 @@ __global__ __launch_bounds__(512) void attn_prefill_wide(AttnPrefillArgs a, SeqL
     char* const Vs = smem + 3 * TILEB;
 
     int pair, tile;
-    if (!prefill_pair_and_tile(a, pair, tile)) return;
+    if (!prefill_pair_and_tile<AHEAD>(a, pair, tile)) return;
     const int b = pair / a.heads, g = pair % a.heads;
     const int L = lens.len[b];
     const int i0 = tile * BQ;
@@ -666,7 +666,7 @@ __device__ __forceinline__ float max_xor16(float x) {
     return fmaxf(__builtin_bit_cast(float, r0), __builtin_bit_cast(float, r1));
 }
 
-template <int D, bool CAUSAL, int NW>
+template <int D, bool CAUSAL, int NW, bool AHEAD>
 __global__ __launch_bounds__(64 * NW) void attn_prefill16(AttnPrefillArgs a, SeqLens lens) {
     constexpr int BQ = 16 * NW, BKV = 64, KK = D / 32, DB = D / 16;
     constexpr int LDK = D + 8;               // halfs between K rows: the 16-byte reads of 16 rows cover every bank once
@@ -677,7 +677,7 @@ __global__ __launch_bounds__(64 * NW) void attn_prefill16(AttnPrefillArgs a, Seq
     __shared__ __attribute__((aligned(16))) half_t Vs[2][BKV * LDV];
 
     int pair, tile;
-    if (!prefill_pair_and_tile(a, pair, tile)) return;
+    if (!prefill_pair_and_tile<AHEAD>(a, pair, tile)) return;
     const int b = pair / a.heads, g = pair % a.heads;
     const int L = lens.len[b];
     const int i0 = tile * BQ;
@@ -853,18 +853,20 @@ hipError_t launch_attention_prefill(const AttnPrefillArgs& a, const SeqLens& len
     AttnPrefillArgs w = a;
     size_t kv_bytes = 0;
     for (int b = 0; b < a.batch; ++b) kv_bytes += (size_t)lens.len[b] * a.heads * a.d * 2 * sizeof(half_t);
-    int chunk = pairs;
+    int chunk = 0;
     if (kv_bytes > kMemorySideCacheBytes) {
         chunk = (int)(kChunkKvBytes / (kv_bytes / pairs)) / 8 * 8;
         chunk = chunk < 16 ? 16 : chunk > 48 ? 48 : chunk;
     }
-    w.chunk_pairs = chunk < pairs ? chunk : pairs;
+    w.chunk_pairs = chunk < pairs ? chunk : 0;
     w.chunk_tiles = tiles;
-    w.tile_blocks = (pairs + w.chunk_pairs - 1) / w.chunk_pairs * w.chunk_pairs * tiles;
-    const dim3 grid(w.tile_blocks + w.ahead.blocks);
+    w.tile_blocks = w.chunk_pairs ? (pairs + chunk - 1) / chunk * chunk * tiles : 0;
+    const bool ahead = w.ahead.blocks > 0;
+    const dim3 grid = w.chunk_pairs ? dim3(w.tile_blocks + w.ahead.blocks) : dim3(pairs, tiles + (w.ahead.blocks + pairs - 1) / pairs);
+#define EET_PREFILL(K, ...) do { if (ahead) hipLaunchKernelGGL((K<__VA_ARGS__, true>), grid, block, 0, s, w, lens); \
+                                 else hipLaunchKernelGGL((K<__VA_ARGS__, false>), grid, block, 0, s, w, lens); } while (0)
     if (fine) {
-#define EET_FINE(D, C) do { if (few) hipLaunchKernelGGL((attn_prefill16<D, C, 4>), grid, block, 0, s, w, lens); \
-                            else hipLaunchKernelGGL((attn_prefill16<D, C, 8>), grid, block, 0, s, w, lens); } while (0)
+#define EET_FINE(D, C) do { if (few) EET_PREFILL(attn_prefill16, D, C, 4); else EET_PREFILL(attn_prefill16, D, C, 8); } while (0)
         if (a.d == 128) {
             if (a.causal) EET_FINE(128, true);
             else EET_FINE(128, false);
@@ -874,15 +876,15 @@ hipError_t launch_attention_prefill(const AttnPrefillArgs& a, const SeqLens& len
         }
 #undef EET_FINE
     } else if (wide) {
-#define EET_WIDE(C) do { if (halves) hipLaunchKernelGGL((attn_prefill_wide<128, C, 2>), grid, block, 0, s, w, lens); \
-                         else hipLaunchKernelGGL((attn_prefill_wide<128, C, 1>), grid, block, 0, s, w, lens); } while (0)
+#define EET_WIDE(C) do { if (halves) EET_PREFILL(attn_prefill_wide, 128, C, 2); else EET_PREFILL(attn_prefill_wide, 128, C, 1); } while (0)
         if (a.causal) EET_WIDE(true);
         else EET_WIDE(false);
 #undef EET_WIDE
     } else {
-        if (a.causal) hipLaunchKernelGGL((attn_prefill<true>), grid, block, 0, s, w, lens);
-        else hipLaunchKernelGGL((attn_prefill<false>), grid, block, 0, s, w, lens);
+        if (a.causal) EET_PREFILL(attn_prefill, true);
+        else EET_PREFILL(attn_prefill, false);
     }
+#undef EET_PREFILL
     return hipGetLastError();
 }
 

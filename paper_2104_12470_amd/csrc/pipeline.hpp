@@ -71,6 +71,26 @@ EET_PIPE_FN unsigned ahead_line(unsigned part, unsigned blocks, unsigned tid, un
 }
 
 // ---------------------------------------------------------------------------------------------------------
+// The (sequence, head) pairs and their query tiles over the workgroups of a prefill attention launch: the tiles of a pair on one XCD (workgroups
+// are dealt round-robin to the 8 XCDs; the chunk size is a multiple of 8), whose L2 then holds its K/V, and within a chunk of pairs the
+// longest tiles of all its pairs first, then the next longest ... (the best balance).  chunk_pairs = 0, grid = (pairs, tiles), is one chunk; otherwise
+// grid = (chunks * chunk_pairs * tiles) takes the pairs chunk after chunk, so that the K/V of the pairs in flight stays in the memory-side cache from
+// one tile of a pair to its next; the last chunk has workgroups whose pair is past the last.  Workgroups past the tiles (more rows of the first
+// grid, more of the second than tile_blocks) get past = 0, 1, ..., the others a negative one (checked on the host).
+// ---------------------------------------------------------------------------------------------------------
+EET_PIPE_FN void prefill_tile(int bx, int by, int grid_x, int chunk_pairs, int tiles, int tile_blocks, int& pair, int& tile, int& past) {
+    pair = bx;
+    tile = tiles - 1 - by;
+    past = bx - (tile + 1) * grid_x;
+    if (chunk_pairs != 0) {
+        const int per = chunk_pairs * tiles, c = bx / per, r = bx - c * per;
+        pair = c * chunk_pairs + r % chunk_pairs;
+        tile = tiles - 1 - r / chunk_pairs;
+        past = bx - tile_blocks;
+    }
+}
+
+// ---------------------------------------------------------------------------------------------------------
 // K loop of the MFMA tile kernel: K tiles of 64 columns through NS LDS stages (tile t in stage t % NS), four
 // sub-steps per tile, fragments double-buffered in registers (buffer = sub-step % 2).
 //

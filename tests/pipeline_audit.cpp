@@ -477,6 +477,30 @@ int main() {
                 snprintf(name, sizeof name, "%u lines in %u parts of %u threads", lines, blocks, threads);
                 expect_ok(once ? "" : "a line is not touched exactly once", name);
             }
+    // the grids of a prefill attention: every tile of every pair once, the workgroups past them numbered from 0
+    for (int pairs : {1, 5, 17, 48, 130, 1071})
+        for (int tiles : {1, 2, 7})
+            for (int chunk : {0, 16, 24, 48})
+                for (int extra : {0, 128}) {
+                    if (chunk >= pairs) continue;
+                    const int tile_blocks = chunk ? (pairs + chunk - 1) / chunk * chunk * tiles : 0;
+                    const int gx = chunk ? tile_blocks + extra : pairs, gy = chunk ? 1 : tiles + (extra + pairs - 1) / pairs;
+                    std::vector<int> seen((size_t)pairs * tiles, 0), extras((size_t)gx * gy, 0);
+                    bool good = true;
+                    for (int y = 0; y < gy; ++y)
+                        for (int x = 0; x < gx; ++x) {
+                            int pair, tile, past;
+                            eet::pipe::prefill_tile(x, y, gx, chunk, tiles, tile_blocks, pair, tile, past);
+                            if (past >= 0) { ++extras[past]; continue; }
+                            if (pair >= pairs && chunk) continue;
+                            if (pair < 0 || pair >= pairs || tile < 0 || tile >= tiles) { good = false; continue; }
+                            ++seen[(size_t)pair * tiles + tile];
+                        }
+                    for (int n : seen) good &= n == 1;
+                    for (int i = 0; i < extra; ++i) good &= extras[i] == 1;
+                    snprintf(name, sizeof name, "prefill attention, %d pairs of %d tiles in chunks of %d, %d workgroups more", pairs, tiles, chunk, extra);
+                    expect_ok(good ? "" : "a tile, or a workgroup past the tiles, does not come exactly once", name);
+                }
     {   // the tile order visits every tile exactly once, for every grid up to 40 x 40 tiles and a few large ones (all three orders)
         int bad = 0;
         auto check_grid = [&](int tm, int tn) {
