@@ -346,9 +346,8 @@ __global__ __launch_bounds__(512) void attn_prefill_wide(AttnPrefillArgs a, SeqL
     constexpr int RPI = 64 / CPR;                // rows one wave-level load instruction covers (1 KB of LDS)
     constexpr int NV = TILEB / 1024 / NWAVE;     // load instructions per wave per tile
     constexpr int KK = D / 16, DB = D / 32;
-    __shared__ __attribute__((aligned(1024))) char smem[6 * TILEB];
-    char* const Ks = smem;                       // rings of three stages
-    char* const Vs = smem + 3 * TILEB;
+    __shared__ __attribute__((aligned(1024))) char Ks[3][TILEB];
+    __shared__ __attribute__((aligned(1024))) char Vs[3][TILEB];
 
     int pair, tile;
     if (!prefill_pair_and_tile<AHEAD>(a, pair, tile)) return;
@@ -402,7 +401,7 @@ __global__ __launch_bounds__(512) void attn_prefill_wide(AttnPrefillArgs a, SeqL
         for (int v = 0; v < NV; ++v) {
             int key = jt * BKV + ld_row[v];
             key = key < L ? key : L - 1;
-            load_lds_16B(kbase + ((uint32_t)key * ROWB + ld_k[v]), Ks + st * TILEB + (wave * NV + v) * 1024);
+            load_lds_16B(kbase + ((uint32_t)key * ROWB + ld_k[v]), &Ks[st][(wave * NV + v) * 1024]);
         }
     };
     auto load_v = [&](int jt, int st) __attribute__((always_inline)) {
@@ -410,7 +409,7 @@ __global__ __launch_bounds__(512) void attn_prefill_wide(AttnPrefillArgs a, SeqL
         for (int v = 0; v < NV; ++v) {
             int key = jt * BKV + ld_row[v];
             key = key < L ? key : L - 1;
-            load_lds_16B(vbase + ((uint32_t)key * ROWB + ld_v[v]), Vs + st * TILEB + (wave * NV + v) * 1024);
+            load_lds_16B(vbase + ((uint32_t)key * ROWB + ld_v[v]), &Vs[st][(wave * NV + v) * 1024]);
         }
     };
 
@@ -419,7 +418,7 @@ __global__ __launch_bounds__(512) void attn_prefill_wide(AttnPrefillArgs a, SeqL
 #pragma unroll
     for (int kk = 0; kk < KK; ++kk) {
         const int sw = D == 128 ? (li & 15) : ((li >> 1) & 7);
-        kaddr[kk] = (unsigned)(uintptr_t)Ks + (kg * 32 + li) * ROWB + (((kk * 2 + G) ^ sw) * 16);
+        kaddr[kk] = (unsigned)(uintptr_t)&Ks[0][0] + (kg * 32 + li) * ROWB + (((kk * 2 + G) ^ sw) * 16);
     }
     unsigned vaddr[DB];     // transpose read: this lane supplies key G*4 + (li%16)/4 (+ offset), 4 halfs at dv db*32 + (li/16)*16 + (li%4)*4
     {
@@ -428,7 +427,7 @@ __global__ __launch_bounds__(512) void attn_prefill_wide(AttnPrefillArgs a, SeqL
 #pragma unroll
         for (int db = 0; db < DB; ++db) {
             const int cc = db * 4 + blk * 2 + ((lb & 3) >> 1);
-            vaddr[db] = (unsigned)(uintptr_t)Vs + (kg * 32 + G * 4 + (lb >> 2)) * ROWB + ((cc ^ sw) * 16) + (lb & 1) * 8;
+            vaddr[db] = (unsigned)(uintptr_t)&Vs[0][0] + (kg * 32 + G * 4 + (lb >> 2)) * ROWB + ((cc ^ sw) * 16) + (lb & 1) * 8;
         }
     }
 
@@ -607,9 +606,11 @@ __global__ __launch_bounds__(512) void attn_prefill_wide(AttnPrefillArgs a, SeqL
     if constexpr (KG == 2) {
         // the upper group hands its reference, sum and values over: 16 bytes per lane and instruction, a wave's side by side
         __syncthreads();
-        float4v* const part = reinterpret_cast<float4v*>(smem) + (wave & 3) * (DB * 4 * 64) + lane;
-        float2v* const part_ml = reinterpret_cast<float2v*>(smem + 4 * DB * 4 * 64 * 16) + (wave & 3) * 64 + lane;
-        static_assert(4 * DB * 4 * 64 * 16 + 4 * 64 * 8 <= sizeof(smem), "the hand-over fits over the rings");
+        constexpr int PARTB = DB * 4 * 64 * 16;            // of a row block: three of them over the K ring, the fourth and the references over the V ring
+        static_assert(3 * PARTB <= (int)sizeof(Ks) && PARTB + 4 * 64 * 8 <= (int)sizeof(Vs), "the hand-over fits over the rings");
+        const int block = wave & 3;
+        float4v* const part = reinterpret_cast<float4v*>(block < 3 ? &Ks[0][0] + block * PARTB : &Vs[0][0]) + lane;
+        float2v* const part_ml = reinterpret_cast<float2v*>(&Vs[0][0] + PARTB) + block * 64 + lane;
         if (kg == 1) {
 #pragma unroll
             for (int db = 0; db < DB; ++db)
