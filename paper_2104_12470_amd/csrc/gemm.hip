@@ -121,6 +121,118 @@ __device__ __forceinline__ void lines_to_rows(half8v& first, half8v& second, boo
     second = __builtin_bit_cast(half8v, d1);
 }
 
+// Rows m of the problem: r0 = output row (EPI_QKV: the sequence whose cache the row's K and V go to), r1 = residual row (EPI_QKV: the cache slot; negative
+// or >= max_seq: dropped).  Every look-up is requested before anything waits for one.  Rows past M come as M-1; they are never stored.
+template <int EPI, int R>
+__device__ __forceinline__ void epilogue_rows(const GemmArgs& a, const int (&m)[R], int (&r0)[R], int (&r1)[R]) {
+    if constexpr (EPI == EPI_QKV) {
+        if (a.tok_row_map) {                             // prefill: token -> (sequence, position)
+            int tok[R];
+#pragma unroll
+            for (int i = 0; i < R; ++i) tok[i] = a.tok_row_map[m[i]];
+#pragma unroll
+            for (int i = 0; i < R; ++i) {
+                r0[i] = tok[i] / a.S;
+                r1[i] = tok[i] - r0[i] * a.S;
+            }
+            if (a.left_pad) {                            // pads lead: token 0 of the sequence is at row S - L_b
+                int len[R];
+#pragma unroll
+                for (int i = 0; i < R; ++i) len[i] = a.lens[r0[i]];
+#pragma unroll
+                for (int i = 0; i < R; ++i) r1[i] -= a.S - len[i];
+            }
+        } else {                                         // decode: the new token goes to slot n_b
+#pragma unroll
+            for (int i = 0; i < R; ++i) {
+                r0[i] = m[i];
+                r1[i] = a.lens[m[i]];
+            }
+        }
+    } else {
+#pragma unroll
+        for (int i = 0; i < R; ++i) {
+            r0[i] = a.out_row_map ? a.out_row_map[m[i]] : m[i];
+            r1[i] = (EPI == EPI_BIAS_RES && a.res_row_map) ? a.res_row_map[m[i]] : m[i];
+        }
+    }
+}
+
+// The tiles of which two workgroups share a CU (192 x 128 and 128 x 128 with two stages) turn theirs around through LDS all the same, unless GELU comes
+// with it: the stages are free, a CU has the other workgroup to go on with, and whole lines out in one go get in its way less.  us, straight
+// out / through LDS (rows x N x K): with a residual 1066 x 7232 x 128 10.4 / 9.2, 367 x 13952 x 128 9.25 / 8.4, 1753 x 11904 x 320 1.07 / 0.99 of what it
+// took when all tiles went through LDS; a bias alone 5535 x 2176 x 128 1.06 / 1.01, 523 x 14336 x 448 1.06 / 1.01; from K = 512 on level; with GELU
+// 1667 x 2816 x 128 7.8 / 8.7, 2319 x 3328 x 384 0.95 / 1.0.  The same for 128 x 64 tiles, three to a CU: level with a residual or a bias, 0.96 / 1.01 with GELU.
+//
+// `stage`: AM*16*128 bytes of LDS no other wave touches, a row of 64 columns in 128 bytes, its sixteen 8-byte units XOR-permuted by (row/2)%16 so
+// that both access patterns spread over all banks.  Whole-line pattern: row it*8 + lane/8, 16-byte chunk lane%8.
+template <int AM, int EPI>
+__device__ __forceinline__ void epilogue_via_lds(const GemmArgs& a, const float4v (&acc)[AM][4], char* stage, int mw, int nw, int lane) {
+    constexpr int R = AM * 2;
+    const int M = a.M, N = a.N, r8 = lane >> 3, c8 = lane & 7;
+    if (nw >= N) return;
+    int m[R], r0[R], r1[R];
+#pragma unroll
+    for (int it = 0; it < R; ++it) {
+        m[it] = mw + it * 8 + r8;
+        m[it] = m[it] < M ? m[it] : M - 1;
+    }
+    epilogue_rows<EPI>(a, m, r0, r1);
+    if constexpr (EPI == EPI_BIAS_RES) {
+        half8v rv[R];
+#pragma unroll
+        for (int it = 0; it < R; ++it) rv[it] = *reinterpret_cast<const half8v*>(a.res + (int64_t)r1[it] * N + nw + c8 * 8);
+#pragma unroll
+        for (int it = 0; it < R; ++it) {
+            const int row = it * 8 + r8, sw = (row >> 1) & 15;
+            half8v v = rv[it];
+            if (sw & 1) v = __builtin_shufflevector(v, v, 4, 5, 6, 7, 0, 1, 2, 3);
+            *reinterpret_cast<half8v*>(stage + row * 128 + ((c8 ^ (sw >> 1)) * 16)) = v;
+        }
+    }
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        const int unit = tile_column(j, (lane >> 4) * 4) / 4;
+        const half4v bias = *reinterpret_cast<const half4v*>(a.bias + nw + unit * 4);
+#pragma unroll
+        for (int i = 0; i < AM; ++i) {
+            const int row = i * 16 + (lane & 15);
+            half4v* slot = reinterpret_cast<half4v*>(stage + row * 128 + ((unit ^ ((row >> 1) & 15)) * 8));
+            half4v v, r{};
+            if (EPI == EPI_BIAS_RES) r = *slot;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                float f = acc[i][j][e] + (float)bias[e];
+                if (EPI == EPI_BIAS_RES) f += (float)r[e];
+                v[e] = (half_t)f;
+            }
+            *slot = v;
+        }
+    }
+#pragma unroll
+    for (int it = 0; it < R; ++it) {
+        const int row = it * 8 + r8, sw = (row >> 1) & 15;
+        if (mw + row >= M) continue;
+        half8v v = *reinterpret_cast<const half8v*>(stage + row * 128 + ((c8 ^ (sw >> 1)) * 16));
+        if (sw & 1) v = __builtin_shufflevector(v, v, 4, 5, 6, 7, 0, 1, 2, 3);
+        const int n = nw + c8 * 8;
+        half_t* dst;
+        if constexpr (EPI == EPI_QKV) {
+            const int which = n / a.hidden, c = n - which * a.hidden;                    // 0 = Q, 1 = K, 2 = V
+            if (which == 0) {
+                dst = a.y + (int64_t)(mw + row) * a.hidden + c;
+            } else {
+                if (r1[it] < 0 || r1[it] >= a.max_seq) continue;                         // see epilogue_apply: never outside the sequence's slots
+                const int g = c / a.d;
+                dst = (which == 1 ? a.k_cache : a.v_cache) + (((int64_t)r0[it] * a.heads + g) * a.max_seq + r1[it]) * a.d + (c - g * a.d);
+            }
+        } else {
+            dst = a.y + (int64_t)r0[it] * (a.ldy ? a.ldy : N) + n;
+        }
+        *reinterpret_cast<half8v*>(dst) = v;
+    }
+}
+
 // mw, nw: first row and column of the wave tile; its columns are inside N in groups of 64, or outside (N % 64 == 0).  Row maps and residual are all
 // requested before anything waits for them: one trip to memory per tile.  (8192 x 16384 x 2048 with a residual: 634 -> 552 us; 25082 x 12288 x
 // 12288: 6.56 -> 6.37 ms).
@@ -130,42 +242,13 @@ __device__ __forceinline__ void epilogue_tile(const GemmArgs& a, const float4v (
     const int M = a.M, N = a.N, fr = lane & 15, G = lane >> 4;
     if (nw >= N) return;
     auto inside = [&](int p) { return P <= 2 || nw + (p / 2) * 64 < N; };
-    // rows: r0 = output row (EPI_QKV: the sequence whose cache the row's K and V go to, r1 = the cache slot; negative or >= max_seq:
-    // dropped).  Rows past M repeat row M-1; they are never stored.
     int m[AM], r0[AM], r1[AM];
 #pragma unroll
     for (int i = 0; i < AM; ++i) {
         m[i] = mw + i * 16 + fr;
         m[i] = m[i] < M ? m[i] : M - 1;
     }
-    if constexpr (EPI == EPI_QKV) {
-        if (a.tok_row_map) {                             // prefill: token -> (sequence, position)
-            int tok[AM];
-#pragma unroll
-            for (int i = 0; i < AM; ++i) tok[i] = a.tok_row_map[m[i]];
-#pragma unroll
-            for (int i = 0; i < AM; ++i) {
-                r0[i] = tok[i] / a.S;
-                r1[i] = tok[i] - r0[i] * a.S;
-            }
-            if (a.left_pad) {                            // pads lead: token 0 of the sequence is at row S - L_b
-                int len[AM];
-#pragma unroll
-                for (int i = 0; i < AM; ++i) len[i] = a.lens[r0[i]];
-#pragma unroll
-                for (int i = 0; i < AM; ++i) r1[i] -= a.S - len[i];
-            }
-        } else {                                         // decode: the new token goes to slot n_b
-#pragma unroll
-            for (int i = 0; i < AM; ++i) {
-                r0[i] = m[i];
-                r1[i] = a.lens[m[i]];
-            }
-        }
-    } else {
-#pragma unroll
-        for (int i = 0; i < AM; ++i) r0[i] = a.out_row_map ? a.out_row_map[m[i]] : m[i];
-    }
+    epilogue_rows<EPI>(a, m, r0, r1);
     half8v bias[P];
 #pragma unroll
     for (int p = 0; p < P; ++p)
@@ -607,7 +690,13 @@ __global__ __launch_bounds__(WGM* WGN* KS * 64, BM == 192 && BN == 128 && NS == 
         }
         return;
     }
-    epilogue_tile<AM, AN, EPI, NTS>(a, acc, m0 + wm0, n0 + wn0, lane);
+    if constexpr (SCHED == 0 && NS == 2 && EPI != EPI_BIAS_GELU) {
+        __syncthreads();                                  // every wave is done with the operand stages
+        static_assert(NW * WM * 128 <= (int)sizeof(As) && !NTS, "turn-around areas");
+        epilogue_via_lds<AM, EPI>(a, acc, reinterpret_cast<char*>(&As[0][0]) + wave * WM * 128, m0 + wm0, n0 + wn0, lane);
+    } else {
+        epilogue_tile<AM, AN, EPI, NTS>(a, acc, m0 + wm0, n0 + wn0, lane);
+    }
 }
 
 // --------------------------------------------------------------------------------------------
