@@ -1808,8 +1808,14 @@ hipError_t launch_gemm(const GemmArgs& a, Epilogue epi, hipStream_t s) {
         }
         switch (tile_for(a.M, a.N, a.K)) {
         case kTile64: launch_dma64_cfg<2, 1, 64, 64, 3, 1, 2>(a, epi, s); break;
-        case kTile64Split: launch_dma64_cfg<2, 1, 64, 64, 3, 2, 2>(a, epi, s); break;
-        case kTile128x64Split: launch_dma64_cfg<4, 1, 128, 64, 3, 2, 2>(a, epi, s); break;
+        case kTile64Split:
+            if (reads_weights_past_l2(a.M, a.N, a.K, 64)) launch_dma64_cfg<2, 1, 64, 64, 3, 2, 0>(a, epi, s);
+            else launch_dma64_cfg<2, 1, 64, 64, 3, 2, 2>(a, epi, s);
+            break;
+        case kTile128x64Split:
+            if (reads_weights_past_l2(a.M, a.N, a.K, 128)) launch_dma64_cfg<4, 1, 128, 64, 3, 2, 0>(a, epi, s);
+            else launch_dma64_cfg<4, 1, 128, 64, 3, 2, 2>(a, epi, s);
+            break;
         case kTile128x64: launch_dma64_cfg<4, 1, 128, 64, 3>(a, epi, s); break;
         case kTile192Pair: launch_dma64_cfg<2, 2, 192, 128, 2, 1, 0>(a, epi, s); break;
         case kTile128PairShared: launch_dma64_cfg<2, 2, 128, 128>(a, epi, s); break;

@@ -244,6 +244,15 @@ inline TileChoice tile_for(int M, int N, int K) {
     return tiles128 > 256 ? kTile128PairShared : tiles128 == 256 ? kTile128 : kTile128x64;
 }
 
+// The tiles with two groups of waves spread the loads of a step over both of its halves, but for one row tile over more weights than the
+// eight L2s hold (32 MB): each is then read once, from the memory-side cache or HBM, and what counts is how early it is asked for, all of a step at once.  us,
+// at once / spread, weights in the memory-side cache: 114 x 16256 x 1152 10.9 / 12.3, 86 x 14080 x 1536 11.3 / 12.2, 105 x 13440 x 2176 14.8 / 16.0, 21 x
+// 14144 x 1408 9.9 / 10.5, 50 x 14016 x 1280 9.2 / 9.9; out of HBM level.  Below
+// the line spread is 2 to 16 % ahead (46 x 11264 x 1408, 30 MB 8.7 / 7.5; 32 x 11200 x 1536, 33 MB 9.6 / 8.6).
+inline bool reads_weights_past_l2(int M, int N, int K, int tile_rows) {
+    return M <= tile_rows && (size_t)N * K * 2 > ((size_t)33 << 20);
+}
+
 // More than 128 rows over outputs of a multiple of 128 columns with K from 768 on (what the projections of a layer mostly are): one tile per CU in any
 // number of rounds, of the height that leaves the least of them idle.  Since the loads of a K step are spread over both of its halves and the
 // output goes straight to memory a tile alone on its CU is faster than two that share it, so what is left to choose is the size.  Measured, us, K in
