@@ -187,6 +187,14 @@ inline int rows_in_whole_rounds(int M, int N) {
 // 276 / 306, 315.  All of the one-per-CU tiles run the one-wave-per-SIMD schedule, a tenth ahead of the shared one at every
 // depth (700 x 4096 x 16384, 128 x 128: 141 with the shared schedule and 3, 4 or 5 stages, 130 and 123 with this one and 3 and 4).
 enum TileChoice { kTile64, kTile64Split, kTile128x64Split, kTile128x64, kTile128PairShared, kTile128Pair, kTile192Pair, kTile96, kTile128, kTile192, kTile128x256, kTile256 };
+inline double two_per_cu(double n, double two, double one) {         // n tiles, `two` the time of both of a CU, `one` the share of one
+    const double whole = (double)(int64_t)(n / 512), rest = n - whole * 512;
+    return two * (whole + (rest == 0 ? 0.0 : rest <= 256 ? one : 0.92));
+}
+inline double pair_us(int M, int N, double k, int rows) {            // 192 x 128 or 128 x 128
+    const double n = (double)((M + rows - 1) / rows) * ((N + 127) / 128);
+    return rows == 192 ? two_per_cu(n, 8 + 21.3 * k, 0.76) : two_per_cu(n, 6 + 14.5 * k, 0.58);
+}
 inline TileChoice choose_tile(int M, int N, int K) {
     auto tiles = [&](int bm, int bn) { return (double)((M + bm - 1) / bm) * ((N + bn - 1) / bn); };
     const double k = K / 1024.0;
@@ -195,15 +203,11 @@ inline TileChoice choose_tile(int M, int N, int K) {
     auto offer = [&](TileChoice c, double us) {
         if (us < best) { best = us; choice = c; }
     };
-    auto pairs = [](double n, double two, double one) {         // n tiles, two per CU, `two` the time of both, `one` the share of one
-        const double whole = (double)(int64_t)(n / 512), rest = n - whole * 512;
-        return two * (whole + (rest == 0 ? 0.0 : rest <= 256 ? one : 0.92));
-    };
     // (the large tile first and with 3 % in hand: past the first round the others' tails are rougher estimates than its own)
     offer(kTile256, (double)(int64_t)((tiles(256, 256) + 255) / 256) * (10 + 21.5 * k) / 1.03);
-    offer(kTile192Pair, pairs(tiles(192, 128), 8 + 21.3 * k, 0.76));
-    if (tiles(128, 128) > 256) offer(kTile128Pair, pairs(tiles(128, 128), 6 + 14.5 * k, 0.58));
-    offer(kTile128x64, pairs(tiles(128, 64), 4.5 + 9 * k, 0.75));
+    offer(kTile192Pair, pair_us(M, N, k, 192));
+    if (tiles(128, 128) > 256) offer(kTile128Pair, pair_us(M, N, k, 128));
+    offer(kTile128x64, two_per_cu(tiles(128, 64), 4.5 + 9 * k, 0.75));
     if (tiles(128, 256) <= 256) offer(kTile128x256, 9 + 12 * k);
     if (tiles(192, 128) <= 256) offer(kTile192, 7 + 9.2 * k);
     if (tiles(128, 128) <= 256) offer(kTile128, 5 + 7.9 * k);
@@ -266,7 +270,10 @@ inline bool reads_weights_past_l2(int M, int N, int K, int tile_rows) {
 // 167 -> 144, 6758 x 2048 x 2048 60 -> 54 (224 x 256), 700 x 5120 x 1280 16.2 -> 13.3 (128 x 128).  Where it stops: at K = 512 the pairs of tile_for
 // are level or ahead (8200 x 2048 x 512 27.8 / 30.8, 3800 x 2048 x 512 14.4 / 15.3); 64 columns left over, which leave part of every last tile
 // idle, keep the tile they have; the tiles shared by two groups of waves are ahead of all of these (900 x 1280 x 5120 28.2 / 31.3, 700 x 2048 x
-// 8192 39.4 / 43.6).  224 rows only where at most one in sixteen of their rows is padding: beyond that 256 are as fast or the next smaller height is.
+// 8192 39.4 / 43.6).  Tiles of 128 columns are for one round: where they would be the cheapest in more, and 192 x 128 below K = 1024 throughout, the pairs of tile_for
+// come first if their own price is the lower one (one round of 128 x 128 or 192 x 128 in two / as pairs: 1031 x 10880 x 1152 40.9 / 34.7, 4290 x 1920 x 1408 33.2 / 28.4, 3302
+// x 2432 x 832 21.3 / 18.9, 8223 x 896 x 1856 35.5 / 33.5; 161 sizes of the first kind 1.04 / 0.98 of what tile_for's choice took before; below K = 1024, 2275 x 10880 x 896
+// 56.1 / 51.4, 4802 x 2432 x 832 29.0 / 27.6).  224 rows only where at most one in sixteen of their rows is padding: beyond that 256 are as fast or the next smaller height is.
 enum FullTile { kFullNone, kFull256, kFull224x256, kFull192x256, kFull160x256, kFull128x256, kFull192, kFull128, kFull96 };
 inline FullTile full_tile(int M, int N, int K) {
     if (M <= 128 || N % 128 != 0 || K < 768 || few_tiles(M, N, K)) return kFullNone;
@@ -275,14 +282,17 @@ inline FullTile full_tile(int M, int N, int K) {
         {kFull160x256, 160, 256, 9.6, 13, 7.3, 14.7},   {kFull128x256, 128, 256, 8.3, 10.8, 6.8, 12},    {kFull192, 192, 128, 6.9, 8.5, 5.2, 9.7},
         {kFull128, 128, 128, 5.6, 6.4, 3.9, 7.1},       {kFull96, 96, 128, 5.5, 5.2, 3.6, 5.8}};
     const double k = K / 1024.0;
-    double best = 1e30;
+    double best = 1e30, best_narrow = 1e30;
     FullTile choice = kFullNone;
     for (const auto& t : kTiles) {
         const int64_t tm = (M + t.rows - 1) / t.rows, tiles = tm * ((N + t.cols - 1) / t.cols), whole = tiles / 256, rest = tiles % 256;
         if (t.tile == kFull224x256 && (tm * t.rows - M) * 16 > tm * t.rows) continue;
         const double us = tiles <= 256 ? t.one + t.one_k * k : ((double)whole + (rest == 0 ? 0.0 : 0.7 + 0.3 * (double)rest / 256)) * (t.each + t.each_k * k);
-        if (us < best) { best = us; choice = t.tile; }
+        if (t.cols == 128 && tiles > 256) best_narrow = us < best_narrow ? us : best_narrow;
+        else if (us < best) { best = us; choice = t.tile; }
     }
+    if ((best_narrow < best || K < 1024) && pair_us(M, N, k, 192) < best) return kFullNone;
+    if (best_narrow < best && pair_us(M, N, k, 128) < best) return kFullNone;
     return choice;
 }
 

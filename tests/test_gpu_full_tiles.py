@@ -67,6 +67,16 @@ def test_shapes_that_other_tests_hold_to_a_tile_keep_it(ask):
     assert all(full in ("none", old) or cut != "0" for cut, full, old in answers), [(s, a) for s, a in zip(sizes, answers) if a[1] not in ("none", a[2])]
 
 
+def test_pairs_that_nearly_fill_a_round_are_not_taken_apart(ask):
+    """Sizes of 420 to 512 tiles of which two share a CU, measured 5 to 17 % slower as two rounds of one tile per CU, and below K = 1024 5 to 9 % slower on taller ones;
+    a few tiles more or less on either side, and the tall tiles stay where they are ahead."""
+    pairs = [((1031, 10880, 1152), "192x128"), ((4290, 1920, 1408), "128x128"), ((3302, 2432, 832), "128x128"), ((5545, 1408, 1728), "128x128"),
+             ((8223, 896, 1856), "128x128"), ((2275, 10880, 896), "192x128"), ((4802, 2432, 832), "192x128"), ((8799, 1408, 960), "192x128")]
+    assert [(full, old) for _, full, old in ask([s for s, _ in pairs])] == [("none", t) for _, t in pairs]
+    tall = [((2140, 4096, 4096), "160x256"), ((1137, 15360, 7232), "160x256"), ((3054, 3072, 12288), "160x256"), ((6758, 2048, 2048), "224x256"), ((1153, 2176, 832), "96x128")]
+    assert [full for _, full, _ in ask([s for s, _ in tall])] == [t for _, t in tall]
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("M,K,N,tile", SHAPES)
 def test_linear_full_tiles(M, K, N, tile):
