@@ -158,11 +158,11 @@ __device__ __forceinline__ void epilogue_rows(const GemmArgs& a, const int (&m)[
     }
 }
 
-// The tiles of which two workgroups share a CU (192 x 128 and 128 x 128 with two stages) turn theirs around through LDS all the same, unless GELU comes
-// with it: the stages are free, a CU has the other workgroup to go on with, and whole lines out in one go get in its way less.  us, straight
+// The tiles of which two workgroups share a CU (192 x 128 and 128 x 128 with two stages, under either schedule) turn theirs around through LDS all the same,
+// unless GELU comes with it: the stages are free, a CU has the other workgroup to go on with, and whole lines out in one go get in its way less.  us, straight
 // out / through LDS (rows x N x K): with a residual 1066 x 7232 x 128 10.4 / 9.2, 367 x 13952 x 128 9.25 / 8.4, 1753 x 11904 x 320 1.07 / 0.99 of what it
-// took when all tiles went through LDS; a bias alone 5535 x 2176 x 128 1.06 / 1.01, 523 x 14336 x 448 1.06 / 1.01; from K = 512 on level; with GELU
-// 1667 x 2816 x 128 7.8 / 8.7, 2319 x 3328 x 384 0.95 / 1.0.  The same for 128 x 64 tiles, three to a CU: level with a residual or a bias, 0.96 / 1.01 with GELU.
+// took when all tiles went through LDS; a bias alone 5535 x 2176 x 128 1.06 / 1.01, 523 x 14336 x 448 1.06 / 1.01; from K = 512 on level; 59 of 128 x 128 tiles with a
+// residual and spread loads, K = 512 to 3072, 0.989 / 0.968 of that; with GELU 1667 x 2816 x 128 7.8 / 8.7, 2319 x 3328 x 384 0.95 / 1.0.  The same for 128 x 64 tiles, three to a CU: level with a residual or a bias, 0.96 / 1.01 with GELU.
 //
 // `stage`: AM*16*128 bytes of LDS no other wave touches, a row of 64 columns in 128 bytes, its sixteen 8-byte units XOR-permuted by (row/2)%16 so
 // that both access patterns spread over all banks.  Whole-line pattern: row it*8 + lane/8, 16-byte chunk lane%8.
@@ -690,7 +690,7 @@ __global__ __launch_bounds__(WGM* WGN* KS * 64, BM == 192 && BN == 128 && NS == 
         }
         return;
     }
-    if constexpr (SCHED == 0 && NS == 2 && EPI != EPI_BIAS_GELU) {
+    if constexpr (NS == 2 && BN == 128 && EPI != EPI_BIAS_GELU) {
         __syncthreads();                                  // every wave is done with the operand stages
         static_assert(NW * WM * 128 <= (int)sizeof(As) && !NTS, "turn-around areas");
         epilogue_via_lds<AM, EPI>(a, acc, reinterpret_cast<char*>(&As[0][0]) + wave * WM * 128, m0 + wm0, n0 + wn0, lane);

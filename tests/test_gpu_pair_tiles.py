@@ -1,4 +1,4 @@
-"""Tiles of which two workgroups share a CU (192 x 128 and 128 x 128 with two LDS stages, the shared schedule): their output goes through LDS unless GELU comes with
+"""Tiles of which two workgroups share a CU (192 x 128 and 128 x 128 with two LDS stages): their output goes through LDS unless GELU comes with
 it.  Every kind of output at the smallest K and at a larger one, with ragged rows and a half column tile: a bias alone, a residual, rows with strides,
 and a prompt's cache rows in both layouts.  Which tile a shape takes is asked of the rules that the library compiles."""
 import os
@@ -17,7 +17,8 @@ OP_MAX, OP_MEAN = 6e-3, 6e-4       # as tests/test_gpu_ops.py: fp16 outputs of o
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 SHAPES = [(801, 64, 12352, "192x128 x2"), (3339, 320, 5056, "192x128 x2"), (1753, 448, 11904, "192x128 x2"),
-          (301, 64, 12352, "128x128 x2, shared schedule"), (1480, 320, 3136, "128x128 x2, shared schedule"), (2319, 384, 3264, "128x128 x2, shared schedule")]
+          (301, 64, 12352, "128x128 x2, shared schedule"), (1480, 320, 3136, "128x128 x2, shared schedule"), (2319, 384, 3264, "128x128 x2, shared schedule"),
+          (615, 512, 9856, "128x128 x2"), (3019, 576, 2432, "128x128 x2"), (1012, 2304, 6208, "128x128 x2")]
 # (heads, sequences, padded length, tile of the QKV projection)
 PROMPTS = [(5, 84, 64, "128x128 x2, shared schedule"), (7, 112, 64, "192x128 x2")]
 
