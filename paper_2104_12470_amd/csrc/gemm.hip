@@ -477,9 +477,8 @@ struct GemmTileExec {
     template <int H, int LOADS, int IDX>
     __device__ __forceinline__ void half_mma_one(unsigned va_, unsigned vw_, int64_t koff, int lstage) {
         constexpr int MF = AM * AN, NR = AM + AN, NL = LOADS == 1 ? LIA : LIW;
-        constexpr int RS = (MF * 3 / 4) / NR, LS = (MF * 3 / 4) / NL > 0 ? (MF * 3 / 4) / NL : 1;   // multiplies per read, per load (both measured best at 3 for 64)
-        constexpr int LP = LS * MF * 3 / 4 >= NL ? 1 : (NL + MF * 3 / 4 - 1) / (MF * 3 / 4);          // loads at a time
-        static_assert(RS >= 1, "side work fits between the multiplies");
+        constexpr int RS = (MF * 3 / 4) / NR, LS = (MF * 3 / 4) / NL;       // multiplies per read, per load (256 x 256 tile, 64 multiplies: 3 and 6)
+        static_assert(RS >= 1 && LS >= 1, "side work fits between the multiplies");
         constexpr int i = IDX / AN, j = IDX % AN;
         acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(gw[H][j], ga[H][i], acc[i][j], 0, 0, 0);
         if constexpr (IDX % RS == 0 && IDX / RS < NR) {
@@ -487,13 +486,11 @@ struct GemmTileExec {
             half_read<1 - H, IDX / RS>(va_, vw_);
             __builtin_amdgcn_sched_barrier(0);
         }
-        if constexpr (IDX % LS == LS / 2 && IDX / LS * LP < NL) {
+        if constexpr (IDX % LS == LS / 2 && IDX / LS < NL) {
+            constexpr int v = IDX / LS;
             __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-            for (int v = IDX / LS * LP; v < IDX / LS * LP + LP && v < NL; ++v) {
-                if constexpr (LOADS == 1) load_lds_16B(pa[v % LIA] + koff, as_base + lstage * (BM * BK) + (wave * LRA + v * 8) * BK);
-                else load_lds_16B<NTW>(pw[v % LIW] + koff, ws_base + lstage * (BN * BK) + (wave * LRW + v * 8) * BK);
-            }
+            if constexpr (LOADS == 1) load_lds_16B(pa[v % LIA] + koff, as_base + lstage * (BM * BK) + (wave * LRA + v * 8) * BK);
+            else load_lds_16B(pw[v % LIW] + koff, ws_base + lstage * (BN * BK) + (wave * LRW + v * 8) * BK);
             __builtin_amdgcn_sched_barrier(0);
         }
     }
@@ -503,20 +500,14 @@ struct GemmTileExec {
         (half_mma_one<H, LOADS, I>(va_, vw_, koff, lstage), ...);
         __builtin_amdgcn_sched_barrier(0);
     }
-    __device__ __forceinline__ int64_t column(int tile) {         // first column of this group's K tile `tile`
-        if constexpr (ROT) {
-            tile += k_first;
-            if (tile >= k_count) tile -= k_count;
-        }
-        return (int64_t)(tile * KS + kg) * BK;
-    }
+    __device__ __forceinline__ int64_t column(int tile) { return (int64_t)(tile * KS + kg) * BK; }    // first column of this group's K tile `tile`
     __device__ __forceinline__ void load_a(int tile, int stage) {
 #pragma unroll
         for (int v = 0; v < LIA; ++v) load_lds_16B(pa[v] + column(tile), as_base + stage * (BM * BK) + (wave * LRA + v * 8) * BK);
     }
     __device__ __forceinline__ void load_w(int tile, int stage) {
 #pragma unroll
-        for (int v = 0; v < LIW; ++v) load_lds_16B<NTW>(pw[v] + column(tile), ws_base + stage * (BN * BK) + (wave * LRW + v * 8) * BK);
+        for (int v = 0; v < LIW; ++v) load_lds_16B(pw[v] + column(tile), ws_base + stage * (BN * BK) + (wave * LRW + v * 8) * BK);
     }
     template <int LA, int LW>
     __device__ __forceinline__ void wait_loads() {
@@ -570,7 +561,7 @@ template <int BM, int BN, int WGM, int WGN, int EPI, int NS, int KS, int SCHED, 
 // (192 x 128 tiles are made for two workgroups per CU: the residual and cache-row look-ups of their epilogue would take the
 // kernel past 256 registers and halve that: 2000 x 4096 x 4096 with a residual 135 us)
 __global__ __launch_bounds__(WGM* WGN* KS * 64, BM == 192 && BN == 128 && NS == 2 ? 2 : 1) void gemm_mfma_dma64(GemmArgs a, int tiles_m, int tiles_n) {
-    static_assert(SCHED == 0 || SCHED == 1 || (SCHED == 2 && NS > 2), "schedule");
+    static_assert(SCHED == 0 || (!NTW && !ROT && (SCHED == 1 || (SCHED == 2 && NS > 2))), "schedule");
     // KS > 1: KS groups of WGM x WGN waves share the tile and take every KS-th K step each, through LDS stages of their
     // own; the other groups' accumulators are added to the first's through LDS at the end.  For the few
     // tiles of a narrow output with a long K, where nothing else puts more loads in flight per CU.

@@ -116,32 +116,10 @@ EET_PIPE_FN void gemm_tile_front(Ops& op, int st) {
     op.template frag<1, 3>(st);
 }
 
-template <int NS, bool EARLY = false, class Ops = void>
+template <int NS, class Ops>
 EET_PIPE_FN void gemm_k_loop(Ops& op, int nk) {
     static_assert(NS == 2 || NS == 3, "LDS stages");
-    static_assert(!EARLY || NS == 2, "early release: two-stage schedule only");
-    if (NS == 2 && EARLY) {
-        // two stages, early release: the reads of a tile's last sub-step are issued after the multiplies of its second,
-        // and the barrier that hands the stage over sits before the multiplies of the last two sub-steps; the request of
-        // tile kt+2 follows the barrier at once, while the fetch of tile kt+1 is still completing
-        op.load(0, 0);
-        op.template wait_vmem<0>();
-        op.barrier();
-        if (nk > 1) op.load(1, 1);
-        op.template frag<0, 0>(0);
-        for (int kt = 0; kt < nk; ++kt) {
-            const int st = kt & 1;
-            gemm_tile_front(op, st);
-            op.template wait_frag<1, 3, -1>();    // every read of stage st has landed (sub-steps 2 and 3 sit in the buffers)
-            op.template wait_frag<0, 2, -1>();
-            op.template wait_vmem<0>();        // this wave's part of tile kt+1 has landed
-            op.barrier();                         // ... and everybody else's; stage st is free
-            if (kt + 2 < nk) op.load(kt + 2, st);
-            op.template mma<0, 2>();
-            op.template frag<0, 0>(st ^ 1);       // (past the last tile: stale data, never multiplied)
-            op.template mma<1, 3>();
-        }
-    } else if (NS == 2) {
+    if (NS == 2) {
         // two stages: tile kt+1 is requested at the start of step kt into the stage that step kt-1 read and that the
         // barrier at its end released; the end of step kt waits for it
         op.load(0, 0);
@@ -192,57 +170,26 @@ EET_PIPE_FN void gemm_k_loop(Ops& op, int nk) {
 }
 
 // ---------------------------------------------------------------------------------------------------------
-// K loop of the MFMA tile kernel for one wave per SIMD, NS LDS stages.  Nothing else runs on the SIMD while a wave
-// waits, and the LDS of the CU is busy most of the time (fragment reads of four waves plus the arriving tiles), so
-// every request is issued between the multiplies of an earlier phase, spread evenly over them: a burst of LDS reads
-// stalls the wave's instruction stream, and the multiplies behind it, until the LDS queue has room.
+// K loop of the MFMA tile kernel for one wave per SIMD, with rings of their own for activations and weights (NSA and NSW stages, NSA = NSW or
+// NSW + 1; tile t in stage t % NSA and t % NSW).  Nothing else runs on the SIMD while a wave waits, and the LDS of the CU is busy most of the
+// time (fragment reads of four waves plus the arriving tiles), so every request is issued between the multiplies of an earlier phase, spread evenly over
+// them: a burst of LDS reads stalls the wave's instruction stream, and the multiplies behind it, until the LDS queue has room.
 //
 // A K tile is two phases, one per k half; the fragments of a whole k half have two register buffers (buffer = k half).
-// While k half 0 of tile kt is multiplied the reads of its k half 1 are issued.  After them every read of the stage
-// has been issued: the wave waits for them and for its part of tile kt+1, and the barrier hands the stage over with
-// half of the tile's multiplies still to come.  While k half 1 is multiplied the loads of tile kt+NS go into the stage
-// just released and the reads of k half 0 of tile kt+1 are issued.  The loads past the last tile repeat the last tile
-// (the number of loads per step, and with it every wait count, stays fixed; nothing reads them).
+// While k half 0 of tile kt is multiplied the reads of its k half 1 are issued.  After them every read of its stages
+// has been issued: the wave waits for them and for its part of tile kt+1, and the barrier hands the stages over with
+// half of the tile's multiplies still to come.  Behind it, while k half 1 is multiplied, the reads of k half 0 of tile kt+1 are issued, and the weights
+// of tile kt+NSW go into the stage just released; the activations of tile kt+NSA-1 follow while k half 0 of the next step's tile is multiplied.  With
+// the loads spread over both halves half as many requests at a time wait for the memory system, and a wave whose request finds no room there stops
+// multiplying.  With NSA = NSW + 1 the activations are on their way for as long as the weights; the 256 x 256 tile has three and two stages, 160 KB,
+// all of the LDS.  The loads past the last tile repeat the last tile (the number of loads per step, and with it every wait count, stays fixed; nothing
+// reads them).
 //
-// Executor interface: load(tile, stage), wait_vmem<L>(), barrier() as for gemm_k_loop, and
-//   fetch_half<H>(stage)                        issue the LDS reads of k half H of the tile in `stage` into buffer H
-//   wait_fetched()                              every LDS read of this wave has landed
-//   mma_half_fetch<H>(stage)                    multiply k half H out of buffer H; between the multiplies issue the reads
-//                                               of k half 1-H of `stage` into the other buffer
-//   mma_half_fetch_load<H>(stage, tile, lstage) the same, and issue the loads of K tile `tile` into stage `lstage`
-// ---------------------------------------------------------------------------------------------------------
-template <int NS = 2, class Ops = void>
-EET_PIPE_FN void gemm_k_loop_interleaved(Ops& op, int nk) {
-    for (int t = 0; t < NS; ++t) op.load(t < nk ? t : nk - 1, t);
-    op.template wait_vmem<NS - 1>();              // tile 0 of this wave has landed ...
-    op.barrier();                                 // ... and everybody else's
-    op.template fetch_half<0>(0);
-    int st = 0;
-    for (int kt = 0; kt < nk; ++kt) {
-        const int st1 = st == NS - 1 ? 0 : st + 1;
-        op.wait_fetched();
-        op.template mma_half_fetch<0>(st);
-        op.wait_fetched();                          // every read of stage st has landed
-        op.template wait_vmem<NS - 2>();          // this wave's part of tile kt+1 has landed
-        op.barrier();                             // ... and everybody else's; stage st is free
-        op.template mma_half_fetch_load<1>(st1, kt + NS < nk ? kt + NS : nk - 1, st);   // (reads past the last tile: stale, never multiplied)
-        st = st1;
-    }
-    op.wait_fetched();                              // the stale reads and the repeated loads too: the epilogue reuses the stages
-    op.template wait_vmem<0>();
-}
-
-// ---------------------------------------------------------------------------------------------------------
-// The same with the tile loads spread over both halves of a step, and rings of their own for activations and weights (NSA and NSW stages, NSA =
-// NSW or NSW + 1; tile t in stage t % NSA and t % NSW).  Behind the barrier of step kt, while k half 1 is multiplied, the weights of tile kt+NSW go into
-// the stage just released; the activations of tile kt+NSA-1 follow while k half 0 of the next step's tile is multiplied.  What it gives: half as many
-// requests at a time wait for the memory system, and a wave whose request finds no room there stops multiplying.  With NSA = NSW + 1 they are on their
-// way for as long as the weights; the 256 x 256 tile has three and two stages, 160 KB, all of the LDS.
-//
-// Executor interface: wait_fetched(), barrier() as above, and
+// Executor interface: barrier() as for gemm_k_loop, and
 //   load_a(tile, stage), load_w(tile, stage)   issue this wave's loads of the activations / the weights of K tile `tile`
 //   wait_loads<LA, LW>()                       the loads of this wave have landed, except those of the newest LA load_a and LW load_w calls
 //   fetch_half<H>(astage, wstage)              issue the LDS reads of k half H into buffer H
+//   wait_fetched()                             every LDS read of this wave has landed
 //   mma_fetch_load_a<H>(astage, wstage, tile, lstage)   multiply k half H out of buffer H; between the multiplies issue the reads of k half 1-H
 //                                              out of the two stages and load_a(tile, lstage); mma_fetch_load_w: load_w
 // ---------------------------------------------------------------------------------------------------------
