@@ -840,7 +840,7 @@ hipError_t launch_attention_prefill(const AttnPrefillArgs& a, const SeqLens& len
     const bool halves = wide && tiles128 <= (!a.causal || a.max_len < 1024 ? 256 : a.max_len < 2048 ? 384 : 512);
     const int bq = halves ? 128 : wide ? 256 : few ? 64 : 128;
     const int pairs = a.heads * a.batch, tiles = (a.max_len + bq - 1) / bq;
-    const dim3 block(wide || halves || (fine && !few) ? 512 : 256);
+    const dim3 block(wide || (fine && !few) ? 512 : 256);
     // In chunks of pairs once the K/V of the launch is more than the memory-side cache holds: with the tiles of all
     // pairs in turn, a pair's K/V then comes from HBM again for every one of its tiles (16 prompts of 1024-2048
     // tokens, 96 heads: 6.3 GB fetched for 1.2 GB of K/V and 0.6 GB of Q).  TFLOP/s by pairs per chunk, one call
@@ -1188,7 +1188,7 @@ __global__ __launch_bounds__(NW * 64) void attn_decode(AttnDecodeArgs a) {
         }
         m = m_new;
     };
-    // blocks wave, wave + 4, ... of the range; two register buffers, loop unrolled by two
+    // blocks wave, wave + NW, ... of the range; two register buffers, loop unrolled by two
     half8v kA[U], vA[U], kB[U], vB[U];
     int j0 = c0 + wave * BK;
     if (j0 < c1) {

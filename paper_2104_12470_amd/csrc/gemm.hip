@@ -364,7 +364,7 @@ __device__ __forceinline__ void wait_vm() {
 }
 
 // The instructions of the tile kernel's K loop.  The loop itself -- which stage is loaded, read, waited for and released
-// when -- is pipe::gemm_k_loop (pipeline.hpp), shared with the host-side audit of the hand-over; this executor supplies the
+// when -- is pipe::gemm_k_loop or pipe::gemm_k_loop_spread (pipeline.hpp), shared with the host-side audit of the hand-over; this executor supplies the
 // instructions, all forced inline.  (Namespace scope because a local class cannot have member templates.)
 //
 // Matrix instruction: v_mfma_f32_16x16x32_f16.  Under this part's power management the 16x16x32 form sustains about a
@@ -547,7 +547,8 @@ struct GemmTileExec {
 // 95.9 -> 88.1, 6758 x 2048 x 8192 208 -> 186, 3262 x 4096 x 16384 351 -> 324, 12288 x 4096 x 12288 932 -> 873, 4096 x 8192 x 32768 2192 -> 1532 (rows
 // 64 KB apart; 128 bytes further 1884 -> 1532), at K = 2048 0 to 2 %; pairs of 128 x 128: 1200 x 6144 x 2048 33.5 -> 31.9; 192 x 128: 700 x 6144 x
 // 2048 24.4 -> 22.4; two K groups, from gemm_k_loop<3>: 300 x 1024 x 4096 17.4 -> 14.3, 100 x 8192 x 2048 11.3 -> 9.9, 300 x 1536 x 1536 9.0 -> 8.2, 160 x 2304 x
-// 768 6.5 -> 6.2 (the weight stream of 17 to 128 rows gains nothing: 120 x 12288 x 12288 79.2 -> 81.7); 96 x 128: 1200 x 2048 x 2048 15.4 -> 14.5, 3054 x 1024 x 4096 29.5 -> 28.4; 128 x 256: 400 x 12288 x 4096 55.4 -> 54.5.  More stages
+// 768 6.5 -> 6.2 (the weight stream of 17 to 128 rows gains nothing: 120 x 12288 x 12288 79.2 -> 81.7, and one row tile over weights past the L2 loses:
+// tile_rules.hpp, reads_weights_past_l2); 96 x 128: 1200 x 2048 x 2048 15.4 -> 14.5, 3054 x 1024 x 4096 29.5 -> 28.4; 128 x 256: 400 x 12288 x 4096 55.4 -> 54.5.  More stages
 // than these gain nothing (96 x 128 in five, 192 x 128 in four, 128 x 256 in four and three: level or 1 to 3 % slower).
 // NTS: the output is stored with the non-temporal hint (outputs of 256 MB and more, which no cache keeps for their reader:
 // 24576 x 49152 x 12288 21.70 -> 21.53 ms, 24576 x 12288 x 12288 5.69 -> 5.59, 8192 x 16384 x 12288 2.436 -> 2.393).

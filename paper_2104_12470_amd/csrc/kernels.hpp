@@ -8,9 +8,6 @@
 namespace eet {
 
 // ---- row-wise kernels (rowops.hip) ---------------------------------------------------------
-// LayerNorm of `rows` rows.  Row r is read from x[in_row_map ? in_row_map[r] : r] and written
-// to y[r].  If bump_lens != nullptr, the block of row r < bump_count also does bump_lens[r] += 1
-// (advances the per-sequence cache length after all readers of this step were enqueued).
 // Words that a launch sets to zero on the side, one to a 128-byte line (counters of a later launch); layernorm_clears says where it can
 constexpr int kClearStride = 32;
 struct ClearLines {
@@ -18,6 +15,9 @@ struct ClearLines {
     int lines;
 };
 bool layernorm_clears(int64_t rows, int width, int lines);
+// LayerNorm of `rows` rows.  Row r is read from x[in_row_map ? in_row_map[r] : r] and written
+// to y[r].  If bump_lens != nullptr, the block of row r < bump_count also does bump_lens[r] += 1
+// (advances the per-sequence cache length after all readers of this step were enqueued).
 hipError_t launch_layernorm(const half_t* x, const int32_t* in_row_map, const half_t* gamma,
                             const half_t* beta, half_t* y, int64_t rows, int width, float eps,
                             int32_t* bump_lens, int bump_count, hipStream_t s, ClearLines clear = {nullptr, 0});
@@ -171,7 +171,7 @@ struct AttnPrefillArgs {
     int max_len;            // max over lens (sizes the grid)
     int causal;             // 1: query i sees keys 0..i; 0: every valid query sees all L_b keys (encoder)
     WeightsAhead ahead;             // launch_attention_prefill only
-    int chunk_pairs, chunk_tiles, tile_blocks;   // set by the launcher (callers leave 0): the grid order of the prefill kernels, and their workgroups that have a tile
+    int chunk_pairs, chunk_tiles, tile_blocks;   // set by the launcher (callers leave 0): pipe::prefill_tile
 };
 hipError_t launch_attention_prefill(const AttnPrefillArgs& a, const SeqLens& lens, hipStream_t s);
 // Unfused form (causal, not packed, S a multiple of 8): raw scores q.k into scores[batch, heads, S, S] for the tiles

@@ -152,9 +152,9 @@ inline bool slices_beat_tiles(int M, int N, int K) {
 // part-filled pays for more than that round: 25082 x 12288 x 49152 (18.4 rounds) 26.3 ms, 24832 rows (18.2 rounds) 26.35 ms,
 // 24576 rows (18 rounds) 24.6 ms; 25082 x 36864 x 12288 (55.1 rounds) 19.1 ms, 24576 rows (54 rounds) 18.2 ms.  Where some
 // number of row tiles gives whole rounds and leaves at most 16 row tiles, the launch is cut there and the rest is a launch
-// of its own, which takes whatever tile_for gives it (506 x 12288 x 49152: 128 x 256 tiles).  The rest is priced in large tiles, at 0.6
-// of their rate below 150 of them; with choose_tile's estimate of the rest in its place the decision is the same for each of 587
-// thousand drawn sizes of two rounds and more.  Returns the rows of the first part, 0 for no cut.  The whole rounds are also what the tile order that lets the XCDs share operand panels
+// of its own, with whatever tile its size takes (506 x 12288 x 49152: 128 x 256).  The rest is priced in large tiles, at 0.6
+// of their rate below 150 of them, and against one launch of large tiles.  (62 sizes that are cut, K = 768 to 6144, as one launch of full_tile's choice: 1.012 of the
+// time, between 0.96 and 1.10; 8246 x 4096 x 1024 76.5 cut, 79.2 in one.)  Returns the rows of the first part, 0 for no cut.  The whole rounds are also what the tile order that lets the XCDs share operand panels
 // needs (pipe::tile_of_block): 20000 x 12288 x 12288, 14.8 rounds, 4.92 ms as one launch.
 inline int rows_in_whole_rounds(int M, int N) {
     constexpr int kCUs = 256;
@@ -171,7 +171,8 @@ inline int rows_in_whole_rounds(int M, int N) {
     return 0;
 }
 
-// The tile of a launch of more than 128 rows, by the time its rounds take.  Measured, us, K in thousands (of 1024):
+// The tile of a launch of more than 128 rows, by the time its rounds take: an odd multiple of 64 columns, K below 768, and what full_tile below leaves to the
+// pairs.  (Prices and examples are from when every size came here and the loads of a step were not spread; the one-per-CU tiles are 1 to 10 % faster since.)  Measured, us, K in thousands (of 1024):
 //   256 x 256, one workgroup per CU                    10 + 21.5 K   per round of up to 256 tiles
 //   128 x 256 (three stages), 192 x 128 (three stages), 128 x 128 (three), 96 x 128 (four), one per CU
 //                                       9 + 12 K, 7 + 9.2 K, 5 + 7.9 K, 4.5 + 6.9 K   for up to 256 tiles (one round only)
@@ -266,10 +267,11 @@ inline bool reads_weights_past_l2(int M, int N, int K, int tile_rows) {
 //   192 x 256  10.2 + 15.5 K  7.4 + 17.3 K      128 x 128  5.6 + 6.4 K   3.9 + 7.1 K
 //   160 x 256  9.6 + 13 K     7.3 + 14.7 K       96 x 128  5.5 + 5.2 K   3.6 + 5.8 K
 // a part-filled last round takes 0.7 of a full one and 0.3 of what it fills.  Over those sizes the time falls to 0.967 of what tile_for's choice
-// takes (the best tile of each: 0.962; the worst of them 1.09), us: 3054 x 3072 x 12288 235 -> 190 (192 x 256), 2140 x 4096 x 4096 82 -> 70, 1700 x 12288 x 4096
+// takes (the best tile of each: 0.962; the worst of them 1.09, since the pairs below come first 1.03 to 1.05, at K below 1216 and part-filled
+// last rounds), us: 3054 x 3072 x 12288 239 -> 198 (160 x 256), 2140 x 4096 x 4096 82 -> 70, 1700 x 12288 x 4096
 // 167 -> 144, 6758 x 2048 x 2048 60 -> 54 (224 x 256), 700 x 5120 x 1280 16.2 -> 13.3 (128 x 128).  Where it stops: at K = 512 the pairs of tile_for
-// are level or ahead (8200 x 2048 x 512 27.8 / 30.8, 3800 x 2048 x 512 14.4 / 15.3); 64 columns left over, which leave part of every last tile
-// idle, keep the tile they have; the tiles shared by two groups of waves are ahead of all of these (900 x 1280 x 5120 28.2 / 31.3, 700 x 2048 x
+// are level or ahead (8200 x 2048 x 512 27.8 / 30.8, 3800 x 2048 x 512 14.4 / 15.3); 64 columns left over keep tile_for's choice (110 such sizes, K = 768 to 6144, with these tiles
+// instead: 0.963 of the time, between 0.79 and 1.085); the tiles shared by two groups of waves are ahead of all of these (900 x 1280 x 5120 28.2 / 31.3, 700 x 2048 x
 // 8192 39.4 / 43.6).  Tiles of 128 columns are for one round: where they would be the cheapest in more, and 192 x 128 below K = 1024 throughout, the pairs of tile_for
 // come first if their own price is the lower one (one round of 128 x 128 or 192 x 128 in two / as pairs: 1031 x 10880 x 1152 40.9 / 34.7, 4290 x 1920 x 1408 33.2 / 28.4, 3302
 // x 2432 x 832 21.3 / 18.9, 8223 x 896 x 1856 35.5 / 33.5; 161 sizes of the first kind 1.04 / 0.98 of what tile_for's choice took before; below K = 1024, 2275 x 10880 x 896
