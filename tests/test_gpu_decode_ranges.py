@@ -49,11 +49,14 @@ def test_steps_against_the_oracle(heads, d, lens, max_seq):
     layer.close()
 
 
-def test_recorded_step():
-    lens = [500, 690]
-    eet, w, W, cfg, rows, oracle = setup(18, 128, lens, 720)
+@pytest.mark.parametrize("heads,d,lens,max_seq", [(18, 128, [500, 690], 720), (32, 128, [767, 900, 30, 1279], 1300)])
+def test_recorded_step(heads, d, lens, max_seq):
+    """Two layers of a stack on one set of counters and partials (and 128 pairs, which have none), directly and recorded, against two oracle layers."""
+    eet, w, W, cfg, rows, oracle = setup(heads, d, lens, max_seq)
+    second = setup(heads, d, lens, max_seq)[-1]      # the stack's second layer: the same weights and cache
     direct, graph = eet.DecoderStack(cfg, [W, W], use_graph=False), eet.DecoderStack(cfg, [W, W])
-    tok = dev(wl.decode_embeddings(w, 0))
+    x = wl.decode_embeddings(w, 0)
+    tok = dev(x)
     out = [torch.empty_like(tok) for _ in range(2)]
     stream = torch.cuda.Stream()
     torch.cuda.synchronize()
@@ -66,6 +69,7 @@ def test_recorded_step():
             graph.decode_step(tok, out[1])
             stream.synchronize()
             assert np.array_equal(host(out[0]).view(np.uint16), host(out[1]).view(np.uint16)), k
-            assert np.isfinite(host(out[0]).astype(np.float32)).all()
+            between = oracle.decode_step(x).astype(np.float16)           # the first layer's output as the second one reads it
+            gate(host(out[0]), second.decode_step(between), f"step {k}")
     direct.close()
     graph.close()

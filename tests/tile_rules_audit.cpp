@@ -42,6 +42,8 @@ std::string route(int M, int N, int K, bool sliceable, bool once) {
     if (eet::rows_stream_uncut(M, N, K, once)) return "rows " + std::to_string(M <= 32 && K % 256 != 0 ? 64 : eet::rows_tile(M));
     if (sliceable && eet::slices_beat_tiles(M, N, K)) return "slices";
     if (const int head = eet::rows_in_whole_rounds(M, N)) return std::to_string(head) + " + " + route(M - head, N, K, sliceable, once);
+    const char* full[] = {nullptr, "256x256 x2", "224x256 x2", "192x256 x2", "160x256 x3", "128x256 x3", "192x128 x3", "128x128 x3", "96x128 x4"};
+    if (const eet::FullTile t = eet::full_tile(M, N, K)) return full[t];
     return tile_name(eet::tile_for(M, N, K));
 }
 
