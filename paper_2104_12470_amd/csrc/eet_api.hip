@@ -246,7 +246,9 @@ static int enqueue_prefill(eet_layer* L, const SeqLens& lens, int batch, int pad
     GemmArgs g{};
     // a short prompt reads every weight once, as a decode step does: with the non-temporal hint where nothing keeps them until
     // the next call anyway (enqueue_decode has the reasons)
-    const size_t stack_weights = (size_t)(L->stack_layers > 0 ? L->stack_layers : 1) * 2 * ((size_t)4 * H * H + (size_t)2 * H * F);
+    const size_t layers = L->stack_layers > 0 ? L->stack_layers : 1;
+    const size_t stack_weights = layers * 2 * ((size_t)4 * H * H + (size_t)2 * H * F);
+    const size_t stack_kv = (causal ? layers : 1) * 4 * H * (size_t)T;       // (an encoder's layers share one region)
     const size_t weights_ahead = ((size_t)H * H + (size_t)H * F) * sizeof(half_t);
     const int once = T <= 128 && stack_weights > kMemorySideCacheBytes;
     g.x = bufA; g.w = (const half_t*)L->w.w_qkv; g.bias = (const half_t*)L->w.b_qkv; g.y = bufB;
@@ -260,7 +262,7 @@ static int enqueue_prefill(eet_layer* L, const SeqLens& lens, int batch, int pad
     at.q = bufB; at.ctx = bufA; at.k_cache = kc; at.v_cache = vc;
     at.batch = batch; at.heads = c.heads; at.d = L->d; at.capacity = c.max_seq; at.hidden = H;
     at.packed = 1; at.S = padded_len; at.max_len = max_len; at.causal = causal ? 1 : 0;
-    if (prefill_touches_weights(T, weights_ahead, stack_weights)) {
+    if (prefill_touches_weights(T, weights_ahead, stack_weights, stack_kv)) {
         at.ahead.at[0] = L->w.w_o; at.ahead.lines[0] = (uint32_t)((size_t)H * H * sizeof(half_t) / 128);
         at.ahead.at[1] = L->w.w_fc2; at.ahead.lines[1] = (uint32_t)((size_t)H * F * sizeof(half_t) / 128);
         at.ahead.blocks = kAheadBlocks;

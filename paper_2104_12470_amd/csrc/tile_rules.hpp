@@ -305,14 +305,17 @@ inline FullTile full_tile(int M, int N, int K) {
 // both are read as coldly: their launches have few K steps.)  us without / with, `ahead` bytes of those two matrices:
 //   stacks up to hidden 1536 (24 MB): those prompts 3167 / 3012, as an encoder's sentences of 64 to 192 2550 / 2360; 24 x 512 1720 / 1634; 12 x 768 1249
 //     / 1140; 12 x 1280 2069 / 1945; 10 x 1536 2266 / 2206; 24 x 1024, one prompt of 37 tokens 1015 / 988, 128 of 8 to 32 2797 / 2612, two of 2000 to 4000
-//     (12 layers) 3783 / 3710; nothing to gain where the weights stay cached (1 x 1024 119.5 / 119.8), nor beyond 6000 rows (12 x 1024, 12000 rows 4730 / 4740;
-//     10 x 1536, 8200 rows 4657 / 4685);
+//     (12 layers) 3783 / 3710; nothing to gain beyond 6000 rows (12 x 1024, 12000 rows 4730 / 4740; 10 x 1536, 8200 rows 4657 / 4685);
+//   nor where the weights are still cached from the call before: by the weights of all layers and the K/V that the call writes, drawn stacks of 1 to 24 layers, hidden 256
+//     to 1600, 20 to 6000 rows, without / with: up to 100 MB 0.994 (127 of them, down to 0.963), 100 to 180 0.999 (61), 180 to 210 1.007 (19), 210 to 240 1.017, 240 to
+//     270 1.028, more 1.04;
 //   up to 72 MB, stacks that no cache holds, 129 to 2048 rows: 8 x 2048, 600 rows 1080 / 986, 1500 1694 / 1615 (of heads of 128, 900 rows, 1183 / 1190);
 //     5 x 2560, 600 887 / 852; 4 x 3072 x 8192 705 / 692; 3054 rows of 2048 2640 / 2674, 60 rows 472 / 514;
 //   more take longer to read than the attention lasts (2 x 4096, 500 rows 625 / 656).
 constexpr int kAheadBlocks = 128;      // (64: 3051 us for those prompts, 256 and 512 as 128; one prompt of 200 tokens 1231, with 256 1244)
-inline bool prefill_touches_weights(int64_t rows, size_t ahead, size_t stack) {
+inline bool prefill_touches_weights(int64_t rows, size_t ahead, size_t stack, size_t kv) {
     if (rows <= 16) return false;          // (7 x 1024, 9 rows 191 / 194)
+    if (stack + kv <= kMemorySideCacheBytes / 4 * 3) return false;
     if (ahead <= (size_t)24 << 20) return rows <= 6144;
     return ahead <= (size_t)72 << 20 && stack > kMemorySideCacheBytes && rows > 128 && rows <= 2048;
 }
