@@ -10,7 +10,8 @@ are resident in HBM before the timed region.  Prints ONE JSON line.
 
 The line's metric, value and roofline are those of --workload (default: cfg5b, the largest configuration, where the
 60 % HBM / 50 % MFMA targets are defined); the workloads of --also are timed the same way, with fewer passes, and
-reported under "other_workloads" in the same line, each with its own roofline records.
+reported under "other_workloads" in the same line.  The line is kept to about five thousand characters, for readers that keep no more of the output;
+--records PATH writes every record, unabridged, as JSON.
 """
 from __future__ import annotations
 
@@ -69,6 +70,7 @@ def parse():
     p.add_argument("--roofline-only", action="store_true",
                    help="skip the timed pass and the CPU baseline: only the per-kernel measurement plus one plain "
                         "256 MiB device copy (the reference for scaling FETCH_SIZE / WRITE_SIZE counters)")
+    p.add_argument("--records", help="file that all records go to, unabridged, as JSON")
     return p.parse_args()
 
 
@@ -486,6 +488,31 @@ def cpu_baseline(w, wl, budget_s=25.0, min_s=10.0):
                       f"{w.decode_steps} decode steps each; {total:.1f} s of CPU work, {tokens} layer-tokens"}
 
 
+def short_name(kernel):
+    return kernel.split(":")[0].split(" (")[0]
+
+
+def printed(rec):
+    """What the line says of the records: numbers to six digits, the kernels beside the first by name, rate, fraction of the peak and
+    time per launch, the other workloads by throughput, times and the fraction of each kernel."""
+    def rounded(x):
+        if isinstance(x, float):
+            return float(f"{x:.6g}")
+        if isinstance(x, dict):
+            return {k: rounded(v) for k, v in x.items()}
+        return [rounded(v) for v in x] if isinstance(x, list) else x
+
+    out = dict(rec)
+    out["roofline_other_kernels"] = [{"kernel": short_name(r["kernel"]), **{k: r[k] for k in ("achieved", "unit", "frac", "avg_launch_us")}}
+                                     for r in rec["roofline_other_kernels"]]
+    if "other_workloads" in rec:
+        out["other_workloads"] = {
+            name: {"value": m["value"], "ms_per_step": m["ms_per_step"], "prefill_ms": m["config"]["prefill_ms"], "decode_ms": m["config"]["decode_ms"],
+                   "roofline_frac": {short_name(r["kernel"]): round(r["frac"], 3) for r in [m["roofline"]] + m["roofline_other_kernels"]}}
+            for name, m in rec["other_workloads"].items()}
+    return rounded(out)
+
+
 def workload_text(w, model=False):
     return (f"{w.name}: {w.layers} layer(s), hidden {w.hidden}, heads {w.heads}, ffn {w.ffn}, batch {w.batch}, prompts "
             f"{w.len_lo}-{w.len_hi} padded to {w.padded_len}, {w.decode_steps} decode steps, cache {w.max_seq}" +
@@ -586,7 +613,10 @@ def main():
     torch.cuda.empty_cache()
     if not a.no_cpu_baseline and not a.model:      # the timed oracle sample is the layer stack's, not the model's
         rec["cpu_baseline"] = cpu_baseline(w, wl)
-    print(json.dumps(rec))
+    if a.records:
+        with open(a.records, "w") as f:
+            json.dump(rec, f, indent=1)
+    print(json.dumps(printed(rec)))
 
 
 if __name__ == "__main__":
