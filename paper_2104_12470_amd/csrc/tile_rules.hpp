@@ -267,15 +267,16 @@ inline bool reads_weights_past_l2(int M, int N, int K, int tile_rows) {
 //   192 x 256  10.2 + 15.5 K  7.4 + 17.3 K      128 x 128  5.6 + 6.4 K   3.9 + 7.1 K
 //   160 x 256  9.6 + 13 K     7.3 + 14.7 K       96 x 128  5.5 + 5.2 K   3.6 + 5.8 K
 // a part-filled last round takes 0.7 of a full one and 0.3 of what it fills.  Over those sizes the time falls to 0.967 of what tile_for's choice
-// takes (the best tile of each: 0.962; the worst of them 1.09, since the pairs below come first 1.03 to 1.05, at K below 1216 and part-filled
-// last rounds), us: 3054 x 3072 x 12288 239 -> 198 (160 x 256), 2140 x 4096 x 4096 82 -> 70, 1700 x 12288 x 4096
+// takes (the best tile of each: 0.962; the worst of them 1.09, before the pairs below came first), us: 3054 x 3072 x 12288 239 -> 198 (160 x 256), 2140 x 4096 x 4096 82 -> 70, 1700 x 12288 x 4096
 // 167 -> 144, 6758 x 2048 x 2048 60 -> 54 (224 x 256), 700 x 5120 x 1280 16.2 -> 13.3 (128 x 128).  Where it stops: at K = 512 the pairs of tile_for
 // are level or ahead (8200 x 2048 x 512 27.8 / 30.8, 3800 x 2048 x 512 14.4 / 15.3); 64 columns left over keep tile_for's choice (110 such sizes, K = 768 to 6144, with these tiles
 // instead: 0.963 of the time, between 0.79 and 1.085); the tiles shared by two groups of waves are ahead of all of these (900 x 1280 x 5120 28.2 / 31.3, 700 x 2048 x
 // 8192 39.4 / 43.6).  Tiles of 128 columns are for one round: where they would be the cheapest in more, and 192 x 128 below K = 1024 throughout, the pairs of tile_for
 // come first if their own price is the lower one (one round of 128 x 128 or 192 x 128 in two / as pairs: 1031 x 10880 x 1152 40.9 / 34.7, 4290 x 1920 x 1408 33.2 / 28.4, 3302
 // x 2432 x 832 21.3 / 18.9, 8223 x 896 x 1856 35.5 / 33.5; 161 sizes of the first kind 1.04 / 0.98 of what tile_for's choice took before; below K = 1024, 2275 x 10880 x 896
-// 56.1 / 51.4, 4802 x 2432 x 832 29.0 / 27.6).  224 rows only where at most one in sixteen of their rows is padding: beyond that 256 are as fast or the next smaller height is.
+// 56.1 / 51.4, 4802 x 2432 x 832 29.0 / 27.6).  Up to K = 1152 taller tiles in more than one round give way as well where the general choice has pairs: its prices
+// are short of their part-filled rounds there (5377 x 6016 x 768 with a residual 72.3 / 66.9, 6000 x 3072 x 768 38.2 / 35.2; 127 sizes 1.018 / 1; K = 1216 to 1536, 41 sizes, 0.984, from
+// 1600 on 0.95).  224 rows only where at most one in sixteen of their rows is padding: beyond that 256 are as fast or the next smaller height is.
 enum FullTile { kFullNone, kFull256, kFull224x256, kFull192x256, kFull160x256, kFull128x256, kFull192, kFull128, kFull96 };
 inline FullTile full_tile(int M, int N, int K) {
     if (M <= 128 || N % 128 != 0 || K < 768 || few_tiles(M, N, K)) return kFullNone;
@@ -286,15 +287,20 @@ inline FullTile full_tile(int M, int N, int K) {
     const double k = K / 1024.0;
     double best = 1e30, best_narrow = 1e30;
     FullTile choice = kFullNone;
+    int64_t choice_tiles = 0;
     for (const auto& t : kTiles) {
         const int64_t tm = (M + t.rows - 1) / t.rows, tiles = tm * ((N + t.cols - 1) / t.cols), whole = tiles / 256, rest = tiles % 256;
         if (t.tile == kFull224x256 && (tm * t.rows - M) * 16 > tm * t.rows) continue;
         const double us = tiles <= 256 ? t.one + t.one_k * k : ((double)whole + (rest == 0 ? 0.0 : 0.7 + 0.3 * (double)rest / 256)) * (t.each + t.each_k * k);
         if (t.cols == 128 && tiles > 256) best_narrow = us < best_narrow ? us : best_narrow;
-        else if (us < best) { best = us; choice = t.tile; }
+        else if (us < best) { best = us; choice = t.tile; choice_tiles = tiles; }
     }
     if ((best_narrow < best || K < 1024) && pair_us(M, N, k, 192) < best) return kFullNone;
     if (best_narrow < best && pair_us(M, N, k, 128) < best) return kFullNone;
+    if (K <= 1152 && choice_tiles > 256) {
+        const TileChoice t = choose_tile(M, N, K);
+        if (t == kTile192Pair || t == kTile128Pair) return kFullNone;
+    }
     return choice;
 }
 

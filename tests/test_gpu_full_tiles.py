@@ -19,7 +19,7 @@ ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 # (M, K, N, tile)
 SHAPES = [(2743, 768, 4992, "256x256"), (2549, 832, 4992, "224x256"), (2161, 768, 4992, "192x256"), (1773, 896, 4992, "160x256"), (1385, 768, 4992, "128x256"),
-          (1093, 768, 4224, "192x128"), (1289, 1088, 2944, "128x128"), (1153, 832, 2176, "96x128"), (5377, 768, 6016, "rounds")]
+          (1093, 768, 4224, "192x128"), (1289, 1088, 2944, "128x128"), (1153, 832, 2176, "96x128"), (5377, 1216, 6016, "rounds")]      # (up to K = 1152 these rounds are the pairs')
 
 ASK = r"""
 #include <cstdio>
@@ -71,9 +71,10 @@ def test_pairs_that_nearly_fill_a_round_are_not_taken_apart(ask):
     """Sizes of 420 to 512 tiles of which two share a CU, measured 5 to 17 % slower as two rounds of one tile per CU, and below K = 1024 5 to 9 % slower on taller ones;
     a few tiles more or less on either side, and the tall tiles stay where they are ahead."""
     pairs = [((1031, 10880, 1152), "192x128"), ((4290, 1920, 1408), "128x128"), ((3302, 2432, 832), "128x128"), ((5545, 1408, 1728), "128x128"),
-             ((8223, 896, 1856), "128x128"), ((2275, 10880, 896), "192x128"), ((4802, 2432, 832), "192x128"), ((8799, 1408, 960), "192x128")]
+             ((8223, 896, 1856), "128x128"), ((2275, 10880, 896), "192x128"), ((4802, 2432, 832), "192x128"), ((8799, 1408, 960), "192x128"),
+             ((5377, 6016, 768), "128x128"), ((6000, 3072, 768), "192x128"), ((5060, 6528, 832), "128x128"), ((5414, 2944, 1024), "128x128"), ((2109, 7680, 1152), "128x128")]
     assert [(full, old) for _, full, old in ask([s for s, _ in pairs])] == [("none", t) for _, t in pairs]
-    tall = [((2140, 4096, 4096), "160x256"), ((1137, 15360, 7232), "160x256"), ((3054, 3072, 12288), "160x256"), ((6758, 2048, 2048), "224x256"), ((1153, 2176, 832), "96x128")]
+    tall = [((5377, 6016, 1216), "192x256"), ((2140, 4096, 4096), "160x256"), ((1137, 15360, 7232), "160x256"), ((3054, 3072, 12288), "160x256"), ((6758, 2048, 2048), "224x256"), ((1153, 2176, 832), "96x128")]
     assert [full for _, full, _ in ask([s for s, _ in tall])] == [t for _, t in tall]
 
 
