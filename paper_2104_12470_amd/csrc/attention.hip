@@ -860,8 +860,9 @@ hipError_t launch_attention_prefill(const AttnPrefillArgs& a, const SeqLens& len
         chunk = chunk < 16 ? 16 : chunk > 48 ? 48 : chunk;
     }
     w.chunk_pairs = chunk < pairs ? chunk : 0;
+    if (w.chunk_pairs == 0 && tiles > 60000) w.chunk_pairs = pairs;       // (more rows than the second dimension of a grid is sure to take)
     w.chunk_tiles = tiles;
-    w.tile_blocks = w.chunk_pairs ? (pairs + chunk - 1) / chunk * chunk * tiles : 0;
+    w.tile_blocks = w.chunk_pairs ? (pairs + w.chunk_pairs - 1) / w.chunk_pairs * w.chunk_pairs * tiles : 0;
     const bool ahead = w.ahead.blocks > 0;
     const dim3 grid = w.chunk_pairs ? dim3(w.tile_blocks + w.ahead.blocks) : dim3(pairs, tiles + (w.ahead.blocks + pairs - 1) / pairs);
 #define EET_PREFILL(K, ...) do { if (ahead) hipLaunchKernelGGL((K<__VA_ARGS__, true>), grid, block, 0, s, w, lens); \

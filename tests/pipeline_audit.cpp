@@ -400,9 +400,9 @@ int main() {
     // the grids of a prefill attention: every tile of every pair once, the workgroups past them numbered from 0
     for (int pairs : {1, 5, 17, 48, 130, 1071})
         for (int tiles : {1, 2, 7})
-            for (int chunk : {0, 16, 24, 48})
+            for (int chunk : {0, 16, 24, 48, pairs})
                 for (int extra : {0, 128}) {
-                    if (chunk >= pairs) continue;
+                    if (chunk > pairs) continue;
                     const int tile_blocks = chunk ? (pairs + chunk - 1) / chunk * chunk * tiles : 0;
                     const int gx = chunk ? tile_blocks + extra : pairs, gy = chunk ? 1 : tiles + (extra + pairs - 1) / pairs;
                     std::vector<int> seen((size_t)pairs * tiles, 0), extras((size_t)gx * gy, 0);
