@@ -158,16 +158,19 @@ __device__ __forceinline__ void epilogue_rows(const GemmArgs& a, const int (&m)[
     }
 }
 
-// The tiles of which two workgroups share a CU (192 x 128 and 128 x 128 with two stages, under either schedule) turn theirs around through LDS all the same,
-// unless GELU comes with it: the stages are free, a CU has the other workgroup to go on with, and whole lines out in one go get in its way less.  us, straight
+// A bias alone or with a residual out of the tiles of which two workgroups share a CU (192 x 128 and 128 x 128 with two stages, under either schedule) goes
+// out through LDS all the same: the stages are free, a CU has the other workgroup to go on with, and whole lines out in one go get in its way less.  us, straight
 // out / through LDS (rows x N x K): with a residual 1066 x 7232 x 128 10.4 / 9.2, 367 x 13952 x 128 9.25 / 8.4, 1753 x 11904 x 320 1.07 / 0.99 of what it
 // took when all tiles went through LDS; a bias alone 5535 x 2176 x 128 1.06 / 1.01, 523 x 14336 x 448 1.06 / 1.01; from K = 512 on level; 59 of 128 x 128 tiles with a
-// residual and spread loads, K = 512 to 3072, 0.989 / 0.968 of that; with GELU 1667 x 2816 x 128 7.8 / 8.7, 2319 x 3328 x 384 0.95 / 1.0.  The same for 128 x 64 tiles, three to a CU: level with a residual or a bias, 0.96 / 1.01 with GELU.
+// residual and spread loads, K = 512 to 3072, 0.989 / 0.968 of that.  GELU and the scatter to Q and the caches go straight out: GELU 1667 x 2816 x 128
+// 7.8 / 8.7, 2319 x 3328 x 384 0.95 / 1.0; Q, K and V by 192 x 128 tiles K = 320 14.8 / 18.0, 128 x 128 tiles K = 256 11.4 / 13.4 and 24.0 / 27.6, spread
+// loads K = 1088 22.4 / 23.9.  128 x 64 tiles, three to a CU, all go straight out: level with a residual or a bias, 0.96 / 1.01 with GELU.
 //
 // `stage`: AM*16*128 bytes of LDS no other wave touches, a row of 64 columns in 128 bytes, its sixteen 8-byte units XOR-permuted by (row/2)%16 so
 // that both access patterns spread over all banks.  Whole-line pattern: row it*8 + lane/8, 16-byte chunk lane%8.
 template <int AM, int EPI>
 __device__ __forceinline__ void epilogue_via_lds(const GemmArgs& a, const float4v (&acc)[AM][4], char* stage, int mw, int nw, int lane) {
+    static_assert(EPI == EPI_BIAS || EPI == EPI_BIAS_RES, "outputs that are better through LDS");
     constexpr int R = AM * 2;
     const int M = a.M, N = a.N, r8 = lane >> 3, c8 = lane & 7;
     if (nw >= N) return;
@@ -216,20 +219,7 @@ __device__ __forceinline__ void epilogue_via_lds(const GemmArgs& a, const float4
         half8v v = *reinterpret_cast<const half8v*>(stage + row * 128 + ((c8 ^ (sw >> 1)) * 16));
         if (sw & 1) v = __builtin_shufflevector(v, v, 4, 5, 6, 7, 0, 1, 2, 3);
         const int n = nw + c8 * 8;
-        half_t* dst;
-        if constexpr (EPI == EPI_QKV) {
-            const int which = n / a.hidden, c = n - which * a.hidden;                    // 0 = Q, 1 = K, 2 = V
-            if (which == 0) {
-                dst = a.y + (int64_t)(mw + row) * a.hidden + c;
-            } else {
-                if (r1[it] < 0 || r1[it] >= a.max_seq) continue;                         // see epilogue_apply: never outside the sequence's slots
-                const int g = c / a.d;
-                dst = (which == 1 ? a.k_cache : a.v_cache) + (((int64_t)r0[it] * a.heads + g) * a.max_seq + r1[it]) * a.d + (c - g * a.d);
-            }
-        } else {
-            dst = a.y + (int64_t)r0[it] * (a.ldy ? a.ldy : N) + n;
-        }
-        *reinterpret_cast<half8v*>(dst) = v;
+        *reinterpret_cast<half8v*>(a.y + (int64_t)r0[it] * (a.ldy ? a.ldy : N) + n) = v;
     }
 }
 
@@ -682,7 +672,7 @@ __global__ __launch_bounds__(WGM* WGN* KS * 64, BM == 192 && BN == 128 && NS == 
         }
         return;
     }
-    if constexpr (NS == 2 && BN == 128 && EPI != EPI_BIAS_GELU) {
+    if constexpr (NS == 2 && BN == 128 && (EPI == EPI_BIAS || EPI == EPI_BIAS_RES)) {
         __syncthreads();                                  // every wave is done with the operand stages
         static_assert(NW * WM * 128 <= (int)sizeof(As) && !NTS, "turn-around areas");
         epilogue_via_lds<AM, EPI>(a, acc, reinterpret_cast<char*>(&As[0][0]) + wave * WM * 128, m0 + wm0, n0 + wn0, lane);

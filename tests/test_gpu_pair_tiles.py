@@ -1,5 +1,5 @@
-"""Tiles of which two workgroups share a CU (192 x 128 and 128 x 128 with two LDS stages): their output goes through LDS unless GELU comes with
-it.  Every kind of output at the smallest K and at a larger one, with ragged rows and a half column tile: a bias alone, a residual, rows with strides,
+"""Tiles of which two workgroups share a CU (192 x 128 and 128 x 128 with two LDS stages): a bias alone or with a residual goes out through
+LDS, GELU and a prompt's cache rows straight.  Every kind of output at the smallest K and at a larger one, with ragged rows and a half column tile: a bias alone, a residual, rows with strides,
 and a prompt's cache rows in both layouts.  Which tile a shape takes is asked of the rules that the library compiles."""
 import os
 import shutil
