@@ -192,7 +192,7 @@ __global__ __launch_bounds__(256, CAUSAL && AHEAD ? 4 : 2) void attn_prefill(Att
 #pragma unroll
                 for (int r = 0; r < 16; ++r) tmax = fmaxf(tmax, st[jb][r]);
         }
-        tmax = fmaxf(tmax, __shfl_xor(tmax, 32, kWave));
+        tmax = max_xor32(tmax);
         // m is the reference of the exponentials in the exp2 domain (score * c): p = 2^(s*c - m), one FMA + one
         // v_exp_f32.  It is moved (and the sum and the accumulators rescaled) only when some row's maximum has
         // grown by more than kSlack since, so p stays below 2^kSlack -- as exact in fp16 and fp32 as below 1 --
@@ -238,7 +238,7 @@ __global__ __launch_bounds__(256, CAUSAL && AHEAD ? 4 : 2) void attn_prefill(Att
                 }
     }
 
-    l += __shfl_xor(l, 32, kWave);
+    l = sum_xor32(l);
     if (!row_ok) return;
     const float inv = 1.0f / l;
     half_t* op = a.ctx + (int64_t)(row0 + i) * a.hidden + g * D;
@@ -304,19 +304,6 @@ __device__ __forceinline__ void wait_vmem() {
     if (N == 2) asm volatile("s_waitcnt vmcnt(2)" ::: "memory");
     if (N == 4) asm volatile("s_waitcnt vmcnt(4)" ::: "memory");
 }
-// lane ^ 32 maximum without the LDS: v_permlane32_swap exchanges the upper half of its first operand
-// with the lower half of its second, so the two results hold, for every lane, its own value and its partner's.
-// The two elements are copied into scalars before the bit casts: __builtin_bit_cast applied to the vector element
-// r[1] directly reads element 0 with this compiler, which silently turned the maximum into "the value of the lower
-// lane" (a reference of the exponentials that ignored half of each row's keys: exact results until a row's scores
-// span more than the 16 bits of headroom fp16 has above one, then infinities).
-__device__ __forceinline__ float max_xor32(float x) {
-    const unsigned u = __builtin_bit_cast(unsigned, x);
-    const auto r = __builtin_amdgcn_permlane32_swap(u, u, false, false);
-    const unsigned r0 = r[0], r1 = r[1];
-    return fmaxf(__builtin_bit_cast(float, r0), __builtin_bit_cast(float, r1));
-}
-
 // Executor of pipe::attn_kv_loop for the kernel below: the tile loads and the arithmetic of a step are the kernel's
 // own lambdas, the waits and the barrier are the instructions themselves.  PAIR = load instructions of one
 // load_k + load_v pair of a wave.
@@ -632,7 +619,7 @@ __global__ __launch_bounds__(512) void attn_prefill_wide(AttnPrefillArgs a, SeqL
                 for (int e = 0; e < 4; ++e) o[db][rg * 4 + e] = o[db][rg * 4 + e] * mine + p[e] * theirs;
             }
     }
-    l += __shfl_xor(l, 32, kWave);
+    l = sum_xor32(l);
     if (i >= L) return;
     const float inv = 1.0f / l;
     half_t* op = a.ctx + (int64_t)(row0 + i) * a.hidden + g * D;
@@ -660,13 +647,6 @@ __global__ __launch_bounds__(512) void attn_prefill_wide(AttnPrefillArgs a, SeqL
 // one of 37 tokens 4.5 -> 4.1; 128 of 256-512, 32 heads 281 -> 272; heads of 128: 16 of 64-192, 32 heads 28.3 -> 24.6, 8 of
 // 256-512, 16 heads 23.1 -> 21.3, 64 of 256-512, 32 heads 266 -> 247.  Longer prompts read every fragment for half as many
 // rows: 16 of 512-1024, 32 heads of 64 85 -> 91, 16 of 1024-2048, 64 heads 552 -> 588; they stay where they were.
-__device__ __forceinline__ float max_xor16(float x) {
-    const unsigned u = __builtin_bit_cast(unsigned, x);
-    const auto r = __builtin_amdgcn_permlane16_swap(u, u, false, false);
-    const unsigned r0 = r[0], r1 = r[1];                     // (copied first: see max_xor32)
-    return fmaxf(__builtin_bit_cast(float, r0), __builtin_bit_cast(float, r1));
-}
-
 template <int D, bool CAUSAL, int NW, bool AHEAD>
 __global__ __launch_bounds__(64 * NW) void attn_prefill16(AttnPrefillArgs a, SeqLens lens) {
     constexpr int BQ = 16 * NW, BKV = 64, KK = D / 32, DB = D / 16;
@@ -802,8 +782,7 @@ __global__ __launch_bounds__(64 * NW) void attn_prefill16(AttnPrefillArgs a, Seq
             __syncthreads();
         }
     }
-    l += __shfl_xor(l, 16, kWave);
-    l += __shfl_xor(l, 32, kWave);
+    l = sum_xor32(sum_xor16(l));
     if (!row_ok) return;
     const float inv = 1.0f / l;
     half_t* op = a.ctx + (int64_t)(row0 + i) * a.hidden + g * D + G * 4;
@@ -1069,11 +1048,6 @@ hipError_t launch_attention_apply(const AttnPrefillArgs& a, const SeqLens& lens,
 //
 // With more than one range per (sequence, head) each workgroup writes a partial (max, sum, values), and the last of the pair merges them
 // (AttnDecodeArgs::arrived), or the projection that follows, or attn_decode_combine.
-template <int CTRL>
-__device__ __forceinline__ float dpp_f(float x) {
-    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), CTRL, 0xf, 0xf, false));
-}
-
 // Column dd of a pair's key ranges, merged in range order: common maximum, rescaled sums, one division.  All loads of up to 16 ranges are requested before they
 // are combined.  AGENT: loads at agent scope, of words that other workgroups of the launch have stored so.
 template <int D, bool AGENT>
@@ -1168,10 +1142,10 @@ __global__ __launch_bounds__(NW * 64) void attn_decode(AttnDecodeArgs a) {
             float d = 0.f;
 #pragma unroll
             for (int e = 0; e < 4; ++e) d = __builtin_amdgcn_fdot2(half2v{kf[u][2 * e], kf[u][2 * e + 1]}, q2[e], d, false);
-            d += dpp_f<0xb1>(d);                          // lane ^ 1
-            d += dpp_f<0x4e>(d);                          // lane ^ 2
-            d += dpp_f<0x141>(d);                         // the other quad of 8
-            if (LPK == 16) d += dpp_f<0x140>(d);          // the other half of 16
+            d += dpp<0xb1>(d);                          // lane ^ 1
+            d += dpp<0x4e>(d);                          // lane ^ 2
+            d += dpp<0x141>(d);                         // the other quad of 8
+            if (LPK == 16) d += dpp<0x140>(d);          // the other half of 16
             sc[u] = (j0 + u * KPI + kslot < c1) ? d * c : -INFINITY;
             mx = fmaxf(mx, sc[u]);
         }
@@ -1209,23 +1183,20 @@ __global__ __launch_bounds__(NW * 64) void attn_decode(AttnDecodeArgs a) {
     }
     // merge the KPI lane groups of the wave: common maximum, rescale, sum
     float mw = m;
-    if (LPK == 8) mw = fmaxf(mw, dpp_f<0x128>(mw));      // lane ^ 8 (rotate the row of 16 by 8)
-    mw = fmaxf(mw, __shfl_xor(mw, 16, kWave));
-    mw = fmaxf(mw, __shfl_xor(mw, 32, kWave));
+    if (LPK == 8) mw = fmaxf(mw, dpp<0x128>(mw));      // lane ^ 8 (rotate the row of 16 by 8)
+    mw = max_xor32(max_xor16(mw));
     {
         const float r = __builtin_amdgcn_exp2f(m - mw);
         l *= r;
 #pragma unroll
         for (int e = 0; e < 8; ++e) acc[e] *= r;
     }
-    if (LPK == 8) l += dpp_f<0x128>(l);
-    l += __shfl_xor(l, 16, kWave);
-    l += __shfl_xor(l, 32, kWave);
+    if (LPK == 8) l += dpp<0x128>(l);
+    l = sum_xor32(sum_xor16(l));
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
-        if (LPK == 8) acc[e] += dpp_f<0x128>(acc[e]);
-        acc[e] += __shfl_xor(acc[e], 16, kWave);
-        acc[e] += __shfl_xor(acc[e], 32, kWave);
+        if (LPK == 8) acc[e] += dpp<0x128>(acc[e]);
+        acc[e] = sum_xor32(sum_xor16(acc[e]));
     }
     if (lane < LPK) {
 #pragma unroll

@@ -24,24 +24,70 @@ struct SeqLens {
     int32_t len[kMaxBatch];
 };
 
+// ---- lane exchanges without the LDS --------------------------------------------------------------
+// A shuffle goes through the LDS unit (ds_bpermute: some 100 cycles until its result is there), and a reduction over a wave is six of
+// them behind one another; as data-parallel primitives and row swaps the same six steps are a few cycles each.  One LayerNorm row has twelve
+// of them in its chain.
+template <int CTRL>
+__device__ __forceinline__ int dpp_word(int x) { return __builtin_amdgcn_update_dpp(0, x, CTRL, 0xf, 0xf, false); }
+template <int CTRL, class T>
+__device__ __forceinline__ T dpp(T x) { return __builtin_bit_cast(T, dpp_word<CTRL>(__builtin_bit_cast(int, x))); }
+// A lane's value and that of lane ^ 16 (^ 32), in the same order in both lanes: a swap of a register with itself leaves both in
+// each.  The two elements are copied into scalars before the bit casts: __builtin_bit_cast applied to the vector element r[1]
+// directly reads element 0 with this compiler, which silently turned a maximum into "the value of the lower lane" (a reference of the
+// exponentials that ignored half of each row's keys: exact results until a row's scores span more than the 16 bits of
+// headroom fp16 has above one, then infinities).
+template <class T>
+struct LanePair {
+    T lower, upper;
+};
+template <class T>
+__device__ __forceinline__ LanePair<T> pair_xor16(T x) {
+    const unsigned u = __builtin_bit_cast(unsigned, x);
+    const auto r = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+    const unsigned r0 = r[0], r1 = r[1];
+    return {__builtin_bit_cast(T, r0), __builtin_bit_cast(T, r1)};
+}
+template <class T>
+__device__ __forceinline__ LanePair<T> pair_xor32(T x) {
+    const unsigned u = __builtin_bit_cast(unsigned, x);
+    const auto r = __builtin_amdgcn_permlane32_swap(u, u, false, false);
+    const unsigned r0 = r[0], r1 = r[1];
+    return {__builtin_bit_cast(T, r0), __builtin_bit_cast(T, r1)};
+}
+__device__ __forceinline__ float sum_xor16(float x) { const auto p = pair_xor16(x); return p.lower + p.upper; }
+__device__ __forceinline__ float sum_xor32(float x) { const auto p = pair_xor32(x); return p.lower + p.upper; }
+__device__ __forceinline__ float max_xor16(float x) { const auto p = pair_xor16(x); return fmaxf(p.lower, p.upper); }
+__device__ __forceinline__ float max_xor32(float x) { const auto p = pair_xor32(x); return fmaxf(p.lower, p.upper); }
+
+// Over the lane's 16: partners ^ 8, ^ 4, ^ 2, ^ 1, as a shuffle loop has them (4 by a rotation: after the first step lanes 8 apart agree)
+template <class T, class Op>
+__device__ __forceinline__ T reduce16(T v, Op op) {
+    v = op(v, dpp<0x128>(v));
+    v = op(v, dpp<0x124>(v));
+    v = op(v, dpp<0x4e>(v));
+    return op(v, dpp<0xb1>(v));
+}
+// Over the wave, ^ 32 and ^ 16 first; every lane calls it and gets the result
+template <class T, class Op>
+__device__ __forceinline__ T reduce_wave(T v, Op op) {
+    const auto a = pair_xor32(v);
+    v = op(a.lower, a.upper);
+    const auto b = pair_xor16(v);
+    return reduce16(op(b.lower, b.upper), op);
+}
 __device__ __forceinline__ float wave_sum(float v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, kWave);
-    return v;
+    return reduce_wave(v, [](float x, float y) { return x + y; });
 }
 __device__ __forceinline__ float wave_max(float v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, kWave));
-    return v;
+    return reduce_wave(v, [](float x, float y) { return fmaxf(x, y); });
 }
 
 // Tokens of the sequences before sequence b: two loads and six lane exchanges whatever b is (a loop over the kernel argument
 // is a scalar load and a wait per sequence).  Every lane of the wave calls it and gets the sum.
 __device__ __forceinline__ int tokens_before(const SeqLens& lens, int b, int lane) {
     int n = (lane < b ? lens.len[lane] : 0) + (lane + 64 < b ? lens.len[lane + 64] : 0);
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) n += __shfl_xor(n, o, kWave);
-    return __builtin_amdgcn_readfirstlane(n);
+    return __builtin_amdgcn_readfirstlane(reduce_wave(n, [](int x, int y) { return x + y; }));
 }
 
 // Sum over a workgroup of NW waves; every thread gets the result.  `red` is LDS scratch of

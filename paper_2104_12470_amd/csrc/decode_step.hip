@@ -82,14 +82,23 @@ struct StepSmem {
     int in_use;                                    // the wait for the exchange set came to its bound
 };
 
-template <int CTRL>
-__device__ __forceinline__ float dpp_move(float x) {
-    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), CTRL, 0xf, 0xf, false));
+// x - m of two halfs in float, the operands taken as they are (a conversion is a half-rate instruction, and the compiler makes a
+// conversion and an addition of a multiply-add by one)
+__device__ __forceinline__ void minus_mean(half2v x, float m, float& d0, float& d1) {
+    asm("v_fma_mix_f32 %0, %2, 1.0, -%3 op_sel_hi:[1,0,0]\n\tv_fma_mix_f32 %1, %2, 1.0, -%3 op_sel:[1,0,0] op_sel_hi:[1,0,0]" : "=&v"(d0), "=v"(d1) : "v"(x), "v"(m));
 }
 __device__ __forceinline__ float sum8(float v) {   // over aligned groups of 8 lanes
-    v += dpp_move<0xb1>(v);
-    v += dpp_move<0x4e>(v);
-    return v + dpp_move<0x141>(v);
+    v += dpp<0xb1>(v);
+    v += dpp<0x4e>(v);
+    return v + dpp<0x141>(v);
+}
+
+template <int LANES>
+__device__ __forceinline__ float sum_shares(float v) {   // over aligned groups of 4 or 8 lanes
+    static_assert(LANES == 4 || LANES == 8, "lanes");
+    v += dpp<0xb1>(v);
+    v += dpp<0x4e>(v);
+    return LANES == 8 ? v + dpp<0x141>(v) : v;
 }
 
 // where this item stands
@@ -169,12 +178,12 @@ struct RowLanes {
 // sum over the lanes of a row
 template <int ROWS>
 __device__ __forceinline__ float row_sum(float v) {
-    v += dpp_move<0xb1>(v);                                    // lane ^ 1
-    v += dpp_move<0x4e>(v);                                    // lane ^ 2: 4 lanes
-    if (ROWS <= 8) v += dpp_move<0x141>(v);                    // 8 lanes
-    if (ROWS <= 4) v += dpp_move<0x140>(v);                    // 16 lanes
-    if (ROWS == 1) v += __shfl_xor(v, 16, kWave);
-    if (ROWS <= 2) v += __shfl_xor(v, 32, kWave);
+    v += dpp<0xb1>(v);                                    // lane ^ 1
+    v += dpp<0x4e>(v);                                    // lane ^ 2: 4 lanes
+    if (ROWS <= 8) v += dpp<0x141>(v);                    // 8 lanes
+    if (ROWS <= 4) v += dpp<0x140>(v);                    // 16 lanes
+    if (ROWS == 1) v = sum_xor16(v);
+    if (ROWS <= 2) v = sum_xor32(v);
     return v;
 }
 
@@ -230,10 +239,14 @@ __device__ __forceinline__ void project(const StepArgs& a, const Where& w, StepS
     const int em = w.tid / (TN / 4), ec = (w.tid % (TN / 4)) * 4, en = n0 + ec;   // the M * TN/4 threads that write: row, first of four columns
     const bool writer = w.tid < M * (TN / 4);
     half4v eb, er;
-    int epos = 0;
+    half_t* slot = nullptr;                                    // where in the cache the row's keys or values go
     if (writer) {
         eb = *reinterpret_cast<const half4v*>(bias + en);
-        if (PH == kStepQkv) epos = a.lens[em];
+        if (PH == kStepQkv) {
+            const int which = n0 / H, c = en - which * H, epos = a.lens[em];      // (a tile lies in one of Q, K and V)
+            if (which != 0 && epos >= 0 && epos < a.max_seq)      // past the capacity (replays the host never saw): dropped
+                slot = (which == 1 ? L.k_cache : L.v_cache) + ((size_t)(em * a.heads + c / a.d) * a.max_seq + epos) * a.d + c % a.d;
+        }
         if (PH == kStepOut && first) er = *reinterpret_cast<const half4v*>(a.x + (size_t)em * H + en);
     }
     // weights into matrix-operand layout by way of LDS (whole lines per load instruction), while there is nothing else to do: two
@@ -385,7 +398,7 @@ __device__ __forceinline__ void project(const StepArgs& a, const Where& w, StepS
         for (int s = 0; s < STEPS; ++s)
             if (has(s)) {
 #pragma unroll
-                for (int e = 0; e < E; ++e) sum = __builtin_fmaf((float)xv[s][e], 1.0f, sum);
+                for (int e = 0; e < E; e += 2) sum = __builtin_amdgcn_fdot2(half2v{xv[s][e], xv[s][e + 1]}, half2v{(half_t)1.f, (half_t)1.f}, sum, false);
             }
         sum = row_sum<ROWS>(sum);
         const float mw = count > 0 ? sum * __builtin_amdgcn_rcpf((float)(64 * count)) : 0.f;      // a power of two, or rounded once: any value near the mean serves
@@ -393,9 +406,11 @@ __device__ __forceinline__ void project(const StepArgs& a, const Where& w, StepS
         for (int s = 0; s < STEPS; ++s)
             if (has(s)) {
 #pragma unroll
-                for (int e = 0; e < E; ++e) {
-                    const float d = __builtin_fmaf((float)xv[s][e], 1.0f, -mw);
-                    sq = __builtin_fmaf(d, d, sq);
+                for (int e = 0; e < E; e += 2) {
+                    float d0, d1;
+                    minus_mean(half2v{xv[s][e], xv[s][e + 1]}, mw, d0, d1);
+                    sq = __builtin_fmaf(d0, d0, sq);
+                    sq = __builtin_fmaf(d1, d1, sq);
                 }
             }
         sq = row_sum<ROWS>(sq);
@@ -408,33 +423,34 @@ __device__ __forceinline__ void project(const StepArgs& a, const Where& w, StepS
             const uint32_t hi = lo + per < a.set_words ? lo + per : a.set_words;
             for (uint32_t c = lo + w.tid; c < hi; c += kSThreads) st_word(w.other + c, kEmpty);
         }
-        float2v sv[kSWaves];
-#pragma unroll
-        for (int v = 0; v < kSWaves; ++v) sv[v] = *reinterpret_cast<const float2v*>(&sm.stat[v][row][0]);
+        // the waves' shares, dealt to the lanes of a row
+        constexpr int SL = LPR < kSWaves ? LPR : kSWaves, SN = kSWaves / SL;
         const float inv_k = 1.0f / (float)K;
-        float mean = 0.f, m2 = 0.f;
+        float2v sv[SN];
+        float weight[SN], mean = 0.f, m2 = 0.f;
 #pragma unroll
-        for (int v = 0; v < kSWaves; ++v) {
-            int c = (units - v + kSWaves - 1) / kSWaves;
-            c = c < 0 ? 0 : c;
-            mean += sv[v][0] * ((float)(64 * c) * inv_k);
+        for (int v = 0; v < SN; ++v) sv[v] = *reinterpret_cast<const float2v*>(&sm.stat[lane % SL + SL * v][row][0]);
+#pragma unroll
+        for (int v = 0; v < SN; ++v) {
+            const int c = (units - (lane % SL + SL * v) + kSWaves - 1) / kSWaves;
+            weight[v] = c < 0 ? 0.f : (float)(64 * c);
+            mean = __builtin_fmaf(sv[v][0], weight[v] * inv_k, mean);
         }
+        mean = sum_shares<SL>(mean);
 #pragma unroll
-        for (int v = 0; v < kSWaves; ++v) {
-            int c = (units - v + kSWaves - 1) / kSWaves;
-            c = c < 0 ? 0 : c;
+        for (int v = 0; v < SN; ++v) {
             const float d = sv[v][0] - mean;
-            m2 += sv[v][1] + (float)(64 * c) * d * d;
+            m2 += sv[v][1] + weight[v] * d * d;
         }
-        const float rstd = rsqrtf(m2 * inv_k + eps);
+        m2 = sum_shares<SL>(m2);
+        const float rstd = rsqrtf(m2 * inv_k + eps), shift = -mean * rstd;
 #pragma unroll
         for (int s = 0; s < STEPS; ++s)
 #pragma unroll
             for (int e = 0; e < E; ++e) {
                 // fused multiply-adds that take their fp16 operands directly
-                const float sc = __builtin_fmaf((float)gv[s][e], rstd, 0.f);
-                const float sh = __builtin_fmaf(-mean, sc, (float)bv[s][e]);
-                xv[s][e] = (half_t)__builtin_fmaf((float)xv[s][e], sc, sh);
+                const float t = __builtin_fmaf((float)xv[s][e], rstd, shift);
+                xv[s][e] = (half_t)__builtin_fmaf(t, (float)gv[s][e], (float)bv[s][e]);
             }
     }
 
@@ -480,9 +496,7 @@ __device__ __forceinline__ void project(const StepArgs& a, const Where& w, StepS
         }
         if constexpr (PH == kStepQkv) {
             publish(w.set + word_at(a.bqkv, em, en), out);
-            const int which = en / H, c = en - which * H;
-            if (which != 0 && epos >= 0 && epos < a.max_seq)      // past the capacity (replays the host never saw): dropped
-                *reinterpret_cast<half4v*>((which == 1 ? L.k_cache : L.v_cache) + ((size_t)(em * a.heads + c / a.d) * a.max_seq + epos) * a.d + c % a.d) = out;
+            if (slot != nullptr) *reinterpret_cast<half4v*>(slot) = out;
         } else if constexpr (PH == kStepOut) {
             publish(w.set + word_at(a.by, em, en), out);
         } else if constexpr (PH == kStepFfn1) {
@@ -580,7 +594,7 @@ __device__ __forceinline__ void attend(const StepArgs& a, const Where& w, StepSm
 #pragma unroll
         for (int e = 0; e < 4; ++e) d = __builtin_amdgcn_fdot2(half2v{k[2 * e], k[2 * e + 1]}, half2v{qv[2 * e], qv[2 * e + 1]}, d, false);
         d = sum8(d);
-        if (LPK == 16) d += dpp_move<0x140>(d);
+        if (LPK == 16) d += dpp<0x140>(d);
         return d * c;
     };
     float acc[8], m = kNone, l = 0.f;
@@ -626,20 +640,17 @@ __device__ __forceinline__ void attend(const StepArgs& a, const Where& w, StepSm
     }
     // lane groups, then waves
     float mw = m;
-    if (LPK == 8) mw = fmaxf(mw, dpp_move<0x128>(mw));
-    mw = fmaxf(mw, __shfl_xor(mw, 16, kWave));
-    mw = fmaxf(mw, __shfl_xor(mw, 32, kWave));
+    if (LPK == 8) mw = fmaxf(mw, dpp<0x128>(mw));
+    mw = max_xor32(max_xor16(mw));
     const float r = __builtin_amdgcn_exp2f(m - mw);
     l *= r;
-    if (LPK == 8) l += dpp_move<0x128>(l);
-    l += __shfl_xor(l, 16, kWave);
-    l += __shfl_xor(l, 32, kWave);
+    if (LPK == 8) l += dpp<0x128>(l);
+    l = sum_xor32(sum_xor16(l));
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
         acc[e] *= r;
-        if (LPK == 8) acc[e] += dpp_move<0x128>(acc[e]);
-        acc[e] += __shfl_xor(acc[e], 16, kWave);
-        acc[e] += __shfl_xor(acc[e], 32, kWave);
+        if (LPK == 8) acc[e] += dpp<0x128>(acc[e]);
+        acc[e] = sum_xor32(sum_xor16(acc[e]));
     }
     float* sm_acc = reinterpret_cast<float*>(&sm.stage[0][0]);       // [waves][D]
     static_assert(sizeof(float) * kSWaves * 128 <= sizeof(sm.stage), "merge over the staging areas");
@@ -674,7 +685,7 @@ __device__ __forceinline__ void attend(const StepArgs& a, const Where& w, StepSm
     }
     const float inv = sum > 0.f ? 1.0f / sum : 0.f;
     const float b0 = a0 * inv, b1 = a1 * inv;
-    const float c0_ = __shfl_xor(b0, 1, kWave), c1_ = __shfl_xor(b1, 1, kWave);
+    const float c0_ = dpp<0xb1>(b0), c1_ = dpp<0xb1>(b1);
     if ((w.tid & 1) == 0)
         publish(w.set + word_at(a.bctx, b, h * D + w.tid * 2), half4v{(half_t)b0, (half_t)b1, (half_t)c0_, (half_t)c1_});
 }

@@ -761,8 +761,7 @@ __global__ __launch_bounds__(NW * 64) void gemm_skinny(GemmArgs a) {
                     for (int e = 0; e < 8; ++e) sum += (float)v[i][e];
                 }
         }
-#pragma unroll
-        for (int o = 8; o > 0; o >>= 1) sum += __shfl_xor(sum, o, kWave);
+        sum = reduce16(sum, [](float x, float y) { return x + y; });
         const float mu = sum / (float)K;
         float sq = 0.f;
         for (int c0 = sub * 8; c0 < K; c0 += 8 * 128) {
@@ -782,8 +781,7 @@ __global__ __launch_bounds__(NW * 64) void gemm_skinny(GemmArgs a) {
                     }
                 }
         }
-#pragma unroll
-        for (int o = 8; o > 0; o >>= 1) sq += __shfl_xor(sq, o, kWave);
+        sq = reduce16(sq, [](float x, float y) { return x + y; });
         if (sub == 0) {
             ln_mean[row] = mu;
             ln_rstd[row] = rsqrtf(sq / (float)K + a.ln_eps);
@@ -873,17 +871,12 @@ __host__ __device__ constexpr int flat_lds_bytes(int nw, int upw, int xrows) {
 // sum over aligned groups of W lanes (W = 32 or 64), result in every lane of the group
 template <int W>
 __device__ __forceinline__ float group_sum(float v) {
-    auto dpp_add = [](float x, auto ctrl) {
-        constexpr int c = decltype(ctrl)::value;
-        const int y = __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), c, 0xf, 0xf, false);
-        return x + __builtin_bit_cast(float, y);
-    };
-    v = dpp_add(v, std::integral_constant<int, 0xb1>{});    // quad_perm [1,0,3,2]: lane ^ 1
-    v = dpp_add(v, std::integral_constant<int, 0x4e>{});    // quad_perm [2,3,0,1]: lane ^ 2
-    v = dpp_add(v, std::integral_constant<int, 0x141>{});   // row_half_mirror: the other quad of 8
-    v = dpp_add(v, std::integral_constant<int, 0x140>{});   // row_mirror: the other half of 16
-    v += __shfl_xor(v, 16, kWave);
-    if (W == 64) v += __shfl_xor(v, 32, kWave);
+    v += dpp<0xb1>(v);                                      // quad_perm [1,0,3,2]: lane ^ 1
+    v += dpp<0x4e>(v);                                      // quad_perm [2,3,0,1]: lane ^ 2
+    v += dpp<0x141>(v);                                     // row_half_mirror: the other quad of 8
+    v += dpp<0x140>(v);                                     // row_mirror: the other half of 16
+    v = sum_xor16(v);
+    if (W == 64) v = sum_xor32(v);
     return v;
 }
 
@@ -1339,8 +1332,7 @@ __global__ __launch_bounds__(256) void gemm_stream(GemmArgs a) {
                 }
             }
         }
-        A += __shfl_xor(A, 16, kWave); B += __shfl_xor(B, 16, kWave); C += __shfl_xor(C, 16, kWave);
-        A += __shfl_xor(A, 32, kWave); B += __shfl_xor(B, 32, kWave); C += __shfl_xor(C, 32, kWave);
+        A = sum_xor32(sum_xor16(A)); B = sum_xor32(sum_xor16(B)); C = sum_xor32(sum_xor16(C));
         if (lane < 16) {
             sm[(wave * 16 + lane) * 3 + 0] = A;
             sm[(wave * 16 + lane) * 3 + 1] = B;

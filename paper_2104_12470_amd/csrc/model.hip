@@ -89,12 +89,21 @@ __global__ __launch_bounds__(kArgmaxThreads) void argmax_rows(const half_t* __re
         const float f = (float)row[j];
         if (f > best) { best = f; bi = j; }
     }
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-        const float ov = __shfl_xor(best, o, kWave);
-        const int oi = __shfl_xor(bi, o, kWave);
-        if (ov > best || (ov == best && oi < bi)) { best = ov; bi = oi; }
-    }
+    auto take = [&](float v, int i, float ov, int oi) {
+        const bool other = ov > v || (ov == v && oi < i);
+        best = other ? ov : v;
+        bi = other ? oi : i;
+    };
+    const auto v32 = pair_xor32(best);
+    const auto i32 = pair_xor32(bi);
+    take(v32.lower, i32.lower, v32.upper, i32.upper);
+    const auto v16 = pair_xor16(best);
+    const auto i16 = pair_xor16(bi);
+    take(v16.lower, i16.lower, v16.upper, i16.upper);
+    take(best, bi, dpp<0x128>(best), dpp<0x128>(bi));       // the steps of reduce16
+    take(best, bi, dpp<0x124>(best), dpp<0x124>(bi));
+    take(best, bi, dpp<0x4e>(best), dpp<0x4e>(bi));
+    take(best, bi, dpp<0xb1>(best), dpp<0xb1>(bi));
     if ((tid & 63) == 0) { sv[tid >> 6] = best; si[tid >> 6] = bi; }
     __syncthreads();
     if (tid == 0) {
