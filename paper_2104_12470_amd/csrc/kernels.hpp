@@ -193,6 +193,7 @@ struct AttnDecodeArgs {
     uint32_t* arrived;      // splits > 1: a zeroed counter per pair, kClearStride apart: the pair's last workgroup merges its ranges, no merge launch (nullptr: there is one)
     int leave_ranges;       // 1: no merge launch, the projection that follows merges the ranges (GemmArgs::x_splits)
     int read_once;          // 1: K/V rows loaded with the non-temporal hint (see GemmArgs::read_once)
+    int longest_first;      // set by the launcher
 };
 int attention_decode_splits(int batch, int heads, int capacity);
 size_t attention_decode_scratch_bytes(int batch, int heads, int d, int splits);
