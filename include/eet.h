@@ -178,8 +178,8 @@ size_t eet_stack_workspace_bytes(const eet_layer_config *cfg, int32_t n_layers);
  * eet_stack_workspace_bytes, 256-byte aligned.  use_graph != 0: eet_stack_decode_step records its
  * launches into a HIP graph the first time it sees a (tokens, out, kv_cache) triple and replays
  * it afterwards (the graph is instantiated inside that call, and once more when what the sequences hold
- * outgrows the memory-side cache; it is skipped on the null stream and while the caller is capturing the
- * stream itself).  Errors as eet_layer_create. */
+ * outgrows the memory-side cache; it is skipped on the null stream, while the caller is capturing the
+ * stream itself, and where a step is one launch for all layers anyway).  Errors as eet_layer_create. */
 int eet_stack_create(const eet_layer_config *cfg, int32_t n_layers, const eet_layer_weights *weights,
                      void *workspace, int32_t use_graph, eet_stack_t **out_stack);
 
@@ -264,7 +264,7 @@ int eet_model_prefill_left_padded(eet_model_t *model, const int32_t *q_lens, int
  * it may be the next_ids buffer of the previous call, so generation needs no host round trip.
  * logits [batch, vocab_padded], next_ids as above.  EET_ERR_CAPACITY when a sequence is at the
  * cache capacity, EET_ERR_STATE before the first prefill; otherwise as eet_stack_decode_step
- * (the stack's recorded graph is replayed: the model feeds it from fixed buffers of its own). */
+ * (a stack's recorded graph is replayed: the model feeds it from fixed buffers of its own). */
 int eet_model_decode_step(eet_model_t *model, const int32_t *ids, void *logits, int32_t *next_ids,
                           void *kv_cache, void *hip_stream);
 

@@ -809,8 +809,11 @@ int eet_stack_decode_step(eet_stack_t* st, const void* tokens, void* out, void* 
     const StepRegime regime = step_regime(st->layers[0], st->host_lens);
     // A step has no other host-varying argument (the cache lengths live on the device), so its launches
     // can be recorded once and replayed.  Not on the null stream (it cannot be captured) and not
-    // while the caller is capturing this stream itself (then the launches join the caller's graph).
-    bool graph = st->use_graph && s != nullptr;
+    // while the caller is capturing this stream itself (then the launches join the caller's graph).  Nor where the step is one
+    // launch (per kStepLayers layers): a graph of one node costs the host 25 us instead of 10 and the stream some 6 us around
+    // it (16 steps, replayed / launched: 24 x hidden 1024, 8 sequences 5231 / 5119 us, 2 x hidden 256 620 / 354, behind an
+    // embedding and before a vocabulary 24 x 1024 5418 / 5349, 2 x 512 885 / 788).
+    bool graph = st->use_graph && s != nullptr && !decodes_in_one_launch(st->layers[0], regime);
     if (graph) {
         hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
         if (hipStreamIsCapturing(s, &cs) != hipSuccess || cs != hipStreamCaptureStatusNone) graph = false;
