@@ -236,6 +236,24 @@ bool decode_step_fits_keys(int rows, int heads, int d, size_t visible);
 uint32_t decode_step_set_words(int max_rows, int hidden, int heads, int ffn, int max_seq);
 hipError_t launch_decode_layers(StepArgs& a, bool read_once, hipStream_t s);
 
+// ---- what comes behind the last layer, in one launch (head.hip) --------------------------------------
+constexpr int kHeadMaxRows = 16, kHeadMaxK = 1792, kHeadGroups = 256;
+struct HeadArgs {
+    const half_t* x;            // row m is x[row_map ? row_map[m] : m]
+    const int32_t* row_map;
+    const half_t *gamma, *beta; // of the final LayerNorm
+    const half_t* w;            // [N, K] the table
+    half_t* logits;             // [M, N]
+    int32_t* next_ids;          // [M]: first maximum of columns [0, vocab); nullptr: no choice, and the two below are not looked at
+    unsigned long long* best;   // [M, kHeadGroups]
+    uint32_t* arrived;          // zero; left zero
+    int M, N, K, vocab;
+    float eps;
+    int x_rows;                 // set by the launcher
+};
+bool head_takes(int rows, int width, int columns);
+hipError_t launch_head(HeadArgs a, hipStream_t s);
+
 // ---- operators around the stack (model.hip) ------------------------------------------------------
 // out[b*S + i] = wte[ids[b*S + i]] + wpe[i - first] for first <= i < first + lens.len[b] (first = 0, or S - lens.len[b]
 // when left_padded), zeros for pad rows (positions == nullptr);
