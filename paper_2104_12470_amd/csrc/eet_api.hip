@@ -195,6 +195,14 @@ static void cut_projection(eet_layer* L, GemmArgs& g, size_t sums) {
     g.part = reinterpret_cast<float*>(L->ws + sums);
 }
 
+// The second feed-forward projection of a layer of a stack, cut along K: its rows also normalised for `next`, into `rows` (where its own input was)
+static bool leave_layernorm(GemmArgs& f2, const eet_layer* next, half_t* rows) {
+    if (next == nullptr || f2.k_ranges <= 1 || f2.K < f2.N) return false;
+    f2.fin_gamma = (const half_t*)next->w.ln1_g; f2.fin_beta = (const half_t*)next->w.ln1_b; f2.fin_y = rows; f2.fin_eps = next->cfg.ln_eps;
+    f2.fin_as_launch = 1;
+    return true;
+}
+
 // The exchange area of `L`'s decode steps, to be set up wherever the cache lengths are set
 static StepArea step_area(const eet_layer* L) {
     const uint32_t set_words = L->lay.step_set_words;
@@ -209,10 +217,14 @@ static StepArea step_area(const eet_layer* L) {
 
 // Enqueue the kernels of one layer's prefill (arguments already validated).
 // index_setup = false: a layer of a stack whose workspace already holds this prefill's lengths, prefix sums and row map
-// and whose output buffer already has its pad rows zeroed (an earlier layer of the same call did both).
+// and whose output buffer already has its pad rows zeroed (an earlier layer of the same call did both) or has none.
+// normalised (in a stack, nullptr elsewhere): in, whether the layer before has left this layer's first LayerNorm in buf_f; out, whether this one
+// has left that of `next` there, which it does where its second feed-forward projection is cut along K: the launch that adds up the ranges
+// normalises the rows as it stores them, one launch of some 4 us less per layer (the bits are those of the launch).
 static int enqueue_prefill(eet_layer* L, const SeqLens& lens, int batch, int padded_len, int64_t T, int max_len,
                            const void* tokens, void* out, void* kv_cache, hipStream_t s, bool causal = true,
-                           bool left_padded = false, bool index_setup = true, bool sets_lengths = true) {
+                           bool left_padded = false, bool index_setup = true, bool sets_lengths = true, const eet_layer* next = nullptr,
+                           bool* normalised = nullptr) {
     const eet_layer_config& c = L->cfg;
     const int H = c.hidden, F = c.ffn;
     int32_t* d_lens = reinterpret_cast<int32_t*>(L->ws + L->lay.lens);
@@ -230,7 +242,9 @@ static int enqueue_prefill(eet_layer* L, const SeqLens& lens, int batch, int pad
     // (left_padded: the packed->padded row map starts each sequence at row S - L_b; every kernel below works on
     // the packed rows and never sees the difference, except the cache scatter, which needs the position)
     // a2: LN1 over valid rows only (gathered into the packed layout), in the same launch for rows of up to 2048
-    if (index_setup && prefill_setup_takes_layernorm(H)) {
+    const bool ready = normalised != nullptr && *normalised;
+    if (ready) {
+    } else if (index_setup && prefill_setup_takes_layernorm(H)) {
         EET_LAUNCH(launch_prefill_setup_layernorm(lens, batch, padded_len, H, d_lens, d_cu, d_map, static_cast<half_t*>(out), left_padded,
                                                   x, (const half_t*)L->w.ln1_g, (const half_t*)L->w.ln1_b, bufA, c.ln_eps,
                                                   causal && sets_lengths ? step_area(L) : StepArea{}, s),
@@ -251,7 +265,7 @@ static int enqueue_prefill(eet_layer* L, const SeqLens& lens, int batch, int pad
     const size_t stack_kv = (causal ? layers : 1) * 4 * H * (size_t)T;       // (an encoder's layers share one region)
     const size_t weights_ahead = ((size_t)H * H + (size_t)H * F) * sizeof(half_t);
     const int once = T <= 128 && stack_weights > kMemorySideCacheBytes;
-    g.x = bufA; g.w = (const half_t*)L->w.w_qkv; g.bias = (const half_t*)L->w.b_qkv; g.y = bufB;
+    g.x = ready ? bufF : bufA; g.w = (const half_t*)L->w.w_qkv; g.bias = (const half_t*)L->w.b_qkv; g.y = bufB;
     g.M = (int)T; g.N = 3 * H; g.K = H; g.read_once = once;
     g.k_cache = kc; g.v_cache = vc; g.tok_row_map = d_map; g.lens = left_padded ? d_lens : nullptr;
     g.left_pad = left_padded ? 1 : 0;
@@ -290,6 +304,7 @@ static int enqueue_prefill(eet_layer* L, const SeqLens& lens, int batch, int pad
     f2.x = bufF; f2.w = (const half_t*)L->w.w_fc2; f2.bias = (const half_t*)L->w.b_fc2; f2.y = static_cast<half_t*>(out);
     f2.M = (int)T; f2.N = H; f2.K = F; f2.res = bufY; f2.res_row_map = nullptr; f2.out_row_map = d_map; f2.read_once = once;
     cut_projection(L, f2, L->lay.cut);
+    if (normalised != nullptr) *normalised = leave_layernorm(f2, next, bufF);
     if (F >= kFfnPadFrom && gemm_takes_row_strides(f1) && gemm_takes_row_strides(f2)) f1.ldy = f2.lda = F + (int)kFfnRowPad;
     EET_LAUNCH(launch_gemm(f1, EPI_BIAS_GELU, s), "ffn 1");
     EET_LAUNCH(launch_gemm(f2, EPI_BIAS_RES, s), "ffn 2");
@@ -383,7 +398,7 @@ static StepRegime step_regime(const eet_layer* L, const int32_t* cached) {
 // Enqueue the kernels of one layer's decode step (arguments already validated).  `bump`: this
 // layer advances the device-side cache lengths (in a stack only the last layer does).
 static int enqueue_decode(eet_layer* L, const void* tokens, void* out, void* kv_cache, hipStream_t s, bool bump, StepRegime regime,
-                          const eet_layer* next = nullptr, const void* next_kv = nullptr) {
+                          const eet_layer* next = nullptr, const void* next_kv = nullptr, bool* normalised = nullptr) {
     const eet_layer_config& c = L->cfg;
     const int B = L->batch, H = c.hidden, F = c.ffn;
     int32_t* d_lens = reinterpret_cast<int32_t*>(L->ws + L->lay.lens);
@@ -446,7 +461,9 @@ static int enqueue_decode(eet_layer* L, const void* tokens, void* out, void* kv_
     if (splits > 1 && !fuse_ln && !merged_by_projection && pairs <= L->lay.arrived_lines && layernorm_clears(B, H, pairs))
         arrived = ClearLines{reinterpret_cast<uint32_t*>(L->ws + L->lay.arrived), pairs};
     const half_t* qkv_in = x;
-    if (!fuse_ln) {
+    if (normalised != nullptr && *normalised) {
+        qkv_in = bufF;                                    // by the layer before (enqueue_prefill: normalised)
+    } else if (!fuse_ln) {
         EET_LAUNCH(launch_layernorm(x, nullptr, (const half_t*)L->w.ln1_g, (const half_t*)L->w.ln1_b, bufA, B, H,
                                     c.ln_eps, nullptr, 0, s, arrived), "layernorm 1");
         qkv_in = bufA;
@@ -518,6 +535,8 @@ static int enqueue_decode(eet_layer* L, const void* tokens, void* out, void* kv_
     f2.x = bufF; f2.w = (const half_t*)L->w.w_fc2; f2.bias = (const half_t*)L->w.b_fc2; f2.y = static_cast<half_t*>(out);
     f2.M = B; f2.N = H; f2.K = F; f2.res = bufY; f2.read_once = once;
     cut_projection(L, f2, L->lay.cut);
+    // (not where the next layer's launch has counters to clear; more than 16 sequences, so no LayerNorm inside a projection)
+    if (normalised != nullptr) *normalised = !bump && arrived.lines == 0 && leave_layernorm(f2, next, bufF);
     if (prefetch && next != nullptr && gemm_takes_prefetch(f2)) {   // during FFN-2 (128 workgroups): the QKV matrix and the K/V rows of the step that follows
         f2.pf.lin[0] = next->w.w_qkv; f2.pf.lin_lines[0] = lines((size_t)3 * H * H * 2);
         f2.pf.k_cache = static_cast<const half_t*>(next_kv);
@@ -718,7 +737,10 @@ int eet_stack_create(const eet_layer_config* cfg, int32_t n_layers, const eet_la
 // all; what is left per layer is zeroing the pad rows of its output buffer.  Layers 0 and 1 do that for the two
 // activation buffers the stack alternates between (nothing writes a pad row afterwards: the last projection of a layer
 // scatters valid rows only), the last layer for the caller's buffer; the layers in between skip the launch.
-static bool stack_layer_needs_setup(int l, int n_layers) { return l < 2 || l == n_layers - 1; }
+// Without pad rows layer 0's is all there is.
+static bool stack_layer_needs_setup(int l, int n_layers, bool pads) { return l == 0 || (pads && (l == 1 || l == n_layers - 1)); }
+// The layer that a layer of a stack may normalise its rows for: the next one, unless that has a set-up launch, which does it on the way
+static const eet_layer* normalises_for(const eet_stack* st, int l, bool pads);
 
 static int stack_prefill(const char* who, bool left_padded, eet_stack_t* st, const int32_t* q_lens, int32_t batch,
                          int32_t padded_len, const void* tokens, void* out, void* kv_cache, void* hip_stream) {
@@ -730,11 +752,13 @@ static int stack_prefill(const char* who, bool left_padded, eet_stack_t* st, con
         return rc;
     hipStream_t s = static_cast<hipStream_t>(hip_stream);
     const void* in = tokens;
+    const bool pads = T < (int64_t)batch * padded_len;
+    bool normalised = false;
     for (int l = 0; l < st->n_layers; ++l) {
         void* o = (l == st->n_layers - 1) ? out : static_cast<void*>(st->ws + st->act[l & 1]);
         char* kv = static_cast<char*>(kv_cache) + (size_t)l * st->layer_cache_bytes;
         const int rc = enqueue_prefill(st->layers[l], lens, batch, padded_len, T, max_len, in, o, kv, s, true, left_padded,
-                                       stack_layer_needs_setup(l, st->n_layers), l == 0);
+                                       stack_layer_needs_setup(l, st->n_layers, pads), l == 0, normalises_for(st, l, pads), &normalised);
         if (rc != EET_OK) return rc;
         st->layers[l]->batch = batch;
         in = o;
@@ -765,16 +789,22 @@ int eet_stack_encode(eet_stack_t* st, const int32_t* q_lens, int32_t batch, int3
     hipStream_t s = static_cast<hipStream_t>(hip_stream);
     st->batch = 0;                                   // the pass overwrites the device-side lengths: no decode state afterwards
     const void* in = tokens;
+    const bool pads = T < (int64_t)batch * padded_len;
+    bool normalised = false;
     for (int l = 0; l < st->n_layers; ++l) {
         void* o = (l == st->n_layers - 1) ? out : static_cast<void*>(st->ws + st->act[l & 1]);
         st->layers[l]->batch = 0;
         // every layer's keys and values of this pass go to the same scratch: the layers run one after another
         const int rc = enqueue_prefill(st->layers[l], lens, batch, padded_len, T, max_len, in, o, kv_scratch, s, false, false,
-                                       stack_layer_needs_setup(l, st->n_layers));
+                                       stack_layer_needs_setup(l, st->n_layers, pads), true, normalises_for(st, l, pads), &normalised);
         if (rc != EET_OK) return rc;
         in = o;
     }
     return EET_OK;
+}
+
+static const eet_layer* normalises_for(const eet_stack* st, int l, bool pads) {
+    return l + 1 < st->n_layers && !stack_layer_needs_setup(l + 1, st->n_layers, pads) ? st->layers[l + 1] : nullptr;
 }
 
 static int stack_enqueue_decode(eet_stack* st, const void* tokens, void* out, void* kv_cache, hipStream_t s, StepRegime regime) {
@@ -783,13 +813,14 @@ static int stack_enqueue_decode(eet_stack* st, const void* tokens, void* out, vo
         return enqueue_decode_layers(st->layers, st->n_layers, tokens, out, kv_cache, st->layer_cache_bytes, act, s, regime);
     }
     const void* in = tokens;
+    bool normalised = false;
     for (int l = 0; l < st->n_layers; ++l) {
         const bool last = l == st->n_layers - 1;
         void* o = last ? out : static_cast<void*>(st->ws + st->act[l & 1]);
         char* kv = static_cast<char*>(kv_cache) + (size_t)l * st->layer_cache_bytes;
         const int ln = last ? 0 : l + 1;                                    // the step that follows this layer's
         const int rc = enqueue_decode(st->layers[l], in, o, kv, s, last, regime,    // lengths shared: advanced once, at the end
-                                      st->layers[ln], static_cast<char*>(kv_cache) + (size_t)ln * st->layer_cache_bytes);
+                                      st->layers[ln], static_cast<char*>(kv_cache) + (size_t)ln * st->layer_cache_bytes, &normalised);
         if (rc != EET_OK) return rc;
         in = o;
     }

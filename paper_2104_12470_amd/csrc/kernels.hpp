@@ -136,6 +136,7 @@ struct GemmArgs {
     const half_t* fin_beta;
     half_t* fin_y;
     float fin_eps;
+    int fin_as_launch;            // 1: in the order of additions of launch_layernorm for as many rows, so that a row has the bits it would have from there
 };
 // For a bias+residual projection that launch_gemm would give to gemm_stream and that then can leave row statistics for
 // `consumer` (which gemm_stream must take too): the layout of row_stats_out (workgroups, columns per workgroup); else false.

@@ -279,7 +279,16 @@ hipError_t launch_finish_rows(const GemmArgs& a, hipStream_t s) {
 #define EET_FINISH(NT, NV)                                                                                                       \
     hipLaunchKernelGGL((finish_rows<NT, NV>), grid, dim3(NT), 0, s, a.part, a.k_ranges, (int64_t)a.M * a.N, a.bias, a.res,       \
                        a.res_row_map, a.y, a.out_row_map, a.fin_gamma, a.fin_beta, a.fin_y, a.fin_eps, a.N, a.bump_lens, a.bump_count)
-    if (a.N <= 1024) EET_FINISH(128, 1);
+    if (a.fin_gamma != nullptr && a.fin_as_launch && a.N <= 2048 && a.M >= kLayerNormWaveRows) {       // layernorm_wave: one wave per row
+        if (a.N <= 512) EET_FINISH(64, 1);
+        else if (a.N <= 1024) EET_FINISH(64, 2);
+        else EET_FINISH(64, 4);
+    } else if (a.fin_gamma != nullptr && a.fin_as_launch && a.N > 2048) {                               // layernorm_cached: 256 threads
+        if (a.N <= 4096) EET_FINISH(256, 2);
+        else if (a.N <= 8192) EET_FINISH(256, 4);
+        else if (a.N <= kFinishRowsMaxWidth) EET_FINISH(256, 8);
+        else return hipErrorInvalidValue;
+    } else if (a.N <= 1024) EET_FINISH(128, 1);
     else if (a.N <= 2048) EET_FINISH(256, 1);
     else if (a.N <= 4096) EET_FINISH(512, 1);
     else if (a.N <= 8192) EET_FINISH(512, 2);
