@@ -187,6 +187,28 @@ __device__ __forceinline__ float row_sum(float v) {
     return v;
 }
 
+// E columns of the input of the first layer, from column c on
+template <int E>
+__device__ __forceinline__ void input_row(const StepArgs& a, int row, int c, half_t (&out)[E]) {
+    typedef half_t halfE __attribute__((ext_vector_type(E), aligned(E == 4 ? 8 : 16)));
+    halfE v;
+    if (a.tok.ids == nullptr) {
+        v = *reinterpret_cast<const halfE*>(a.x + (size_t)row * a.H + c);
+    } else {
+        const int id = a.tok.ids[row], pos = a.lens[row];
+        if (id < 0 || id >= a.tok.vocab || pos < 0 || pos >= a.tok.max_pos) {
+#pragma unroll
+            for (int e = 0; e < E; ++e) v[e] = no_value();
+        } else {
+            const halfE t = *reinterpret_cast<const halfE*>(a.tok.wte + (size_t)id * a.H + c), p = *reinterpret_cast<const halfE*>(a.tok.wpe + (size_t)pos * a.H + c);
+#pragma unroll
+            for (int e = 0; e < E; ++e) v[e] = (half_t)((float)t[e] + (float)p[e]);     // exact in fp32, rounded once
+        }
+    }
+#pragma unroll
+    for (int e = 0; e < E; ++e) out[e] = v[e];
+}
+
 template <int ROWS, int U, int NT, int PH, bool ONCE>
 __device__ __forceinline__ void project(const StepArgs& a, const Where& w, StepSmem& sm, int tile) {
     constexpr bool LN = PH == kStepQkv || PH == kStepFfn1, RES = PH == kStepOut || PH == kStepFfn2;
@@ -247,7 +269,12 @@ __device__ __forceinline__ void project(const StepArgs& a, const Where& w, StepS
             if (which != 0 && epos >= 0 && epos < a.max_seq)      // past the capacity (replays the host never saw): dropped
                 slot = (which == 1 ? L.k_cache : L.v_cache) + ((size_t)(em * a.heads + c / a.d) * a.max_seq + epos) * a.d + c % a.d;
         }
-        if (PH == kStepOut && first) er = *reinterpret_cast<const half4v*>(a.x + (size_t)em * H + en);
+        if (PH == kStepOut && first) {
+            half_t r[4];
+            input_row(a, em, en, r);
+            er = half4v{r[0], r[1], r[2], r[3]};
+            if (a.tok.ids != nullptr) *reinterpret_cast<half4v*>(a.tok.rows + (size_t)em * H + en) = er;
+        }
     }
     // weights into matrix-operand layout by way of LDS (whole lines per load instruction), while there is nothing else to do: two
     // 16-row units at a time
@@ -284,7 +311,12 @@ __device__ __forceinline__ void project(const StepArgs& a, const Where& w, StepS
     if (PH == kStepQkv && first) {
 #pragma unroll
         for (int s = 0; s < STEPS; ++s)
-            if (has(s) && mine) xv[s] = *reinterpret_cast<const halfE*>(a.x + (size_t)row * H + column(s));
+            if (has(s) && mine) {
+                half_t r[E];
+                input_row(a, row, column(s), r);
+#pragma unroll
+                for (int e = 0; e < E; ++e) xv[s][e] = r[e];
+            }
     } else if (PH == kStepOut && a.splits > 1) {
         // the attention's key ranges: merge them (common maximum, rescaled sums, one division)
         const int stride = step_range_words(a.d);

@@ -556,7 +556,7 @@ static bool decodes_in_one_launch(const eet_layer* L, StepRegime regime) {
 // A decode step through `n` layers of one configuration that share a workspace, as one launch per kStepLayers of them.  The last
 // layer's launch advances the lengths.  act: where a launch leaves its output for the next (two buffers, alternating).
 static int enqueue_decode_layers(eet_layer* const* layers, int n, const void* tokens, void* out, void* kv_cache, size_t layer_cache_bytes,
-                                 void* const* act, hipStream_t s, StepRegime regime) {
+                                 void* const* act, hipStream_t s, StepRegime regime, const StepTokens& tok = {}) {
     const eet_layer* L0 = layers[0];
     const eet_layer_config& c = L0->cfg;
     const int H = c.hidden, F = c.ffn;
@@ -567,6 +567,7 @@ static int enqueue_decode_layers(eet_layer* const* layers, int n, const void* to
         const bool last = l0 + a.n_layers == n;
         void* o = last ? out : act[k & 1];
         a.x = static_cast<const half_t*>(in);
+        if (l0 == 0) a.tok = tok;
         a.out = static_cast<half_t*>(o);
         a.ctl = reinterpret_cast<unsigned long long*>(L0->ws + L0->lay.step);
         a.set_words = L0->lay.step_set_words;
@@ -807,10 +808,10 @@ static const eet_layer* normalises_for(const eet_stack* st, int l, bool pads) {
     return l + 1 < st->n_layers && !stack_layer_needs_setup(l + 1, st->n_layers, pads) ? st->layers[l + 1] : nullptr;
 }
 
-static int stack_enqueue_decode(eet_stack* st, const void* tokens, void* out, void* kv_cache, hipStream_t s, StepRegime regime) {
+static int stack_enqueue_decode(eet_stack* st, const void* tokens, void* out, void* kv_cache, hipStream_t s, StepRegime regime, const StepTokens& tok) {
     if (decodes_in_one_launch(st->layers[0], regime)) {
         void* act[2] = {st->ws + st->act[0], st->ws + st->act[1]};
-        return enqueue_decode_layers(st->layers, st->n_layers, tokens, out, kv_cache, st->layer_cache_bytes, act, s, regime);
+        return enqueue_decode_layers(st->layers, st->n_layers, tokens, out, kv_cache, st->layer_cache_bytes, act, s, regime, tok);
     }
     const void* in = tokens;
     bool normalised = false;
@@ -827,7 +828,9 @@ static int stack_enqueue_decode(eet_stack* st, const void* tokens, void* out, vo
     return EET_OK;
 }
 
-int eet_stack_decode_step(eet_stack_t* st, const void* tokens, void* out, void* kv_cache, void* hip_stream) {
+// tok: where the rows of `tokens` come from, for a step that is one launch (it embeds them itself: 2 to 4 us less per token than behind a launch of
+// its own); elsewhere they are embedded first.
+static int stack_decode_step(eet_stack* st, const void* tokens, void* out, void* kv_cache, void* hip_stream, const StepTokens& tok) {
     if (!st || !tokens || !out || !kv_cache) return fail(EET_ERR_INVALID_ARG, "eet_stack_decode_step: null argument");
     if (st->batch == 0) return fail(EET_ERR_STATE, "eet_stack_decode_step: no prefill has been run on this stack");
     if (!aligned16(tokens) || !aligned16(out) || !aligned16(kv_cache))
@@ -849,15 +852,21 @@ int eet_stack_decode_step(eet_stack_t* st, const void* tokens, void* out, void* 
         hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
         if (hipStreamIsCapturing(s, &cs) != hipSuccess || cs != hipStreamCaptureStatusNone) graph = false;
     }
+    if (tok.ids != nullptr && !decodes_in_one_launch(st->layers[0], regime)) {
+        SeqLens none;
+        std::memset(&none, 0, sizeof(none));
+        EET_LAUNCH(launch_embedding(tok.ids, none, reinterpret_cast<const int32_t*>(st->layers[0]->ws + st->layers[0]->lay.lens), B, 1, st->cfg.hidden, tok.vocab,
+                                    tok.max_pos, tok.wte, tok.wpe, tok.rows, nullptr, s), "embedding");
+    }
     if (!graph) {
-        if (const int rc = stack_enqueue_decode(st, tokens, out, kv_cache, s, regime)) return rc;
+        if (const int rc = stack_enqueue_decode(st, tokens, out, kv_cache, s, regime, tok)) return rc;
     } else {
         if (st->g_tokens != tokens || st->g_out != out || st->g_kv != kv_cache || st->g_batch != B) drop_graphs(st);
         hipGraphExec_t& exec = st->exec[regime];
         if (!exec) {
             hipGraph_t g = nullptr;
             EET_LAUNCH(hipStreamBeginCapture(s, hipStreamCaptureModeThreadLocal), "begin capture");
-            const int rc = stack_enqueue_decode(st, tokens, out, kv_cache, s, regime);
+            const int rc = stack_enqueue_decode(st, tokens, out, kv_cache, s, regime, tok);
             const hipError_t e = hipStreamEndCapture(s, &g);
             if (rc != EET_OK) {
                 if (g) (void)hipGraphDestroy(g);
@@ -876,6 +885,10 @@ int eet_stack_decode_step(eet_stack_t* st, const void* tokens, void* out, void* 
     }
     for (int b = 0; b < B; ++b) st->host_lens[b] += 1;
     return EET_OK;
+}
+
+int eet_stack_decode_step(eet_stack_t* st, const void* tokens, void* out, void* kv_cache, void* hip_stream) {
+    return stack_decode_step(st, tokens, out, kv_cache, hip_stream, StepTokens{});
 }
 
 int eet_stack_restore(eet_stack_t* st, const int32_t* cache_lens, int32_t batch, void* hip_stream) {
@@ -1047,18 +1060,14 @@ int eet_model_decode_step(eet_model_t* m, const int32_t* ids, void* logits, int3
     eet_stack* st = m->st;
     if (st->batch == 0) return fail(EET_ERR_STATE, "eet_model_decode_step: no prefill has been run on this model");
     const int B = st->batch;
-    for (int b = 0; b < B; ++b)      // before anything is enqueued (the stack call repeats the check, but after the embedding)
+    for (int b = 0; b < B; ++b)      // (the stack call repeats the check, under its own name)
         if (st->host_lens[b] + 1 > st->cfg.max_seq)
             return fail(EET_ERR_CAPACITY, "eet_model_decode_step: sequence %d is at the cache capacity %d", b, st->cfg.max_seq);
     hipStream_t s = static_cast<hipStream_t>(hip_stream);
     void* x = m->ws + m->x_dec;
     void* y = m->ws + m->y_dec;
-    const int32_t* d_lens = reinterpret_cast<const int32_t*>(st->layers[0]->ws + st->layers[0]->lay.lens);
-    SeqLens none;
-    std::memset(&none, 0, sizeof(none));
-    EET_LAUNCH(launch_embedding(ids, none, d_lens, B, 1, st->cfg.hidden, m->mc.vocab, m->mc.max_pos, (const half_t*)m->w.wte,
-                                (const half_t*)m->w.wpe, (half_t*)x, nullptr, s), "embedding");
-    if (const int rc = eet_stack_decode_step(st, x, y, kv_cache, hip_stream)) return rc;
+    const StepTokens tok{ids, (const half_t*)m->w.wte, (const half_t*)m->w.wpe, static_cast<half_t*>(x), m->mc.vocab, m->mc.max_pos};
+    if (const int rc = stack_decode_step(st, x, y, kv_cache, hip_stream, tok)) return rc;
     m->hidden_in = x;
     m->hidden_out = y;
     return model_head(m, y, nullptr, B, logits, next_ids, s);

@@ -212,8 +212,17 @@ struct StepBuffer {                      // part of an exchange set (words): blo
     uint32_t at, block;
     int log_cols;
 };
+// Where the input of a decode step comes from when it is not handed over: row m = wte[ids[m]] + wpe[lens[m]] (launch_embedding's rows, its NaN
+// included), which the launch also leaves in `rows`
+struct StepTokens {
+    const int32_t* ids;                  // nullptr: StepArgs::x
+    const half_t *wte, *wpe;
+    half_t* rows;
+    int vocab, max_pos;
+};
 struct StepArgs {
     const half_t* x;                     // [M, H] input of the first layer
+    StepTokens tok;
     half_t* out;                         // [M, H] output of the last
     unsigned long long* ctl;             // kStepCtlWords words, then the two exchange sets
     uint32_t set_words;                  // words of a set: decode_step_set_words of the layer's configuration, whatever M is
