@@ -919,13 +919,13 @@ struct eet_model {
     eet_model_config mc;
     eet_model_weights w;
     char* ws;
-    size_t zero_bias, last_row, x_dec, y_dec, ln_out, best;   // byte offsets into ws; arrived: behind the zero bias
+    size_t zero_bias, last_row, x_dec, y_dec, ln_out;   // byte offsets into ws
     const void* hidden_in;                               // what the latest call left behind (see eet_model_hidden_states)
     const void* hidden_out;
 };
 
 struct ModelLayout {
-    size_t zero_bias, last_row, x_dec, y_dec, ln_out, best, total;
+    size_t zero_bias, last_row, x_dec, y_dec, ln_out, total;
 };
 
 // What model creation clears: the bias of the output projection, and behind it the counter of the launch that holds all of the head
@@ -941,7 +941,6 @@ static ModelLayout model_layout(const eet_layer_config* c, const eet_model_confi
     l.x_dec = off;     off += row;
     l.y_dec = off;     off += row;
     l.ln_out = off;    off += row;
-    l.best = off;      off += sizeof(unsigned long long) * kHeadMaxRows * kHeadGroups;
     l.total = off;
     return l;
 }
@@ -983,7 +982,7 @@ int eet_model_create(eet_stack_t* stack, const eet_layer_config* cfg, const eet_
     if (!m) return fail(EET_ERR_INVALID_ARG, "eet_model_create: out of host memory");
     const ModelLayout l = model_layout(cfg, mcfg);
     m->st = stack; m->mc = *mcfg; m->w = *weights; m->ws = static_cast<char*>(workspace);
-    m->zero_bias = l.zero_bias; m->last_row = l.last_row; m->x_dec = l.x_dec; m->y_dec = l.y_dec; m->ln_out = l.ln_out; m->best = l.best;
+    m->zero_bias = l.zero_bias; m->last_row = l.last_row; m->x_dec = l.x_dec; m->y_dec = l.y_dec; m->ln_out = l.ln_out;
     m->hidden_in = m->hidden_out = nullptr;
     const hipError_t e = hipMemset(m->ws + m->zero_bias, 0, zeroed_bytes(mcfg));
     if (e != hipSuccess) {
@@ -998,11 +997,14 @@ int eet_model_create(eet_stack_t* stack, const eet_layer_config* cfg, const eet_
 static int model_head(eet_model* m, const void* hidden, const int32_t* row_map, int batch, void* logits, int32_t* next_ids,
                       hipStream_t s) {
     const eet_layer_config& c = m->st->cfg;
-    if (head_takes(batch, c.hidden, m->mc.vocab_padded)) {
+    // The best columns of its workgroups lie in the layers' scratch (feed-forward and row buffers), which nobody needs any more
+    const eet_layer* L0 = m->st->layers[0];
+    const bool room = L0->lay.buf_y - L0->lay.buf_f >= sizeof(unsigned long long) * (size_t)batch * kHeadGroups;
+    if (room && head_takes(batch, c.hidden, m->mc.vocab_padded)) {
         HeadArgs h{};
         h.x = (const half_t*)hidden; h.row_map = row_map; h.gamma = (const half_t*)m->w.lnf_g; h.beta = (const half_t*)m->w.lnf_b; h.eps = c.ln_eps;
         h.w = (const half_t*)m->w.wte; h.logits = (half_t*)logits; h.next_ids = next_ids;
-        h.best = reinterpret_cast<unsigned long long*>(m->ws + m->best);
+        h.best = reinterpret_cast<unsigned long long*>(L0->ws + L0->lay.buf_f);
         h.arrived = reinterpret_cast<uint32_t*>(m->ws + m->zero_bias + counter_at(&m->mc));
         h.M = batch; h.N = m->mc.vocab_padded; h.K = c.hidden; h.vocab = m->mc.vocab;
         EET_LAUNCH(launch_head(h, s), "final layernorm, output projection and greedy choice");

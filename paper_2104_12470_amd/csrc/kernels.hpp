@@ -255,7 +255,7 @@ struct HeadArgs {
     const half_t* w;            // [N, K] the table
     half_t* logits;             // [M, N]
     int32_t* next_ids;          // [M]: first maximum of columns [0, vocab); nullptr: no choice, and the two below are not looked at
-    unsigned long long* best;   // [M, kHeadGroups]
+    unsigned long long* best;   // room for [M, kHeadGroups]
     uint32_t* arrived;          // zero; left zero
     int M, N, K, vocab;
     float eps;

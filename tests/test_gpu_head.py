@@ -15,13 +15,13 @@ pytestmark = pytest.mark.gpu
 def test_logits_and_choice(hidden, rows, vocab):
     from paper_2104_12470_amd import eet
     S, cap = 3, 8
-    w = wl.Workload(f"head{hidden}x{rows}", 73, hidden, hidden // 64, 128, 1, rows, S, 1, S, 2, cap)
+    w = wl.Workload(f"head{hidden}x{rows}", 73, hidden, hidden // 64, 896, 1, rows, S, 1, S, 2, cap)
     head = wl.model_head(w, vocab, cap)
     head["lnf_g"] = (1 + 0.1 * wl.normal(73, 11, (hidden,))).astype(np.float16)
     head["lnf_b"] = (0.1 * wl.normal(73, 12, (hidden,))).astype(np.float16)
     tie = vocab // 2                                              # equal columns: the first of them is chosen
     head["wte"][tie:] = head["wte"][:vocab - tie][:len(head["wte"][tie:])]
-    cfg = eet.make_config(hidden, hidden // 64, 128, rows, S, cap, w.ln_eps)
+    cfg = eet.make_config(hidden, hidden // 64, 896, rows, S, cap, w.ln_eps)
     W = {k: torch.from_numpy(v) for k, v in wl.layer_weights(w, 0, random_affine=True).items()}
     model = eet.DecoderModel(cfg, [W], {k: torch.from_numpy(v) for k, v in head.items()}, vocab)
     ids = dev(wl.uniform_int(73, 13, rows * S, 0, vocab - 1).reshape(rows, S).astype(np.int32))
