@@ -1,6 +1,6 @@
 // Decode steps of small layers: all layers of a step in one launch.
 //
-// A decode step of a small layer (up to 16 sequences, a few MB per projection) is a chain of five dependent phases, and as five
+// A decode step of a small layer (up to 16 sequences, or several groups of as many, a few MB per projection) is a chain of five dependent phases, and as five
 // launches each of them costs the floor of a dependent launch (drain, start, first trip to memory: about 4 us for 1 to 8 MB of
 // weights), whatever its bytes.  Here the chain runs inside one launch.  A workgroup is one ITEM of one layer: 64 columns of a projection (16
 // of the second feed-forward one), or one key range of a (sequence, head) pair.  It requests its weights (or K/V rows), up to 256 KB, into
@@ -32,6 +32,10 @@
 //               not come read as NaN, an item that found its exchange set still in use hands NaN on, and both say so in ctl: the sets
 //               may hold words of another layer from then on, so the output of every later launch is NaN until the area is set up again
 //               (prefill, restore).
+//
+//   groups      Steps of more sequences are groups of up to 16 (8 of the wider layers), each a chain of its own: a ticket counter, a count of resets
+//               and exchange sets for every group, workgroups dealt to the groups in turn.  What another step leaves out it does not touch, so
+//               steps of other numbers of sequences may come in between.
 //
 // K/V rows of earlier tokens are ordinary memory (written by earlier launches); the new token's K and V row reaches the attention
 // through the exchange set, and the cache for the steps that follow.
@@ -106,6 +110,8 @@ struct Where {
     int layer;                                     // inside the launch
     uint32_t g;                                    // layer number since the last prefill
     int lane, wave, tid;
+    int row0, M;                                   // this group's rows
+    word_t* ctl;                                   // ... and control words
     word_t* set;                                   // exchange set of layer g
     word_t* other;                                 // ... and of layers g-1 and g+1
     bool void_area;                                // a wait was given up since the area was set up
@@ -114,15 +120,15 @@ struct Where {
 // A wait came to its bound: said in ctl.  (At the wait itself, and read with the item's number in later launches, where neither costs the chain
 // anything: a flag looked at before each result is handed on was 10.56 -> 10.72 us per layer-step of 24 x hidden 1024, ctl looked at before
 // the last output is written up to 0.9 us per launch, 28.2 -> 29.0 for one layer of hidden 1280.)
-__device__ __forceinline__ void give_up(const StepArgs& a) { __hip_atomic_fetch_or(a.ctl, (word_t)kStepGaveUp, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+__device__ __forceinline__ void give_up(const Where& w) { __hip_atomic_fetch_or(w.ctl, (word_t)kStepGaveUp, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 
 // Thread 0 waits until the exchange set is this layer's, then for one word of the phase before the one whose output the item
 // needs: the tight polling that follows lasts one phase instead of a whole layer.  `input`: a word of the input itself, for the QKV
 // projection, whose faster items empty the set of that earlier word as soon as they have all of theirs; looked at now and then only, since
 // every look at a line that is still to be written makes the write slower.  (Giving up on that word loses nothing: the input
 // itself is waited for next.)
-__device__ __forceinline__ void wait_resets(const StepArgs& a, StepSmem& sm, uint32_t layers) {
-    const uint32_t* resets = reinterpret_cast<const uint32_t*>(a.ctl + 16);
+__device__ __forceinline__ void wait_resets(const StepArgs& a, const Where& w, StepSmem& sm, uint32_t layers) {
+    const uint32_t* resets = reinterpret_cast<const uint32_t*>(w.ctl + 16);
     const uint32_t target = layers * (uint32_t)a.n_qkv;
     int spin = 0;
     while (true) {
@@ -131,30 +137,30 @@ __device__ __forceinline__ void wait_resets(const StepArgs& a, StepSmem& sm, uin
         __builtin_amdgcn_s_sleep(16);
     }
     sm.in_use = 1;
-    give_up(a);
+    give_up(w);
 }
 // -> whether that set came in time
 __device__ __forceinline__ bool gate(const StepArgs& a, const Where& w, StepSmem& sm, const word_t* before, const word_t* input, bool emptied_by_this_layer) {
     if (w.tid == 0) {
-        wait_resets(a, sm, w.g);
+        wait_resets(a, w, sm, w.g);
         if (before != nullptr)
             for (int spin = 0; spin < kSpinLimit; ++spin) {
                 if (ld_word(before) != kEmpty) break;
                 if (input != nullptr && spin % 16 == 15 && ld_word(input) != kEmpty) break;
                 __builtin_amdgcn_s_sleep(4);
             }
-        if (emptied_by_this_layer) wait_resets(a, sm, w.g + 1u);
+        if (emptied_by_this_layer) wait_resets(a, w, sm, w.g + 1u);
     }
     __syncthreads();
     return sm.in_use == 0;
 }
 
-__device__ __forceinline__ word_t wait_word(const StepArgs& a, const word_t* p) {
+__device__ __forceinline__ word_t wait_word(const Where& w, const word_t* p) {
     word_t v;
     int spin = 0;
     do v = ld_word(p);
     while ((v == kEmpty) & (++spin < kSpinLimit));
-    if (v == kEmpty) give_up(a);
+    if (v == kEmpty) give_up(w);
     return v;
 }
 
@@ -218,7 +224,7 @@ __device__ __forceinline__ void project(const StepArgs& a, const Where& w, StepS
     typedef half_t halfE __attribute__((ext_vector_type(E), aligned(E == 4 ? 8 : 16)));
     constexpr int XU = ROWS == 16 ? 2 : 4;                     // units of the input staged at a time
     const StepLayer& L = a.layer[w.layer];
-    const int M = a.M, H = a.H, K = PH == kStepFfn2 ? a.F : H;
+    const int M = w.M, H = a.H, K = PH == kStepFfn2 ? a.F : H;
     const int units = K / 64, n0 = tile * TN;
     const int lane = w.lane, wave = w.wave;
     const int wrow = lane >> 3, wchunk = lane & 7;             // this lane's 16 bytes of 8 weight rows
@@ -265,15 +271,15 @@ __device__ __forceinline__ void project(const StepArgs& a, const Where& w, StepS
     if (writer) {
         eb = *reinterpret_cast<const half4v*>(bias + en);
         if (PH == kStepQkv) {
-            const int which = n0 / H, c = en - which * H, epos = a.lens[em];      // (a tile lies in one of Q, K and V)
+            const int which = n0 / H, c = en - which * H, epos = a.lens[w.row0 + em];      // (a tile lies in one of Q, K and V)
             if (which != 0 && epos >= 0 && epos < a.max_seq)      // past the capacity (replays the host never saw): dropped
-                slot = (which == 1 ? L.k_cache : L.v_cache) + ((size_t)(em * a.heads + c / a.d) * a.max_seq + epos) * a.d + c % a.d;
+                slot = (which == 1 ? L.k_cache : L.v_cache) + ((size_t)((w.row0 + em) * a.heads + c / a.d) * a.max_seq + epos) * a.d + c % a.d;
         }
         if (PH == kStepOut && first) {
             half_t r[4];
-            input_row(a, em, en, r);
+            input_row(a, w.row0 + em, en, r);
             er = half4v{r[0], r[1], r[2], r[3]};
-            if (a.tok.ids != nullptr) *reinterpret_cast<half4v*>(a.tok.rows + (size_t)em * H + en) = er;
+            if (a.tok.ids != nullptr) *reinterpret_cast<half4v*>(a.tok.rows + (size_t)(w.row0 + em) * H + en) = er;
         }
     }
     // weights into matrix-operand layout by way of LDS (whole lines per load instruction), while there is nothing else to do: two
@@ -302,7 +308,7 @@ __device__ __forceinline__ void project(const StepArgs& a, const Where& w, StepS
                          : PH == kStepFfn1 ? w.set + a.bctx.at : w.set + a.by.at;
     const bool in_time = gate(a, w, sm, before, PH == kStepQkv ? w.set + in.at : nullptr, PH == kStepFfn2);
     if (RES && writer && !(PH == kStepOut && first))
-        er = __builtin_bit_cast(half4v, wait_word(a, w.set + word_at(PH == kStepOut ? a.bx : a.by, em, en)));
+        er = __builtin_bit_cast(half4v, wait_word(w, w.set + word_at(PH == kStepOut ? a.bx : a.by, em, en)));
     // not in time: every value of the item becomes NaN, by way of the LayerNorm or of the residual
     const float eps = in_time ? a.eps : __builtin_nanf("");
     if (RES && !in_time) er = half4v{no_value(), no_value(), no_value(), no_value()};
@@ -313,7 +319,7 @@ __device__ __forceinline__ void project(const StepArgs& a, const Where& w, StepS
         for (int s = 0; s < STEPS; ++s)
             if (has(s) && mine) {
                 half_t r[E];
-                input_row(a, row, column(s), r);
+                input_row(a, w.row0 + row, column(s), r);
 #pragma unroll
                 for (int e = 0; e < E; ++e) xv[s][e] = r[e];
             }
@@ -346,7 +352,7 @@ __device__ __forceinline__ void project(const StepArgs& a, const Where& w, StepS
 #pragma unroll
                             for (int e = 0; e <= E / 2; ++e) ok &= v[r][e] != kEmpty;
                     } while (!ok & (++spin < kSpinLimit));
-                    if (!ok) give_up(a);
+                    if (!ok) give_up(w);
 #pragma unroll
                     for (int r = 0; r < 2; ++r) {
                         const float2v ml = __builtin_bit_cast(float2v, v[r][E / 2]);
@@ -402,7 +408,7 @@ __device__ __forceinline__ void project(const StepArgs& a, const Where& w, StepS
                 }
             ok = __all(most != kEmptyHalf);
         } while (!ok & (++spin < kSpinLimit));
-        if (!ok) give_up(a);
+        if (!ok) give_up(w);
         struct Words { word_t w[VW]; };
 #pragma unroll
         for (int s = 0; s < STEPS; ++s) {
@@ -417,7 +423,7 @@ __device__ __forceinline__ void project(const StepArgs& a, const Where& w, StepS
         // everyone who reads the cache lengths in this step is an ancestor of this item's input
         if (last && a.bump && tile == 0) {
             __syncthreads();                                   // all waves have their share of the input: together, all of it
-            if (w.tid < M) a.lens[w.tid] += 1;
+            if (w.tid < M) a.lens[w.row0 + w.tid] += 1;
         }
     }
 
@@ -536,7 +542,7 @@ __device__ __forceinline__ void project(const StepArgs& a, const Where& w, StepS
         } else {
             if (last) {
                 if (w.void_area) out = half4v{no_value(), no_value(), no_value(), no_value()};
-                *reinterpret_cast<half4v*>(a.out + (size_t)em * H + en) = out;
+                *reinterpret_cast<half4v*>(a.out + (size_t)(w.row0 + em) * H + en) = out;
             } else publish(w.other + word_at(a.bx, em, en), out);
         }
     }
@@ -544,7 +550,7 @@ __device__ __forceinline__ void project(const StepArgs& a, const Where& w, StepS
         // what this item emptied of the other set is empty in memory before it is counted
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         __syncthreads();
-        if (w.tid == 0) __hip_atomic_fetch_add(reinterpret_cast<uint32_t*>(a.ctl + 16), 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (w.tid == 0) __hip_atomic_fetch_add(reinterpret_cast<uint32_t*>(w.ctl + 16), 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
 }
 
@@ -558,8 +564,9 @@ __device__ __forceinline__ void attend(const StepArgs& a, const Where& w, StepSm
     constexpr float kNone = -1e30f, kLog2e = 1.4426950408889634f;
     const StepLayer& L = a.layer[w.layer];
     const int sp = item % a.splits, bh = item / a.splits, b = bh / a.heads, h = bh - b * a.heads;
+    if (b >= w.M) return;                                     // (the last group may have fewer rows)
     const int lane = w.lane, wave = w.wave, kslot = lane / LPK, chunk = lane % LPK;
-    int n = a.lens[b];                                        // cached keys; the new token's is number n
+    int n = a.lens[w.row0 + b];                                        // cached keys; the new token's is number n
     n = n < 0 ? 0 : n;
     const bool room = n < a.max_seq;
     const int visible = room ? n + 1 : a.max_seq;
@@ -568,8 +575,8 @@ __device__ __forceinline__ void attend(const StepArgs& a, const Where& w, StepSm
     const int c0 = sp * per, c1 = c0 + per < visible ? c0 + per : visible;
     const bool has_new = room && c0 <= n && n < c1;
     const int ce = has_new ? n : c1;                          // cached keys of the range: [c0, ce)
-    const char* kbase = reinterpret_cast<const char*>(L.k_cache + (size_t)bh * a.max_seq * D);
-    const char* vbase = reinterpret_cast<const char*>(L.v_cache + (size_t)bh * a.max_seq * D);
+    const char* kbase = reinterpret_cast<const char*>(L.k_cache + (size_t)(w.row0 * a.heads + bh) * a.max_seq * D);
+    const char* vbase = reinterpret_cast<const char*>(L.v_cache + (size_t)(w.row0 * a.heads + bh) * a.max_seq * D);
     half8v kr[PF][U], vr[PF][U];
     auto request = [&](half8v (&kf)[U], half8v (&vf)[U], int j0) {
 #pragma unroll
@@ -610,7 +617,7 @@ __device__ __forceinline__ void attend(const StepArgs& a, const Where& w, StepSm
             if (take_new) ok &= v[2] != kEmpty && v[3] != kEmpty && v[4] != kEmpty && v[5] != kEmpty;
             ok = __all(ok);
         } while (!ok & (++spin < kSpinLimit));
-        if (!ok) give_up(a);
+        if (!ok) give_up(w);
         auto join = [](word_t x, word_t y) {
             return __builtin_shufflevector(__builtin_bit_cast(half4v, x), __builtin_bit_cast(half4v, y), 0, 1, 2, 3, 4, 5, 6, 7);
         };
@@ -733,10 +740,15 @@ __global__ __launch_bounds__(kSThreads, 2) void decode_layers(StepArgs a) {
     w.wave = __builtin_amdgcn_readfirstlane(w.tid >> 6);
     // The number of this item, in the order in which workgroups start (low half), and the layer number of the launch's first layer
     // (high half).  The launch's last workgroup to ask turns both on for the next launch.
+    const int group = (int)blockIdx.x % a.groups;
+    w.row0 = group * a.rows;
+    w.M = a.M - w.row0 < a.rows ? a.M - w.row0 : a.rows;
+    w.ctl = a.ctl + (size_t)group * (kStepCtlWords + 2 * (size_t)a.set_words);
+    word_t* const ex = w.ctl + kStepCtlWords;
     if (w.tid == 0) {
-        const word_t t = __hip_atomic_fetch_add(a.ctl, (word_t)1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        const word_t t = __hip_atomic_fetch_add(w.ctl, (word_t)1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         if (((uint32_t)t & ~kStepGaveUp) == (uint32_t)a.items - 1u)
-            __hip_atomic_fetch_add(a.ctl, ((word_t)a.n_layers << 32) - (word_t)a.items, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            __hip_atomic_fetch_add(w.ctl, ((word_t)a.n_layers << 32) - (word_t)a.items, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         sm.ticket = t;
         sm.in_use = 0;
     }
@@ -746,8 +758,8 @@ __global__ __launch_bounds__(kSThreads, 2) void decode_layers(StepArgs a) {
     w.layer = (int)(item / (uint32_t)a.per_layer);
     int r = (int)(item - (uint32_t)w.layer * (uint32_t)a.per_layer);
     w.g = g0 + (uint32_t)w.layer;
-    w.set = a.ex + (size_t)(w.g & 1u) * a.set_words;
-    w.other = a.ex + (size_t)(~w.g & 1u) * a.set_words;
+    w.set = ex + (size_t)(w.g & 1u) * a.set_words;
+    w.other = ex + (size_t)(~w.g & 1u) * a.set_words;
     w.void_area = (low & kStepGaveUp) != 0;
     if (r < a.n_qkv) { project<ROWS, UH, NTH, kStepQkv, ONCE>(a, w, sm, r); return; }
     r -= a.n_qkv;
@@ -776,10 +788,29 @@ int step_splits(int rows, int heads, int capacity) {
 
 // More than 8 rows double the registers of the input: only where the weights leave them.
 static bool step_is_narrow(int hidden, int ffn) { return hidden <= 64 * kSWaves * 2 && ffn <= 64 * kSWaves * 8; }
-bool decode_step_fits(int rows, int hidden, int heads, int ffn) {
+static int step_group_rows(int hidden, int ffn) { return step_is_narrow(hidden, ffn) ? 16 : 8; }
+// The groups of a step of `rows` rows (as even as they come) and the rows of the largest
+static void step_groups(int rows, int hidden, int ffn, int& groups, int& group_rows) {
+    const int most = step_group_rows(hidden, ffn);
+    group_rows = (rows + (rows + most - 1) / most - 1) / ((rows + most - 1) / most);
+    groups = (rows + group_rows - 1) / group_rows;
+}
+// More than one group: what the launch costs is its items, about 7 us per 256 of them beyond the first 512, against launches that grow
+// little with the rows.  us per layer-step (stacks of 2, 200 to 400 keys unless said), launch by launch / one launch, items: 24 sequences of hidden 256 27.5 / 14.3 (156);
+// 128 of it 33.8 / 23.2 (624); 96 of 512 (heads of 64) 39.5 / 34.1 (1344); 32 of 768 36.3 / 25.8 (672), 64 42.0 / 37.6 (1344), 20 to 40 keys 34.9 / 34.5, 128 60 /
+// 70 (2688); 1024 x 4096, 24 37.8 / 26.9 (768), 48 45.4 / 40.3 (1344), 64 51.1 / 49.1, 20 to 40 keys 41.6 / 45.2 (1792).  Where it stops besides: more than 256
+// pairs over 512 slots and more keep the attention kernel of their own, whose bits are the operator's (24 x 16 heads, 800 to 1600 keys 55.0 / 41.7, so
+// not for speed); up to 256 pairs gain there too (24 x 4 heads 33.8 / 18.1).  The wider layers' groups of 8 rows read the weights once more each: level from
+// 16 sequences of 1792 on (43.3 / 45.6), and below that their steps of 9 to 16 stay with the small-layer kernel and its LayerNorms.
+constexpr int kStepGroupItems = 1350;
+bool decode_step_fits(int rows, int hidden, int heads, int ffn, int max_seq) {
     const int d = hidden / heads;
-    return rows >= 1 && rows <= (step_is_narrow(hidden, ffn) ? 16 : 8) && (d == 64 || d == 128) && hidden % 64 == 0 && ffn % 64 == 0 &&
-           hidden <= 64 * kSWaves * kSUnitsH && ffn <= 64 * kSWaves * kSUnitsF;
+    if (rows < 1 || rows > kStepGroups * step_group_rows(hidden, ffn) || (d != 64 && d != 128) || hidden % 64 != 0 || ffn % 64 != 0 ||
+        hidden > 64 * kSWaves * kSUnitsH || ffn > 64 * kSWaves * kSUnitsF) return false;
+    int groups, group_rows;
+    step_groups(rows, hidden, ffn, groups, group_rows);
+    return groups == 1 || (step_is_narrow(hidden, ffn) && groups * (hidden / 16 + ffn / 64 + hidden / 16 + group_rows * heads) <= kStepGroupItems &&
+                           (rows * heads <= 256 || max_seq < 512));
 }
 
 // Long sequences: a CU streams the K/V rows of one item at a time, and next to that the launches that are saved count for little.  Where
@@ -791,6 +822,8 @@ bool decode_step_fits(int rows, int hidden, int heads, int ffn) {
 // 8000 95.7 / 55.6.
 bool decode_step_fits_keys(int rows, int heads, int d, size_t visible) {
     const int pairs = rows * heads;
+    // (several groups of sequences, launch by launch / one launch: 17 of hidden 512, 8500 keys each 79 / 68; of 256, 12000 66 / 91; 20 of 384 89 / 99)
+    if (rows > 16) return visible <= (size_t)8192 * rows;
     return visible <= (size_t)8192 * rows || !(pairs >= 224 || (d == 128 && pairs > 64 && pairs <= 112));
 }
 
@@ -798,10 +831,11 @@ bool decode_step_fits_keys(int rows, int heads, int d, size_t visible) {
 static uint32_t step_layout(StepArgs& a) {
     const int d = a.H / a.heads, log_h = 6;                   // 64 columns per item
     a.d = d;
+    step_groups(a.M, a.H, a.F, a.groups, a.rows);
     a.splits = step_splits(a.M, a.heads, a.max_seq);
     uint32_t at = 0;
     auto buffer = [&](int cols, int log_cols) {
-        const uint32_t block = (uint32_t)((a.M << log_cols) / 4 + 15) / 16 * 16;
+        const uint32_t block = (uint32_t)((a.rows << log_cols) / 4 + 15) / 16 * 16;
         const StepBuffer b{at, block, log_cols};
         at += (uint32_t)(cols >> log_cols) * block;
         return b;
@@ -809,15 +843,26 @@ static uint32_t step_layout(StepArgs& a) {
     a.bx = buffer(a.H, 4);
     a.bqkv = buffer(3 * a.H, log_h);
     a.bctx = buffer(a.H, 6);
-    if (a.splits > 1) at = a.bctx.at + (uint32_t)(a.M * a.heads * a.splits * step_range_words(d));
+    if (a.splits > 1) at = a.bctx.at + (uint32_t)(a.rows * a.heads * a.splits * step_range_words(d));
     a.by = buffer(a.H, log_h);
     a.bf = buffer(a.F, log_h);
     return at;
 }
 
+int decode_step_groups(int max_rows, int hidden, int heads, int ffn, int max_seq) {
+    int most = 0;
+    for (int rows = 1; rows <= max_rows && rows <= kStepGroups * step_group_rows(hidden, ffn); ++rows) {
+        if (!decode_step_fits(rows, hidden, heads, ffn, max_seq)) continue;
+        int groups, group_rows;
+        step_groups(rows, hidden, ffn, groups, group_rows);
+        most = groups > most ? groups : most;
+    }
+    return most;
+}
+
 uint32_t decode_step_set_words(int max_rows, int hidden, int heads, int ffn, int max_seq) {
     uint32_t most = 0;
-    for (int rows = 1; rows <= max_rows && decode_step_fits(rows, hidden, heads, ffn); ++rows) {
+    for (int rows = 1; rows <= max_rows && rows <= step_group_rows(hidden, ffn) && decode_step_fits(rows, hidden, heads, ffn, max_seq); ++rows) {
         StepArgs a{};
         a.M = rows; a.H = hidden; a.heads = heads; a.F = ffn; a.max_seq = max_seq;
         const uint32_t words = step_layout(a);
@@ -828,27 +873,26 @@ uint32_t decode_step_set_words(int max_rows, int hidden, int heads, int ffn, int
 
 hipError_t launch_decode_layers(StepArgs& a, bool read_once, hipStream_t s) {
     if (step_layout(a) > a.set_words) return hipErrorInvalidValue;
-    a.ex = a.ctl + kStepCtlWords;
     const int log_h = a.bqkv.log_cols;
     a.n_qkv = 3 * a.H >> log_h;
-    a.n_att = a.M * a.heads * a.splits;
+    a.n_att = a.rows * a.heads * a.splits;
     a.n_out = a.H >> log_h;
     a.n_ffn1 = a.F >> log_h;
     a.per_layer = a.n_qkv + a.n_att + a.n_out + a.n_ffn1 + a.H / 16;
     a.items = a.per_layer * a.n_layers;
-    const dim3 grid(a.items), block(kSThreads);
+    const dim3 grid(a.items * a.groups), block(kSThreads);
 #define EET_STEP(ROWS, UH, UF) do { if (read_once) hipLaunchKernelGGL((decode_layers<ROWS, UH, 4, UF, true>), grid, block, 0, s, a); \
                                     else hipLaunchKernelGGL((decode_layers<ROWS, UH, 4, UF, false>), grid, block, 0, s, a); } while (0)
     if (step_is_narrow(a.H, a.F)) {
-        if (a.M <= 1) EET_STEP(1, 2, 8);
-        else if (a.M <= 2) EET_STEP(2, 2, 8);
-        else if (a.M <= 4) EET_STEP(4, 2, 8);
-        else if (a.M <= 8) EET_STEP(8, 2, 8);
+        if (a.rows <= 1) EET_STEP(1, 2, 8);
+        else if (a.rows <= 2) EET_STEP(2, 2, 8);
+        else if (a.rows <= 4) EET_STEP(4, 2, 8);
+        else if (a.rows <= 8) EET_STEP(8, 2, 8);
         else EET_STEP(16, 2, 8);
     } else {
-        if (a.M <= 1) EET_STEP(1, 4, 16);
-        else if (a.M <= 2) EET_STEP(2, 4, 16);
-        else if (a.M <= 4) EET_STEP(4, 4, 16);
+        if (a.rows <= 1) EET_STEP(1, 4, 16);
+        else if (a.rows <= 2) EET_STEP(2, 4, 16);
+        else if (a.rows <= 4) EET_STEP(4, 4, 16);
         else EET_STEP(8, 4, 16);
     }
 #undef EET_STEP

@@ -54,6 +54,7 @@ constexpr int kFfnPadFrom = 32768;
 struct WorkspaceLayout {
     size_t lens, cu, row_map, buf_f, cut, buf_a, buf_b, buf_y, part, arrived, step, row_stats, total;
     uint32_t step_set_words;           // of one exchange set of the decode steps that run as one launch (0: none do)
+    int step_groups;                   // ... of which each group of sequences has two
     int arrived_lines;                 // counters of decode attention that merges its own key ranges (0: none does)
 };
 
@@ -96,7 +97,7 @@ WorkspaceLayout layout_of(const eet_layer_config* c) {
     // sized for the split count of any batch <= max_batch (fewer sequences -> more splits) that does not run as one launch
     size_t part = 0;
     for (int b = 1; b <= c->max_batch; ++b) {
-        if (decode_step_fits(b, c->hidden, c->heads, c->ffn) && decode_step_fits_keys(b, c->heads, (int)H / c->heads, (size_t)b * c->max_seq)) continue;
+        if (decode_step_fits(b, c->hidden, c->heads, c->ffn, c->max_seq) && decode_step_fits_keys(b, c->heads, (int)H / c->heads, (size_t)b * c->max_seq)) continue;
         const int splits = attention_decode_splits(b, c->heads, c->max_seq);
         const size_t p = attention_decode_scratch_bytes(b, c->heads, H / c->heads, splits);
         part = p > part ? p : part;
@@ -108,7 +109,8 @@ WorkspaceLayout layout_of(const eet_layer_config* c) {
     // the exchange area of those that do (decode_step.hip); no other step writes to it
     w.step = off;
     w.step_set_words = decode_step_set_words(c->max_batch, c->hidden, c->heads, c->ffn, c->max_seq);
-    if (w.step_set_words > 0) off = align_up(off + (kStepCtlWords + 2 * (size_t)w.step_set_words) * sizeof(unsigned long long), 256);
+    w.step_groups = decode_step_groups(c->max_batch, c->hidden, c->heads, c->ffn, c->max_seq);
+    if (w.step_set_words > 0) off = align_up(off + w.step_groups * (kStepCtlWords + 2 * (size_t)w.step_set_words) * sizeof(unsigned long long), 256);
     // LayerNorm statistics handed from the output projection of a decode step to the first feed-forward projection:
     // (mean, squared deviations) per row and workgroup of the producer, at most hidden/16 workgroups of 16 rows
     w.row_stats = off;
@@ -206,7 +208,7 @@ static bool leave_layernorm(GemmArgs& f2, const eet_layer* next, half_t* rows) {
 // The exchange area of `L`'s decode steps, to be set up wherever the cache lengths are set
 static StepArea step_area(const eet_layer* L) {
     const uint32_t set_words = L->lay.step_set_words;
-    return StepArea{reinterpret_cast<unsigned long long*>(L->ws + L->lay.step), set_words > 0 ? kStepCtlWords + 2 * set_words : 0};
+    return StepArea{reinterpret_cast<unsigned long long*>(L->ws + L->lay.step), set_words > 0 ? kStepCtlWords + 2 * set_words : 0, L->lay.step_groups};
 }
 
 #define EET_LAUNCH(expr, what)                        \
@@ -391,7 +393,7 @@ static StepRegime step_regime(const eet_layer* L, const int32_t* cached) {
     const size_t H = L->cfg.hidden, F = L->cfg.ffn;
     size_t visible = 0;
     for (int b = 0; b < L->batch; ++b) visible += (size_t)cached[b] + 1;
-    if (decode_step_fits(L->batch, L->cfg.hidden, L->cfg.heads, L->cfg.ffn) && !decode_step_fits_keys(L->batch, L->cfg.heads, L->d, visible)) return kLongKeys;
+    if (decode_step_fits(L->batch, L->cfg.hidden, L->cfg.heads, L->cfg.ffn, L->cfg.max_seq) && !decode_step_fits_keys(L->batch, L->cfg.heads, L->d, visible)) return kLongKeys;
     return (size_t)(L->stack_layers > 0 ? L->stack_layers : 1) * (2 * (4 * H * H + 2 * H * F) + 4 * H * visible) > kMemorySideCacheBytes ? kExceedsCache : kInCache;
 }
 
@@ -550,7 +552,7 @@ static int enqueue_decode(eet_layer* L, const void* tokens, void* out, void* kv_
 }
 
 static bool decodes_in_one_launch(const eet_layer* L, StepRegime regime) {
-    return regime != kLongKeys && decode_step_fits(L->batch, L->cfg.hidden, L->cfg.heads, L->cfg.ffn);
+    return regime != kLongKeys && decode_step_fits(L->batch, L->cfg.hidden, L->cfg.heads, L->cfg.ffn, L->cfg.max_seq);
 }
 
 // A decode step through `n` layers of one configuration that share a workspace, as one launch per kStepLayers of them.  The last
@@ -638,11 +640,14 @@ int eet_cache_lens(eet_layer_t* L, int32_t* out_host, void* hip_stream) {
     hipStream_t s = static_cast<hipStream_t>(hip_stream);
     EET_LAUNCH(hipMemcpyAsync(out_host, L->ws + L->lay.lens, sizeof(int32_t) * L->batch, hipMemcpyDeviceToHost, s),
                "copy of cache lengths");
-    uint32_t step_state = 0;
+    uint32_t step_state[kStepGroups] = {};
     if (L->lay.step_set_words > 0)
-        EET_LAUNCH(hipMemcpyAsync(&step_state, L->ws + L->lay.step, sizeof(step_state), hipMemcpyDeviceToHost, s), "copy of the decode state");
+        EET_LAUNCH(hipMemcpy2DAsync(step_state, sizeof(uint32_t), L->ws + L->lay.step, (kStepCtlWords + 2 * (size_t)L->lay.step_set_words) * sizeof(unsigned long long),
+                                    sizeof(uint32_t), L->lay.step_groups, hipMemcpyDeviceToHost, s), "copy of the decode state");
     EET_LAUNCH(hipStreamSynchronize(s), "stream synchronise");
-    if (step_state & kStepGaveUp)
+    uint32_t any = 0;
+    for (const uint32_t state : step_state) any |= state;
+    if (any & kStepGaveUp)
         return fail(EET_ERR_HIP, "eet_cache_lens: a decode step gave up waiting for a part of its own launch: its output and all since are NaN "
                                  "until the next prefill or restore");
     return EET_OK;

@@ -33,11 +33,12 @@ hipError_t launch_softmax_maskfree(half_t* scores, const SeqLens& lens, int batc
 hipError_t launch_prefill_setup(const SeqLens& lens, int batch, int S, int width, int32_t* cache_lens,
                                 int32_t* cu_seqlens, int32_t* row_map, half_t* out, hipStream_t s,
                                 bool left_padded = false);
-// The exchange area of decode_step.hip, for the launches that set the cache lengths: its first kStepCtlWords words become zero,
-// the others all ones.  words == 0: none.
+// The exchange area of decode_step.hip, for the launches that set the cache lengths: of every group's words the first kStepCtlWords
+// become zero, the others all ones.  words == 0: none.
 struct StepArea {
     unsigned long long* ctl;
     uint32_t words;
+    int groups;
 };
 // The same together with the LayerNorm of the valid rows of x ([batch, S, width]) into the packed rows of y, where the width allows.
 bool prefill_setup_takes_layernorm(int width);
@@ -204,6 +205,7 @@ hipError_t launch_attention_decode(const AttnDecodeArgs& a, hipStream_t s);
 constexpr int kStepLayers = 32;          // layers per launch (their pointers travel as kernel arguments)
 constexpr int kStepCtlWords = 32;        // ctl[0]: next item (and kStepGaveUp), layer number; ctl[16]: items that have reset their part; a line each
 constexpr uint32_t kStepGaveUp = 1u << 31;
+constexpr int kStepGroups = 8;           // groups of rows that a step may have, each with control words and exchange sets of its own
 struct StepLayer {
     const half_t *ln1_g, *ln1_b, *w_qkv, *b_qkv, *w_o, *b_o, *ln2_g, *ln2_b, *w_fc1, *b_fc1, *w_fc2, *b_fc2;
     half_t *k_cache, *v_cache;
@@ -224,19 +226,18 @@ struct StepArgs {
     const half_t* x;                     // [M, H] input of the first layer
     StepTokens tok;
     half_t* out;                         // [M, H] output of the last
-    unsigned long long* ctl;             // kStepCtlWords words, then the two exchange sets
+    unsigned long long* ctl;             // per group kStepCtlWords words, then two exchange sets
     uint32_t set_words;                  // words of a set: decode_step_set_words of the layer's configuration, whatever M is
     int32_t* lens;                       // DEVICE: cached keys; += 1 by the launch when bump
     float eps;
     int bump, M, H, F, heads, max_seq, n_layers;
     // set by the launcher
-    unsigned long long* ex;
     StepBuffer bx, bqkv, bctx, by, bf;
-    int d, splits, n_qkv, n_att, n_out, n_ffn1, per_layer, items;
+    int d, splits, groups, rows, n_qkv, n_att, n_out, n_ffn1, per_layer, items;     // rows: of a group; items: of a group
     StepLayer layer[kStepLayers];
 };
 // Rows and widths the kernel takes.
-bool decode_step_fits(int rows, int hidden, int heads, int ffn);
+bool decode_step_fits(int rows, int hidden, int heads, int ffn, int max_seq);
 // ... and whether it is the faster way with `visible` keys in all (decode_step.hip has the figures).
 bool decode_step_fits_keys(int rows, int heads, int d, size_t visible);
 // Words of an exchange set that holds a step of any number of rows up to max_rows that the kernel takes (0: it takes none).  A set has
@@ -244,6 +245,7 @@ bool decode_step_fits_keys(int rows, int heads, int d, size_t visible);
 // emptied whole, whatever the rows of a step: a caller may have recorded a step of another number of sequences than those
 // of the latest prefill or of the step before, and replay it now.
 uint32_t decode_step_set_words(int max_rows, int hidden, int heads, int ffn, int max_seq);
+int decode_step_groups(int max_rows, int hidden, int heads, int ffn, int max_seq);     // groups of a step of up to max_rows rows
 hipError_t launch_decode_layers(StepArgs& a, bool read_once, hipStream_t s);
 
 // ---- what comes behind the last layer, in one launch (head.hip) --------------------------------------

@@ -538,9 +538,10 @@ __global__ __launch_bounds__(64) void prefill_setup(SeqLens lens, int batch, int
 
 // Part `part` of `parts` of the exchange area of a decode step (kernels.hpp: StepArea), `nthreads` threads
 __device__ __forceinline__ void set_up_step_area(const StepArea& st, int part, int parts, int tid, int nthreads) {
-    for (uint32_t i = part * nthreads + tid; i < st.words; i += parts * nthreads) st.ctl[i] = i < (uint32_t)kStepCtlWords ? 0ull : ~0ull;
+    const uint32_t words = st.words * (uint32_t)st.groups;
+    for (uint32_t i = part * nthreads + tid; i < words; i += parts * nthreads) st.ctl[i] = i % st.words < (uint32_t)kStepCtlWords ? 0ull : ~0ull;
 }
-static int step_area_blocks(const StepArea& st, int nthreads) { return (int)((st.words + 4 * nthreads - 1) / (4 * nthreads)); }
+static int step_area_blocks(const StepArea& st, int nthreads) { return (int)((st.words * (uint32_t)st.groups + 4 * nthreads - 1) / (4 * nthreads)); }
 
 // The same set-up and the first LayerNorm of a prefill in one launch, rows of up to 2048 (width % 8 == 0): one wave per padded
 // row, which is either zeroed in `out` or normalised into its packed place in `y`.  A short prompt is a chain of dependent
