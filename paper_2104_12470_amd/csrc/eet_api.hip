@@ -90,6 +90,9 @@ WorkspaceLayout layout_of(const eet_layer_config* c) {
     const size_t for_o = gemm_cut_bytes_up_to((int64_t)T, c->hidden, c->hidden), for_f2 = gemm_cut_bytes_up_to((int64_t)T, c->hidden, c->ffn);
     if (for_o > room_f) off = align_up(w.cut + for_o - room_f, 256);
     if (for_f2 > room_ab + (off - w.cut)) off = align_up(w.cut + for_f2 - room_ab, 256);
+    // short prefills that run as one launch (prompt_step.hip) use all of it, from buf_f to the end of buf_y, in an order of their own
+    const size_t rows_held = 3 * align_up(2 * T * H, 256), one_launch = prompt_step_bytes_up_to((int64_t)T, c->hidden, c->heads, c->ffn);
+    if (w.buf_f + one_launch > off + rows_held) off = align_up(w.buf_f + one_launch - rows_held, 256);
     w.buf_a = off;   off = align_up(off + 2 * T * H, 256);
     w.buf_b = off;   off = align_up(off + 2 * T * H, 256);
     w.buf_y = off;   off = align_up(off + 2 * T * H, 256);
@@ -314,6 +317,63 @@ static int enqueue_prefill(eet_layer* L, const SeqLens& lens, int batch, int pad
     return EET_OK;
 }
 
+// Prefills (and encoder passes) of few rows through narrow layers run as one launch for all layers behind their set-up
+// (prompt_step.hip).  x: where the rows of `n` > 1 layers lie between two of them; layer_cache_bytes: 0 where all layers share one region.
+static bool prefills_in_one_launch(const eet_layer* L, int64_t T, int batch, int padded_len, int max_len) {
+    return prompt_step_fits(T, (int64_t)batch * padded_len, batch, max_len, L->cfg.hidden, L->cfg.heads, L->cfg.ffn);
+}
+static int enqueue_prompt_layers(eet_layer* const* layers, int n, const SeqLens& lens, int batch, int padded_len, int64_t T, int max_len,
+                                 const void* tokens, void* out, void* x, void* kv_cache, size_t layer_cache_bytes, hipStream_t s, bool causal, bool left_padded) {
+    const eet_layer* L0 = layers[0];
+    const eet_layer_config& c = L0->cfg;
+    const int H = c.hidden, F = c.ffn;
+    const size_t weights = (size_t)n * 2 * ((size_t)4 * H * H + (size_t)2 * H * F);
+    const void* in = tokens;
+    for (int l0 = 0; l0 < n; l0 += kStepLayers) {
+        PromptArgs a{};
+        static_cast<PromptShape&>(a) = prompt_step_shape((int)T, H, F);
+        a.n_layers = n - l0 < kStepLayers ? n - l0 : kStepLayers;
+        void* o = l0 + a.n_layers == n ? out : x;
+        a.tokens = static_cast<const half_t*>(in);
+        a.x = static_cast<half_t*>(x);
+        a.out = static_cast<half_t*>(o);
+        char* area = L0->ws + L0->lay.buf_f;
+        a.ctl = reinterpret_cast<uint32_t*>(area + a.at_ctl);
+        a.f = reinterpret_cast<half_t*>(area + a.at_f);
+        a.q = reinterpret_cast<half_t*>(area + a.at_q);
+        a.ctx = reinterpret_cast<half_t*>(area + a.at_ctx);
+        a.y = reinterpret_cast<half_t*>(area + a.at_y);
+        a.part = reinterpret_cast<float*>(area + a.at_part);
+        int32_t* d_lens = reinterpret_cast<int32_t*>(L0->ws + L0->lay.lens);
+        int32_t* d_cu = reinterpret_cast<int32_t*>(L0->ws + L0->lay.cu);
+        int32_t* d_map = reinterpret_cast<int32_t*>(L0->ws + L0->lay.row_map);
+        a.lens = d_lens; a.cu = d_cu; a.row_map = d_map;
+        a.eps = c.ln_eps;
+        a.T = (int)T; a.padded_rows = batch * padded_len; a.S = padded_len; a.batch = batch; a.max_len = max_len;
+        a.H = H; a.F = F; a.heads = c.heads; a.max_seq = c.max_seq; a.causal = causal ? 1 : 0; a.left_pad = left_padded ? 1 : 0;
+        for (int l = 0; l < a.n_layers; ++l) {
+            const eet_layer_weights& w = layers[l0 + l]->w;
+            half_t* kv = reinterpret_cast<half_t*>(static_cast<char*>(kv_cache) + (size_t)(l0 + l) * layer_cache_bytes);
+            auto p = [](const void* q) { return static_cast<const half_t*>(q); };
+            a.layer[l] = StepLayer{p(w.ln1_g), p(w.ln1_b), p(w.w_qkv), p(w.b_qkv), p(w.w_o), p(w.b_o), p(w.ln2_g), p(w.ln2_b), p(w.w_fc1),
+                                   p(w.b_fc1), p(w.w_fc2), p(w.b_fc2), kv, kv + (size_t)c.max_batch * H * c.max_seq};
+        }
+        EET_LAUNCH(launch_prompt_setup(lens, a, d_lens, d_cu, d_map, causal ? step_area(L0) : StepArea{}, s), "prefill set-up");
+        // weights that several row tiles share, or that the memory-side cache keeps until the next call, are read with plain loads
+        EET_LAUNCH(launch_prompt_layers(a, a.row_tiles == 1 && weights > kMemorySideCacheBytes, s), "prefill layers");
+        in = o;
+    }
+    return EET_OK;
+}
+
+// One layer's prefill
+static int enqueue_layer_prefill(eet_layer* L, const SeqLens& lens, int batch, int padded_len, int64_t T, int max_len, const void* tokens, void* out,
+                                 void* kv_cache, hipStream_t s, bool causal, bool left_padded) {
+    if (prefills_in_one_launch(L, T, batch, padded_len, max_len))
+        return enqueue_prompt_layers(&L, 1, lens, batch, padded_len, T, max_len, tokens, out, nullptr, kv_cache, 0, s, causal, left_padded);
+    return enqueue_prefill(L, lens, batch, padded_len, T, max_len, tokens, out, kv_cache, s, causal, left_padded);
+}
+
 // Shared argument checks of a prefill; fills the by-value length table.
 static int check_prefill(const char* who, const eet_layer_config& cfg, const int32_t* q_lens, int32_t batch,
                          int32_t padded_len, const void* tokens, const void* out, const void* kv_cache, SeqLens& lens,
@@ -346,8 +406,7 @@ int eet_prefill(eet_layer_t* L, const int32_t* q_lens, int32_t batch, int32_t pa
     int max_len;
     if (const int rc = check_prefill("eet_prefill", L->cfg, q_lens, batch, padded_len, tokens, out, kv_cache, lens, T, max_len))
         return rc;
-    const int rc = enqueue_prefill(L, lens, batch, padded_len, T, max_len, tokens, out, kv_cache,
-                                   static_cast<hipStream_t>(hip_stream));
+    const int rc = enqueue_layer_prefill(L, lens, batch, padded_len, T, max_len, tokens, out, kv_cache, static_cast<hipStream_t>(hip_stream), true, false);
     if (rc != EET_OK) return rc;
     L->batch = batch;
     for (int b = 0; b < batch; ++b) L->host_lens[b] = q_lens[b];
@@ -363,8 +422,7 @@ int eet_prefill_left_padded(eet_layer_t* L, const int32_t* q_lens, int32_t batch
     if (const int rc = check_prefill("eet_prefill_left_padded", L->cfg, q_lens, batch, padded_len, tokens, out, kv_cache, lens, T,
                                      max_len))
         return rc;
-    const int rc = enqueue_prefill(L, lens, batch, padded_len, T, max_len, tokens, out, kv_cache,
-                                   static_cast<hipStream_t>(hip_stream), true, true);
+    const int rc = enqueue_layer_prefill(L, lens, batch, padded_len, T, max_len, tokens, out, kv_cache, static_cast<hipStream_t>(hip_stream), true, true);
     if (rc != EET_OK) return rc;
     L->batch = batch;
     for (int b = 0; b < batch; ++b) L->host_lens[b] = q_lens[b];
@@ -381,8 +439,7 @@ int eet_layer_encode(eet_layer_t* L, const int32_t* q_lens, int32_t batch, int32
         return rc;
     // the pass overwrites the device-side lengths: whatever prefill / decode state the layer held is gone
     L->batch = 0;
-    return enqueue_prefill(L, lens, batch, padded_len, T, max_len, tokens, out, kv_scratch,
-                           static_cast<hipStream_t>(hip_stream), false);
+    return enqueue_layer_prefill(L, lens, batch, padded_len, T, max_len, tokens, out, kv_scratch, static_cast<hipStream_t>(hip_stream), false, false);
 }
 
 // How a decode step of `L`'s handle runs (a layer, or the stack it belongs to, whose sequences hold `cached` keys each).  kInCache: all
@@ -757,10 +814,16 @@ static int stack_prefill(const char* who, bool left_padded, eet_stack_t* st, con
     if (const int rc = check_prefill(who, st->cfg, q_lens, batch, padded_len, tokens, out, kv_cache, lens, T, max_len))
         return rc;
     hipStream_t s = static_cast<hipStream_t>(hip_stream);
+    const bool one_launch = prefills_in_one_launch(st->layers[0], T, batch, padded_len, max_len);
+    if (one_launch) {
+        if (const int rc = enqueue_prompt_layers(st->layers, st->n_layers, lens, batch, padded_len, T, max_len, tokens, out, st->ws + st->act[0], kv_cache,
+                                                 st->layer_cache_bytes, s, true, left_padded)) return rc;
+        for (int l = 0; l < st->n_layers; ++l) st->layers[l]->batch = batch;
+    }
     const void* in = tokens;
     const bool pads = T < (int64_t)batch * padded_len;
     bool normalised = false;
-    for (int l = 0; l < st->n_layers; ++l) {
+    for (int l = 0; l < st->n_layers && !one_launch; ++l) {
         void* o = (l == st->n_layers - 1) ? out : static_cast<void*>(st->ws + st->act[l & 1]);
         char* kv = static_cast<char*>(kv_cache) + (size_t)l * st->layer_cache_bytes;
         const int rc = enqueue_prefill(st->layers[l], lens, batch, padded_len, T, max_len, in, o, kv, s, true, left_padded,
@@ -794,6 +857,10 @@ int eet_stack_encode(eet_stack_t* st, const int32_t* q_lens, int32_t batch, int3
         return rc;
     hipStream_t s = static_cast<hipStream_t>(hip_stream);
     st->batch = 0;                                   // the pass overwrites the device-side lengths: no decode state afterwards
+    if (prefills_in_one_launch(st->layers[0], T, batch, padded_len, max_len)) {
+        for (int l = 0; l < st->n_layers; ++l) st->layers[l]->batch = 0;
+        return enqueue_prompt_layers(st->layers, st->n_layers, lens, batch, padded_len, T, max_len, tokens, out, st->ws + st->act[0], kv_scratch, 0, s, false, false);
+    }
     const void* in = tokens;
     const bool pads = T < (int64_t)batch * padded_len;
     bool normalised = false;

@@ -248,6 +248,38 @@ uint32_t decode_step_set_words(int max_rows, int hidden, int heads, int ffn, int
 int decode_step_groups(int max_rows, int hidden, int heads, int ffn, int max_seq);     // groups of a step of up to max_rows rows
 hipError_t launch_decode_layers(StepArgs& a, bool read_once, hipStream_t s);
 
+// ---- all layers of a short prefill in one launch (prompt_step.hip) ---------------------------------
+constexpr int kPromptStepRows = 512;     // rows of the largest prompt
+constexpr int kPromptStepK = 1024;       // longest K of an item: hidden, and the range of ffn that an item of the second feed-forward projection takes
+constexpr int kPromptStepRanges = 4;
+struct PromptShape {
+    int row_tiles;                       // of 16 rows
+    int ranges, range_units;             // ranges of ffn, units of 64 of each
+    int counters;                        // per row tile
+    uint32_t ctl_words;                  // number of the next item, then the counters, kClearStride apart
+    uint32_t at_ctl, at_f, at_q, at_ctx, at_y, at_part, bytes;   // what the launch hands on
+};
+struct PromptArgs : PromptShape {
+    const half_t* tokens;                // [padded_rows, H] input of the first layer
+    half_t* x;                           // [padded_rows, H] between layers (may be tokens or out: a row tile reads and writes its own rows only)
+    half_t* out;                         // [padded_rows, H] output of the last
+    half_t *q, *ctx, *y, *f;             // packed rows
+    float* part;
+    uint32_t* ctl;
+    const int32_t *lens, *cu, *row_map;  // DEVICE, left by launch_prompt_setup
+    float eps;
+    int T, padded_rows, S, batch, max_len, H, F, heads, max_seq, n_layers, causal, left_pad;
+    // set by the launcher
+    int d, n_qkv, n_att, n_out, n_ffn1, per_layer, items;
+    StepLayer layer[kStepLayers];
+};
+bool prompt_step_fits(int64_t rows, int64_t padded_rows, int batch, int max_len, int hidden, int heads, int ffn);
+PromptShape prompt_step_shape(int rows, int hidden, int ffn);
+size_t prompt_step_bytes_up_to(int64_t max_rows, int hidden, int heads, int ffn);
+// Lengths, prefix sums and row map, pad rows of a.out, the counters, and the exchange area of the decode steps to come
+hipError_t launch_prompt_setup(const SeqLens& lens, const PromptArgs& a, int32_t* cache_lens, int32_t* cu, int32_t* row_map, StepArea step, hipStream_t s);
+hipError_t launch_prompt_layers(PromptArgs& a, bool read_once, hipStream_t s);
+
 // ---- what comes behind the last layer, in one launch (head.hip) --------------------------------------
 constexpr int kHeadMaxRows = 16, kHeadMaxK = 1792, kHeadGroups = 256;
 struct HeadArgs {

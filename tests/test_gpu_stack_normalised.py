@@ -27,9 +27,9 @@ def launches(names):
 
 
 # rows below and from 64 on (two orders of additions), widths on both sides of 2048, with and without pad rows, a feed-forward part narrower than the layer
-@pytest.mark.parametrize("hidden,heads,ffn,lens,S", [(1024, 16, 4096, [37], 37), (512, 8, 2048, [20, 20], 20), (768, 6, 3072, [64], 64), (1024, 8, 2688, [100, 50], 100),
+@pytest.mark.parametrize("hidden,heads,ffn,lens,S", [(1024, 16, 8192, [37], 37), (512, 8, 5120, [20, 20], 20), (768, 6, 3072, [160], 160), (1024, 8, 4096, [100, 50], 100),
                                                      (2048, 16, 8192, [60], 60), (2048, 32, 8192, [100, 100], 100), (2560, 20, 6784, [48], 48),
-                                                     (2560, 20, 6784, [80, 60], 80), (1024, 16, 512, [30], 30)])
+                                                     (2560, 20, 6784, [80, 60], 80), (1280, 10, 512, [30], 30)])
 def test_prompts_and_encoder_passes(hidden, heads, ffn, lens, S):
     B, n = len(lens), 4
     w, stack, layers = build(hidden, heads, ffn, B, S, S + 4, n)
