@@ -1,15 +1,15 @@
 // Decode steps of small layers: all layers of a step in one launch.
 //
-// A decode step of a small layer (up to 16 sequences, or several groups of as many, a few MB per projection) is a chain of five dependent phases, and as five
-// launches each of them costs the floor of a dependent launch (drain, start, first trip to memory: about 4 us for 1 to 8 MB of
+// A decode step of a small layer (up to 16 sequences, or several groups of as many, a few MB per projection) is a chain of five dependent
+// phases, and as five launches each of them costs the floor of a dependent launch (drain, start, first trip to memory: about 4 us for 1 to 8 MB of
 // weights), whatever its bytes.  Here the chain runs inside one launch.  A workgroup is one ITEM of one layer: 64 columns of a projection (16
 // of the second feed-forward one), or one key range of a (sequence, head) pair.  It requests its weights (or K/V rows), up to 256 KB, into
 // registers first, since they depend on nothing, and only then waits for its input, which the items of the phase before hand
 // over through memory.  While a phase runs, the CUs that it leaves idle hold the weights of the next ones: HBM never waits for the chain, and a
 // phase costs its hand-over (1.0 to 1.5 us from the producers' sums to a consumer's whole input, of which 0.45 to 0.7 is one store seen by
 // one load across the chip) and its arithmetic.
-// us per layer-step, five launches -> now: hidden 1024 in a stack of 24, 1 sequence 21.2 -> 10.6, 8 sequences of 384 to 768 tokens
-// 26.4 -> 14.0; 60 drawn sizes (hidden 256 to 2048, 1 to 24 layers, 1 to 8 sequences of 1 to 3200 tokens) 1.18 to 3.1 times as
+// us per layer-step, five launches -> now: hidden 1024 in a stack of 24, 1 sequence 21.2 -> 9.7, 8 sequences of 384 to 768 tokens
+// 26.4 -> 13.3; 60 drawn sizes (hidden 256 to 2048, 1 to 24 layers, 1 to 8 sequences of 1 to 3200 tokens) 1.18 to 3.1 times as
 // fast, geometric mean 1.86; 30 of 9 to 16 sequences 1.09 to 2.9, 1.58.
 //
 //   hand-over   The exchange buffers hold 8-byte words (four halfs, or two floats) that are all ones until their producer stores them,
@@ -41,7 +41,7 @@
 // through the exchange set, and the cache for the steps that follow.
 //
 // One workgroup per CU (the registers see to that): two, with 128 registers each, start so far ahead that their polling
-// slows the phases they wait for (12.4 -> 14.2 us per layer-step with one sequence on the variant of 8 rows, 10.6 on its own).
+// slows the phases they wait for (12.4 -> 14.2 us per layer-step with one sequence on the variant of 8 rows, 9.7 on its own).
 #include "kernels.hpp"
 
 namespace eet {
@@ -850,14 +850,14 @@ static uint32_t step_layout(StepArgs& a) {
 }
 
 int decode_step_groups(int max_rows, int hidden, int heads, int ffn, int max_seq) {
-    int most = 0;
-    for (int rows = 1; rows <= max_rows && rows <= kStepGroups * step_group_rows(hidden, ffn); ++rows) {
+    const int limit = kStepGroups * step_group_rows(hidden, ffn);
+    for (int rows = max_rows < limit ? max_rows : limit; rows >= 1; --rows) {   // more rows, more groups
         if (!decode_step_fits(rows, hidden, heads, ffn, max_seq)) continue;
         int groups, group_rows;
         step_groups(rows, hidden, ffn, groups, group_rows);
-        most = groups > most ? groups : most;
+        return groups;
     }
-    return most;
+    return 0;
 }
 
 uint32_t decode_step_set_words(int max_rows, int hidden, int heads, int ffn, int max_seq) {

@@ -25,7 +25,6 @@ namespace eet {
 
 namespace {
 
-typedef unsigned uint4v __attribute__((ext_vector_type(4)));
 typedef unsigned long long word_t;
 constexpr int kAgentScope = 16;                    // cache policy of a buffer access at agent scope: sc1
 constexpr int kPWaves = 8, kPThreads = 64 * kPWaves;
@@ -637,16 +636,12 @@ PromptShape prompt_step_shape(int rows, int hidden, int ffn) {
     p.bytes = at;
     return p;
 }
-// For any prompt of up to max_rows rows: of the rows that share their tiles the most take the most
+// For any prompt of up to max_rows rows: more rows take more, so the most rows of the most tiles (17 rows: two tiles, past the rule for few rows)
 size_t prompt_step_bytes_up_to(int64_t max_rows, int hidden, int heads, int ffn) {
-    size_t most = 0;
-    for (int m = 16; m < kPromptStepRows + 16; m += 16) {
-        const int64_t rows = m < max_rows ? m : max_rows;
-        if (takes_layer(rows, hidden, heads, ffn)) most = prompt_step_shape((int)rows, hidden, ffn).bytes;
-        else if (rows > 16) break;
-        if (rows == max_rows) break;
-    }
-    return most;
+    if (!takes_layer(max_rows < 17 ? max_rows : 17, hidden, heads, ffn)) return 0;
+    int64_t rows = kPRows * (kPromptStepItems / items_of_rows(1, hidden, ffn));
+    rows = rows < kPromptStepRows ? rows : kPromptStepRows;
+    return prompt_step_shape((int)(rows < max_rows ? rows : max_rows), hidden, ffn).bytes;
 }
 
 hipError_t launch_prompt_setup(const SeqLens& lens, const PromptArgs& a, int32_t* cache_lens, int32_t* cu, int32_t* row_map, StepArea step, hipStream_t s) {

@@ -59,6 +59,7 @@ inline int gemm_k_ranges(int M, int N, int K) {
 // 88 -> 84; one layer of 1280 x 5120, 64 rows 63 -> 49.  Where it stops: 20 to 64 rows of hidden 256 (a quarter of a million weights: 32 -> 34);
 // 65 to 128 of 640 x 1664 (one million: 44.2 -> 45.3); 160 of hidden 1024 (output projection, one million: 47 -> 48.5); 400 and 700 rows
 // (1024 54 -> 55, 63 -> 66; 768 and 2048 gain 4 % at 400 and nothing at 700).
+// (Most prompts of layers of up to 1024 x 4096 are one launch by now, prompt_step.hip, which asks nothing here; their layers' capacity does.)
 inline int prompt_k_ranges(int M, int N, int K) {
     if (M > 16 && M <= 256 && K % 128 == 0 && N % 64 == 0 && N <= kFinishRowsMaxWidth && (int64_t)N * K >= (M <= 64 ? (int64_t)1 << 19 : (int64_t)2 << 20)) {
         const int tiles = (M + rows_tile(M) - 1) / rows_tile(M) * ((N + 63) / 64), least = M <= 64 ? 256 : 512;
