@@ -1086,7 +1086,7 @@ __device__ __forceinline__ half_t merge_ranges(const float* ml, const float* pa,
 // lanes of the wave call it.  It is worked out from the lengths of the moment and kept nowhere: a step that was recorded for some number
 // of sequences finds those in any later state.
 __device__ __forceinline__ int sequence_at_place(const int32_t* lens, int batch, int capacity, int place, int lane) {
-    static_assert(kMaxBatch == 2 * kWave, "two lengths per lane");
+    static_assert(kOrderedSequences == 2 * kWave, "two lengths per lane");       // decode_longest_first: batch is no more than that
     const int bits = 32 - __builtin_clz((unsigned)capacity | 1u), shift = bits > 4 ? bits - 4 : 0;
     auto length = [&](int b) {
         const int n = b < batch ? lens[b] : 0;
@@ -1301,16 +1301,10 @@ size_t attention_decode_scratch_bytes(int batch, int heads, int d, int splits) {
     return (size_t)batch * heads * splits * (d + 2) * sizeof(float);
 }
 
-// More pairs than CUs: a pair is one workgroup, and the launch ends with those of the longest sequences, wherever the batch has them; so they
-// start first.  us per pass of decode steps, in the order of the batch / longest first (lengths): "server tokens 4096" (48 x 32 heads of 128, 100 to
-// 1500) 3226 / 3134; 12 x 32 of 128 (100 to 2000) 1982 / 1895; 24 x 16 of 64 (100 to 1000) 2697 / 2608; 100 x 16 of 64, four layers 5023 / 4888; 16 x 96 of 128
-// (1024 to 2104) 5902 / 5885.  A workgroup pays some 0.2 us for its place, which sequences of one length give nothing for: 64 x 16 of 64, 500 and
-// 900 keys 3607 / 3621, 4481 / 4497; and which counts where all are short, so not below 512 slots: 128 x 16 of 64, 200 keys 879 / 888, 128 x 8 of at
-// most 30 3870 / 3996; 24 x 32 of 128, 40 to 400 1716 / 1708.  (All bits of the lengths instead of the four upper ones: 905 and 3960.)
 hipError_t launch_attention_decode(const AttnDecodeArgs& a, hipStream_t s) {
     const dim3 grid(a.splits, a.heads, a.batch), block(256);
     AttnDecodeArgs b = a;
-    b.longest_first = a.splits == 1 && a.batch > 1 && a.batch * a.heads > 256 && a.capacity >= 512;
+    b.longest_first = decode_longest_first(a.splits, a.batch, a.heads, a.capacity);
     if (a.d == 128) {
         if (a.read_once) hipLaunchKernelGGL((attn_decode<128, 4, true>), grid, block, 0, s, b);
         else hipLaunchKernelGGL((attn_decode<128, 4, false>), grid, block, 0, s, b);

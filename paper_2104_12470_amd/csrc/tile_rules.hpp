@@ -327,4 +327,17 @@ inline bool prefill_touches_weights(int64_t rows, size_t ahead, size_t stack, si
     return ahead <= (size_t)72 << 20 && stack > kMemorySideCacheBytes && rows > 128 && rows <= 2048;
 }
 
+// ---- decode attention: the longest sequences first ----
+// With more pairs than CUs a pair is one workgroup, and the launch ends with those of the longest sequences, wherever the batch has them; so they
+// start first.  us per pass of decode steps, in the order of the batch / longest first (lengths): "server tokens 4096" (48 x 32 heads of 128, 100 to
+// 1500) 3226 / 3134; 12 x 32 of 128 (100 to 2000) 1982 / 1895; 24 x 16 of 64 (100 to 1000) 2697 / 2608; 100 x 16 of 64, four layers 5023 / 4888; 16 x 96 of 128
+// (1024 to 2104) 5902 / 5885.  A workgroup pays some 0.2 us for its place, which sequences of one length give nothing for: 64 x 16 of 64, 500 and
+// 900 keys 3607 / 3621, 4481 / 4497; and which counts where all are short, so not below 512 slots: 128 x 16 of 64, 200 keys 879 / 888, 128 x 8 of at
+// most 30 3870 / 3996; 24 x 32 of 128, 40 to 400 1716 / 1708.  (All bits of the lengths instead of the four upper ones: 905 and 3960.)
+// A wave counts two lengths per lane and no more (attention.hip: sequence_at_place), so the operators' calls with more sequences than that keep the order of the batch.
+constexpr int kOrderedSequences = 128;
+inline bool decode_longest_first(int splits, int batch, int heads, int capacity) {
+    return splits == 1 && batch > 1 && batch <= kOrderedSequences && (int64_t)batch * heads > 256 && capacity >= 512;
+}
+
 }  // namespace eet

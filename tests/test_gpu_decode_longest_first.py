@@ -1,5 +1,5 @@
-"""Decode attention of more pairs than CUs over 512 slots and more: its workgroups take the sequences longest first.  Whatever the lengths, every sequence
-is somebody's, against a plain reference in float32."""
+"""Decode attention of more pairs than CUs over 512 slots and more: its workgroups take the sequences longest first, up to as many as a wave counts (128).
+Whatever the lengths and however many, every sequence is somebody's, with a scratch buffer and without, against a plain reference in float32."""
 import math
 import random
 
@@ -21,7 +21,8 @@ def lengths(kind, batch, capacity):
 
 
 @pytest.mark.parametrize("kind", ["mixed", "equal", "ties"])
-@pytest.mark.parametrize("batch,heads,d,capacity", [(2, 129, 64, 512), (33, 8, 128, 513), (64, 5, 64, 1000), (65, 4, 128, 600), (128, 3, 64, 777)])
+@pytest.mark.parametrize("batch,heads,d,capacity", [(2, 129, 64, 512), (33, 8, 128, 513), (64, 5, 64, 1000), (65, 4, 128, 600), (128, 3, 64, 777),
+                                                     (129, 2, 64, 512), (129, 5, 128, 600), (200, 8, 64, 1024), (300, 1, 128, 513), (300, 4, 64, 700)])
 def test_every_sequence_is_served(kind, batch, heads, d, capacity):
     from paper_2104_12470_amd import eet
     g = torch.Generator(device="cuda:0")
@@ -33,6 +34,9 @@ def test_every_sequence_is_served(kind, batch, heads, d, capacity):
     ctx = torch.full_like(q, float("nan"))
     scratch = torch.empty(max(1, eet.eet_op_attention_decode_scratch_bytes(batch, heads, d, capacity)), dtype=torch.uint8, device="cuda:0")
     eet.eet_op_attention_decode(q, k, v, ctx, n, scratch)
+    alone = torch.full_like(q, float("nan"))
+    eet.eet_op_attention_decode_static(q, k, v, alone, n)
+    assert torch.equal(ctx.view(torch.int16), alone.view(torch.int16))
     seen = torch.arange(capacity, device="cuda:0")[None, None] < n[:, None, None]
     s = (k.float() * q.view(batch, heads, 1, d).float()).sum(-1) / math.sqrt(d)
     p = torch.softmax(s.masked_fill(~seen, -math.inf), -1)

@@ -77,6 +77,13 @@ def test_room_for_the_sums_of_cut_projections(ask):
     assert sum(a != "0 0" for a in got) > 100
 
 
+def test_only_as_many_sequences_as_a_wave_counts_are_put_in_order(ask):
+    """Two lengths per lane of a wave: 128 sequences.  The operators take up to 65535, whose order stays the batch's."""
+    taken = [("longest_first", *q) for q in ((2, 129, 512), (48, 32, 1516), (128, 3, 777), (128, 65535, 4096))]
+    left = [("longest_first", *q) for q in ((1, 1000, 512), (2, 128, 4096), (48, 32, 511), (129, 2, 512), (129, 96, 4096), (200, 8, 1024), (300, 1, 512), (65535, 65535, 4096))]
+    assert ask(taken) == ["1"] * len(taken) and ask(left) == ["0"] * len(left)
+
+
 def test_creating_a_handle_costs_microseconds():
     """Sizing a layer's workspace is a few dozen arithmetic rules: one query stays below the price of a walk over a thousand row
     counts (17 us where this takes one)."""

@@ -11,6 +11,7 @@
 //   ranges M N K      K ranges of a bias + residual projection
 //   sums M N K        bytes that the sums of such a cut projection of up to M rows need at most; then the same from a walk over
 //                     every row count
+//   longest_first B H C  whether the decode attention of B sequences, H heads, C slots and one key range takes the longest first
 #include <cstdint>
 #include <cstdio>
 #include <cstring>
@@ -68,7 +69,8 @@ int main() {
                 if (b > most) most = b;
             }
             std::printf("%lld %lld\n", (long long)eet::gemm_cut_bytes_up_to(M, N, K), (long long)most);
-        } else return 1;
+        } else if (!std::strcmp(what, "longest_first")) std::printf("%d\n", eet::decode_longest_first(1, M, N, K));
+        else return 1;
     }
     return 0;
 }
