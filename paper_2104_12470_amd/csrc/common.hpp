@@ -83,6 +83,14 @@ __device__ __forceinline__ float wave_max(float v) {
     return reduce_wave(v, [](float x, float y) { return fmaxf(x, y); });
 }
 
+// total / n (the same n in all lanes), inv_n = 1 / n as it is in float: the product, which is exact for a power of two, else corrected once by what it
+// leaves over
+__device__ __forceinline__ float mean_of(float total, int n, float inv_n) {
+    float m = total * inv_n;
+    if ((n & (n - 1)) != 0) m = __builtin_fmaf(__builtin_fmaf(-m, (float)n, total), inv_n, m);
+    return m;
+}
+
 // Tokens of the sequences before sequence b: two loads and six lane exchanges whatever b is (a loop over the kernel argument
 // is a scalar load and a wait per sequence).  Every lane of the wave calls it and gets the sum.
 __device__ __forceinline__ int tokens_before(const SeqLens& lens, int b, int lane) {

@@ -81,7 +81,7 @@ struct StepSmem {
     // wave-private: 2 weight units of 16 rows, or units of the input with 32 rows in all; the attention's merge lies over it
     half_t stage[kSWaves][2 * 16 * kSRow];
     float red[kSWaves][16 * 68];                   // [wave][row][up to 64 columns + 4]
-    float stat[kSWaves][16][2];                    // [wave][row] mean and squared deviations of the wave's share of the row
+    float stat[16][kSWaves * 4 + 4];               // [row][wave] sum, mean and squared deviations of the wave's share of the row (+4: rows in other banks)
     word_t ticket;
     int in_use;                                    // the wait for the exchange set came to its bound
 };
@@ -193,6 +193,15 @@ __device__ __forceinline__ float row_sum(float v) {
     return v;
 }
 
+// Partial sums of neighbouring columns, in pairs: the order in which row_sum goes on over the lanes
+template <int N>
+__device__ __forceinline__ float pair_sum(const float (&p)[N]) {
+    static_assert(N == 1 || N == 2 || N == 4, "partial sums");
+    if constexpr (N == 4) return (p[0] + p[1]) + (p[2] + p[3]);
+    else if constexpr (N == 2) return p[0] + p[1];
+    else return p[0];
+}
+
 // E columns of the input of the first layer, from column c on
 template <int E>
 __device__ __forceinline__ void input_row(const StepArgs& a, int row, int c, half_t (&out)[E]) {
@@ -281,6 +290,20 @@ __device__ __forceinline__ void project(const StepArgs& a, const Where& w, StepS
             er = half4v{r[0], r[1], r[2], r[3]};
             if (a.tok.ids != nullptr) *reinterpret_cast<half4v*>(a.tok.rows + (size_t)(w.row0 + em) * H + en) = er;
         }
+    }
+    // of the LayerNorm: the size of this wave's share of a row and of those that this lane merges (worked out here: behind the wait they are in the chain)
+    constexpr int SL = LPR < kSWaves ? LPR : kSWaves, SN = kSWaves / SL;       // the waves' shares, neighbours dealt to the lanes of a row
+    float inv_k, inv_share, weight[SN];
+    if constexpr (LN) {
+        auto share = [&](int v) { return (float)(v < units ? 64 * ((units - v + kSWaves - 1) / kSWaves) : 0); };
+        inv_k = 1.0f / (float)K;
+        inv_share = wave < units ? __builtin_amdgcn_rcpf(share(wave)) : 0.f;     // a power of two, or rounded once: any value near the mean serves
+#pragma unroll
+        for (int v = 0; v < SN; ++v) {
+            weight[v] = share(lane % SL * SN + v);
+            asm volatile("" : "+v"(weight[v]));
+        }
+        asm volatile("" : "+v"(inv_k), "+v"(inv_share));
     }
     // weights into matrix-operand layout by way of LDS (whole lines per load instruction), while there is nothing else to do: two
     // 16-row units at a time
@@ -428,31 +451,33 @@ __device__ __forceinline__ void project(const StepArgs& a, const Where& w, StepS
     }
 
     if constexpr (LN) {
-        // mean and squared deviations of the wave's share of each row, then of the row (shares merged by their sizes)
-        int count = (units - wave + kSWaves - 1) / kSWaves;
-        count = count < 0 ? 0 : count;
-        float sum = 0.f, sq = 0.f;
+        // Sum and squared deviations of the wave's share of each row, then of the row (shares merged by their sizes).  The mean is one sum, divided once, as in
+        // the LayerNorm's own launches, and the share's own mean is taken from the values before anything else, which leaves a small shift: a row far
+        // from zero loses no bits.  (x * rstd - mean * rstd has an error of 2e-5 deviations where the mean is a thousand of them.)
+        // Added up per four columns, then in pairs: a row has the same bits on the variants of 4, 8 and 16 rows, whose lanes hold 4, 8 and 16 columns.
+        float psum[E / 4], psq[E / 4], dev[STEPS][E];
+#pragma unroll
+        for (int p = 0; p < E / 4; ++p) psum[p] = psq[p] = 0.f;
 #pragma unroll
         for (int s = 0; s < STEPS; ++s)
             if (has(s)) {
 #pragma unroll
-                for (int e = 0; e < E; e += 2) sum = __builtin_amdgcn_fdot2(half2v{xv[s][e], xv[s][e + 1]}, half2v{(half_t)1.f, (half_t)1.f}, sum, false);
+                for (int e = 0; e < E; e += 2) psum[e / 4] = __builtin_amdgcn_fdot2(half2v{xv[s][e], xv[s][e + 1]}, half2v{(half_t)1.f, (half_t)1.f}, psum[e / 4], false);
             }
-        sum = row_sum<ROWS>(sum);
-        const float mw = count > 0 ? sum * __builtin_amdgcn_rcpf((float)(64 * count)) : 0.f;      // a power of two, or rounded once: any value near the mean serves
+        const float sum = row_sum<ROWS>(pair_sum(psum));
+        const float mw = sum * inv_share;
 #pragma unroll
         for (int s = 0; s < STEPS; ++s)
             if (has(s)) {
 #pragma unroll
                 for (int e = 0; e < E; e += 2) {
-                    float d0, d1;
-                    minus_mean(half2v{xv[s][e], xv[s][e + 1]}, mw, d0, d1);
-                    sq = __builtin_fmaf(d0, d0, sq);
-                    sq = __builtin_fmaf(d1, d1, sq);
+                    minus_mean(half2v{xv[s][e], xv[s][e + 1]}, mw, dev[s][e], dev[s][e + 1]);
+                    psq[e / 4] = __builtin_fmaf(dev[s][e], dev[s][e], psq[e / 4]);
+                    psq[e / 4] = __builtin_fmaf(dev[s][e + 1], dev[s][e + 1], psq[e / 4]);
                 }
             }
-        sq = row_sum<ROWS>(sq);
-        if (lane % LPR == 0 && sub == 0) *reinterpret_cast<float2v*>(&sm.stat[wave][row][0]) = float2v{mw, sq};
+        const float sq = row_sum<ROWS>(pair_sum(psq));
+        if (lane % LPR == 0 && sub == 0) *reinterpret_cast<float4v*>(&sm.stat[row][wave * 4]) = float4v{sum, mw, sq, 0.f};
         __syncthreads();
         if constexpr (PH == kStepQkv) {
             // all waves together have seen all of x(g): layer g-1 is finished, its exchange set is nobody's (the acknowledgement
@@ -461,33 +486,26 @@ __device__ __forceinline__ void project(const StepArgs& a, const Where& w, StepS
             const uint32_t hi = lo + per < a.set_words ? lo + per : a.set_words;
             for (uint32_t c = lo + w.tid; c < hi; c += kSThreads) st_word(w.other + c, kEmpty);
         }
-        // the waves' shares, dealt to the lanes of a row
-        constexpr int SL = LPR < kSWaves ? LPR : kSWaves, SN = kSWaves / SL;
-        const float inv_k = 1.0f / (float)K;
-        float2v sv[SN];
-        float weight[SN], mean = 0.f, m2 = 0.f;
+        float4v sv[SN];
+        float total = 0.f, m2 = 0.f;
 #pragma unroll
-        for (int v = 0; v < SN; ++v) sv[v] = *reinterpret_cast<const float2v*>(&sm.stat[lane % SL + SL * v][row][0]);
+        for (int v = 0; v < SN; ++v) sv[v] = *reinterpret_cast<const float4v*>(&sm.stat[row][(lane % SL * SN + v) * 4]);
 #pragma unroll
-        for (int v = 0; v < SN; ++v) {
-            const int c = (units - (lane % SL + SL * v) + kSWaves - 1) / kSWaves;
-            weight[v] = c < 0 ? 0.f : (float)(64 * c);
-            mean = __builtin_fmaf(sv[v][0], weight[v] * inv_k, mean);
-        }
-        mean = sum_shares<SL>(mean);
+        for (int v = 0; v < SN; ++v) total += sv[v][0];
+        const float mean = mean_of(sum_shares<SL>(total), K, inv_k);
 #pragma unroll
         for (int v = 0; v < SN; ++v) {
-            const float d = sv[v][0] - mean;
-            m2 += sv[v][1] + weight[v] * d * d;
+            const float d = sv[v][1] - mean;
+            m2 += __builtin_fmaf(weight[v] * d, d, sv[v][2]);
         }
         m2 = sum_shares<SL>(m2);
-        const float rstd = rsqrtf(m2 * inv_k + eps), shift = -mean * rstd;
+        const float rstd = rsqrtf(m2 * inv_k + eps), shift = (mw - mean) * rstd;
 #pragma unroll
         for (int s = 0; s < STEPS; ++s)
 #pragma unroll
             for (int e = 0; e < E; ++e) {
                 // fused multiply-adds that take their fp16 operands directly
-                const float t = __builtin_fmaf((float)xv[s][e], rstd, shift);
+                const float t = __builtin_fmaf(dev[s][e], rstd, shift);
                 xv[s][e] = (half_t)__builtin_fmaf(t, (float)gv[s][e], (float)bv[s][e]);
             }
     }
@@ -697,14 +715,14 @@ __device__ __forceinline__ void attend(const StepArgs& a, const Where& w, StepSm
 #pragma unroll
         for (int e = 0; e < 8; ++e) sm_acc[wave * D + lane * 8 + e] = acc[e];
     }
-    if (lane == 0) *reinterpret_cast<float2v*>(&sm.stat[wave][0][0]) = float2v{mw, l};
+    if (lane == 0) *reinterpret_cast<float2v*>(&sm.stat[wave][0]) = float2v{mw, l};
     __syncthreads();
     if (w.tid >= D / 2) return;
     float2v ml[kSWaves];
     float mx = kNone;
 #pragma unroll
     for (int v = 0; v < kSWaves; ++v) {
-        ml[v] = *reinterpret_cast<const float2v*>(&sm.stat[v][0][0]);
+        ml[v] = *reinterpret_cast<const float2v*>(&sm.stat[v][0]);
         mx = fmaxf(mx, ml[v][0]);
     }
     float sum = 0.f, a0 = 0.f, a1 = 0.f;

@@ -8,7 +8,7 @@
 //   items       QKV: 64 columns of a row tile (16 rows), LayerNorm inside; attention: 128 query rows of a (sequence, head) pair; output
 //               projection: as QKV, residual added; first feed-forward projection: LayerNorm inside, GELU; second: 64 columns and a range of at
 //               most 1024 of K, whose fp32 sums the last item of a tile to arrive adds up in the order of the ranges.  Two workgroups share a CU
-//               (124 registers, 77 KB of LDS), so one's weights arrive while the other waits or computes.
+//               (127 registers, 78 KB of LDS), so one's weights arrive while the other waits or computes.
 //   hand-over   Rows go through memory at agent scope (relaxed stores and loads, which is what makes them coherent between the XCDs' caches);
 //               a producer waits until its stores are acknowledged, then raises a counter of its phase and row tile, and the consumers' first
 //               wave polls that counter.  (Words that are their own flags, as in decode_step.hip, save the counter's trip, but here a
@@ -74,7 +74,7 @@ struct PromptSmem {
     uint32_t word;                                 // number of this item; arrivals at its tile
     int late;                                      // the wait came to its bound
     half_t scale[2][kPromptStepK];                 // of the LayerNorm, and its shift
-    float stat[kPWaves][kPRows][2];                 // mean and squared deviations of the wave's share of the row
+    float stat[kPRows][kPWaves * 4 + 4];           // [row][wave] sum, mean and squared deviations of the wave's share of the row (+4: rows in other banks)
     union {
         // wave-private: two weight units of 16 rows, a unit of the input (rows of 72 halfs), then the wave's partial tile (rows of 68 floats)
         __attribute__((aligned(16))) char wave[kPWaves][kWaveBytes];
@@ -178,6 +178,16 @@ __device__ __forceinline__ void project(const PromptArgs& a, const Spot& w, Prom
             }
         }
     }
+    // of the LayerNorm: the size of this wave's share of a row and of the one that this lane merges (worked out here: behind the wait they are in the chain)
+    static_assert(kPWaves == 8, "a share per lane of a row");
+    float inv_k, inv_share, weight;
+    if constexpr (LN) {
+        auto share = [&](int v) { return (float)(v < units ? 64 * ((units - v + kPWaves - 1) / kPWaves) : 0); };
+        inv_k = 1.0f / (float)K;
+        inv_share = wave < units ? __builtin_amdgcn_rcpf(share(wave)) : 0.f;     // a power of two, or rounded once: any value near the mean serves
+        weight = share(chunk);
+        asm volatile("" : "+v"(inv_k), "+v"(inv_share), "+v"(weight));
+    }
     // weights into matrix-operand layout by way of LDS (whole lines per load instruction), two 16-row units at a time
     half_t* st = reinterpret_cast<half_t*>(sm.wave[wave]);
 #pragma unroll
@@ -250,10 +260,9 @@ __device__ __forceinline__ void project(const PromptArgs& a, const Spot& w, Prom
     }
 
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");    if constexpr (LN) {
-        // mean and squared deviations of the wave's share of each row, then of the row (shares merged by their sizes)
-        int count = (units - wave + kPWaves - 1) / kPWaves;
-        count = count < 0 ? 0 : count;
-        const float share = count > 0 ? 1.0f / (float)(64 * count) : 0.f;
+        // Sum and squared deviations of the wave's share of each row, then of the row (shares merged by their sizes).  As in the LayerNorm's own launches
+        // the mean is one sum, divided once, and is taken from the values before anything else: a row far from zero loses no bits (x * rstd - mean *
+        // rstd, an instruction less per value, has an error of 2e-5 deviations where the mean is a thousand of them).
 #pragma unroll
         for (int j = 0; j < J; ++j) {
             float sum = 0.f, sq = 0.f;
@@ -263,7 +272,8 @@ __device__ __forceinline__ void project(const PromptArgs& a, const Spot& w, Prom
 #pragma unroll
                     for (int e = 0; e < 8; e += 2) sum = __builtin_amdgcn_fdot2(half2v{xv[i][j][e], xv[i][j][e + 1]}, half2v{(half_t)1.f, (half_t)1.f}, sum, false);
                 }
-            const float mw = sum8(sum) * share;
+            sum = sum8(sum);
+            const float mw = sum * inv_share;
 #pragma unroll
             for (int i = 0; i < U; ++i)
                 if (has(i)) {
@@ -277,27 +287,26 @@ __device__ __forceinline__ void project(const PromptArgs& a, const Spot& w, Prom
                     }
                 }
             sq = sum8(sq);
-            if (chunk == 0) *reinterpret_cast<float2v*>(&sm.stat[wave][8 * j + wrow][0]) = float2v{mw, sq};
+            if (chunk == 0) *reinterpret_cast<float4v*>(&sm.stat[8 * j + wrow][wave * 4]) = float4v{sum, mw, sq, 0.f};
         }
         __syncthreads();
         // eight lanes per row, a wave's share each
-        static_assert(kPWaves == 8, "a share per lane of a row");
-        const float inv_k = 1.0f / (float)K;
-        int theirs = (units - chunk + kPWaves - 1) / kPWaves;
-        const float weight = theirs < 0 ? 0.f : (float)(64 * theirs);
 #pragma unroll
         for (int j = 0; j < J; ++j) {
-            const float2v sv = *reinterpret_cast<const float2v*>(&sm.stat[chunk][8 * j + wrow][0]);
-            const float mean = sum8(sv[0] * (weight * inv_k)), d = sv[0] - mean, m2 = sum8(sv[1] + weight * d * d);
-            const float rstd = rsqrtf(m2 * inv_k + a.eps), shift = -mean * rstd;
+            const float4v sv = *reinterpret_cast<const float4v*>(&sm.stat[8 * j + wrow][chunk * 4]);
+            const float mean = mean_of(sum8(sv[0]), K, inv_k), d = sv[1] - mean, m2 = sum8(sv[2] + weight * d * d);
+            const float rstd = rsqrtf(m2 * inv_k + a.eps);
 #pragma unroll
             for (int i = 0; i < U; ++i)
                 if (has(i)) {
                     const half8v gv = *reinterpret_cast<const half8v*>(&sm.scale[0][column(i)]), bv = *reinterpret_cast<const half8v*>(&sm.scale[1][column(i)]);
 #pragma unroll
-                    for (int e = 0; e < 8; ++e) {
-                        const float t = __builtin_fmaf((float)xv[i][j][e], rstd, shift);
-                        xv[i][j][e] = (half_t)__builtin_fmaf(t, (float)gv[e], (float)bv[e]);
+                    for (int e = 0; e < 8; e += 2) {
+                        float d0, d1;
+                        const half2v x2 = half2v{xv[i][j][e], xv[i][j][e + 1]};
+                        minus_mean(x2, mean, d0, d1);
+                        xv[i][j][e] = (half_t)__builtin_fmaf(d0 * rstd, (float)gv[e], (float)bv[e]);
+                        xv[i][j][e + 1] = (half_t)__builtin_fmaf(d1 * rstd, (float)gv[e + 1], (float)bv[e + 1]);
                     }
                 }
         }
