@@ -99,6 +99,10 @@ int eet_layer_create(const eet_layer_config *cfg, const eet_layer_weights *weigh
  *   kv_cache   DEVICE, eet_kv_cache_bytes(cfg); slots [0, q_lens[b]) of sequence b are written,
  *              all other bytes are left untouched
  * Afterwards the cache length of sequence b is q_lens[b].
+ * A short prompt of a narrow layer is one launch whose parts wait for one another, behind a small one.  Should such a wait, which takes
+ * microseconds, have to give up after a tenth of a second or more, the launch still ends, what depends on it is NaN (in `out` and in the
+ * cache), eet_cache_lens returns HIP until the next prefill or restore, and steps that are one launch leave NaN until then.  The same
+ * holds for the stack and model entry points.
  * Errors: INVALID_ARG, CAPACITY (batch > max_batch or padded_len > max_prompt). */
 int eet_prefill(eet_layer_t *layer, const int32_t *q_lens, int32_t batch, int32_t padded_len,
                 const void *tokens, void *out, void *kv_cache, void *hip_stream);
@@ -117,7 +121,8 @@ int eet_prefill_left_padded(eet_layer_t *layer, const int32_t *q_lens, int32_t b
  * Arguments as eet_prefill; kv_scratch is DEVICE memory of eet_kv_cache_bytes(cfg) that holds the
  * keys and values of this pass only (slots [0, q_lens[b]) are written).  The layer's workspace is
  * reused, so any prefill / decode state of the layer is dropped: a following eet_decode_step
- * returns STATE until the next eet_prefill.  Errors as eet_prefill. */
+ * returns STATE until the next eet_prefill.  No lengths are kept either, so NaN in `out` is all that
+ * tells of a wait that gave up (see eet_prefill).  Errors as eet_prefill. */
 int eet_layer_encode(eet_layer_t *layer, const int32_t *q_lens, int32_t batch, int32_t padded_len,
                      const void *tokens, void *out, void *kv_scratch, void *hip_stream);
 
@@ -143,7 +148,8 @@ int eet_decode_step(eet_layer_t *layer, const void *tokens, void *out, void *kv_
 
 /* Copy the device-side cache lengths n_b of the current batch to HOST int32[batch] (Section 3.1: the
  * number of keys and values kept per sequence; with the padding offsets of Section 2.1 these are the
- * integers that must match exactly).  Synchronises the stream.  Errors: STATE, HIP. */
+ * integers that must match exactly).  Synchronises the stream.  Errors: STATE, HIP (also where a prefill or a
+ * decode step since the lengths were last set has given up a wait inside its launch). */
 int eet_cache_lens(eet_layer_t *layer, int32_t *out_host, void *hip_stream);
 
 /* Resume from a saved state.  The resumable state of a layer is its K/V cache (the caller's memory) and the

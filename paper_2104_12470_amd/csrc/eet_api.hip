@@ -348,6 +348,7 @@ static int enqueue_prompt_layers(eet_layer* const* layers, int n, const SeqLens&
         int32_t* d_cu = reinterpret_cast<int32_t*>(L0->ws + L0->lay.cu);
         int32_t* d_map = reinterpret_cast<int32_t*>(L0->ws + L0->lay.row_map);
         a.lens = d_lens; a.cu = d_cu; a.row_map = d_map;
+        a.step = causal ? step_area(L0) : StepArea{};
         a.eps = c.ln_eps;
         a.T = (int)T; a.padded_rows = batch * padded_len; a.S = padded_len; a.batch = batch; a.max_len = max_len;
         a.H = H; a.F = F; a.heads = c.heads; a.max_seq = c.max_seq; a.causal = causal ? 1 : 0; a.left_pad = left_padded ? 1 : 0;
@@ -358,7 +359,7 @@ static int enqueue_prompt_layers(eet_layer* const* layers, int n, const SeqLens&
             a.layer[l] = StepLayer{p(w.ln1_g), p(w.ln1_b), p(w.w_qkv), p(w.b_qkv), p(w.w_o), p(w.b_o), p(w.ln2_g), p(w.ln2_b), p(w.w_fc1),
                                    p(w.b_fc1), p(w.w_fc2), p(w.b_fc2), kv, kv + (size_t)c.max_batch * H * c.max_seq};
         }
-        EET_LAUNCH(launch_prompt_setup(lens, a, d_lens, d_cu, d_map, causal ? step_area(L0) : StepArea{}, s), "prefill set-up");
+        EET_LAUNCH(launch_prompt_setup(lens, a, d_lens, d_cu, d_map, l0 == 0 ? a.step : StepArea{}, s), "prefill set-up");
         // weights that several row tiles share, or that the memory-side cache keeps until the next call, are read with plain loads
         EET_LAUNCH(launch_prompt_layers(a, a.row_tiles == 1 && weights > kMemorySideCacheBytes, s), "prefill layers");
         in = o;
@@ -705,8 +706,8 @@ int eet_cache_lens(eet_layer_t* L, int32_t* out_host, void* hip_stream) {
     uint32_t any = 0;
     for (const uint32_t state : step_state) any |= state;
     if (any & kStepGaveUp)
-        return fail(EET_ERR_HIP, "eet_cache_lens: a decode step gave up waiting for a part of its own launch: its output and all since are NaN "
-                                 "until the next prefill or restore");
+        return fail(EET_ERR_HIP, "eet_cache_lens: a prefill or a decode step gave up waiting for a part of its own launch: its output and all since are "
+                                 "NaN until the next prefill or restore");
     return EET_OK;
 }
 

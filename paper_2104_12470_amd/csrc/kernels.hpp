@@ -267,6 +267,7 @@ struct PromptArgs : PromptShape {
     float* part;
     uint32_t* ctl;
     const int32_t *lens, *cu, *row_map;  // DEVICE, left by launch_prompt_setup
+    StepArea step;                       // of the decode steps to come: where a wait given up is said (no groups: nowhere)
     float eps;
     int T, padded_rows, S, batch, max_len, H, F, heads, max_seq, n_layers, causal, left_pad;
     // set by the launcher
@@ -276,7 +277,8 @@ struct PromptArgs : PromptShape {
 bool prompt_step_fits(int64_t rows, int64_t padded_rows, int batch, int max_len, int hidden, int heads, int ffn);
 PromptShape prompt_step_shape(int rows, int hidden, int ffn);
 size_t prompt_step_bytes_up_to(int64_t max_rows, int hidden, int heads, int ffn);
-// Lengths, prefix sums and row map, pad rows of a.out, the counters, and the exchange area of the decode steps to come
+// Lengths, prefix sums and row map, pad rows of a.out, the counters, and the exchange area of the decode steps to come (not where an earlier
+// launch of the same prefill has done that, and may have said something there)
 hipError_t launch_prompt_setup(const SeqLens& lens, const PromptArgs& a, int32_t* cache_lens, int32_t* cu, int32_t* row_map, StepArea step, hipStream_t s);
 hipError_t launch_prompt_layers(PromptArgs& a, bool read_once, hipStream_t s);
 

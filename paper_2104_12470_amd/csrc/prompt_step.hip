@@ -18,7 +18,8 @@
 //               rows, which every writer of layer l+1 waits for; except the keys and values of an encoder, whose layers share one
 //               region: its QKV items also wait for the attention of every tile that shares a sequence with theirs.
 //   progress    as in decode_step.hip: no assumption about how many workgroups are resident or what else runs.  The waits are bounded all the
-//               same; an item whose wait comes to its bound hands NaN on, which reaches the output.
+//               same; an item whose wait comes to its bound hands NaN on, which reaches the output, and a prefill says so where its decode steps
+//               would (kStepGaveUp, in every group's control words): the lengths come back with an error, and the steps that follow are NaN.
 #include "kernels.hpp"
 
 namespace eet {
@@ -95,7 +96,7 @@ enum { kCntX = 0, kCntQkv = 1, kCntAtt = 2, kCntOut = 3, kCntFfn1 = 4 };   // kC
 
 // The first wave waits until each of its lanes' counters has come to its target (lanes without one: true); all threads go on together.
 template <class Reached>
-__device__ __forceinline__ void await(const Spot& w, int& late, const uint32_t* before, uint32_t at_least, Reached reached) {
+__device__ __forceinline__ void await(const PromptArgs& a, const Spot& w, int& late, const uint32_t* before, uint32_t at_least, Reached reached) {
     if (w.wave == 0) {
         if (before != nullptr)
             for (int spin = 0; spin < kPSpinLimit; ++spin) {
@@ -108,7 +109,10 @@ __device__ __forceinline__ void await(const Spot& w, int& late, const uint32_t* 
             ok = __all(reached(w.lane));
             if (!ok) __builtin_amdgcn_s_sleep(1);
         } while (!ok & (++spin < kPSpinLimit));
-        if (!ok && w.lane == 0) late = 1;
+        if (!ok) {
+            if (w.lane == 0) late = 1;
+            if (w.lane < a.step.groups) __hip_atomic_fetch_or(a.step.ctl + (size_t)w.lane * a.step.words, (word_t)kStepGaveUp, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
     }
 }
 
@@ -217,7 +221,7 @@ __device__ __forceinline__ void project(const PromptArgs& a, const Spot& w, Prom
                 lo = a.cu[a.row_map[t0] / a.S] / TR;
                 hi = (a.cu[a.row_map[end - 1] / a.S + 1] - 1) / TR;
             }
-            await(w, sm.late, counter(a, r, kCntFfn1), lay * (uint32_t)(a.range_units), [&](int i) {
+            await(a, w, sm.late, counter(a, r, kCntFfn1), lay * (uint32_t)(a.range_units), [&](int i) {
                 bool ok = true;
                 if (i == 0) ok = ld_count(counter(a, r, kCntX)) >= lay * (uint32_t)(H / 64);
                 const int o = lo + i;
@@ -230,12 +234,12 @@ __device__ __forceinline__ void project(const PromptArgs& a, const Spot& w, Prom
         }
     } else if constexpr (PH == kPOut) {
         const int rows = a.T - t0 < TR ? a.T - t0 : TR;
-        await(w, sm.late, counter(a, r, kCntQkv), next * (uint32_t)(3 * H / 64), [&](int i) { return i != 0 || ld_count(counter(a, r, kCntAtt)) >= next * (uint32_t)(a.heads * rows); });
+        await(a, w, sm.late, counter(a, r, kCntQkv), next * (uint32_t)(3 * H / 64), [&](int i) { return i != 0 || ld_count(counter(a, r, kCntAtt)) >= next * (uint32_t)(a.heads * rows); });
     } else if constexpr (PH == kPFfn1) {
         const int rows = a.T - t0 < TR ? a.T - t0 : TR;
-        await(w, sm.late, counter(a, r, kCntAtt), next * (uint32_t)(a.heads * rows), [&](int i) { return i != 0 || ld_count(counter(a, r, kCntOut)) >= next * (uint32_t)(H / 64); });
+        await(a, w, sm.late, counter(a, r, kCntAtt), next * (uint32_t)(a.heads * rows), [&](int i) { return i != 0 || ld_count(counter(a, r, kCntOut)) >= next * (uint32_t)(H / 64); });
     } else {
-        await(w, sm.late, counter(a, r, kCntOut), next * (uint32_t)(H / 64), [&](int i) { return i != 0 || ld_count(counter(a, r, kCntFfn1 + range)) >= next * (uint32_t)units; });
+        await(a, w, sm.late, counter(a, r, kCntOut), next * (uint32_t)(H / 64), [&](int i) { return i != 0 || ld_count(counter(a, r, kCntFfn1 + range)) >= next * (uint32_t)units; });
     }
     __syncthreads();
     const float poison = sm.late != 0 ? __builtin_nanf("") : 0.f;
@@ -422,7 +426,7 @@ __device__ __forceinline__ void attend(const PromptArgs& a, const Spot& w, Promp
     const int keys = a.causal ? i0 + rows : len;                              // keys it looks at
     const int lo = row0 / TR, hi = (row0 + (a.causal ? keys : len) - 1) / TR; // row tiles they and the queries lie in
     const uint32_t target = (uint32_t)(w.layer + 1) * (uint32_t)(3 * a.H / 64);
-    await(w, base.late, w.layer == 0 ? nullptr : counter(a, hi, kCntX), (uint32_t)w.layer * (uint32_t)(a.H / 64), [&](int l) { return lo + l > hi || ld_count(counter(a, lo + l, kCntQkv)) >= target; });
+    await(a, w, base.late, w.layer == 0 ? nullptr : counter(a, hi, kCntX), (uint32_t)w.layer * (uint32_t)(a.H / 64), [&](int l) { return lo + l > hi || ld_count(counter(a, lo + l, kCntQkv)) >= target; });
     __syncthreads();    const float c = base.late != 0 ? __builtin_nanf("") : rsqrtf((float)D) * kPLog2e;
     const AgentBuffer qb(a.q, (uint32_t)a.T * (uint32_t)(a.H * 2));
     const size_t head = ((size_t)b * a.heads + g) * a.max_seq * D;
