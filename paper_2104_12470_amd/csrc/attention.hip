@@ -1082,31 +1082,37 @@ __device__ __forceinline__ half_t merge_ranges(const float* ml, const float* pa,
 }
 
 // The sequence that comes at place `place` when the longest come first, lengths in sixteenths of the capacity (rounded up to a power of two), of equals the
-// one with the lower number: the largest length that more than `place` sequences reach, bit by bit, by counting over the lanes (two lengths each).  All
-// lanes of the wave call it.  It is worked out from the lengths of the moment and kept nowhere: a step that was recorded for some number
-// of sequences finds those in any later state.
-__device__ __forceinline__ int sequence_at_place(const int32_t* lens, int batch, int capacity, int place, int lane) {
+// one with the lower number: the largest length that more than `place` sequences reach, bit by bit, by counting over the lanes (two lengths each); where all
+// are equal, that of the batch's order without counting.  All lanes of the wave call it.  It is worked out from the lengths of the moment and kept
+// nowhere: a step that was recorded for some number of sequences finds those in any later state.
+struct Placed {
+    int b, len;                                          // the sequence, and its length as it was read: no second trip to memory behind the first
+};
+__device__ __forceinline__ Placed sequence_at_place(const int32_t* lens, int batch, int capacity, int place, int lane) {
     static_assert(kOrderedSequences == 2 * kWave, "two lengths per lane");       // decode_longest_first: batch is no more than that
     const int bits = 32 - __builtin_clz((unsigned)capacity | 1u), shift = bits > 4 ? bits - 4 : 0;
-    auto length = [&](int b) {
-        const int n = b < batch ? lens[b] : 0;
-        return b < batch ? (n < 0 ? 0 : n > capacity ? capacity : n) >> shift : -1;
-    };
-    const int n0 = length(lane), n1 = length(lane + kWave);
-    auto reach = [&](int t) { return __popcll(__ballot(n0 >= t)) + __popcll(__ballot(n1 >= t)); };
-    int t = 0;
+    const bool has0 = lane < batch, has1 = lane + kWave < batch;
+    const int len0 = has0 ? lens[lane] : 0, len1 = has1 ? lens[lane + kWave] : 0;
+    auto part = [&](int n) { return (n < 0 ? 0 : n > capacity ? capacity : n) >> shift; };
+    const int n0 = has0 ? part(len0) : -1, n1 = has1 ? part(len1) : -1, first = __builtin_amdgcn_readfirstlane(n0);
+    int b = place;
+    if (__any((has0 && n0 != first) || (has1 && n1 != first))) {
+        auto reach = [&](int t) { return __popcll(__ballot(n0 >= t)) + __popcll(__ballot(n1 >= t)); };
+        int t = 0;
 #pragma unroll
-    for (int bit = 8; bit > 0; bit >>= 1)
-        if (reach(t + bit) > place) t += bit;
-    int k = place - reach(t + 1);                        // which of those of length t
-    unsigned long long equal = __ballot(n0 == t);
-    const bool upper = k >= __popcll(equal);
-    if (upper) {
-        k -= __popcll(equal);
-        equal = __ballot(n1 == t);
+        for (int bit = 8; bit > 0; bit >>= 1)
+            if (reach(t + bit) > place) t += bit;
+        int k = place - reach(t + 1);                    // which of those of length t
+        unsigned long long equal = __ballot(n0 == t);
+        const bool upper = k >= __popcll(equal);
+        if (upper) {
+            k -= __popcll(equal);
+            equal = __ballot(n1 == t);
+        }
+        const int before = __builtin_amdgcn_mbcnt_hi((unsigned)(equal >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)equal, 0));
+        b = __builtin_ctzll(__ballot((equal >> lane & 1ull) != 0 && before == k)) + (upper ? kWave : 0);
     }
-    const int before = __builtin_amdgcn_mbcnt_hi((unsigned)(equal >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)equal, 0));
-    return __builtin_ctzll(__ballot((equal >> lane & 1ull) != 0 && before == k)) + (upper ? kWave : 0);
+    return Placed{b, __builtin_amdgcn_readlane(b < kWave ? len0 : len1, b & (kWave - 1))};
 }
 
 // NT: K and V rows are loaded with the non-temporal hint (AttnDecodeArgs::read_once); a template parameter because the
@@ -1123,9 +1129,14 @@ __global__ __launch_bounds__(NW * 64) void attn_decode(AttnDecodeArgs a) {
 
     const int sp = blockIdx.x, g = blockIdx.y;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int b = a.longest_first ? sequence_at_place(a.lens, a.batch, a.capacity, blockIdx.z, lane) : (int)blockIdx.z;
+    int b = blockIdx.z, n;
+    if (a.longest_first) {
+        const Placed p = sequence_at_place(a.lens, a.batch, a.capacity, b, lane);
+        b = p.b;
+        n = p.len;
+    } else n = a.lens[b];
     const int kslot = lane / LPK, chunk = lane % LPK;
-    int n = a.lens[b] + a.len_bias;                      // visible keys
+    n += a.len_bias;                                     // visible keys
     n = n < 0 ? 0 : (n > a.capacity ? a.capacity : n);   // whatever the device-side length says, never outside the pair's slots
     const int splits = a.splits;
     int per = (n + splits - 1) / splits;

@@ -330,10 +330,11 @@ inline bool prefill_touches_weights(int64_t rows, size_t ahead, size_t stack, si
 // ---- decode attention: the longest sequences first ----
 // With more pairs than CUs a pair is one workgroup, and the launch ends with those of the longest sequences, wherever the batch has them; so they
 // start first.  us per pass of decode steps, in the order of the batch / longest first (lengths): "server tokens 4096" (48 x 32 heads of 128, 100 to
-// 1500) 3226 / 3134; 12 x 32 of 128 (100 to 2000) 1982 / 1895; 24 x 16 of 64 (100 to 1000) 2697 / 2608; 100 x 16 of 64, four layers 5023 / 4888; 16 x 96 of 128
-// (1024 to 2104) 5902 / 5885.  A workgroup pays some 0.2 us for its place, which sequences of one length give nothing for: 64 x 16 of 64, 500 and
-// 900 keys 3607 / 3621, 4481 / 4497; and which counts where all are short, so not below 512 slots: 128 x 16 of 64, 200 keys 879 / 888, 128 x 8 of at
-// most 30 3870 / 3996; 24 x 32 of 128, 40 to 400 1716 / 1708.  (All bits of the lengths instead of the four upper ones: 905 and 3960.)
+// 1500) 3219 / 3134; 12 x 32 of 128 (100 to 2000) 1982 / 1895; 24 layers of 24 x 16 of 64 (100 to 1000) 4071 / 3913; four of 100 x 16 of 64 2508 / 2423; 16 x 96 of
+// 128 (1024 to 2104) 5902 / 5885.  Sequences of one length gain nothing and pay nothing that stands out of the noise: 24 layers of 64 x 16 of 64, 500 and 900
+// keys 5445 / 5439, 6888 / 6902; 48 x 32 of 128, 800 keys 1541 / 1538; four of 100 x 16 of 64, 508 keys 2367 / 2363.  (They paid 0.2 us per workgroup as long as the
+// length was read a second time and equal lengths were counted too.)  Measured then: short sequences, 128 x 16 of 64, 200 keys 879 / 888, 128 x 8 of at most 30
+// 3870 / 3996, 24 x 32 of 128, 40 to 400 1716 / 1708, so not below 512 slots; and all bits of the lengths instead of the four upper ones, 905 and 3960.
 // A wave counts two lengths per lane and no more (attention.hip: sequence_at_place), so the operators' calls with more sequences than that keep the order of the batch.
 constexpr int kOrderedSequences = 128;
 inline bool decode_longest_first(int splits, int batch, int heads, int capacity) {
