@@ -277,13 +277,6 @@ __global__ __launch_bounds__(256, CAUSAL && AHEAD ? 4 : 2) void attn_prefill(Att
 // is the only one that compares indices.  Waves whose rows end before the workgroup's last key
 // tile keep loading and synchronising but skip the arithmetic; the row blocks are dealt to the
 // waves so that the two waves of a SIMD (w and w+4) always sum to the same amount of work.
-// LDS transpose read (gfx950): within 16 lanes, lane r supplies the address of 4 consecutive halfs "row r"; lane l
-// receives element l%4 of rows l/4, l/4+4, l/4+8, l/4+12.
-__device__ __forceinline__ half4v lds_read_tr16(const char* p) {
-    typedef short short4v __attribute__((ext_vector_type(4)));
-    const short4v v = __builtin_amdgcn_ds_read_tr16_b64_v4i16((short4v __attribute__((address_space(3)))*)p);
-    return __builtin_bit_cast(half4v, v);
-}
 
 // 16 bytes per lane from global memory straight into LDS: lane l lands at lds + 16*l (the LDS base
 // must be wave-uniform).  Kept out of the templates: the builtin only exists for the device.

@@ -83,6 +83,25 @@ __device__ __forceinline__ float wave_max(float v) {
     return reduce_wave(v, [](float x, float y) { return fmaxf(x, y); });
 }
 
+// Over aligned groups of 8 lanes
+__device__ __forceinline__ float sum8(float v) {
+    v += dpp<0xb1>(v);
+    v += dpp<0x4e>(v);
+    return v + dpp<0x141>(v);
+}
+// x - m of two halfs in float, the operands taken as they are (a conversion is a half-rate instruction, and the compiler makes a
+// conversion and an addition of a multiply-add by one)
+__device__ __forceinline__ void minus_mean(half2v x, float m, float& d0, float& d1) {
+    asm("v_fma_mix_f32 %0, %2, 1.0, -%3 op_sel_hi:[1,0,0]\n\tv_fma_mix_f32 %1, %2, 1.0, -%3 op_sel:[1,0,0] op_sel_hi:[1,0,0]" : "=&v"(d0), "=v"(d1) : "v"(x), "v"(m));
+}
+// LDS transpose read (gfx950): within 16 lanes, lane r supplies the address of 4 consecutive halfs "row r"; lane l
+// receives element l%4 of rows l/4, l/4+4, l/4+8, l/4+12.
+__device__ __forceinline__ half4v lds_read_tr16(const char* p) {
+    typedef short short4v __attribute__((ext_vector_type(4)));
+    const short4v v = __builtin_amdgcn_ds_read_tr16_b64_v4i16((short4v __attribute__((address_space(3)))*)p);
+    return __builtin_bit_cast(half4v, v);
+}
+
 // total / n (the same n in all lanes), inv_n = 1 / n as it is in float: the product, which is exact for a power of two, else corrected once by what it
 // leaves over
 __device__ __forceinline__ float mean_of(float total, int n, float inv_n) {

@@ -86,17 +86,6 @@ struct StepSmem {
     int in_use;                                    // the wait for the exchange set came to its bound
 };
 
-// x - m of two halfs in float, the operands taken as they are (a conversion is a half-rate instruction, and the compiler makes a
-// conversion and an addition of a multiply-add by one)
-__device__ __forceinline__ void minus_mean(half2v x, float m, float& d0, float& d1) {
-    asm("v_fma_mix_f32 %0, %2, 1.0, -%3 op_sel_hi:[1,0,0]\n\tv_fma_mix_f32 %1, %2, 1.0, -%3 op_sel:[1,0,0] op_sel_hi:[1,0,0]" : "=&v"(d0), "=v"(d1) : "v"(x), "v"(m));
-}
-__device__ __forceinline__ float sum8(float v) {   // over aligned groups of 8 lanes
-    v += dpp<0xb1>(v);
-    v += dpp<0x4e>(v);
-    return v + dpp<0x141>(v);
-}
-
 template <int LANES>
 __device__ __forceinline__ float sum_shares(float v) {   // over aligned groups of 4 or 8 lanes
     static_assert(LANES == 4 || LANES == 8, "lanes");

@@ -8,7 +8,7 @@
 //   items       QKV: 64 columns of a row tile (16 rows), LayerNorm inside; attention: 128 query rows of a (sequence, head) pair; output
 //               projection: as QKV, residual added; first feed-forward projection: LayerNorm inside, GELU; second: 64 columns and a range of at
 //               most 1024 of K, whose fp32 sums the last item of a tile to arrive adds up in the order of the ranges.  Two workgroups share a CU
-//               (127 registers, 78 KB of LDS), so one's weights arrive while the other waits or computes.
+//               (115 registers, 78 KB of LDS), so one's weights arrive while the other waits or computes.
 //   hand-over   Rows go through memory at agent scope (relaxed stores and loads, which is what makes them coherent between the XCDs' caches);
 //               a producer waits until its stores are acknowledged, then raises a counter of its phase and row tile, and the consumers' first
 //               wave polls that counter.  (Words that are their own flags, as in decode_step.hip, save the counter's trip, but here a
@@ -53,17 +53,6 @@ struct AgentBuffer {
         return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b128(r, (int)off, 0, kAgentScope));
     }
 };
-
-__device__ __forceinline__ float sum8(float v) {
-    v += dpp<0xb1>(v);
-    v += dpp<0x4e>(v);
-    return v + dpp<0x141>(v);
-}   // over aligned groups of 8 lanes
-
-// x - m in float, the operands taken as they are (the compiler makes a conversion and an addition of a multiply-add by one)
-__device__ __forceinline__ void minus_mean(half2v x, float m, float& d0, float& d1) {
-    asm("v_fma_mix_f32 %0, %2, 1.0, -%3 op_sel_hi:[1,0,0]\n\tv_fma_mix_f32 %1, %2, 1.0, -%3 op_sel:[1,0,0] op_sel_hi:[1,0,0]" : "=&v"(d0), "=v"(d1) : "v"(x), "v"(m));
-}
 
 template <int D>
 struct PromptAttnSmem {
@@ -118,11 +107,12 @@ __device__ __forceinline__ void await(const PromptArgs& a, const Spot& w, int& l
 
 enum PromptPhase { kPQkv = 0, kPOut = 1, kPFfn1 = 2, kPFfn2 = 3 };
 
-// ---- one item of a projection: 64 columns of 16*RB rows, K in units of 64 dealt round-robin to the waves ----
+// ---- one item of a projection: 64 columns of a row tile, K in units of 64 dealt round-robin to the waves ----
 template <int PH, bool ONCE>
 __device__ __forceinline__ void project(const PromptArgs& a, const Spot& w, PromptSmem& sm, int r, int tile, int range) {
     constexpr bool LN = PH == kPQkv || PH == kPFfn1, RES = PH == kPOut || PH == kPFfn2;
-    constexpr int U = kPUnits, NT = 4, TR = kPRows, RT = 68, J = TR / 8, QUADS = TR * 16, Q = (QUADS + kPThreads - 1) / kPThreads;
+    constexpr int U = kPUnits, NT = 4, TR = kPRows, RT = 68, J = TR / 8;
+    static_assert(TR * 16 <= kPThreads, "four columns of a row per thread, of the first half of the threads");
     const StepLayer& L = a.layer[w.layer];
     const int H = a.H, K = PH == kPFfn2 ? a.F : H, lane = w.lane, wave = w.wave;
     const bool first = w.layer == 0, last = w.layer == a.n_layers - 1;
@@ -163,23 +153,20 @@ __device__ __forceinline__ void project(const PromptArgs& a, const Spot& w, Prom
         off[j] = kOutOfRange;
         if (t < a.T) off[j] = (uint32_t)(PH == kPQkv ? a.row_map[t] : t) * (uint32_t)(K * 2);
     }
-    half4v eb[Q], er[Q];
-    int place[Q];                                                              // row of the padded layout
+    // what this thread writes: four columns, from ec on, of row et
+    const int et = t0 + w.tid / 16, ec = n0 + (w.tid & 15) * 4;
+    half4v eb, er;
+    int place = -1;                                                            // row of the padded layout
     const int which = n0 / H, c0 = n0 - which * H;                             // Q, K or V; its first column
-    size_t slot[PH == kPQkv ? Q : 1];                                          // where in the cache the row's keys or values go
-#pragma unroll
-    for (int q = 0; q < Q; ++q) {
-        const int i = w.tid + q * kPThreads, t = t0 + i / 16;
-        place[q] = -1;
-        if (i < QUADS && t < a.T) {
-            eb[q] = *reinterpret_cast<const half4v*>(bias + n0 + (i & 15) * 4);
-            place[q] = PH == kPFfn1 ? t : a.row_map[t];
-            if constexpr (PH == kPQkv) {
-                const int b = place[q] / a.S, col = c0 + (i & 15) * 4;
-                int pos = place[q] - b * a.S;
-                if (a.left_pad) pos -= a.S - a.lens[b];
-                slot[q] = ((size_t)(b * a.heads + col / a.d) * a.max_seq + pos) * a.d + col % a.d;
-            }
+    size_t slot = 0;                                                           // where in the cache the row's keys or values go
+    if (w.tid < TR * 16 && et < a.T) {
+        eb = *reinterpret_cast<const half4v*>(bias + ec);
+        place = PH == kPFfn1 ? et : a.row_map[et];
+        if constexpr (PH == kPQkv) {
+            const int b = place / a.S, col = c0 + (w.tid & 15) * 4;
+            int pos = place - b * a.S;
+            if (a.left_pad) pos -= a.S - a.lens[b];
+            slot = ((size_t)(b * a.heads + col / a.d) * a.max_seq + pos) * a.d + col % a.d;
         }
     }
     // of the LayerNorm: the size of this wave's share of a row and of the one that this lane merges (worked out here: behind the wait they are in the chain)
@@ -254,16 +241,13 @@ __device__ __forceinline__ void project(const PromptArgs& a, const Spot& w, Prom
         }
     if constexpr (RES) {
         const half_t* res = PH == kPOut ? (first ? a.tokens : a.x) : a.y;
-#pragma unroll
-        for (int q = 0; q < Q; ++q) {
-            const int i = w.tid + q * kPThreads;
-            if (place[q] >= 0)
-                er[q] = __builtin_bit_cast(half4v, __hip_atomic_load(reinterpret_cast<const word_t*>(res + (size_t)(PH == kPOut ? place[q] : t0 + i / 16) * H + n0 + (i & 15) * 4),
-                                                                      __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
-        }
+        if (place >= 0)
+            er = __builtin_bit_cast(half4v, __hip_atomic_load(reinterpret_cast<const word_t*>(res + (size_t)(PH == kPOut ? place : et) * H + ec), __ATOMIC_RELAXED,
+                                                              __HIP_MEMORY_SCOPE_AGENT));
     }
 
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");    if constexpr (LN) {
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    if constexpr (LN) {
         // Sum and squared deviations of the wave's share of each row, then of the row (shares merged by their sizes).  As in the LayerNorm's own launches
         // the mean is one sum, divided once, and is taken from the values before anything else: a row far from zero loses no bits (x * rstd - mean *
         // rstd, an instruction less per value, has an error of 2e-5 deviations where the mean is a thousand of them).
@@ -339,29 +323,20 @@ __device__ __forceinline__ void project(const PromptArgs& a, const Spot& w, Prom
 #pragma unroll
     for (int t = 0; t < NT; ++t) *reinterpret_cast<float4v*>(&red[fr * RT + 16 * t + 4 * G]) = acc[t];
     __syncthreads();
-    float4v v[Q];
+    float4v v = float4v{poison, poison, poison, poison};
+    if (place >= 0) {
 #pragma unroll
-    for (int q = 0; q < Q; ++q) {
-        const int i = w.tid + q * kPThreads;
-        v[q] = float4v{poison, poison, poison, poison};
-        if (place[q] >= 0) {
-#pragma unroll
-            for (int o = 0; o < kPWaves; ++o)
-                if (o < units) v[q] += *reinterpret_cast<const float4v*>(reinterpret_cast<const float*>(sm.wave[o]) + (i / 16) * RT + (i & 15) * 4);
-        }
+        for (int o = 0; o < kPWaves; ++o)
+            if (o < units) v += *reinterpret_cast<const float4v*>(reinterpret_cast<const float*>(sm.wave[o]) + (w.tid / 16) * RT + (w.tid & 15) * 4);
     }
     if constexpr (PH == kPFfn2) {
         if (a.ranges > 1) {
             // the sums of this range, then, by whoever is the last to come, of all of them in their order
             float* part = a.part + ((size_t)(r * (H / 64) + tile) * a.ranges) * (TR * 64);
-#pragma unroll
-            for (int q = 0; q < Q; ++q) {
-                const int i = w.tid + q * kPThreads;
-                if (place[q] >= 0) {
-                    float* p = part + (size_t)range * (TR * 64) + i * 4;
-                    st_agent(p, v[q][0], v[q][1]);
-                    st_agent(p + 2, v[q][2], v[q][3]);
-                }
+            if (place >= 0) {
+                float* p = part + (size_t)range * (TR * 64) + w.tid * 4;
+                st_agent(p, v[0], v[1]);
+                st_agent(p + 2, v[2], v[3]);
             }
             asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
             __syncthreads();
@@ -369,37 +344,31 @@ __device__ __forceinline__ void project(const PromptArgs& a, const Spot& w, Prom
             __syncthreads();
             if (sm.word != next * (uint32_t)a.ranges - 1u) return;
             const AgentBuffer sums(part, (uint32_t)a.ranges * (TR * 64 * 4));
-#pragma unroll
-            for (int q = 0; q < Q; ++q) {
-                const int i = w.tid + q * kPThreads;
-                if (place[q] < 0) continue;
-                v[q] = float4v{0.f, 0.f, 0.f, 0.f};
-                for (int s = 0; s < a.ranges; ++s) v[q] += sums.load16<float4v>((uint32_t)(s * TR * 64 + i * 4) * 4u);
+            if (place >= 0) {
+                v = float4v{0.f, 0.f, 0.f, 0.f};
+                for (int s = 0; s < a.ranges; ++s) v += sums.load16<float4v>((uint32_t)(s * TR * 64 + w.tid * 4) * 4u);
             }
         }
     }
-#pragma unroll
-    for (int q = 0; q < Q; ++q) {
-        const int i = w.tid + q * kPThreads, n = n0 + (i & 15) * 4, t = t0 + i / 16;
-        if (place[q] < 0) continue;
+    if (place >= 0) {
         half4v out;
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-            float f = v[q][e] + (float)eb[q][e];
+            float f = v[e] + (float)eb[e];
             if (PH == kPFfn1) f = gelu_tanh(f);
-            if (RES) f += (float)er[q][e];
+            if (RES) f += (float)er[e];
             out[e] = (half_t)f;
         }
         if constexpr (PH == kPQkv) {
-            if (which == 0) st_agent(a.q + (size_t)t * H + n, out);
-            else st_agent((which == 1 ? L.k_cache : L.v_cache) + slot[q], out);
+            if (which == 0) st_agent(a.q + (size_t)et * H + ec, out);
+            else st_agent((which == 1 ? L.k_cache : L.v_cache) + slot, out);
         } else if constexpr (PH == kPOut) {
-            st_agent(a.y + (size_t)t * H + n, out);
+            st_agent(a.y + (size_t)et * H + ec, out);
         } else if constexpr (PH == kPFfn1) {
-            st_agent(a.f + (size_t)t * a.F + n, out);
+            st_agent(a.f + (size_t)et * a.F + ec, out);
         } else {
-            if (last) *reinterpret_cast<half4v*>(a.out + (size_t)place[q] * H + n) = out;
-            else st_agent(a.x + (size_t)place[q] * H + n, out);
+            if (last) *reinterpret_cast<half4v*>(a.out + (size_t)place * H + ec) = out;
+            else st_agent(a.x + (size_t)place * H + ec, out);
         }
     }
     if (PH == kPFfn2 && last) return;
@@ -409,10 +378,6 @@ __device__ __forceinline__ void project(const PromptArgs& a, const Spot& w, Prom
 }
 
 // ---- 128 query rows of a (sequence, head) pair: the arithmetic of attn_prefill16 (attention.hip), 16 rows per wave ----
-__device__ __forceinline__ half4v lds_read_transposed(const char* p) {
-    typedef short short4v __attribute__((ext_vector_type(4)));
-    return __builtin_bit_cast(half4v, __builtin_amdgcn_ds_read_tr16_b64_v4i16((short4v __attribute__((address_space(3)))*)p));
-}
 template <int D>
 __device__ __forceinline__ void attend(const PromptArgs& a, const Spot& w, PromptSmem& base, int b, int g, int block) {
     constexpr int BKV = 64, KK = D / 32, DB = D / 16, LDK = D + 8, LDV = D + 16, CH = D / 8, VEC = BKV * CH / kPThreads, TR = kPRows, BQ = 16 * kPWaves;
@@ -427,7 +392,8 @@ __device__ __forceinline__ void attend(const PromptArgs& a, const Spot& w, Promp
     const int lo = row0 / TR, hi = (row0 + (a.causal ? keys : len) - 1) / TR; // row tiles they and the queries lie in
     const uint32_t target = (uint32_t)(w.layer + 1) * (uint32_t)(3 * a.H / 64);
     await(a, w, base.late, w.layer == 0 ? nullptr : counter(a, hi, kCntX), (uint32_t)w.layer * (uint32_t)(a.H / 64), [&](int l) { return lo + l > hi || ld_count(counter(a, lo + l, kCntQkv)) >= target; });
-    __syncthreads();    const float c = base.late != 0 ? __builtin_nanf("") : rsqrtf((float)D) * kPLog2e;
+    __syncthreads();
+    const float c = base.late != 0 ? __builtin_nanf("") : rsqrtf((float)D) * kPLog2e;
     const AgentBuffer qb(a.q, (uint32_t)a.T * (uint32_t)(a.H * 2));
     const size_t head = ((size_t)b * a.heads + g) * a.max_seq * D;
     const AgentBuffer kb_(L.k_cache + head, (uint32_t)len * (D * 2)), vb_(L.v_cache + head, (uint32_t)len * (D * 2));
@@ -489,7 +455,7 @@ __device__ __forceinline__ void attend(const PromptArgs& a, const Spot& w, Promp
                     tmax = fmaxf(tmax, st[kb][e]);
                 }
             tmax = max_xor32(max_xor16(tmax));
-            constexpr float kSlack = 8.0f;                                    // the reference moves only where a maximum grew by more (attn_prefill)
+            constexpr float kSlack = 8.0f;                                    // the reference moves only where a maximum grew by more (attn_prefill), or is NaN: a wait given up
             const float tm = tmax * c;
             if (__any(!(tm <= m + kSlack))) {
                 const float m_new = fmaxf(m, tm), alpha = __builtin_amdgcn_exp2f(m - m_new);
@@ -514,7 +480,7 @@ __device__ __forceinline__ void attend(const PromptArgs& a, const Spot& w, Promp
 #pragma unroll
                 for (int db = 0; db < DB; ++db) {
                     const char* vp = reinterpret_cast<const char*>(&sm.v[buf][(p * 32 + G * 4 + (fr >> 2)) * LDV + db * 16 + (fr & 3) * 4]);
-                    const half4v x = lds_read_transposed(vp), y = lds_read_transposed(vp + 16 * LDV * 2);
+                    const half4v x = lds_read_tr16(vp), y = lds_read_tr16(vp + 16 * LDV * 2);
                     o[db] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_shufflevector(x, y, 0, 1, 2, 3, 4, 5, 6, 7), pf[p], o[db], 0, 0, 0);
                 }
         }
@@ -536,7 +502,8 @@ __device__ __forceinline__ void attend(const PromptArgs& a, const Spot& w, Promp
         }
     }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    __syncthreads();    // rows of each tile that the item covers
+    __syncthreads();
+    // rows of each tile that the item covers
     const int first = row0 + i0, past = first + rows, t = first / TR + w.tid;
     if (t * TR < past) {
         const int from = t * TR > first ? t * TR : first, to = (t + 1) * TR < past ? (t + 1) * TR : past;
