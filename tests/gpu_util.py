@@ -27,7 +27,7 @@ def gate(got, want, what="", max_abs=MAX_ABS, mean_abs=MEAN_ABS):
 
 
 def kernels_of(call):
-    """Names of what `call` launches (directly: replays of a graph do not show)."""
+    """Names of what `call` launches, directly or by replaying a graph, and of the runtime calls that do it."""
     from torch.profiler import ProfilerActivity, profile
     with profile(activities=[ProfilerActivity.CUDA]) as p:
         call()

@@ -223,8 +223,8 @@ def test_a_wait_given_up_is_not_taken_for_a_result(eet, how):
 
 def test_a_stack_counts_the_keys_its_sequences_hold(eet):
     """Weights and K/V rows of a step that moves more than the memory-side cache (256 MiB) holds are loaded as read once, and what a step moves
-    grows with the sequences: two layers of hidden 1024 (50 MB of weights) pass the line at 25000 keys.  The recorded step changes with
-    it: direct launches and replays give the same bits on both sides, back and forth."""
+    grows with the sequences: two layers of hidden 1024 (50 MB of weights) pass the line at 25000 keys.  A stack created with use_graph
+    launches such steps directly too and gives the same bits on both sides, back and forth (recorded steps: test_gpu_stack_recorded.py)."""
     layers, H, line = 2, 1024, (256 << 20) - 2 * 2 * 12 * 1024 * 1024
     keys = line // (layers * 4 * H)                            # visible keys of both sequences together, the new tokens' among them: the last that fit
     w = wl.Workload("held", 59, H, 16, 4 * H, layers, 2, 1, 1, 1, 4, keys // 2 + 8)

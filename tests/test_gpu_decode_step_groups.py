@@ -79,8 +79,10 @@ def test_other_numbers_of_sequences_in_between(layers):
     stack.close()
 
 
-def test_a_wait_given_up_in_one_group():
-    """The second group's wait for its exchange set comes to its bound: its sequences are NaN, the first group's are not, and the lengths come back with an error."""
+@pytest.mark.parametrize("how", ["said before", "a wait that ends by itself"])
+def test_a_wait_given_up_in_one_group(how):
+    """A step of two groups where the second has given up a wait before, or gives up now: its count of emptied parts starts far below what its items wait for,
+    so each of them runs into its own bound.  Its sequences are NaN, the first group's are not, and the lengths come back with an error."""
     eet, w, Ws, cfg = build(128, 2, 256, 20, 1, 6, 24)
     layer = eet.DecoderLayer(cfg, {k: torch.from_numpy(v) for k, v in Ws[0].items()})
     layer.prefill(dev(wl.prompt_embeddings(w)), [3] * 20)
@@ -89,7 +91,11 @@ def test_a_wait_given_up_in_one_group():
     now = words.cpu().numpy()
     at = [i for i in range(0, len(now) - 256, 16) if not now[i:i + 32].any() and np.all(now[i + 32:i + 256] == -1)]
     assert len(at) == 2
-    words[at[1]] = 1 << 31                                     # as a wait given up in an earlier step leaves it
+    if how == "said before":
+        words[at[1]] = 1 << 31
+    else:
+        words[at[1] + 16] = 0xfff00000
+    torch.cuda.synchronize()
     got = host(layer.decode_step(dev(wl.decode_embeddings(w, 0))))
     torch.cuda.synchronize()
     assert np.all(np.isfinite(got[:10])) and np.all(np.isnan(got[10:]))

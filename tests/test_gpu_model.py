@@ -341,7 +341,7 @@ def differs(what, a, b):
 
 def test_cfg2_model_at_full_size_is_embedding_then_stack_then_head(eet):
     """The benchmark's --model configuration (24 layers, batch 8, prompts of 256-512 tokens, vocabulary 50257, decode
-    steps replayed from the stack's graph): the model call is bit for bit the embedding operator, then the stack entry
+    steps of one launch): the model call is bit for bit the embedding operator, then the stack entry
     points on a second stack with the same weights, and its logits are the output projection of its own last-layer rows
     within tolerance, with the exact greedy choice -- each of those parts is compared with the oracle on its own
     (embedding: above; stack: layer by layer in test_gpu_layer.py; head: check_head)."""
@@ -390,8 +390,7 @@ def test_cfg2_model_at_full_size_is_embedding_then_stack_then_head(eet):
 
 
 def test_model_sized_for_more_sequences_serves_smaller_batches_one_after_another(eet):
-    """A model created for 6 sequences runs a batch of 4, generates, then a batch of 2 with other prompts, generates again
-    (the recorded decode graph is re-recorded for the new batch): every call against a fresh oracle model."""
+    """A model created for 6 sequences runs a batch of 4, generates, then a batch of 2 with other prompts, generates again: every call against a fresh oracle model."""
     w = replace(wl.WORKLOADS["small64"], batch=6, decode_steps=3)
     V = 333
     gpu, _, head = build(eet, w, V)

@@ -35,6 +35,12 @@ def on_device(W):
     (256, 4, 640, [1 + b % 6 for b in range(60)], True),  # many sequences to a tile
     (256, 4, 1024, [129, 128, 200], True),               # 457 rows
     (768, 12, 3072, [90, 60], False),                    # more items than are taken
+    (768, 12, 3072, [30, 60, 64, 23], False),
+    (512, 8, 2048, [100, 150, 80], False),
+    (1024, 8, 4096, [100], False),
+    (384, 6, 1536, [130, 190], True),                    # 1224 items
+    (384, 6, 1536, [130, 200], False),                   # 1284, 24 of them attention
+    (256, 4, 1024, [300, 220], False),                   # more rows than are taken
     (1024, 16, 4096, [16], False),                       # rows of the small-layer kernel
     (1024, 16, 4160, [20], False),                       # feed-forward part too wide
 ])
@@ -104,6 +110,27 @@ def test_stack_is_the_chain_of_its_layers():
         layer.close()
     assert torch.equal(got, h)
     stack.close()
+
+
+def test_weights_read_once():
+    """One row tile through a stack whose weights no cache keeps until the next call: they are loaded with the hint, and the bits are those of the single
+    layers, whose weights are kept."""
+    lens, layers = [6, 4], 15
+    eet, w, Ws, cfg = build(1024, 16, 2688, lens)
+    W = {k: v.to("cuda:0") for k, v in on_device(Ws[0]).items()}
+    stack, layer = eet.DecoderStack(cfg, [W] * layers), eet.DecoderLayer(cfg, W)
+    h = x = dev(wl.prompt_embeddings(w))
+    kinds = lambda names: [n.split("prompt_layers<")[1].split(">")[0] for n in names if "prompt_layers<" in n]     # noqa: E731
+    assert kinds(kernels_of(lambda: stack.prefill(x, lens))) == ["true"] and kinds(kernels_of(lambda: layer.prefill(x, lens))) == ["false"]
+    got = stack.prefill(x, lens)
+    for l in range(layers):
+        h = layer.prefill(h, lens)
+        torch.cuda.synchronize()
+        a, b = (kv.view(2, 2, 16, w.max_seq, 64) for kv in (stack.kv_cache.view(layers, -1)[l], layer.kv_cache))
+        assert all(torch.equal(a[:, s, :, :n], b[:, s, :, :n]) for s, n in enumerate(lens)), l
+    assert bool(torch.isfinite(got[0, :6]).all()) and torch.equal(got, h)
+    stack.close()
+    layer.close()
 
 
 def test_recorded_prefill():

@@ -8,8 +8,8 @@ context, output-projection result, normalised rows, feed-forward activations) an
 A difference is reported with the first differing piece, so it names the kernel that produced it.
 
 Cases reach the paths the small workloads do not: 256x256 tiles, 128x64 and 64x64 tiles with two K groups, decode steps in
-one launch and, launch by launch, with prefetch workgroups and merged key ranges, all replayed from the stack's graph, the
-256-row attention."""
+one launch and, launch by launch and replayed from the stack's graph, with prefetch workgroups and merged key ranges, the 256-row
+attention."""
 from dataclasses import replace
 
 import numpy as np
@@ -70,7 +70,7 @@ def run_stack(eet, w, LW, steps):
         outs.append(st.prefill(dev(wl.prompt_embeddings(w)), lens, stream=stream).clone())
         tok = torch.empty((w.batch, w.hidden), dtype=torch.float16, device="cuda:0")
         out = torch.empty_like(tok)
-        for k in range(steps):                      # fixed buffers: steps 1.. replay the graph recorded by step 0
+        for k in range(steps):                      # fixed buffers: steps 1.. replay the graph recorded by step 0, where a step is several launches
             tok.copy_(dev(wl.decode_embeddings(w, k)))
             st.decode_step(tok, out, stream=stream)
             outs.append(out.clone())
@@ -84,13 +84,13 @@ def run_stack(eet, w, LW, steps):
 H1536 = wl.Workload("h1536", 1007, 1536, 12, 3072, 1, 9, 384, 128, 384, 3, 512)
 
 
-@pytest.mark.parametrize("name,batch,layers", [("cfg2", 8, 24),      # 256x256 and 128x64 tiles, decode steps in one launch, graph
+@pytest.mark.parametrize("name,batch,layers", [("cfg2", 8, 24),      # 256x256 and 128x64 tiles, decode steps in one launch
                                                ("cfg2", 2, 4),       # 128x64 and 64x64 tiles with two K groups
                                                ("h1536", 9, 4)])
 def test_stack_runs_are_bitwise_reproducible_at_full_size(eet, name, batch, layers):
     w = replace(H1536 if name == "h1536" else wl.WORKLOADS[name], batch=batch, layers=layers)
     LW = [{k: torch.from_numpy(v) for k, v in wl.layer_weights(w, l).items()} for l in range(layers)]
-    print(f"reproducibility: {name} batch {batch}, {layers} layers, prefill + 3 graph-replayed decode steps, two handles", flush=True)
+    print(f"reproducibility: {name} batch {batch}, {layers} layers, prefill + 3 decode steps, two handles", flush=True)
     a, outs_a = run_stack(eet, w, LW, 3)
     b, outs_b = run_stack(eet, w, LW, 3)
     what = f"{name} batch {batch} x {layers} layers"

@@ -1,5 +1,5 @@
-"""The stack entry points (all layers per call, decode steps replayed from a HIP graph) against the
-per-layer entry points and against the CPU oracle."""
+"""The stack entry points (all layers per call) against the per-layer entry points and against the CPU oracle.  The layers here are narrow: a decode step is
+one launch, with use_graph or without (steps of several launches, replayed from a HIP graph: test_gpu_stack_recorded.py)."""
 import numpy as np
 import pytest
 import torch
@@ -98,9 +98,9 @@ def test_short_prompts_through_a_stack_equal_the_layer_chain(eet, hidden, heads,
 
 
 def test_graph_replay_matches_direct_launches(eet):
-    """Decode steps replayed from the recorded graph, with unrelated eager work and synchronisations
-    between the replays, give the same bits as direct launches, step after step; a new prefill with
-    another batch size re-records the graph."""
+    """The decode steps of a stack created with use_graph, with unrelated eager work and synchronisations between them, give the
+    same bits as those of one without, step after step, also after a new prefill with another batch size.  (These are one launch
+    each, so neither stack records them.)"""
     w = wl.WORKLOADS["small64"]
     cfg, Ws, direct = build(eet, w, 2, use_graph=False)
     _, _, graphed = build(eet, w, 2, use_graph=True)
