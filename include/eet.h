@@ -185,7 +185,7 @@ size_t eet_stack_workspace_bytes(const eet_layer_config *cfg, int32_t n_layers);
  * launches into a HIP graph the first time it sees a (tokens, out, kv_cache) triple and replays
  * it afterwards (the graph is instantiated inside that call, and once more when what the sequences hold
  * outgrows the memory-side cache; it is skipped on the null stream, while the caller is capturing the
- * stream itself, and where a step is one launch for all layers anyway).  Errors as eet_layer_create. */
+ * stream itself, and where a step is one launch per 32 layers anyway).  Errors as eet_layer_create. */
 int eet_stack_create(const eet_layer_config *cfg, int32_t n_layers, const eet_layer_weights *weights,
                      void *workspace, int32_t use_graph, eet_stack_t **out_stack);
 

@@ -579,7 +579,8 @@ __global__ __launch_bounds__(256) void prompt_setup(SeqLens lens, int batch, int
 // launch / one launch, rows (items), stacks of 4: hidden 256 x 1024, 40 rows 115 / 70, 240 (564) 125 / 81, 480 (1128) 125 / 96; 384 x 1536, 240 (936) 136 / 106, 480
 // (1872) 142 / 148; 512 x 2048, 40 121 / 93, 240 (1248) 149 / 120, 400 (2080) 157 / 168; 768 x 3072, 40 129 / 112, 120 (1092) 161 / 133, 200 (1740) 171 / 168; 1024 x 4096, 40
 // 144 / 131, 80 (992) 171 / 148, 120 (1584) 174 / 165, 200 (2528) 184 / 242; 24 of it, 37 rows 917 / 744.  One layer: 256, 40 rows 36 / 21, 480 35 / 30; 512, 240
-// 38.3 / 37.7; 768, 120 42.6 / 41.3, 240 (2052) 44 / 55; 1024, 40 39.8 / 40.3, 80 46.3 / 44.0.  Up to 16 rows are taken by the small-layer kernel
+// 38.3 / 37.7; 768, 120 42.6 / 41.3, 240 (2052) 44 / 55; 1024, 40 39.8 / 40.3, 80 46.3 / 44.0 (33 to 64 rows: the launches are up to 3 % ahead in passes behind
+// one another, 10 % behind where each pass is waited for; taken all the same, so that a stack has the bits of its layers one by one).  Up to 16 rows are taken by the small-layer kernel
 // elsewhere, which is ahead from 1024 x 4096 on (10 rows, 4 layers 104 / 113; 1024 x 2688 118 / 109); feed-forward parts of more than 4096 columns
 // (1024 x 8192, 80 rows 184 / 195) are not worth their ranges.  (Row tiles of 32 and 64: 24 x 1024, 37 rows 892 and 1098; 512, 250 rows 32.5, 34.9 and 42.6 per layer.)
 constexpr int kPromptStepItems = 1280;
