@@ -809,15 +809,24 @@ static void step_groups(int rows, int hidden, int ffn, int& groups, int& group_r
 // pairs over 512 slots and more keep the attention kernel of their own, whose bits are the operator's (24 x 16 heads, 800 to 1600 keys 55.0 / 41.7, so
 // not for speed); up to 256 pairs gain there too (24 x 4 heads 33.8 / 18.1).  The wider layers' groups of 8 rows read the weights once more each: level from
 // 16 sequences of 1792 on (43.3 / 45.6), and below that their steps of 9 to 16 stay with the small-layer kernel and its LayerNorms.
-constexpr int kStepGroupItems = 1350;
-bool decode_step_fits(int rows, int hidden, int heads, int ffn, int max_seq) {
+// A layer on its own has no next layer to begin with while the last items end, and its launches find their weights in the caches: it stops earlier, and the
+// sooner the more attention items stand before the rest of a wide layer.  us per step of one layer, launch by launch / one launch, 20 to 40, 100 to 200, 250 to 450
+// keys: 1024 with 16 heads, 30 sequences 26.7 / 29.9, 30.5 / 31.0, 33.2 / 32.8; 40 30.3 / 32.4, 33.8 / 33.8, 39.0 / 37.3; 44 30.4 / 38.1, 34.6 / 39.8, 40.4 / 43.9; with
+// 8 heads, 48 30.9 / 29.1, 35.3 / 31.3, 42.5 / 36.5; 768 with 12, 48 29.6 / 27.2, 30.4 / 28.9, 33.3 / 31.7; 56 29.4 / 30.4, 30.4 / 32.2, 35.0 / 35.1; 64 30.3 / 32.8, 31.5 /
+// 34.8, 37.6 / 38.3; 512 with 8, 80 29.8 / 26.0, 29.8 / 27.4, 32.0 / 30.7; 96 29.9 / 29.5, 30.1 / 31.6, 34.5 / 35.5.  Stacks do not lose
+// at any of these, of 6 layers, short keys: 48 of 1024 1645 / 1604 in 8 steps, 40 1604 / 1568, 64 of 768 1477 / 1479, 96 of 512 1344 / 1317; of 2, 200 to 450 keys, 40 of 1024
+// 709 / 600.  (So here, and only here, a layer's bits are not those of the same layer in a stack.)
+constexpr int kStepGroupItems = 1350, kStepGroupItemsAlone = 1280, kStepPairsAlone = 460 << 10;    // the last: pairs times hidden
+bool decode_step_fits(int rows, int hidden, int heads, int ffn, int max_seq, int layers) {
     const int d = hidden / heads;
     if (rows < 1 || rows > kStepGroups * step_group_rows(hidden, ffn) || (d != 64 && d != 128) || hidden % 64 != 0 || ffn % 64 != 0 ||
         hidden > 64 * kSWaves * kSUnitsH || ffn > 64 * kSWaves * kSUnitsF) return false;
     int groups, group_rows;
     step_groups(rows, hidden, ffn, groups, group_rows);
-    return groups == 1 || (step_is_narrow(hidden, ffn) && groups * (hidden / 16 + ffn / 64 + hidden / 16 + group_rows * heads) <= kStepGroupItems &&
-                           (rows * heads <= 256 || max_seq < 512));
+    if (groups == 1) return true;
+    const int items = groups * (hidden / 16 + ffn / 64 + hidden / 16 + group_rows * heads);
+    return step_is_narrow(hidden, ffn) && items <= kStepGroupItems && (rows * heads <= 256 || max_seq < 512) &&
+           (layers > 1 || (items <= kStepGroupItemsAlone && rows * heads * hidden <= kStepPairsAlone));
 }
 
 // Long sequences: a CU streams the K/V rows of one item at a time, and next to that the launches that are saved count for little.  Where
@@ -859,7 +868,7 @@ static uint32_t step_layout(StepArgs& a) {
 int decode_step_groups(int max_rows, int hidden, int heads, int ffn, int max_seq) {
     const int limit = kStepGroups * step_group_rows(hidden, ffn);
     for (int rows = max_rows < limit ? max_rows : limit; rows >= 1; --rows) {   // more rows, more groups
-        if (!decode_step_fits(rows, hidden, heads, ffn, max_seq)) continue;
+        if (!decode_step_fits(rows, hidden, heads, ffn, max_seq, 2)) continue;                 // (a stack's: a layer on its own has no more)
         int groups, group_rows;
         step_groups(rows, hidden, ffn, groups, group_rows);
         return groups;
@@ -869,7 +878,7 @@ int decode_step_groups(int max_rows, int hidden, int heads, int ffn, int max_seq
 
 uint32_t decode_step_set_words(int max_rows, int hidden, int heads, int ffn, int max_seq) {
     uint32_t most = 0;
-    for (int rows = 1; rows <= max_rows && rows <= step_group_rows(hidden, ffn) && decode_step_fits(rows, hidden, heads, ffn, max_seq); ++rows) {
+    for (int rows = 1; rows <= max_rows && rows <= step_group_rows(hidden, ffn) && decode_step_fits(rows, hidden, heads, ffn, max_seq, 2); ++rows) {
         StepArgs a{};
         a.M = rows; a.H = hidden; a.heads = heads; a.F = ffn; a.max_seq = max_seq;
         const uint32_t words = step_layout(a);

@@ -97,10 +97,10 @@ WorkspaceLayout layout_of(const eet_layer_config* c) {
     w.buf_b = off;   off = align_up(off + 2 * T * H, 256);
     w.buf_y = off;   off = align_up(off + 2 * T * H, 256);
     w.part = off;
-    // sized for the split count of any batch <= max_batch (fewer sequences -> more splits) that does not run as one launch
+    // sized for the split count of any batch <= max_batch (fewer sequences -> more splits) that does not run as one launch, in a layer on its own or in a stack
     size_t part = 0;
     for (int b = 1; b <= c->max_batch; ++b) {
-        if (decode_step_fits(b, c->hidden, c->heads, c->ffn, c->max_seq) && decode_step_fits_keys(b, c->heads, (int)H / c->heads, (size_t)b * c->max_seq)) continue;
+        if (decode_step_fits(b, c->hidden, c->heads, c->ffn, c->max_seq, 1) && decode_step_fits_keys(b, c->heads, (int)H / c->heads, (size_t)b * c->max_seq)) continue;
         const int splits = attention_decode_splits(b, c->heads, c->max_seq);
         const size_t p = attention_decode_scratch_bytes(b, c->heads, H / c->heads, splits);
         part = p > part ? p : part;
@@ -447,12 +447,14 @@ int eet_layer_encode(eet_layer_t* L, const int32_t* q_lens, int32_t batch, int32
 // that it moves, every layer's weights and visible K/V, stays in the memory-side cache until the next step; kExceedsCache: more than
 // that; kLongKeys: more, and launch by launch where shorter sequences would run as one launch (kernels.hpp: decode_step_fits_keys).
 enum StepRegime { kInCache, kExceedsCache, kLongKeys, kStepRegimes };
+static int layers_of(const eet_layer* L) { return L->stack_layers > 0 ? L->stack_layers : 1; }
+static bool step_fits(const eet_layer* L) { return decode_step_fits(L->batch, L->cfg.hidden, L->cfg.heads, L->cfg.ffn, L->cfg.max_seq, layers_of(L)); }
 static StepRegime step_regime(const eet_layer* L, const int32_t* cached) {
     const size_t H = L->cfg.hidden, F = L->cfg.ffn;
     size_t visible = 0;
     for (int b = 0; b < L->batch; ++b) visible += (size_t)cached[b] + 1;
-    if (decode_step_fits(L->batch, L->cfg.hidden, L->cfg.heads, L->cfg.ffn, L->cfg.max_seq) && !decode_step_fits_keys(L->batch, L->cfg.heads, L->d, visible)) return kLongKeys;
-    return (size_t)(L->stack_layers > 0 ? L->stack_layers : 1) * (2 * (4 * H * H + 2 * H * F) + 4 * H * visible) > kMemorySideCacheBytes ? kExceedsCache : kInCache;
+    if (step_fits(L) && !decode_step_fits_keys(L->batch, L->cfg.heads, L->d, visible)) return kLongKeys;
+    return (size_t)layers_of(L) * (2 * (4 * H * H + 2 * H * F) + 4 * H * visible) > kMemorySideCacheBytes ? kExceedsCache : kInCache;
 }
 
 // Enqueue the kernels of one layer's decode step (arguments already validated).  `bump`: this
@@ -610,7 +612,7 @@ static int enqueue_decode(eet_layer* L, const void* tokens, void* out, void* kv_
 }
 
 static bool decodes_in_one_launch(const eet_layer* L, StepRegime regime) {
-    return regime != kLongKeys && decode_step_fits(L->batch, L->cfg.hidden, L->cfg.heads, L->cfg.ffn, L->cfg.max_seq);
+    return regime != kLongKeys && step_fits(L);
 }
 
 // A decode step through `n` layers of one configuration that share a workspace, as one launch per kStepLayers of them.  The last

@@ -236,8 +236,8 @@ struct StepArgs {
     int d, splits, groups, rows, n_qkv, n_att, n_out, n_ffn1, per_layer, items;     // rows: of a group; items: of a group
     StepLayer layer[kStepLayers];
 };
-// Rows and widths the kernel takes.
-bool decode_step_fits(int rows, int hidden, int heads, int ffn, int max_seq);
+// Rows and widths the kernel takes, of a stack of so many layers (1: a layer on its own).
+bool decode_step_fits(int rows, int hidden, int heads, int ffn, int max_seq, int layers);
 // ... and whether it is the faster way with `visible` keys in all (decode_step.hip has the figures).
 bool decode_step_fits_keys(int rows, int heads, int d, size_t visible);
 // Words of an exchange set that holds a step of any number of rows up to max_rows that the kernel takes (0: it takes none).  A set has

@@ -47,6 +47,39 @@ def test_steps_against_the_oracle(hidden, heads, ffn, batch, S, cap):
     layer.close()
 
 
+@pytest.mark.parametrize("hidden,heads,ffn,batch,alone", [
+    (1024, 16, 4096, 28, True), (1024, 16, 4096, 29, False),    # pairs times hidden: 448 and 464 K
+    (1024, 16, 4096, 40, False),
+    (768, 12, 3072, 48, True),
+    (512, 4, 2048, 128, True), (512, 8, 2048, 88, False),       # 1280 and 1296 items
+])
+def test_a_layer_on_its_own_stops_earlier(hidden, heads, ffn, batch, alone):
+    """Steps in one launch of a layer, up to where its launches are ahead, and of two layers, beyond it: which kernels run, and the oracle."""
+    S, cap = 6, 24
+    eet, w, Ws, cfg = build(hidden, heads, ffn, batch, 2, S, cap)
+    tw = [{k: torch.from_numpy(v) for k, v in W.items()} for W in Ws]
+    layer, stack = eet.DecoderLayer(cfg, tw[0]), eet.DecoderStack(cfg, tw, use_graph=False)
+    oracles = [orc.DecoderLayerOracle(W, heads, batch, cap, w.ln_eps) for W in Ws]
+    lens, x = [1 + b * 5 % S for b in range(batch)], wl.prompt_embeddings(w)
+    layer.prefill(dev(x), lens)
+    stack.prefill(dev(x), lens)
+    oracles[1].prefill(oracles[0].prefill(x, lens).astype(np.float16), lens)
+    for k in range(2):
+        xs = wl.decode_embeddings(w, k)
+        got, both = layer.decode_step(dev(xs)), stack.decode_step(dev(xs))
+        torch.cuda.synchronize()
+        want = oracles[0].decode_step(xs)
+        gate(host(got), want, f"layer, step {k}")
+        gate(host(both), oracles[1].decode_step(want.astype(np.float16)), f"stack, step {k}", 5e-2, 5e-3)
+    assert layer.cache_lens(batch) == stack.cache_lens(batch) == oracles[0].lens[:batch].tolist()
+    tok = dev(wl.decode_embeddings(w, 0))
+    for st, one in ((layer, alone), (stack, True)):
+        names = kernels_of(lambda: st.decode_step(tok))
+        assert (any("decode_layers" in n for n in names), any("attn_decode" in n for n in names)) == (one, not one), names
+    layer.close()
+    stack.close()
+
+
 @pytest.mark.parametrize("layers", [2, 35])
 def test_other_numbers_of_sequences_in_between(layers):
     """Prompts of 40, 5, 21 and 40 sequences on one handle, steps after each, a recorded step of 40 replayed in between: every sequence as on a handle of
